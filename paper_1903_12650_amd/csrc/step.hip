@@ -272,18 +272,23 @@ void destroy_streams(rn50_plan* p) {
   p->side = p->branch = nullptr;
   p->streams_ready = false;
 }
+// These events only order kernels on this GPU's streams (every kernel's own end already makes its stores visible across
+// the device), so a record carries no system-scope fence: with one, each of the step's ~25 records held its stream up
+// while the caches were written back for the host.  Whole step, batch 40: 4.756 -> 4.688 ms; batch 4: 2.289 -> 2.214 ms.
+// Host visibility comes from the caller's own synchronization of its stream, which joins both side streams.
+constexpr unsigned kEventFlags = hipEventDisableTiming | hipEventDisableSystemFence;
 int ensure_side_stream(rn50_plan* p) {
   if (p->streams_ready) return RN50_OK;
   auto ok = [](hipError_t e) { return e == hipSuccess; };
   bool good = ok(hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking)) &&
               ok(hipStreamCreateWithFlags(&p->branch, hipStreamNonBlocking)) &&
-              ok(hipEventCreateWithFlags(&p->ev_bfork, hipEventDisableTiming)) &&
-              ok(hipEventCreateWithFlags(&p->ev_bjoin, hipEventDisableTiming)) &&
-              ok(hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming)) &&
-              ok(hipEventCreateWithFlags(&p->ev_wt, hipEventDisableTiming));
+              ok(hipEventCreateWithFlags(&p->ev_bfork, kEventFlags)) &&
+              ok(hipEventCreateWithFlags(&p->ev_bjoin, kEventFlags)) &&
+              ok(hipEventCreateWithFlags(&p->ev_fork, kEventFlags)) &&
+              ok(hipEventCreateWithFlags(&p->ev_wt, kEventFlags));
   for (size_t i = 0; good && i < p->blocks.size() + 1; ++i) {  // the blocks and the stem
     hipEvent_t a = nullptr, b = nullptr;
-    good = ok(hipEventCreateWithFlags(&a, hipEventDisableTiming)) && ok(hipEventCreateWithFlags(&b, hipEventDisableTiming));
+    good = ok(hipEventCreateWithFlags(&a, kEventFlags)) && ok(hipEventCreateWithFlags(&b, kEventFlags));
     if (a) p->ev_dy.push_back(a);
     if (b) p->ev_wg.push_back(b);
   }
