@@ -89,7 +89,8 @@ size_t conv_wgrad_workspace_bytes(const rn50_conv_desc* d);
 int conv_fwd(const rn50_conv_desc* d, const void* x, const void* w, void* y, void* workspace,
              size_t workspace_bytes, void* stream);
 /* Data gradient: dx[n,h,w,c] = sum over (k,r,s) with h = p*stride-pad+r,
- * w = q*stride-pad+s of dy[n,p,q,k] * w[k,r,s,c].  dy [N,Ho,Wo,Cout], dx [N,H,W,Cin]. */
+ * w = q*stride-pad+s of dy[n,p,q,k] * w[k,r,s,c].  dy [N,Ho,Wo,Cout], dx [N,H,W,Cin].
+ * (The workspace is required for the interface's sake; the weights are read where they lie.) */
 int conv_dgrad(const rn50_conv_desc* d, const void* dy, const void* w, void* dx, void* workspace,
                size_t workspace_bytes, void* stream);
 /* Weight gradient: dw[k,r,s,c] = sum_{n,p,q} dy[n,p,q,k] * x[n,p*stride-pad+r,q*stride-pad+s,c].
@@ -350,7 +351,7 @@ size_t resnet_plan_workspace_bytes(const rn50_plan* plan);
  * runtime (RN50_ERR_HIP) can end a step early, with the kernels enqueued so far left to run.
  * Stream semantics: everything is ordered after the work `stream` holds at the call and
  * is complete when the work this call enqueues on `stream` is.  Inside, independent parts
- * (weight gradients, the projection shortcuts, the weight transposition) run on two
+ * (weight gradients, the projection shortcuts) run on two
  * streams the plan creates at its first step (default priority; host-side handles, no
  * device memory) and are forked from / joined into `stream` with events; the fork/join
  * can be captured into a graph together with `stream`.  One step at a time per plan. */

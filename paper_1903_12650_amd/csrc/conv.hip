@@ -7,9 +7,10 @@
 // where row m is an output pixel, A is gathered on the fly from the NHWC
 // activation tensor (k = tap*Cg + channel, 128 contiguous bytes per tap and row,
 // zero outside the image), and B is the weight matrix with K contiguous
-// (the KRSC weights as they are for the forward pass; for the data gradient a
-// [Cin][R][S][Cout] transposition written by a small kernel first).
-// 256 threads = 4 waves; global -> registers -> LDS double buffering (one
+// (the KRSC weights as they are; in the data gradient K runs over the output channels, the
+// weights' slow index, so its B tiles are [K][columns] and its fragments transposing LDS reads,
+// as in the weight gradient: no transposed copy of the weights is made).
+// 256 threads = 4 waves; both operands go straight into LDS (one
 // barrier per 128-byte K chunk); each wave owns 32x32 MFMA tiles fed by 16-byte
 // LDS reads; the MFMA is issued with the weight fragment as its first operand
 // so that every lane ends up with 4 consecutive output channels of one pixel,
@@ -109,6 +110,12 @@ struct IgemmArgs {
   // channel the two doubles (sum y, sum y^2), the tile's shifted float sums moved to shift 0 here; data gradient:
   // partial[plane][tile row][Ncols] in float.
   int partial_rm;
+  // Forward with an inference-mode batch norm in the output stage (MODE 2): the output is
+  // [relu](product * scale + bias [+ addend]), scale = bn_gamma / sqrt(aff_var + aff_eps), bias = bn_beta - bn_mean * scale,
+  // from the float accumulators and rounded once; addend [M][Ncols] (or null) is the residual.
+  const float* aff_var;
+  float aff_eps;
+  int aff_relu;
 };
 
 // relu(bn(x)) of one 16-byte vector with the arithmetic of the stand-alone BN pass (bn_affine, one rounding to
@@ -192,12 +199,66 @@ __device__ __forceinline__ void ring_wait(int chunks_after) {
   else wait_loads_then_barrier<0>();
 }
 
+// LDS tiles of the weight gradient are [k row][column] with rows of RBY = 16 * (columns per 16 bytes ...) bytes,
+// filled by LDS-destination loads (RBY/16 lanes per row).  The 16-byte slots of a row are stored permuted,
+// slot s of row r at s ^ wgrad_swz(r), so that the fragment reads below touch every bank once:
+//   bf16, 128-byte rows: a transposing read's 32 lanes take 64 bytes of 4 consecutive rows -- rows two apart
+//                        share their banks, so they swap halves;
+//   bf16, 256-byte rows: the same 4 rows all start at bank 0 -- each is rotated by a different 64 bytes;
+//   float:               lanes 32-63 read the row 4 below lanes 0-31 -- it is shifted by 128 bytes.
+template <typename T, int RBY>
+__device__ __forceinline__ int wgrad_swz(int row) {
+  if (sizeof(T) == 4) return ((row >> 2) & 1) << 3;
+  return RBY == 128 ? ((row >> 1) & 1) << 2 : (row & 3) << 2;
+}
+// Byte offset, inside a tile, of this lane's first read for the MFMA operand "32 columns from col0 x one k step"
+// at k step 0; step kk is KSTEP * kk rows further down.
+template <typename T, int RBY>
+__device__ __forceinline__ int wgrad_frag_base(int lane, int col0) {
+  if (sizeof(T) == 2) {
+    // ds_read_b64_tr_b16: within 16 lanes, lane t supplies the address of row t/4, columns 4*(t%4)..+3 and
+    // receives column t of rows 0..3.  Two reads (rows +0 and +4) give 8 k values of column lane%32.
+    const int g = lane >> 4, t = lane & 15;
+    const int krow = 8 * (g >> 1) + (t >> 2);
+    const int cb = 2 * (col0 + 16 * (g & 1) + 4 * (t & 3));
+    return krow * RBY + (((cb >> 4) ^ wgrad_swz<T, RBY>(krow)) << 4) + (cb & 15);
+  }
+  const int krow = (lane >> 5) * 4;  // + j, j = 0..3: the permutation only looks at bit 2
+  const int cb = 4 * (col0 + (lane & 31));
+  return krow * RBY + (((cb >> 4) ^ wgrad_swz<T, RBY>(krow)) << 4) + (cb & 15);
+}
+template <typename T, int RBY>
+__device__ __forceinline__ Vec16 wgrad_read_frag(const unsigned char* tile, int base, int kk) {
+  Vec16 v;
+  if constexpr (sizeof(T) == 2) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
+    const unsigned char* p0 = tile + base + kk * 16 * RBY;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0 + 4 * RBY));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v.h[j] = static_cast<uint16_t>(lo[j]);
+      v.h[4 + j] = static_cast<uint16_t>(hi[j]);
+    }
+  } else {
+    const unsigned char* p = tile + base + kk * 8 * RBY;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v.f[j] = *reinterpret_cast<const float*>(p + j * RBY);
+  }
+  return v;
+}
+
+
 // MODE 0: forward gather  ih = p*stride - pad + r.
 // MODE 1: data-gradient gather  ih = (p + pad - r)/stride when divisible (stride 1 or 2).  With stride 2
 // an output pixel only receives the taps r = (p + pad) mod 2, s = (q + pad) mod 2 (mod 2), so the pixels
 // are processed in four parity classes (p mod 2, q mod 2): a row tile holds pixels of one class and loops
 // over that class's taps only (a quarter of the taps on average, none for three classes of a 1x1 filter,
 // whose tiles just store zeros).
+// MODE 2: the forward gather with an inference-mode batch norm (+ residual, + ReLU) applied to the accumulators: an
+// evaluation pass needs no statistics of the tensor it produces, so the separate pass that read y and wrote z (two
+// thirds of the bytes of a 1x1 layer with its neighbours in HBM, and a third of the pass's time at batch 256) is gone.
 // LIN: compiled for a 1x1 filter with stride 1 and no padding (output row m is pixel m of the gathered
 // tensor): no pixel decode, no tap cursor, no bounds checks -- these layers have the shortest reductions
 // of the network, and a workgroup's instruction count outside the main loop is what bounds them.
@@ -220,6 +281,13 @@ constexpr int igemm_ring() {
   return (NW == 4 && 3 * (BM + BN) * 128 > 80 * 1024) ? 2 : 3;
 }
 //
+// Data gradient (MODE 1): the B tile of a chunk is BK output channels (K) x BN input channels of the weights as they lie
+// in memory, filled and read like wgrad_kernel's tiles (transposing reads in bf16).  A transposing read delivers fewer
+// bytes per clock than a plain one, but the tile is the smaller half of the fragment traffic and was never what bounds
+// these layers: per layer at batch 40 7.5 to 33 us against 8.9 to 34 with a transposed copy (whole network 794 against
+// 854 us, 3884 against 3926 at batch 256), and the copy itself -- 4 to 5 us per conv_dgrad call, 57 us per step on the
+// side stream -- is gone (the 22 shapes at batch 40, call by call: 578 -> 475 us).
+//
 // HALO: compiled for a 3x3 filter with stride 1 and padding 1 (output pixel m reads input pixels m + dy*W + dx,
 // dy, dx in -1..1, of the same flat pixel index space).  The nine taps of a tile then read one contiguous run of
 // BM + 2W + 2 input pixels: that run is brought into LDS once per 128-byte channel chunk (instead of a gathered
@@ -232,6 +300,7 @@ template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN = false
 __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) {
   static_assert(!BNIN || (LIN && MODE == 0), "the input-side BN is compiled for the linear forward kernel only");
   static_assert(!HALO || (!LIN && !BNIN), "the halo main loop is a kernel of its own");
+  constexpr bool DG = MODE == 1, FWD = !DG, AFF = MODE == 2;
   constexpr int NW = WM * WN, NT = 64 * NW;
   constexpr int V = 16 / sizeof(T);
   constexpr int BK = 128 / sizeof(T);
@@ -258,16 +327,17 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
   const rsrc_words rsA = make_rsrc_words(a.act, a.act_bytes), rsB = make_rsrc_words(a.wgt, a.wgt_bytes);
 
   // Rows of this tile: pixels m0.. of the whole output grid, or of one parity class of it.
-  const bool classes = !LIN && MODE == 1 && a.stride == 2;
+  const bool classes = !LIN && DG && a.stride == 2;
   __shared__ int pix_s[BM];  // classes only: output pixel index of every tile row
   // Data gradient with batch-norm sums: the per-channel coefficients of this tile's columns, fetched by one
   // thread per column while the main loop runs (every thread loading its own copies costs the texture path
   // as much as two chunks of the main loop).
-  __shared__ float prm_s[MODE == 1 ? 4 * BN : 4];
+  // (MODE 2: the same for the inference-mode affine step.)
+  __shared__ __align__(16) float prm_s[DG ? 4 * BN : (AFF ? 2 * BN : 4)];
   float pg = 0.f, pb = 0.f, pm = 0.f, pr = 0.f;
-  if (MODE == 1 && a.partial != nullptr && tid < BN) {
+  if ((AFF || (DG && a.partial != nullptr)) && tid < BN) {
     const int c = min(n0 + tid, a.Ncols - 1);
-    pg = a.bn_gamma[c]; pb = a.bn_beta[c]; pm = a.bn_mean[c]; pr = a.bn_rstd[c];
+    pg = a.bn_gamma[c]; pb = a.bn_beta[c]; pm = a.bn_mean[c]; pr = AFF ? a.aff_var[c] : a.bn_rstd[c];
   }
   int ph = 0, pw = 0, Hc = a.P, Wc = a.Q, Mc = a.M, m0 = mt * BM;
   int r0 = 0, s0 = 0, tstep = 1;
@@ -309,21 +379,39 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
     }
     a_base[i] = n * a.H * a.W;
     // a row beyond the last gets coordinates that fail every bounds check below
-    a_h0[i] = ok ? (MODE == 0 ? p * a.stride - a.pad : p + a.pad) : -(1 << 20);
-    a_w0[i] = MODE == 0 ? q * a.stride - a.pad : q + a.pad;
+    a_h0[i] = ok ? (FWD ? p * a.stride - a.pad : p + a.pad) : -(1 << 20);
+    a_w0[i] = FWD ? q * a.stride - a.pad : q + a.pad;
   }
+  // The B tile: BN rows (output columns) of one 128-byte chunk of K each, or (data gradient) BK rows (K) of BN columns.
+  constexpr int BRB = BN * static_cast<int>(sizeof(T)), LB = BRB / 16;  // data gradient: bytes and 16-byte pieces per tile row
+  const int b_krow = DG ? tid / LB : 0;                                 // ... this thread's tile row in load pass 0
+  const int k_pitch = a.R * a.S * a.Ncols;                              // ... elements from one K row of the weights to the next
   uint32_t b_row[RB];
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
-    const int n = n0 + lrow + RPL * i;
-    b_row[i] = n < a.Ncols ? static_cast<uint32_t>(n * a.Ktot + piece * V) * sizeof(T) : kOob;
+    if constexpr (DG) {
+      const int col = n0 + ((tid % LB) ^ wgrad_swz<T, BRB>(b_krow)) * V;
+      b_row[i] = col < a.Ncols ? static_cast<uint32_t>((b_krow + (NT / LB) * i) * k_pitch + col) * sizeof(T) : kOob;
+    } else {
+      const int n = n0 + lrow + RPL * i;
+      b_row[i] = n < a.Ncols ? static_cast<uint32_t>(n * a.Ktot + piece * V) * sizeof(T) : kOob;
+    }
   }
+  // byte offset of (tap, chunk cc) in the weights, and whether load pass i brings anything (cval: the forward pass's answer)
+  auto b_at = [&](int tap, int cc) __attribute__((always_inline)) {
+    return DG ? static_cast<uint32_t>(cc * BK * k_pitch + tap * a.Ncols) * static_cast<uint32_t>(sizeof(T))
+              : static_cast<uint32_t>(tap * a.Cg) * static_cast<uint32_t>(sizeof(T)) + static_cast<uint32_t>(cc) * 128u;
+  };
+  auto b_live = [&](int i, int cc, bool cval) __attribute__((always_inline)) {
+    return DG ? (a.Cg % BK == 0 || cc * BK + b_krow + (NT / LB) * i < a.Cg) : cval;
+  };
 
   // Load cursor: tap (r,s), chunk cc within the tap.  Per tap, the byte offset of every row's pixel (or
   // kOob); within a tap successive chunks only differ by a scalar offset.
   const int nchunks = nr * ns * a.cpt;
   int cur_r = r0, cur_s = s0, cur_cc = 0, cur = 0;
-  uint32_t a_off[RA], b_tap = static_cast<uint32_t>((r0 * a.S + s0) * a.Cg) * sizeof(T);
+  uint32_t a_off[RA];
+  int b_tap = r0 * a.S + s0;
   const bool ragged = (a.Cg % BK) != 0;
   auto tap_setup = [&]() __attribute__((always_inline)) {
     if constexpr (LIN) {
@@ -336,7 +424,7 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
     for (int i = 0; i < RA; ++i) {
       int ih, iw;
       bool ok = true;
-      if (MODE == 0) {
+      if (FWD) {
         ih = a_h0[i] + (a.pair ? 2 * cur_r + (piece >> 2) : cur_r);
         iw = a_w0[i] + cur_s;
       } else {
@@ -348,7 +436,7 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
       }
       ok = ok && static_cast<unsigned>(ih) < static_cast<unsigned>(a.H) &&
            static_cast<unsigned>(iw) < static_cast<unsigned>(a.W);
-      const int pc = (MODE == 0 && a.pair) ? (piece & 3) : piece;
+      const int pc = (FWD && a.pair) ? (piece & 3) : piece;
       a_off[i] = ok ? static_cast<uint32_t>((a_base[i] + ih * a.W + iw) * a.PS + pc * V) * sizeof(T) : kOob;
     }
   };
@@ -362,11 +450,11 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
     ++cur;
     const uint32_t sa = wave_dst + static_cast<uint32_t>(stage) * STAGE;
     const uint32_t sb = sa + BM * 128;
-    const uint32_t sob = __builtin_amdgcn_readfirstlane(b_tap + so);
+    const uint32_t sob = __builtin_amdgcn_readfirstlane(b_at(b_tap, cur_cc));
 #pragma unroll
     for (int i = 0; i < RA; ++i) buffer_load16_to_lds(rsA, sa + i * (RPL * 128), cval ? a_off[i] : kOob, so);
 #pragma unroll
-    for (int i = 0; i < RB; ++i) buffer_load16_to_lds(rsB, sb + i * (RPL * 128), cval ? b_row[i] : kOob, sob);
+    for (int i = 0; i < RB; ++i) buffer_load16_to_lds(rsB, sb + i * (RPL * 128), b_live(i, cur_cc, cval) ? b_row[i] : kOob, sob);
     // advance the cursor
     if constexpr (LIN) {
       ++cur_cc;
@@ -377,7 +465,7 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
         cur_s = s0;
         cur_r += tstep;
       }
-      b_tap = static_cast<uint32_t>((cur_r * a.S + cur_s) * a.Cg) * sizeof(T);
+      b_tap = cur_r * a.S + cur_s;
       if (cur < nchunks) tap_setup();  // (nothing is loaded past the last chunk)
     }
   };
@@ -399,16 +487,22 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
   // The fragment reads run ahead of the MFMAs that use them -- a whole chunk ahead for the small wave tiles
   // (one MFMA per k step is far shorter than an LDS read's latency), one k step ahead for 64x64 wave tiles --
   // so a wave pays the LDS latency once per chunk, not once per k step.
+  int bt_base[TN];  // data gradient: the transposing reads of the [K][columns] tile
+#pragma unroll
+  for (int j = 0; j < TN; ++j) bt_base[j] = DG ? wgrad_frag_base<T, BRB>(lane, wn * (BN / WN) + j * 32) : 0;
   constexpr int AHEAD = (TM + TN <= 3) ? 4 : 1;  // k steps whose fragments are in registers before the first MFMA
   auto compute = [&](int stage) __attribute__((always_inline)) {
     const unsigned char* sa = smem + stage * STAGE + wm * (BM / WM) * 128;
-    const unsigned char* sb = smem + stage * STAGE + BM * 128 + wn * (BN / WN) * 128;
+    const unsigned char* sb = smem + stage * STAGE + BM * 128 + (DG ? 0 : wn * (BN / WN) * 128);
     Vec16 fa[4][TM], fb[4][TN];
     auto read_frags = [&](int kk) __attribute__((always_inline)) {
 #pragma unroll
       for (int i = 0; i < TM; ++i) fa[kk][i].u = *reinterpret_cast<const uint4*>(sa + i * 32 * 128 + frag_off[kk]);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) fb[kk][j].u = *reinterpret_cast<const uint4*>(sb + j * 32 * 128 + frag_off[kk]);
+      for (int j = 0; j < TN; ++j) {
+        if constexpr (DG) fb[kk][j] = wgrad_read_frag<T, BRB>(sb, bt_base[j], kk);
+        else fb[kk][j].u = *reinterpret_cast<const uint4*>(sb + j * 32 * 128 + frag_off[kk]);
+      }
     };
 #pragma unroll
     for (int kk = 0; kk < AHEAD; ++kk) read_frags(kk);
@@ -448,13 +542,12 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
                            __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(cc) * 128u));
     };
     auto load_b_tile = [&](int stage, int cc, int tap, bool live) __attribute__((always_inline)) {
-      const bool cval = live && (!ragged || cc * BK + piece * V < a.Cg);
-      const uint32_t sob = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(tap * a.Cg) * static_cast<uint32_t>(sizeof(T)) +
-                                                          static_cast<uint32_t>(cc) * 128u);
+      const bool cval = !ragged || cc * BK + piece * V < a.Cg;
+      const uint32_t sob = __builtin_amdgcn_readfirstlane(b_at(tap, cc));
 #pragma unroll
       for (int i = 0; i < RB; ++i)
         buffer_load16_to_lds(rsB, lds0 + b_base + static_cast<uint32_t>(stage) * (BN * 128) + i * (RPL * 128),
-                             cval ? b_row[i] : kOob, sob);
+                             live && b_live(i, cc, cval) ? b_row[i] : kOob, sob);
     };
     auto load_nothing = [&]() __attribute__((always_inline)) { buffer_load16_to_lds(rsA, lds0 + dump, kOob, 0); };
     // Which taps of which rows exist: bit `tap` of vmask[i] for this lane's row of the wave's row block i.
@@ -470,7 +563,7 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
       uint32_t bits = 0;
 #pragma unroll
       for (int tap = 0; tap < 9; ++tap) {
-        const int dyo = MODE == 0 ? tap / 3 - 1 : 1 - tap / 3, dxo = MODE == 0 ? tap % 3 - 1 : 1 - tap % 3;
+        const int dyo = FWD ? tap / 3 - 1 : 1 - tap / 3, dxo = FWD ? tap % 3 - 1 : 1 - tap % 3;
         const bool v = ok && static_cast<unsigned>(y + dyo) < static_cast<unsigned>(a.H) &&
                        static_cast<unsigned>(x + dxo) < static_cast<unsigned>(a.W);
         bits |= v ? (1u << tap) : 0u;
@@ -487,13 +580,16 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
 #pragma unroll
       for (int i = 0; i < TM; ++i) mk[i] = ((vmask[i] >> tap) & 1u) ? 0xffffffffu : 0u;
       const unsigned char* sa = smem + static_cast<uint32_t>(buf) * run_bytes + wm * (BM / WM) * 128;
-      const unsigned char* sb = smem + b_base + bstage * (BN * 128) + wn * (BN / WN) * 128;
+      const unsigned char* sb = smem + b_base + bstage * (BN * 128) + (DG ? 0 : wn * (BN / WN) * 128);
       Vec16 fa[4][TM], fb[4][TN];
       auto read_frags = [&](int kk) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) fa[kk][i].u = *reinterpret_cast<const uint4*>(sa + i * 32 * 128 + aoff[kk]);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) fb[kk][j].u = *reinterpret_cast<const uint4*>(sb + j * 32 * 128 + frag_off[kk]);
+        for (int j = 0; j < TN; ++j) {
+          if constexpr (DG) fb[kk][j] = wgrad_read_frag<T, BRB>(sb, bt_base[j], kk);
+          else fb[kk][j].u = *reinterpret_cast<const uint4*>(sb + j * 32 * 128 + frag_off[kk]);
+        }
       };
       constexpr int AH = (TM + TN <= 3) ? 4 : 1;
 #pragma unroll
@@ -531,7 +627,7 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
         load_b_tile(bstage >= 1 ? bstage - 1 : NSB - 1, cc2, tap2, cc2 < cpt);  // the tile of step - 1: free again
         if (tap < NA && cc + 1 < cpt) load_run_pass(tap, cc + 1, buf ^ 1);
         else load_nothing();
-        compute_tap(buf, bstage, tap, MODE == 0 ? tap / 3 - 1 : 1 - tap / 3, MODE == 0 ? tap % 3 - 1 : 1 - tap % 3);
+        compute_tap(buf, bstage, tap, FWD ? tap / 3 - 1 : 1 - tap / 3, FWD ? tap % 3 - 1 : 1 - tap % 3);
         bstage = bstage == NSB - 1 ? 0 : bstage + 1;
       }
     }
@@ -578,12 +674,21 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
     stage = stage == NSTAGE - 1 ? 0 : stage + 1;
   }
   }
-  __builtin_amdgcn_s_barrier();  // the output tile below reuses the pipeline buffers
-  asm volatile("" ::: "memory");
+  if constexpr (AFF) {
+    if (tid < BN) {
+      float sc, bi;
+      bn_coeffs(pg, pb, pm, static_cast<float>(1.0 / sqrt(static_cast<double>(pr) + static_cast<double>(a.aff_eps))), &sc, &bi);
+      prm_s[tid] = sc; prm_s[BN + tid] = bi;
+    }
+    lds_writes_then_barrier();
+  } else {
+    __builtin_amdgcn_s_barrier();  // the output tile below reuses the pipeline buffers
+    asm volatile("" ::: "memory");
+  }
 
   // Epilogue.  acc[i][j][v]: output channel n = j*32 + (v/4)*8 + (lane/32)*4 + v%4, pixel m = i*32 + lane%32.
   // The tile goes to LDS in the storage type, or in float when a bf16 data gradient has an addend.
-  const bool wide = sizeof(T) == 2 && MODE == 1 && a.partial != nullptr && a.addend != nullptr;
+  const bool wide = sizeof(T) == 2 && (AFF || (DG && a.partial != nullptr)) && a.addend != nullptr;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -593,6 +698,17 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
       for (int g = 0; g < 4; ++g) {
         const int col = wn * (BN / WN) + j * 32 + g * 8 + (lane >> 5) * 4;
         unsigned char* dst = smem + row * CP + col * sizeof(T);
+        if constexpr (AFF) {
+          const float4 sc = *reinterpret_cast<const float4*>(prm_s + col), bi = *reinterpret_cast<const float4*>(prm_s + BN + col);
+          acc[i][j][g * 4 + 0] = bn_affine(acc[i][j][g * 4 + 0], sc.x, bi.x);
+          acc[i][j][g * 4 + 1] = bn_affine(acc[i][j][g * 4 + 1], sc.y, bi.y);
+          acc[i][j][g * 4 + 2] = bn_affine(acc[i][j][g * 4 + 2], sc.z, bi.z);
+          acc[i][j][g * 4 + 3] = bn_affine(acc[i][j][g * 4 + 3], sc.w, bi.w);
+          if (a.aff_relu && !a.addend) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[i][j][g * 4 + v] = fmaxf(acc[i][j][g * 4 + v], 0.f);
+          }
+        }
         if (wide) {
           *reinterpret_cast<float4*>(smem + row * CPW + col * 4) =
               make_float4(acc[i][j][g * 4 + 0], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
@@ -606,7 +722,7 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
         }
       }
     }
-  if (MODE == 1 && a.partial != nullptr && tid < BN) {
+  if (DG && a.partial != nullptr && tid < BN) {
     float sc, bi;
     bn_coeffs(pg, pb, pm, pr, &sc, &bi);
     prm_s[tid] = sc; prm_s[BN + tid] = bi; prm_s[2 * BN + tid] = pr; prm_s[3 * BN + tid] = -pm * pr;
@@ -618,7 +734,35 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
   T* out = static_cast<T*>(a.out);
   const int op = tid % PPR, orow = tid / PPR;
   const int n = n0 + op * V;
-  if (a.partial == nullptr) {
+  if constexpr (AFF) {
+    if (a.addend != nullptr) {
+      const T* add = static_cast<const T*>(a.addend);
+      const int nc = n < a.Ncols ? n : 0;
+      Vec16 av[NPASS];
+#pragma unroll
+      for (int pass = 0; pass < NPASS; ++pass)
+        av[pass] = load16(add + (static_cast<int64_t>(min(m0 + orow + pass * RPP, a.M - 1)) * a.Ncols + nc));
+#pragma unroll
+      for (int pass = 0; pass < NPASS; ++pass) {
+        const int row = orow + pass * RPP, m = m0 + row;
+        if (m < Mc && n < a.Ncols) {
+          float r[V], t[V];
+          Elem<T>::unpack(av[pass], r);
+          load_floats<V>(reinterpret_cast<const float*>(smem + row * CPW) + op * V, t);
+#pragma unroll
+          for (int j = 0; j < V; ++j) {
+            t[j] += r[j];
+            if (a.aff_relu) t[j] = fmaxf(t[j], 0.f);
+          }
+          Vec16 o;
+          Elem<T>::pack(t, o);
+          store16(out + (static_cast<int64_t>(m) * a.Ncols + n), o);
+        }
+      }
+      return;
+    }
+  }
+  if (AFF || a.partial == nullptr) {
 #pragma unroll
     for (int pass = 0; pass < NPASS; ++pass) {
       const int row = orow + pass * RPP;
@@ -797,57 +941,6 @@ struct WgradArgs {
 template <typename T> struct WgradCfg;
 template <> struct WgradCfg<uint16_t> { static constexpr int BKM = 64; };
 template <> struct WgradCfg<float> { static constexpr int BKM = 32; };
-
-// LDS tiles of the weight gradient are [k row][column] with rows of RBY = 16 * (columns per 16 bytes ...) bytes,
-// filled by LDS-destination loads (RBY/16 lanes per row).  The 16-byte slots of a row are stored permuted,
-// slot s of row r at s ^ wgrad_swz(r), so that the fragment reads below touch every bank once:
-//   bf16, 128-byte rows: a transposing read's 32 lanes take 64 bytes of 4 consecutive rows -- rows two apart
-//                        share their banks, so they swap halves;
-//   bf16, 256-byte rows: the same 4 rows all start at bank 0 -- each is rotated by a different 64 bytes;
-//   float:               lanes 32-63 read the row 4 below lanes 0-31 -- it is shifted by 128 bytes.
-template <typename T, int RBY>
-__device__ __forceinline__ int wgrad_swz(int row) {
-  if (sizeof(T) == 4) return ((row >> 2) & 1) << 3;
-  return RBY == 128 ? ((row >> 1) & 1) << 2 : (row & 3) << 2;
-}
-// Byte offset, inside a tile, of this lane's first read for the MFMA operand "32 columns from col0 x one k step"
-// at k step 0; step kk is KSTEP * kk rows further down.
-template <typename T, int RBY>
-__device__ __forceinline__ int wgrad_frag_base(int lane, int col0) {
-  if (sizeof(T) == 2) {
-    // ds_read_b64_tr_b16: within 16 lanes, lane t supplies the address of row t/4, columns 4*(t%4)..+3 and
-    // receives column t of rows 0..3.  Two reads (rows +0 and +4) give 8 k values of column lane%32.
-    const int g = lane >> 4, t = lane & 15;
-    const int krow = 8 * (g >> 1) + (t >> 2);
-    const int cb = 2 * (col0 + 16 * (g & 1) + 4 * (t & 3));
-    return krow * RBY + (((cb >> 4) ^ wgrad_swz<T, RBY>(krow)) << 4) + (cb & 15);
-  }
-  const int krow = (lane >> 5) * 4;  // + j, j = 0..3: the permutation only looks at bit 2
-  const int cb = 4 * (col0 + (lane & 31));
-  return krow * RBY + (((cb >> 4) ^ wgrad_swz<T, RBY>(krow)) << 4) + (cb & 15);
-}
-template <typename T, int RBY>
-__device__ __forceinline__ Vec16 wgrad_read_frag(const unsigned char* tile, int base, int kk) {
-  Vec16 v;
-  if constexpr (sizeof(T) == 2) {
-    typedef short s16x4 __attribute__((ext_vector_type(4)));
-    typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-    const unsigned char* p0 = tile + base + kk * 16 * RBY;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0 + 4 * RBY));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      v.h[j] = static_cast<uint16_t>(lo[j]);
-      v.h[4 + j] = static_cast<uint16_t>(hi[j]);
-    }
-  } else {
-    const unsigned char* p = tile + base + kk * 8 * RBY;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v.f[j] = *reinterpret_cast<const float*>(p + j * RBY);
-  }
-  return v;
-}
-
 
 // One workgroup: the BMO x BC tile (output channels x input channels of one tap) of one split of the pixel
 // range.  2 x 2 waves; per 64-row (32 in float) chunk of pixels the dy and x rows go straight into LDS
@@ -1210,64 +1303,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 }
 
 // ------------------------------------------------------- layout helper kernels
-// wT[c][t][k] = w[k][t][c]  (t = r*S+s): the B matrix of the data gradient.
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_kc_kernel(const T* __restrict__ w, T* __restrict__ wT,
-                                                           int K, int taps, int C) {
-  __shared__ T tile[32][33];
-  const int t = blockIdx.z, c0 = blockIdx.x * 32, k0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int i = ty; i < 32; i += 8) {
-    const int k = k0 + i, c = c0 + tx;
-    if (k < K && c < C) tile[i][tx] = w[(static_cast<int64_t>(k) * taps + t) * C + c];
-  }
-  __syncthreads();
-  for (int i = ty; i < 32; i += 8) {
-    const int c = c0 + i, k = k0 + tx;
-    if (k < K && c < C) wT[(static_cast<int64_t>(c) * taps + t) * K + k] = tile[tx][i];
-  }
-}
-
-// The same transposition for a whole list of weight tensors in one launch (the step's backward pass
-// needs every convolution's [Cin][R][S][Cout] form once per step).
-constexpr int kTransposeBatchMax = 64;
-struct TransposeBatchArgs {
-  const void* src;  // arena of [K][taps][C] tensors
-  void* dst;        // arena of [C][taps][K] tensors, same offsets
-  int num;
-  int tile_prefix[kTransposeBatchMax + 1];
-  uint32_t offset[kTransposeBatchMax];  // elements
-  int K[kTransposeBatchMax], taps[kTransposeBatchMax], C[kTransposeBatchMax];
-};
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_batch_kernel(const TransposeBatchArgs a) {
-  __shared__ T tile[32][33];
-  int lo = 0, hi = a.num;
-  const int b = blockIdx.x;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (a.tile_prefix[mid] <= b) lo = mid; else hi = mid;
-  }
-  const int K = a.K[lo], taps = a.taps[lo], C = a.C[lo];
-  const T* w = static_cast<const T*>(a.src) + a.offset[lo];
-  T* wT = static_cast<T*>(a.dst) + a.offset[lo];
-  int rem = b - a.tile_prefix[lo];
-  const int ct = (C + 31) / 32, kt = (K + 31) / 32;
-  const int c0 = (rem % ct) * 32; rem /= ct;
-  const int k0 = (rem % kt) * 32;
-  const int t = rem / kt;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int i = ty; i < 32; i += 8) {
-    const int k = k0 + i, c = c0 + tx;
-    if (k < K && c < C) tile[i][tx] = w[(static_cast<int64_t>(k) * taps + t) * C + c];
-  }
-  __syncthreads();
-  for (int i = ty; i < 32; i += 8) {
-    const int c = c0 + i, k = k0 + tx;
-    if (k < K && c < C) wT[(static_cast<int64_t>(c) * taps + t) * K + k] = tile[tx][i];
-  }
-}
-
 // Stem input: x [N][H][W][3] -> xp [N][H+6][Wp][4], zero border (3 pixels each side, Wp - W - 3 on the
 // right) and zero 4th channel, so that a 7-tap filter row is 8 pixels = 32 contiguous elements.
 template <typename T>
@@ -1379,18 +1414,21 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
     a.div_h[c] = make_fastdiv(classes ? (a.P - c + 1) >> 1 : a.P);
   }
   if (a.linear) {
-    if (a.mode == 0 && a.in_gamma) launch_igemm_mode<T, BM, BN, WM, WN, 0, true, true>(a, tag, grid, s);
+    if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, true>(a, tag, grid, s);
+    else if (a.mode == 0 && a.in_gamma) launch_igemm_mode<T, BM, BN, WM, WN, 0, true, true>(a, tag, grid, s);
     else if (a.mode == 0) launch_igemm_mode<T, BM, BN, WM, WN, 0, true>(a, tag, grid, s);
     else launch_igemm_mode<T, BM, BN, WM, WN, 1, true>(a, tag, grid, s);
     return;
   }
   const bool halo_shape = igemm_halo_shape(a);
   if (const int halo_lds = halo_shape ? halo_lds_bytes<BM, BN, WM, WN>(a.W, a.cpt) : 0) {
-    if (a.mode == 0) launch_igemm_halo<T, BM, BN, WM, WN, 0>(a, tag, grid, halo_lds, s);
+    if (a.mode == 2) launch_igemm_halo<T, BM, BN, WM, WN, 2>(a, tag, grid, halo_lds, s);
+    else if (a.mode == 0) launch_igemm_halo<T, BM, BN, WM, WN, 0>(a, tag, grid, halo_lds, s);
     else launch_igemm_halo<T, BM, BN, WM, WN, 1>(a, tag, grid, halo_lds, s);
     return;
   }
-  if (a.mode == 0) launch_igemm_mode<T, BM, BN, WM, WN, 0, false>(a, tag, grid, s);
+  if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, false>(a, tag, grid, s);
+  else if (a.mode == 0) launch_igemm_mode<T, BM, BN, WM, WN, 0, false>(a, tag, grid, s);
   else launch_igemm_mode<T, BM, BN, WM, WN, 1, false>(a, tag, grid, s);
 }
 
@@ -1700,11 +1738,17 @@ static IgemmArgs stem_igemm_args(const rn50_conv_desc* d, const void* xp, const 
 }
 
 // Forward of the stem from an already padded input; wp is scratch for the padded weights.
+static void set_affine(IgemmArgs& a, const BnAffine& f) {
+  a.mode = 2;
+  a.bn_gamma = f.gamma; a.bn_beta = f.beta; a.bn_mean = f.mean; a.aff_var = f.var;
+  a.aff_eps = f.eps; a.aff_relu = f.relu; a.addend = f.residual;
+}
 void stem_fwd_padded(const rn50_conv_desc* d, const void* xp, const void* w, void* wp, void* y, float* bn_partial,
-                     hipStream_t s) {
+                     hipStream_t s, const BnAffine* affine) {
   const int nw = d->Cout * kStemK;
   IgemmArgs a = stem_igemm_args(d, xp, wp, y);
   a.partial = bn_partial;
+  if (affine) set_affine(a, *affine);
   if (d->dtype == RN50_BF16) {
     RN50_LAUNCH("stem_pad", stem_pad_weight_kernel<uint16_t>, dim3(ceil_div(nw, 256)), dim3(256), 0, s,
                        static_cast<const uint16_t*>(w), static_cast<uint16_t*>(wp), d->Cout);
@@ -1870,7 +1914,7 @@ void wgrad_run(const rn50_conv_desc* d, const void* x_or_xp, const void* dy, flo
 }
 
 void fwd_run(const rn50_conv_desc* d, const void* x, const void* w, void* y, float* bn_partial, hipStream_t s,
-             const char* tag, const BnIn* in) {
+             const char* tag, const BnIn* in, const BnAffine* affine) {
   IgemmArgs a{};
   a.act = x; a.wgt = w; a.out = y; a.partial = bn_partial;
   if (in) { a.in_gamma = in->gamma; a.in_beta = in->beta; a.in_mean = in->mean; a.in_rstd = in->rstd; }
@@ -1881,44 +1925,19 @@ void fwd_run(const rn50_conv_desc* d, const void* x, const void* w, void* y, flo
   a.act_bytes = static_cast<uint32_t>(static_cast<size_t>(d->N) * d->H * d->W * d->Cin * esize(d->dtype));
   a.wgt_bytes = static_cast<uint32_t>(static_cast<size_t>(d->Cout) * a.Ktot * esize(d->dtype));
   a.cpt = static_cast<int>(ceil_div(d->Cin * esize(d->dtype), 128));
+  if (affine) set_affine(a, *affine);
   if (d->dtype == RN50_BF16) launch_igemm<uint16_t>(a, tag, s); else launch_igemm<float>(a, tag, s);
 }
 
-size_t dgrad_wt_bytes(const rn50_conv_desc* d) {
+// What conv_dgrad's callers are asked for (the size of the weights).  The kernels read the weights as they lie and
+// nothing is written there any more; the query and the checks stay as the interface has them.
+static size_t dgrad_ws_bytes(const rn50_conv_desc* d) {
   return align_up(static_cast<size_t>(d->Cout) * d->R * d->S * d->Cin * esize(d->dtype), 256);
 }
-void dgrad_transpose_weights(const rn50_conv_desc* d, const void* w, void* wT, hipStream_t s) {
-  const dim3 grid(ceil_div(d->Cin, 32), ceil_div(d->Cout, 32), d->R * d->S);
-  if (d->dtype == RN50_BF16)
-    hipLaunchKernelGGL(transpose_kc_kernel<uint16_t>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(w),
-                       static_cast<uint16_t*>(wT), d->Cout, d->R * d->S, d->Cin);
-  else
-    hipLaunchKernelGGL(transpose_kc_kernel<float>, grid, dim3(256), 0, s, static_cast<const float*>(w),
-                       static_cast<float*>(wT), d->Cout, d->R * d->S, d->Cin);
-}
-void transpose_batch_run(const std::vector<TransposeEntry>& list, int dtype, const void* src_arena, void* dst_arena,
-                         hipStream_t s) {
-  for (size_t i0 = 0; i0 < list.size(); i0 += kTransposeBatchMax) {
-    TransposeBatchArgs a{};
-    a.src = src_arena; a.dst = dst_arena;
-    a.num = static_cast<int>(list.size() - i0 < kTransposeBatchMax ? list.size() - i0 : kTransposeBatchMax);
-    a.tile_prefix[0] = 0;
-    for (int i = 0; i < a.num; ++i) {
-      const TransposeEntry& e = list[i0 + i];
-      a.offset[i] = static_cast<uint32_t>(e.offset);
-      a.K[i] = e.K; a.taps[i] = e.taps; a.C[i] = e.C;
-      a.tile_prefix[i + 1] = a.tile_prefix[i] + static_cast<int>(ceil_div(e.K, 32) * ceil_div(e.C, 32) * e.taps);
-    }
-    const int grid = a.tile_prefix[a.num];
-    if (dtype == RN50_BF16) RN50_LAUNCH("weight_transpose", transpose_batch_kernel<uint16_t>, dim3(grid), dim3(256), 0, s, a);
-    else RN50_LAUNCH("weight_transpose", transpose_batch_kernel<float>, dim3(grid), dim3(256), 0, s, a);
-  }
-}
-
-// Data gradient from already transposed weights wT [Cin][R][S][Cout].
-void dgrad_run(const rn50_conv_desc* d, const void* dy, const void* wT, void* dx, const BnBwdSums* bn, hipStream_t s) {
+void dgrad_run(const rn50_conv_desc* d, const void* dy, const void* w, void* dx, const BnBwdSums* bn, hipStream_t s,
+               const char* tag) {
   IgemmArgs a{};
-  a.act = dy; a.wgt = wT; a.out = dx;
+  a.act = dy; a.wgt = w; a.out = dx;
   if (bn) {
     a.partial = bn->partial; a.bn_x = bn->x;
     a.bn_gamma = bn->gamma; a.bn_beta = bn->beta; a.bn_mean = bn->mean; a.bn_rstd = bn->rstd;
@@ -1932,7 +1951,7 @@ void dgrad_run(const rn50_conv_desc* d, const void* dy, const void* wT, void* dx
   a.act_bytes = static_cast<uint32_t>(static_cast<size_t>(d->N) * a.H * a.W * d->Cout * esize(d->dtype));
   a.wgt_bytes = static_cast<uint32_t>(static_cast<size_t>(d->Cin) * a.Ktot * esize(d->dtype));
   a.cpt = static_cast<int>(ceil_div(d->Cout * esize(d->dtype), 128));
-  if (d->dtype == RN50_BF16) launch_igemm<uint16_t>(a, "conv_dgrad", s); else launch_igemm<float>(a, "conv_dgrad", s);
+  if (d->dtype == RN50_BF16) launch_igemm<uint16_t>(a, tag, s); else launch_igemm<float>(a, tag, s);
 }
 
 }  // namespace rn50
@@ -1945,7 +1964,7 @@ extern "C" size_t conv_fwd_workspace_bytes(const rn50_conv_desc* d) {
 }
 extern "C" size_t conv_dgrad_workspace_bytes(const rn50_conv_desc* d) {
   if (!d || check_conv(d, "conv_dgrad_workspace_bytes")) return 0;
-  return dgrad_wt_bytes(d);
+  return dgrad_ws_bytes(d);
 }
 extern "C" size_t conv_wgrad_workspace_bytes(const rn50_conv_desc* d) {
   if (!d || check_conv(d, "conv_wgrad_workspace_bytes")) return 0;
@@ -1983,11 +2002,10 @@ extern "C" int conv_dgrad(const rn50_conv_desc* d, const void* dy, const void* w
   RN50_REQUIRE(dy && w && dx && workspace, RN50_ERR_INVALID, "conv_dgrad: null pointer");
   RN50_REQUIRE(aligned16(dy) && aligned16(w) && aligned16(dx) && aligned16(workspace), RN50_ERR_ALIGN,
                "conv_dgrad: pointer not 16-byte aligned");
-  RN50_REQUIRE(workspace_bytes >= dgrad_wt_bytes(d), RN50_ERR_WORKSPACE, "conv_dgrad: workspace %zu < %zu bytes",
-               workspace_bytes, dgrad_wt_bytes(d));
+  RN50_REQUIRE(workspace_bytes >= dgrad_ws_bytes(d), RN50_ERR_WORKSPACE, "conv_dgrad: workspace %zu < %zu bytes",
+               workspace_bytes, dgrad_ws_bytes(d));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  dgrad_transpose_weights(d, w, workspace, s);
-  dgrad_run(d, dy, workspace, dx, nullptr, s);
+  dgrad_run(d, dy, w, dx, nullptr, s);
   return launch_status("conv_dgrad");
 }
 
@@ -2062,15 +2080,14 @@ extern "C" int conv_dgrad_bn_sums(const rn50_conv_desc* d, const void* dy, const
                    aligned16(sums) && aligned16(addend) && aligned16(gamma) && aligned16(beta) &&
                    aligned16(save_mean) && aligned16(save_rstd),
                RN50_ERR_ALIGN, "conv_dgrad_bn_sums: pointer not 16-byte aligned");
-  RN50_REQUIRE(workspace_bytes >= dgrad_wt_bytes(d), RN50_ERR_WORKSPACE,
-               "conv_dgrad_bn_sums: workspace %zu < %zu bytes", workspace_bytes, dgrad_wt_bytes(d));
+  RN50_REQUIRE(workspace_bytes >= dgrad_ws_bytes(d), RN50_ERR_WORKSPACE,
+               "conv_dgrad_bn_sums: workspace %zu < %zu bytes", workspace_bytes, dgrad_ws_bytes(d));
   RN50_REQUIRE(sums_bytes >= conv_bn_sums_bytes(d), RN50_ERR_WORKSPACE, "conv_dgrad_bn_sums: sums %zu < %zu bytes",
                sums_bytes, conv_bn_sums_bytes(d));
   RN50_REQUIRE(!addend_mask || addend, RN50_ERR_INVALID, "conv_dgrad_bn_sums: addend_mask without addend");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  dgrad_transpose_weights(d, w, workspace, s);
   const BnBwdSums bn{bn_x, gamma, beta, save_mean, save_rstd, sums, addend, relu_mask, addend_mask};
-  dgrad_run(d, dy, workspace, dx, &bn, s);
+  dgrad_run(d, dy, w, dx, &bn, s);
   return launch_status("conv_dgrad_bn_sums");
 }
 

@@ -324,78 +324,62 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(const TA* __restrict__ 
     }
 }
 
-// logits[n][k] = sum_c a[n][c]*W[k][c] + b[k]: one wave per class k.  The wave streams its weight row
-// once per block of 8 batch rows (the activations, N*Cin elements, stay in cache), accumulates in
-// float and finishes each dot product with a wave reduction.
 __device__ __forceinline__ f32x16 mfma_bf16_32x32x16(const Vec16& a, const Vec16& b, f32x16 acc) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(&a),
                                                  *reinterpret_cast<const bf16x8*>(&b), acc, 0, 0, 0);
 }
 
-// Matrix-core form for bf16 and a batch of at most 64 rows: a workgroup owns 32 classes; its four waves
-// split the input channels (wave w takes channels 16*(w + 4i)..+15), each multiplying the [32 classes x
-// 16] weight fragment with the [16 x 32 rows] activation fragments read straight from memory
-// (v_mfma_f32_32x32x16_bf16: lane l supplies row l%32, k = 8*(l/32)..+7 of both operands).  The waves'
-// partial tiles are added through LDS in wave order.  Every workgroup reads the activations once.
-__global__ __launch_bounds__(256) void fc_fwd_mfma_kernel(const uint16_t* __restrict__ a,
-                                                          const uint16_t* __restrict__ W,
-                                                          const float* __restrict__ b,
-                                                          float* __restrict__ logits, int N, int Cin, int K) {
-  __shared__ float red[4][2][32 * 32];
+// logits[n][k] = sum_c a[n][c]*W[k][c] + b[k] for bf16 on the matrix cores: a workgroup owns 32 classes x 32 rows, its
+// sixteen waves a sixteenth of the input channels each, reading both operands straight from memory
+// (v_mfma_f32_32x32x16_bf16: lane l supplies row l%32, k = 8*(l/32)..+7) and adding their tiles through LDS in wave order.
+// What bounds it is latency: 2048 channels are eight k steps per wave, all of whose loads are in flight at once (four
+// waves with eight times the loop took 16 us at batch 4 and 19 at 40; batches above 64 rows, which went one class per
+// wave, 409 us at 256).
+constexpr int kFcWaves = 16;
+__global__ __launch_bounds__(64 * kFcWaves) void fc_fwd_mfma_kernel(const uint16_t* __restrict__ a,
+                                                                    const uint16_t* __restrict__ W,
+                                                                    const float* __restrict__ b,
+                                                                    float* __restrict__ logits, int N, int Cin, int K) {
+  __shared__ float red[kFcWaves][32 * 33];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int k0 = blockIdx.x * 32;
-  const int krow = min(k0 + (lane & 31), K - 1);
-  const int n_lo = min(lane & 31, N - 1), n_hi = min(32 + (lane & 31), N - 1);
-  const bool hi_ok = 32 + (lane & 31) < N, lo_ok = (lane & 31) < N;
+  const int k0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
+  const int krow = min(k0 + (lane & 31), K - 1), nrow = min(r0 + (lane & 31), N - 1);  // (rows past the end: never stored)
+  const int span = (Cin / 16 + kFcWaves - 1) / kFcWaves * 16;
+  const int c0 = wave * span, c1 = min(c0 + span, Cin);
   const uint16_t* wp = W + static_cast<int64_t>(krow) * Cin + 8 * (lane >> 5);
-  const uint16_t* ap0 = a + static_cast<int64_t>(n_lo) * Cin + 8 * (lane >> 5);
-  const uint16_t* ap1 = a + static_cast<int64_t>(n_hi) * Cin + 8 * (lane >> 5);
-  f32x16 acc0, acc1;
+  const uint16_t* ap = a + static_cast<int64_t>(nrow) * Cin + 8 * (lane >> 5);
+  f32x16 acc;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) acc0[v] = acc1[v] = 0.f;
-  constexpr int U = 8;  // loads in flight per operand: the kernel runs at the latency of its batches of loads
-  int c = wave * 16;
-  for (; c + (U - 1) * 64 < Cin; c += U * 64) {
-    Vec16 fw[U], f0[U], f1[U];
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  constexpr int U = 8;
+  for (int c = c0; c < c1; c += U * 16) {
+    Vec16 fw[U], fa[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      fw[u] = load16(wp + c + u * 64);
-      f0[u] = load16(ap0 + c + u * 64);
-      f1[u] = load16(ap1 + c + u * 64);
+      const int at = min(c + u * 16, c1 - 16);
+      fw[u] = load16(wp + at);
+      fa[u] = load16(ap + at);
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (!lo_ok) f0[u].u = make_uint4(0, 0, 0, 0);
-      if (!hi_ok) f1[u].u = make_uint4(0, 0, 0, 0);
-      acc0 = mfma_bf16_32x32x16(fw[u], f0[u], acc0);
-      acc1 = mfma_bf16_32x32x16(fw[u], f1[u], acc1);
-    }
+    for (int u = 0; u < U; ++u)
+      if (c + u * 16 < c1) acc = mfma_bf16_32x32x16(fw[u], fa[u], acc);
   }
-  for (; c < Cin; c += 64) {
-    Vec16 fw = load16(wp + c), f0 = load16(ap0 + c), f1 = load16(ap1 + c);
-    if (!lo_ok) f0.u = make_uint4(0, 0, 0, 0);
-    if (!hi_ok) f1.u = make_uint4(0, 0, 0, 0);
-    acc0 = mfma_bf16_32x32x16(fw, f0, acc0);
-    acc1 = mfma_bf16_32x32x16(fw, f1, acc1);
-  }
-  // D[class][row]: class = (v/4)*8 + (lane/32)*4 + v%4, row = lane%32
+  // D[class][row]: class = (v/4)*8 + (lane/32)*4 + v%4, row = lane%32; kept [row][class] so that rows leave contiguously
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int cls = (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-    red[wave][0][cls * 32 + (lane & 31)] = acc0[v];
-    red[wave][1][cls * 32 + (lane & 31)] = acc1[v];
-  }
+  for (int v = 0; v < 16; ++v) red[wave][(lane & 31) * 33 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3)] = acc[v];
   __syncthreads();
-  for (int i = threadIdx.x; i < 2 * 32 * 32; i += 256) {
-    const int t = i >> 10, cls = (i >> 5) & 31, row = t * 32 + (i & 31);
-    const int k = k0 + cls;
-    if (k < K && row < N) {
-      const int j = cls * 32 + (i & 31);
-      logits[static_cast<int64_t>(row) * K + k] = ((red[0][t][j] + red[1][t][j]) + red[2][t][j]) + red[3][t][j] + b[k];
-    }
+  const int row = threadIdx.x >> 5, cls = threadIdx.x & 31;
+  if (r0 + row < N && k0 + cls < K) {
+    float s = red[0][row * 33 + cls];
+#pragma unroll
+    for (int w = 1; w < kFcWaves; ++w) s += red[w][row * 33 + cls];
+    logits[static_cast<int64_t>(r0 + row) * K + k0 + cls] = s + b[k0 + cls];
   }
 }
 
+// The other cases (float, ragged channel counts): one wave per class k.  The wave streams its weight row
+// once per block of 8 batch rows (the activations, N*Cin elements, stay in cache), accumulates in
+// float and finishes each dot product with a wave reduction.
 template <typename T>
 __global__ __launch_bounds__(256) void fc_fwd_kernel(const T* __restrict__ a, const T* __restrict__ W,
                                                      const float* __restrict__ b,
@@ -471,7 +455,8 @@ __global__ __launch_bounds__(256) void xent_rows_kernel(const float* __restrict_
                                                         const int32_t* __restrict__ labels, int N,
                                                         int K, float ls, float grad_scale,
                                                         float* __restrict__ row_loss,
-                                                        float* __restrict__ dlogits) {
+                                                        float* __restrict__ dlogits,
+                                                        uint16_t* __restrict__ dlogits_bf16) {
   __shared__ float red[8];
   const int n = blockIdx.x;
   const float* l = logits + static_cast<int64_t>(n) * K;
@@ -496,7 +481,9 @@ __global__ __launch_bounds__(256) void xent_rows_kernel(const float* __restrict_
   for (int k = threadIdx.x; k < K; k += 256) {
     const float logp = l[k] - mx - lse;
     const float q = qoff + (k == label ? qon : 0.f);
-    dlogits[static_cast<int64_t>(n) * K + k] = coef * (expf(logp) - q);
+    const float d = coef * (expf(logp) - q);
+    dlogits[static_cast<int64_t>(n) * K + k] = d;
+    if (dlogits_bf16) dlogits_bf16[static_cast<int64_t>(n) * K + k] = float_to_bf16_bits(d);
   }
   if (threadIdx.x == 0) {
     // -sum_k q_k logp_k = -(ls/K) * sum_k logp_k - (1-ls) * logp_label
@@ -514,6 +501,15 @@ __global__ __launch_bounds__(256) void mean_kernel(const float* __restrict__ v, 
   for (int i = threadIdx.x; i < n; i += 256) s += v[i];
   s = block256_sum(s, red);
   if (threadIdx.x == 0) out[0] = s / static_cast<float>(n);
+}
+
+void xent_rows(int N, int K, const float* logits, const int32_t* labels, float label_smoothing, float grad_scale,
+               float* row_loss, float* dlogits, void* dlogits_t, int dtype, hipStream_t s) {
+  RN50_LAUNCH("xent", xent_rows_kernel, dim3(N), dim3(256), 0, s, logits, labels, N, K, label_smoothing, grad_scale,
+              row_loss, dlogits, dtype == RN50_BF16 ? static_cast<uint16_t*>(dlogits_t) : nullptr);
+}
+void loss_mean(int N, const float* row_loss, float* loss_out, hipStream_t s) {
+  RN50_LAUNCH("xent", mean_kernel, dim3(1), dim3(256), 0, s, row_loss, N, loss_out);
 }
 
 static int check_dtype(int dtype, const char* who) {
@@ -623,9 +619,9 @@ extern "C" int fc_fwd(int N, int Cin, int K, int dtype, const void* a, const voi
   RN50_REQUIRE(Cin % (dtype == RN50_BF16 ? 8 : 4) == 0, RN50_ERR_UNSUPPORTED, "fc_fwd: Cin=%d", Cin);
   RN50_REQUIRE(aligned16(a) && aligned16(W), RN50_ERR_ALIGN, "fc_fwd: pointer not 16-byte aligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (dtype == RN50_BF16 && N <= 64 && Cin % 16 == 0) {
-    RN50_LAUNCH("fc_fwd", fc_fwd_mfma_kernel, dim3(ceil_div(K, 32)), dim3(256), 0, s, static_cast<const uint16_t*>(a),
-                static_cast<const uint16_t*>(W), b, logits, N, Cin, K);
+  if (dtype == RN50_BF16 && Cin % 16 == 0 && N <= 65535 * 32) {
+    RN50_LAUNCH("fc_fwd", fc_fwd_mfma_kernel, dim3(ceil_div(K, 32), ceil_div(N, 32)), dim3(64 * kFcWaves), 0, s,
+                static_cast<const uint16_t*>(a), static_cast<const uint16_t*>(W), b, logits, N, Cin, K);
     return launch_status("fc_fwd");
   }
   DISPATCH_T(dtype, {
@@ -636,14 +632,14 @@ extern "C" int fc_fwd(int N, int Cin, int K, int dtype, const void* a, const voi
 }
 
 // The data gradient runs on the matrix cores when the shapes allow it (Cin and K multiples of the
-// 16-byte vector): da = dl x W as a 1x1 "convolution" over N pixels with K input channels, reading
-// dl in the storage type and W transposed to [Cin][K].
-static bool fc_mfma_ok(int Cin, int K, int dtype) {
+// 16-byte vector): the classifier is a 1x1 convolution of N pixels, da its data gradient, from dl in the storage type.
+bool rn50::fc_mfma_ok(int Cin, int K, int dtype) {
   const int V = dtype == RN50_BF16 ? 8 : 4;
   return Cin % V == 0 && K % V == 0;
 }
-static rn50_conv_desc fc_dgrad_desc(int N, int Cin, int K, int dtype) {
-  return rn50_conv_desc{N, 1, 1, K, Cin, 1, 1, 1, 0, dtype};  // "input channels" K -> "output channels" Cin
+void rn50::fc_bwd_da(int N, int Cin, int K, int dtype, const void* W, const void* dlogits_t, void* da, hipStream_t s) {
+  const rn50_conv_desc d{N, 1, 1, Cin, K, 1, 1, 1, 0, dtype};
+  dgrad_run(&d, dlogits_t, W, da, nullptr, s, "fc_bwd_da");
 }
 
 extern "C" size_t fc_bwd_workspace_bytes(int N, int Cin, int K, int dtype) {
@@ -678,7 +674,6 @@ extern "C" int fc_bwd(int N, int Cin, int K, int dtype, const void* a, const voi
                RN50_ERR_ALIGN, "fc_bwd: pointer not 16-byte aligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (fc_mfma_ok(Cin, K, dtype)) {
-    const size_t es = dtype == RN50_BF16 ? 2 : 4;
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     const void* dl_t = dlogits;
     if (dtype == RN50_BF16) {
@@ -687,11 +682,7 @@ extern "C" int fc_bwd(int N, int Cin, int K, int dtype, const void* a, const voi
                          reinterpret_cast<uint16_t*>(ws), n);
       dl_t = ws;
     }
-    void* wT = ws + align_up(static_cast<size_t>(N) * K * es, 256);
-    const rn50_conv_desc wdesc{1, 1, 1, Cin, K, 1, 1, 1, 0, dtype};  // W [K][Cin] -> wT [Cin][K]
-    dgrad_transpose_weights(&wdesc, W, wT, s);
-    const rn50_conv_desc d = fc_dgrad_desc(N, Cin, K, dtype);
-    fwd_run(&d, dl_t, wT, da, nullptr, s, "fc_bwd_da");
+    fc_bwd_da(N, Cin, K, dtype, W, dl_t, da, s);
   } else {
     DISPATCH_T(dtype, {
       small_gemm<float, T, T>(dlogits, K, 1, static_cast<const T*>(W), Cin, 1, nullptr,
@@ -713,9 +704,8 @@ extern "C" int xent_fwd_bwd(int N, int K, const float* logits, const int32_t* la
   RN50_REQUIRE(label_smoothing >= 0.f && label_smoothing <= 1.f, RN50_ERR_INVALID,
                "xent_fwd_bwd: label_smoothing %g", label_smoothing);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  RN50_LAUNCH("xent", xent_rows_kernel, dim3(N), dim3(256), 0, s, logits, labels, N, K,
-                     label_smoothing, grad_scale, row_loss_out, dlogits);
-  RN50_LAUNCH("xent", mean_kernel, dim3(1), dim3(256), 0, s, row_loss_out, N, loss_out);
+  xent_rows(N, K, logits, labels, label_smoothing, grad_scale, row_loss_out, dlogits, nullptr, RN50_F32, s);
+  loss_mean(N, row_loss_out, loss_out, s);
   return launch_status("xent_fwd_bwd");
 }
 

@@ -55,16 +55,14 @@ struct rn50_plan {
   size_t ws_bytes = 0;
   size_t xp = 0, wp = 0, pool = 0, avg = 0, logits = 0, dlogits = 0, row_loss = 0, davg = 0;
   size_t g[5] = {0, 0, 0, 0, 0};
-  size_t wT = 0, wgrad_scratch = 0, bn_scratch = 0, lars_scratch = 0, pool_argmax = 0, fc_scratch = 0;
+  size_t wgrad_scratch = 0, bn_scratch = 0, lars_scratch = 0, pool_argmax = 0, fc_scratch = 0;
   size_t bn_scratch_bytes = 0, fc_scratch_bytes = 0;
-  std::vector<rn50::TransposeEntry> transposes;
   rn50::LarsArenaSpec lars_rest, lars_stem;  // every tensor but the stem's weight / the stem's weight
   size_t lars_stem_scratch = 0;
-  // Second stream for the work that is off the step's critical path (weight gradients, the weight
-  // transposition), with the events that order it against the caller's stream.  Created at the first
+  // Second stream for the work that is off the step's critical path (the weight gradients), with the events that order it against the caller's stream.  Created at the first
   // step (default priority), destroyed with the plan.
   hipStream_t side = nullptr;
-  hipEvent_t ev_fork = nullptr, ev_wt = nullptr;
+  hipEvent_t ev_fork = nullptr;
   // Third stream: the projection shortcut of a stage's first block, forward and backward, runs beside the
   // block's main branch (its own BN scratch; fork/join events reused block after block).
   hipStream_t branch = nullptr;
@@ -179,7 +177,7 @@ extern "C" int resnet_plan_create(const rn50_step_config* cfg, rn50_plan** plan_
   const Unit& u0 = p->units[0];
   p->xp = bump(&top, stem_padded_input_bytes(&u0.conv));
   p->wp = bump(&top, stem_padded_weight_bytes(&u0.conv));
-  size_t max_act = 0, max_wT = 0, max_wg = 0, max_bn = 0;
+  size_t max_act = 0, max_wg = 0, max_bn = 0;
   for (Unit& u : p->units) {
     const size_t out_elems = static_cast<size_t>(N) * u.P * u.Q * u.conv.Cout;
     const size_t in_elems = static_cast<size_t>(N) * u.conv.H * u.conv.W * u.conv.Cin;
@@ -194,7 +192,6 @@ extern "C" int resnet_plan_create(const rn50_step_config* cfg, rn50_plan** plan_
     u.rstd = bump(&top, u.conv.Cout * sizeof(float));
     if (out_elems > max_act) max_act = out_elems;
     if (in_elems > max_act && u.conv.Cin != 3) max_act = in_elems;
-    if (u.conv.Cin != 3 && dgrad_wt_bytes(&u.conv) > max_wT) max_wT = dgrad_wt_bytes(&u.conv);
     if (wgrad_partial_bytes(&u.conv) > max_wg) max_wg = wgrad_partial_bytes(&u.conv);
     if (bn_relu_fwd_workspace_bytes(&u.bn) > max_bn) max_bn = bn_relu_fwd_workspace_bytes(&u.bn);
     // sums fused into the convolutions: one row per output tile, at most ceil(M/64) rows of 16 bytes per channel
@@ -210,11 +207,6 @@ extern "C" int resnet_plan_create(const rn50_step_config* cfg, rn50_plan** plan_
   p->dlogits = bump(&top, static_cast<size_t>(N) * cfg->classes * sizeof(float));
   p->row_loss = bump(&top, static_cast<size_t>(N) * sizeof(float));
   for (int i = 0; i < 5; ++i) p->g[i] = bump(&top, max_act * es);
-  (void)max_wT;
-  p->wT = bump(&top, static_cast<size_t>(p->arena_elems) * es);  // transposed copy of every conv weight
-  for (const Unit& u : p->units)
-    if (u.conv.Cin != 3)
-      p->transposes.push_back(TransposeEntry{p->tensors[u.iw].offset, u.conv.Cout, u.conv.R * u.conv.S, u.conv.Cin});
   p->pool_argmax = bump(&top, static_cast<size_t>(N) * Hpool * Hpool * cfg->stem);
   p->fc_scratch_bytes = fc_bwd_workspace_bytes(N, cin, cfg->classes, cfg->dtype);
   p->fc_scratch = bump(&top, p->fc_scratch_bytes);
@@ -260,7 +252,7 @@ void destroy_streams(rn50_plan* p) {
     (void)hipStreamSynchronize(p->branch);
     (void)hipStreamDestroy(p->branch);
   }
-  for (hipEvent_t* e : {&p->ev_bfork, &p->ev_bjoin, &p->ev_fork, &p->ev_wt})
+  for (hipEvent_t* e : {&p->ev_bfork, &p->ev_bjoin, &p->ev_fork})
     if (*e) {
       (void)hipEventDestroy(*e);
       *e = nullptr;
@@ -284,8 +276,7 @@ int ensure_side_stream(rn50_plan* p) {
               ok(hipStreamCreateWithFlags(&p->branch, hipStreamNonBlocking)) &&
               ok(hipEventCreateWithFlags(&p->ev_bfork, kEventFlags)) &&
               ok(hipEventCreateWithFlags(&p->ev_bjoin, kEventFlags)) &&
-              ok(hipEventCreateWithFlags(&p->ev_fork, kEventFlags)) &&
-              ok(hipEventCreateWithFlags(&p->ev_wt, kEventFlags));
+              ok(hipEventCreateWithFlags(&p->ev_fork, kEventFlags));
   for (size_t i = 0; good && i < p->blocks.size() + 1; ++i) {  // the blocks and the stem
     hipEvent_t a = nullptr, b = nullptr;
     good = ok(hipEventCreateWithFlags(&a, kEventFlags)) && ok(hipEventCreateWithFlags(&b, kEventFlags));
@@ -418,9 +409,6 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
   RN50_REQUIRE(cfg.dtype == RN50_F32 || master, RN50_ERR_INVALID,
                "resnet_step: BF16 mode reads BN gamma/beta and the FC bias from the float master arena");
 
-  // The side stream starts after whatever the caller's stream holds so far (the previous step's update
-  // of the model weights, for one) and transposes the weights for the data gradients while the forward
-  // pass runs: [Cout][R][S][Cin] -> [Cin][R][S][Cout], every convolution in one launch.
   STEP_TRY(ensure_side_stream(plan));
 #ifdef RN50_TUNING  // what-if measurement: the whole step on the caller's stream (no concurrency between its parts)
   static const bool one_stream = getenv("RN50_ONE_STREAM") != nullptr;
@@ -428,12 +416,6 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
   constexpr bool one_stream = false;
 #endif
   hipStream_t side = one_stream ? s : plan->side;
-  (void)hipEventRecord(plan->ev_fork, s);
-  (void)hipStreamWaitEvent(side, plan->ev_fork, 0);
-  // the learning rate of this step (read by the update at the end, which waits for the side stream)
-  if (ctl) hipLaunchKernelGGL(lr_tick_kernel, dim3(1), dim3(64), 0, side, ctl->sched, ctl->t, ctl->lr);
-  transpose_batch_run(plan->transposes, dt, model, ws + plan->wT, side);
-  (void)hipEventRecord(plan->ev_wt, side);
   float* const run_mean = ctl ? ctl->run_mean : nullptr;
   float* const run_var = ctl ? ctl->run_var : nullptr;
   const float bn_momentum = ctl ? ctl->bn_momentum : 0.f;
@@ -495,17 +477,25 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
   float* logits = logits_out ? logits_out : F(plan->logits);
   STEP_TRY(avgpool_fwd(cfg.N, HW, plan->fc_in, dt, cur, ws + plan->avg, s));
   STEP_TRY(fc_fwd(cfg.N, plan->fc_in, cfg.classes, dt, ws + plan->avg, W(fcw), MP(fcb), logits, s));
-  STEP_TRY(xent_fwd_bwd(cfg.N, cfg.classes, logits, labels, cfg.label_smoothing, cfg.grad_scale, loss_out,
-                        F(plan->row_loss), F(plan->dlogits), s));
+  // (dlogits also in the storage type: what the classifier's data gradient reads)
+  const bool fc_mfma = fc_mfma_ok(plan->fc_in, cfg.classes, dt);
+  void* const dlogits_t = dt == RN50_BF16 && fc_mfma ? ws + plan->fc_scratch : nullptr;
+  xent_rows(cfg.N, cfg.classes, logits, labels, cfg.label_smoothing, cfg.grad_scale, F(plan->row_loss), F(plan->dlogits),
+            dlogits_t, dt, s);
 
   // -------------------------------------------------------------- backward
-  // the classifier's parameter gradients, which only the update reads, run on the side stream
+  // What only the end of the step needs runs on the side stream: the mean loss, the learning rate of this step (read by
+  // the update), the classifier's parameter gradients.
   (void)hipEventRecord(plan->ev_fork, s);
   (void)hipStreamWaitEvent(side, plan->ev_fork, 0);
+  loss_mean(cfg.N, F(plan->row_loss), loss_out, side);
+  if (ctl) hipLaunchKernelGGL(lr_tick_kernel, dim3(1), dim3(64), 0, side, ctl->sched, ctl->t, ctl->lr);
   fc_bwd_params(cfg.N, plan->fc_in, cfg.classes, dt, ws + plan->avg, F(plan->dlogits), G(fcw), G(fcb), side);
-  STEP_TRY(fc_bwd(cfg.N, plan->fc_in, cfg.classes, dt, ws + plan->avg, W(fcw), F(plan->dlogits), ws + plan->davg,
-                  nullptr, nullptr, ws + plan->fc_scratch, plan->fc_scratch_bytes, s));
-  (void)hipStreamWaitEvent(s, plan->ev_wt, 0);  // the transposed weights
+  if (fc_mfma)
+    fc_bwd_da(cfg.N, plan->fc_in, cfg.classes, dt, W(fcw), dlogits_t ? dlogits_t : F(plan->dlogits), ws + plan->davg, s);
+  else
+    STEP_TRY(fc_bwd(cfg.N, plan->fc_in, cfg.classes, dt, ws + plan->avg, W(fcw), F(plan->dlogits), ws + plan->davg,
+                    nullptr, nullptr, ws + plan->fc_scratch, plan->fc_scratch_bytes, s));
   unsigned char* g[5];
   for (int i = 0; i < 5; ++i) g[i] = ws + plan->g[i];
   // g[0], g[1]: the two summands of the gradient w.r.t. the current block output (g[1] may be unused)
@@ -581,7 +571,7 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
                        below->bn.mode == 2 ? ws + below->relu_mask : nullptr, addend_mask};
       dgrad_sums_rows = dgrad_partial_rows(&u.conv).num;
     }
-    dgrad_run(&u.conv, dy, ws + plan->wT + plan->tensors[u.iw].offset * es, dx, below ? &fuse : nullptr, st);
+    dgrad_run(&u.conv, dy, W(u.iw), dx, below ? &fuse : nullptr, st);
   };
   auto unit_bwd = [&](Unit& u, const void* in, const void* dz, const void* dz2, void* dres, void* dx,
                       bool sums_ready, Unit* below, const void* addend) -> int {
@@ -787,31 +777,30 @@ extern "C" int resnet_eval(rn50_plan* plan, const void* state, const void* image
   auto W = [&](int ti) -> const void* { return static_cast<const unsigned char*>(model) + plan->tensors[ti].offset * es; };
   auto MP = [&](int ti) -> const float* { return master + plan->tensors[ti].offset; };
   auto F = [&](size_t off) -> float* { return reinterpret_cast<float*>(ws + off); };
-  auto bn = [&](Unit& u, const void* residual) {
-    bn_infer_run(&u.bn, ws + u.y, MP(u.ig), MP(u.ib), run_mean + u.bn_off, run_var + u.bn_off, residual, ws + u.z,
-                 F(u.rstd), s);
+  // every layer's batch norm (+ residual, + ReLU) is the output stage of its convolution
+  auto affine = [&](const Unit& u, const void* residual) {
+    return BnAffine{MP(u.ig), MP(u.ib), run_mean + u.bn_off, run_var + u.bn_off, u.bn.eps, u.bn.mode != 0, residual};
+  };
+  auto conv_bn = [&](Unit& u, const void* in, const void* residual) {
+    const BnAffine f = affine(u, residual);
+    fwd_run(&u.conv, in, W(u.iw), ws + u.z, nullptr, s, "conv_fwd", nullptr, &f);
   };
   Unit& u0 = plan->units[0];
   stem_pad_input(&u0.conv, images, ws + plan->xp, s);
-  stem_fwd_padded(&u0.conv, ws + plan->xp, W(u0.iw), ws + plan->wp, ws + u0.y, nullptr, s);
-  bn(u0, nullptr);
-  STEP_TRY(maxpool_fwd(cfg.N, u0.P, u0.Q, cfg.stem, dt, ws + u0.z, ws + plan->pool, ws + plan->pool_argmax, s));
+  const BnAffine f0 = affine(u0, nullptr);
+  stem_fwd_padded(&u0.conv, ws + plan->xp, W(u0.iw), ws + plan->wp, ws + u0.z, nullptr, s, &f0);
+  STEP_TRY(maxpool_fwd(cfg.N, u0.P, u0.Q, cfg.stem, dt, ws + u0.z, ws + plan->pool, nullptr, s));
   const unsigned char* cur = ws + plan->pool;
   for (const Block& b : plan->blocks) {
     Unit &u1 = plan->units[b.u1], &u2 = plan->units[b.u2], &u3 = plan->units[b.u3];
     const void* shortcut = cur;
     if (b.up >= 0) {
-      Unit& up = plan->units[b.up];
-      fwd_run(&up.conv, cur, W(up.iw), ws + up.y, nullptr, s);
-      bn(up, nullptr);
-      shortcut = ws + up.z;
+      conv_bn(plan->units[b.up], cur, nullptr);
+      shortcut = ws + plan->units[b.up].z;
     }
-    fwd_run(&u1.conv, cur, W(u1.iw), ws + u1.y, nullptr, s);
-    bn(u1, nullptr);
-    fwd_run(&u2.conv, ws + u1.z, W(u2.iw), ws + u2.y, nullptr, s);
-    bn(u2, nullptr);
-    fwd_run(&u3.conv, ws + u2.z, W(u3.iw), ws + u3.y, nullptr, s);
-    bn(u3, shortcut);
+    conv_bn(u1, cur, nullptr);
+    conv_bn(u2, ws + u1.z, nullptr);
+    conv_bn(u3, ws + u2.z, shortcut);
     cur = ws + u3.z;
   }
   const int HW = plan->final_hw * plan->final_hw;

@@ -1,5 +1,5 @@
 // Entry points of the kernel files that the whole-step driver calls directly
-// (below the argument checking of the C ABI), so that padded / transposed
+// (below the argument checking of the C ABI), so that padded
 // operands and scratch buffers are shared across the passes of one step.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -27,8 +27,16 @@ PartialRows fwd_partial_rows(const rn50_conv_desc* d);    // tiles of the forwar
 PartialRows dgrad_partial_rows(const rn50_conv_desc* d);  // tiles of the data gradient
 int64_t dgrad_partial_rows_bound(const rn50_conv_desc* d);  // most rows any tile choice gives (tiles of >= 64 pixels)
 // bn_partial (null: none): float[3][Cout][num] = shift, sum(y - shift), sum((y - shift)^2) per tile.
+// An inference-mode BN layer applied in a convolution's output stage: [relu](gamma*(product - mean)/sqrt(var + eps) +
+// beta [+ residual]); residual: [M][Cout] or null.
+struct BnAffine {
+  const float *gamma, *beta, *mean, *var;
+  float eps;
+  int relu;
+  const void* residual;
+};
 void stem_fwd_padded(const rn50_conv_desc* d, const void* xp, const void* w, void* wp, void* y, float* bn_partial,
-                     hipStream_t s);
+                     hipStream_t s, const BnAffine* affine = nullptr);
 // A BN+ReLU layer applied to a convolution's input on the fly (1x1, stride 1 convolutions only): its parameters
 // and saved statistics, float[Cin] each.
 // The BN sums that a convolution's output stage leaves (one row per row tile) are stored ROW-major when there are
@@ -50,7 +58,7 @@ struct BnIn {
   const float *gamma, *beta, *mean, *rstd;
 };
 void fwd_run(const rn50_conv_desc* d, const void* x, const void* w, void* y, float* bn_partial, hipStream_t s,
-             const char* tag = "conv_fwd", const BnIn* in = nullptr);
+             const char* tag = "conv_fwd", const BnIn* in = nullptr, const BnAffine* affine = nullptr);
 // The BN layer (with ReLU) whose output gradient a data gradient produces: x is that
 // layer's input [N*H*W][Cin]; partial receives float[2][Cin][num] = sum(g), sum(g * xhat) per tile.
 // addend (or null): a second branch of the gradient, [N*H*W][Cin], added to the data gradient before it
@@ -65,15 +73,8 @@ struct BnBwdSums {
   const uint8_t* relu_mask = nullptr;
   const uint8_t* addend_mask = nullptr;
 };
-size_t dgrad_wt_bytes(const rn50_conv_desc* d);
-void dgrad_transpose_weights(const rn50_conv_desc* d, const void* w, void* wT, hipStream_t s);
-void dgrad_run(const rn50_conv_desc* d, const void* dy, const void* wT, void* dx, const BnBwdSums* bn, hipStream_t s);
-struct TransposeEntry {
-  int64_t offset;  // element offset of the tensor in both arenas
-  int K, taps, C;
-};
-void transpose_batch_run(const std::vector<TransposeEntry>& list, int dtype, const void* src_arena, void* dst_arena,
-                         hipStream_t s);
+void dgrad_run(const rn50_conv_desc* d, const void* dy, const void* w, void* dx, const BnBwdSums* bn, hipStream_t s,
+               const char* tag = "conv_dgrad");
 size_t wgrad_partial_bytes(const rn50_conv_desc* d);
 void wgrad_run(const rn50_conv_desc* d, const void* x_or_xp, const void* dy, float* dw, void* scratch, hipStream_t s,
                const BnIn* in = nullptr);
@@ -95,7 +96,15 @@ void bn_infer_run(const rn50_bn_desc* d, const void* x, const float* gamma, cons
                   const float* running_mean, const float* running_var, const void* residual, void* y,
                   float* rstd_scratch, hipStream_t s);
 
-// head.hip: the classifier's parameter gradients alone (fc_bwd with dW = db = null leaves them out)
+// head.hip: the pieces of xent_fwd_bwd and fc_bwd that a step runs on different streams.
+// The rows of the loss: row_loss, dlogits and (bf16, or null) the copy of dlogits rounded to the storage type.
+void xent_rows(int N, int K, const float* logits, const int32_t* labels, float label_smoothing, float grad_scale,
+               float* row_loss, float* dlogits, void* dlogits_t, int dtype, hipStream_t s);
+void loss_mean(int N, const float* row_loss, float* loss_out, hipStream_t s);
+// The classifier's data gradient from dlogits in the storage type (Cin and K multiples of the 16-byte vector).
+bool fc_mfma_ok(int Cin, int K, int dtype);
+void fc_bwd_da(int N, int Cin, int K, int dtype, const void* W, const void* dlogits_t, void* da, hipStream_t s);
+// The classifier's parameter gradients alone (fc_bwd with dW = db = null leaves them out).
 void fc_bwd_params(int N, int Cin, int K, int dtype, const void* a, const float* dlogits, float* dW, float* db,
                    hipStream_t s);
 

@@ -39,7 +39,7 @@ MEASURED_TRAFFIC_BYTES_PER_LAUNCH = {
 
 # Kernel classes of the step: (class, launch tags whose durations it sums, tag whose launches it is counted in).
 # bn_finalize / bn_bwd_finalize (the passes from per-tile sums to per-channel statistics) and "other" (stem
-# padding, weight transposition, pooling, classifier, cross-entropy) move next to nothing: they are listed with
+# padding, pooling, classifier, cross-entropy) move next to nothing: they are listed with
 # their time and no bound, so that the classes add up to all of the step's tagged kernel time.
 CLASSES = [
     ("conv_fwd", ("conv_fwd",)), ("conv_dgrad", ("conv_dgrad",)), ("conv_wgrad", ("conv_wgrad", "splitk_reduce", "stem_unpad")),
