@@ -34,6 +34,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "conv_internal.h"
 #include "step_internal.h"
 
 namespace rn50 {
@@ -52,14 +53,6 @@ template <> struct Mma<float> {  // float: four 32x32x2 MFMAs (k pairs {j, 4+j} 
     for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.f[j], b.f[j], acc, 0, 0, 0);
   }
 };
-
-// Workgroups are dealt to the 8 XCDs round-robin; renumber them so that consecutive logical ids
-// (which share rows of the activation tile) run on the same XCD and meet in its L2.
-__device__ __forceinline__ int xcd_remap(int id, int n) {
-  const int xcd = id & 7, idx = id >> 3;
-  const int q = n >> 3, rem = n & 7;
-  return xcd < rem ? xcd * (q + 1) + idx : rem * (q + 1) + (xcd - rem) * q + idx;
-}
 
 // ------------------------------------------------- forward / dgrad implicit GEMM
 struct IgemmArgs {
@@ -117,138 +110,6 @@ struct IgemmArgs {
   float aff_eps;
   int aff_relu;
 };
-
-// relu(bn(x)) of one 16-byte vector with the arithmetic of the stand-alone BN pass (bn_affine, one rounding to
-// the storage type), so that a convolution reading it sees bit for bit the tensor that pass would have stored.
-template <typename T>
-__device__ __forceinline__ Vec16 bn_relu_vector(const Vec16& v, const float* scale, const float* bias) {
-  constexpr int V = 16 / sizeof(T);
-  float f[V];
-  Elem<T>::unpack(v, f);
-#pragma unroll
-  for (int j = 0; j < V; ++j) f[j] = fmaxf(bn_affine(f[j], scale[j], bias[j]), 0.f);
-  Vec16 o;
-  Elem<T>::pack(f, o);
-  return o;
-}
-// Barrier behind LDS writes of this wave (s_barrier alone does not wait for them), leaving vector-memory loads in flight.
-__device__ __forceinline__ void lds_writes_then_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt, expcnt: no wait
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-constexpr uint32_t kOob = 0x80000000u;  // buffer offset beyond every tensor: the load returns zeros
-
-// Raw buffer descriptor over a tensor: loads whose offset is >= bytes return 0, which is how padding,
-// tile tails and ragged channel counts are zero-filled without any per-element masking.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, static_cast<int>(bytes), 0x00020000);
-}
-__device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t voffset, uint32_t soffset) {
-  typedef int v4i __attribute__((ext_vector_type(4)));
-  const v4i v = __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(voffset), static_cast<int>(soffset), 0);
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-// The same load with LDS as its destination (buffer_load_dwordx4 ... lds): lane l of the wave writes its 16
-// bytes to LDS address lds_addr + 16*l (lds_addr uniform, taken from M0), so one instruction fills 1 KB; lanes
-// whose offset is out of range write zeros.  Nothing passes through registers; the transfer is counted by
-// vmcnt like any other vector-memory load.  Written as assembly on purpose: the compiler would make every
-// later LDS read wait for ALL outstanding loads of this kind (it cannot tell the ring buffers apart), which
-// is the prefetch distance this kernel lives on; the waits are placed by hand (wait_loads_then_barrier).
-typedef int rsrc_words __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ rsrc_words make_rsrc_words(const void* p, uint32_t bytes) {
-  const uint64_t addr = reinterpret_cast<uint64_t>(p);
-  rsrc_words r;
-  r.x = static_cast<int>(addr);
-  r.y = static_cast<int>((addr >> 32) & 0xffffu);  // stride 0: a raw buffer
-  r.z = static_cast<int>(bytes);
-  r.w = 0x00020000;
-  return r;
-}
-__device__ __forceinline__ void buffer_load16_to_lds(rsrc_words r, uint32_t lds_addr, uint32_t voffset, uint32_t soffset) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(lds_addr), "v"(voffset), "s"(r), "s"(soffset)
-               : "memory");  // (m0 is reserved: the compiler keeps nothing in it across statements)
-}
-// Wait until at most N of this wave's vector-memory loads are outstanding, then the workgroup barrier, without
-// the full memory fence of __syncthreads() (which would also wait for the loads of the chunks still in flight).
-template <int N>
-__device__ __forceinline__ void wait_loads_then_barrier() {
-  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-  // s_waitcnt immediate on gfx9: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] << 14; 7 / 15 = no wait
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-// Top of iteration kc of a ring of NSTAGE chunk buffers (loads NSTAGE-1 chunks ahead, NL load instructions per
-// thread and chunk): wait until this wave's loads of chunk kc have landed -- those of the chunks behind it that
-// have been issued, at most NSTAGE-2 of them and none past the last chunk, may stay in flight -- then the barrier.
-template <int NSTAGE, int NL>
-__device__ __forceinline__ void ring_wait(int chunks_after) {
-  static_assert(NSTAGE >= 2 && NSTAGE <= 6 && NL * (NSTAGE - 2) < 64, "ring depth");
-  const int ahead = chunks_after < NSTAGE - 2 ? chunks_after : NSTAGE - 2;
-  if (NSTAGE >= 6 && ahead == 4) wait_loads_then_barrier<(NSTAGE >= 6 ? 4 : 0) * NL>();
-  else if (NSTAGE >= 5 && ahead == 3) wait_loads_then_barrier<(NSTAGE >= 5 ? 3 : 0) * NL>();
-  else if (NSTAGE >= 4 && ahead == 2) wait_loads_then_barrier<(NSTAGE >= 4 ? 2 : 0) * NL>();
-  else if (NSTAGE >= 3 && ahead == 1) wait_loads_then_barrier<(NSTAGE >= 3 ? 1 : 0) * NL>();
-  else wait_loads_then_barrier<0>();
-}
-
-// LDS tiles of the weight gradient are [k row][column] with rows of RBY = 16 * (columns per 16 bytes ...) bytes,
-// filled by LDS-destination loads (RBY/16 lanes per row).  The 16-byte slots of a row are stored permuted,
-// slot s of row r at s ^ wgrad_swz(r), so that the fragment reads below touch every bank once:
-//   bf16, 128-byte rows: a transposing read's 32 lanes take 64 bytes of 4 consecutive rows -- rows two apart
-//                        share their banks, so they swap halves;
-//   bf16, 256-byte rows: the same 4 rows all start at bank 0 -- each is rotated by a different 64 bytes;
-//   float:               lanes 32-63 read the row 4 below lanes 0-31 -- it is shifted by 128 bytes.
-template <typename T, int RBY>
-__device__ __forceinline__ int wgrad_swz(int row) {
-  if (sizeof(T) == 4) return ((row >> 2) & 1) << 3;
-  return RBY == 128 ? ((row >> 1) & 1) << 2 : (row & 3) << 2;
-}
-// Byte offset, inside a tile, of this lane's first read for the MFMA operand "32 columns from col0 x one k step"
-// at k step 0; step kk is KSTEP * kk rows further down.
-template <typename T, int RBY>
-__device__ __forceinline__ int wgrad_frag_base(int lane, int col0) {
-  if (sizeof(T) == 2) {
-    // ds_read_b64_tr_b16: within 16 lanes, lane t supplies the address of row t/4, columns 4*(t%4)..+3 and
-    // receives column t of rows 0..3.  Two reads (rows +0 and +4) give 8 k values of column lane%32.
-    const int g = lane >> 4, t = lane & 15;
-    const int krow = 8 * (g >> 1) + (t >> 2);
-    const int cb = 2 * (col0 + 16 * (g & 1) + 4 * (t & 3));
-    return krow * RBY + (((cb >> 4) ^ wgrad_swz<T, RBY>(krow)) << 4) + (cb & 15);
-  }
-  const int krow = (lane >> 5) * 4;  // + j, j = 0..3: the permutation only looks at bit 2
-  const int cb = 4 * (col0 + (lane & 31));
-  return krow * RBY + (((cb >> 4) ^ wgrad_swz<T, RBY>(krow)) << 4) + (cb & 15);
-}
-template <typename T, int RBY>
-__device__ __forceinline__ Vec16 wgrad_read_frag(const unsigned char* tile, int base, int kk) {
-  Vec16 v;
-  if constexpr (sizeof(T) == 2) {
-    typedef short s16x4 __attribute__((ext_vector_type(4)));
-    typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-    const unsigned char* p0 = tile + base + kk * 16 * RBY;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0 + 4 * RBY));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      v.h[j] = static_cast<uint16_t>(lo[j]);
-      v.h[4 + j] = static_cast<uint16_t>(hi[j]);
-    }
-  } else {
-    const unsigned char* p = tile + base + kk * 8 * RBY;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v.f[j] = *reinterpret_cast<const float*>(p + j * RBY);
-  }
-  return v;
-}
-
 
 // MODE 0: forward gather  ih = p*stride - pad + r.
 // MODE 1: data-gradient gather  ih = (p + pad - r)/stride when divisible (stride 1 or 2).  With stride 2
@@ -913,395 +774,6 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
   if (MODE == 0 && tid < BN && n0 + tid < a.Ncols) a.partial[static_cast<int64_t>(n0 + tid) * nrows + mt] = kshift;
 }
 
-// ------------------------------------------------------------ weight gradient
-struct WgradArgs {
-  const void* x;   // gathered activation tensor (as in IgemmArgs, forward gather)
-  const void* dy;  // [M][Cout]
-  float* out;      // dw [Cout][Ktot], or split partials
-  uint32_t x_bytes, dy_bytes;
-  int M, Cout, Ktot;
-  int H, W, P, Q, PS, Cg, R, S, stride, pad;
-  int ctiles;          // column tiles per tap
-  int tiles_per_split; // taps * ctiles * output-channel tiles
-  int rows_per_split;  // multiple of the K chunk
-  int linear;          // 1x1, stride 1, pad 0: gathered row m is pixel m
-  int pair;            // stem in bf16: a tap is two filter rows (column pieces 0-3: row 2r, 4-7: row 2r+1)
-  int64_t split_stride;
-  FastDiv divQ, divP;
-  FastDiv div_tps, div_tiles_x, div_ctiles, div_S;  // the tile decode's divisors
-  // BNIN kernels (1x1, stride 1): x is the INPUT of a BN+ReLU layer whose output is the convolution's input;
-  // relu(x*scale + bias) is applied to the x tile in LDS (as in igemm_kernel).  Null: x is used as is.
-  const float *in_gamma, *in_beta, *in_mean, *in_rstd;
-  // wgrad3x3_kernel: the padded pixel index space, Gpad = N * (H + 1) * (W + 1) positions
-  int Gpad;
-  FastDiv div_img, div_w1;  // by (H + 1) * (W + 1) and by W + 1
-  int whatif;  // tuning builds only: 1 = leave out the stores of the result, 2 = leave out the MFMAs (what-if timings)
-};
-
-template <typename T> struct WgradCfg;
-template <> struct WgradCfg<uint16_t> { static constexpr int BKM = 64; };
-template <> struct WgradCfg<float> { static constexpr int BKM = 32; };
-
-// One workgroup: the BMO x BC tile (output channels x input channels of one tap) of one split of the pixel
-// range.  2 x 2 waves; per 64-row (32 in float) chunk of pixels the dy and x rows go straight into LDS
-// (a ring of chunk buffers, one barrier per chunk, as in igemm_kernel) and are read back transposed.
-// NSTAGE: chunk buffers in the ring.  Both operands stream past a workgroup exactly once, from memory that is cold
-// inside a training step, so a workgroup's rate is (bytes in flight) / (memory latency): the launch picks the
-// deepest ring that the workgroups sharing a compute unit have LDS for (wgrad_stages).
-template <typename T, int BMO, int BC, int NSTAGE, bool BNIN = false>
-__global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
-  constexpr int V = 16 / sizeof(T);
-  constexpr int BKM = WgradCfg<T>::BKM;
-  constexpr int KSTEP = sizeof(T) == 2 ? 16 : 8;
-  constexpr int RA = BMO * sizeof(T), RB = BC * sizeof(T);  // row bytes of the two tiles
-  constexpr int LA = RA / 16, LB = RB / 16;                  // lanes (16-byte pieces) per row
-  constexpr int NA = BKM * LA / 256, NB = BKM * LB / 256;    // load instructions per thread and chunk
-  constexpr int NL = NA + NB;
-  constexpr int STAGE = BKM * (RA + RB);
-  constexpr int TM = BMO / 64, TN = BC / 64;  // 2x2 waves
-  static_assert(NA >= 1 && NB >= 1 && 256 % LA == 0 && 256 % LB == 0, "tile shape");
-  extern __shared__ __align__(16) unsigned char smem[];
-
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wm = wave & 1, wn = wave >> 1;
-  // Logical id = (split, output-channel tile, tap, column tile), the last fastest.  All tiles of one
-  // split read the same rows of x and dy, so the renumbering keeps them on one XCD and in its L2.
-  const int lid = xcd_remap(blockIdx.x, gridDim.x);
-  const int split = static_cast<int>(fdiv(static_cast<uint32_t>(lid), a.div_tps)), tile = lid - split * a.tiles_per_split;
-  const int tiles_x = a.R * a.S * a.ctiles;
-  const int ko_tile = static_cast<int>(fdiv(static_cast<uint32_t>(tile), a.div_tiles_x)), tx = tile - ko_tile * tiles_x;
-  const int tap = static_cast<int>(fdiv(static_cast<uint32_t>(tx), a.div_ctiles)), c0 = (tx - tap * a.ctiles) * BC;
-  const int r = static_cast<int>(fdiv(static_cast<uint32_t>(tap), a.div_S)), s = tap - r * a.S;
-  const int ko0 = ko_tile * BMO;
-  const int row_begin = split * a.rows_per_split;
-  const int row_end = min(row_begin + a.rows_per_split, a.M);
-  const rsrc_words rsX = make_rsrc_words(a.x, a.x_bytes), rsD = make_rsrc_words(a.dy, a.dy_bytes);
-
-  // this thread's rows of a chunk and the 16-byte piece of them it fetches (the slot's permuted partner)
-  const int rowa = tid / LA, rowb = tid / LB;
-  const int pa = (tid % LA) ^ wgrad_swz<T, RA>(rowa), pb = (tid % LB) ^ wgrad_swz<T, RB>(rowb);
-  const bool a_col_ok = ko0 + pa * V < a.Cout;
-  const bool b_col_ok = c0 + pb * V < a.Cg;
-  // byte offsets of this thread's first rows at m = row_begin; later chunks add a scalar offset
-  uint32_t a_off[NA], b_off[NB];
-#pragma unroll
-  for (int i = 0; i < NA; ++i)
-    a_off[i] = a_col_ok ? static_cast<uint32_t>((row_begin + rowa + i * (256 / LA)) * a.Cout + ko0 + pa * V) * sizeof(T) : kOob;
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-    b_off[i] = b_col_ok ? static_cast<uint32_t>((row_begin + rowb + i * (256 / LB)) * a.PS + c0 + pb * V) * sizeof(T) : kOob;
-
-  typedef __attribute__((address_space(3))) unsigned char* lds_byte_ptr;
-  const uint32_t wave_dst = __builtin_amdgcn_readfirstlane(
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_byte_ptr)smem)) + static_cast<uint32_t>(wave) * 1024u);
-  int cur = 0;  // chunk index of the load cursor
-  // Rows past row_end load zeros (no memory access): the last chunk of a split needs no special case.
-  auto load_chunk = [&](int stage) __attribute__((always_inline)) {
-    const int m_base = row_begin + cur * BKM;
-    const int left = row_end - m_base;  // rows of this chunk that belong to the split
-    const uint32_t sa = wave_dst + static_cast<uint32_t>(stage) * STAGE, sb = sa + BKM * RA;
-    const uint32_t soA = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(cur) * static_cast<uint32_t>(BKM * a.Cout) * sizeof(T));
-#pragma unroll
-    for (int i = 0; i < NA; ++i)
-      buffer_load16_to_lds(rsD, sa + i * 4096, (rowa + i * (256 / LA) < left) ? a_off[i] : kOob, soA);
-    if (a.linear) {
-      const uint32_t soB = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(cur) * static_cast<uint32_t>(BKM * a.PS) * sizeof(T));
-#pragma unroll
-      for (int i = 0; i < NB; ++i)
-        buffer_load16_to_lds(rsX, sb + i * 4096, (rowb + i * (256 / LB) < left) ? b_off[i] : kOob, soB);
-    } else {
-#pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const int lr = rowb + i * (256 / LB);
-        bool ok = b_col_ok && lr < left;
-        const uint32_t mm = ok ? static_cast<uint32_t>(m_base + lr) : 0u;
-        const uint32_t t = fdiv(mm, a.divQ);
-        const int q = static_cast<int>(mm - t * a.Q);
-        const uint32_t n = fdiv(t, a.divP);
-        const int p = static_cast<int>(t - n * a.P);
-        const int ih = p * a.stride - a.pad + (a.pair ? 2 * r + (pb >> 2) : r), iw = q * a.stride - a.pad + s;
-        ok = ok && static_cast<unsigned>(ih) < static_cast<unsigned>(a.H) &&
-             static_cast<unsigned>(iw) < static_cast<unsigned>(a.W);
-        const int pcol = a.pair ? (pb & 3) * V : c0 + pb * V;
-        const uint32_t off = static_cast<uint32_t>(((static_cast<int>(n) * a.H + ih) * a.W + iw) * a.PS + pcol) * sizeof(T);
-        buffer_load16_to_lds(rsX, sb + i * 4096, ok ? off : kOob, 0u);
-      }
-    }
-    ++cur;
-  };
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  int fa_base[TM], fb_base[TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) fa_base[i] = wgrad_frag_base<T, RA>(lane, wm * (BMO / 2) + i * 32);
-#pragma unroll
-  for (int j = 0; j < TN; ++j) fb_base[j] = BKM * RA + wgrad_frag_base<T, RB>(lane, wn * (BC / 2) + j * 32);
-  const int nchunks = (row_end - row_begin + BKM - 1) / BKM;
-  constexpr int KK = BKM / KSTEP;
-  constexpr int AHEAD = (TM + TN <= 3) ? KK : 1;  // k steps whose fragments are read before the first MFMA
-  auto compute = [&](int stage) __attribute__((always_inline)) {
-    const unsigned char* st = smem + stage * STAGE;
-    Vec16 fa[KK][TM], fb[KK][TN];
-    auto read_frags = [&](int kk) __attribute__((always_inline)) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i) fa[kk][i] = wgrad_read_frag<T, RA>(st, fa_base[i], kk);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) fb[kk][j] = wgrad_read_frag<T, RB>(st, fb_base[j], kk);
-    };
-#pragma unroll
-    for (int kk = 0; kk < AHEAD; ++kk) read_frags(kk);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      if (kk + AHEAD < KK) {
-        read_frags(kk + AHEAD);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#ifdef RN50_TUNING
-      if (a.whatif == 2) {  // the fragments are still read; one add keeps them alive
-        acc[0][0][0] += fa[kk][0].f[0] + fb[kk][0].f[0];
-        continue;
-      }
-#endif
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) Mma<T>::run(fa[kk][i], fb[kk][j], acc[i][j]);  // D[ko][c]
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  // BNIN: this thread's piece of every x row is the same 16 bytes of channels for the whole launch
-  float in_scale[V], in_bias[V];
-  if constexpr (BNIN) {
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      const int c = min(c0 + pb * V + j, a.Cg - 1);
-      bn_coeffs(a.in_gamma[c], a.in_beta[c], a.in_mean[c], a.in_rstd[c], &in_scale[j], &in_bias[j]);
-    }
-  }
-  // the ring of igemm_kernel: loads NSTAGE-1 chunks ahead, one barrier per chunk
-#pragma unroll
-  for (int c = 0; c < NSTAGE - 1; ++c)
-    if (c < nchunks) load_chunk(c);
-  int stage = 0;
-  for (int kc = 0; kc < nchunks; ++kc) {
-    ring_wait<NSTAGE, NL>(nchunks - 1 - kc);
-    if (kc + NSTAGE - 1 < nchunks) load_chunk(stage >= 1 ? stage - 1 : NSTAGE - 1);
-    if constexpr (BNIN) {
-      // every thread transforms, in place, the x vectors of chunk kc that its own loads brought.  Rows past the
-      // split's end (loaded as zeros) become relu(bias); their dy rows are zeros, so they add nothing.
-#pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        uint4* p = reinterpret_cast<uint4*>(smem + stage * STAGE + BKM * RA + i * 4096 + tid * 16);
-        Vec16 v;
-        v.u = *p;
-        *p = bn_relu_vector<T>(v, in_scale, in_bias).u;
-      }
-      lds_writes_then_barrier();
-    }
-    compute(stage);
-    stage = stage == NSTAGE - 1 ? 0 : stage + 1;
-  }
-
-  // acc[i][j][v]: ko = i*32 + (v/4)*8 + (lane/32)*4 + v%4, c = j*32 + lane%32
-  float* out = a.out + static_cast<int64_t>(split) * a.split_stride;
-#ifdef RN50_TUNING
-  if (a.whatif == 1 && acc[0][0][0] != 12345.678f) return;
-#endif
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int c = c0 + wn * (BC / 2) + j * 32 + (lane & 31);
-      if (c >= a.Cg) continue;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int ko = ko0 + wm * (BMO / 2) + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-        if (ko < a.Cout) out[static_cast<int64_t>(ko) * a.Ktot + tap * a.Cg + c] = acc[i][j][v];
-      }
-    }
-}
-
-// Weight gradient of a 3x3 / stride 1 / padding 1 layer, bf16, all nine taps in one workgroup.
-// The reduction index is a PADDED pixel position: every image row gets one more column and every image one more
-// row, whose dy and x are zero (never stored: the loads of those positions carry an out-of-range offset and
-// write zeros).  In that index space tap (r, s) of position k reads x at k + (r-1)(W+1) + (s-1), a constant shift,
-// and every tap that falls off the image lands on a zero position -- so there is nothing to mask: per chunk of 64
-// positions the workgroup brings one dy tile [64][64 output channels] and one x run [64 + 2W + 4][64 input
-// channels] into LDS and multiplies the dy tile with nine row-shifted windows of the run (transposing reads, the
-// slot permutation follows the shifted row) into nine 64x64 accumulator tiles.  Against one gathered tile per tap
-// that is 9x fewer dy loads and 9 / (1 + (2W+4)/64) fewer x loads; the reduction grows by (1+1/H)(1+1/W).
-// NBX: load passes (32 rows each) of the run; NSTAGE: chunk buffers in the ring (as in wgrad_kernel).
-template <int NBX, int NSTAGE>
-__global__ __launch_bounds__(256) void wgrad3x3_kernel(const WgradArgs a) {
-  typedef uint16_t T;
-  constexpr int V = 8, BKM = 64, RBY = 128, KK = 4;
-  constexpr int NA = 2, NL = NA + NBX;
-  constexpr int STAGE = BKM * RBY + NBX * 4096;
-  extern __shared__ __align__(16) unsigned char smem[];
-
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wm = wave & 1, wn = wave >> 1;
-  // logical id = (split, output-channel tile, input-channel tile): the tiles of a split share its rows
-  const int lid = xcd_remap(blockIdx.x, gridDim.x);
-  const int split = static_cast<int>(fdiv(static_cast<uint32_t>(lid), a.div_tps)), tile = lid - split * a.tiles_per_split;
-  const int ko_tile = static_cast<int>(fdiv(static_cast<uint32_t>(tile), a.div_ctiles));
-  const int c0 = (tile - ko_tile * a.ctiles) * 64, ko0 = ko_tile * 64;
-  const int row_begin = split * a.rows_per_split;
-  const int row_end = min(row_begin + a.rows_per_split, a.Gpad);
-  const rsrc_words rsX = make_rsrc_words(a.x, a.x_bytes), rsD = make_rsrc_words(a.dy, a.dy_bytes);
-
-  const int row = tid >> 3;                                  // this thread's row in every 32-row load pass
-  const int pc = (tid & 7) ^ wgrad_swz<T, RBY>(row);        // the 16-byte piece of its rows it fetches
-  const bool a_col_ok = ko0 + pc * V < a.Cout, b_col_ok = c0 + pc * V < a.Cg;
-  const int W1 = a.W + 1, IMG = (a.H + 1) * W1;
-  // padded position -> pixel index; ok: the position is a real pixel
-  auto pixel_of = [&](int g, bool* ok) __attribute__((always_inline)) {
-    const bool in = static_cast<unsigned>(g) < static_cast<unsigned>(a.Gpad);
-    const uint32_t gg = in ? static_cast<uint32_t>(g) : 0u;
-    const uint32_t n = fdiv(gg, a.div_img), rem = gg - n * static_cast<uint32_t>(IMG);
-    const uint32_t y = fdiv(rem, a.div_w1), x = rem - y * static_cast<uint32_t>(W1);
-    *ok = in && y < static_cast<uint32_t>(a.H) && x < static_cast<uint32_t>(a.W);
-    return static_cast<int>((n * a.H + y) * a.W + x);
-  };
-  typedef __attribute__((address_space(3))) unsigned char* lds_byte_ptr;
-  const uint32_t wave_dst = __builtin_amdgcn_readfirstlane(
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_byte_ptr)smem)) + static_cast<uint32_t>(wave) * 1024u);
-  int cur = 0;
-  auto load_chunk = [&](int stage) __attribute__((always_inline)) {
-    const int g0 = row_begin + cur * BKM;
-    const uint32_t sa = wave_dst + static_cast<uint32_t>(stage) * STAGE, sb = sa + BKM * RBY;
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {  // dy: positions of this split only (the others belong to other workgroups)
-      const int g = g0 + row + 32 * i;
-      bool ok;
-      const int pix = pixel_of(g, &ok);
-      ok = ok && a_col_ok && g < row_end;
-      buffer_load16_to_lds(rsD, sa + i * 4096, ok ? static_cast<uint32_t>(pix * a.Cout + ko0 + pc * V) * 2u : kOob, 0u);
-    }
-#pragma unroll
-    for (int i = 0; i < NBX; ++i) {  // x: the run starts W + 2 positions before the chunk
-      const int g = g0 - (a.W + 2) + row + 32 * i;
-      bool ok;
-      const int pix = pixel_of(g, &ok);
-      ok = ok && b_col_ok;
-      buffer_load16_to_lds(rsX, sb + i * 4096, ok ? static_cast<uint32_t>(pix * a.PS + c0 + pc * V) * 2u : kOob, 0u);
-    }
-    ++cur;
-  };
-
-  f32x16 acc[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
-
-  // Fragment addresses.  dy: as in wgrad_kernel.  x: the same transposing read r*(W+1) + s rows further down the
-  // run; the slot permutation of a row depends on bit 1 of the row, so it is taken from the shifted row (the
-  // reads' +4 and +16*kk rows leave that bit alone).
-  const int fa_base = wgrad_frag_base<T, RBY>(lane, wm * 32);
-  int fb_base[9];
-  {
-    const int g4 = lane >> 4, t = lane & 15;
-    const int krow = 8 * (g4 >> 1) + (t >> 2);
-    const int cb = 2 * (wn * 32 + 16 * (g4 & 1) + 4 * (t & 3));
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const int kr = krow + (tap / 3) * W1 + (tap % 3);
-      fb_base[tap] = BKM * RBY + kr * RBY + (((cb >> 4) ^ wgrad_swz<T, RBY>(kr)) << 4) + (cb & 15);
-    }
-  }
-  const int nchunks = (row_end - row_begin + BKM - 1) / BKM;
-  auto compute = [&](int stage) __attribute__((always_inline)) {
-    const unsigned char* st = smem + stage * STAGE;
-    Vec16 fa[KK], fb[2][KK];
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) fa[kk] = wgrad_read_frag<T, RBY>(st, fa_base, kk);
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) fb[0][kk] = wgrad_read_frag<T, RBY>(st, fb_base[0], kk);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      if (tap + 1 < 9) {
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) fb[(tap + 1) & 1][kk] = wgrad_read_frag<T, RBY>(st, fb_base[tap + 1], kk);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) Mma<T>::run(fa[kk], fb[tap & 1][kk], acc[tap]);  // D[ko][c]
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-#pragma unroll
-  for (int c = 0; c < NSTAGE - 1; ++c)
-    if (c < nchunks) load_chunk(c);
-  int stage = 0;
-  for (int kc = 0; kc < nchunks; ++kc) {
-    ring_wait<NSTAGE, NL>(nchunks - 1 - kc);
-    if (kc + NSTAGE - 1 < nchunks) load_chunk(stage >= 1 ? stage - 1 : NSTAGE - 1);
-    compute(stage);
-    stage = stage == NSTAGE - 1 ? 0 : stage + 1;
-  }
-
-  // acc[tap][v]: ko = (v/4)*8 + (lane/32)*4 + v%4, c = lane%32 of this wave's 32x32 block
-  float* out = a.out + static_cast<int64_t>(split) * a.split_stride;
-  const int c = c0 + wn * 32 + (lane & 31);
-  if (c < a.Cg) {
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int ko = ko0 + wm * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-        if (ko < a.Cout) out[static_cast<int64_t>(ko) * a.Ktot + tap * a.Cg + c] = acc[tap][v];
-      }
-  }
-}
-
-// dw[i] = sum_s partial[s][i].  A workgroup owns 64 float4 outputs; its four waves each sum every
-// fourth split (ascending) and the four sums are added in wave order: a fixed order.
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, int splits,
-                                                            int64_t n, float* __restrict__ out) {
-  __shared__ float4 red[4][64];
-  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int64_t i = (static_cast<int64_t>(blockIdx.x) * 64 + lane) * 4;
-  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (i + 4 <= n) {
-#pragma unroll 4
-    for (int k = grp; k < splits; k += 4) {
-      const float4 v = *reinterpret_cast<const float4*>(partial + k * n + i);
-      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-    }
-  } else if (i < n) {
-    for (int k = grp; k < splits; k += 4) {
-      const float* p = partial + k * n + i;
-      s.x += p[0];
-      if (i + 1 < n) s.y += p[1];
-      if (i + 2 < n) s.z += p[2];
-    }
-  }
-  red[grp][lane] = s;
-  __syncthreads();
-  if (grp == 0 && i < n) {
-    const float4 a = red[0][lane], b = red[1][lane], c = red[2][lane], d = red[3][lane];
-    const float4 r = make_float4((a.x + b.x) + (c.x + d.x), (a.y + b.y) + (c.y + d.y), (a.z + b.z) + (c.z + d.z),
-                                 (a.w + b.w) + (c.w + d.w));
-    if (i + 4 <= n) {
-      *reinterpret_cast<float4*>(out + i) = r;
-    } else {
-      out[i] = r.x;
-      if (i + 1 < n) out[i + 1] = r.y;
-      if (i + 2 < n) out[i + 2] = r.z;
-    }
-  }
-}
-
 // ------------------------------------------------------- layout helper kernels
 // Stem input: x [N][H][W][3] -> xp [N][H+6][Wp][4], zero border (3 pixels each side, Wp - W - 3 on the
 // right) and zero 4th channel, so that a 7-tap filter row is 8 pixels = 32 contiguous elements.
@@ -1323,7 +795,6 @@ __global__ __launch_bounds__(256) void stem_pad_input_kernel(const T* __restrict
   d[0] = v[0]; d[1] = v[1]; d[2] = v[2]; d[3] = v[3];
 }
 // Stem weights: w [K][7][7][3] -> wp [K][8][8][4] with zeros in filter row 7, tap column 7 and channel 3.
-constexpr int kStemK = 256;  // padded reduction length of the stem: 8 filter rows x 8 taps x 4 channels
 template <typename T>
 __global__ __launch_bounds__(256) void stem_pad_weight_kernel(const T* __restrict__ w, T* __restrict__ wp, int K) {
   const int i = blockIdx.x * 256 + threadIdx.x;
@@ -1331,20 +802,7 @@ __global__ __launch_bounds__(256) void stem_pad_weight_kernel(const T* __restric
   const int c = i & 3, s = (i >> 2) & 7, r = (i >> 5) & 7, k = i >> 8;
   wp[i] = (c < 3 && s < 7 && r < 7) ? w[((k * 7 + r) * 7 + s) * 3 + c] : static_cast<T>(0);
 }
-// dw [K][7][7][3] <- dwp [K][8][8][4]
-__global__ __launch_bounds__(256) void stem_unpad_dw_kernel(const float* __restrict__ dwp, float* __restrict__ dw, int K) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= K * 147) return;
-  const int c = i % 3, s = (i / 3) % 7, r = (i / 21) % 7, k = i / 147;
-  dw[i] = dwp[((k * 8 + r) * 8 + s) * 4 + c];
-}
-
 // ------------------------------------------------------------------ host side
-template <typename K>
-static void allow_big_lds(K kernel, int bytes) {
-  if (bytes > 48 * 1024) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-}
-
 template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN, bool BNIN = false>
 static void launch_igemm_mode(IgemmArgs a, const char* tag, int64_t grid, hipStream_t s) {
   constexpr int NT = 64 * WM * WN;
@@ -1504,132 +962,6 @@ static void launch_igemm(const IgemmArgs& a, const char* tag, hipStream_t s) {
 #undef X
 }
 
-struct WgradPlan {
-  int bmo, bc, ctiles, splits, rows_per_split;
-};
-// Tile shape and number of reduction splits.  Inside a training step the weight gradients run beside the
-// backward pass on a stream of their own (nothing waits for them until the update), so what counts is the
-// compute-unit time and the memory traffic they take from the kernels next to them, not their latency alone:
-// the largest tile the channel counts allow (a 64x64 wave tile reads half the LDS bytes per MFMA of a 32x32
-// one, a 128x128 workgroup tile loads half the operand bytes per flop of a 64x64 one), and only as many splits
-// of the pixel range as give about 192 workgroups (384 for very long reductions), each at least 8 chunks
-// long -- every split costs a full-size partial result written and read again by the reduction pass.
-// Measured on the whole step at batch 40 (profiles/wgrad_plan_step_time_batch40.txt): 128 to 256 workgroups
-// are within 1 % of each other, 64 and 576 lose 13 % and 3 %.
-static WgradPlan plan_wgrad(int M, int Cout, int Cg, int taps, int dtype, bool tunable = true) {
-  const int bkm = dtype == RN50_BF16 ? 64 : 32;
-  WgradPlan best{};
-  auto fill = [&](int bmo, int bc, int64_t want_splits, int min_chunks) {
-    const int64_t cap = M / (min_chunks * bkm) > 1 ? M / (min_chunks * bkm) : 1;
-    int64_t sp = want_splits < 1 ? 1 : (want_splits > cap ? cap : want_splits);
-    const int64_t rps = ceil_div(ceil_div(M, sp), bkm) * bkm;
-    best.bmo = bmo; best.bc = bc; best.ctiles = static_cast<int>(ceil_div(Cg, bc));
-    best.splits = static_cast<int>(ceil_div(M, rps));
-    best.rows_per_split = static_cast<int>(rps);
-  };
-  int target = M > 200000 ? 384 : 192, min_chunks = 8;
-  int bmo = Cout >= 128 ? 128 : 64, bc = Cg >= 128 ? 128 : 64;
-#ifdef RN50_TUNING  // tuning builds only: RN50_WGRAD_PLAN=bmo,bc,splits or RN50_WGRAD_TARGET=workgroups[,min chunks]
-  if (const char* e = tunable ? getenv("RN50_WGRAD_PLAN") : nullptr) {
-    int fbmo = 0, fbc = 0, sp = 0;
-    if (sscanf(e, "%d,%d,%d", &fbmo, &fbc, &sp) == 3 && (fbmo == 64 || fbmo == 128) && (fbc == 64 || fbc == 128) && sp >= 1) {
-      fill(fbmo, fbc, sp, 1);
-      return best;
-    }
-  }
-  if (const char* e2 = tunable ? getenv("RN50_WGRAD_TARGET") : nullptr) sscanf(e2, "%d,%d", &target, &min_chunks);
-#else
-  (void)tunable;
-#endif
-  const int64_t tiles = static_cast<int64_t>(taps) * ceil_div(Cg, bc) * ceil_div(Cout, bmo);
-  fill(bmo, bc, (target + tiles / 2) / tiles, min_chunks);
-  return best;
-}
-
-// Ring depth of a weight-gradient launch: as many chunk buffers as fit when the compute unit's 160 KB of LDS
-// are shared by the workgroups it will hold (grid / 256 compute units, rounded up, at most 3), between 2 and 6.
-static int wgrad_stages(int stage_bytes, int64_t grid) {
-#ifdef RN50_TUNING  // tuning builds only: RN50_WGRAD_STAGES=n forces the depth
-  if (const char* e = getenv("RN50_WGRAD_STAGES")) {
-    const int n = atoi(e);
-    if (n >= 2 && n <= 6 && n * stage_bytes <= 160 * 1024) return n;
-  }
-#endif
-  int64_t per_cu = ceil_div(grid, 256);
-  if (per_cu > 3) per_cu = 3;
-  int n = static_cast<int>((156 * 1024 / per_cu) / stage_bytes);
-  return n < 2 ? 2 : (n > 6 ? 6 : n);
-}
-template <typename T, int BMO, int BC, int NSTAGE>
-static void launch_wgrad_ring(const WgradArgs& b, dim3 grid, hipStream_t s) {
-  constexpr int BKM = WgradCfg<T>::BKM;
-  constexpr int lds = NSTAGE * BKM * (BMO + BC) * static_cast<int>(sizeof(T));
-  if (b.in_gamma) {  // the input-side BN variant is compiled for the two deepest rings only
-    if constexpr (NSTAGE == 2 || NSTAGE == 3) {
-      static std::once_flag once_in;
-      std::call_once(once_in, [] { allow_big_lds(wgrad_kernel<T, BMO, BC, NSTAGE, true>, lds); });
-      RN50_LAUNCH("conv_wgrad", (wgrad_kernel<T, BMO, BC, NSTAGE, true>), grid, dim3(256), lds, s, b);
-      return;
-    }
-  }
-  static std::once_flag once;
-  std::call_once(once, [] { allow_big_lds(wgrad_kernel<T, BMO, BC, NSTAGE>, lds); });
-  RN50_LAUNCH("conv_wgrad", (wgrad_kernel<T, BMO, BC, NSTAGE>), grid, dim3(256), lds, s, b);
-}
-template <typename T, int BMO, int BC>
-static void launch_wgrad_cfg(const WgradArgs& a, int splits, hipStream_t s) {
-  constexpr int BKM = WgradCfg<T>::BKM;
-  constexpr int stage = BKM * (BMO + BC) * static_cast<int>(sizeof(T));
-  WgradArgs b = a;
-  b.tiles_per_split = a.R * a.S * a.ctiles * static_cast<int>(ceil_div(a.Cout, BMO));
-  b.div_tps = make_fastdiv(b.tiles_per_split);
-  b.div_tiles_x = make_fastdiv(a.R * a.S * a.ctiles);
-  b.div_ctiles = make_fastdiv(a.ctiles);
-  b.div_S = make_fastdiv(a.S);
-  const dim3 grid(static_cast<unsigned>(b.tiles_per_split) * splits);
-  int stages = wgrad_stages(stage, grid.x);
-  if (b.in_gamma) stages = (stages >= 3 && 3 * stage <= 160 * 1024) ? 3 : 2;
-  switch (stages) {
-    case 2: return launch_wgrad_ring<T, BMO, BC, 2>(b, grid, s);
-    case 3: return launch_wgrad_ring<T, BMO, BC, 3>(b, grid, s);
-    case 4: return launch_wgrad_ring<T, BMO, BC, 4>(b, grid, s);
-    case 5: return launch_wgrad_ring<T, BMO, BC, (stage * 5 <= 160 * 1024 ? 5 : 4)>(b, grid, s);
-    default: return launch_wgrad_ring<T, BMO, BC, (stage * 6 <= 160 * 1024 ? 6 : 4)>(b, grid, s);
-  }
-}
-
-template <typename T>
-static void launch_wgrad(WgradArgs a, const WgradPlan& p, float* dw, float* partial, hipStream_t s) {
-  a.ctiles = p.ctiles;
-  a.rows_per_split = p.rows_per_split;
-  a.split_stride = static_cast<int64_t>(a.Cout) * a.Ktot;
-  a.out = p.splits > 1 ? partial : dw;
-#ifdef RN50_TUNING
-  static const int whatif = getenv("RN50_WGRAD_WHATIF") ? atoi(getenv("RN50_WGRAD_WHATIF")) : 0;
-  a.whatif = whatif;
-#endif
-  a.divQ = make_fastdiv(a.Q);
-  a.divP = make_fastdiv(a.P);
-  if (p.bmo == 128 && p.bc == 128) launch_wgrad_cfg<T, 128, 128>(a, p.splits, s);
-  else if (p.bmo == 128) launch_wgrad_cfg<T, 128, 64>(a, p.splits, s);
-  else if (p.bc == 128) launch_wgrad_cfg<T, 64, 128>(a, p.splits, s);
-  else launch_wgrad_cfg<T, 64, 64>(a, p.splits, s);
-  if (p.splits > 1) {
-    const int64_t n = a.split_stride;
-#ifdef RN50_TUNING  // what-if measurement: the weight gradients without their reduction launches (results wrong)
-    static const bool skip_red = getenv("RN50_SKIP_SPLITK_REDUCE") != nullptr;
-    if (!skip_red)
-#endif
-    RN50_LAUNCH("splitk_reduce", splitk_reduce_kernel, dim3(static_cast<unsigned>(ceil_div(ceil_div(n, 4), 64))), dim3(256), 0, s, partial, p.splits, n, dw);
-  }
-}
-
-static int out_dim(int in, int pad, int k, int stride) { return (in + 2 * pad - k) / stride + 1; }
-static bool is_stem(const rn50_conv_desc* d) {
-  return d->Cin == 3 && d->R == 7 && d->S == 7 && d->stride == 2 && d->pad == 3;
-}
-static int esize(int dtype) { return dtype == RN50_BF16 ? 2 : 4; }
-
 static int check_conv(const rn50_conv_desc* d, const char* who) {
   RN50_REQUIRE(d, RN50_ERR_INVALID, "%s: null descriptor", who);
   RN50_REQUIRE(d->N > 0 && d->H > 0 && d->W > 0 && d->Cin > 0 && d->Cout > 0 && d->R > 0 && d->S > 0 &&
@@ -1651,20 +983,6 @@ static int check_conv(const rn50_conv_desc* d, const char* who) {
                    static_cast<int64_t>(d->Cout) * d->R * d->S * (d->Cin < 4 ? 32 : d->Cin) < lim,
                RN50_ERR_UNSUPPORTED, "%s: a tensor is 2 GiB or larger", who);
   return RN50_OK;
-}
-
-// Geometry of the padded stem: 7 "taps" (filter rows) of 32 elements on pixels of 4 channels.
-struct StemGeom {
-  int Hp, Wp;
-  size_t xp_bytes, wp_bytes;
-};
-static StemGeom stem_geom(const rn50_conv_desc* d) {
-  StemGeom g;
-  g.Hp = d->H + 6;
-  g.Wp = (d->W + 6 + 2 + 3) / 4 * 4;  // room for the 8th (zero-weight) tap, row pitch a multiple of 16 bytes
-  g.xp_bytes = align_up(static_cast<size_t>(d->N) * g.Hp * g.Wp * 4 * esize(d->dtype), 256);
-  g.wp_bytes = align_up(static_cast<size_t>(d->Cout) * kStemK * esize(d->dtype), 256);
-  return g;
 }
 
 }  // namespace rn50
@@ -1758,159 +1076,6 @@ void stem_fwd_padded(const rn50_conv_desc* d, const void* xp, const void* w, voi
                        static_cast<const float*>(w), static_cast<float*>(wp), d->Cout);
     launch_igemm<float>(a, "conv_fwd", s);
   }
-}
-
-static int esize(int dtype);
-static bool is_stem(const rn50_conv_desc* d);
-
-// The nine-tap weight gradient (wgrad3x3_kernel): bf16, 3x3, stride 1, padding 1, and an image width whose run
-// of 2W + 68 rows fits six load passes.  Plan: 64x64 tiles, the padded pixel range split to give about 192
-// workgroups (384 for the longest reductions), each at least 8 chunks long (as for wgrad_kernel).
-struct Wgrad3x3Plan {
-  int nbx;  // load passes of the x run: 3, 4 or 6; 0: the layer does not run this kernel
-  int ctiles, kotiles, splits, rows_per_split, gpad;
-};
-static Wgrad3x3Plan plan_wgrad3x3(const rn50_conv_desc* d) {
-  Wgrad3x3Plan p{};
-#ifdef RN50_TUNING  // tuning builds only: RN50_NO_WGRAD3X3 sends these layers through the per-tap kernel
-  static const bool off = getenv("RN50_NO_WGRAD3X3") != nullptr;
-  if (off) return p;
-#endif
-  if (d->dtype != RN50_BF16 || d->R != 3 || d->S != 3 || d->stride != 1 || d->pad != 1 || is_stem(d)) return p;
-  const int need = static_cast<int>(ceil_div(2 * d->W + 68, 32));
-  if (need > 6) return p;
-  const int64_t gpad = static_cast<int64_t>(d->N) * (d->H + 1) * (d->W + 1);
-  if (gpad >= (1ll << 31) - 64) return p;
-  p.nbx = need <= 3 ? 3 : (need == 4 ? 4 : 6);
-  p.ctiles = static_cast<int>(ceil_div(d->Cin, 64));
-  p.kotiles = static_cast<int>(ceil_div(d->Cout, 64));
-  p.gpad = static_cast<int>(gpad);
-  int target = 384, min_chunks = 8;
-  bool always = false;
-#ifdef RN50_TUNING  // RN50_WGRAD3X3_TARGET=workgroups,min chunks[,1: every eligible layer]
-  if (const char* e = getenv("RN50_WGRAD3X3_TARGET")) {
-    int al = 0;
-    sscanf(e, "%d,%d,%d", &target, &min_chunks, &al);
-    always = al != 0;
-  }
-#endif
-  // Where it pays (per-layer sweeps at batch 40 and 256, profiles/wgrad3x3_nine_tap_sweep_batch40_batch256_bf16.txt): where the
-  // per-tap kernel is held to 64-wide tiles by the channel counts, and where its plan leaves a workgroup a
-  // reduction of 100 chunks or more (few, long-running workgroups: the wide layers at large batch).  Elsewhere
-  // the per-tap kernel's 128x128 tiles (64x64 wave tiles: half the LDS reads per MFMA) are as fast or faster.
-  if (!always && d->Cin > 64 && d->Cout > 64 &&
-      plan_wgrad(d->N * d->H * d->W, d->Cout, d->Cin, 9, d->dtype).rows_per_split < 100 * 64) {
-    p.nbx = 0;
-    return p;
-  }
-  const int64_t tiles = static_cast<int64_t>(p.ctiles) * p.kotiles;
-  const int64_t cap = gpad / (min_chunks * 64) > 1 ? gpad / (min_chunks * 64) : 1;
-  int64_t sp = (target + tiles / 2) / tiles;
-  sp = sp < 1 ? 1 : (sp > cap ? cap : sp);
-  const int64_t rps = ceil_div(ceil_div(gpad, sp), 64) * 64;
-  p.rows_per_split = static_cast<int>(rps);
-  p.splits = static_cast<int>(ceil_div(gpad, rps));
-  return p;
-}
-template <int NBX, int NSTAGE>
-static void launch_wgrad3x3_ring(const WgradArgs& a, dim3 grid, hipStream_t s) {
-  constexpr int lds = NSTAGE * (64 * 128 + NBX * 4096);
-  static std::once_flag once;
-  std::call_once(once, [] { allow_big_lds(wgrad3x3_kernel<NBX, NSTAGE>, lds); });
-  RN50_LAUNCH("conv_wgrad", (wgrad3x3_kernel<NBX, NSTAGE>), grid, dim3(256), lds, s, a);
-}
-template <int NBX>
-static void launch_wgrad3x3_nbx(const WgradArgs& a, dim3 grid, hipStream_t s) {
-  // three chunk buffers where the workgroups sharing a compute unit have the LDS for them, else two
-  int64_t per_cu = ceil_div(grid.x, 256);
-  if (per_cu > 3) per_cu = 3;
-  const bool three = 3 * (64 * 128 + NBX * 4096) * per_cu <= 156 * 1024;
-  if (three) launch_wgrad3x3_ring<NBX, 3>(a, grid, s);
-  else launch_wgrad3x3_ring<NBX, 2>(a, grid, s);
-}
-static void launch_wgrad3x3(WgradArgs a, const Wgrad3x3Plan& p, int H, float* dw, float* partial, hipStream_t s) {
-  a.ctiles = p.ctiles;
-  a.tiles_per_split = p.ctiles * p.kotiles;
-  a.rows_per_split = p.rows_per_split;
-  a.split_stride = static_cast<int64_t>(a.Cout) * a.Ktot;
-  a.out = p.splits > 1 ? partial : dw;
-  a.Gpad = p.gpad;
-  a.div_tps = make_fastdiv(a.tiles_per_split);
-  a.div_ctiles = make_fastdiv(a.ctiles);
-  a.div_img = make_fastdiv((H + 1) * (a.W + 1));
-  a.div_w1 = make_fastdiv(a.W + 1);
-  const dim3 grid(static_cast<unsigned>(a.tiles_per_split) * p.splits);
-  if (p.nbx == 3) launch_wgrad3x3_nbx<3>(a, grid, s);
-  else if (p.nbx == 4) launch_wgrad3x3_nbx<4>(a, grid, s);
-  else launch_wgrad3x3_nbx<6>(a, grid, s);
-  if (p.splits > 1) {
-    const int64_t n = a.split_stride;
-    RN50_LAUNCH("splitk_reduce", splitk_reduce_kernel, dim3(static_cast<unsigned>(ceil_div(ceil_div(n, 4), 64))), dim3(256), 0, s, partial, p.splits, n, dw);
-  }
-}
-static WgradArgs wgrad_args(const rn50_conv_desc* d, const void* x, const void* dy) {
-  WgradArgs a{};
-  a.x = x; a.dy = dy;
-  a.P = out_dim(d->H, d->pad, d->R, d->stride); a.Q = out_dim(d->W, d->pad, d->S, d->stride);
-  a.M = d->N * a.P * a.Q; a.Cout = d->Cout; a.Ktot = d->R * d->S * d->Cin;
-  a.H = d->H; a.W = d->W; a.PS = d->Cin; a.Cg = d->Cin; a.R = d->R; a.S = d->S; a.stride = d->stride; a.pad = d->pad;
-  a.x_bytes = static_cast<uint32_t>(static_cast<size_t>(d->N) * d->H * d->W * d->Cin * esize(d->dtype));
-  a.dy_bytes = static_cast<uint32_t>(static_cast<size_t>(a.M) * d->Cout * esize(d->dtype));
-  a.linear = d->R == 1 && d->S == 1 && d->stride == 1 && d->pad == 0;
-  return a;
-}
-static WgradArgs stem_wgrad_args(const rn50_conv_desc* d, const void* xp, const void* dy) {
-  const StemGeom g = stem_geom(d);
-  WgradArgs a{};
-  a.x = xp; a.dy = dy;
-  a.P = out_dim(d->H, 3, 7, 2); a.Q = out_dim(d->W, 3, 7, 2);
-  a.M = d->N * a.P * a.Q; a.Cout = d->Cout; a.Ktot = kStemK;
-  a.H = g.Hp; a.W = g.Wp; a.PS = 4; a.S = 1; a.stride = 2; a.pad = 0;
-  a.pair = d->dtype == RN50_BF16;  // as in stem_igemm_args
-  a.R = a.pair ? 4 : 7;
-  a.Cg = a.pair ? 64 : 32;
-  a.x_bytes = static_cast<uint32_t>(static_cast<size_t>(d->N) * g.Hp * g.Wp * 4 * esize(d->dtype));
-  a.dy_bytes = static_cast<uint32_t>(static_cast<size_t>(a.M) * d->Cout * esize(d->dtype));
-  a.linear = 0;
-  return a;
-}
-
-size_t wgrad_partial_bytes(const rn50_conv_desc* d) {
-  const bool stem = is_stem(d);
-  const int P = out_dim(d->H, d->pad, d->R, d->stride), Q = out_dim(d->W, d->pad, d->S, d->stride);
-  const int M = d->N * P * Q;
-  const bool pair = d->dtype == RN50_BF16;
-  const WgradPlan p = stem ? plan_wgrad(M, d->Cout, pair ? 64 : 32, pair ? 4 : 7, d->dtype, false)
-                           : plan_wgrad(M, d->Cout, d->Cin, d->R * d->S, d->dtype);
-  const size_t dw_elems = static_cast<size_t>(d->Cout) * (stem ? kStemK : d->R * d->S * d->Cin);
-  const Wgrad3x3Plan p9 = plan_wgrad3x3(d);
-  const int splits = p9.nbx ? p9.splits : p.splits;
-  size_t b = splits > 1 ? align_up(dw_elems * splits * sizeof(float), 256) : 0;
-  if (stem) b += align_up(dw_elems * sizeof(float), 256);  // padded dw
-  return b;
-}
-
-// Weight gradient; for the stem x must be the padded input.  scratch: wgrad_partial_bytes(d).
-void wgrad_run(const rn50_conv_desc* d, const void* x_or_xp, const void* dy, float* dw, void* scratch, hipStream_t s,
-               const BnIn* in) {
-  const bool stem = is_stem(d);
-  WgradArgs a = stem ? stem_wgrad_args(d, x_or_xp, dy) : wgrad_args(d, x_or_xp, dy);
-  if (in) { a.in_gamma = in->gamma; a.in_beta = in->beta; a.in_mean = in->mean; a.in_rstd = in->rstd; }
-  if (const Wgrad3x3Plan p9 = plan_wgrad3x3(d); p9.nbx && !in) {
-    launch_wgrad3x3(a, p9, d->H, dw, static_cast<float*>(scratch), s);
-    return;
-  }
-  const WgradPlan p = plan_wgrad(a.M, a.Cout, a.Cg, a.R * a.S, d->dtype, !stem);  // the stem's tile is fixed (64x64)
-  float* partial = static_cast<float*>(scratch);
-  float* target = dw;
-  if (stem) {
-    target = partial;
-    partial += align_up(static_cast<size_t>(d->Cout) * kStemK * sizeof(float), 256) / sizeof(float);
-  }
-  if (d->dtype == RN50_BF16) launch_wgrad<uint16_t>(a, p, target, partial, s);
-  else launch_wgrad<float>(a, p, target, partial, s);
-  if (stem)
-    RN50_LAUNCH("stem_unpad", stem_unpad_dw_kernel, dim3(ceil_div(d->Cout * 147, 256)), dim3(256), 0, s, target, dw, d->Cout);
 }
 
 void fwd_run(const rn50_conv_desc* d, const void* x, const void* w, void* y, float* bn_partial, hipStream_t s,
