@@ -31,6 +31,7 @@
 // pixels in four parity classes, each looping over its own taps only.
 #include <stdlib.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -141,6 +142,16 @@ template <int BM, int BN, int NW>
 constexpr int igemm_ring() {
   return (NW == 4 && 3 * (BM + BN) * 128 > 80 * 1024) ? 2 : 3;
 }
+// KS (launched with WM = WN = 1): the four waves of a workgroup split K instead of the tile.  Every wave computes the whole
+// BM x BN tile over a quarter of the chunks, with a ring of its own that it fills and reads without any barrier; at the end
+// the four partial tiles are added in wave order through LDS.  For grids that leave compute units idle or give each a single
+// workgroup: there a chunk costs the latency of its loads (0.35 us per chunk in the shared ring, whose depth is bounded
+// by LDS), and four independent rings take four of these latencies at a time; the wave tile is also the whole tile, so
+// fragments are read from LDS once (64x64: half the bytes per MFMA of four 32x32 waves).  Buffers per wave:
+template <int BM, int BN, bool BNIN>
+constexpr int igemm_ks_ring() {
+  return BNIN || BM + BN > 96 ? 2 : (BM + BN > 64 ? 3 : 4);
+}
 //
 // Data gradient (MODE 1): the B tile of a chunk is BK output channels (K) x BN input channels of the weights as they lie
 // in memory, filled and read like wgrad_kernel's tiles (transposing reads in bf16).  A transposing read delivers fewer
@@ -158,19 +169,22 @@ constexpr int igemm_ring() {
 // BN-row tiles, two taps ahead; the next chunk's run is loaded one pass per tap while the
 // current one is in use, so that every step issues the same number of loads (the load waits count them).
 template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN = false, bool BNIN = false, bool HALO = false>
-__global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) {
+__global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kernel(const IgemmArgs a) {
   static_assert(!BNIN || (LIN && MODE == 0), "the input-side BN is compiled for the linear forward kernel only");
   static_assert(!HALO || (!LIN && !BNIN), "the halo main loop is a kernel of its own");
   constexpr bool DG = MODE == 1, FWD = !DG, AFF = MODE == 2;
-  constexpr int NW = WM * WN, NT = 64 * NW;
+  constexpr bool KS = WM * WN == 1;
+  static_assert(!KS || !HALO, "a wave's own chunks are gathered");
+  constexpr int NW = KS ? 4 : WM * WN, NT = 64 * NW;
+  constexpr int LT = KS ? 64 : NT;              // threads that fill a chunk buffer together
   constexpr int V = 16 / sizeof(T);
   constexpr int BK = 128 / sizeof(T);
-  constexpr int RPL = NT / 8;                   // tile rows covered by one load pass of the workgroup
+  constexpr int RPL = LT / 8;                   // tile rows covered by one load pass
   constexpr int RA = BM / RPL, RB = BN / RPL;  // load passes (= load instructions per thread and chunk)
   constexpr int NL = RA + RB;
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
   constexpr int STAGE = (BM + BN) * 128;
-  constexpr int NSTAGE = igemm_ring<BM, BN, WM * WN>();
+  constexpr int NSTAGE = KS ? igemm_ks_ring<BM, BN, BNIN>() : igemm_ring<BM, BN, WM * WN>();
   constexpr int CP = BN * sizeof(T) + 16;  // epilogue pitch
   static_assert((NW == 4 || NW == 8) && TM >= 1 && TN >= 1 && RA >= 1 && RB >= 1, "tile shape");
   static_assert(BM % RPL == 0 && BN % RPL == 0, "every load pass covers whole rows of the tile");
@@ -178,10 +192,12 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
   // (the launch sizes the dynamic LDS as the larger of the ring and what the output stage stores in it)
   extern __shared__ __align__(16) unsigned char smem[];
 
-  const int tid = threadIdx.x, slot = tid & 7, lrow = tid >> 3;
-  const int piece = slot ^ ((lrow >> 1) & 7);  // the 16-byte piece of its rows' chunk this thread fetches
-  const int wave = tid >> 6, lane = tid & 63;
-  const int wm = wave % WM, wn = wave / WM;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int lt = KS ? lane : tid, slot = lt & 7, lrow = lt >> 3;
+  const int piece0 = slot ^ ((lrow >> 1) & 7);  // the 16-byte piece of its rows' chunk this thread fetches
+  // (KS: passes are 8 rows apart, which moves bit 2 of the permutation from one to the next)
+  auto piece_of = [&](int i) __attribute__((always_inline)) { return KS ? piece0 ^ ((i & 1) << 2) : piece0; };
+  const int wm = KS ? 0 : wave % WM, wn = KS ? 0 : wave / WM;
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   const int mt = static_cast<int>(fdiv(static_cast<uint32_t>(bid), a.div_ntn)), nt = bid - mt * a.ntn;
   const int n0 = nt * BN;
@@ -245,17 +261,17 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
   }
   // The B tile: BN rows (output columns) of one 128-byte chunk of K each, or (data gradient) BK rows (K) of BN columns.
   constexpr int BRB = BN * static_cast<int>(sizeof(T)), LB = BRB / 16;  // data gradient: bytes and 16-byte pieces per tile row
-  const int b_krow = DG ? tid / LB : 0;                                 // ... this thread's tile row in load pass 0
+  const int b_krow = DG ? lt / LB : 0;                                 // ... this thread's tile row in load pass 0
   const int k_pitch = a.R * a.S * a.Ncols;                              // ... elements from one K row of the weights to the next
   uint32_t b_row[RB];
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
     if constexpr (DG) {
-      const int col = n0 + ((tid % LB) ^ wgrad_swz<T, BRB>(b_krow)) * V;
-      b_row[i] = col < a.Ncols ? static_cast<uint32_t>((b_krow + (NT / LB) * i) * k_pitch + col) * sizeof(T) : kOob;
+      const int col = n0 + ((lt % LB) ^ wgrad_swz<T, BRB>(b_krow + (LT / LB) * i)) * V;
+      b_row[i] = col < a.Ncols ? static_cast<uint32_t>((b_krow + (LT / LB) * i) * k_pitch + col) * sizeof(T) : kOob;
     } else {
       const int n = n0 + lrow + RPL * i;
-      b_row[i] = n < a.Ncols ? static_cast<uint32_t>(n * a.Ktot + piece * V) * sizeof(T) : kOob;
+      b_row[i] = n < a.Ncols ? static_cast<uint32_t>(n * a.Ktot + piece_of(i) * V) * sizeof(T) : kOob;
     }
   }
   // byte offset of (tap, chunk cc) in the weights, and whether load pass i brings anything (cval: the forward pass's answer)
@@ -264,25 +280,40 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
               : static_cast<uint32_t>(tap * a.Cg) * static_cast<uint32_t>(sizeof(T)) + static_cast<uint32_t>(cc) * 128u;
   };
   auto b_live = [&](int i, int cc, bool cval) __attribute__((always_inline)) {
-    return DG ? (a.Cg % BK == 0 || cc * BK + b_krow + (NT / LB) * i < a.Cg) : cval;
+    return DG ? (a.Cg % BK == 0 || cc * BK + b_krow + (LT / LB) * i < a.Cg) : cval;
   };
 
   // Load cursor: tap (r,s), chunk cc within the tap.  Per tap, the byte offset of every row's pixel (or
   // kOob); within a tap successive chunks only differ by a scalar offset.
-  const int nchunks = nr * ns * a.cpt;
+  const int allchunks = nr * ns * a.cpt;
   int cur_r = r0, cur_s = s0, cur_cc = 0, cur = 0;
+  int nchunks = allchunks, first_chunk = 0;  // this wave's (KS) or the workgroup's range of chunks
+  if constexpr (KS) {
+    const int w = __builtin_amdgcn_readfirstlane(wave);
+    first_chunk = (allchunks * w) >> 2;
+    nchunks = ((allchunks * (w + 1)) >> 2) - first_chunk;
+    if (LIN) {
+      cur_cc = first_chunk;
+    } else if (nchunks > 0) {
+      const int tap = first_chunk / a.cpt;
+      cur_cc = first_chunk - tap * a.cpt;
+      cur_r = r0 + tstep * (tap / ns);
+      cur_s = s0 + tstep * (tap % ns);
+    }
+  }
   uint32_t a_off[RA];
-  int b_tap = r0 * a.S + s0;
+  int b_tap = cur_r * a.S + cur_s;
   const bool ragged = (a.Cg % BK) != 0;
   auto tap_setup = [&]() __attribute__((always_inline)) {
     if constexpr (LIN) {
 #pragma unroll
       for (int i = 0; i < RA; ++i)
-        a_off[i] = a_h0[i] < 0 ? kOob : static_cast<uint32_t>(a_base[i] * a.PS + piece * V) * sizeof(T);
+        a_off[i] = a_h0[i] < 0 ? kOob : static_cast<uint32_t>(a_base[i] * a.PS + piece_of(i) * V) * sizeof(T);
       return;
     }
 #pragma unroll
     for (int i = 0; i < RA; ++i) {
+      const int piece = piece_of(i);
       int ih, iw;
       bool ok = true;
       if (FWD) {
@@ -304,18 +335,18 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
   // One chunk into one ring buffer: every wave fills its 8 rows of each load pass (1 KB per instruction).
   typedef __attribute__((address_space(3))) unsigned char* lds_byte_ptr;
   const uint32_t wave_dst = __builtin_amdgcn_readfirstlane(
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_byte_ptr)smem)) + static_cast<uint32_t>(wave) * 1024u);
+      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_byte_ptr)smem)) + static_cast<uint32_t>(wave) * (KS ? NSTAGE * STAGE : 1024u));
   auto load_chunk = [&](int stage) __attribute__((always_inline)) {
     const uint32_t so = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(cur_cc) * 128u);
-    const bool cval = !ragged || (cur_cc * BK + piece * V < a.Cg);
+    auto cval = [&](int i) __attribute__((always_inline)) { return !ragged || (cur_cc * BK + piece_of(i) * V < a.Cg); };
     ++cur;
     const uint32_t sa = wave_dst + static_cast<uint32_t>(stage) * STAGE;
     const uint32_t sb = sa + BM * 128;
     const uint32_t sob = __builtin_amdgcn_readfirstlane(b_at(b_tap, cur_cc));
 #pragma unroll
-    for (int i = 0; i < RA; ++i) buffer_load16_to_lds(rsA, sa + i * (RPL * 128), cval ? a_off[i] : kOob, so);
+    for (int i = 0; i < RA; ++i) buffer_load16_to_lds(rsA, sa + i * (RPL * 128), cval(i) ? a_off[i] : kOob, so);
 #pragma unroll
-    for (int i = 0; i < RB; ++i) buffer_load16_to_lds(rsB, sb + i * (RPL * 128), b_live(i, cur_cc, cval) ? b_row[i] : kOob, sob);
+    for (int i = 0; i < RB; ++i) buffer_load16_to_lds(rsB, sb + i * (RPL * 128), b_live(i, cur_cc, cval(i)) ? b_row[i] : kOob, sob);
     // advance the cursor
     if constexpr (LIN) {
       ++cur_cc;
@@ -353,8 +384,9 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
   for (int j = 0; j < TN; ++j) bt_base[j] = DG ? wgrad_frag_base<T, BRB>(lane, wn * (BN / WN) + j * 32) : 0;
   constexpr int AHEAD = (TM + TN <= 3) ? 4 : 1;  // k steps whose fragments are in registers before the first MFMA
   auto compute = [&](int stage) __attribute__((always_inline)) {
-    const unsigned char* sa = smem + stage * STAGE + wm * (BM / WM) * 128;
-    const unsigned char* sb = smem + stage * STAGE + BM * 128 + (DG ? 0 : wn * (BN / WN) * 128);
+    const unsigned char* base = smem + (KS ? wave * (NSTAGE * STAGE) : 0) + stage * STAGE;
+    const unsigned char* sa = base + wm * (BM / WM) * 128;
+    const unsigned char* sb = base + BM * 128 + (DG ? 0 : wn * (BN / WN) * 128);
     Vec16 fa[4][TM], fb[4][TN];
     auto read_frags = [&](int kk) __attribute__((always_inline)) {
 #pragma unroll
@@ -395,6 +427,7 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
     const uint32_t dump = b_base + NSB * BN * 128;          // where the loads that only keep the count go (zeros)
     const uint32_t lds0 = wave_dst;                           // LDS address of smem + this wave's 1 KB share of a pass
     const int q0 = m0 - Wd - 1 + lrow;                        // input pixel of this thread's row in pass 0 of a run
+    const int piece = piece0;
     auto load_run_pass = [&](int j, int cc, int buf) __attribute__((always_inline)) {
       const int q = q0 + RPL * j;
       const bool ok = static_cast<unsigned>(q) < static_cast<unsigned>(a.M) && (!ragged || cc * BK + piece * V < a.Cg);
@@ -499,7 +532,7 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
   tap_setup();
   float* const in_tab = reinterpret_cast<float*>(smem + (BNIN ? a.in_lds : 0));  // [2][nchunks * BK]: scale, bias
   if constexpr (BNIN) {
-    const int kpad = nchunks * BK;
+    const int kpad = allchunks * BK;
     for (int c = tid; c < kpad; c += NT) {
       float sc = 0.f, bi = 0.f;
       if (c < a.Cg) bn_coeffs(a.in_gamma[c], a.in_beta[c], a.in_mean[c], a.in_rstd[c], &sc, &bi);
@@ -513,27 +546,62 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
     if (c < nchunks) load_chunk(c);
   int stage = 0;
   for (int kc = 0; kc < nchunks; ++kc) {
-    ring_wait<NSTAGE, NL>(nchunks - 1 - kc);
-    if (kc + NSTAGE - 1 < nchunks) load_chunk(stage >= 1 ? stage - 1 : NSTAGE - 1);  // buffer (kc - 1) mod NSTAGE
+    if constexpr (KS) {  // (nobody else reads this wave's buffers: the next loads go out before the wait)
+      if (kc + NSTAGE - 1 < nchunks) load_chunk(stage >= 1 ? stage - 1 : NSTAGE - 1);
+      ring_wait<NSTAGE + 1, NL, false>(nchunks - 1 - kc);
+    } else {
+      ring_wait<NSTAGE, NL>(nchunks - 1 - kc);
+      if (kc + NSTAGE - 1 < nchunks) load_chunk(stage >= 1 ? stage - 1 : NSTAGE - 1);  // buffer (kc - 1) mod NSTAGE
+    }
     if constexpr (BNIN) {
       // every thread transforms, in place, the vectors of chunk kc that its own loads brought (its slot of its
       // rows holds piece `piece`, i.e. channels kc*BK + piece*V ..), then a second barrier
       float scale[V], bias[V];
-      const int kpad = nchunks * BK;
-      load_floats<V>(in_tab + kc * BK + piece * V, scale);
-      load_floats<V>(in_tab + kpad + kc * BK + piece * V, bias);
+      const int kpad = allchunks * BK;
 #pragma unroll
-      for (int i = 0; i < RA; ++i) {
-        uint4* p = reinterpret_cast<uint4*>(smem + stage * STAGE + (lrow + RPL * i) * 128 + slot * 16);
-        Vec16 v;
-        v.u = *p;
-        *p = bn_relu_vector<T>(v, scale, bias).u;
+      for (int par = 0; par < (KS ? 2 : 1); ++par) {
+        const int at = (first_chunk + kc) * BK + piece_of(par) * V;
+        load_floats<V>(in_tab + at, scale);
+        load_floats<V>(in_tab + kpad + at, bias);
+#pragma unroll
+        for (int i = par; i < RA; i += KS ? 2 : 1) {
+          uint4* p = reinterpret_cast<uint4*>(smem + (KS ? wave * (NSTAGE * STAGE) : 0) + stage * STAGE + (lrow + RPL * i) * 128 + slot * 16);
+          Vec16 v;
+          v.u = *p;
+          *p = bn_relu_vector<T>(v, scale, bias).u;
+        }
       }
-      lds_writes_then_barrier();
+      if (!KS) lds_writes_then_barrier();  // (KS: the wave's own LDS operations stay in order)
     }
     compute(stage);
     stage = stage == NSTAGE - 1 ? 0 : stage + 1;
   }
+  }
+  if constexpr (KS) {
+    // wave w takes rows g = w (four consecutive output channels) of every 32x32 block from the four partial tiles
+    float4* red = reinterpret_cast<float4*>(smem);  // [wave][i][j][g][lane]
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          red[(((wave * TM + i) * TN + j) * 4 + g) * 64 + lane] =
+              make_float4(acc[i][j][g * 4], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        float4 r[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) r[w] = red[(((w * TM + i) * TN + j) * 4 + wave) * 64 + lane];
+        acc[i][j][0] = ((r[0].x + r[1].x) + r[2].x) + r[3].x;
+        acc[i][j][1] = ((r[0].y + r[1].y) + r[2].y) + r[3].y;
+        acc[i][j][2] = ((r[0].z + r[1].z) + r[2].z) + r[3].z;
+        acc[i][j][3] = ((r[0].w + r[1].w) + r[2].w) + r[3].w;
+      }
   }
   if constexpr (AFF) {
     if (tid < BN) {
@@ -542,6 +610,8 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
       prm_s[tid] = sc; prm_s[BN + tid] = bi;
     }
     lds_writes_then_barrier();
+  } else if constexpr (KS) {
+    __syncthreads();  // the output tile below reuses the exchange buffers
   } else {
     __builtin_amdgcn_s_barrier();  // the output tile below reuses the pipeline buffers
     asm volatile("" ::: "memory");
@@ -556,31 +626,19 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
     for (int j = 0; j < TN; ++j) {
       const int row = wm * (BM / WM) + i * 32 + (lane & 31);
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g0 = 0; g0 < (KS ? 1 : 4); ++g0) {
+        const int g = KS ? wave : g0;
         const int col = wn * (BN / WN) + j * 32 + g * 8 + (lane >> 5) * 4;
         unsigned char* dst = smem + row * CP + col * sizeof(T);
+        float4 v = make_float4(acc[i][j][g0 * 4 + 0], acc[i][j][g0 * 4 + 1], acc[i][j][g0 * 4 + 2], acc[i][j][g0 * 4 + 3]);
         if constexpr (AFF) {
           const float4 sc = *reinterpret_cast<const float4*>(prm_s + col), bi = *reinterpret_cast<const float4*>(prm_s + BN + col);
-          acc[i][j][g * 4 + 0] = bn_affine(acc[i][j][g * 4 + 0], sc.x, bi.x);
-          acc[i][j][g * 4 + 1] = bn_affine(acc[i][j][g * 4 + 1], sc.y, bi.y);
-          acc[i][j][g * 4 + 2] = bn_affine(acc[i][j][g * 4 + 2], sc.z, bi.z);
-          acc[i][j][g * 4 + 3] = bn_affine(acc[i][j][g * 4 + 3], sc.w, bi.w);
-          if (a.aff_relu && !a.addend) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[i][j][g * 4 + v] = fmaxf(acc[i][j][g * 4 + v], 0.f);
-          }
+          v = make_float4(bn_affine(v.x, sc.x, bi.x), bn_affine(v.y, sc.y, bi.y), bn_affine(v.z, sc.z, bi.z), bn_affine(v.w, sc.w, bi.w));
+          if (a.aff_relu && !a.addend) v = make_float4(fmaxf(v.x, 0.f), fmaxf(v.y, 0.f), fmaxf(v.z, 0.f), fmaxf(v.w, 0.f));
         }
-        if (wide) {
-          *reinterpret_cast<float4*>(smem + row * CPW + col * 4) =
-              make_float4(acc[i][j][g * 4 + 0], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
-        } else if (sizeof(T) == 2) {
-          uint2 p;
-          p.x = float2_to_bf16x2_bits(acc[i][j][g * 4 + 0], acc[i][j][g * 4 + 1]);
-          p.y = float2_to_bf16x2_bits(acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
-          *reinterpret_cast<uint2*>(dst) = p;
-        } else {
-          *reinterpret_cast<float4*>(dst) = make_float4(acc[i][j][g * 4 + 0], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
-        }
+        if (wide) *reinterpret_cast<float4*>(smem + row * CPW + col * 4) = v;
+        else if (sizeof(T) == 2) *reinterpret_cast<uint2*>(dst) = make_uint2(float2_to_bf16x2_bits(v.x, v.y), float2_to_bf16x2_bits(v.z, v.w));
+        else *reinterpret_cast<float4*>(dst) = v;
       }
     }
   if (DG && a.partial != nullptr && tid < BN) {
@@ -735,7 +793,6 @@ __global__ __launch_bounds__(64 * WM * WN) void igemm_kernel(const IgemmArgs a) 
   if (MODE == 0 && tid < BN) kshift = Elem<T>::load(reinterpret_cast<const T*>(smem) + tid);  // row m0 of the tile
   __syncthreads();
   float* cs = reinterpret_cast<float*>(smem);
-  static_assert(RPP * 2 * BN * 4 <= BM * CPW, "the column sums fit where the output tile was");
   static_assert(2 * BN <= NT && NPASS >= 1, "one thread per plane and column");
 #pragma unroll
   for (int j = 0; j < V; j += 4) {
@@ -805,17 +862,20 @@ __global__ __launch_bounds__(256) void stem_pad_weight_kernel(const T* __restric
 // ------------------------------------------------------------------ host side
 template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN, bool BNIN = false>
 static void launch_igemm_mode(IgemmArgs a, const char* tag, int64_t grid, hipStream_t s) {
-  constexpr int NT = 64 * WM * WN;
-  constexpr int stage = (BM + BN) * 128;
+  constexpr bool KS = WM * WN == 1;
+  constexpr int NT = KS ? 256 : 64 * WM * WN;
+  constexpr int stage = (BM + BN) * 128 * (KS ? 4 : 1);  // (KS: every wave has a ring)
   constexpr int es = static_cast<int>(sizeof(T));
   // the output stage reuses the ring: the tile (in float when a bf16 data gradient adds a second branch) and
   // the column sums of the fused batch norm
   constexpr int out_tile = BM * (BN * 4 + 16);
   constexpr int col_sums = (NT / (BN * es / 16)) * 2 * BN * 4;
-  constexpr int out_need = out_tile > col_sums ? out_tile : col_sums;
+  constexpr int exchange = KS ? 4 * BM * BN * 4 : 0;     // (KS: the four partial tiles)
+  constexpr int out_need = std::max({out_tile, col_sums, exchange});
   static std::once_flag once;
-  constexpr int nring = igemm_ring<BM, BN, WM * WN>();
-  constexpr int kInTabMax = 8 * 4096;  // input-side BN coefficients: two floats per channel, at most 4096 channels
+  constexpr int nring = KS ? igemm_ks_ring<BM, BN, BNIN>() : igemm_ring<BM, BN, WM * WN>();
+  // input-side BN coefficients: two floats per channel, at most 4096 channels (KS: 2048)
+  constexpr int kInTabMax = 8 * (KS ? 2048 : 4096);
   std::call_once(once, [] {
     allow_big_lds(igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN>,
                   (nring * stage > out_need ? nring * stage : out_need) + (BNIN ? kInTabMax : 0));
@@ -823,11 +883,11 @@ static void launch_igemm_mode(IgemmArgs a, const char* tag, int64_t grid, hipStr
   // A short reduction never touches the later ring buffers; without them more workgroups fit a CU (the 1x1
   // layers with 64 channels, the largest pixel counts of the net, have a single chunk).
   const int chunks = a.R * a.S * a.cpt;
-  const int ring = (chunks < nring ? (chunks < 1 ? 1 : chunks) : nring) * stage;
+  const int ring = (!KS && chunks < nring ? (chunks < 1 ? 1 : chunks) : nring) * stage;
   int lds = ring > out_need ? ring : out_need;
   if (BNIN) {
     a.in_lds = lds;
-    lds += 8 * chunks * (128 / es);
+    lds += 8 * a.R * a.S * a.cpt * (128 / es);
   }
   RN50_LAUNCH(tag, (igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN>), dim3(static_cast<unsigned>(grid)), dim3(NT), lds, s, a);
 }
@@ -878,12 +938,13 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
     else launch_igemm_mode<T, BM, BN, WM, WN, 1, true>(a, tag, grid, s);
     return;
   }
-  const bool halo_shape = igemm_halo_shape(a);
-  if (const int halo_lds = halo_shape ? halo_lds_bytes<BM, BN, WM, WN>(a.W, a.cpt) : 0) {
-    if (a.mode == 2) launch_igemm_halo<T, BM, BN, WM, WN, 2>(a, tag, grid, halo_lds, s);
-    else if (a.mode == 0) launch_igemm_halo<T, BM, BN, WM, WN, 0>(a, tag, grid, halo_lds, s);
-    else launch_igemm_halo<T, BM, BN, WM, WN, 1>(a, tag, grid, halo_lds, s);
-    return;
+  if constexpr (WM * WN > 1) {
+    if (const int halo_lds = igemm_halo_shape(a) ? halo_lds_bytes<BM, BN, WM, WN>(a.W, a.cpt) : 0) {
+      if (a.mode == 2) launch_igemm_halo<T, BM, BN, WM, WN, 2>(a, tag, grid, halo_lds, s);
+      else if (a.mode == 0) launch_igemm_halo<T, BM, BN, WM, WN, 0>(a, tag, grid, halo_lds, s);
+      else launch_igemm_halo<T, BM, BN, WM, WN, 1>(a, tag, grid, halo_lds, s);
+      return;
+    }
   }
   if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, false>(a, tag, grid, s);
   else if (a.mode == 0) launch_igemm_mode<T, BM, BN, WM, WN, 0, false>(a, tag, grid, s);
@@ -894,7 +955,7 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
 struct TileShape {
   int bm, bn, wm, wn;
 };
-#define RN50_IGEMM_SHAPES(X) X(64, 64, 2, 2) X(128, 64, 2, 2) X(128, 128, 2, 2) X(256, 128, 4, 2)
+#define RN50_IGEMM_SHAPES(X) X(64, 64, 2, 2) X(128, 64, 2, 2) X(128, 128, 2, 2) X(256, 128, 4, 2) X(64, 64, 1, 1)
 static bool igemm_shape_compiled(const TileShape& t) {
 #define X(BM, BN, WM, WN) if (t.bm == BM && t.bn == BN && t.wm == WM && t.wn == WN) return true;
   RN50_IGEMM_SHAPES(X)
@@ -951,14 +1012,34 @@ static bool halo_filter(int R, int S, int stride, int pad) {
 static bool igemm_halo_shape(const IgemmArgs& a) {
   return halo_filter(a.R, a.S, a.stride, a.pad) && !a.pair && a.H == a.P && a.W == a.Q;
 }
+// The tile of a launch.  rows: output pixels (of one parity class for a stride-2 data gradient, `live` of whose four classes
+// have any taps); taps x cpt 128-byte chunks of reduction; lin_fwd_channels: input channels of a 1x1 stride-1 forward
+// layer (else 0), whose coefficient table bounds the K-split kernels.
+// Where 64x64 tiles would give at most one workgroup per compute unit and there are chunks for four waves, the waves split K
+// (KS); at half of that or less the tile is halved again (in float, whose MFMAs take sixteen times as long per chunk, in
+// both directions), so that twice (four times) as many compute units work.  Measured on the whole float gradient pass (batch 4:
+// 4055 -> 2919 us, batch 8: 4752 -> 4024, batch 16: 6789 -> 6384) and on single layers (2048 -> 512 channels at 7x7,
+// batch 40: 14.0 -> 9.3 us; 3x3 512 -> 512 at 7x7, batch 12: 28.7 -> 14.4); with 257 to 512 tiles the two workgroups per
+// compute unit of the shared ring do better.
+static TileShape pick_tile(int64_t rows, int Ncols, int chunks, bool dgrad, bool strided_dgrad, int live, bool halo,
+                           int lin_fwd_channels, int dtype) {
+  const int64_t groups64 = ceil_div(rows, 64) * ceil_div(Ncols, 64) * (strided_dgrad ? live : 1);
+  if (chunks >= 4 && lin_fwd_channels <= 2048 && groups64 <= 256) {
+    if (groups64 > 128) return TileShape{64, 64, 1, 1};
+    return dtype == RN50_F32 ? TileShape{32, 32, 1, 1} : TileShape{32, 64, 1, 1};
+  }
+  return halo ? igemm_halo_tile(rows, Ncols) : igemm_tile(rows, Ncols, chunks, dgrad, strided_dgrad, live);
+}
 template <typename T>
 static void launch_igemm(const IgemmArgs& a, const char* tag, hipStream_t s) {
   const bool classes = a.mode == 1 && a.stride == 2;
   const int64_t rows = classes ? static_cast<int64_t>(a.M / (a.P * a.Q)) * ((a.P + 1) / 2) * ((a.Q + 1) / 2) : a.M;
-  TileShape t = igemm_tile(rows, a.Ncols, a.R * a.S * a.cpt, a.mode == 1, classes, a.R * a.S > 1 ? 4 : 1);
-  if (igemm_halo_shape(a)) t = igemm_halo_tile(a.M, a.Ncols);
+  const bool lin_fwd = a.mode != 1 && a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0 && !a.pair;
+  const TileShape t = pick_tile(rows, a.Ncols, a.R * a.S * a.cpt, a.mode == 1, classes, a.R * a.S > 1 ? 4 : 1,
+                                igemm_halo_shape(a), lin_fwd ? a.Cg : 0, sizeof(T) == 2 ? RN50_BF16 : RN50_F32);
 #define X(BM, BN, WM, WN) if (t.bm == BM && t.bn == BN && t.wm == WM && t.wn == WN) return launch_igemm_cfg<T, BM, BN, WM, WN>(a, tag, s);
   RN50_IGEMM_SHAPES(X)
+  if constexpr (sizeof(T) == 4) { X(32, 32, 1, 1) } else { X(32, 64, 1, 1) }
 #undef X
 }
 
@@ -1012,28 +1093,28 @@ static int chunks_per_tap(int channels, int dtype) { return static_cast<int>(cei
 // stride-2 data gradient: four parity classes of ceil(N * ceil(H/2) * ceil(W/2) / bm) row tiles each
 static PartialRows class_tile_rows(const rn50_conv_desc* d) {
   const int64_t rows = static_cast<int64_t>(d->N) * ((d->H + 1) / 2) * ((d->W + 1) / 2);
-  const int bm = igemm_tile(rows, d->Cin, d->R * d->S * chunks_per_tap(d->Cout, d->dtype), true, true, d->R * d->S > 1 ? 4 : 1).bm;
+  const int bm = pick_tile(rows, d->Cin, d->R * d->S * chunks_per_tap(d->Cout, d->dtype), true, true, d->R * d->S > 1 ? 4 : 1,
+                           false, 0, d->dtype).bm;
   return PartialRows{bm, static_cast<int>(4 * ceil_div(rows, bm))};
 }
 PartialRows fwd_partial_rows(const rn50_conv_desc* d) {
   const int64_t M = static_cast<int64_t>(d->N) * out_dim(d->H, d->pad, d->R, d->stride) * out_dim(d->W, d->pad, d->S, d->stride);
   // the chunk count as the launch computes it (the bf16 stem runs as 4 taps of one chunk, the float stem as 7)
   const int chunks = is_stem(d) ? (d->dtype == RN50_BF16 ? 4 : 7) : d->R * d->S * chunks_per_tap(d->Cin, d->dtype);
-  const int bm = halo_filter(d->R, d->S, d->stride, d->pad) ? igemm_halo_tile(M, d->Cout).bm
-                                                            : igemm_tile(M, d->Cout, chunks, false, false).bm;
+  const bool lin = d->R == 1 && d->S == 1 && d->stride == 1 && d->pad == 0;
+  const int bm = pick_tile(M, d->Cout, chunks, false, false, 4, halo_filter(d->R, d->S, d->stride, d->pad), lin ? d->Cin : 0, d->dtype).bm;
   return PartialRows{bm, static_cast<int>(ceil_div(M, bm))};
 }
 int64_t dgrad_partial_rows_bound(const rn50_conv_desc* d) {
-  const int64_t plain = ceil_div(static_cast<int64_t>(d->N) * d->H * d->W, 64);
-  const int64_t classes = 4 * ceil_div(static_cast<int64_t>(d->N) * ((d->H + 1) / 2) * ((d->W + 1) / 2), 64);
+  const int64_t plain = ceil_div(static_cast<int64_t>(d->N) * d->H * d->W, 32);
+  const int64_t classes = 4 * ceil_div(static_cast<int64_t>(d->N) * ((d->H + 1) / 2) * ((d->W + 1) / 2), 32);
   return d->stride == 2 && classes > plain ? classes : plain;
 }
 PartialRows dgrad_partial_rows(const rn50_conv_desc* d) {
   if (d->stride == 2) return class_tile_rows(d);
   const int64_t M = static_cast<int64_t>(d->N) * d->H * d->W;
-  const int bm = halo_filter(d->R, d->S, d->stride, d->pad)
-                     ? igemm_halo_tile(M, d->Cin).bm
-                     : igemm_tile(M, d->Cin, d->R * d->S * chunks_per_tap(d->Cout, d->dtype), true, false).bm;
+  const int bm = pick_tile(M, d->Cin, d->R * d->S * chunks_per_tap(d->Cout, d->dtype), true, false, 4,
+                           halo_filter(d->R, d->S, d->stride, d->pad), 0, d->dtype).bm;
   return PartialRows{bm, static_cast<int>(ceil_div(M, bm))};
 }
 
@@ -1198,10 +1279,10 @@ extern "C" int conv_wgrad(const rn50_conv_desc* d, const void* x, const void* dy
 // ---- fused batch-norm sums (the BN side is in bn.hip)
 extern "C" size_t conv_bn_sums_bytes(const rn50_conv_desc* d) {
   if (!d || check_conv(d, "conv_bn_sums_bytes")) return 0;
-  // one row per output tile of at least 64 pixels; forward three float planes or, row-major, two doubles per
+  // one row per output tile of at least 32 pixels; forward three float planes or, row-major, two doubles per
   // channel and row; two planes backward
   const int P = out_dim(d->H, d->pad, d->R, d->stride), Q = out_dim(d->W, d->pad, d->S, d->stride);
-  const size_t fwd = static_cast<size_t>(ceil_div(static_cast<int64_t>(d->N) * P * Q, 64)) * 4 * d->Cout;
+  const size_t fwd = static_cast<size_t>(ceil_div(static_cast<int64_t>(d->N) * P * Q, 32)) * 4 * d->Cout;
   const size_t bwd = static_cast<size_t>(dgrad_partial_rows_bound(d)) * 2 * d->Cin;
   return align_up((fwd > bwd ? fwd : bwd) * sizeof(float), 256);
 }

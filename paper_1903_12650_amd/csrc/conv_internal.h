@@ -72,28 +72,29 @@ __device__ __forceinline__ void buffer_load16_to_lds(rsrc_words r, uint32_t lds_
 }
 // Wait until at most N of this wave's vector-memory loads are outstanding, then the workgroup barrier, without
 // the full memory fence of __syncthreads() (which would also wait for the loads of the chunks still in flight).
-template <int N>
+template <int N, bool BARRIER = true>
 __device__ __forceinline__ void wait_loads_then_barrier() {
   static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
   // s_waitcnt immediate on gfx9: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] << 14; 7 / 15 = no wait
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-  __builtin_amdgcn_s_barrier();
+  if (BARRIER) __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
 
 // Top of iteration kc of a ring of NSTAGE chunk buffers (loads NSTAGE-1 chunks ahead, NL load instructions per
 // thread and chunk): wait until this wave's loads of chunk kc have landed -- those of the chunks behind it that
 // have been issued, at most NSTAGE-2 of them and none past the last chunk, may stay in flight -- then the barrier.
-template <int NSTAGE, int NL>
+// (BARRIER = false: a ring that only this wave fills and reads.)
+template <int NSTAGE, int NL, bool BARRIER = true>
 __device__ __forceinline__ void ring_wait(int chunks_after) {
   static_assert(NSTAGE >= 2 && NSTAGE <= 6 && NL * (NSTAGE - 2) < 64, "ring depth");
   const int ahead = chunks_after < NSTAGE - 2 ? chunks_after : NSTAGE - 2;
-  if (NSTAGE >= 6 && ahead == 4) wait_loads_then_barrier<(NSTAGE >= 6 ? 4 : 0) * NL>();
-  else if (NSTAGE >= 5 && ahead == 3) wait_loads_then_barrier<(NSTAGE >= 5 ? 3 : 0) * NL>();
-  else if (NSTAGE >= 4 && ahead == 2) wait_loads_then_barrier<(NSTAGE >= 4 ? 2 : 0) * NL>();
-  else if (NSTAGE >= 3 && ahead == 1) wait_loads_then_barrier<(NSTAGE >= 3 ? 1 : 0) * NL>();
-  else wait_loads_then_barrier<0>();
+  if (NSTAGE >= 6 && ahead == 4) wait_loads_then_barrier<(NSTAGE >= 6 ? 4 : 0) * NL, BARRIER>();
+  else if (NSTAGE >= 5 && ahead == 3) wait_loads_then_barrier<(NSTAGE >= 5 ? 3 : 0) * NL, BARRIER>();
+  else if (NSTAGE >= 4 && ahead == 2) wait_loads_then_barrier<(NSTAGE >= 4 ? 2 : 0) * NL, BARRIER>();
+  else if (NSTAGE >= 3 && ahead == 1) wait_loads_then_barrier<(NSTAGE >= 3 ? 1 : 0) * NL, BARRIER>();
+  else wait_loads_then_barrier<0, BARRIER>();
 }
 
 // LDS tiles of the weight gradient are [k row][column] with rows of RBY = 16 * (columns per 16 bytes ...) bytes,
@@ -105,6 +106,7 @@ __device__ __forceinline__ void ring_wait(int chunks_after) {
 //   float:               lanes 32-63 read the row 4 below lanes 0-31 -- it is shifted by 128 bytes.
 template <typename T, int RBY>
 __device__ __forceinline__ int wgrad_swz(int row) {
+  if (RBY == 64 || (sizeof(T) == 4 && RBY == 128)) return 0;  // rows too short to permute
   if (sizeof(T) == 4) return ((row >> 2) & 1) << 3;
   return RBY == 128 ? ((row >> 1) & 1) << 2 : (row & 3) << 2;
 }

@@ -163,3 +163,44 @@ def test_3x3_taps_never_reach_into_the_neighbouring_image(rn, mode_name):
     for a, b in zip(*outs):
         assert torch.equal(a[0], b[0]) and torch.equal(a[2], b[2])
         assert torch.isnan(b[1]).any()
+
+
+# Where the waves of a workgroup split the reduction (few output tiles, at least four 128-byte chunks): chunk counts that
+# are and are not multiples of four, ragged channels, the tile counts at which the tile changes, stride-2 pixel classes,
+# the channel count beyond which the linear forward kernel keeps the shared ring.
+K_SPLIT = [  # N,H,W,C,K,R,stride,pad (channels in 128-byte chunks of the bf16 type)
+    (1, 7, 7, 256, 64, 1, 1, 0),       # four chunks, one ragged row tile
+    (1, 5, 5, 320, 72, 1, 1, 0),       # five chunks, ragged columns
+    (2, 6, 7, 424, 136, 1, 1, 0),      # seven chunks, the last one ragged
+    (1, 32, 32, 256, 512, 1, 1, 0),    # 128 tiles of 64x64
+    (1, 32, 33, 256, 512, 1, 1, 0),    # 136
+    (2, 32, 32, 256, 512, 1, 1, 0),    # 256
+    (2, 32, 33, 256, 512, 1, 1, 0),    # 264: the shared ring
+    (1, 9, 8, 8, 16, 3, 1, 1),         # nine chunks of one ragged tap each
+    (2, 9, 7, 136, 72, 3, 1, 1),       # taps of three chunks, wave ranges that begin inside a tap
+    (3, 9, 11, 72, 40, 3, 2, 1),       # stride 2: classes of one, two and four taps
+    (2, 7, 6, 264, 520, 1, 2, 0),      # stride 2 without taps in three of the classes
+    (1, 4, 4, 2048, 64, 1, 1, 0),      # the most channels of a linear forward layer
+    (1, 4, 4, 2056, 64, 1, 1, 0),      # one vector more
+]
+
+
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("case", K_SPLIT)
+def test_k_split_edges(rn, mode_name, case):
+    N, H, W, C, K, R, stride, pad = case
+    if mode_name == "f32":
+        C = C if C > 2000 else max(4, C // 2)          # the same number of 128-byte chunks
+    run_case(rn, mode_name, N, H, W, C, K, R, stride, pad, tag="ks" + str(case))
+
+
+# Weight gradient: tiles that span filter taps, channel counts at the edges of the tile widths, pixel ranges of less than one
+# chunk, one chunk more than a whole number of splits, and the most splits.
+WGRAD_EDGES = [(1, 3, 3, 40, 64, 3, 1, 1), (2, 8, 8, 64, 72, 1, 1, 0), (2, 8, 8, 72, 64, 1, 1, 0), (1, 1, 1, 128, 128, 3, 1, 1),
+               (5, 23, 29, 64, 64, 1, 1, 0), (3, 40, 41, 8, 8, 3, 2, 1), (1, 9, 9, 56, 136, 5, 1, 2), (2, 14, 14, 512, 1024, 1, 2, 0)]
+
+
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("case", WGRAD_EDGES)
+def test_wgrad_plan_edges(rn, mode_name, case):
+    run_case(rn, mode_name, *case, tag="wg" + str(case))
