@@ -23,6 +23,8 @@
 // within a few standard deviations of the mean.
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "step_internal.h"
 
@@ -57,6 +59,23 @@ static BnGeom bn_geom(int64_t m, int C, int dtype) {
   const int64_t rpb = rpt * TY;
   g.rpb = static_cast<int>(rpb);
   g.nblk = static_cast<int>(ceil_div(m, rpb));
+  return g;
+}
+
+// Geometry of the stand-alone sums passes (statistics, backward sums).  Layers of at most kBnSelfRows rows are summed in at
+// most 128 row blocks of at least 32 rows, row-major, and their apply pass finalizes by itself (bn_apply_kernel's FIN): a
+// finalize launch costs about 4 us whatever it computes, reading 128 rows of sums in every apply workgroup 1 to 2.  Beyond
+// that, 128 row blocks would leave a block more than 256 rows and the chip too few of them.
+constexpr int64_t kBnSelfRows = 32768;
+static bool bn_self_sums(int64_t m) { return m <= kBnSelfRows; }
+static BnGeom bn_sums_geom(int64_t m, int C, int dtype) {
+  BnGeom g = bn_geom(m, C, dtype);
+  if (bn_self_sums(m)) {
+    const int TY = 256 >> g.tx_log2;
+    const int64_t rows = std::max<int64_t>(ceil_div(m, 128), 32);
+    g.rpb = static_cast<int>(ceil_div(rows, TY) * TY);
+    g.nblk = static_cast<int>(ceil_div(m, g.rpb));
+  }
   return g;
 }
 
@@ -100,53 +119,65 @@ static void bn_self_finalize_geom(int64_t m, int C, int V, int* gy_out, int* rpb
   *rpb_out = static_cast<int>(rpt) * TY;
 }
 
-// Tree-combine NV floats per thread over the TY rows of the workgroup; the
-// result lands in the threads of row 0.
-template <int NV>
-__device__ __forceinline__ void combine_rows(float* vals, float* lds, int tx_log2) {
-  const int TX = 1 << tx_log2, TY = 256 >> tx_log2;
-  const int tcol = threadIdx.x & (TX - 1), trow = threadIdx.x >> tx_log2;
-  float* mine = lds + static_cast<size_t>(threadIdx.x) * NV;
+// The per-thread sums (2V values: V channels of two quantities) of a workgroup meet: rows of one wave by shuffles, the four
+// waves through LDS, in a fixed order.  Thread t < TX * V then owns channel t of the workgroup's column slice: true, with
+// the two sums.  (A tree over LDS with every thread's 16 values side by side took longer than a small layer's loads.)
+template <int V>
+__device__ __forceinline__ bool combine_sums(float* acc, float* lds, int tx_log2, float* t1, float* t2) {
+  const int TX = 1 << tx_log2, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (int off = TX; off < 64; off <<= 1) {
 #pragma unroll
-  for (int j = 0; j < NV; ++j) mine[j] = vals[j];
-  __syncthreads();
-  for (int s = TY >> 1; s >= 1; s >>= 1) {
-    if (trow < s) {
-      const float* other = lds + static_cast<size_t>((trow + s) * TX + tcol) * NV;
-#pragma unroll
-      for (int j = 0; j < NV; ++j) mine[j] += other[j];
-    }
-    __syncthreads();
+    for (int j = 0; j < 2 * V; ++j) acc[j] += __shfl_xor(acc[j], off, 64);
   }
+  if (lane < TX) {
 #pragma unroll
-  for (int j = 0; j < NV; ++j) vals[j] = mine[j];
+    for (int j = 0; j < 2 * V; ++j) lds[(wave * 2 * V + j) * TX + lane] = acc[j];
+  }
+  __syncthreads();
+  if (static_cast<int>(threadIdx.x) >= TX * V) return false;
+  const int col = threadIdx.x / V, j = threadIdx.x % V;
+  float a[4], b[4];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    a[w] = lds[(w * 2 * V + j) * TX + col];
+    b[w] = lds[(w * 2 * V + V + j) * TX + col];
+  }
+  *t1 = (a[0] + a[1]) + (a[2] + a[3]);
+  *t2 = (b[0] + b[1]) + (b[2] + b[3]);
+  return true;
 }
 
 // ------------------------------------------------------------------- forward
+// Sums of a row block, about a shift of its own channel's first element: channel-major float planes (shift, S1, S2) for
+// the finalize kernel, or (row_major) the doubles (sum x, sum x^2) per row block and channel for a self-finalizing apply
+// pass.  Bound by the bytes in flight: eight rows per thread are requested before the first is used (with four, and the
+// LDS tree at the end, 64 MB took 29 us).
 template <typename T>
 __global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ x, int64_t m, int C,
-                                                       int tx_log2, int rpb,
+                                                       int tx_log2, int rpb, int row_major,
                                                        float* __restrict__ partial) {
-  constexpr int V = Elem<T>::VEC;
-  extern __shared__ float lds[];
+  constexpr int V = Elem<T>::VEC, U = 8;
+  __shared__ float lds[4 * 2 * V * 32];
   const int TX = 1 << tx_log2, TY = 256 >> tx_log2;
   const int tcol = threadIdx.x & (TX - 1), trow = threadIdx.x >> tx_log2;
   const int col = blockIdx.y * TX + tcol;
-  const bool active = col < C / V;
   float acc[2 * V], K[V];
 #pragma unroll
   for (int j = 0; j < 2 * V; ++j) acc[j] = 0.f;
-  if (active) {
-    Elem<T>::unpack(load16(x + static_cast<int64_t>(col) * V), K);
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * rpb;
-    const int64_t r1 = min(r0 + rpb, m);
+  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * rpb;
+  const int64_t r1 = min(r0 + rpb, m);
+  if (col < C / V) {
     const T* p = x + static_cast<int64_t>(col) * V;
-    for (int64_t r = r0 + trow; r < r1; r += kBnRows * TY) {
-      Vec16 v[kBnRows];
+    const Vec16 k0 = load16(p);
+    Vec16 v[U];
+    bool first = true;
+    for (int64_t r = r0 + trow; r < r1; r += U * TY) {
 #pragma unroll
-      for (int u = 0; u < kBnRows; ++u) v[u] = load16(p + min(r + u * TY, r1 - 1) * C);
+      for (int u = 0; u < U; ++u) v[u] = load16(p + min(r + u * TY, r1 - 1) * C);
+      if (first) Elem<T>::unpack(k0, K);
+      first = false;
 #pragma unroll
-      for (int u = 0; u < kBnRows; ++u) {
+      for (int u = 0; u < U; ++u) {
         if (r + u * TY < r1) {
           float f[V];
           Elem<T>::unpack(v[u], f);
@@ -160,17 +191,22 @@ __global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ x, 
       }
     }
   }
-  combine_rows<2 * V>(acc, lds, tx_log2);
-  if (active && trow == 0) {
+  float t1, t2;
+  const int c = blockIdx.y * TX * V + threadIdx.x;
+  if (!combine_sums<V>(acc, lds, tx_log2, &t1, &t2) || c >= C) return;
+  const float k = Elem<T>::load(x + c);
+  if (row_major) {
+    const double kd = static_cast<double>(k), n = static_cast<double>(r1 - r0);
+    const double d1 = static_cast<double>(t1), d2 = static_cast<double>(t2);
+    reinterpret_cast<double2*>(partial)[static_cast<int64_t>(blockIdx.x) * C + c] =
+        make_double2(d1 + n * kd, d2 + kd * (2.0 * d1 + n * kd));
+  } else {
     // partial[plane][c][row]: the rows of one channel are contiguous for the finalize pass
     const int64_t nrows = gridDim.x;
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      float* o = partial + static_cast<int64_t>(col * V + j) * nrows + blockIdx.x;
-      o[0] = K[j];
-      o[C * nrows] = acc[j];
-      o[2 * C * nrows] = acc[V + j];
-    }
+    float* o = partial + static_cast<int64_t>(c) * nrows + blockIdx.x;
+    o[0] = k;
+    o[C * nrows] = t1;
+    o[2 * C * nrows] = t2;
   }
 }
 
@@ -498,9 +534,9 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(
     const T* __restrict__ z, const uint8_t* __restrict__ zmask, const float* __restrict__ gamma,
     const float* __restrict__ beta,
     const float* __restrict__ mean, const float* __restrict__ rstd, int64_t m, int C, int tx_log2,
-    int rpb, int mode, float* __restrict__ partial) {
+    int rpb, int mode, int row_major, float* __restrict__ partial) {
   constexpr int V = Elem<T>::VEC;
-  extern __shared__ float lds[];
+  __shared__ float lds[4 * 2 * V * 32];
   const int TX = 1 << tx_log2, TY = 256 >> tx_log2;
   const int tcol = threadIdx.x & (TX - 1), trow = threadIdx.x >> tx_log2;
   const int col = blockIdx.y * TX + tcol;
@@ -544,16 +580,14 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(
       }
     }
   }
-  combine_rows<2 * V>(acc, lds, tx_log2);
-  if (active && trow == 0) {
-    const int64_t nrows = gridDim.x;
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      float* o = partial + static_cast<int64_t>(col * V + j) * nrows + blockIdx.x;
-      o[0] = acc[j];
-      o[C * nrows] = acc[V + j];
-    }
-  }
+  float t1, t2;
+  const int c = blockIdx.y * TX * V + threadIdx.x;
+  if (!combine_sums<V>(acc, lds, tx_log2, &t1, &t2) || c >= C) return;
+  // planes (sum g, sum g * xhat): [plane][row block][C] for a self-finalizing apply pass, else [plane][C][row block]
+  const int64_t nrows = gridDim.x;
+  float* o = partial + (row_major ? static_cast<int64_t>(blockIdx.x) * C + c : static_cast<int64_t>(c) * nrows + blockIdx.x);
+  o[0] = t1;
+  o[C * nrows] = t2;
 }
 
 __global__ __launch_bounds__(256) void bn_bwd_finalize_kernel(const float* __restrict__ partial,
@@ -737,8 +771,8 @@ int bn_desc_check(const rn50_bn_desc* d, const char* who) { return check_desc(d,
 
 static size_t bn_ws_bytes(const rn50_bn_desc* d) {
   const int64_t m = static_cast<int64_t>(d->N) * d->H * d->W;
-  const BnGeom g = bn_geom(m, d->C, d->dtype);
-  return align_up(static_cast<size_t>(g.nblk) * 3 * d->C * sizeof(float), 256);
+  const BnGeom g = bn_sums_geom(m, d->C, d->dtype);
+  return align_up(static_cast<size_t>(g.nblk) * 4 * d->C * sizeof(float), 256);
 }
 
 // finalize + apply from partial statistics rows (see bn_finalize_kernel)
@@ -771,10 +805,10 @@ static void launch_fwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const 
                        const float* gamma, const float* beta, const void* residual, void* y,
                        uint8_t* relu_mask, float* save_mean, float* save_rstd, float* rm, float* rv,
                        float momentum, float* partial, hipStream_t s) {
-  const size_t lds = 256 * 2 * Elem<T>::VEC * sizeof(float);
-  RN50_LAUNCH("bn_stats", bn_stats_kernel<T>, dim3(g.nblk, g.gy), dim3(256), lds, s, static_cast<const T*>(x), m, d->C, g.tx_log2, g.rpb, partial);
+  const bool self = bn_self_sums(m);
+  RN50_LAUNCH("bn_stats", bn_stats_kernel<T>, dim3(g.nblk, g.gy), dim3(256), 0, s, static_cast<const T*>(x), m, d->C, g.tx_log2, g.rpb, self ? 1 : 0, partial);
   launch_fwd_tail<T>(d, g, m, x, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv, momentum,
-                     partial, g.nblk, g.rpb, false, s);
+                     partial, g.nblk, g.rpb, self, s);
 }
 
 // finalize + apply from partial sums rows [sum g, sum g*xhat]
@@ -824,11 +858,11 @@ static void launch_bwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const 
                        const void* dz2, const void* x, const void* z, const uint8_t* zmask,
                        const float* gamma, const float* beta, const float* mean, const float* rstd, void* dx,
                        void* dres, float* dgamma, float* dbeta, float* partial, hipStream_t s) {
-  const size_t lds = 256 * 2 * Elem<T>::VEC * sizeof(float);
+  const bool self = bn_self_sums(m);
 #define RN50_BWD_REDUCE(DZ2, ZK)                                                                                 \
-  RN50_LAUNCH("bn_bwd_reduce", (bn_bwd_reduce_kernel<T, DZ2, ZK>), dim3(g.nblk, g.gy), dim3(256), lds, s,          \
+  RN50_LAUNCH("bn_bwd_reduce", (bn_bwd_reduce_kernel<T, DZ2, ZK>), dim3(g.nblk, g.gy), dim3(256), 0, s,            \
               static_cast<const T*>(dz), static_cast<const T*>(dz2), static_cast<const T*>(x),                     \
-              static_cast<const T*>(z), zmask, gamma, beta, mean, rstd, m, d->C, g.tx_log2, g.rpb, d->mode, partial)
+              static_cast<const T*>(z), zmask, gamma, beta, mean, rstd, m, d->C, g.tx_log2, g.rpb, d->mode, self ? 1 : 0, partial)
   const int zk = d->mode == 0 ? 0 : (zmask ? 2 : (z ? 1 : 0));
   if (dz2) {
     if (zk == 2) RN50_BWD_REDUCE(true, 2); else if (zk == 1) RN50_BWD_REDUCE(true, 1); else RN50_BWD_REDUCE(true, 0);
@@ -837,7 +871,7 @@ static void launch_bwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const 
   }
 #undef RN50_BWD_REDUCE
   launch_bwd_tail<T>(d, g, m, dz, dz2, x, z, zmask, gamma, beta, mean, rstd, dx, dres, dgamma, dbeta, partial,
-                     g.nblk, false, s);
+                     g.nblk, self, s);
 }
 
 // Entry points for the whole-step driver and the fused C-ABI calls: the sums come from the output stage
@@ -917,7 +951,7 @@ extern "C" int bn_relu_fwd(const rn50_bn_desc* d, const void* x, const float* ga
   RN50_REQUIRE(workspace_bytes >= bn_ws_bytes(d), RN50_ERR_WORKSPACE,
                "bn_relu_fwd: workspace %zu < %zu bytes", workspace_bytes, bn_ws_bytes(d));
   const int64_t m = static_cast<int64_t>(d->N) * d->H * d->W;
-  const BnGeom g = bn_geom(m, d->C, d->dtype);
+  const BnGeom g = bn_sums_geom(m, d->C, d->dtype);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (d->dtype == RN50_BF16)
     launch_fwd<uint16_t>(d, g, m, x, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, running_mean,
@@ -947,7 +981,7 @@ extern "C" int bn_relu_bwd(const rn50_bn_desc* d, const void* dz, const void* dz
   RN50_REQUIRE(workspace_bytes >= bn_ws_bytes(d), RN50_ERR_WORKSPACE,
                "bn_relu_bwd: workspace %zu < %zu bytes", workspace_bytes, bn_ws_bytes(d));
   const int64_t m = static_cast<int64_t>(d->N) * d->H * d->W;
-  const BnGeom g = bn_geom(m, d->C, d->dtype);
+  const BnGeom g = bn_sums_geom(m, d->C, d->dtype);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (d->dtype == RN50_BF16)
     launch_bwd<uint16_t>(d, g, m, dz, dz2, x, z, relu_mask, gamma, beta, save_mean, save_rstd, dx, dresidual,

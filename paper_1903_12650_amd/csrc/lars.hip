@@ -135,7 +135,12 @@ __global__ __launch_bounds__(256) void lars_norms_kernel(const Args a) {
   }
 }
 
-template <bool GBF16, typename Args>
+// STREAM: v and the stores bypass the caches.  w and g come from the norms pass a moment ago and are the only reads that can
+// hit the last-level cache, v and the results are not looked at before the next update: let in, they push out what is still
+// to be read.  Where all of it fits (kLarsStreamElems), the next update finds its operands cached instead.
+// 14.4 M parameters, bf16 gradients: 77.0 -> 65.1 us; 25.6 M, float: 134.6 -> 129.1; 2.5 M: 18.5 -> 21.9, hence the line.
+constexpr int64_t kLarsStreamElems = 8 << 20;  // 96 MB of w, g and v
+template <bool GBF16, bool STREAM, typename Args>
 __global__ __launch_bounds__(256) void lars_apply_kernel(const Args a) {
   __shared__ float red[8];
   const int chunk = blockIdx.x;
@@ -165,7 +170,9 @@ __global__ __launch_bounds__(256) void lars_apply_kernel(const Args a) {
   uint16_t* lowp = static_cast<uint16_t*>(T.w_lowp);
   for (int64_t i = base + threadIdx.x * 4; i < vend; i += 1024) {
     float4 w4 = *reinterpret_cast<const float4*>(T.w + i);
-    float4 v4 = *reinterpret_cast<const float4*>(T.v + i);
+    const f32x4* vp = reinterpret_cast<const f32x4*>(T.v + i);
+    const f32x4 vv = STREAM ? __builtin_nontemporal_load(vp) : *vp;
+    float4 v4 = make_float4(vv[0], vv[1], vv[2], vv[3]);
     float g4[4];
     load_g4<GBF16>(T.g, i, g4);
     v4.x = mu * v4.x + step * (g4[0] + wd * w4.x);
@@ -173,8 +180,13 @@ __global__ __launch_bounds__(256) void lars_apply_kernel(const Args a) {
     v4.z = mu * v4.z + step * (g4[2] + wd * w4.z);
     v4.w = mu * v4.w + step * (g4[3] + wd * w4.w);
     w4.x -= v4.x; w4.y -= v4.y; w4.z -= v4.z; w4.w -= v4.w;
-    *reinterpret_cast<float4*>(T.v + i) = v4;
-    *reinterpret_cast<float4*>(T.w + i) = w4;
+    if (STREAM) {
+      __builtin_nontemporal_store(f32x4{v4.x, v4.y, v4.z, v4.w}, reinterpret_cast<f32x4*>(T.v + i));
+      __builtin_nontemporal_store(f32x4{w4.x, w4.y, w4.z, w4.w}, reinterpret_cast<f32x4*>(T.w + i));
+    } else {
+      *reinterpret_cast<float4*>(T.v + i) = v4;
+      *reinterpret_cast<float4*>(T.w + i) = w4;
+    }
     if (lowp) {
       uint2 p;
       p.x = float2_to_bf16x2_bits(w4.x, w4.y);
@@ -241,7 +253,10 @@ void lars_arena_run(const LarsArenaSpec& sp, float* master, const float* grads, 
     }
     const int grid = a.chunk_prefix[a.num];
     RN50_LAUNCH("lars_norms", (lars_norms_kernel<false, LarsArenaArgs>), dim3(grid), dim3(256), 0, s, a);
-    RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, LarsArenaArgs>), dim3(grid), dim3(256), 0, s, a);
+    if (static_cast<int64_t>(grid) * kLarsChunk > kLarsStreamElems)
+      RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, true, LarsArenaArgs>), dim3(grid), dim3(256), 0, s, a);
+    else
+      RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, false, LarsArenaArgs>), dim3(grid), dim3(256), 0, s, a);
     partial += 2 * static_cast<size_t>(grid);
   }
 }
@@ -272,12 +287,15 @@ static void run_table(const rn50_lars_desc* d, const rn50_lars_tensor* table_hos
     for (int t = 0; t < a.num; ++t)
       a.chunk_prefix[t + 1] = a.chunk_prefix[t] + static_cast<int>(ceil_div(table_host[t0 + t].n, kLarsChunk));
     const int grid = a.chunk_prefix[a.num];
+    const bool stream = static_cast<int64_t>(grid) * kLarsChunk > kLarsStreamElems;
     if (a.grad_bf16) {
       RN50_LAUNCH("lars_norms", (lars_norms_kernel<true, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
-      RN50_LAUNCH("lars_apply", (lars_apply_kernel<true, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
+      if (stream) RN50_LAUNCH("lars_apply", (lars_apply_kernel<true, true, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
+      else RN50_LAUNCH("lars_apply", (lars_apply_kernel<true, false, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
     } else {
       RN50_LAUNCH("lars_norms", (lars_norms_kernel<false, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
-      RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
+      if (stream) RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, true, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
+      else RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, false, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
     }
     partial += 2 * static_cast<size_t>(grid);
   }
