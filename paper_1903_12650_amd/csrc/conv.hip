@@ -660,7 +660,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       Vec16 av[NPASS];
 #pragma unroll
       for (int pass = 0; pass < NPASS; ++pass)
-        av[pass] = load16(add + (static_cast<int64_t>(min(m0 + orow + pass * RPP, a.M - 1)) * a.Ncols + nc));
+        av[pass] = load16_stream(add + (static_cast<int64_t>(min(m0 + orow + pass * RPP, a.M - 1)) * a.Ncols + nc));
 #pragma unroll
       for (int pass = 0; pass < NPASS; ++pass) {
         const int row = orow + pass * RPP, m = m0 + row;
@@ -736,7 +736,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       pix[pass] = classes ? pix_s[row] : min(m0 + row, a.M - 1);  // rows past the last read a valid pixel
       const int64_t at = static_cast<int64_t>(pix[pass]) * a.Ncols + nc;
       xv[pass] = load16(bx + at);
-      if (add) av[pass] = load16(add + at);
+      if (add) av[pass] = load16_stream(add + at);  // (its last reader)
       if (a.bn_zmask) zb[pass] = a.bn_zmask[at / V];
       ab[pass] = a.addend_mask ? a.addend_mask[at / V] : 0xffu;
     }
