@@ -259,6 +259,41 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     a_h0[i] = ok ? (FWD ? p * a.stride - a.pad : p + a.pad) : -(1 << 20);
     a_w0[i] = FWD ? q * a.stride - a.pad : q + a.pad;
   }
+  // What the output stage reads besides the tile: the BN layer's input, the second branch, recorded ReLU bits.  EARLY: requested
+  // here, in front of everything the main loop loads (the hand-placed load waits count in order, and these are the oldest), so
+  // that it is there when the last product is.  That is for workgroups that have a compute unit to themselves (KS: step at
+  // batch 4 2.03 -> 1.99 ms) and for the evaluation pass (4.68 -> 4.65 ms at batch 256); where several workgroups hide each
+  // other's latencies the registers cost more than the wait (step at batch 256 20.65 -> 20.9 ms).
+  constexpr bool EARLY = KS || AFF;
+  constexpr int PPR = BN * sizeof(T) / 16;  // 16-byte pieces per output row
+  constexpr int RPP = NT / PPR;             // rows per pass
+  constexpr int NPASS = BM / RPP;
+  const int op = tid % PPR, orow = tid / PPR;
+  const int n = n0 + op * V;
+  const bool col_ok = n < a.Ncols;
+  Vec16 xv[DG ? NPASS : 1], av[DG || AFF ? NPASS : 1];
+  uint32_t zb[DG ? NPASS : 1], ab[DG ? NPASS : 1];
+  auto load_output_operands = [&]() __attribute__((always_inline)) {
+    if (AFF ? a.addend == nullptr : a.partial == nullptr) return;
+    const T* add = static_cast<const T*>(a.addend);
+    const int nc = col_ok ? n : 0;
+#pragma unroll
+    for (int pass = 0; pass < NPASS; ++pass) {
+      const int row = orow + pass * RPP;
+      const int px = classes ? pix_s[row] : min(m0 + row, a.M - 1);  // rows past the last read a valid pixel
+      const int64_t at = static_cast<int64_t>(px) * a.Ncols + nc;
+      if constexpr (DG) {
+        xv[pass] = load16(static_cast<const T*>(a.bn_x) + at);
+        if (a.bn_zmask) zb[pass] = a.bn_zmask[at / V];
+        ab[pass] = a.addend_mask ? a.addend_mask[at / V] : 0xffu;
+      }
+      if (add) av[pass] = load16_stream(add + at);  // (its last reader)
+    }
+  };
+  if constexpr ((DG || AFF) && EARLY) {
+    if (classes) __syncthreads();  // (pix_s)
+    load_output_operands();
+  }
   // The B tile: BN rows (output columns) of one 128-byte chunk of K each, or (data gradient) BK rows (K) of BN columns.
   constexpr int BRB = BN * static_cast<int>(sizeof(T)), LB = BRB / 16;  // data gradient: bytes and 16-byte pieces per tile row
   const int b_krow = DG ? lt / LB : 0;                                 // ... this thread's tile row in load pass 0
@@ -647,20 +682,9 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     prm_s[tid] = sc; prm_s[BN + tid] = bi; prm_s[2 * BN + tid] = pr; prm_s[3 * BN + tid] = -pm * pr;
   }
   __syncthreads();
-  constexpr int PPR = BN * sizeof(T) / 16;  // 16-byte pieces per output row
-  constexpr int RPP = NT / PPR;             // rows per pass
-  constexpr int NPASS = BM / RPP;
   T* out = static_cast<T*>(a.out);
-  const int op = tid % PPR, orow = tid / PPR;
-  const int n = n0 + op * V;
   if constexpr (AFF) {
     if (a.addend != nullptr) {
-      const T* add = static_cast<const T*>(a.addend);
-      const int nc = n < a.Ncols ? n : 0;
-      Vec16 av[NPASS];
-#pragma unroll
-      for (int pass = 0; pass < NPASS; ++pass)
-        av[pass] = load16_stream(add + (static_cast<int64_t>(min(m0 + orow + pass * RPP, a.M - 1)) * a.Ncols + nc));
 #pragma unroll
       for (int pass = 0; pass < NPASS; ++pass) {
         const int row = orow + pass * RPP, m = m0 + row;
@@ -696,7 +720,6 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   }
 
   // Output stage with batch-norm sums: every thread owns V channels and NPASS rows of the tile.
-  const bool col_ok = n < a.Ncols;
   float s1[V], s2[V];
 #pragma unroll
   for (int j = 0; j < V; ++j) s1[j] = s2[j] = 0.f;
@@ -724,22 +747,8 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       }
     }
   } else {
-    const T* bx = static_cast<const T*>(a.bn_x);
-    const int nc = col_ok ? n : 0;
-    const T* add = static_cast<const T*>(a.addend);
-    Vec16 xv[NPASS], av[NPASS];
-    uint32_t zb[NPASS], ab[NPASS];
-    int pix[NPASS];
-#pragma unroll
-    for (int pass = 0; pass < NPASS; ++pass) {
-      const int row = orow + pass * RPP;
-      pix[pass] = classes ? pix_s[row] : min(m0 + row, a.M - 1);  // rows past the last read a valid pixel
-      const int64_t at = static_cast<int64_t>(pix[pass]) * a.Ncols + nc;
-      xv[pass] = load16(bx + at);
-      if (add) av[pass] = load16_stream(add + at);  // (its last reader)
-      if (a.bn_zmask) zb[pass] = a.bn_zmask[at / V];
-      ab[pass] = a.addend_mask ? a.addend_mask[at / V] : 0xffu;
-    }
+    const bool add = a.addend != nullptr;
+    if constexpr (!EARLY) load_output_operands();
     float scale[V], bias[V], rs[V], nmr[V];
 #pragma unroll
     for (int j = 0; j < V; ++j) {
@@ -773,7 +782,8 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         } else {
           v.u = *reinterpret_cast<const uint4*>(smem + row * CP + op * 16);
         }
-        *reinterpret_cast<uint4*>(out + (static_cast<int64_t>(pix[pass]) * a.Ncols + n)) = v.u;
+        const int pix = classes ? pix_s[row] : m0 + row;
+        *reinterpret_cast<uint4*>(out + (static_cast<int64_t>(pix) * a.Ncols + n)) = v.u;
         Elem<T>::unpack(v, g);  // the sums range over the stored (rounded) values
         Elem<T>::unpack(xv[pass], xf);
 #pragma unroll
