@@ -1108,6 +1108,7 @@ static PartialRows class_tile_rows(const rn50_conv_desc* d) {
   return PartialRows{bm, static_cast<int>(4 * ceil_div(rows, bm))};
 }
 PartialRows fwd_partial_rows(const rn50_conv_desc* d) {
+  if (const PartialRows pr = stem_partial_rows(d); pr.num) return pr;
   const int64_t M = static_cast<int64_t>(d->N) * out_dim(d->H, d->pad, d->R, d->stride) * out_dim(d->W, d->pad, d->S, d->stride);
   // the chunk count as the launch computes it (the bf16 stem runs as 4 taps of one chunk, the float stem as 7)
   const int chunks = is_stem(d) ? (d->dtype == RN50_BF16 ? 4 : 7) : d->R * d->S * chunks_per_tap(d->Cin, d->dtype);
@@ -1154,6 +1155,7 @@ static void set_affine(IgemmArgs& a, const BnAffine& f) {
 }
 void stem_fwd_padded(const rn50_conv_desc* d, const void* xp, const void* w, void* wp, void* y, float* bn_partial,
                      hipStream_t s, const BnAffine* affine) {
+  if (stem_fwd_run(d, xp, w, y, bn_partial, s, affine)) return;
   const int nw = d->Cout * kStemK;
   IgemmArgs a = stem_igemm_args(d, xp, wp, y);
   a.partial = bn_partial;

@@ -177,4 +177,11 @@ inline StemGeom stem_geom(const rn50_conv_desc* d) {
   return g;
 }
 
+
+// stem.hip: the bf16 stem from the padded image (false: a shape it does not take; the general kernel's turn), and the rows
+// of batch-norm sums it leaves (num = 0: likewise).
+bool stem_fwd_run(const rn50_conv_desc* d, const void* xp, const void* w, void* y, float* bn_partial, hipStream_t s,
+                  const BnAffine* affine);
+PartialRows stem_partial_rows(const rn50_conv_desc* d);
+
 }  // namespace rn50

@@ -165,6 +165,24 @@ def test_3x3_taps_never_reach_into_the_neighbouring_image(rn, mode_name):
         assert torch.isnan(b[1]).any()
 
 
+# The stem's own kernel: one and two output rows per tile, ragged pixel blocks, several tiles per workgroup, fewer than 64
+# filters; shapes it leaves to the general kernel.
+@pytest.mark.parametrize("N,H,W,K", [(1, 64, 64, 64), (40, 64, 64, 64), (2, 100, 100, 24), (1, 130, 130, 64), (2, 65, 140, 8),
+                                     (1, 30, 300, 64), (1, 66, 66, 64), (1, 64, 64, 72), (1, 16, 700, 64)])
+def test_stem_tiles(rn, N, H, W, K):
+    x = synth.activation_nhwc(SEED, "x", N, 3, H, W)
+    w = synth.conv_weight_krsc(SEED, "w", K, 3, 7, 7)
+    x, w = inputs("bf16", x, w)
+    y, handle = rn.conv_fwd_bn_sums(dev(x, True), dev(w, True), 2, 3)
+    assert_close(y, orc.conv_fwd(x, w, 2, 3), TOL["bf16"], "y")
+    assert torch.equal(y, rn.conv_fwd(dev(x, True), dev(w, True), 2, 3))
+    g, b = torch.ones(K, device="cuda"), torch.zeros(K, device="cuda")
+    _, mean, rstd = rn.bn_relu_fwd_from_sums(y, handle, g, b)
+    _, mean2, rstd2 = rn.bn_relu_fwd(y, g, b)
+    assert_close(mean, host(mean2), 1e-5, "mean")
+    assert_close(rstd, host(rstd2), 1e-5, "rstd")
+
+
 # Where the waves of a workgroup split the reduction (few output tiles, at least four 128-byte chunks): chunk counts that
 # are and are not multiples of four, ragged channels, the tile counts at which the tile changes, stride-2 pixel classes,
 # the channel count beyond which the linear forward kernel keeps the shared ring.
