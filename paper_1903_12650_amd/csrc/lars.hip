@@ -236,7 +236,7 @@ size_t lars_arena_partial_bytes(const LarsArenaSpec& sp) {
 
 void lars_arena_run(const LarsArenaSpec& sp, float* master, const float* grads, float* velocity, void* lowp,
                     float eta, float momentum, float lr, const float* lr_dev, float eps, float weight_decay,
-                    float* partial, hipStream_t s) {
+                    float* partial, int64_t arena_elems, hipStream_t s) {
   for (int t0 = 0; t0 < sp.num; t0 += kLarsArenaMaxTensors) {
     LarsArenaArgs a{};
     a.num = sp.num - t0 < kLarsArenaMaxTensors ? sp.num - t0 : kLarsArenaMaxTensors;
@@ -253,7 +253,7 @@ void lars_arena_run(const LarsArenaSpec& sp, float* master, const float* grads, 
     }
     const int grid = a.chunk_prefix[a.num];
     RN50_LAUNCH("lars_norms", (lars_norms_kernel<false, LarsArenaArgs>), dim3(grid), dim3(256), 0, s, a);
-    if (static_cast<int64_t>(grid) * kLarsChunk > kLarsStreamElems)
+    if (arena_elems > kLarsStreamElems)
       RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, true, LarsArenaArgs>), dim3(grid), dim3(256), 0, s, a);
     else
       RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, false, LarsArenaArgs>), dim3(grid), dim3(256), 0, s, a);

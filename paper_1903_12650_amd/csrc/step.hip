@@ -40,6 +40,14 @@ struct Tensor {
   int fan_in;  // weights: inputs per output (He scaling of the initializer); 0: BN gamma (ones); -1: zeros
 };
 
+// Tensors that the update takes in one go.  after: the backward pass's blocks (numbered as it meets them, the stem last)
+// whose weight gradients it waits for.
+struct LarsGroup {
+  LarsArenaSpec spec;
+  size_t scratch = 0;
+  int after = 0;
+};
+
 }  // namespace rn50
 
 struct rn50_plan {
@@ -55,10 +63,9 @@ struct rn50_plan {
   size_t ws_bytes = 0;
   size_t xp = 0, wp = 0, pool = 0, avg = 0, logits = 0, dlogits = 0, row_loss = 0, davg = 0;
   size_t g[5] = {0, 0, 0, 0, 0};
-  size_t wgrad_scratch = 0, bn_scratch = 0, lars_scratch = 0, pool_argmax = 0, fc_scratch = 0;
+  size_t wgrad_scratch = 0, bn_scratch = 0, pool_argmax = 0, fc_scratch = 0;
   size_t bn_scratch_bytes = 0, fc_scratch_bytes = 0;
-  rn50::LarsArenaSpec lars_rest, lars_stem;  // every tensor but the stem's weight / the stem's weight
-  size_t lars_stem_scratch = 0;
+  std::vector<rn50::LarsGroup> lars_groups;  // in the order in which the backward pass completes them
   // Second stream for the work that is off the step's critical path (the weight gradients), with the events that order it against the caller's stream.  Created at the first
   // step (default priority), destroyed with the plan.
   hipStream_t side = nullptr;
@@ -112,6 +119,47 @@ size_t bump(size_t* top, size_t bytes) {
   const size_t at = *top;
   *top += align_up(bytes, 256);
   return at;
+}
+
+// The update by groups.  A block's tensors have their last reader in its own data gradients, so they can be updated as soon
+// as the backward pass has left the block, beside what is left of it: 40 % of the parameters belong to the first two blocks
+// it meets, and the layers it goes through next work out of the caches and leave the memory idle.  A group is closed at the
+// first block that brings it to kLarsGroupElems (smaller ones pay two launches for less than their latency); what the
+// last blocks leave, with the stem's BN, is one group behind the backward pass, and the stem's weight, whose
+// gradient is the last thing to arrive, is one of its own.
+constexpr int64_t kLarsGroupElems = 4 << 20;
+void plan_lars_groups(rn50_plan* p) {
+  const int stem_w = p->units[0].iw, fcw = static_cast<int>(p->tensors.size()) - 2, nb = static_cast<int>(p->blocks.size());
+  LarsGroup g;
+  int64_t elems = 0;
+  auto take = [&](int i) {
+    const Tensor& t = p->tensors[i];
+    g.spec.offset.push_back(t.offset);
+    g.spec.count.push_back(t.count);
+    g.spec.decay.push_back(t.decay ? 1 : 0);
+    ++g.spec.num;
+    elems += t.count;
+  };
+  auto close = [&](int after) {
+    g.after = after;
+    p->lars_groups.push_back(g);
+    g = LarsGroup();
+    elems = 0;
+  };
+  take(fcw);
+  take(fcw + 1);
+  for (int bi = nb - 1; bi >= 0; --bi) {
+    const Block& b = p->blocks[bi];
+    for (int u : {b.u1, b.u2, b.u3, b.up})
+      if (u >= 0)
+        for (int i : {p->units[u].iw, p->units[u].ig, p->units[u].ib}) take(i);
+    if (bi > 0 && elems >= kLarsGroupElems) close(nb - 1 - bi);
+  }
+  take(p->units[0].ig);
+  take(p->units[0].ib);
+  close(nb - 1);
+  take(stem_w);
+  close(nb);
 }
 
 }  // namespace
@@ -214,18 +262,8 @@ extern "C" int resnet_plan_create(const rn50_step_config* cfg, rn50_plan** plan_
   p->bn_scratch = bump(&top, max_bn);
   p->bn_scratch2 = bump(&top, max_bn);
   p->bn_scratch_bytes = max_bn;
-  // The stem's weight gradient is the last thing the backward pass produces; the update of every other
-  // tensor runs beside it.
-  for (size_t i = 0; i < p->tensors.size(); ++i) {
-    const Tensor& t = p->tensors[i];
-    LarsArenaSpec& sp = i == static_cast<size_t>(p->units[0].iw) ? p->lars_stem : p->lars_rest;
-    sp.offset.push_back(t.offset);
-    sp.count.push_back(t.count);
-    sp.decay.push_back(t.decay ? 1 : 0);
-    ++sp.num;
-  }
-  p->lars_scratch = bump(&top, lars_arena_partial_bytes(p->lars_rest));
-  p->lars_stem_scratch = bump(&top, lars_arena_partial_bytes(p->lars_stem));
+  plan_lars_groups(p);
+  for (LarsGroup& g : p->lars_groups) g.scratch = bump(&top, lars_arena_partial_bytes(g.spec));
   p->ws_bytes = top;
   *plan_out = owner.release();
   return RN50_OK;
@@ -519,6 +557,12 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
   };
   PendingWgrad pending[4];
   int npending = 0, blk = 0;  // blocks processed so far in this backward pass
+  void* const lowp = cfg.dtype == RN50_BF16 ? model : nullptr;
+  auto update_group = [&](const LarsGroup& g, hipStream_t st) {
+    lars_arena_run(g.spec, master, grads, velocity, lowp, cfg.eta, cfg.momentum, lr, lr_dev, cfg.lars_eps, cfg.weight_decay,
+                   F(g.scratch), plan->arena_elems, st);
+  };
+  size_t next_group = 0;
   auto block_end = [&]() {
     (void)hipEventRecord(plan->ev_dy[blk], s);
     (void)hipStreamWaitEvent(side, plan->ev_dy[blk], 0);
@@ -529,6 +573,8 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
     for (int i = 0; i < npending; ++i)
       wgrad_run(&pending[i].u->conv, pending[i].in, pending[i].dy, G(pending[i].u->iw), ws + plan->wgrad_scratch, side,
                 pending[i].bn_in ? &pending[i].bn : nullptr);
+    if (update && next_group + 2 < plan->lars_groups.size() && plan->lars_groups[next_group].after == blk)
+      update_group(plan->lars_groups[next_group++], side);
     (void)hipEventRecord(plan->ev_wg[blk], side);
     npending = 0;
     ++blk;
@@ -636,18 +682,13 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
   STEP_TRY(unit_bwd(u0, ws + plan->xp, dz_next, nullptr, nullptr, nullptr, false, nullptr, nullptr));
   block_end();
   // ------------------------------------------------------------------ LARS
-  // The side stream runs in order: the event of the last block but one covers every weight gradient
-  // except the stem's, which is still running while the other tensors are updated.
-  void* lowp = cfg.dtype == RN50_BF16 ? model : nullptr;
-  if (update) {
-    if (blk >= 2) (void)hipStreamWaitEvent(s, plan->ev_wg[blk - 2], 0);
-    lars_arena_run(plan->lars_rest, master, grads, velocity, lowp, cfg.eta, cfg.momentum, lr, lr_dev, cfg.lars_eps,
-                   cfg.weight_decay, F(plan->lars_scratch), s);
-  }
+  // (the groups before these two went with their blocks)  The side stream runs in order: the event of the last block but
+  // one covers every weight gradient except the stem's, which is still running while the others are updated.
+  const size_t ng = plan->lars_groups.size();
+  (void)hipStreamWaitEvent(s, plan->ev_wg[blk - 2], 0);
+  if (update) update_group(plan->lars_groups[ng - 2], s);
   (void)hipStreamWaitEvent(s, plan->ev_wg[blk - 1], 0);  // join
-  if (update)
-    lars_arena_run(plan->lars_stem, master, grads, velocity, lowp, cfg.eta, cfg.momentum, lr, lr_dev, cfg.lars_eps,
-                   cfg.weight_decay, F(plan->lars_stem_scratch), s);
+  if (update) update_group(plan->lars_groups[ng - 1], s);
   return launch_status(who);
 }
 

@@ -117,6 +117,6 @@ struct LarsArenaSpec {
 size_t lars_arena_partial_bytes(const LarsArenaSpec& sp);
 void lars_arena_run(const LarsArenaSpec& sp, float* master, const float* grads, float* velocity, void* lowp,
                     float eta, float momentum, float lr, const float* lr_dev, float eps, float weight_decay,
-                    float* partial, hipStream_t s);
+                    float* partial, int64_t arena_elems, hipStream_t s);
 
 }  // namespace rn50
