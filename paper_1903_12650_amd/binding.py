@@ -5,7 +5,9 @@ enqueued on torch's current stream.  There is no CPU fallback: importing this
 module fails loudly when the library has not been built.
 """
 import ctypes
+import functools
 import os
+import struct
 
 import torch
 
@@ -79,20 +81,45 @@ for _n in ("resnet_plan_tensor_shape", "resnet_plan_tensor_offset", "resnet_plan
         getattr(raw, _n).restype = ctypes.c_int64
 
 
+# The operations that are called once per layer take a few microseconds of GPU time at small batches, so what the call costs
+# in Python counts: their argument types are declared (plain ints are passed as pointers and sizes, no ctypes object is made
+# per argument), descriptors and workspace sizes are kept per shape, and the stream is asked for as a number.  `raw` stays undeclared for direct use.
+_P, _I, _F, _Z = ctypes.c_void_p, ctypes.c_int, ctypes.c_float, ctypes.c_size_t
+_lib = ctypes.CDLL(lib_path())
+for _n, _a in (("conv_fwd", (_P,) * 5 + (_Z, _P)), ("conv_dgrad", (_P,) * 5 + (_Z, _P)), ("conv_wgrad", (_P,) * 5 + (_Z, _P)),
+               ("bn_relu_fwd", (_P,) * 11 + (_F, _P, _Z, _P)), ("bn_relu_bwd", (_P,) * 15 + (_Z, _P)),
+               ("lars_update", (_P,) * 5 + (_Z, _P)),
+               ("resnet_step", (_P,) * 7 + (_F, _I, _P, _P, _P, _Z, _P)),
+               ("resnet_train_step", (_P,) * 3 + (_F,) + (_P,) * 9 + (_Z, _P)),
+               ("resnet_eval", (_P,) * 10 + (_Z, _P))):
+    getattr(_lib, _n).argtypes = _a
+_current_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
+
+
 def _check(rc):
     if rc != 0:
         raise Rn50Error(rc, raw.rn50_last_error().decode())
 
 
-def _ptr(t):
+def _addr(t):
+    """Address of a tensor (None: a null pointer), for the functions with declared argument types."""
     if t is None:
-        return ctypes.c_void_p(0)
+        return None
     assert t.is_cuda and t.is_contiguous(), "device, contiguous tensors only"
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _ptr(t):
+    return ctypes.c_void_p(_addr(t))
+
+
+def _raw_stream():
+    return _current_raw_stream(_current_device())
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream())
 
 
 def _dt(t):
@@ -127,38 +154,42 @@ def conv_wgrad_workspace_bytes(desc):
     return raw.conv_wgrad_workspace_bytes(ctypes.byref(desc))
 
 
-def conv_fwd(x, w, stride, pad, y=None, workspace=None):
-    d = _conv_desc(x.shape, w.shape, stride, pad, _dt(x))
+@functools.lru_cache(maxsize=1024)
+def _conv_call(x_shape, w_shape, stride, pad, dtype, workspace_bytes):
+    """What a call of this shape needs besides its tensors: descriptor (by reference), output shape, workspace bytes."""
+    d = _conv_desc(x_shape, w_shape, stride, pad, dtype)
     P = (d.H + 2 * pad - d.R) // stride + 1
     Q = (d.W + 2 * pad - d.S) // stride + 1
+    return ctypes.byref(d), (d.N, P, Q, d.Cout), workspace_bytes(d)
+
+
+def conv_fwd(x, w, stride, pad, y=None, workspace=None):
+    d, y_shape, need = _conv_call(x.shape, w.shape, stride, pad, _dt(x), conv_fwd_workspace_bytes)
     if y is None:
-        y = torch.empty((d.N, P, Q, d.Cout), dtype=x.dtype, device=x.device)
+        y = torch.empty(y_shape, dtype=x.dtype, device=x.device)
     if workspace is None:
-        workspace = _ws(conv_fwd_workspace_bytes(d), x.device)
-    _check(raw.conv_fwd(ctypes.byref(d), _ptr(x), _ptr(w), _ptr(y), _ptr(workspace),
-                        ctypes.c_size_t(workspace.numel()), _stream()))
+        workspace = _ws(need, x.device)
+    _check(_lib.conv_fwd(d, _addr(x), _addr(w), _addr(y), _addr(workspace), workspace.numel(), _raw_stream()))
     return y
 
 
 def conv_dgrad(dy, w, x_shape, stride, pad, dx=None, workspace=None):
-    d = _conv_desc(x_shape, w.shape, stride, pad, _dt(dy))
+    d, _, need = _conv_call(tuple(x_shape), w.shape, stride, pad, _dt(dy), conv_dgrad_workspace_bytes)
     if dx is None:
         dx = torch.empty(tuple(x_shape), dtype=dy.dtype, device=dy.device)
     if workspace is None:
-        workspace = _ws(conv_dgrad_workspace_bytes(d), dy.device)
-    _check(raw.conv_dgrad(ctypes.byref(d), _ptr(dy), _ptr(w), _ptr(dx), _ptr(workspace),
-                          ctypes.c_size_t(workspace.numel()), _stream()))
+        workspace = _ws(need, dy.device)
+    _check(_lib.conv_dgrad(d, _addr(dy), _addr(w), _addr(dx), _addr(workspace), workspace.numel(), _raw_stream()))
     return dx
 
 
 def conv_wgrad(x, dy, w_shape, stride, pad, dw=None, workspace=None):
-    d = _conv_desc(x.shape, w_shape, stride, pad, _dt(x))
+    d, _, need = _conv_call(x.shape, tuple(w_shape), stride, pad, _dt(x), conv_wgrad_workspace_bytes)
     if dw is None:
         dw = torch.empty(tuple(w_shape), dtype=torch.float32, device=x.device)
     if workspace is None:
-        workspace = _ws(conv_wgrad_workspace_bytes(d), x.device)
-    _check(raw.conv_wgrad(ctypes.byref(d), _ptr(x), _ptr(dy), _ptr(dw), _ptr(workspace),
-                          ctypes.c_size_t(workspace.numel()), _stream()))
+        workspace = _ws(need, x.device)
+    _check(_lib.conv_wgrad(d, _addr(x), _addr(dy), _addr(dw), _addr(workspace), workspace.numel(), _raw_stream()))
     return dw
 
 
@@ -182,35 +213,41 @@ def relu_mask_like(x):
     return torch.empty(x.numel() // V, dtype=torch.uint8, device=x.device)
 
 
+@functools.lru_cache(maxsize=1024)
+def _bn_call(shape, eps, dtype, mode):
+    """Descriptor (by reference), channels, workspace bytes of either direction."""
+    C = shape[-1]
+    d = BnDesc(*shape[:3], C, eps, dtype, mode) if len(shape) == 4 else BnDesc(1, 1, shape.numel() // C, C, eps, dtype, mode)
+    return ctypes.byref(d), C, max(bn_relu_fwd_workspace_bytes(d), bn_relu_bwd_workspace_bytes(d))
+
+
 def bn_relu_fwd(x, gamma, beta, residual=None, eps=1e-5, mode=1, running_mean=None, running_var=None,
                 momentum=0.9, workspace=None, relu_mask=None):
     """Returns y, save_mean, save_rstd.  relu_mask: optional uint8 tensor (see relu_mask_like) to fill."""
-    d = _bn_desc(x, eps, mode)
+    d, C, need = _bn_call(x.shape, eps, _dt(x), mode)
     y = torch.empty_like(x)
-    mean = torch.empty(d.C, dtype=torch.float32, device=x.device)
-    rstd = torch.empty(d.C, dtype=torch.float32, device=x.device)
+    mean = torch.empty(C, dtype=torch.float32, device=x.device)
+    rstd = torch.empty_like(mean)
     if workspace is None:
-        workspace = _ws(bn_relu_fwd_workspace_bytes(d), x.device)
-    _check(raw.bn_relu_fwd(ctypes.byref(d), _ptr(x), _ptr(gamma), _ptr(beta), _ptr(residual), _ptr(y),
-                           _ptr(relu_mask), _ptr(mean),
-                           _ptr(rstd), _ptr(running_mean), _ptr(running_var), ctypes.c_float(momentum),
-                           _ptr(workspace), ctypes.c_size_t(workspace.numel()), _stream()))
+        workspace = _ws(need, x.device)
+    _check(_lib.bn_relu_fwd(d, _addr(x), _addr(gamma), _addr(beta), _addr(residual), _addr(y), _addr(relu_mask), _addr(mean),
+                            _addr(rstd), _addr(running_mean), _addr(running_var), momentum, _addr(workspace),
+                            workspace.numel(), _raw_stream()))
     return y, mean, rstd
 
 
 def bn_relu_bwd(dz, x, z, gamma, mean, rstd, mode=1, beta=None, dz2=None, eps=1e-5, workspace=None, relu_mask=None):
     """Returns dx, dresidual (None unless mode 2), dgamma, dbeta."""
-    d = _bn_desc(x, eps, mode)
+    d, C, need = _bn_call(x.shape, eps, _dt(x), mode)
     dx = torch.empty_like(x)
     dres = torch.empty_like(x) if mode == 2 else None
-    dgamma = torch.empty(d.C, dtype=torch.float32, device=x.device)
-    dbeta = torch.empty(d.C, dtype=torch.float32, device=x.device)
+    dgamma = torch.empty(C, dtype=torch.float32, device=x.device)
+    dbeta = torch.empty_like(dgamma)
     if workspace is None:
-        workspace = _ws(bn_relu_bwd_workspace_bytes(d), x.device)
-    _check(raw.bn_relu_bwd(ctypes.byref(d), _ptr(dz), _ptr(dz2), _ptr(x), _ptr(z), _ptr(relu_mask), _ptr(gamma),
-                           _ptr(beta),
-                           _ptr(mean), _ptr(rstd), _ptr(dx), _ptr(dres), _ptr(dgamma), _ptr(dbeta),
-                           _ptr(workspace), ctypes.c_size_t(workspace.numel()), _stream()))
+        workspace = _ws(need, x.device)
+    _check(_lib.bn_relu_bwd(d, _addr(dz), _addr(dz2), _addr(x), _addr(z), _addr(relu_mask), _addr(gamma), _addr(beta),
+                            _addr(mean), _addr(rstd), _addr(dx), _addr(dres), _addr(dgamma), _addr(dbeta), _addr(workspace),
+                            workspace.numel(), _raw_stream()))
     return dx, dres, dgamma, dbeta
 
 
@@ -369,6 +406,10 @@ def xent_fwd_bwd(logits, labels, label_smoothing=0.0, grad_scale=1.0):
 
 
 # ----------------------------------------------------------------------- LARS
+_LARS_ENTRY = struct.Struct("=4QqfI")  # LarsTensor
+assert _LARS_ENTRY.size == ctypes.sizeof(LarsTensor)
+
+
 class LarsTable:
     """Host and device copies of the tensor table of lars_update (built once, reused every step)."""
 
@@ -378,24 +419,28 @@ class LarsTable:
         self.host = (LarsTensor * T)()
         self.keep = (ws, gs, vs, w_lowp)
         self.grad_dtype = _dt(gs[0])
+        g_type, f32 = gs[0].dtype, torch.float32
         for t in range(T):
-            assert ws[t].dtype == torch.float32 and vs[t].dtype == torch.float32
-            assert ws[t].numel() == gs[t].numel() == vs[t].numel() and _dt(gs[t]) == self.grad_dtype
+            w, g, v = ws[t], gs[t], vs[t]
+            n = w.numel()
+            assert w.dtype == f32 and v.dtype == f32
+            assert n == g.numel() and n == v.numel() and g.dtype == g_type
             lp = w_lowp[t] if w_lowp is not None else None
-            self.host[t] = LarsTensor(ws[t].data_ptr(), gs[t].data_ptr(), vs[t].data_ptr(),
-                                      lp.data_ptr() if lp is not None else 0, ws[t].numel(),
-                                      float(weight_decays[t]), int(1 if apply_trust is None else apply_trust[t]))
-        blob = bytes(self.host)
-        self.dev = torch.frombuffer(bytearray(blob), dtype=torch.uint8).to(ws[0].device)
+            _LARS_ENTRY.pack_into(self.host, t * _LARS_ENTRY.size, w.data_ptr(), g.data_ptr(), v.data_ptr(),
+                                  lp.data_ptr() if lp is not None else 0, n, weight_decays[t],
+                                  1 if apply_trust is None else int(apply_trust[t]))
+        # from pinned memory the copy is queued like a kernel: nothing waits for the work in front of it
         self.device = ws[0].device
+        table = torch.frombuffer(self.host, dtype=torch.uint8)
+        self.dev = table.pin_memory().to(self.device, non_blocking=True) if ws[0].is_cuda else table.to(self.device)
 
 
 def lars_update(table, eta, momentum, lr, eps=0.0, norms_out=None, workspace=None):
     d = LarsDesc(table.T, eta, momentum, lr, eps, table.grad_dtype)
     if workspace is None:
         workspace = _ws(raw.lars_update_workspace_bytes(ctypes.byref(d), table.host), table.device)
-    _check(raw.lars_update(ctypes.byref(d), table.host, _ptr(table.dev), _ptr(norms_out), _ptr(workspace),
-                           ctypes.c_size_t(workspace.numel()), _stream()))
+    _check(_lib.lars_update(ctypes.byref(d), ctypes.addressof(table.host), _addr(table.dev), _addr(norms_out),
+                            _addr(workspace), workspace.numel(), _raw_stream()))
     return norms_out
 
 
@@ -447,9 +492,9 @@ def resnet_step(plan, images, labels, master, velocity, grads, model, lr, worksp
                 logits_out=None):
     if loss_out is None:
         loss_out = torch.empty(1, dtype=torch.float32, device=images.device)
-    _check(raw.resnet_step(plan.handle, _ptr(images), _ptr(labels), _ptr(master), _ptr(velocity), _ptr(grads),
-                           _ptr(model), ctypes.c_float(lr), int(bool(update)), _ptr(loss_out), _ptr(logits_out),
-                           _ptr(workspace), ctypes.c_size_t(workspace.numel()), _stream()))
+    _check(_lib.resnet_step(plan.handle, _addr(images), _addr(labels), _addr(master), _addr(velocity), _addr(grads),
+                            _addr(model), lr, int(bool(update)), _addr(loss_out), _addr(logits_out), _addr(workspace),
+                            workspace.numel(), _raw_stream()))
     return loss_out
 
 
@@ -519,10 +564,9 @@ def resnet_train_step(plan, schedule, state, images, labels, master, velocity, g
                       loss_out=None, logits_out=None):
     if loss_out is None:
         loss_out = torch.empty(1, dtype=torch.float32, device=images.device)
-    _check(raw.resnet_train_step(plan.handle, ctypes.byref(schedule), _ptr(state.buf), ctypes.c_float(bn_momentum),
-                                 _ptr(images), _ptr(labels), _ptr(master), _ptr(velocity), _ptr(grads), _ptr(model),
-                                 _ptr(loss_out), _ptr(logits_out), _ptr(workspace), ctypes.c_size_t(workspace.numel()),
-                                 _stream()))
+    _check(_lib.resnet_train_step(plan.handle, ctypes.byref(schedule), _addr(state.buf), bn_momentum, _addr(images),
+                                  _addr(labels), _addr(master), _addr(velocity), _addr(grads), _addr(model),
+                                  _addr(loss_out), _addr(logits_out), _addr(workspace), workspace.numel(), _raw_stream()))
     return loss_out
 
 
@@ -553,9 +597,9 @@ def resnet_eval(plan, state, images, labels, master, model, workspace, logits_ou
     """Returns (pred int32[N], correct int32[1]) device tensors."""
     pred = torch.empty(plan.N, dtype=torch.int32, device=images.device)
     correct = torch.empty(1, dtype=torch.int32, device=images.device)
-    _check(raw.resnet_eval(plan.handle, _ptr(state.buf), _ptr(images), _ptr(labels), _ptr(master), _ptr(model),
-                           _ptr(logits_out), _ptr(pred), _ptr(correct), _ptr(workspace),
-                           ctypes.c_size_t(workspace.numel()), _stream()))
+    _check(_lib.resnet_eval(plan.handle, _addr(state.buf), _addr(images), _addr(labels), _addr(master), _addr(model),
+                            _addr(logits_out), _addr(pred), _addr(correct), _addr(workspace), workspace.numel(),
+                            _raw_stream()))
     return pred, correct
 
 
