@@ -15,12 +15,10 @@
 // output tile): the *_from_partials entry points then run finalize + apply only.
 // Partial sums are combined in a fixed order, so results are bitwise reproducible.
 //
-// Variance uses shifted sums: every row of partials carries its own shift K (the
-// first element its producer saw), S1 = sum(x-K), S2 = sum((x-K)^2); the finalize
-// pass moves all rows to the first row's shift exactly, in double, and then
-//   mean = K + S1/m, var = S2/m - (S1/m)^2,
-// which removes the cancellation of the plain E[x^2]-E[x]^2 form whenever K lies
-// within a few standard deviations of the mean.
+// Variance uses shifted sums: every row of partials is summed in float about a shift K of its own (the first
+// element its producer saw), S1 = sum(x-K), S2 = sum((x-K)^2), and stored either moved to shift 0, in double, or as
+// its mean K + S1/n and the squared deviations from it, S2 - S1^2/n.  Nowhere does float rounding see the cancellation
+// of the plain E[x^2]-E[x]^2 form.  (Forms and layout of the rows: bn_sums_at.)
 #include <stdlib.h>
 
 #include <algorithm>
@@ -62,20 +60,26 @@ static BnGeom bn_geom(int64_t m, int C, int dtype) {
   return g;
 }
 
-// Geometry of the stand-alone sums passes (statistics, backward sums).  Layers of at most kBnSelfRows rows are summed in at
-// most 128 row blocks of at least 32 rows, row-major, and their apply pass finalizes by itself (bn_apply_kernel's FIN): a
-// finalize launch costs about 4 us whatever it computes, reading 128 rows of sums in every apply workgroup 1 to 2.  Beyond
-// that, 128 row blocks would leave a block more than 256 rows and the chip too few of them.
-constexpr int64_t kBnSelfRows = 32768;
-static bool bn_self_sums(int64_t m) { return m <= kBnSelfRows; }
+// Geometry of the stand-alone sums passes (statistics, backward sums).  Small layers are summed in at most 128 row blocks of
+// at least 32 rows, row-major, and their apply pass finalizes by itself (bn_apply_kernel's FIN): a finalize launch costs
+// about 4 us whatever it computes, reading 128 rows of sums in every apply workgroup 1 to 2 -- as long as the workgroups
+// are few: beyond kBnSelfElems the sums they read together are as many bytes as the tensor.
+// Larger layers: up to kBnSumsGroups workgroups whose threads load their eight rows (kBnSumsRows) once.  Workgroups that
+// loop over more rows all load at the same time and all compute at the same time.
+constexpr int64_t kBnSelfRows = 32768, kBnSelfElems = 4 << 20;
+constexpr int kBnSumsGroups = 4096, kBnSumsRows = 8;
+static bool bn_self_sums(int64_t m, int C) { return m <= kBnSelfRows && m * C <= kBnSelfElems; }
 static BnGeom bn_sums_geom(int64_t m, int C, int dtype) {
   BnGeom g = bn_geom(m, C, dtype);
-  if (bn_self_sums(m)) {
-    const int TY = 256 >> g.tx_log2;
+  const int TY = 256 >> g.tx_log2;
+  if (bn_self_sums(m, C)) {
     const int64_t rows = std::max<int64_t>(ceil_div(m, 128), 32);
     g.rpb = static_cast<int>(ceil_div(rows, TY) * TY);
-    g.nblk = static_cast<int>(ceil_div(m, g.rpb));
+  } else {
+    const int64_t rows = ceil_div(m * g.gy, static_cast<int64_t>(TY) * kBnSumsGroups);  // per thread
+    g.rpb = static_cast<int>(ceil_div(rows, kBnSumsRows) * kBnSumsRows) * TY;
   }
+  g.nblk = static_cast<int>(ceil_div(m, g.rpb));
   return g;
 }
 
@@ -148,15 +152,13 @@ __device__ __forceinline__ bool combine_sums(float* acc, float* lds, int tx_log2
 }
 
 // ------------------------------------------------------------------- forward
-// Sums of a row block, about a shift of its own channel's first element: channel-major float planes (shift, S1, S2) for
-// the finalize kernel, or (row_major) the doubles (sum x, sum x^2) per row block and channel for a self-finalizing apply
-// pass.  Bound by the bytes in flight: eight rows per thread are requested before the first is used (with four, and the
+// Sums of a row block, about a shift of its own channel's first element, stored in either form (wide: doubles).  Bound by the bytes in flight: eight rows per thread are requested before the first is used (with four, and the
 // LDS tree at the end, 64 MB took 29 us).
 template <typename T>
 __global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ x, int64_t m, int C,
-                                                       int tx_log2, int rpb, int row_major,
+                                                       int tx_log2, int rpb, int wide,
                                                        float* __restrict__ partial) {
-  constexpr int V = Elem<T>::VEC, U = 8;
+  constexpr int V = Elem<T>::VEC, U = kBnSumsRows;
   __shared__ float lds[4 * 2 * V * 32];
   const int TX = 1 << tx_log2, TY = 256 >> tx_log2;
   const int tcol = threadIdx.x & (TX - 1), trow = threadIdx.x >> tx_log2;
@@ -195,112 +197,83 @@ __global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ x, 
   const int c = blockIdx.y * TX * V + threadIdx.x;
   if (!combine_sums<V>(acc, lds, tx_log2, &t1, &t2) || c >= C) return;
   const float k = Elem<T>::load(x + c);
-  if (row_major) {
-    const double kd = static_cast<double>(k), n = static_cast<double>(r1 - r0);
-    const double d1 = static_cast<double>(t1), d2 = static_cast<double>(t2);
-    reinterpret_cast<double2*>(partial)[static_cast<int64_t>(blockIdx.x) * C + c] =
-        make_double2(d1 + n * kd, d2 + kd * (2.0 * d1 + n * kd));
-  } else {
-    // partial[plane][c][row]: the rows of one channel are contiguous for the finalize pass
-    const int64_t nrows = gridDim.x;
-    float* o = partial + static_cast<int64_t>(c) * nrows + blockIdx.x;
-    o[0] = k;
-    o[C * nrows] = t1;
-    o[2 * C * nrows] = t2;
-  }
+  const int64_t at = bn_sums_at(blockIdx.x, c, gridDim.x);
+  if (wide) reinterpret_cast<double2*>(partial)[at] = bn_tile_sums(k, t1, t2, static_cast<int>(r1 - r0));
+  else reinterpret_cast<float2*>(partial)[at] = bn_tile_moments(k, t1, t2, static_cast<int>(r1 - r0));
 }
 
-// Finalize passes.  The partial sums lie as partial[plane][c][row], `nrows` rows per channel, so one wave
-// reads the rows of one channel with contiguous 256-byte loads.  A workgroup serves 4/wpc channels with
-// wpc (1 or 4) waves each; lane l of wave w adds rows (w*64 + l) + 64*wpc*i, i = 0, 1, ... in order, then
-// the lanes are combined by a fixed butterfly and the waves in order: all in double, a fixed order.
-__device__ __forceinline__ double wave_sum_double(double v) {
+// Finalize passes, for layers with more rows of partial sums than an apply pass should add up itself.  A workgroup takes
+// kFinCh of the eight channels whose rows are contiguous: thread (channel ch, group g) adds rows g, g + G, ... in order,
+// kFinRows of them requested at once, then the G groups are added by a fixed tree; all in double.  The pass is a chain of
+// load latencies in front of everything that follows it, so there are as many groups as leave a thread a few rows; and its
+// workgroups are small, because beside the weight gradients one of sixteen waves waits for a compute unit to empty.
+constexpr int kFinCh = 2, kFinRows = 8, kFinThreads = 256;
+static int finalize_grid(int C) { return static_cast<int>(ceil_div(C, kFinCh)); }
+// Adds (s1, s2) over the groups of the workgroup; the totals of channel ch are in the threads of group 0.
+__device__ __forceinline__ void finalize_combine(double* s1, double* s2) {
+  __shared__ double red[2][kFinThreads / 64][kFinCh];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ch = threadIdx.x % kFinCh;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-// Combines (s1, s2) over the waves of a channel; true in lane 0 of the channel's first wave, with the totals.
-__device__ __forceinline__ bool finalize_combine(double* s1, double* s2, int wpc, int c, int C) {
-  __shared__ double red[2][4];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  double a = wave_sum_double(*s1), b = wave_sum_double(*s2);
-  if (wpc == 1) {
-    *s1 = a; *s2 = b;
-    return lane == 0 && c < C;
+  for (int off = 32; off >= kFinCh; off >>= 1) {
+    *s1 += __shfl_xor(*s1, off, 64);
+    *s2 += __shfl_xor(*s2, off, 64);
   }
-  if (lane == 0) {
-    red[0][wave] = a;
-    red[1][wave] = b;
+  if (lane < kFinCh) {
+    red[0][wave][ch] = *s1;
+    red[1][wave][ch] = *s2;
   }
   __syncthreads();
-  *s1 = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
-  *s2 = ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3];
-  return threadIdx.x == 0 && c < C;
-}
-static int finalize_wpc(int nrows) { return nrows >= 512 ? 4 : 1; }
-static int finalize_grid(int C, int nrows) { return static_cast<int>(ceil_div(C * finalize_wpc(nrows), 4)); }
-
-// Forward statistics: rows [shift, S1, S2] over `rpp` consecutive rows of x each (the last may cover
-// fewer), every row with a shift of its own: S1 = sum(x - shift), S2 = sum((x - shift)^2).  They are moved
-// to the first row's shift K0 exactly, in double,
-//   sum(x - K0) = S1 + n e,  sum((x - K0)^2) = S2 + 2 e S1 + n e^2,  e = shift - K0.
-__global__ __launch_bounds__(256) void bn_finalize_kernel(const float* __restrict__ partial, int nrows, int rpp,
-                                                          int64_t m, int C, int wpc, int row_major, float eps,
-                                                          float* __restrict__ mean_out,
-                                                          float* __restrict__ rstd_out,
-                                                          float* running_mean, float* running_var,
-                                                          float momentum) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int c = wpc == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
-  const int first = (wpc == 1 ? 0 : wave * 64) + lane, step = 64 * wpc;
-  double s1 = 0.0, s2 = 0.0, k0 = 0.0;
-  if (c < C && row_major) {
-    // the layout of layers with few tile rows, whose apply pass normally finalizes by itself: per tile row and
-    // channel the doubles (sum y, sum y^2); k0 stays 0
-    const double2* pd = reinterpret_cast<const double2*>(partial) + c;
-    for (int b = first; b < nrows; b += step) {
-      const double2 v = pd[static_cast<int64_t>(b) * C];
-      s1 += v.x;
-      s2 += v.y;
-    }
-  } else if (c < C) {
-    const int64_t rs = 1;
-    const float* pk = partial + static_cast<int64_t>(c) * nrows;
-    const float* p1 = pk + static_cast<int64_t>(C) * nrows;
-    const float* p2 = p1 + static_cast<int64_t>(C) * nrows;
-    k0 = static_cast<double>(pk[0]);
-    constexpr int U = 4;
-    int b = first;
-    for (; b + (U - 1) * step < nrows; b += U * step) {
-      float vk[U], v1[U], v2[U];
+  if (threadIdx.x < kFinCh) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        vk[u] = pk[(b + u * step) * rs];
-        v1[u] = p1[(b + u * step) * rs];
-        v2[u] = p2[(b + u * step) * rs];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t left = m - static_cast<int64_t>(b + u * step) * rpp;
-        const double n = static_cast<double>(left < rpp ? left : rpp);
-        const double e = static_cast<double>(vk[u]) - k0, a1 = static_cast<double>(v1[u]);
-        s1 += a1 + n * e;
-        s2 += static_cast<double>(v2[u]) + e * (2.0 * a1 + n * e);
-      }
-    }
-    for (; b < nrows; b += step) {
-      const int64_t left = m - static_cast<int64_t>(b) * rpp;
-      const double n = static_cast<double>(left < rpp ? left : rpp);
-      const double e = static_cast<double>(pk[b * rs]) - k0, a1 = static_cast<double>(p1[b * rs]);
-      s1 += a1 + n * e;
-      s2 += static_cast<double>(p2[b * rs]) + e * (2.0 * a1 + n * e);
+    for (int w = 1; w < kFinThreads / 64; ++w) {
+      *s1 += red[0][w][ch];
+      *s2 += red[1][w][ch];
     }
   }
-  if (!finalize_combine(&s1, &s2, wpc, c, C)) return;
-  const double d = s1 / static_cast<double>(m);
+}
+
+// Forward: adds row b's (mean, squared deviations) over n rows of x to the sums s1 = sum(x - k0), s2 = sum((x - k0)^2).
+__device__ __forceinline__ void add_moments(float2 v, double n, double k0, double* s1, double* s2) {
+  const double e = static_cast<double>(v.x) - k0;
+  *s1 += n * e;
+  *s2 += static_cast<double>(v.y) + n * (e * e);
+}
+__device__ __forceinline__ double rows_of(int b, int nrows, int rpp, int64_t m) {  // rows of x behind row b of the sums
+  return static_cast<double>(b == nrows - 1 ? m - static_cast<int64_t>(b) * rpp : rpp);
+}
+
+// Forward: rows of (mean, squared deviations) over rpp rows of x each (the last over what is left of m), or of sums (wide;
+// for a layer whose apply pass is left to its consumer).
+__global__ __launch_bounds__(kFinThreads) void bn_finalize_kernel(const float* __restrict__ partial, int nrows, int rpp,
+                                                           int wide, int64_t m, int C, float eps, float* __restrict__ mean_out,
+                                                           float* __restrict__ rstd_out, float* running_mean,
+                                                           float* running_var, float momentum) {
+  constexpr int G = kFinThreads / kFinCh;
+  const int c = blockIdx.x * kFinCh + threadIdx.x % kFinCh;
+  const float2* p = reinterpret_cast<const float2*>(partial) + bn_sums_at(0, c, nrows);  // (the last piece of C is padded)
+  const double k0 = wide ? 0.0 : static_cast<double>(p[0].x);
+  double s1 = 0.0, s2 = 0.0;
+  if (wide) {
+    const double2* pd = reinterpret_cast<const double2*>(partial) + bn_sums_at(0, c, nrows);
+    for (int b = threadIdx.x / kFinCh; b < nrows; b += G) {
+      s1 += pd[b * 8].x;
+      s2 += pd[b * 8].y;
+    }
+    nrows = 0;
+  }
+  for (int b = threadIdx.x / kFinCh; b < nrows; b += kFinRows * G) {
+    float2 v[kFinRows];
+#pragma unroll
+    for (int u = 0; u < kFinRows; ++u) v[u] = p[min(b + u * G, nrows - 1) * 8];
+#pragma unroll
+    for (int u = 0; u < kFinRows; ++u)
+      if (b + u * G < nrows) add_moments(v[u], rows_of(b + u * G, nrows, rpp, m), k0, &s1, &s2);
+  }
+  finalize_combine(&s1, &s2);
+  if (threadIdx.x >= kFinCh || c >= C) return;
+  const double d = s1 / static_cast<double>(m), mean = k0 + d;
   double var = s2 / static_cast<double>(m) - d * d;
   if (var < 0.0) var = 0.0;
-  const double mean = k0 + d;
   mean_out[c] = static_cast<float>(mean);
   rstd_out[c] = static_cast<float>(1.0 / sqrt(var + static_cast<double>(eps)));
   if (running_mean) running_mean[c] = momentum * running_mean[c] + (1.f - momentum) * static_cast<float>(mean);
@@ -308,17 +281,15 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(const float* __restric
 }
 
 // What a pass that finalizes its own statistics gets on top of the apply pass's arguments (FIN kernels below):
-// the per-tile sums in ROW-major order (forward: double2 per tile row and channel, sums at shift 0; backward: float
-// planes partial[plane][tile row][C]) and where the results go (backward: mean_out = dbeta, rstd_out = dgamma).
+// the rows of sums and where the results go (backward: mean_out = dbeta, rstd_out = dgamma).
 struct BnFinArgs {
   const float* partial;
-  int nrows, rpp;  // tile rows; (unused by the row-major layouts) pixel rows summed per tile row
+  int nrows;  // tile rows
   float eps, momentum;
   float *mean_out, *rstd_out, *running_mean, *running_var;
 };
-// Forward statistics of the CS channels from c0 on, by all 256 threads of a workgroup, into mean_s / rstd_s (LDS),
-// from row-major sums: per tile row and channel the doubles (sum y, sum y^2) that the convolution's output stage
-// made of its shifted float sums.  Thread (channel ch, part p) adds tile rows p, p + P, ... in order, the P parts
+// Forward statistics of the CS channels from c0 on, by all 256 threads of a workgroup, into mean_s / rstd_s (LDS).
+// Thread (channel ch, part p) adds tile rows p, p + P, ... in order, the P parts
 // are added in order: a fixed order, the same in every workgroup that computes these channels.  Ends with a barrier.
 template <int CS>
 __device__ __forceinline__ void finalize_slice_fwd(const BnFinArgs& f, int64_t m, int C, int c0, bool writer,
@@ -327,12 +298,12 @@ __device__ __forceinline__ void finalize_slice_fwd(const BnFinArgs& f, int64_t m
   __shared__ double red[2][256];
   const int ch = threadIdx.x % CS, part = threadIdx.x / CS;
   const int c = min(c0 + ch, C - 1);
-  const double2* pk = reinterpret_cast<const double2*>(f.partial) + c;
+  const double2* pk = reinterpret_cast<const double2*>(f.partial) + bn_sums_at(0, c, f.nrows);
   double s1 = 0.0, s2 = 0.0;
   for (int b = part; b < f.nrows; b += P * U) {
     double2 v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = pk[static_cast<int64_t>(min(b + u * P, f.nrows - 1)) * C];
+    for (int u = 0; u < U; ++u) v[u] = pk[min(b + u * P, f.nrows - 1) * 8];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (b + u * P < f.nrows) {
@@ -537,7 +508,7 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(
     const T* __restrict__ z, const uint8_t* __restrict__ zmask, const float* __restrict__ gamma,
     const float* __restrict__ beta,
     const float* __restrict__ mean, const float* __restrict__ rstd, int64_t m, int C, int tx_log2,
-    int rpb, int mode, int row_major, float* __restrict__ partial) {
+    int rpb, int mode, float* __restrict__ partial) {
   constexpr int V = Elem<T>::VEC;
   __shared__ float lds[4 * 2 * V * 32];
   const int TX = 1 << tx_log2, TY = 256 >> tx_log2;
@@ -586,51 +557,34 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(
   float t1, t2;
   const int c = blockIdx.y * TX * V + threadIdx.x;
   if (!combine_sums<V>(acc, lds, tx_log2, &t1, &t2) || c >= C) return;
-  // planes (sum g, sum g * xhat): [plane][row block][C] for a self-finalizing apply pass, else [plane][C][row block]
-  const int64_t nrows = gridDim.x;
-  float* o = partial + (row_major ? static_cast<int64_t>(blockIdx.x) * C + c : static_cast<int64_t>(c) * nrows + blockIdx.x);
-  o[0] = t1;
-  o[C * nrows] = t2;
+  reinterpret_cast<float2*>(partial)[bn_sums_at(blockIdx.x, c, gridDim.x)] = make_float2(t1, t2);
 }
 
-__global__ __launch_bounds__(256) void bn_bwd_finalize_kernel(const float* __restrict__ partial,
-                                                              int nrows, int C, int wpc,
-                                                              float* __restrict__ dgamma,
-                                                              float* __restrict__ dbeta) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int c = wpc == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
-  const int first = (wpc == 1 ? 0 : wave * 64) + lane, step = 64 * wpc;
+__global__ __launch_bounds__(kFinThreads) void bn_bwd_finalize_kernel(const float* __restrict__ partial, int nrows, int C,
+                                                               float* __restrict__ dgamma, float* __restrict__ dbeta) {
+  constexpr int G = kFinThreads / kFinCh;
+  const int c = blockIdx.x * kFinCh + threadIdx.x % kFinCh;
+  const float2* p = reinterpret_cast<const float2*>(partial) + bn_sums_at(0, c, nrows);
   double s1 = 0.0, s2 = 0.0;
-  if (c < C) {
-    const float* p1 = partial + static_cast<int64_t>(c) * nrows;
-    const float* p2 = p1 + static_cast<int64_t>(C) * nrows;
-    constexpr int U = 4;
-    int b = first;
-    for (; b + (U - 1) * step < nrows; b += U * step) {
-      float v1[U], v2[U];
+  for (int b = threadIdx.x / kFinCh; b < nrows; b += kFinRows * G) {
+    float2 v[kFinRows];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        v1[u] = p1[b + u * step];
-        v2[u] = p2[b + u * step];
-      }
+    for (int u = 0; u < kFinRows; ++u) v[u] = p[min(b + u * G, nrows - 1) * 8];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        s1 += static_cast<double>(v1[u]);
-        s2 += static_cast<double>(v2[u]);
+    for (int u = 0; u < kFinRows; ++u) {
+      if (b + u * G < nrows) {
+        s1 += static_cast<double>(v[u].x);
+        s2 += static_cast<double>(v[u].y);
       }
-    }
-    for (; b < nrows; b += step) {
-      s1 += static_cast<double>(p1[b]);
-      s2 += static_cast<double>(p2[b]);
     }
   }
-  if (!finalize_combine(&s1, &s2, wpc, c, C)) return;
+  finalize_combine(&s1, &s2);
+  if (threadIdx.x >= kFinCh || c >= C) return;
   dbeta[c] = static_cast<float>(s1);
   dgamma[c] = static_cast<float>(s2);
 }
 
-// Backward sums of the CS channels from c0 on, from row-major float planes partial[plane][tile row][C]
-// (plane 0: sum g, plane 1: sum g * xhat), by all 256 threads, in double and in the fixed order of
+// Backward sums (sum g, sum g * xhat) of the CS channels from c0 on, by all 256 threads, in double and in the fixed order of
 // finalize_slice_fwd; dbeta / dgamma land in db_s / dg_s (LDS).  Ends with a barrier.
 template <int CS>
 __device__ __forceinline__ void finalize_slice_bwd(const BnFinArgs& f, int C, int c0, bool writer, float* db_s,
@@ -639,22 +593,17 @@ __device__ __forceinline__ void finalize_slice_bwd(const BnFinArgs& f, int C, in
   __shared__ double red[2][256];
   const int ch = threadIdx.x % CS, part = threadIdx.x / CS;
   const int c = min(c0 + ch, C - 1);
-  const int64_t plane = static_cast<int64_t>(f.nrows) * C;
-  const float* p1 = f.partial + c;
+  const float2* pk = reinterpret_cast<const float2*>(f.partial) + bn_sums_at(0, c, f.nrows);
   double s1 = 0.0, s2 = 0.0;
   for (int b = part; b < f.nrows; b += P * U) {
-    float v1[U], v2[U];
+    float2 v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t at = static_cast<int64_t>(min(b + u * P, f.nrows - 1)) * C;
-      v1[u] = p1[at];
-      v2[u] = p1[plane + at];
-    }
+    for (int u = 0; u < U; ++u) v[u] = pk[min(b + u * P, f.nrows - 1) * 8];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (b + u * P < f.nrows) {
-        s1 += static_cast<double>(v1[u]);
-        s2 += static_cast<double>(v2[u]);
+        s1 += static_cast<double>(v[u].x);
+        s2 += static_cast<double>(v[u].y);
       }
     }
   }
@@ -775,7 +724,7 @@ int bn_desc_check(const rn50_bn_desc* d, const char* who) { return check_desc(d,
 static size_t bn_ws_bytes(const rn50_bn_desc* d) {
   const int64_t m = static_cast<int64_t>(d->N) * d->H * d->W;
   const BnGeom g = bn_sums_geom(m, d->C, d->dtype);
-  return align_up(static_cast<size_t>(g.nblk) * 4 * d->C * sizeof(float), 256);
+  return align_up(bn_sums_bytes(g.nblk, d->C, bn_self_sums(m, d->C)), 256);
 }
 
 // finalize + apply from partial statistics rows (see bn_finalize_kernel)
@@ -783,12 +732,12 @@ template <typename T>
 static void launch_fwd_tail(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const void* x,
                             const float* gamma, const float* beta, const void* residual, void* y,
                             uint8_t* relu_mask, float* save_mean, float* save_rstd, float* rm, float* rv,
-                            float momentum, const float* partial, int nrows, int rpp, bool row_major, hipStream_t s) {
-  if (row_major && y) {
+                            float momentum, const float* partial, int nrows, int rpp, bool self, hipStream_t s) {
+  if (self && y) {
     // few tile rows: the apply pass finalizes for itself
     int gy, rpb;
     bn_self_finalize_geom(m, d->C, d->dtype == RN50_BF16 ? 8 : 4, &gy, &rpb);
-    const BnFinArgs fin{partial, nrows, rpp, d->eps, momentum, save_mean, save_rstd, rm, rv};
+    const BnFinArgs fin{partial, nrows, d->eps, momentum, save_mean, save_rstd, rm, rv};
     RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, true>), dim3(static_cast<unsigned>(ceil_div(m, rpb)), gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, nullptr, nullptr, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, 3, rpb, d->mode, fin);
     return;
   }
@@ -797,7 +746,7 @@ static void launch_fwd_tail(const rn50_bn_desc* d, const BnGeom& g, int64_t m, c
   static const int skip_below = getenv("RN50_SKIP_BN_FINALIZE_ROWS") ? atoi(getenv("RN50_SKIP_BN_FINALIZE_ROWS")) : 1 << 30;
   if (!skip_fin || nrows > skip_below)
 #endif
-  RN50_LAUNCH("bn_finalize", bn_finalize_kernel, dim3(finalize_grid(d->C, nrows)), dim3(256), 0, s, partial, nrows, rpp, m, d->C, finalize_wpc(nrows), row_major ? 1 : 0, d->eps, save_mean, save_rstd, rm, rv, momentum);
+  RN50_LAUNCH("bn_finalize", bn_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, partial, nrows, rpp, self ? 1 : 0, m, d->C, d->eps, save_mean, save_rstd, rm, rv, momentum);
   if (!y) return;  // statistics only: the consumer applies the layer while it loads its operand
   const BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnApplyGroups);
   RN50_LAUNCH("bn_apply", bn_apply_kernel<T>, dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, save_mean, save_rstd, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, ga.tx_log2, ga.rpb, d->mode, BnFinArgs{});
@@ -808,7 +757,7 @@ static void launch_fwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const 
                        const float* gamma, const float* beta, const void* residual, void* y,
                        uint8_t* relu_mask, float* save_mean, float* save_rstd, float* rm, float* rv,
                        float momentum, float* partial, hipStream_t s) {
-  const bool self = bn_self_sums(m);
+  const bool self = bn_self_sums(m, d->C);
   RN50_LAUNCH("bn_stats", bn_stats_kernel<T>, dim3(g.nblk, g.gy), dim3(256), 0, s, static_cast<const T*>(x), m, d->C, g.tx_log2, g.rpb, self ? 1 : 0, partial);
   launch_fwd_tail<T>(d, g, m, x, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv, momentum,
                      partial, g.nblk, g.rpb, self, s);
@@ -820,22 +769,22 @@ static void launch_bwd_tail(const rn50_bn_desc* d, const BnGeom& g, int64_t m, c
                             const void* dz2, const void* x, const void* z, const uint8_t* zmask,
                             const float* gamma, const float* beta, const float* mean, const float* rstd,
                             void* dx, void* dres, float* dgamma, float* dbeta, const float* partial,
-                            int nrows, bool row_major, hipStream_t s) {
+                            int nrows, bool self, hipStream_t s) {
   BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnBwdApplyGroups);
   BnFinArgs fin{};
-  if (row_major) {
+  if (self) {
     // few tile rows: the apply pass adds them up itself
     ga.tx_log2 = 3;
     bn_self_finalize_geom(m, d->C, ga.V, &ga.gy, &ga.rpb);
     ga.nblk = static_cast<int>(ceil_div(m, ga.rpb));
-    fin = BnFinArgs{partial, nrows, 0, 0.f, 0.f, dbeta, dgamma, nullptr, nullptr};
+    fin = BnFinArgs{partial, nrows, 0.f, 0.f, dbeta, dgamma, nullptr, nullptr};
   } else {
 #ifdef RN50_TUNING
     static const bool skip_fin = getenv("RN50_SKIP_BN_FINALIZE") != nullptr;
     static const int skip_below = getenv("RN50_SKIP_BN_FINALIZE_ROWS") ? atoi(getenv("RN50_SKIP_BN_FINALIZE_ROWS")) : 1 << 30;
     if (!skip_fin || nrows > skip_below)
 #endif
-    RN50_LAUNCH("bn_bwd_finalize", bn_bwd_finalize_kernel, dim3(finalize_grid(d->C, nrows)), dim3(256), 0, s, partial, nrows, d->C, finalize_wpc(nrows), dgamma, dbeta);
+    RN50_LAUNCH("bn_bwd_finalize", bn_bwd_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, partial, nrows, d->C, dgamma, dbeta);
   }
 #define RN50_BWD_APPLY_K(DZ2, ZK, FIN)                                                                             \
   RN50_LAUNCH("bn_bwd_apply", (bn_bwd_apply_kernel<T, DZ2, ZK, FIN>), dim3(ga.nblk, ga.gy), dim3(256), 0, s,       \
@@ -844,7 +793,7 @@ static void launch_bwd_tail(const rn50_bn_desc* d, const BnGeom& g, int64_t m, c
               static_cast<T*>(dres), m, d->C, ga.tx_log2, ga.rpb, d->mode, fin)
 #define RN50_BWD_APPLY(DZ2, ZK)                                                  \
   do {                                                                           \
-    if (row_major) RN50_BWD_APPLY_K(DZ2, ZK, true); else RN50_BWD_APPLY_K(DZ2, ZK, false); \
+    if (self) RN50_BWD_APPLY_K(DZ2, ZK, true); else RN50_BWD_APPLY_K(DZ2, ZK, false); \
   } while (0)
   const int zk = d->mode == 0 ? 0 : (zmask ? 2 : (z ? 1 : 0));
   if (dz2) {
@@ -861,11 +810,11 @@ static void launch_bwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const 
                        const void* dz2, const void* x, const void* z, const uint8_t* zmask,
                        const float* gamma, const float* beta, const float* mean, const float* rstd, void* dx,
                        void* dres, float* dgamma, float* dbeta, float* partial, hipStream_t s) {
-  const bool self = bn_self_sums(m);
+  const bool self = bn_self_sums(m, d->C);
 #define RN50_BWD_REDUCE(DZ2, ZK)                                                                                 \
   RN50_LAUNCH("bn_bwd_reduce", (bn_bwd_reduce_kernel<T, DZ2, ZK>), dim3(g.nblk, g.gy), dim3(256), 0, s,            \
               static_cast<const T*>(dz), static_cast<const T*>(dz2), static_cast<const T*>(x),                     \
-              static_cast<const T*>(z), zmask, gamma, beta, mean, rstd, m, d->C, g.tx_log2, g.rpb, d->mode, self ? 1 : 0, partial)
+              static_cast<const T*>(z), zmask, gamma, beta, mean, rstd, m, d->C, g.tx_log2, g.rpb, d->mode, partial)
   const int zk = d->mode == 0 ? 0 : (zmask ? 2 : (z ? 1 : 0));
   if (dz2) {
     if (zk == 2) RN50_BWD_REDUCE(true, 2); else if (zk == 1) RN50_BWD_REDUCE(true, 1); else RN50_BWD_REDUCE(true, 0);
@@ -887,10 +836,10 @@ void bn_fwd_from_partials(const rn50_bn_desc* d, const void* x, const float* par
   const BnGeom g = bn_geom(m, d->C, d->dtype);
   if (d->dtype == RN50_BF16)
     launch_fwd_tail<uint16_t>(d, g, m, x, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv,
-                              momentum, partial, nrows, rpp, bn_partials_row_major(nrows, false), s);
+                              momentum, partial, nrows, rpp, bn_self_finalizes(nrows, false), s);
   else
     launch_fwd_tail<float>(d, g, m, x, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv, momentum,
-                           partial, nrows, rpp, bn_partials_row_major(nrows, false), s);
+                           partial, nrows, rpp, bn_self_finalizes(nrows, false), s);
 }
 // Evaluation mode: 1/sqrt(running_var + eps) per channel, then the training pass's apply kernel with the
 // moving averages in place of the batch statistics.
@@ -920,10 +869,10 @@ void bn_bwd_from_partials(const rn50_bn_desc* d, const void* dz, const void* x, 
   const BnGeom g = bn_geom(m, d->C, d->dtype);
   if (d->dtype == RN50_BF16)
     launch_bwd_tail<uint16_t>(d, g, m, dz, nullptr, x, nullptr, relu_mask, gamma, beta, mean, rstd, dx, dres, dgamma,
-                              dbeta, partial, nrows, bn_partials_row_major(nrows, true), s);
+                              dbeta, partial, nrows, bn_self_finalizes(nrows, true), s);
   else
     launch_bwd_tail<float>(d, g, m, dz, nullptr, x, nullptr, relu_mask, gamma, beta, mean, rstd, dx, dres, dgamma,
-                           dbeta, partial, nrows, bn_partials_row_major(nrows, true), s);
+                           dbeta, partial, nrows, bn_self_finalizes(nrows, true), s);
 }
 
 }  // namespace rn50

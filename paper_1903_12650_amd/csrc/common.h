@@ -159,6 +159,17 @@ __device__ __forceinline__ void bn_coeffs(float gamma, float beta, float mean, f
   *bias = fmaf(-mean, *scale, beta);
 }
 
+// Sums (v, v^2) about zero of n values whose sums about the shift k are s1 = sum(v - k), s2 = sum((v - k)^2).
+__device__ __forceinline__ double2 bn_tile_sums(float k, float s1, float s2, int n) {
+  const double kd = static_cast<double>(k), nd = static_cast<double>(n), d1 = static_cast<double>(s1);
+  return make_double2(d1 + nd * kd, static_cast<double>(s2) + kd * (2.0 * d1 + nd * kd));
+}
+// Mean and squared deviations from it of n values whose sums about the shift k are s1 = sum(v - k), s2 = sum((v - k)^2).
+__device__ __forceinline__ float2 bn_tile_moments(float k, float s1, float s2, int n) {
+  const double d1 = static_cast<double>(s1), d = d1 / static_cast<double>(n);
+  return make_float2(static_cast<float>(static_cast<double>(k) + d), fmaxf(static_cast<float>(static_cast<double>(s2) - d1 * d), 0.f));
+}
+
 // V (4 or 8) consecutive floats from a 16-byte aligned address, as 16-byte loads.
 template <int V>
 __device__ __forceinline__ void load_floats(const float* __restrict__ p, float* out) {

@@ -79,11 +79,12 @@ struct IgemmArgs {
   FastDiv div_ntn, div_w[2], div_h[2];
   int mode;         // host side only: selects the MODE template argument
   // Optional batch-norm sums over the rows of each output tile, taken from the rounded values that are
-  // stored (null: none).  Forward: partial[3][Ncols][tiles] = shift (the tile's first row), sum(y - shift),
-  // sum((y - shift)^2).  Data gradient: partial[2][Ncols][tiles] = sum(g), sum(g * xhat) with g the output
+  // stored (null: none), one row per tile row (bn_sums_at).  Forward: mean and squared deviations, from float sums about
+  // the tile's first row.  Data gradient: sum(g), sum(g * xhat) with g the output
   // gradient masked by the ReLU of the BN layer whose conv output is bn_x [M][Ncols], xhat its
   // normalized input.
   float* partial;
+  int partial_wide;  // forward: as doubles (bn_self_finalizes)
   const void* bn_x;
   const float *bn_gamma, *bn_beta, *bn_mean, *bn_rstd;
   // Data gradient with sums only.  addend [M][Ncols] (or null): a second gradient branch, added to the
@@ -100,10 +101,6 @@ struct IgemmArgs {
   // in_lds: byte offset of the per-channel coefficient table behind the ring (host side: lds bytes without it).
   const float *in_gamma, *in_beta, *in_mean, *in_rstd;
   int in_lds;
-  // Sums stored row-major for a BN pass that finalizes by itself (bn_partials_row_major).  Forward: per tile row and
-  // channel the two doubles (sum y, sum y^2), the tile's shifted float sums moved to shift 0 here; data gradient:
-  // partial[plane][tile row][Ncols] in float.
-  int partial_rm;
   // Forward with an inference-mode batch norm in the output stage (MODE 2): the output is
   // [relu](product * scale + bias [+ addend]), scale = bn_gamma / sqrt(aff_var + aff_eps), bias = bn_beta - bn_mean * scale,
   // from the float accumulators and rounded once; addend [M][Ncols] (or null) is the residual.
@@ -810,11 +807,9 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     *reinterpret_cast<float4*>(cs + (orow * 2 + 1) * BN + op * V + j) = make_float4(s2[j], s2[j + 1], s2[j + 2], s2[j + 3]);
   }
   __syncthreads();
-  // partial[plane][channel][tile row]: the rows of one channel are contiguous for the finalize pass
-  const int64_t nrows = a.mtiles, plane = static_cast<int64_t>(a.Ncols) * nrows;
-  if (MODE == 0 && a.partial_rm) {
-    // row-major, for an apply pass that finalizes by itself: one thread per column moves the tile's sums from the
-    // tile's shift k to shift 0, exactly enough in double (S1 + n k, S2 + 2 k S1 + n k^2), so that the readers only add
+  float2* const out2 = reinterpret_cast<float2*>(a.partial);
+  if (MODE == 0) {
+    // one thread per column, from the tile's sums about the shift, in double
     if (tid < BN && n0 + tid < a.Ncols) {
       float t1 = 0.f, t2 = 0.f;
 #pragma unroll 8
@@ -822,23 +817,19 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         t1 += cs[(r * 2 + 0) * BN + tid];
         t2 += cs[(r * 2 + 1) * BN + tid];
       }
-      const double k = static_cast<double>(kshift), n = static_cast<double>(min(BM, Mc - m0));
-      const double d1 = static_cast<double>(t1), d2 = static_cast<double>(t2);
-      double2* out2 = reinterpret_cast<double2*>(a.partial);
-      out2[static_cast<int64_t>(mt) * a.Ncols + n0 + tid] = make_double2(d1 + n * k, d2 + k * (2.0 * d1 + n * k));
+      const int64_t at = bn_sums_at(mt, n0 + tid, a.mtiles);
+      if (a.partial_wide) reinterpret_cast<double2*>(a.partial)[at] = bn_tile_sums(kshift, t1, t2, min(BM, Mc - m0));
+      else out2[at] = bn_tile_moments(kshift, t1, t2, min(BM, Mc - m0));
     }
     return;
   }
   if (tid < 2 * BN) {
-    const int pl = tid / BN, ch = tid % BN;
+    const int pl = tid & 1, ch = tid >> 1;
     float t = 0.f;
 #pragma unroll 8
     for (int r = 0; r < RPP; ++r) t += cs[(r * 2 + pl) * BN + ch];
-    if (n0 + ch < a.Ncols)
-      a.partial[(MODE == 0 ? pl + 1 : pl) * plane +
-                (a.partial_rm ? static_cast<int64_t>(mt) * a.Ncols + n0 + ch : static_cast<int64_t>(n0 + ch) * nrows + mt)] = t;
+    if (n0 + ch < a.Ncols) a.partial[2 * bn_sums_at(mt, n0 + ch, a.mtiles) + pl] = t;
   }
-  if (MODE == 0 && tid < BN && n0 + tid < a.Ncols) a.partial[static_cast<int64_t>(n0 + tid) * nrows + mt] = kshift;
 }
 
 // ------------------------------------------------------- layout helper kernels
@@ -934,7 +925,7 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
   const bool classes = a.mode == 1 && a.stride == 2;
   a.mtiles = static_cast<int>(classes ? 4 * tiles_per_class : ceil_div(a.M, BM));
   const int64_t grid = static_cast<int64_t>(a.mtiles) * a.ntn;
-  a.partial_rm = a.partial != nullptr && bn_partials_row_major(a.mtiles, a.mode == 1);
+  a.partial_wide = bn_self_finalizes(a.mtiles, false);
   a.div_ntn = make_fastdiv(a.ntn);
   a.linear = a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0 && !a.pair && a.H == a.P && a.W == a.Q;
   for (int c = 0; c < 2; ++c) {
@@ -1291,12 +1282,11 @@ extern "C" int conv_wgrad(const rn50_conv_desc* d, const void* x, const void* dy
 // ---- fused batch-norm sums (the BN side is in bn.hip)
 extern "C" size_t conv_bn_sums_bytes(const rn50_conv_desc* d) {
   if (!d || check_conv(d, "conv_bn_sums_bytes")) return 0;
-  // one row per output tile of at least 32 pixels; forward three float planes or, row-major, two doubles per
-  // channel and row; two planes backward
+  // one row per output tile of at least 32 pixels
   const int P = out_dim(d->H, d->pad, d->R, d->stride), Q = out_dim(d->W, d->pad, d->S, d->stride);
-  const size_t fwd = static_cast<size_t>(ceil_div(static_cast<int64_t>(d->N) * P * Q, 32)) * 4 * d->Cout;
-  const size_t bwd = static_cast<size_t>(dgrad_partial_rows_bound(d)) * 2 * d->Cin;
-  return align_up((fwd > bwd ? fwd : bwd) * sizeof(float), 256);
+  const size_t fwd = bn_sums_bytes(ceil_div(static_cast<int64_t>(d->N) * P * Q, 32), d->Cout, true);
+  const size_t bwd = bn_sums_bytes(dgrad_partial_rows_bound(d), d->Cin, false);
+  return align_up(fwd > bwd ? fwd : bwd, 256);
 }
 
 extern "C" int conv_fwd_bn_sums(const rn50_conv_desc* d, const void* x, const void* w, void* y, float* sums,

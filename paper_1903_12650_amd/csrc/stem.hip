@@ -34,7 +34,7 @@ struct StemArgs {
   int M;
   FastDiv div_tpi;     // by the tiles of an image
   float* partial;      // batch-norm sums, one row per workgroup (as IgemmArgs::partial), or null
-  int nrows, partial_rm;
+  int partial_wide;    // as doubles (bn_self_finalizes)
   // inference-mode batch norm in the output stage (AFF)
   const float *gamma, *beta, *mean, *var;
   float eps;
@@ -198,15 +198,9 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const StemArgs a) {
       t2s += static_cast<double>(sums[w][2][tid]) + e * (2.0 * d1 + cn * e);
       n += cn;
     }
-    if (a.partial_rm) {
-      reinterpret_cast<double2*>(a.partial)[static_cast<int64_t>(blockIdx.x) * a.Cout + tid] = make_double2(t1s + n * k0, t2s + k0 * (2.0 * t1s + n * k0));
-    } else {
-      const int64_t plane = static_cast<int64_t>(a.Cout) * a.nrows;
-      float* o = a.partial + static_cast<int64_t>(tid) * a.nrows + blockIdx.x;
-      o[0] = static_cast<float>(k0);
-      o[plane] = static_cast<float>(t1s);
-      o[2 * plane] = static_cast<float>(t2s);
-    }
+    const int64_t at = bn_sums_at(blockIdx.x, tid, gridDim.x);
+    if (a.partial_wide) reinterpret_cast<double2*>(a.partial)[at] = make_double2(t1s + n * k0, t2s + k0 * (2.0 * t1s + n * k0));
+    else reinterpret_cast<float2*>(a.partial)[at] = make_float2(static_cast<float>(k0 + t1s / n), static_cast<float>(fmax(t2s - t1s * t1s / n, 0.0)));
   }
 }
 
@@ -247,7 +241,7 @@ bool stem_fwd_run(const rn50_conv_desc* d, const void* xp, const void* w, void* 
   a.xp_bytes = static_cast<uint32_t>(static_cast<size_t>(d->N) * g.Hp * a.pitch);
   a.rows = p.rows; a.patch = p.patch; a.patch_lds = p.patch_lds; a.tiles = p.tiles; a.per_wg = p.per_wg;
   a.div_tpi = make_fastdiv(a.P / a.rows);
-  a.partial = bn_partial; a.nrows = p.grid; a.partial_rm = bn_partials_row_major(p.grid, false) ? 1 : 0;
+  a.partial = bn_partial; a.partial_wide = bn_self_finalizes(p.grid, false);
   const int lds = std::max(2 * p.patch_lds + 4 * kStemStage, 64 * 448);
   static std::once_flag once;
   std::call_once(once, [] {

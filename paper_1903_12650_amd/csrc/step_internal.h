@@ -26,7 +26,7 @@ struct PartialRows {
 PartialRows fwd_partial_rows(const rn50_conv_desc* d);    // tiles of the forward convolution's output
 PartialRows dgrad_partial_rows(const rn50_conv_desc* d);  // tiles of the data gradient
 int64_t dgrad_partial_rows_bound(const rn50_conv_desc* d);  // most rows any tile choice gives (tiles of >= 32 pixels)
-// bn_partial (null: none): float[3][Cout][num] = shift, sum(y - shift), sum((y - shift)^2) per tile.
+// bn_partial (null: none): (mean, sum of squared deviations from it) per tile row and channel, see bn_sums_at.
 // An inference-mode BN layer applied in a convolution's output stage: [relu](gamma*(product - mean)/sqrt(var + eps) +
 // beta [+ residual]); residual: [M][Cout] or null.
 struct BnAffine {
@@ -39,18 +39,27 @@ void stem_fwd_padded(const rn50_conv_desc* d, const void* xp, const void* w, voi
                      hipStream_t s, const BnAffine* affine = nullptr);
 // A BN+ReLU layer applied to a convolution's input on the fly (1x1, stride 1 convolutions only): its parameters
 // and saved statistics, float[Cin] each.
-// The BN sums that a convolution's output stage leaves (one row per row tile) are stored ROW-major when there are
-// few tile rows: the BN apply pass (forward or backward) then adds them up itself, in every workgroup, for the
-// channels it applies, and the finalize launch in front of it -- about 4 us on the step's dependency chain whatever
-// it computes -- is gone.  Forward: per tile row and channel the doubles (sum y, sum y^2), moved from the tile's
-// shift to shift 0 by the writer so that the readers only add; backward: float planes [plane][tile row][C].
-// Otherwise channel-major float planes, partial[plane][C][tile row], for the finalize kernels.  The writer and the
-// reader both decide by this function.  Threshold from whole-step measurements at batch 40 (40 / 128 / 256 rows
+// The BN sums that a convolution's output stage (or a stand-alone sums pass) leaves: one row per row tile, a pair per row
+// and channel.  Backward: the floats (sum g, sum g * xhat).  Forward, two forms: for a reader that adds rows up in every
+// workgroup (bn_self_finalizes), the doubles (sum y, sum y^2), moved from the tile's shift to shift 0 by the writer so that
+// the readers only add; else, for the finalize launch, the floats (mean of the tile's rows, sum of their squared deviations
+// from it), which are combined in double about the first tile's mean: half the bytes, which at 12544 rows count.
+// Eight channels by all rows are contiguous: the writer stores whole 64-byte pieces (with the rows of a single channel
+// contiguous its 2 to 3 * 64 sums were a partial cache line each), and a finalize workgroup reads one run of memory
+// (row-major, it picked 64 bytes out of every row: 12544 rows, batch 256, 45 us).
+__host__ __device__ inline int64_t bn_sums_at(int row, int c, int nrows) {
+  return (static_cast<int64_t>(c >> 3) * nrows + row) * 8 + (c & 7);
+}
+inline size_t bn_sums_bytes(int64_t nrows, int C, bool wide) { return static_cast<size_t>(nrows) * ((C + 7) / 8 * 8) * (wide ? 16 : 8); }
+// They are added up by a finalize launch, or, when there are few tile rows, by the BN apply pass (forward or backward)
+// itself, in every workgroup, for the channels it applies: the launch in front of it -- about 4 us on the step's
+// dependency chain whatever it computes -- is gone.
+// Threshold from whole-step measurements at batch 40 (40 / 128 / 256 rows
 // against none: 4.613 / 4.577 / 4.666 against 4.649 ms): up to 123 tile rows (the 14x14 and 7x7 layers) the
 // redundant sums cost less than the launch; at 245 (28x28) every workgroup would read more sums than data (raising
 // the backward threshold alone to 256 / 512 rows: 4.78 -> 4.83 / 4.84 ms).
 constexpr int kBnSelfFinalizeRows = 128, kBnSelfFinalizeRowsBwd = 128;
-inline bool bn_partials_row_major(int nrows, bool backward) {
+inline bool bn_self_finalizes(int nrows, bool backward) {
   return nrows <= (backward ? kBnSelfFinalizeRowsBwd : kBnSelfFinalizeRows);
 }
 
