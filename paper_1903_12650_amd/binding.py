@@ -429,13 +429,40 @@ class LarsTable:
             _LARS_ENTRY.pack_into(self.host, t * _LARS_ENTRY.size, w.data_ptr(), g.data_ptr(), v.data_ptr(),
                                   lp.data_ptr() if lp is not None else 0, n, weight_decays[t],
                                   1 if apply_trust is None else int(apply_trust[t]))
-        # from pinned memory the copy is queued like a kernel: nothing waits for the work in front of it
-        self.device = ws[0].device
         table = torch.frombuffer(self.host, dtype=torch.uint8)
-        self.dev = table.pin_memory().to(self.device, non_blocking=True) if ws[0].is_cuda else table.to(self.device)
+        self.device = ws[0].device
+        if not ws[0].is_cuda:
+            self.dev, self._ready = table.to(self.device), None
+            return
+        # From pinned memory the copy is queued like a kernel: nothing waits for the work in front of it.  It is complete for
+        # what follows on this stream; lars_update orders every other use behind it (_order).
+        self._pinned = table.pin_memory()
+        self.dev = self._pinned.to(self.device, non_blocking=True)
+        self._stream = _raw_stream()
+        self._ready = torch.cuda.Event()
+        self._ready.record()
+        self._arrived = False
+
+    def _order(self):
+        """The current stream's next kernels read the device table: behind its copy, whichever stream that was queued on."""
+        if self._ready is None:
+            return
+        capturing = torch.cuda.is_current_stream_capturing()
+        if not self._arrived:
+            if capturing:
+                # A capture cannot wait for an event from outside it, and the graph may replay on any stream: it brings the
+                # table along (the same bytes).
+                self.dev.copy_(self._pinned, non_blocking=True)
+            elif self._ready.query():
+                self._arrived = True
+            elif _raw_stream() != self._stream:
+                torch.cuda.current_stream().wait_event(self._ready)
+        if not capturing and _raw_stream() != self._stream:
+            self.dev.record_stream(torch.cuda.current_stream())  # (its memory belongs to the construction's stream)
 
 
 def lars_update(table, eta, momentum, lr, eps=0.0, norms_out=None, workspace=None):
+    table._order()
     d = LarsDesc(table.T, eta, momentum, lr, eps, table.grad_dtype)
     if workspace is None:
         workspace = _ws(raw.lars_update_workspace_bytes(ctypes.byref(d), table.host), table.device)
@@ -446,6 +473,7 @@ def lars_update(table, eta, momentum, lr, eps=0.0, norms_out=None, workspace=Non
 
 def lars_update_noalloc(table, eta, momentum, lr, eps=0.0, norms_out=None):
     """lars_update without a workspace: the library's built-in scratch array holds the partial norms."""
+    table._order()
     d = LarsDesc(table.T, eta, momentum, lr, eps, table.grad_dtype)
     _check(raw.lars_update_noalloc(ctypes.byref(d), table.host, _ptr(table.dev), _ptr(norms_out), _stream()))
     return norms_out

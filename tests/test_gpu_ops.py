@@ -274,6 +274,64 @@ def test_lars_variants(rn):
     _lars_case(rn, table, with_lowp=False, apply_trust=[1, 0, 0, 1, 1, 0, 1], eps=1e-3)
 
 
+def _small_lars(rn):
+    """Weights, gradients, velocities of three tensors (in one arena each) and their update by the oracle."""
+    table = [("a.w", (5, 3, 3, 7), "conv"), ("a.gamma", (5,), "gamma"), ("c.w", (17, 8193), "fcw")]
+    host_p, host_g = synth.params_from_table(SEED, table), synth.grads_from_table(SEED, table, 1e-3)
+    wds = net.lars_hyper(table, 5e-5)
+    w_o, _, _ = orc.lars_update(host_p, host_g, [np.zeros_like(p) for p in host_p], 0.001, 0.9, 1.0, wds)
+    return [dev(p) for p in host_p], [dev(g) for g in host_g], [dev(np.zeros_like(p)) for p in host_p], wds, w_o
+
+
+def test_lars_table_is_ordered_behind_its_copy_on_any_stream(rn):
+    """A table built on one stream and used on another: the other stream waits for the table's copy, which is queued behind
+    whatever the construction's stream is doing."""
+    W, G, V, wds, w_o = _small_lars(rn)
+    rn.LarsTable(W, G, V, wds)                                # (the first one also sets up the pinned allocator)
+    build, use = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(build):
+        torch.cuda._sleep(500_000_000)                        # (a bounded spin: about 0.2 s)
+        tab = rn.LarsTable(W, G, V, wds)
+    reached = torch.cuda.Event()
+    with torch.cuda.stream(use):
+        tab._order()                                          # what lars_update does first, without its kernels
+        reached.record()
+    assert not tab._ready.query(), "the copy has to be outstanding for this test to mean anything"
+    assert not reached.query(), "the other stream ran past the table's copy"
+    reached.synchronize()
+    assert tab._ready.query()
+    with torch.cuda.stream(use):
+        rn.lars_update(tab, 0.001, 0.9, 1.0)
+    use.synchronize()
+    for w, wo in zip(W, w_o):
+        assert_close(w, wo, TOL["lars"], "w")
+
+
+@pytest.mark.parametrize("arrived", [False, True])
+def test_lars_update_captured_with_a_table_from_outside(rn, arrived):
+    """Every replay of a captured update equals an eager one, whether or not the table's copy was known to be complete when
+    the capture began."""
+    W, G, V, wds, _ = _small_lars(rn)
+    W2, V2 = [w.clone() for w in W], [v.clone() for v in V]
+    ws = torch.empty(1 << 16, dtype=torch.uint8, device="cuda")
+    tab, tab2 = rn.LarsTable(W, G, V, wds), rn.LarsTable(W2, G, V2, wds)
+    if arrived:
+        torch.cuda.synchronize()
+        tab._order()
+        assert tab._arrived
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rn.lars_update(tab, 0.001, 0.9, 1.0, workspace=ws)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        rn.lars_update(tab2, 0.001, 0.9, 1.0)
+        torch.cuda.synchronize()
+        for a, b in zip(W + V, W2 + V2):
+            assert torch.equal(a, b)
+
+
 def test_lars_many_tensors_needs_two_launches(rn):
     table = [(f"t{i}.w", (3 + i % 5, 1, 1, 4), "conv") for i in range(700)]
     _lars_case(rn, table, v_zero=False)
