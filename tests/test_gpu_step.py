@@ -90,6 +90,58 @@ def test_config1_bottleneck_block_f32(rn):
         assert_close(v, vo, TOL["lars"], name + " v_new")
 
 
+@pytest.mark.parametrize("N,H", [(2, 56), (4, 41), (8, 56)])
+def test_bottleneck_block_f32_against_the_double_oracle(rn, N, H):
+    """The float block at sizes whose 3x3 layer splits its reduction over the waves (98 and 106 tiles of 64x64) and at one
+    whose does not (392).  Another summation order puts a pre-activation within rounding of zero on the other side of the
+    ReLU, and one such decision moves a gradient by up to 2e-3; that is all that may differ.  So the decisions are counted
+    against the oracle in double, and with the same decisions every value is held to float rounding: a sum of n terms carries
+    about sqrt(n) roundings of 2^-24, and the longest sequential sums here (pixels of a split, tile rows) stay below 4096
+    terms, 4e-6.  (Seen: at most two decisions, |z| <= 8e-7; outputs 4e-7, gradients 1.4e-6.)"""
+    bar = 2.0 ** -24 * 4096 ** 0.5
+    C, Wd = 64, 64
+    x, T = synth.activation_nhwc(SEED, "x", N, C, H, H), synth.activation_nhwc(SEED, "T", N, 4 * Wd, H, H)
+    shapes = [(Wd, 1, 1, C), (Wd, 3, 3, Wd), (4 * Wd, 1, 1, Wd), (4 * Wd, 1, 1, C)]
+    params = []
+    for i, s in enumerate(shapes):
+        params += [synth.conv_weight_krsc(SEED, f"c{i}", s[0], s[3], s[1], s[2]), np.ones(s[0], np.float32),
+                   (0.1 * synth.normal(SEED, f"b{i}", (s[0],))).astype(np.float32)]
+    _, tape = net.bottleneck_fwd(x.astype(np.float64), [p.astype(np.float64) for p in params], 1, True)
+    P, xd = [dev(p) for p in params], dev(x)
+
+    def fwd(inp, i, pad, mode, res=None):
+        y = rn.conv_fwd(inp, P[3 * i], 1, pad)
+        z, mean, rstd = rn.bn_relu_fwd(y, P[3 * i + 1], P[3 * i + 2], res, 1e-5, mode)
+        return dict(x=inp, y=y, z=z, mean=mean, rstd=rstd, i=i, pad=pad, mode=mode)
+
+    def bwd(dz, t):
+        i = t["i"]
+        dy, dres, dg, db = rn.bn_relu_bwd(dz, t["y"], t["z"], P[3 * i + 1], t["mean"], t["rstd"], t["mode"], beta=P[3 * i + 2])
+        return (rn.conv_dgrad(dy, P[3 * i], t["x"].shape, 1, t["pad"]), dres,
+                [rn.conv_wgrad(t["x"], dy, P[3 * i].shape, 1, t["pad"]), dg, db])
+
+    t1 = fwd(xd, 0, 0, 1); t2 = fwd(t1["z"], 1, 1, 1); tp = fwd(xd, 3, 0, 0); t3 = fwd(t2["z"], 2, 0, 2, tp["z"])
+    differing = 0
+    for t_g, t_o in ((t1, tape[0]), (t2, tape[1]), (t3, tape[2])):
+        zg, zo = host(t_g["z"]).astype(np.float64), t_o["z"]
+        assert_close(zg, zo, bar, "z", elementwise=False)
+        differ = (zg > 0) != (zo > 0)
+        rms = np.sqrt(np.mean(zo * zo))
+        assert not differ.any() or np.maximum(zg, zo)[differ].max() <= bar * rms
+        differing += int(differ.sum())
+        t_o["z"] = np.where(zg > 0, np.maximum(zo, 1e-300), 0.0)
+    # a value of size rms lies within bar * rms of zero with a density of 0.4 per rms: a handful of the block's values
+    assert differing <= max(8, int(2 * 0.4 * bar * N * H * H * (2 * Wd + 4 * Wd))), differing
+    dx_o, grads_o = net.bottleneck_bwd(T.astype(np.float64), tape)
+    d2, dsc, g3 = bwd(dev(T), t3)
+    d1, _, g2 = bwd(d2, t2)
+    dxa, _, g1 = bwd(d1, t1)
+    dxb, _, gp = bwd(dsc, tp)
+    assert_close(dxa + dxb, dx_o, bar, "dx")
+    for k, (g, go) in enumerate(zip(g1 + g2 + g3 + gp, grads_o)):
+        assert_close(g, go, bar, f"gradient {k}")
+
+
 def setup_step(rn, mode_name, N, hw, widths, blocks, stem, classes, expansion=4, ls=0.0):
     bf = mode_name == "bf16"
     plan = rn.ResnetPlan(N, rn.BF16 if bf else rn.F32, hw, classes, widths, blocks, stem, expansion,
