@@ -16,9 +16,9 @@
 // Partial sums are combined in a fixed order, so results are bitwise reproducible.
 //
 // Variance uses shifted sums: every row of partials is summed in float about a shift K of its own (the first
-// element its producer saw), S1 = sum(x-K), S2 = sum((x-K)^2), and stored either moved to shift 0, in double, or as
-// its mean K + S1/n and the squared deviations from it, S2 - S1^2/n.  Nowhere does float rounding see the cancellation
-// of the plain E[x^2]-E[x]^2 form.  (Forms and layout of the rows: bn_sums_at.)
+// element its producer saw), S1 = sum(x-K), S2 = sum((x-K)^2), and stored either moved to shift 0, in double, or with its
+// shift; all combining is in double.  Nowhere does float rounding see the cancellation of the plain E[x^2]-E[x]^2 form.
+// (Forms and layout of the rows: bn_sums_at.)
 #include <stdlib.h>
 
 #include <algorithm>
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ x, 
   const float k = Elem<T>::load(x + c);
   const int64_t at = bn_sums_at(blockIdx.x, c, gridDim.x);
   if (wide) reinterpret_cast<double2*>(partial)[at] = bn_tile_sums(k, t1, t2, static_cast<int>(r1 - r0));
-  else reinterpret_cast<float2*>(partial)[at] = bn_tile_moments(k, t1, t2, static_cast<int>(r1 - r0));
+  else reinterpret_cast<BnTileRow*>(partial)[at] = BnTileRow{k, t1, t2};
 }
 
 // Finalize passes, for layers with more rows of partial sums than an apply pass should add up itself.  A workgroup takes
@@ -232,26 +232,26 @@ __device__ __forceinline__ void finalize_combine(double* s1, double* s2) {
   }
 }
 
-// Forward: adds row b's (mean, squared deviations) over n rows of x to the sums s1 = sum(x - k0), s2 = sum((x - k0)^2).
-__device__ __forceinline__ void add_moments(float2 v, double n, double k0, double* s1, double* s2) {
-  const double e = static_cast<double>(v.x) - k0;
-  *s1 += n * e;
-  *s2 += static_cast<double>(v.y) + n * (e * e);
+// Forward: adds a row of sums over n rows of x to s1 = sum(x - k0), s2 = sum((x - k0)^2).
+__device__ __forceinline__ void add_tile_row(const BnTileRow& v, double n, double k0, double* s1, double* s2) {
+  const double e = static_cast<double>(v.k) - k0, d1 = static_cast<double>(v.s1);
+  *s1 += d1 + n * e;
+  *s2 += static_cast<double>(v.s2) + e * (2.0 * d1 + n * e);
 }
 __device__ __forceinline__ double rows_of(int b, int nrows, int rpp, int64_t m) {  // rows of x behind row b of the sums
   return static_cast<double>(b == nrows - 1 ? m - static_cast<int64_t>(b) * rpp : rpp);
 }
 
-// Forward: rows of (mean, squared deviations) over rpp rows of x each (the last over what is left of m), or of sums (wide;
-// for a layer whose apply pass is left to its consumer).
+// Forward: rows of sums over rpp rows of x each (the last over what is left of m), with their shifts, or about zero (wide; for
+// a layer whose apply pass is left to its consumer).
 __global__ __launch_bounds__(kFinThreads) void bn_finalize_kernel(const float* __restrict__ partial, int nrows, int rpp,
                                                            int wide, int64_t m, int C, float eps, float* __restrict__ mean_out,
                                                            float* __restrict__ rstd_out, float* running_mean,
                                                            float* running_var, float momentum) {
   constexpr int G = kFinThreads / kFinCh;
   const int c = blockIdx.x * kFinCh + threadIdx.x % kFinCh;
-  const float2* p = reinterpret_cast<const float2*>(partial) + bn_sums_at(0, c, nrows);  // (the last piece of C is padded)
-  const double k0 = wide ? 0.0 : static_cast<double>(p[0].x);
+  const BnTileRow* p = reinterpret_cast<const BnTileRow*>(partial) + bn_sums_at(0, c, nrows);  // (the last piece of C is padded)
+  const double k0 = wide ? 0.0 : static_cast<double>(p[0].k);
   double s1 = 0.0, s2 = 0.0;
   if (wide) {
     const double2* pd = reinterpret_cast<const double2*>(partial) + bn_sums_at(0, c, nrows);
@@ -262,12 +262,12 @@ __global__ __launch_bounds__(kFinThreads) void bn_finalize_kernel(const float* _
     nrows = 0;
   }
   for (int b = threadIdx.x / kFinCh; b < nrows; b += kFinRows * G) {
-    float2 v[kFinRows];
+    BnTileRow v[kFinRows];
 #pragma unroll
     for (int u = 0; u < kFinRows; ++u) v[u] = p[min(b + u * G, nrows - 1) * 8];
 #pragma unroll
     for (int u = 0; u < kFinRows; ++u)
-      if (b + u * G < nrows) add_moments(v[u], rows_of(b + u * G, nrows, rpp, m), k0, &s1, &s2);
+      if (b + u * G < nrows) add_tile_row(v[u], rows_of(b + u * G, nrows, rpp, m), k0, &s1, &s2);
   }
   finalize_combine(&s1, &s2);
   if (threadIdx.x >= kFinCh || c >= C) return;
@@ -724,7 +724,7 @@ int bn_desc_check(const rn50_bn_desc* d, const char* who) { return check_desc(d,
 static size_t bn_ws_bytes(const rn50_bn_desc* d) {
   const int64_t m = static_cast<int64_t>(d->N) * d->H * d->W;
   const BnGeom g = bn_sums_geom(m, d->C, d->dtype);
-  return align_up(bn_sums_bytes(g.nblk, d->C, bn_self_sums(m, d->C)), 256);
+  return align_up(bn_sums_bytes(g.nblk, d->C, bn_self_sums(m, d->C) ? kBnWideSumBytes : kBnTileRowBytes), 256);
 }
 
 // finalize + apply from partial statistics rows (see bn_finalize_kernel)

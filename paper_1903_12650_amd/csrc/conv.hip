@@ -79,7 +79,7 @@ struct IgemmArgs {
   FastDiv div_ntn, div_w[2], div_h[2];
   int mode;         // host side only: selects the MODE template argument
   // Optional batch-norm sums over the rows of each output tile, taken from the rounded values that are
-  // stored (null: none), one row per tile row (bn_sums_at).  Forward: mean and squared deviations, from float sums about
+  // stored (null: none), one row per tile row (bn_sums_at).  Forward: float sums of the values and of their squares about
   // the tile's first row.  Data gradient: sum(g), sum(g * xhat) with g the output
   // gradient masked by the ReLU of the BN layer whose conv output is bn_x [M][Ncols], xhat its
   // normalized input.
@@ -807,9 +807,8 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     *reinterpret_cast<float4*>(cs + (orow * 2 + 1) * BN + op * V + j) = make_float4(s2[j], s2[j + 1], s2[j + 2], s2[j + 3]);
   }
   __syncthreads();
-  float2* const out2 = reinterpret_cast<float2*>(a.partial);
   if (MODE == 0) {
-    // one thread per column, from the tile's sums about the shift, in double
+    // one thread per column
     if (tid < BN && n0 + tid < a.Ncols) {
       float t1 = 0.f, t2 = 0.f;
 #pragma unroll 8
@@ -819,7 +818,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       }
       const int64_t at = bn_sums_at(mt, n0 + tid, a.mtiles);
       if (a.partial_wide) reinterpret_cast<double2*>(a.partial)[at] = bn_tile_sums(kshift, t1, t2, min(BM, Mc - m0));
-      else out2[at] = bn_tile_moments(kshift, t1, t2, min(BM, Mc - m0));
+      else reinterpret_cast<BnTileRow*>(a.partial)[at] = BnTileRow{kshift, t1, t2};
     }
     return;
   }
@@ -1284,8 +1283,8 @@ extern "C" size_t conv_bn_sums_bytes(const rn50_conv_desc* d) {
   if (!d || check_conv(d, "conv_bn_sums_bytes")) return 0;
   // one row per output tile of at least 32 pixels
   const int P = out_dim(d->H, d->pad, d->R, d->stride), Q = out_dim(d->W, d->pad, d->S, d->stride);
-  const size_t fwd = bn_sums_bytes(ceil_div(static_cast<int64_t>(d->N) * P * Q, 32), d->Cout, true);
-  const size_t bwd = bn_sums_bytes(dgrad_partial_rows_bound(d), d->Cin, false);
+  const size_t fwd = bn_sums_bytes(ceil_div(static_cast<int64_t>(d->N) * P * Q, 32), d->Cout, kBnWideSumBytes);
+  const size_t bwd = bn_sums_bytes(dgrad_partial_rows_bound(d), d->Cin, kBnBwdSumBytes);
   return align_up(fwd > bwd ? fwd : bwd, 256);
 }
 

@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const StemArgs a) {
     }
     const int64_t at = bn_sums_at(blockIdx.x, tid, gridDim.x);
     if (a.partial_wide) reinterpret_cast<double2*>(a.partial)[at] = make_double2(t1s + n * k0, t2s + k0 * (2.0 * t1s + n * k0));
-    else reinterpret_cast<float2*>(a.partial)[at] = make_float2(static_cast<float>(k0 + t1s / n), static_cast<float>(fmax(t2s - t1s * t1s / n, 0.0)));
+    else reinterpret_cast<BnTileRow*>(a.partial)[at] = BnTileRow{sums[0][0][tid], static_cast<float>(t1s), static_cast<float>(t2s)};
   }
 }
 

@@ -243,8 +243,8 @@ extern "C" int resnet_plan_create(const rn50_step_config* cfg, rn50_plan** plan_
     if (wgrad_partial_bytes(&u.conv) > max_wg) max_wg = wgrad_partial_bytes(&u.conv);
     if (bn_relu_fwd_workspace_bytes(&u.bn) > max_bn) max_bn = bn_relu_fwd_workspace_bytes(&u.bn);
     // sums fused into the convolutions: one row per output tile, at most ceil(M/32) rows
-    max_bn = std::max(max_bn, align_up(bn_sums_bytes(ceil_div(static_cast<int32_t>(N) * u.P * u.Q, 32), u.conv.Cout, true), 256));
-    if (u.conv.Cin != 3) max_bn = std::max(max_bn, align_up(bn_sums_bytes(dgrad_partial_rows_bound(&u.conv), u.conv.Cin, false), 256));
+    max_bn = std::max(max_bn, align_up(bn_sums_bytes(ceil_div(static_cast<int32_t>(N) * u.P * u.Q, 32), u.conv.Cout, kBnWideSumBytes), 256));
+    if (u.conv.Cin != 3) max_bn = std::max(max_bn, align_up(bn_sums_bytes(dgrad_partial_rows_bound(&u.conv), u.conv.Cin, kBnBwdSumBytes), 256));
   }
   p->pool = bump(&top, static_cast<size_t>(N) * Hpool * Hpool * cfg->stem * es);
   p->avg = bump(&top, static_cast<size_t>(N) * cin * es);

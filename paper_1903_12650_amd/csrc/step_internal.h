@@ -26,7 +26,6 @@ struct PartialRows {
 PartialRows fwd_partial_rows(const rn50_conv_desc* d);    // tiles of the forward convolution's output
 PartialRows dgrad_partial_rows(const rn50_conv_desc* d);  // tiles of the data gradient
 int64_t dgrad_partial_rows_bound(const rn50_conv_desc* d);  // most rows any tile choice gives (tiles of >= 32 pixels)
-// bn_partial (null: none): (mean, sum of squared deviations from it) per tile row and channel, see bn_sums_at.
 // An inference-mode BN layer applied in a convolution's output stage: [relu](gamma*(product - mean)/sqrt(var + eps) +
 // beta [+ residual]); residual: [M][Cout] or null.
 struct BnAffine {
@@ -39,18 +38,20 @@ void stem_fwd_padded(const rn50_conv_desc* d, const void* xp, const void* w, voi
                      hipStream_t s, const BnAffine* affine = nullptr);
 // A BN+ReLU layer applied to a convolution's input on the fly (1x1, stride 1 convolutions only): its parameters
 // and saved statistics, float[Cin] each.
-// The BN sums that a convolution's output stage (or a stand-alone sums pass) leaves: one row per row tile, a pair per row
-// and channel.  Backward: the floats (sum g, sum g * xhat).  Forward, two forms: for a reader that adds rows up in every
-// workgroup (bn_self_finalizes), the doubles (sum y, sum y^2), moved from the tile's shift to shift 0 by the writer so that
-// the readers only add; else, for the finalize launch, the floats (mean of the tile's rows, sum of their squared deviations
-// from it), which are combined in double about the first tile's mean: half the bytes, which at 12544 rows count.
+// The BN sums that a convolution's output stage (or a stand-alone sums pass) leaves, one row per row tile.  Backward: the floats
+// (sum g, sum g * xhat) per row and channel.  Forward, two forms: for a reader that adds rows up in every workgroup
+// (bn_self_finalizes), the doubles (sum y, sum y^2), moved from the tile's shift to shift 0 by the writer so that the readers
+// only add; else, for the finalize launch, the floats of a BnTileRow (shift, sums about it), which that launch moves to the
+// first tile's shift in double: exact either way, and at 12544 rows the fewer bytes count.
 // Eight channels by all rows are contiguous: the writer stores whole 64-byte pieces (with the rows of a single channel
 // contiguous its 2 to 3 * 64 sums were a partial cache line each), and a finalize workgroup reads one run of memory
 // (row-major, it picked 64 bytes out of every row: 12544 rows, batch 256, 45 us).
 __host__ __device__ inline int64_t bn_sums_at(int row, int c, int nrows) {
   return (static_cast<int64_t>(c >> 3) * nrows + row) * 8 + (c & 7);
 }
-inline size_t bn_sums_bytes(int64_t nrows, int C, bool wide) { return static_cast<size_t>(nrows) * ((C + 7) / 8 * 8) * (wide ? 16 : 8); }
+// Bytes per row and channel; bn_sums_bytes: of nrows rows.
+constexpr int kBnBwdSumBytes = 8, kBnTileRowBytes = 12, kBnWideSumBytes = 16;
+inline size_t bn_sums_bytes(int64_t nrows, int C, int each) { return static_cast<size_t>(nrows) * ((C + 7) / 8 * 8) * each; }
 // They are added up by a finalize launch, or, when there are few tile rows, by the BN apply pass (forward or backward)
 // itself, in every workgroup, for the channels it applies: the launch in front of it -- about 4 us on the step's
 // dependency chain whatever it computes -- is gone.

@@ -90,6 +90,21 @@ def test_conv_fwd_bn_sums_large_mean_and_running_stats(rn):
     assert_close(rv, rv_o, 1e-4, "running_var")
 
 
+@pytest.mark.parametrize("N,H,C,K", [(40, 28, 64, 72), (8, 28, 64, 72)])
+def test_conv_fwd_bn_sums_mean_far_from_zero(rn, N, H, C, K):
+    """Outputs 4000 +- 0.5 in float: the statistics stay within 2^-22 of their 64-bit values, summed by the finalize launch (490
+    tile rows) and by the apply pass (98)."""
+    x = synth.activation_nhwc(SEED, "x", N, C, H, H) * 4.0 + 4000.0
+    w = np.full((K, 1, 1, C), 1.0 / C, np.float32)
+    y, sums = rn.conv_fwd_bn_sums(dev(x), dev(w), 1, 0)
+    _, mean, rstd = rn.bn_relu_fwd_from_sums(y, sums, dev(np.ones(K, np.float32)), dev(np.zeros(K, np.float32)), None, 1e-5, 0)
+    y64 = host(y).reshape(-1, K).astype(np.float64)
+    mean_o, rstd_o = y64.mean(0), 1.0 / np.sqrt(y64.var(0) + 1e-5)
+    assert (mean_o * rstd_o).min() > 4000
+    assert np.all(np.abs(host(mean) - mean_o) <= 2.0 ** -24 * mean_o + 2.0 ** -22 / rstd_o)
+    assert np.abs(host(rstd) / rstd_o - 1).max() <= 2.0 ** -22, np.abs(host(rstd) / rstd_o - 1).max() * 2 ** 24
+
+
 DGRAD_SHAPES = [s for s in FUSED_SHAPES if s[3] != 3]
 
 

@@ -110,6 +110,31 @@ def test_bn_running_stats_and_large_mean(rn):
     assert_close(rv, rv_o, 1e-3, "running_var")
 
 
+# Stand-alone sums at the edges of their two forms: 32768 rows and 4 M elements are the last that the apply pass adds up
+# itself.  A mean far from zero: 8000 standard deviations in float, 60 in bf16.
+@pytest.mark.parametrize("mode_name,mean,std", [("f32", 0.2, 1.3), ("f32", 4000.0, 0.5), ("bf16", 30.0, 0.5)])
+@pytest.mark.parametrize("shape", [(1, 128, 256, 64), (1, 128, 256, 128), (1, 128, 256, 136), (1, 129, 255, 64), (1, 1, 32769, 8)])
+def test_bn_sums_forms(rn, mode_name, mean, std, shape):
+    """Batch statistics within 2^-22 of their 64-bit values (one rounding of the result is 2^-24, the rest is for the tiles'
+    float sums about a shift of their own), whatever the mean; the backward sums at the usual bar."""
+    N, H, W, C = shape
+    bf = mode_name == "bf16"
+    x = synth.activation_nhwc(SEED, "x", N, C, H, W) * std + mean
+    x, dz = inputs(mode_name, x, synth.activation_nhwc(SEED, "dz", N, C, H, W))
+    g, b = np.ones(C, np.float32), np.zeros(C, np.float32)
+    z, m, r = rn.bn_relu_fwd(dev(x, bf), dev(g), dev(b), None, 1e-5, 0)
+    x64 = x.reshape(-1, C).astype(np.float64)
+    mean_o, rstd_o = x64.mean(0), 1.0 / np.sqrt(x64.var(0) + 1e-5)
+    assert np.all(np.abs(host(m) - mean_o) <= 2.0 ** -24 * np.abs(mean_o) + 2.0 ** -22 / rstd_o)
+    assert np.abs(host(r) / rstd_o - 1).max() <= 2.0 ** -22, np.abs(host(r) / rstd_o - 1).max() * 2 ** 24
+    if mean > 100:
+        return  # (the backward pass forms x * rstd - mean * rstd in float: 2^-24 * 8000 per element, beyond its bar by itself)
+    dx, _, dg, db = rn.bn_relu_bwd(dev(dz, bf), dev(x, bf), None, dev(g), m, r, 0)
+    dx_o, _, dg_o, db_o = orc.bn_relu_bwd(dz, x, host(z), g, host(m), host(r), 0)
+    for got, want, name in ((dx, dx_o, "dx"), (dg, dg_o, "dgamma"), (db, db_o, "dbeta")):
+        assert_close(got, want, TOL[mode_name], name)
+
+
 def test_bn_bitwise_reproducible(rn):
     x = dev(synth.activation_nhwc(SEED, "x", 8, 64, 56, 56), True)
     g = dev(np.ones(64, np.float32)); b = dev(np.zeros(64, np.float32))
