@@ -447,17 +447,17 @@ class LarsTable:
         """The current stream's next kernels read the device table: behind its copy, whichever stream that was queued on."""
         if self._ready is None:
             return
-        capturing = torch.cuda.is_current_stream_capturing()
-        if not self._arrived:
+        capturing, elsewhere = torch.cuda.is_current_stream_capturing(), _raw_stream() != self._stream
+        if not self._arrived and (capturing or elsewhere):
             if capturing:
                 # A capture cannot wait for an event from outside it, and the graph may replay on any stream: it brings the
                 # table along (the same bytes).
                 self.dev.copy_(self._pinned, non_blocking=True)
             elif self._ready.query():
                 self._arrived = True
-            elif _raw_stream() != self._stream:
+            else:
                 torch.cuda.current_stream().wait_event(self._ready)
-        if not capturing and _raw_stream() != self._stream:
+        if elsewhere and not capturing:
             self.dev.record_stream(torch.cuda.current_stream())  # (its memory belongs to the construction's stream)
 
 
