@@ -448,14 +448,14 @@ class LarsTable:
         if self._ready is None:
             return
         capturing, elsewhere = torch.cuda.is_current_stream_capturing(), _raw_stream() != self._stream
-        if not self._arrived and (capturing or elsewhere):
+        if not self._arrived:
             if capturing:
                 # A capture cannot wait for an event from outside it, and the graph may replay on any stream: it brings the
                 # table along (the same bytes).
                 self.dev.copy_(self._pinned, non_blocking=True)
             elif self._ready.query():
                 self._arrived = True
-            else:
+            elif elsewhere:
                 torch.cuda.current_stream().wait_event(self._ready)
         if elsewhere and not capturing:
             self.dev.record_stream(torch.cuda.current_stream())  # (its memory belongs to the construction's stream)
