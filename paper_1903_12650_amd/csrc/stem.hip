@@ -44,11 +44,11 @@ struct StemArgs {
 template <bool AFF>
 __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const StemArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ float sums[4][3][64];                  // per wave: shift, S1, S2
+  __shared__ double sums[4][2][64];                 // per wave: sums of the values and of their squares
   __shared__ __align__(16) float prm[AFF ? 128 : 4];  // scale, bias
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
   unsigned char* const stage = smem + 2 * a.patch_lds + wave * kStemStage;
-  const int t0 = blockIdx.x * a.per_wg, t1 = min(t0 + a.per_wg, a.tiles);
+  const int tile0 = blockIdx.x * a.per_wg, tile1 = min(tile0 + a.per_wg, a.tiles);
 
   // The weights as [channel][row][tap][4 channels] in LDS (over the image buffers, which are not in use yet), then this
   // lane's fragments of them: channel l32 (+ 32), values 8 * half .. of every k step.
@@ -94,16 +94,18 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const StemArgs a) {
   const int npix = a.rows * a.Q, nblk = (npix + 31) >> 5;
   const int op = lane & 7, orow = lane >> 3;      // output stage: 16-byte piece and row of a pass
   const bool col_ok = op * 8 < a.Cout;
-  float s1[8], s2[8], shift[8];
-  bool have_shift = false;
-  int counted = 0;                                 // this wave's pixels in the sums
+  // Sums of what is stored, about zero, in double: a lane adds up to some 200 pixels at batch 256.  (In float about the wave's
+  // first pixel 1 / std was 6.3 units in the last place off at batch 256, and 160 where images have a mean of 5 and that pixel
+  // lies at the border; the general kernel's tiles: 1.0 and 1.9; this: 0.5.  A square of a bf16 value is exact in double.  It
+  // costs 30.1 -> 32.0 us at batch 40, 133.6 -> 138.1 at batch 256.)
+  double s1[8], s2[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) s1[j] = s2[j] = shift[j] = 0.f;
-  if (t0 < t1) load_patch(t0, 0);
-  for (int t = t0; t < t1; ++t) {
+  for (int j = 0; j < 8; ++j) s1[j] = s2[j] = 0.0;
+  if (tile0 < tile1) load_patch(tile0, 0);
+  for (int t = tile0; t < tile1; ++t) {
     wait_loads_then_barrier<0>();                  // tile t has landed; everybody is done with tile t - 1
-    if (t + 1 < t1) load_patch(t + 1, (t + 1 - t0) & 1);
-    const unsigned char* img = smem + ((t - t0) & 1) * a.patch_lds;
+    if (t + 1 < tile1) load_patch(t + 1, (t + 1 - tile0) & 1);
+    const unsigned char* img = smem + ((t - tile0) & 1) * a.patch_lds;
     const int64_t m0 = static_cast<int64_t>(t) * npix;
     for (int blk = wave; blk < nblk; blk += 4) {
       const int px = blk * 32 + l32, pc = px < npix ? px : npix - 1;
@@ -140,14 +142,7 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const StemArgs a) {
       Vec16 o[4];
 #pragma unroll
       for (int p = 0; p < 4; ++p) o[p].u = *reinterpret_cast<const uint4*>(stage + (orow + p * 8) * kStemRowBytes + op * 16);
-      if (!AFF && a.partial && !have_shift) {  // the shift: the wave's first pixel
-        Vec16 k0;
-        k0.u = *reinterpret_cast<const uint4*>(stage + op * 16);
-        Elem<uint16_t>::unpack(k0, shift);
-        have_shift = true;
-      }
       const int live = min(32, npix - blk * 32);
-      counted += live;
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
         const int r = orow + p * 8;
@@ -158,9 +153,9 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const StemArgs a) {
             Elem<uint16_t>::unpack(o[p], f);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-              const float d = f[j] - shift[j];
+              const double d = static_cast<double>(f[j]);
               s1[j] += d;
-              s2[j] = fmaf(d, d, s2[j]);
+              s2[j] = fma(d, d, s2[j]);
             }
           }
         }
@@ -168,8 +163,7 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const StemArgs a) {
     }
   }
   if (AFF || a.partial == nullptr) return;
-  // The sums of the workgroup's pixels: eight row groups of a wave by shuffles, the four waves (each about its own first
-  // pixel) moved to wave 0's shift exactly enough in double.
+  // The sums of the workgroup's pixels: eight row groups of a wave by shuffles, then the four waves in order.
 #pragma unroll
   for (int off = 8; off < 64; off <<= 1)
 #pragma unroll
@@ -177,30 +171,26 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const StemArgs a) {
       s1[j] += __shfl_xor(s1[j], off, 64);
       s2[j] += __shfl_xor(s2[j], off, 64);
     }
-  __shared__ int count[4];
-  if (lane == 0) count[wave] = counted;
   if (orow == 0) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      sums[wave][0][op * 8 + j] = shift[j];
-      sums[wave][1][op * 8 + j] = s1[j];
-      sums[wave][2][op * 8 + j] = s2[j];
+      sums[wave][0][op * 8 + j] = s1[j];
+      sums[wave][1][op * 8 + j] = s2[j];
     }
   }
   __syncthreads();
   if (tid < a.Cout) {
-    const double k0 = static_cast<double>(sums[0][0][tid]);
-    double t1s = static_cast<double>(sums[0][1][tid]), t2s = static_cast<double>(sums[0][2][tid]), n = count[0];
-#pragma unroll
-    for (int w = 1; w < 4; ++w) {
-      const double e = static_cast<double>(sums[w][0][tid]) - k0, d1 = static_cast<double>(sums[w][1][tid]), cn = count[w];
-      t1s += d1 + cn * e;
-      t2s += static_cast<double>(sums[w][2][tid]) + e * (2.0 * d1 + cn * e);
-      n += cn;
-    }
+    const double t1 = ((sums[0][0][tid] + sums[1][0][tid]) + sums[2][0][tid]) + sums[3][0][tid];
+    const double t2 = ((sums[0][1][tid] + sums[1][1][tid]) + sums[2][1][tid]) + sums[3][1][tid];
     const int64_t at = bn_sums_at(blockIdx.x, tid, gridDim.x);
-    if (a.partial_wide) reinterpret_cast<double2*>(a.partial)[at] = make_double2(t1s + n * k0, t2s + k0 * (2.0 * t1s + n * k0));
-    else reinterpret_cast<BnTileRow*>(a.partial)[at] = BnTileRow{sums[0][0][tid], static_cast<float>(t1s), static_cast<float>(t2s)};
+    if (a.partial_wide) {
+      reinterpret_cast<double2*>(a.partial)[at] = make_double2(t1, t2);
+    } else {  // moved to their mean, rounded to float, as shift
+      const double n = static_cast<double>((tile1 - tile0) * npix);
+      const float k = static_cast<float>(t1 / n);
+      const double kd = static_cast<double>(k);
+      reinterpret_cast<BnTileRow*>(a.partial)[at] = BnTileRow{k, static_cast<float>(t1 - n * kd), static_cast<float>(t2 - kd * (2.0 * t1 - n * kd))};
+    }
   }
 }
 

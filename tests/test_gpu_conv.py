@@ -183,6 +183,24 @@ def test_stem_tiles(rn, N, H, W, K):
     assert_close(rstd, host(rstd2), 1e-5, "rstd")
 
 
+@pytest.mark.parametrize("N,HW,mean", [(4, 224, 5.0), (40, 224, 5.0), (256, 224, 0.0), (256, 224, 5.0)])
+def test_stem_sums_against_64_bits(rn, N, HW, mean):
+    """The stem's batch statistics over 1 to 28 tiles per workgroup, also where the images' mean is far from zero and the border
+    pixels far from the others: within 2^-23 of the 64-bit values of the stored outputs (sums in double; one rounding of a
+    workgroup's row, which averages out, and one of the result, 2^-24)."""
+    gen = torch.Generator(device="cuda").manual_seed(SEED)
+    x = (mean + torch.randn((N, HW, HW, 3), device="cuda", generator=gen)).bfloat16()
+    w = dev(inputs("bf16", synth.conv_weight_krsc(SEED, "w", 64, 3, 7, 7))[0], True)
+    y, handle = rn.conv_fwd_bn_sums(x, w, 2, 3)
+    _, m, r = rn.bn_relu_fwd_from_sums(y, handle, torch.ones(64, device="cuda"), torch.zeros(64, device="cuda"))
+    y64 = y.view(-1, 64).double()
+    mean_o = y64.mean(0)
+    var_o = (y64 - mean_o).square().mean(0)
+    rstd_o = (var_o + 1e-5).rsqrt()
+    assert float((m.double() - mean_o).abs().div(mean_o.abs() + var_o.sqrt()).max()) <= 2.0 ** -23
+    assert float((r.double() / rstd_o - 1).abs().max()) <= 2.0 ** -23
+
+
 # Where the waves of a workgroup split the reduction (few output tiles, at least four 128-byte chunks): chunk counts that
 # are and are not multiples of four, ragged channels, the tile counts at which the tile changes, stride-2 pixel classes,
 # the channel count beyond which the linear forward kernel keeps the shared ring.
