@@ -338,11 +338,16 @@ __device__ __forceinline__ void finalize_slice_fwd(const BnFinArgs& f, int64_t m
   __syncthreads();
 }
 
-// FIN: the pass takes its statistics from the row-major per-tile sums itself (fin), every workgroup for the 8
+// FIN: the pass takes its statistics from the per-tile sums itself (fin), every workgroup for the 8
 // vector columns it applies (tx_log2 = 3), and the first row block of every column slice stores them: no
 // finalize launch in front.  For layers with few tile rows the redundant reads of the sums are far cheaper than a
 // launch on the step's dependency chain (about 4 us whatever it computes).
-template <typename T, bool FIN = false>
+// LAST (apply passes of both directions): nobody reads the operands again for a long while, as in a training step, where the
+// next layers are larger than the caches: their loads bypass the caches, which keep what the next kernel reads -- the output,
+// the weight gradient's operands.  Whole step: batch 40 4.506 -> 4.457 ms, batch 256 20.90 -> 20.55 (stores past the caches
+// made batch 40 slower).  Not for the calls of one operation, whose next one may read the same tensor: bn_relu_fwd and then
+// bn_relu_bwd over ResNet-50's layers at batch 40 take 589 us with these loads and 523 without.
+template <typename T, bool FIN, bool LAST>
 __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ x,
                                                        const float* __restrict__ gamma,
                                                        const float* __restrict__ beta,
@@ -368,11 +373,11 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ x,
 #pragma unroll
     for (int u = 0; u < kBnRows; ++u) {
       off[u] = min(r + u * TY, r1 - 1) * C + static_cast<int64_t>(col) * V;
-      vx[u] = load16_stream(x + off[u]);
+      vx[u] = LAST ? load16_stream(x + off[u]) : load16(x + off[u]);
     }
     if (mode == 2) {
 #pragma unroll
-      for (int u = 0; u < kBnRows; ++u) vr[u] = load16_stream(residual + off[u]);
+      for (int u = 0; u < kBnRows; ++u) vr[u] = LAST ? load16_stream(residual + off[u]) : load16(residual + off[u]);
     }
   };
   // the first rows are requested before the per-channel values, so both arrive in one round trip
@@ -442,9 +447,6 @@ struct BwdRows {
   uint32_t zbits[ZK == 2 ? kBnRows : 1];
   int64_t off[kBnRows];
 };
-// LAST: the apply pass is the last reader of x and dz for a long while (so is the forward apply pass of its operands): their
-// loads bypass the caches, which keep what the next kernel reads -- dx, the weight gradient's operands.  Whole step, both
-// directions: batch 40 4.506 -> 4.457 ms, batch 256 20.90 -> 20.55 (stores past the caches made batch 40 slower).
 template <bool LAST, typename T, bool DZ2, int ZK>
 __device__ __forceinline__ void load_bwd_rows(BwdRows<DZ2, ZK>& b, const T* dz, const T* dz2, const T* x,
                                               const T* z, const uint8_t* zmask, int64_t r, int64_t r1, int TY,
@@ -627,9 +629,9 @@ __device__ __forceinline__ void finalize_slice_bwd(const BnFinArgs& f, int C, in
   __syncthreads();
 }
 
-// FIN: as in bn_apply_kernel -- the pass adds up the row-major per-tile sums of its 8 vector columns itself
+// FIN, LAST: as in bn_apply_kernel -- the pass adds up the per-tile sums of its 8 vector columns itself
 // (tx_log2 = 3) and the first row block of every column slice stores dgamma / dbeta.
-template <typename T, bool DZ2, int ZK, bool FIN = false>
+template <typename T, bool DZ2, int ZK, bool FIN, bool LAST>
 __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(
     const T* __restrict__ dz, const T* __restrict__ dz2, const T* __restrict__ x,
     const T* __restrict__ z, const uint8_t* __restrict__ zmask, const float* __restrict__ gamma,
@@ -650,7 +652,7 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(
   int64_t r = r0 + trow;
   // the first rows are requested before the per-channel values, so both arrive in one round trip
   BwdRows<DZ2, ZK> b;
-  if (live && r < r1) load_bwd_rows<true, T, DZ2, ZK>(b, dz, dz2, x, z, zmask, r, r1, TY, C, col);
+  if (live && r < r1) load_bwd_rows<LAST, T, DZ2, ZK>(b, dz, dz2, x, z, zmask, r, r1, TY, C, col);
   const float inv_m = 1.0f / static_cast<float>(m);
   float scale[V], bias[V], rs[V], nmr[V], mg[V], mgx[V], cg[V], cb[V], cm[V];
   load_floats<V>(gamma + col * V, cg);
@@ -682,7 +684,7 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(
     mgx[j] *= inv_m;
   }
   for (; r < r1; r += kBnRows * TY) {
-    if (r != r0 + trow) load_bwd_rows<true, T, DZ2, ZK>(b, dz, dz2, x, z, zmask, r, r1, TY, C, col);
+    if (r != r0 + trow) load_bwd_rows<LAST, T, DZ2, ZK>(b, dz, dz2, x, z, zmask, r, r1, TY, C, col);
 #pragma unroll
     for (int u = 0; u < kBnRows; ++u) {
       if (r + u * TY < r1) {
@@ -728,8 +730,8 @@ static size_t bn_ws_bytes(const rn50_bn_desc* d) {
 }
 
 // finalize + apply from partial statistics rows (see bn_finalize_kernel)
-template <typename T>
-static void launch_fwd_tail(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const void* x,
+template <typename T, bool LAST>
+static void launch_fwd_tail(const rn50_bn_desc* d, int64_t m, const void* x,
                             const float* gamma, const float* beta, const void* residual, void* y,
                             uint8_t* relu_mask, float* save_mean, float* save_rstd, float* rm, float* rv,
                             float momentum, const float* partial, int nrows, int rpp, bool self, hipStream_t s) {
@@ -738,7 +740,7 @@ static void launch_fwd_tail(const rn50_bn_desc* d, const BnGeom& g, int64_t m, c
     int gy, rpb;
     bn_self_finalize_geom(m, d->C, d->dtype == RN50_BF16 ? 8 : 4, &gy, &rpb);
     const BnFinArgs fin{partial, nrows, d->eps, momentum, save_mean, save_rstd, rm, rv};
-    RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, true>), dim3(static_cast<unsigned>(ceil_div(m, rpb)), gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, nullptr, nullptr, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, 3, rpb, d->mode, fin);
+    RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, true, LAST>), dim3(static_cast<unsigned>(ceil_div(m, rpb)), gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, nullptr, nullptr, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, 3, rpb, d->mode, fin);
     return;
   }
 #ifdef RN50_TUNING  // what-if measurement: the step without its finalize launches (results are then wrong)
@@ -749,7 +751,7 @@ static void launch_fwd_tail(const rn50_bn_desc* d, const BnGeom& g, int64_t m, c
   RN50_LAUNCH("bn_finalize", bn_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, partial, nrows, rpp, self ? 1 : 0, m, d->C, d->eps, save_mean, save_rstd, rm, rv, momentum);
   if (!y) return;  // statistics only: the consumer applies the layer while it loads its operand
   const BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnApplyGroups);
-  RN50_LAUNCH("bn_apply", bn_apply_kernel<T>, dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, save_mean, save_rstd, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, ga.tx_log2, ga.rpb, d->mode, BnFinArgs{});
+  RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, false, LAST>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, save_mean, save_rstd, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, ga.tx_log2, ga.rpb, d->mode, BnFinArgs{});
 }
 
 template <typename T>
@@ -759,13 +761,13 @@ static void launch_fwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const 
                        float momentum, float* partial, hipStream_t s) {
   const bool self = bn_self_sums(m, d->C);
   RN50_LAUNCH("bn_stats", bn_stats_kernel<T>, dim3(g.nblk, g.gy), dim3(256), 0, s, static_cast<const T*>(x), m, d->C, g.tx_log2, g.rpb, self ? 1 : 0, partial);
-  launch_fwd_tail<T>(d, g, m, x, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv, momentum,
+  launch_fwd_tail<T, false>(d, m, x, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv, momentum,
                      partial, g.nblk, g.rpb, self, s);
 }
 
 // finalize + apply from partial sums rows [sum g, sum g*xhat]
-template <typename T>
-static void launch_bwd_tail(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const void* dz,
+template <typename T, bool LAST>
+static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
                             const void* dz2, const void* x, const void* z, const uint8_t* zmask,
                             const float* gamma, const float* beta, const float* mean, const float* rstd,
                             void* dx, void* dres, float* dgamma, float* dbeta, const float* partial,
@@ -787,7 +789,7 @@ static void launch_bwd_tail(const rn50_bn_desc* d, const BnGeom& g, int64_t m, c
     RN50_LAUNCH("bn_bwd_finalize", bn_bwd_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, partial, nrows, d->C, dgamma, dbeta);
   }
 #define RN50_BWD_APPLY_K(DZ2, ZK, FIN)                                                                             \
-  RN50_LAUNCH("bn_bwd_apply", (bn_bwd_apply_kernel<T, DZ2, ZK, FIN>), dim3(ga.nblk, ga.gy), dim3(256), 0, s,       \
+  RN50_LAUNCH("bn_bwd_apply", (bn_bwd_apply_kernel<T, DZ2, ZK, FIN, LAST && ZK != 1>), dim3(ga.nblk, ga.gy), dim3(256), 0, s,       \
               static_cast<const T*>(dz), static_cast<const T*>(dz2), static_cast<const T*>(x),                     \
               static_cast<const T*>(z), zmask, gamma, beta, mean, rstd, dgamma, dbeta, static_cast<T*>(dx),        \
               static_cast<T*>(dres), m, d->C, ga.tx_log2, ga.rpb, d->mode, fin)
@@ -805,7 +807,7 @@ static void launch_bwd_tail(const rn50_bn_desc* d, const BnGeom& g, int64_t m, c
 #undef RN50_BWD_APPLY_K
 }
 
-template <typename T>
+template <typename T, bool LAST>
 static void launch_bwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const void* dz,
                        const void* dz2, const void* x, const void* z, const uint8_t* zmask,
                        const float* gamma, const float* beta, const float* mean, const float* rstd, void* dx,
@@ -822,24 +824,26 @@ static void launch_bwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const 
     if (zk == 2) RN50_BWD_REDUCE(false, 2); else if (zk == 1) RN50_BWD_REDUCE(false, 1); else RN50_BWD_REDUCE(false, 0);
   }
 #undef RN50_BWD_REDUCE
-  launch_bwd_tail<T>(d, g, m, dz, dz2, x, z, zmask, gamma, beta, mean, rstd, dx, dres, dgamma, dbeta, partial,
+  launch_bwd_tail<T, LAST>(d, m, dz, dz2, x, z, zmask, gamma, beta, mean, rstd, dx, dres, dgamma, dbeta, partial,
                      g.nblk, self, s);
 }
 
-// Entry points for the whole-step driver and the fused C-ABI calls: the sums come from the output stage
+// Entry points for the whole-step driver (last_reader) and the fused C-ABI calls: the sums come from the output stage
 // of the convolution that produced x (forward) or dz (backward).
+template <typename T, bool LAST>
+static void fwd_from_partials(const rn50_bn_desc* d, const void* x, const float* partial, int nrows, int rpp,
+                              const float* gamma, const float* beta, const void* residual, void* y, uint8_t* relu_mask,
+                              float* save_mean, float* save_rstd, float* rm, float* rv, float momentum, hipStream_t s) {
+  launch_fwd_tail<T, LAST>(d, static_cast<int64_t>(d->N) * d->H * d->W, x, gamma, beta, residual, y, relu_mask, save_mean,
+                           save_rstd, rm, rv, momentum, partial, nrows, rpp, bn_self_finalizes(nrows, false), s);
+}
 void bn_fwd_from_partials(const rn50_bn_desc* d, const void* x, const float* partial, int nrows, int rpp,
                           const float* gamma, const float* beta, const void* residual, void* y,
                           uint8_t* relu_mask, float* save_mean, float* save_rstd, float* rm, float* rv,
-                          float momentum, hipStream_t s) {
-  const int64_t m = static_cast<int64_t>(d->N) * d->H * d->W;
-  const BnGeom g = bn_geom(m, d->C, d->dtype);
-  if (d->dtype == RN50_BF16)
-    launch_fwd_tail<uint16_t>(d, g, m, x, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv,
-                              momentum, partial, nrows, rpp, bn_self_finalizes(nrows, false), s);
-  else
-    launch_fwd_tail<float>(d, g, m, x, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv, momentum,
-                           partial, nrows, rpp, bn_self_finalizes(nrows, false), s);
+                          float momentum, bool last_reader, hipStream_t s) {
+  auto* run = d->dtype == RN50_BF16 ? (last_reader ? fwd_from_partials<uint16_t, true> : fwd_from_partials<uint16_t, false>)
+                                    : (last_reader ? fwd_from_partials<float, true> : fwd_from_partials<float, false>);
+  run(d, x, partial, nrows, rpp, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv, momentum, s);
 }
 // Evaluation mode: 1/sqrt(running_var + eps) per channel, then the training pass's apply kernel with the
 // moving averages in place of the batch statistics.
@@ -848,31 +852,43 @@ __global__ __launch_bounds__(256) void bn_infer_rstd_kernel(const float* __restr
   const int c = blockIdx.x * 256 + threadIdx.x;
   if (c < C) rstd[c] = static_cast<float>(1.0 / sqrt(static_cast<double>(running_var[c]) + static_cast<double>(eps)));
 }
-void bn_infer_run(const rn50_bn_desc* d, const void* x, const float* gamma, const float* beta,
-                  const float* running_mean, const float* running_var, const void* residual, void* y,
-                  float* rstd_scratch, hipStream_t s) {
+static void infer_run(const rn50_bn_desc* d, const void* x, const float* gamma, const float* beta,
+                      const float* running_mean, const float* running_var, const void* residual, void* y,
+                      float* rstd_scratch, hipStream_t s) {
   const int64_t m = static_cast<int64_t>(d->N) * d->H * d->W;
   hipLaunchKernelGGL(bn_infer_rstd_kernel, dim3(static_cast<unsigned>(ceil_div(d->C, 256))), dim3(256), 0, s,
                      running_var, d->eps, d->C, rstd_scratch);
   const BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnApplyGroups);
   if (d->dtype == RN50_BF16)
-    RN50_LAUNCH("bn_apply", bn_apply_kernel<uint16_t>, dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const uint16_t*>(x), gamma, beta, running_mean, rstd_scratch, static_cast<const uint16_t*>(residual), static_cast<uint16_t*>(y), static_cast<uint8_t*>(nullptr), m, d->C, ga.tx_log2, ga.rpb, d->mode, BnFinArgs{});
+    RN50_LAUNCH("bn_apply", (bn_apply_kernel<uint16_t, false, false>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const uint16_t*>(x), gamma, beta, running_mean, rstd_scratch, static_cast<const uint16_t*>(residual), static_cast<uint16_t*>(y), static_cast<uint8_t*>(nullptr), m, d->C, ga.tx_log2, ga.rpb, d->mode, BnFinArgs{});
   else
-    RN50_LAUNCH("bn_apply", bn_apply_kernel<float>, dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const float*>(x), gamma, beta, running_mean, rstd_scratch, static_cast<const float*>(residual), static_cast<float*>(y), static_cast<uint8_t*>(nullptr), m, d->C, ga.tx_log2, ga.rpb, d->mode, BnFinArgs{});
+    RN50_LAUNCH("bn_apply", (bn_apply_kernel<float, false, false>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const float*>(x), gamma, beta, running_mean, rstd_scratch, static_cast<const float*>(residual), static_cast<float*>(y), static_cast<uint8_t*>(nullptr), m, d->C, ga.tx_log2, ga.rpb, d->mode, BnFinArgs{});
 }
 
+template <typename T, bool LAST>
+static void bwd_from_partials(const rn50_bn_desc* d, const void* dz, const void* x, const uint8_t* relu_mask,
+                              const float* gamma, const float* beta, const float* mean, const float* rstd,
+                              const float* partial, int nrows, void* dx, void* dres, float* dgamma, float* dbeta,
+                              hipStream_t s) {
+  launch_bwd_tail<T, LAST>(d, static_cast<int64_t>(d->N) * d->H * d->W, dz, nullptr, x, nullptr, relu_mask, gamma, beta, mean,
+                           rstd, dx, dres, dgamma, dbeta, partial, nrows, bn_self_finalizes(nrows, true), s);
+}
 void bn_bwd_from_partials(const rn50_bn_desc* d, const void* dz, const void* x, const uint8_t* relu_mask,
                           const float* gamma, const float* beta, const float* mean, const float* rstd,
                           const float* partial, int nrows, void* dx, void* dres, float* dgamma, float* dbeta,
-                          hipStream_t s) {
+                          bool last_reader, hipStream_t s) {
+  auto* run = d->dtype == RN50_BF16 ? (last_reader ? bwd_from_partials<uint16_t, true> : bwd_from_partials<uint16_t, false>)
+                                    : (last_reader ? bwd_from_partials<float, true> : bwd_from_partials<float, false>);
+  run(d, dz, x, relu_mask, gamma, beta, mean, rstd, partial, nrows, dx, dres, dgamma, dbeta, s);
+}
+void bn_bwd_run(const rn50_bn_desc* d, const void* dz, const void* dz2, const void* x, const void* z,
+                const uint8_t* relu_mask, const float* gamma, const float* beta, const float* mean, const float* rstd,
+                void* dx, void* dres, float* dgamma, float* dbeta, float* scratch, bool last_reader, hipStream_t s) {
   const int64_t m = static_cast<int64_t>(d->N) * d->H * d->W;
-  const BnGeom g = bn_geom(m, d->C, d->dtype);
-  if (d->dtype == RN50_BF16)
-    launch_bwd_tail<uint16_t>(d, g, m, dz, nullptr, x, nullptr, relu_mask, gamma, beta, mean, rstd, dx, dres, dgamma,
-                              dbeta, partial, nrows, bn_self_finalizes(nrows, true), s);
-  else
-    launch_bwd_tail<float>(d, g, m, dz, nullptr, x, nullptr, relu_mask, gamma, beta, mean, rstd, dx, dres, dgamma,
-                           dbeta, partial, nrows, bn_self_finalizes(nrows, true), s);
+  const BnGeom g = bn_sums_geom(m, d->C, d->dtype);
+  auto* run = d->dtype == RN50_BF16 ? (last_reader ? launch_bwd<uint16_t, true> : launch_bwd<uint16_t, false>)
+                                    : (last_reader ? launch_bwd<float, true> : launch_bwd<float, false>);
+  run(d, g, m, dz, dz2, x, z, relu_mask, gamma, beta, mean, rstd, dx, dres, dgamma, dbeta, scratch, s);
 }
 
 }  // namespace rn50
@@ -932,15 +948,8 @@ extern "C" int bn_relu_bwd(const rn50_bn_desc* d, const void* dz, const void* dz
                RN50_ERR_ALIGN, "bn_relu_bwd: pointer not 16-byte aligned");
   RN50_REQUIRE(workspace_bytes >= bn_ws_bytes(d), RN50_ERR_WORKSPACE,
                "bn_relu_bwd: workspace %zu < %zu bytes", workspace_bytes, bn_ws_bytes(d));
-  const int64_t m = static_cast<int64_t>(d->N) * d->H * d->W;
-  const BnGeom g = bn_sums_geom(m, d->C, d->dtype);
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  if (d->dtype == RN50_BF16)
-    launch_bwd<uint16_t>(d, g, m, dz, dz2, x, z, relu_mask, gamma, beta, save_mean, save_rstd, dx, dresidual,
-                         dgamma, dbeta, static_cast<float*>(workspace), s);
-  else
-    launch_bwd<float>(d, g, m, dz, dz2, x, z, relu_mask, gamma, beta, save_mean, save_rstd, dx, dresidual,
-                      dgamma, dbeta, static_cast<float*>(workspace), s);
+  bn_bwd_run(d, dz, dz2, x, z, relu_mask, gamma, beta, save_mean, save_rstd, dx, dresidual, dgamma, dbeta,
+             static_cast<float*>(workspace), false, static_cast<hipStream_t>(stream));
   return launch_status("bn_relu_bwd");
 }
 
@@ -968,7 +977,7 @@ extern "C" int bn_relu_fwd_from_sums(const rn50_bn_desc* d, const rn50_conv_desc
                RN50_ERR_INVALID, "bn_relu_fwd_from_sums: the producer's output is not this layer's input");
   const PartialRows pr = fwd_partial_rows(producer);
   bn_fwd_from_partials(d, x, sums, pr.num, pr.rows, gamma, beta, residual, y, relu_mask, save_mean, save_rstd,
-                       running_mean, running_var, momentum, static_cast<hipStream_t>(stream));
+                       running_mean, running_var, momentum, false, static_cast<hipStream_t>(stream));
   return launch_status("bn_relu_fwd_from_sums");
 }
 
@@ -995,7 +1004,7 @@ extern "C" int bn_relu_bwd_from_sums(const rn50_bn_desc* d, const rn50_conv_desc
                RN50_ERR_INVALID, "bn_relu_bwd_from_sums: the producer's input is not this layer's output");
   const PartialRows pr = dgrad_partial_rows(producer);
   bn_bwd_from_partials(d, dz, x, relu_mask, gamma, beta, save_mean, save_rstd, sums, pr.num, dx,
-                       d->mode == 2 ? dresidual : nullptr, dgamma, dbeta, static_cast<hipStream_t>(stream));
+                       d->mode == 2 ? dresidual : nullptr, dgamma, dbeta, false, static_cast<hipStream_t>(stream));
   return launch_status("bn_relu_bwd_from_sums");
 }
 
@@ -1018,7 +1027,7 @@ extern "C" int bn_relu_infer(const rn50_bn_desc* d, const void* x, const float* 
                RN50_ERR_ALIGN, "bn_relu_infer: pointer not 16-byte aligned");
   RN50_REQUIRE(workspace_bytes >= bn_relu_infer_workspace_bytes(d), RN50_ERR_WORKSPACE,
                "bn_relu_infer: workspace %zu < %zu bytes", workspace_bytes, bn_relu_infer_workspace_bytes(d));
-  bn_infer_run(d, x, gamma, beta, running_mean, running_var, residual, y, static_cast<float*>(workspace),
-               static_cast<hipStream_t>(stream));
+  infer_run(d, x, gamma, beta, running_mean, running_var, residual, y, static_cast<float*>(workspace),
+            static_cast<hipStream_t>(stream));
   return launch_status("bn_relu_infer");
 }

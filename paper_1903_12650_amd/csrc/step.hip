@@ -64,7 +64,7 @@ struct rn50_plan {
   size_t xp = 0, wp = 0, pool = 0, avg = 0, logits = 0, dlogits = 0, row_loss = 0, davg = 0;
   size_t g[5] = {0, 0, 0, 0, 0};
   size_t wgrad_scratch = 0, bn_scratch = 0, pool_argmax = 0, fc_scratch = 0;
-  size_t bn_scratch_bytes = 0, fc_scratch_bytes = 0;
+  size_t fc_scratch_bytes = 0;
   std::vector<rn50::LarsGroup> lars_groups;  // in the order in which the backward pass completes them
   // Second stream for the work that is off the step's critical path (the weight gradients), with the events that order it against the caller's stream.  Created at the first
   // step (default priority), destroyed with the plan.
@@ -259,7 +259,6 @@ extern "C" int resnet_plan_create(const rn50_step_config* cfg, rn50_plan** plan_
   p->wgrad_scratch = bump(&top, max_wg);
   p->bn_scratch = bump(&top, max_bn);
   p->bn_scratch2 = bump(&top, max_bn);
-  p->bn_scratch_bytes = max_bn;
   plan_lars_groups(p);
   for (LarsGroup& g : p->lars_groups) g.scratch = bump(&top, lars_arena_partial_bytes(g.spec));
   p->ws_bytes = top;
@@ -441,7 +440,6 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
   auto G = [&](int ti) -> float* { return grads + plan->tensors[ti].offset; };
   auto F = [&](size_t off) -> float* { return reinterpret_cast<float*>(ws + off); };
   void* bn_ws = ws + plan->bn_scratch;
-  const size_t bn_ws_bytes = plan->bn_scratch_bytes;
   RN50_REQUIRE(cfg.dtype == RN50_F32 || master, RN50_ERR_INVALID,
                "resnet_step: BF16 mode reads BN gamma/beta and the FC bias from the float master arena");
 
@@ -472,7 +470,7 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
     // vector instead of z
     bn_fwd_from_partials(&u.bn, ws + u.y, sm, pr.num, pr.rows, MP(u.ig), MP(u.ib), residual,
                          stats_only ? nullptr : ws + u.z, u.bn.mode == 2 ? ws + u.relu_mask : nullptr, F(u.mean), F(u.rstd),
-                         run_mean ? run_mean + u.bn_off : nullptr, run_var ? run_var + u.bn_off : nullptr, bn_momentum, st);
+                         run_mean ? run_mean + u.bn_off : nullptr, run_var ? run_var + u.bn_off : nullptr, bn_momentum, true, st);
   };
   stem_fwd_padded(&u0.conv, ws + plan->xp, W(u0.iw), ws + plan->wp, ws + u0.y, sums, s);
   bn_after_conv(u0, nullptr, sums, s);
@@ -582,27 +580,26 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
   // BN, whose output gradient is the block output's gradient under the block's ReLU): for the backward
   // arithmetic that is a BN+ReLU layer with recorded bits.
   auto unit_bn_bwd = [&](Unit& u, const void* in, const void* dz, const void* dz2, void* dres, bool sums_ready,
-                         hipStream_t st, void* wsx, void** dy_out, const uint8_t* outer_bits = nullptr,
-                         const BnIn* bn_in = nullptr) -> int {
+                         hipStream_t st, void* wsx, const uint8_t* outer_bits = nullptr,
+                         const BnIn* bn_in = nullptr) -> void* {
     void* dy = ws + u.dy;
     // the ReLU mask: recorded bits (residual-add layers) or recomputed from x (BN+ReLU layers)
     const uint8_t* bits = u.bn.mode == 2 ? ws + u.relu_mask : nullptr;
     if (outer_bits) {
       rn50_bn_desc masked = u.bn;
       masked.mode = 1;
-      STEP_TRY(bn_relu_bwd(&masked, dz, dz2, ws + u.y, nullptr, outer_bits, MP(u.ig), MP(u.ib), F(u.mean), F(u.rstd), dy,
-                           nullptr, G(u.ig), G(u.ib), wsx, bn_ws_bytes, st));
+      bn_bwd_run(&masked, dz, dz2, ws + u.y, nullptr, outer_bits, MP(u.ig), MP(u.ib), F(u.mean), F(u.rstd), dy, nullptr,
+                 G(u.ig), G(u.ib), static_cast<float*>(wsx), true, st);
     } else if (sums_ready) {
       bn_bwd_from_partials(&u.bn, dz, ws + u.y, bits, MP(u.ig), MP(u.ib), F(u.mean), F(u.rstd),
                            static_cast<const float*>(wsx), dgrad_sums_rows, dy, u.bn.mode == 2 ? dres : nullptr,
-                           G(u.ig), G(u.ib), st);
+                           G(u.ig), G(u.ib), true, st);
     } else {
-      STEP_TRY(bn_relu_bwd(&u.bn, dz, dz2, ws + u.y, nullptr, bits, MP(u.ig), MP(u.ib), F(u.mean), F(u.rstd), dy, dres,
-                           G(u.ig), G(u.ib), wsx, bn_ws_bytes, st));
+      bn_bwd_run(&u.bn, dz, dz2, ws + u.y, nullptr, bits, MP(u.ig), MP(u.ib), F(u.mean), F(u.rstd), dy, dres, G(u.ig),
+                 G(u.ib), static_cast<float*>(wsx), true, st);
     }
     pending[npending++] = PendingWgrad{&u, in, dy, bn_in != nullptr, bn_in ? *bn_in : BnIn{}};
-    *dy_out = dy;
-    return RN50_OK;
+    return dy;
   };
   // Phase 2: the data gradient of dy into dx.  `below`: the unit whose BN output is this unit's input,
   // when dx (+ addend, the gradient of that output's other consumer) is its complete dz: the data gradient
@@ -618,11 +615,9 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
     dgrad_run(&u.conv, dy, W(u.iw), dx, below ? &fuse : nullptr, st);
   };
   auto unit_bwd = [&](Unit& u, const void* in, const void* dz, const void* dz2, void* dres, void* dx,
-                      bool sums_ready, Unit* below, const void* addend) -> int {
-    void* dy = nullptr;
-    STEP_TRY(unit_bn_bwd(u, in, dz, dz2, dres, sums_ready, s, bn_ws, &dy));
+                      bool sums_ready, Unit* below, const void* addend) {
+    void* const dy = unit_bn_bwd(u, in, dz, dz2, dres, sums_ready, s, bn_ws);
     if (dx) unit_dgrad(u, dy, dx, below, addend, s);
-    return RN50_OK;
   };
   // dzo (+ dzo2): the gradient w.r.t. the current block's output; top_sums: its BN sums are in bn_ws.
   // It alternates between two buffers: a block's conv1 data gradient reads the old one (as the shortcut's
@@ -643,9 +638,9 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
     void* dy3 = nullptr;
     if (plan->fuse_conv3_input) {
       const BnIn in{MP(u2.ig), MP(u2.ib), F(u2.mean), F(u2.rstd)};
-      STEP_TRY(unit_bn_bwd(u3, ws + u2.y, dzo, dzo2, nullptr, top_sums, s, bn_ws, &dy3, nullptr, &in));
+      dy3 = unit_bn_bwd(u3, ws + u2.y, dzo, dzo2, nullptr, top_sums, s, bn_ws, nullptr, &in);
     } else {
-      STEP_TRY(unit_bn_bwd(u3, ws + u2.z, dzo, dzo2, nullptr, top_sums, s, bn_ws, &dy3));
+      dy3 = unit_bn_bwd(u3, ws + u2.z, dzo, dzo2, nullptr, top_sums, s, bn_ws);
     }
     const void* shortcut_grad = dzo;
     const uint8_t* shortcut_mask = ws + u3.relu_mask;
@@ -653,17 +648,15 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
       Unit& up = plan->units[b.up];
       (void)hipEventRecord(plan->ev_bfork, s);
       (void)hipStreamWaitEvent(branch, plan->ev_bfork, 0);
-      void* dyp = nullptr;
-      STEP_TRY(unit_bn_bwd(up, block_in, dzo, dzo2, nullptr, false, branch, bn_ws2, &dyp, ws + u3.relu_mask));
+      void* const dyp = unit_bn_bwd(up, block_in, dzo, dzo2, nullptr, false, branch, bn_ws2, ws + u3.relu_mask);
       unit_dgrad(up, dyp, g[1], nullptr, nullptr, branch);
       (void)hipEventRecord(plan->ev_bjoin, branch);
       shortcut_grad = g[1];
       shortcut_mask = nullptr;
     }
     unit_dgrad(u3, dy3, g[4], &u2, nullptr, s);
-    STEP_TRY(unit_bwd(u2, ws + u1.z, g[4], nullptr, nullptr, g[4], true, &u1, nullptr));
-    void* dy1 = nullptr;
-    STEP_TRY(unit_bn_bwd(u1, block_in, g[4], nullptr, nullptr, true, s, bn_ws, &dy1));
+    unit_bwd(u2, ws + u1.z, g[4], nullptr, nullptr, g[4], true, &u1, nullptr);
+    void* const dy1 = unit_bn_bwd(u1, block_in, g[4], nullptr, nullptr, true, s, bn_ws);
     if (b.up >= 0) (void)hipStreamWaitEvent(s, plan->ev_bjoin, 0);
     unsigned char* const dz_new = dz_next;
     dz_next = const_cast<unsigned char*>(static_cast<const unsigned char*>(dzo));
@@ -677,7 +670,7 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
     block_end();
   }
   STEP_TRY(maxpool_bwd(cfg.N, u0.P, u0.Q, cfg.stem, dt, ws + u0.z, ws + plan->pool_argmax, dzo, dzo2, dz_next, s));
-  STEP_TRY(unit_bwd(u0, ws + plan->xp, dz_next, nullptr, nullptr, nullptr, false, nullptr, nullptr));
+  unit_bwd(u0, ws + plan->xp, dz_next, nullptr, nullptr, nullptr, false, nullptr, nullptr);
   block_end();
   // ------------------------------------------------------------------ LARS
   // (the groups before these two went with their blocks)  The side stream runs in order: the event of the last block but

@@ -89,22 +89,22 @@ size_t wgrad_partial_bytes(const rn50_conv_desc* d);
 void wgrad_run(const rn50_conv_desc* d, const void* x_or_xp, const void* dy, float* dw, void* scratch, hipStream_t s,
                const BnIn* in = nullptr);
 
-// bn.hip: the part of the forward / backward pass that follows the sums
+// bn.hip.  last_reader: the operands are not read again for a long while (bn_apply_kernel's LAST).
+// The part of the forward / backward pass that follows the sums.
 void bn_fwd_from_partials(const rn50_bn_desc* d, const void* x, const float* partial, int nrows, int rpp,
                           const float* gamma, const float* beta, const void* residual, void* y,
                           uint8_t* relu_mask, float* save_mean, float* save_rstd, float* rm, float* rv,
-                          float momentum, hipStream_t s);
+                          float momentum, bool last_reader, hipStream_t s);
 // relu_mask: recorded ReLU decisions (required in mode 2, where dres receives the masked gradient), or
 // null: recomputed from x (mode 1).
 void bn_bwd_from_partials(const rn50_bn_desc* d, const void* dz, const void* x, const uint8_t* relu_mask,
                           const float* gamma, const float* beta, const float* mean, const float* rstd,
                           const float* partial, int nrows, void* dx, void* dres, float* dgamma, float* dbeta,
-                          hipStream_t s);
-
-// evaluation mode (moving averages instead of batch statistics); rstd_scratch: float[C]
-void bn_infer_run(const rn50_bn_desc* d, const void* x, const float* gamma, const float* beta,
-                  const float* running_mean, const float* running_var, const void* residual, void* y,
-                  float* rstd_scratch, hipStream_t s);
+                          bool last_reader, hipStream_t s);
+// The whole backward pass (bn_relu_bwd without its checks); scratch: bn_relu_bwd_workspace_bytes(d).
+void bn_bwd_run(const rn50_bn_desc* d, const void* dz, const void* dz2, const void* x, const void* z,
+                const uint8_t* relu_mask, const float* gamma, const float* beta, const float* mean, const float* rstd,
+                void* dx, void* dres, float* dgamma, float* dbeta, float* scratch, bool last_reader, hipStream_t s);
 
 // head.hip: the pieces of xent_fwd_bwd and fc_bwd that a step runs on different streams.
 // The rows of the loss: row_loss, dlogits and (bf16, or null) the copy of dlogits rounded to the storage type.
