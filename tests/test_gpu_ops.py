@@ -227,9 +227,10 @@ def test_fc_ragged_sizes(rn):
     assert_close(da, da_o, 1e-6, "da"); assert_close(dW, dW_o, 1e-6, "dW"); assert_close(db, db_o, 1e-6, "db")
 
 
-@pytest.mark.parametrize("shape", [(40, 2048, 1000), (5, 80, 37), (64, 48, 64), (33, 144, 100), (1, 16, 8)])
+@pytest.mark.parametrize("shape", [(40, 2048, 1000), (5, 80, 37), (64, 48, 64), (33, 144, 100), (1, 16, 8),
+                                   (65, 2048, 1000), (256, 2048, 1000), (97, 16, 33)])
 def test_fc_fwd_bf16_matrix_core_path(rn, shape):
-    """bf16 operands, batch <= 64, channels a multiple of 16: the classifier's forward runs on the matrix cores
+    """bf16 operands, channels a multiple of 16, any batch: the classifier's forward runs on the matrix cores
     (float accumulation of exact bf16 products: float-level agreement with the oracle on the same rounded inputs)."""
     N, C, K = shape
     a = synth.round_bf16(synth.normal(SEED, "a", (N, C)))

@@ -336,6 +336,60 @@ def test_resnet_eval_vs_oracle_after_training_steps(rn, mode_name, cfg):
     assert np.array_equal(host(pred)[clear], o["pred"][clear])   # and the oracle's wherever its margin is clear
 
 
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("N", [2, 40, 200])
+def test_resnet_eval_is_the_chain_of_its_operations(rn, mode_name, N):
+    """The evaluation pass applies every batch norm (with the residual) in its convolution's output stage.  ResNet-50 at batches
+    whose layers run on every forward tile: the K splits, 64x64, 128x64, 128x128, the one-run 3x3 loop's 64x64 to 256x128.
+    In float the products are those of conv_fwd and the arithmetic that of bn_relu_infer: the same bits.  In bf16 the chain
+    multiplies the rounded operands in float and rounds once behind the batch norm, as the output stage does, so only the
+    order of the sums differs (and what a value on the other side of a rounding makes of it downstream)."""
+    bf = mode_name == "bf16"
+    dt = torch.bfloat16 if bf else torch.float32
+    plan = rn.ResnetPlan(N, rn.BF16 if bf else rn.F32)
+    gen = torch.Generator(device="cuda").manual_seed(SEED)
+    M = torch.empty(plan.arena_elems, device="cuda")
+    rn.resnet_init_params(plan, SEED, M)
+    M += 0.05 * M.abs().mean() * torch.randn(M.shape, device="cuda", generator=gen)      # (scales and shifts off 1 and 0)
+    Mod = M.to(dt) if bf else M
+    st = rn.TrainState(plan)
+    for rm, rv in zip(st.running_mean, st.running_var):
+        rm.copy_(0.1 * torch.randn(rm.shape, device="cuda", generator=gen))
+        rv.copy_(torch.exp(0.2 * torch.randn(rv.shape, device="cuda", generator=gen)))
+    img = torch.randn((N, 224, 224, 3), device="cuda", generator=gen).to(dt)
+    lab = torch.zeros(N, dtype=torch.int32, device="cuda")
+    logits = torch.empty((N, 1000), device="cuda")
+    rn.resnet_eval(plan, st, img, lab, M, Mod, torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda"), logits_out=logits)
+    unit = [0]
+
+    def cbn(x, stride, pad, mode, res=None):
+        u, unit[0] = unit[0], unit[0] + 1
+        y = rn.conv_fwd(x.float(), plan.view(Mod, 3 * u).float(), stride, pad)
+        return rn.bn_relu_infer(y, plan.view(M, 3 * u + 1), plan.view(M, 3 * u + 2), st.running_mean[u], st.running_var[u],
+                                None if res is None else res.float(), 1e-5, mode).to(dt)
+
+    x = rn.maxpool_fwd(cbn(img, 2, 3, 1))
+    for stage, blocks in enumerate((3, 4, 6, 3)):
+        for b in range(blocks):
+            stride = 2 if b == 0 and stage > 0 else 1
+            z = cbn(cbn(x, 1, 0, 1), stride, 1, 1)
+            if b == 0:                                       # (parameter order: conv3, then the projection)
+                unit[0] += 1
+                short = cbn(x, stride, 0, 0)
+                unit[0] -= 2
+                x = cbn(z, 1, 0, 2, short)
+                unit[0] += 1
+            else:
+                x = cbn(z, 1, 0, 2, x)
+    fc = plan.num_tensors - 2
+    want = rn.fc_fwd(rn.avgpool_fwd(x), plan.view(Mod, fc), plan.view(M, fc + 1))
+    assert float(want.std()) > 0.01
+    if bf:
+        assert_close(logits, host(want), TOL["bf16"], "evaluation logits", elementwise=False)
+    else:
+        assert torch.equal(logits, want)
+
+
 def test_init_train_eval_round_trip_resnet50_batch40(rn):
     """The pieces together at the measured configuration: parameters from the seed on the device, twenty
     loop steps on one fixed synthetic batch, then the evaluation pass on that batch with the moving
