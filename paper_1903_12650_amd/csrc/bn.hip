@@ -61,7 +61,7 @@ static BnGeom bn_geom(int64_t m, int C, int dtype) {
 }
 
 // Geometry of the stand-alone sums passes (statistics, backward sums).  Small layers are summed in at most 128 row blocks of
-// at least 32 rows, row-major, and their apply pass finalizes by itself (bn_apply_kernel's FIN): a finalize launch costs
+// at least 32 rows, as doubles, and their apply pass finalizes by itself (bn_apply_kernel's FIN): a finalize launch costs
 // about 4 us whatever it computes, reading 128 rows of sums in every apply workgroup 1 to 2 -- as long as the workgroups
 // are few: beyond kBnSelfElems the sums they read together are as many bytes as the tensor.
 // Larger layers: up to kBnSumsGroups workgroups whose threads load their eight rows (kBnSumsRows) once.  Workgroups that
@@ -152,8 +152,9 @@ __device__ __forceinline__ bool combine_sums(float* acc, float* lds, int tx_log2
 }
 
 // ------------------------------------------------------------------- forward
-// Sums of a row block, about a shift of its own channel's first element, stored in either form (wide: doubles).  Bound by the bytes in flight: eight rows per thread are requested before the first is used (with four, and the
-// LDS tree at the end, 64 MB took 29 us).
+// Sums of a row block, about a shift of its own channel's first element, stored in either form (wide: doubles).  Bound by the
+// bytes in flight: eight rows per thread are requested before the first is used (with four, and the LDS tree at the end, 64 MB
+// took 29 us).
 template <typename T>
 __global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ x, int64_t m, int C,
                                                        int tx_log2, int rpb, int wide,
@@ -743,11 +744,6 @@ static void launch_fwd_tail(const rn50_bn_desc* d, int64_t m, const void* x,
     RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, true, LAST>), dim3(static_cast<unsigned>(ceil_div(m, rpb)), gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, nullptr, nullptr, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, 3, rpb, d->mode, fin);
     return;
   }
-#ifdef RN50_TUNING  // what-if measurement: the step without its finalize launches (results are then wrong)
-  static const bool skip_fin = getenv("RN50_SKIP_BN_FINALIZE") != nullptr;
-  static const int skip_below = getenv("RN50_SKIP_BN_FINALIZE_ROWS") ? atoi(getenv("RN50_SKIP_BN_FINALIZE_ROWS")) : 1 << 30;
-  if (!skip_fin || nrows > skip_below)
-#endif
   RN50_LAUNCH("bn_finalize", bn_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, partial, nrows, rpp, self ? 1 : 0, m, d->C, d->eps, save_mean, save_rstd, rm, rv, momentum);
   if (!y) return;  // statistics only: the consumer applies the layer while it loads its operand
   const BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnApplyGroups);
@@ -781,11 +777,6 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
     ga.nblk = static_cast<int>(ceil_div(m, ga.rpb));
     fin = BnFinArgs{partial, nrows, 0.f, 0.f, dbeta, dgamma, nullptr, nullptr};
   } else {
-#ifdef RN50_TUNING
-    static const bool skip_fin = getenv("RN50_SKIP_BN_FINALIZE") != nullptr;
-    static const int skip_below = getenv("RN50_SKIP_BN_FINALIZE_ROWS") ? atoi(getenv("RN50_SKIP_BN_FINALIZE_ROWS")) : 1 << 30;
-    if (!skip_fin || nrows > skip_below)
-#endif
     RN50_LAUNCH("bn_bwd_finalize", bn_bwd_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, partial, nrows, d->C, dgamma, dbeta);
   }
 #define RN50_BWD_APPLY_K(DZ2, ZK, FIN)                                                                             \

@@ -1,4 +1,4 @@
-// Convolution forward, data gradient and weight gradient as implicit GEMMs on
+// Convolution forward and data gradient as implicit GEMMs on
 // the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16 for bf16 storage,
 // v_mfma_f32_32x32x2_f32 for float storage; float accumulation in both).
 //
@@ -16,16 +16,11 @@
 // so that every lane ends up with 4 consecutive output channels of one pixel,
 // which the epilogue packs, stages through LDS and stores as full rows.
 //
-// The weight gradient, wgrad_kernel, is the GEMM whose reduction runs over the
-// pixels: dw[ko][tap][c] = sum_m dy[m][ko] * A[m][tap*Cg + c].  Both operands
-// have the reduction index as their slow (row) index in memory, so tiles are
-// copied to LDS untransposed and the bf16 fragments are fetched with the
-// gfx950 transposing LDS read (ds_read_b64_tr_b16); the reduction is split over
-// workgroups and finished by a fixed-order sum (bitwise reproducible).
+// (The weight gradient is in wgrad.hip, the bf16 stem's forward pass in stem.hip.)
 //
 // The output stage of igemm_kernel can also take the per-channel sums of the
-// batch norm that consumes the output (forward: shifted sum and sum of squares
-// per tile; data gradient: sum(g), sum(g*xhat) of the BN layer below, with an
+// batch norm that consumes the output (forward: sum and sum of squares about a
+// shift of the tile's own, or about zero in double; data gradient: sum(g), sum(g*xhat) of the BN layer below, with an
 // optional second gradient branch added before the one rounding), so that no
 // separate pass re-reads the tensor.  Stride-2 data gradients process the output
 // pixels in four parity classes, each looping over its own taps only.
@@ -155,7 +150,7 @@ constexpr int igemm_ks_ring() {
 // bytes per clock than a plain one, but the tile is the smaller half of the fragment traffic and was never what bounds
 // these layers: per layer at batch 40 7.5 to 33 us against 8.9 to 34 with a transposed copy (whole network 794 against
 // 854 us, 3884 against 3926 at batch 256), and the copy itself -- 4 to 5 us per conv_dgrad call, 57 us per step on the
-// side stream -- is gone (the 22 shapes at batch 40, call by call: 578 -> 475 us).
+// side stream -- is gone (the 22 shapes at batch 40, call by call: 562 -> 465 us).
 //
 // HALO: compiled for a 3x3 filter with stride 1 and padding 1 (output pixel m reads input pixels m + dy*W + dx,
 // dy, dx in -1..1, of the same flat pixel index space).  The nine taps of a tile then read one contiguous run of
@@ -1137,12 +1132,12 @@ static IgemmArgs stem_igemm_args(const rn50_conv_desc* d, const void* xp, const 
   return a;
 }
 
-// Forward of the stem from an already padded input; wp is scratch for the padded weights.
 static void set_affine(IgemmArgs& a, const BnAffine& f) {
   a.mode = 2;
   a.bn_gamma = f.gamma; a.bn_beta = f.beta; a.bn_mean = f.mean; a.aff_var = f.var;
   a.aff_eps = f.eps; a.aff_relu = f.relu; a.addend = f.residual;
 }
+// Forward of the stem from an already padded input; wp is scratch for the padded weights.
 void stem_fwd_padded(const rn50_conv_desc* d, const void* xp, const void* w, void* wp, void* y, float* bn_partial,
                      hipStream_t s, const BnAffine* affine) {
   if (stem_fwd_run(d, xp, w, y, bn_partial, s, affine)) return;

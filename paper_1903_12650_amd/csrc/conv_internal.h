@@ -148,8 +148,6 @@ __device__ __forceinline__ Vec16 wgrad_read_frag(const unsigned char* tile, int 
   return v;
 }
 
-
-
 template <typename K>
 inline void allow_big_lds(K kernel, int bytes) {
   if (bytes > 48 * 1024) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
@@ -160,7 +158,6 @@ inline bool is_stem(const rn50_conv_desc* d) {
   return d->Cin == 3 && d->R == 7 && d->S == 7 && d->stride == 2 && d->pad == 3;
 }
 inline int esize(int dtype) { return dtype == RN50_BF16 ? 2 : 4; }
-
 
 constexpr int kStemK = 256;  // padded reduction length of the stem: 8 filter rows x 8 taps x 4 channels
 // Geometry of the padded stem: 7 "taps" (filter rows) of 32 elements on pixels of 4 channels.
@@ -176,7 +173,6 @@ inline StemGeom stem_geom(const rn50_conv_desc* d) {
   g.wp_bytes = align_up(static_cast<size_t>(d->Cout) * kStemK * esize(d->dtype), 256);
   return g;
 }
-
 
 // stem.hip: the bf16 stem from the padded image (false: a shape it does not take; the general kernel's turn), and the rows
 // of batch-norm sums it leaves (num = 0: likewise).

@@ -644,6 +644,7 @@ void rn50::fc_bwd_da(int N, int Cin, int K, int dtype, const void* W, const void
 
 extern "C" size_t fc_bwd_workspace_bytes(int N, int Cin, int K, int dtype) {
   if (N <= 0 || Cin <= 0 || K <= 0 || !fc_mfma_ok(Cin, K, dtype)) return 0;
+  // dlogits in the storage type; the second part (the size of the weights) is as the interface has it, nothing is written there
   const size_t es = dtype == RN50_BF16 ? 2 : 4;
   return align_up(static_cast<size_t>(N) * K * es, 256) + align_up(static_cast<size_t>(K) * Cin * es, 256);
 }

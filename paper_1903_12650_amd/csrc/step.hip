@@ -66,8 +66,9 @@ struct rn50_plan {
   size_t wgrad_scratch = 0, bn_scratch = 0, pool_argmax = 0, fc_scratch = 0;
   size_t fc_scratch_bytes = 0;
   std::vector<rn50::LarsGroup> lars_groups;  // in the order in which the backward pass completes them
-  // Second stream for the work that is off the step's critical path (the weight gradients), with the events that order it against the caller's stream.  Created at the first
-  // step (default priority), destroyed with the plan.
+  // Second stream for the work that is off the step's critical path (the weight gradients, the update of the blocks that are
+  // done), with the events that order it against the caller's stream.  Created at the first step (default priority),
+  // destroyed with the plan.
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr;
   // Third stream: the projection shortcut of a stage's first block, forward and backward, runs beside the
@@ -254,7 +255,8 @@ extern "C" int resnet_plan_create(const rn50_step_config* cfg, rn50_plan** plan_
   p->row_loss = bump(&top, static_cast<size_t>(N) * sizeof(float));
   for (int i = 0; i < 5; ++i) p->g[i] = bump(&top, max_act * es);
   p->pool_argmax = bump(&top, static_cast<size_t>(N) * Hpool * Hpool * cfg->stem);
-  p->fc_scratch_bytes = fc_bwd_workspace_bytes(N, cin, cfg->classes, cfg->dtype);
+  // (dlogits in the storage type; without the matrix-core path fc_bwd needs nothing)
+  p->fc_scratch_bytes = fc_mfma_ok(cin, cfg->classes, cfg->dtype) ? static_cast<size_t>(N) * cfg->classes * es : 0;
   p->fc_scratch = bump(&top, p->fc_scratch_bytes);
   p->wgrad_scratch = bump(&top, max_wg);
   p->bn_scratch = bump(&top, max_bn);
@@ -299,10 +301,13 @@ void destroy_streams(rn50_plan* p) {
   p->side = p->branch = nullptr;
   p->streams_ready = false;
 }
-// These events only order kernels on this GPU's streams (every kernel's own end already makes its stores visible across
-// the device), so a record carries no system-scope fence: with one, each of the step's ~25 records held its stream up
-// while the caches were written back for the host.  Whole step, batch 40: 4.756 -> 4.688 ms; batch 4: 2.289 -> 2.214 ms.
-// Host visibility comes from the caller's own synchronization of its stream, which joins both side streams.
+// These events only order kernels on this GPU's streams, so a record carries no system-scope fence.  By HIP's documentation of
+// the flag (hipEventCreateWithFlags) device memory may then not be visible to the host and to other devices, and
+// hipEventSynchronize, hipEventQuery and hipEventElapsedTime do not synchronize with the work in front of the event; none of
+// these is done with them.  Visibility on this device, all that the waiting kernels need, is not what the flag takes away.  The
+// host and other devices see the results through the caller's own synchronization of its stream, which joins both side streams.  With the
+// fence each of the step's ~25 records held its stream up while the caches were written back for the host: batch 40 4.756 ->
+// 4.688 ms, batch 4 2.289 -> 2.214 ms.
 constexpr unsigned kEventFlags = hipEventDisableTiming | hipEventDisableSystemFence;
 int ensure_side_stream(rn50_plan* p) {
   if (p->streams_ready) return RN50_OK;
@@ -562,10 +567,6 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
   auto block_end = [&]() {
     (void)hipEventRecord(plan->ev_dy[blk], s);
     (void)hipStreamWaitEvent(side, plan->ev_dy[blk], 0);
-#ifdef RN50_TUNING  // what-if measurement: the step without its weight gradients
-    static const bool skip_wgrad = getenv("RN50_SKIP_WGRAD") != nullptr;
-    if (skip_wgrad) npending = 0;
-#endif
     for (int i = 0; i < npending; ++i)
       wgrad_run(&pending[i].u->conv, pending[i].in, pending[i].dy, G(pending[i].u->iw), ws + plan->wgrad_scratch, side,
                 pending[i].bn_in ? &pending[i].bn : nullptr);

@@ -34,16 +34,15 @@ struct BnAffine {
   int relu;
   const void* residual;
 };
+// bn_partial (null: none): the sums of the batch norm behind the convolution (bn_sums_at).
 void stem_fwd_padded(const rn50_conv_desc* d, const void* xp, const void* w, void* wp, void* y, float* bn_partial,
                      hipStream_t s, const BnAffine* affine = nullptr);
-// A BN+ReLU layer applied to a convolution's input on the fly (1x1, stride 1 convolutions only): its parameters
-// and saved statistics, float[Cin] each.
 // The BN sums that a convolution's output stage (or a stand-alone sums pass) leaves, one row per row tile.  Backward: the floats
 // (sum g, sum g * xhat) per row and channel.  Forward, two forms: for a reader that adds rows up in every workgroup
 // (bn_self_finalizes), the doubles (sum y, sum y^2), moved from the tile's shift to shift 0 by the writer so that the readers
 // only add; else, for the finalize launch, the floats of a BnTileRow (shift, sums about it), which that launch moves to the
 // first tile's shift in double: exact either way, and at 12544 rows the fewer bytes count.
-// Eight channels by all rows are contiguous: the writer stores whole 64-byte pieces (with the rows of a single channel
+// Eight channels by all rows are contiguous: the writer stores runs of 64 to 128 bytes (with the rows of a single channel
 // contiguous its 2 to 3 * 64 sums were a partial cache line each), and a finalize workgroup reads one run of memory
 // (row-major, it picked 64 bytes out of every row: 12544 rows, batch 256, 45 us).
 __host__ __device__ inline int64_t bn_sums_at(int row, int c, int nrows) {
@@ -64,13 +63,15 @@ inline bool bn_self_finalizes(int nrows, bool backward) {
   return nrows <= (backward ? kBnSelfFinalizeRowsBwd : kBnSelfFinalizeRows);
 }
 
+// A BN+ReLU layer applied to a convolution's input on the fly (1x1, stride 1 convolutions only): its parameters
+// and saved statistics, float[Cin] each.
 struct BnIn {
   const float *gamma, *beta, *mean, *rstd;
 };
 void fwd_run(const rn50_conv_desc* d, const void* x, const void* w, void* y, float* bn_partial, hipStream_t s,
              const char* tag = "conv_fwd", const BnIn* in = nullptr, const BnAffine* affine = nullptr);
 // The BN layer (with ReLU) whose output gradient a data gradient produces: x is that
-// layer's input [N*H*W][Cin]; partial receives float[2][Cin][num] = sum(g), sum(g * xhat) per tile.
+// layer's input [N*H*W][Cin]; partial receives the pairs sum(g), sum(g * xhat) per tile and channel (bn_sums_at).
 // addend (or null): a second branch of the gradient, [N*H*W][Cin], added to the data gradient before it
 // is stored; relu_mask (or null): the BN layer's recorded ReLU decisions (else recomputed from x);
 // addend_mask (or null): ReLU bits under which the addend counts (the addend is then the still unmasked

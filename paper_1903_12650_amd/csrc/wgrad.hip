@@ -241,7 +241,7 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
     }
 }
 
-// Weight gradient of a 3x3 / stride 1 / padding 1 layer, bf16, all nine taps in one workgroup.
+// Weight gradient of a 3x3 / stride 1 / padding 1 layer of at most 64 channels each way, bf16, all nine taps in one workgroup.
 // The reduction index is a PADDED pixel position: every image row gets one more column and every image one more
 // row, whose dy and x are zero (never stored: the loads of those positions carry an out-of-range offset and
 // write zeros).  In that index space tap (r, s) of position k reads x at k + (r-1)(W+1) + (s-1), a constant shift,
@@ -261,18 +261,14 @@ __global__ __launch_bounds__(256) void wgrad3x3_kernel(const WgradArgs a) {
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave & 1, wn = wave >> 1;
-  // logical id = (split, output-channel tile, input-channel tile): the tiles of a split share its rows
-  const int lid = xcd_remap(blockIdx.x, gridDim.x);
-  const int split = static_cast<int>(fdiv(static_cast<uint32_t>(lid), a.div_tps)), tile = lid - split * a.tiles_per_split;
-  const int ko_tile = static_cast<int>(fdiv(static_cast<uint32_t>(tile), a.div_ctiles));
-  const int c0 = (tile - ko_tile * a.ctiles) * 64, ko0 = ko_tile * 64;
+  const int split = xcd_remap(blockIdx.x, gridDim.x);  // neighbours share the run's border rows
   const int row_begin = split * a.rows_per_split;
   const int row_end = min(row_begin + a.rows_per_split, a.Gpad);
   const rsrc_words rsX = make_rsrc_words(a.x, a.x_bytes), rsD = make_rsrc_words(a.dy, a.dy_bytes);
 
   const int row = tid >> 3;                                  // this thread's row in every 32-row load pass
   const int pc = (tid & 7) ^ wgrad_swz<T, RBY>(row);        // the 16-byte piece of its rows it fetches
-  const bool a_col_ok = ko0 + pc * V < a.Cout, b_col_ok = c0 + pc * V < a.Cg;
+  const bool a_col_ok = pc * V < a.Cout, b_col_ok = pc * V < a.Cg;
   const int W1 = a.W + 1, IMG = (a.H + 1) * W1;
   // padded position -> pixel index; ok: the position is a real pixel
   auto pixel_of = [&](int g, bool* ok) __attribute__((always_inline)) {
@@ -296,7 +292,7 @@ __global__ __launch_bounds__(256) void wgrad3x3_kernel(const WgradArgs a) {
       bool ok;
       const int pix = pixel_of(g, &ok);
       ok = ok && a_col_ok && g < row_end;
-      buffer_load16_to_lds(rsD, sa + i * 4096, ok ? static_cast<uint32_t>(pix * a.Cout + ko0 + pc * V) * 2u : kOob, 0u);
+      buffer_load16_to_lds(rsD, sa + i * 4096, ok ? static_cast<uint32_t>(pix * a.Cout + pc * V) * 2u : kOob, 0u);
     }
 #pragma unroll
     for (int i = 0; i < NBX; ++i) {  // x: the run starts W + 2 positions before the chunk
@@ -304,7 +300,7 @@ __global__ __launch_bounds__(256) void wgrad3x3_kernel(const WgradArgs a) {
       bool ok;
       const int pix = pixel_of(g, &ok);
       ok = ok && b_col_ok;
-      buffer_load16_to_lds(rsX, sb + i * 4096, ok ? static_cast<uint32_t>(pix * a.PS + c0 + pc * V) * 2u : kOob, 0u);
+      buffer_load16_to_lds(rsX, sb + i * 4096, ok ? static_cast<uint32_t>(pix * a.PS + pc * V) * 2u : kOob, 0u);
     }
     ++cur;
   };
@@ -364,13 +360,13 @@ __global__ __launch_bounds__(256) void wgrad3x3_kernel(const WgradArgs a) {
 
   // acc[tap][v]: ko = (v/4)*8 + (lane/32)*4 + v%4, c = lane%32 of this wave's 32x32 block
   float* out = a.out + static_cast<int64_t>(split) * a.split_stride;
-  const int c = c0 + wn * 32 + (lane & 31);
+  const int c = wn * 32 + (lane & 31);
   if (c < a.Cg) {
 #pragma unroll
     for (int tap = 0; tap < 9; ++tap)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int ko = ko0 + wm * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
+        const int ko = wm * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
         if (ko < a.Cout) out[static_cast<int64_t>(ko) * a.Ktot + tap * a.Cg + c] = acc[tap][v];
       }
   }
@@ -427,7 +423,8 @@ struct WgradPlan {
 // pixels are gathered; `ends` is prologue and result stores; splits add the reduction launch and the partials' traffic.
 // Constants fitted to ResNet-50's 23 shapes x 12 plans at batch 12 to 256 (bf16) and 2 to 24 (float): the plan it
 // takes is within 2 % of the best of the twelve on average.  Against the fixed rule before it (128-wide tiles, 192 or 384
-// workgroups): 23 shapes at batch 40 638 -> 490 us, at batch 256 2387 -> 1830, float at batch 8 833 -> 536.
+// workgroups): 23 shapes at batch 40 640 -> 565 us call by call, at batch 256 2343 -> 2000, float at batch 8
+// 830 -> 531.
 struct WgradCost {
   float thr[3], lat[3], ends[3];  // us; tile area 64x64, 128x64, 128x128
   float thr_gather, lat_gather, reduce, partial_us_per_mb;
@@ -513,12 +510,12 @@ static WgradArgs wgrad_args(const rn50_conv_desc* d, const void* x, const void* 
   a.split_stride = static_cast<int64_t>(a.Cout) * a.Ktot;
   return a;
 }
-// The nine-tap weight gradient (wgrad3x3_kernel): bf16, 3x3, stride 1, padding 1, and an image width whose run
-// of 2W + 68 rows fits six load passes.  Plan: 64x64 tiles, the padded pixel range split to give about 192
-// workgroups (384 for the longest reductions), each at least 8 chunks long (as for wgrad_kernel).
+// The nine-tap weight gradient (wgrad3x3_kernel): bf16, 3x3, stride 1, padding 1, at most 64 channels each way (one 64x64 tile;
+// wider layers do better on wgrad_kernel's 128-wide tiles), and an image width whose run of 2W + 68 rows fits six load passes.
+// Plan: the padded pixel range split to give about 384 workgroups, each at least 8 chunks long.
 struct Wgrad3x3Plan {
   int nbx;  // load passes of the x run: 3, 4 or 6; 0: the layer does not run this kernel
-  int ctiles, kotiles, splits, rows_per_split, gpad;
+  int splits, rows_per_split, gpad;
 };
 static Wgrad3x3Plan plan_wgrad3x3(const rn50_conv_desc* d) {
   Wgrad3x3Plan p{};
@@ -529,14 +526,10 @@ static Wgrad3x3Plan plan_wgrad3x3(const rn50_conv_desc* d) {
   const int64_t gpad = static_cast<int64_t>(d->N) * (d->H + 1) * (d->W + 1);
   if (gpad >= (1ll << 31) - 64) return p;
   p.nbx = need <= 3 ? 3 : (need == 4 ? 4 : 6);
-  p.ctiles = static_cast<int>(ceil_div(d->Cin, 64));
-  p.kotiles = static_cast<int>(ceil_div(d->Cout, 64));
   p.gpad = static_cast<int>(gpad);
   constexpr int target = 384, min_chunks = 8;
-  const int64_t tiles = static_cast<int64_t>(p.ctiles) * p.kotiles;
   const int64_t cap = gpad / (min_chunks * 64) > 1 ? gpad / (min_chunks * 64) : 1;
-  int64_t sp = (target + tiles / 2) / tiles;
-  sp = sp < 1 ? 1 : (sp > cap ? cap : sp);
+  const int64_t sp = std::min<int64_t>(target, cap);
   const int64_t rps = ceil_div(ceil_div(gpad, sp), 64) * 64;
   p.rows_per_split = static_cast<int>(rps);
   p.splits = static_cast<int>(ceil_div(gpad, rps));
@@ -559,15 +552,11 @@ static void launch_wgrad3x3_nbx(const WgradArgs& a, dim3 grid, hipStream_t s) {
   else launch_wgrad3x3_ring<NBX, 2>(a, grid, s);
 }
 static void launch_wgrad3x3(WgradArgs a, const Wgrad3x3Plan& p, int H, hipStream_t s) {
-  a.ctiles = p.ctiles;
-  a.tiles_per_split = p.ctiles * p.kotiles;
   a.rows_per_split = p.rows_per_split;
   a.Gpad = p.gpad;
-  a.div_tps = make_fastdiv(a.tiles_per_split);
-  a.div_ctiles = make_fastdiv(a.ctiles);
   a.div_img = make_fastdiv((H + 1) * (a.W + 1));
   a.div_w1 = make_fastdiv(a.W + 1);
-  const dim3 grid(static_cast<unsigned>(a.tiles_per_split) * p.splits);
+  const dim3 grid(static_cast<unsigned>(p.splits));
   if (p.nbx == 3) launch_wgrad3x3_nbx<3>(a, grid, s);
   else if (p.nbx == 4) launch_wgrad3x3_nbx<4>(a, grid, s);
   else launch_wgrad3x3_nbx<6>(a, grid, s);
