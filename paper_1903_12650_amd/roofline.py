@@ -127,17 +127,30 @@ def per_launch_cost(tag, plan):
             seq = [l for l in seq if l["mode"] == 0 or l["Cin"] == 3 or l is last_add]
         bits = (2, 0) if tag == "bn_bwd_apply" else (2,)   # layers that read recorded ReLU bits / a residual
         return [(0.0, elems(l) * (base + (extra if l["mode"] in bits else 0))) for l in seq]
-    # two launches each: every tensor but the stem's weight, then the stem's weight (whose gradient comes last)
-    n_params, n_stem = sum(plan.sizes), plan.sizes[0]
-    if tag == "lars_norms":
-        return [(0.0, 8.0 * (n_params - n_stem)), (0.0, 8.0 * n_stem)]
-    if tag == "lars_apply":
-        per = 20.0 + (2.0 if plan.dtype == 1 else 0.0)
-        return [(0.0, per * (n_params - n_stem)), (0.0, per * n_stem)]
-    if tag == "lars_update":  # the whole update against the single-pass figure: w, g, v read, w, v written (+ bf16 copy)
-        per = 20.0 + (2.0 if plan.dtype == 1 else 0.0)
-        return [(0.0, per * (n_params - n_stem)), (0.0, per * n_stem)]
+    # one launch of each kernel per group of tensors; lars_update: the whole update against the single-pass figure (w, g, v
+    # read, w, v written, + bf16 copy)
+    per = {"lars_norms": 8.0, "lars_apply": 20.0 + (2.0 if plan.dtype == 1 else 0.0)}
+    per["lars_update"] = per["lars_apply"]
+    if tag in per:
+        return [(0.0, per[tag] * n) for n in _lars_groups(plan)]
     raise KeyError(tag)
+
+
+def _lars_groups(plan):
+    """Parameters of the groups in which the step updates the tensors, in launch order: the classifier and the blocks from the
+    last to the first, a group closed at the first block that brings it to 4 Mi; then the rest with the stem's BN; then
+    the stem's weight (csrc/step.hip, plan_lars_groups)."""
+    at, blocks = 3, []
+    for b in _blocks(layers(plan))[1:]:
+        blocks.append(sum(plan.sizes[at:at + 3 * len(b)]))
+        at += 3 * len(b)
+    groups, n = [], sum(plan.sizes[at:])
+    for bi in range(len(blocks) - 1, -1, -1):
+        n += blocks[bi]
+        if bi > 0 and n >= 4 << 20:
+            groups.append(n)
+            n = 0
+    return groups + [n + sum(plan.sizes[1:3]), plan.sizes[0]]
 
 
 def _blocks(L):

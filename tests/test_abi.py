@@ -148,3 +148,4 @@ def test_roofline_cost_model_totals():
     assert abs(E / 1e6 - 444.6) < 0.5
     assert sum(b for _, b in apply) == 4 * E + 2 * E_add and sum(b for _, b in bwd) == 6 * E + (E_add + E_proj) / 8
     assert sum(b for _, b in rl.per_launch_cost("lars_apply", plan)) == 22 * 25_557_032
+    assert len(rl.per_launch_cost("lars_norms", plan)) == 6   # groups of tensors, in the order in which they are complete
