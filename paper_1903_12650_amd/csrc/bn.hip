@@ -63,7 +63,9 @@ static BnGeom bn_geom(int64_t m, int C, int dtype) {
 // Geometry of the stand-alone sums passes (statistics, backward sums).  Small layers are summed in at most 128 row blocks of
 // at least 32 rows, as doubles, and their apply pass finalizes by itself (bn_apply_kernel's FIN): a finalize launch costs
 // about 4 us whatever it computes, reading 128 rows of sums in every apply workgroup 1 to 2 -- as long as the workgroups
-// are few: beyond kBnSelfElems the sums they read together are as many bytes as the tensor.
+// are few: beyond kBnSelfElems the sums they read together are as many bytes as the tensor.  Nine layers, both directions, batch
+// 8 / 40: 272 / 485 us; never 311 / 501; up to 8192 rows 278 / 488; up to 16 M elements 280 / 495
+// (profiles/bn_standalone_sums_forms.txt).
 // Larger layers: up to kBnSumsGroups workgroups whose threads load their eight rows (kBnSumsRows) once.  Workgroups that
 // loop over more rows all load at the same time and all compute at the same time.
 constexpr int64_t kBnSelfRows = 32768, kBnSelfElems = 4 << 20;
@@ -84,7 +86,7 @@ static BnGeom bn_sums_geom(int64_t m, int C, int dtype) {
 }
 
 // The elementwise passes have no sums to combine, so their geometry is free: at most `target` workgroups,
-// each thread streaming 4 to 32 rows.  Measured inside the training step (profiles/bn_apply_grid_step_time_batch40.txt)
+// each thread streaming 4 to 32 rows.  Measured inside the training step (profiles/step_time_against_dispatch_constants.txt)
 // and on a plain copy kernel: many small workgroups that make one round of loads each stream faster than few
 // long-running ones (a 16-byte-per-thread copy of 1 GiB runs at 6.2 TB/s, the same copy by 2,048 looping workgroups
 // at 4.9), so the target is high enough that every thread of ResNet-50's layers takes its minimum of 4 rows.

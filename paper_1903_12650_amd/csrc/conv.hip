@@ -951,26 +951,16 @@ struct TileShape {
   int bm, bn, wm, wn;
 };
 #define RN50_IGEMM_SHAPES(X) X(64, 64, 2, 2) X(128, 64, 2, 2) X(128, 128, 2, 2) X(256, 128, 4, 2) X(64, 64, 1, 1)
-static bool igemm_shape_compiled(const TileShape& t) {
-#define X(BM, BN, WM, WN) if (t.bm == BM && t.bn == BN && t.wm == WM && t.wn == WN) return true;
-  RN50_IGEMM_SHAPES(X)
-#undef X
-  return false;
-}
+#define RN50_IGEMM_SHAPE_BF16(X) X(32, 64, 1, 1)
+#define RN50_IGEMM_SHAPE_F32(X) X(32, 32, 1, 1)
 // The tile of a layer shape: M rows (output pixels; of one parity class for a stride-2 data gradient, `live` of
 // whose four classes have any taps), Ncols output channels, `chunks` 128-byte steps of the reduction.  The rule
 // is fitted to per-layer sweeps of all compiled shapes over ResNet-50's 23 convolution shapes at batch 40 and at
-// batch 256 (profiles/conv_tile_sweep_*.txt): the largest tile that still leaves about two workgroups per
-// compute unit wins -- larger tiles load fewer operand bytes per flop (the main loop's bound) but a grid that
-// does not give every compute unit at least one and a half workgroups leaves the latencies of a workgroup's load -> LDS -> MFMA chain exposed; a
-// reduction of one or two chunks has nothing to reuse and takes the smallest tile.
+// batch 256 (profiles/conv_tile_sweep_*.txt): the largest tile that still leaves about one and a half
+// workgroups per compute unit wins -- larger tiles load fewer operand bytes per flop (the main loop's bound) but with a smaller
+// grid the latencies of a workgroup's load -> LDS -> MFMA chain are exposed; a reduction of one chunk has nothing to reuse and
+// takes the smallest tile.
 static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool dgrad, bool strided_dgrad, int live = 4) {
-#ifdef RN50_TUNING  // tuning builds only: RN50_IGEMM_TILE=bm,bn,wm,wn forces a compiled tile shape
-  if (const char* e = getenv("RN50_IGEMM_TILE")) {
-    TileShape f{0, 0, 0, 0};
-    if (sscanf(e, "%d,%d,%d,%d", &f.bm, &f.bn, &f.wm, &f.wn) == 4 && igemm_shape_compiled(f)) return f;
-  }
-#endif
   const int64_t classes = strided_dgrad ? live : 1;
   auto groups = [&](int bm, int bn) { return ceil_div(M, bm) * ceil_div(Ncols, bn) * classes; };
   constexpr int64_t kCover = 384;  // workgroups: one and a half per compute unit (two four-wave workgroups fit each)
@@ -998,8 +988,8 @@ static TileShape igemm_halo_tile(int64_t M, int Ncols) {
 // layers of the halo main loop.  The launch and the callers that size the batch-norm sums (one row per row tile)
 // both go through halo_filter / igemm_halo_tile, so they agree on the tile.
 static bool halo_filter(int R, int S, int stride, int pad) {
-#ifdef RN50_TUNING  // tuning builds only: a forced tile shape, or RN50_NO_HALO, send these layers down the general path
-  static const bool off = getenv("RN50_IGEMM_TILE") != nullptr || getenv("RN50_NO_HALO") != nullptr;
+#ifdef RN50_TUNING  // tuning builds only: RN50_NO_HALO sends these layers down the general path
+  static const bool off = getenv("RN50_NO_HALO") != nullptr;
   if (off) return false;
 #endif
   return R == 3 && S == 3 && stride == 1 && pad == 1;
@@ -1015,9 +1005,22 @@ static bool igemm_halo_shape(const IgemmArgs& a) {
 // both directions), so that twice (four times) as many compute units work.  Measured on the whole float gradient pass (batch 4:
 // 4055 -> 2919 us, batch 8: 4752 -> 4024, batch 16: 6789 -> 6384) and on single layers (2048 -> 512 channels at 7x7,
 // batch 40: 14.0 -> 9.3 us; 3x3 512 -> 512 at 7x7, batch 12: 28.7 -> 14.4); with 257 to 512 tiles the two workgroups per
-// compute unit of the shared ring do better.
+// compute unit of the shared ring do better.  Limits of 0 / 128 / 256 / 384 / 512 tiles in the whole step: float at batch 8 4.75 /
+// 4.13 / 4.06 / 4.06 / 4.49 ms, bf16 at batch 40 4.373 / 4.371 / 4.356 / 4.352 / 4.630 (profiles/step_time_against_dispatch_constants.txt;
+// layer by layer: profiles/conv_tile_sweep_*.txt).
 static TileShape pick_tile(int64_t rows, int Ncols, int chunks, bool dgrad, bool strided_dgrad, int live, bool halo,
                            int lin_fwd_channels, int dtype) {
+#ifdef RN50_TUNING  // tuning builds only: RN50_IGEMM_TILE=bm,bn,wm,wn forces a compiled tile shape
+  if (const char* e = getenv("RN50_IGEMM_TILE")) {
+    TileShape f{0, 0, 0, 0};
+    if (sscanf(e, "%d,%d,%d,%d", &f.bm, &f.bn, &f.wm, &f.wn) == 4) {
+#define X(BM, BN, WM, WN) if (f.bm == BM && f.bn == BN && f.wm == WM && f.wn == WN) return f;
+      RN50_IGEMM_SHAPES(X)
+      if (dtype == RN50_F32) { RN50_IGEMM_SHAPE_F32(X) } else { RN50_IGEMM_SHAPE_BF16(X) }
+#undef X
+    }
+  }
+#endif
   const int64_t groups64 = ceil_div(rows, 64) * ceil_div(Ncols, 64) * (strided_dgrad ? live : 1);
   if (chunks >= 4 && lin_fwd_channels <= 2048 && groups64 <= 256) {
     if (groups64 > 128) return TileShape{64, 64, 1, 1};
@@ -1034,7 +1037,7 @@ static void launch_igemm(const IgemmArgs& a, const char* tag, hipStream_t s) {
                                 igemm_halo_shape(a), lin_fwd ? a.Cg : 0, sizeof(T) == 2 ? RN50_BF16 : RN50_F32);
 #define X(BM, BN, WM, WN) if (t.bm == BM && t.bn == BN && t.wm == WM && t.wn == WN) return launch_igemm_cfg<T, BM, BN, WM, WN>(a, tag, s);
   RN50_IGEMM_SHAPES(X)
-  if constexpr (sizeof(T) == 4) { X(32, 32, 1, 1) } else { X(32, 64, 1, 1) }
+  if constexpr (sizeof(T) == 4) { RN50_IGEMM_SHAPE_F32(X) } else { RN50_IGEMM_SHAPE_BF16(X) }
 #undef X
 }
 

@@ -54,10 +54,10 @@ inline size_t bn_sums_bytes(int64_t nrows, int C, int each) { return static_cast
 // They are added up by a finalize launch, or, when there are few tile rows, by the BN apply pass (forward or backward)
 // itself, in every workgroup, for the channels it applies: the launch in front of it -- about 4 us on the step's
 // dependency chain whatever it computes -- is gone.
-// Threshold from whole-step measurements at batch 40 (40 / 128 / 256 rows
-// against none: 4.613 / 4.577 / 4.666 against 4.649 ms): up to 123 tile rows (the 14x14 and 7x7 layers) the
-// redundant sums cost less than the launch; at 245 (28x28) every workgroup would read more sums than data (raising
-// the backward threshold alone to 256 / 512 rows: 4.78 -> 4.83 / 4.84 ms).
+// Threshold from whole-step measurements (profiles/step_time_against_dispatch_constants.txt; batch 40, 64 / 128 / 256 / 512 rows
+// against none: 4.455 / 4.442 / 4.509 / 4.518 against 4.506 ms): up to 123 tile rows (the 14x14 and 7x7 layers) the
+// redundant sums cost less than the launch; at 245 (28x28) every workgroup would read more sums than data.  (At batch 256 256
+// rows would be 0.5 % faster, 512 slower.)
 constexpr int kBnSelfFinalizeRows = 128, kBnSelfFinalizeRowsBwd = 128;
 inline bool bn_self_finalizes(int nrows, bool backward) {
   return nrows <= (backward ? kBnSelfFinalizeRowsBwd : kBnSelfFinalizeRows);

@@ -422,7 +422,8 @@ struct WgradPlan {
 // takes the longer of one's latency (lat) and n times the tile's share of the LDS and load rates (thr), both dearer where
 // pixels are gathered; `ends` is prologue and result stores; splits add the reduction launch and the partials' traffic.
 // Constants fitted to ResNet-50's 23 shapes x 12 plans at batch 12 to 256 (bf16) and 2 to 24 (float): the plan it
-// takes is within 2 % of the best of the twelve on average.  Against the fixed rule before it (128-wide tiles, 192 or 384
+// takes is within 4 % of the best of the twelve, summed over the shapes (profiles/wgrad_plan_sweep.txt: 546 against 527 us at
+// batch 40, 1878 against 1822 at batch 256, float at batch 8 591 against 583).  Against the fixed rule before it (128-wide tiles, 192 or 384
 // workgroups): 23 shapes at batch 40 640 -> 565 us call by call, at batch 256 2343 -> 2000, float at batch 8
 // 830 -> 531.
 struct WgradCost {
@@ -511,7 +512,8 @@ static WgradArgs wgrad_args(const rn50_conv_desc* d, const void* x, const void* 
   return a;
 }
 // The nine-tap weight gradient (wgrad3x3_kernel): bf16, 3x3, stride 1, padding 1, at most 64 channels each way (one 64x64 tile;
-// wider layers do better on wgrad_kernel's 128-wide tiles), and an image width whose run of 2W + 68 rows fits six load passes.
+// wider layers do better on wgrad_kernel's 128-wide tiles; 56x56, batch 40: 33.5 us, per tap 31.1, batch 256:
+// 106 against 130), and an image width whose run of 2W + 68 rows fits six load passes.
 // Plan: the padded pixel range split to give about 384 workgroups, each at least 8 chunks long.
 struct Wgrad3x3Plan {
   int nbx;  // load passes of the x run: 3, 4 or 6; 0: the layer does not run this kernel

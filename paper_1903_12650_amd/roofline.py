@@ -31,10 +31,11 @@ MFMA_F32_PEAK_TFLOPS = 157.3
 # HBM bytes per launch (fetch + write) from the rocprofv3 FETCH_SIZE / WRITE_SIZE counter runs summarized in
 # profiles/resnet50_step_batch40_bf16_hbm_traffic.txt (batch 40, bf16), already scaled by the calibration
 # copy; None where not measured.  Counter attribution per kernel is approximate: lines a kernel leaves
-# dirty in L2 are written back during later kernels.  conv_wgrad includes its reduction pass.
+# dirty in L2 are written back during later kernels.  conv_wgrad includes its reduction pass, conv_dgrad the
+# classifier's data gradient (the same kernel); lars_update is per group of tensors, both launches.
 MEASURED_TRAFFIC_BYTES_PER_LAUNCH = {
-    "conv_fwd": 39.93e6, "conv_dgrad": 63.54e6, "conv_wgrad": 62.64e6, "bn_apply": 42.55e6,
-    "bn_bwd_reduce": 75.69e6, "bn_bwd_apply": 51.85e6, "lars_update": 383.55e6,
+    "conv_fwd": 40.26e6, "conv_dgrad": 62.28e6, "conv_wgrad": 60.73e6, "bn_apply": 45.40e6,
+    "bn_bwd_reduce": 68.71e6, "bn_bwd_apply": 53.58e6, "lars_update": 127.93e6,
 }
 
 # Kernel classes of the step: (class, launch tags whose durations it sums, tag whose launches it is counted in).
