@@ -438,9 +438,10 @@ class LarsTable:
         # what follows on this stream; lars_update orders every other use behind it (_order).
         self._pinned = table.pin_memory()
         self.dev = self._pinned.to(self.device, non_blocking=True)
-        self._stream = _raw_stream()
+        stream = torch.cuda.current_stream(self.device)
+        self._stream = stream.cuda_stream
         self._ready = torch.cuda.Event()
-        self._ready.record()
+        self._ready.record(stream)
         self._arrived = False
 
     def _order(self):

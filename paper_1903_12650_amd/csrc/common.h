@@ -165,7 +165,7 @@ __device__ __forceinline__ double2 bn_tile_sums(float k, float s1, float s2, int
   return make_double2(d1 + nd * kd, static_cast<double>(s2) + kd * (2.0 * d1 + nd * kd));
 }
 // The same sums as they are, with their shift: the row of a tile for the finalize launch.  (As mean and squared deviations, two
-// floats, the mean is rounded at its own size: where it is 600 standard deviations from zero, 1 / std of 125,000 rows came out
+// floats, the mean is rounded at its own size: where it is 2000 standard deviations from zero, 1 / std of 125,000 rows came out
 // up to 5.6 units in the last place off instead of 1.0.)
 struct BnTileRow {
   float k, s1, s2;
