@@ -60,7 +60,7 @@ def test_host_side_argument_checks_need_no_gpu():
 
 
 def test_dgrad_bn_sums_rejects_a_mask_without_addend_before_any_launch():
-    """Every argument check of conv_dgrad_bn_sums precedes its first launch (the weight transposition): with no
+    """Every argument check of conv_dgrad_bn_sums precedes its first launch: with no
     GPU here a launch attempt would surface as a HIP error (-5), an argument error comes back as -1."""
     import paper_1903_12650_amd as rn
     raw = rn.raw
