@@ -245,20 +245,86 @@ __device__ __forceinline__ double rows_of(int b, int nrows, int rpp, int64_t m) 
   return static_cast<double>(b == nrows - 1 ? m - static_cast<int64_t>(b) * rpp : rpp);
 }
 
-// Forward: rows of sums over rpp rows of x each (the last over what is left of m), with their shifts, or about zero (wide; for
-// a layer whose apply pass is left to its consumer).
+// First reduction of many tile rows: workgroup (piece of eight channels, share of the rows) adds its share up to one row of
+// doubles, forward about the shift of the layer's first tile (add_tile_row, as the finalize launch does it).  Thread (channel,
+// group g of 32) takes rows g, g + 32, ... in order; groups by a fixed tree.
+// The finalize launch alone has a workgroup per two channels, so at 64 channels 32 compute units read 12544 rows, 24 of every
+// 96 bytes each: bound by one unit's load instructions (25 us behind an idle chip, 35 to 87 beside the weight gradients).  Here
+// a row's 96 (64) bytes are read together and 8 x 64 workgroups share the rows, and the finalize launch is left with 64 rows:
+// 12544 rows, step at batch 256: 64 channels 25 -> 14, 256 channels 33 -> 16 us with both launches, beside the weight gradients
+// 55 to 87 -> 25 to 60; the step 20.27 -> 20.15 ms.  At 3136 rows the finalize launch alone takes 9 us, as long as both.
+template <bool BWD>
+__global__ __launch_bounds__(256) void bn_reduce_rows_kernel(const float* __restrict__ partial, int nrows, int per, int rpp,
+                                                             int64_t m, double2* __restrict__ out) {
+  __shared__ double red[2][4][8];
+  const int ch = threadIdx.x & 7, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t base = bn_sums_at(0, blockIdx.x * 8 + ch, nrows);
+  const int b0 = blockIdx.y * per, b1 = min(b0 + per, nrows);
+  double s1 = 0.0, s2 = 0.0;
+  if constexpr (BWD) {
+    const float2* p = reinterpret_cast<const float2*>(partial) + base;
+    for (int b = b0 + (threadIdx.x >> 3); b < b1; b += 32 * kFinRows) {
+      float2 v[kFinRows];
+#pragma unroll
+      for (int u = 0; u < kFinRows; ++u) v[u] = p[min(b + u * 32, b1 - 1) * 8];
+#pragma unroll
+      for (int u = 0; u < kFinRows; ++u) {
+        if (b + u * 32 < b1) {
+          s1 += static_cast<double>(v[u].x);
+          s2 += static_cast<double>(v[u].y);
+        }
+      }
+    }
+  } else {
+    const BnTileRow* p = reinterpret_cast<const BnTileRow*>(partial) + base;
+    const double k0 = static_cast<double>(p[0].k);
+    for (int b = b0 + (threadIdx.x >> 3); b < b1; b += 32 * kFinRows) {
+      BnTileRow v[kFinRows];
+#pragma unroll
+      for (int u = 0; u < kFinRows; ++u) v[u] = p[min(b + u * 32, b1 - 1) * 8];
+#pragma unroll
+      for (int u = 0; u < kFinRows; ++u)
+        if (b + u * 32 < b1) add_tile_row(v[u], rows_of(b + u * 32, nrows, rpp, m), k0, &s1, &s2);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off >= 8; off >>= 1) {
+    s1 += __shfl_xor(s1, off, 64);
+    s2 += __shfl_xor(s2, off, 64);
+  }
+  if (lane < 8) {
+    red[0][wave][ch] = s1;
+    red[1][wave][ch] = s2;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 8) return;
+  out[bn_sums_at(blockIdx.y, blockIdx.x * 8 + ch, kBnReducedRows)] =
+      make_double2(((red[0][0][ch] + red[0][1][ch]) + red[0][2][ch]) + red[0][3][ch],
+                   ((red[1][0][ch] + red[1][1][ch]) + red[1][2][ch]) + red[1][3][ch]);
+}
+void bn_reduce_rows(float* sums, int nrows, int rpp, int64_t m, int C, bool backward, hipStream_t s) {
+  const dim3 grid(static_cast<unsigned>(ceil_div(C, 8)), kBnReducedRows);
+  const int per = static_cast<int>(ceil_div(nrows, kBnReducedRows));
+  double2* out = bn_reduced_rows(sums, nrows, C, backward);
+  if (backward) RN50_LAUNCH("bn_bwd_finalize", bn_reduce_rows_kernel<true>, grid, dim3(256), 0, s, sums, nrows, per, rpp, m, out);
+  else RN50_LAUNCH("bn_finalize", bn_reduce_rows_kernel<false>, grid, dim3(256), 0, s, sums, nrows, per, rpp, m, out);
+}
+
+// Forward: rows of sums over rpp rows of x each (the last over what is left of m), with their shifts; or (wide not null) rows of
+// doubles: about zero (for a layer whose apply pass is left to its consumer), or reduced, about the shift of partial's first row.
 __global__ __launch_bounds__(kFinThreads) void bn_finalize_kernel(const float* __restrict__ partial, int nrows, int rpp,
-                                                           int wide, int64_t m, int C, float eps, float* __restrict__ mean_out,
+                                                           const double2* __restrict__ wide, int nwide, int64_t m, int C,
+                                                           float eps, float* __restrict__ mean_out,
                                                            float* __restrict__ rstd_out, float* running_mean,
                                                            float* running_var, float momentum) {
   constexpr int G = kFinThreads / kFinCh;
   const int c = blockIdx.x * kFinCh + threadIdx.x % kFinCh;
   const BnTileRow* p = reinterpret_cast<const BnTileRow*>(partial) + bn_sums_at(0, c, nrows);  // (the last piece of C is padded)
-  const double k0 = wide ? 0.0 : static_cast<double>(p[0].k);
+  const double k0 = partial ? static_cast<double>(p[0].k) : 0.0;
   double s1 = 0.0, s2 = 0.0;
   if (wide) {
-    const double2* pd = reinterpret_cast<const double2*>(partial) + bn_sums_at(0, c, nrows);
-    for (int b = threadIdx.x / kFinCh; b < nrows; b += G) {
+    const double2* pd = wide + bn_sums_at(0, c, nwide);
+    for (int b = threadIdx.x / kFinCh; b < nwide; b += G) {
       s1 += pd[b * 8].x;
       s2 += pd[b * 8].y;
     }
@@ -565,12 +631,22 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(
   reinterpret_cast<float2*>(partial)[bn_sums_at(blockIdx.x, c, gridDim.x)] = make_float2(t1, t2);
 }
 
-__global__ __launch_bounds__(kFinThreads) void bn_bwd_finalize_kernel(const float* __restrict__ partial, int nrows, int C,
+// (wide not null: rows of doubles from bn_reduce_rows_kernel instead)
+__global__ __launch_bounds__(kFinThreads) void bn_bwd_finalize_kernel(const float* __restrict__ partial, int nrows,
+                                                               const double2* __restrict__ wide, int nwide, int C,
                                                                float* __restrict__ dgamma, float* __restrict__ dbeta) {
   constexpr int G = kFinThreads / kFinCh;
   const int c = blockIdx.x * kFinCh + threadIdx.x % kFinCh;
   const float2* p = reinterpret_cast<const float2*>(partial) + bn_sums_at(0, c, nrows);
   double s1 = 0.0, s2 = 0.0;
+  if (wide) {
+    const double2* pd = wide + bn_sums_at(0, c, nwide);
+    for (int b = threadIdx.x / kFinCh; b < nwide; b += G) {
+      s1 += pd[b * 8].x;
+      s2 += pd[b * 8].y;
+    }
+    nrows = 0;
+  }
   for (int b = threadIdx.x / kFinCh; b < nrows; b += kFinRows * G) {
     float2 v[kFinRows];
 #pragma unroll
@@ -732,12 +808,13 @@ static size_t bn_ws_bytes(const rn50_bn_desc* d) {
   return align_up(bn_sums_bytes(g.nblk, d->C, bn_self_sums(m, d->C) ? kBnWideSumBytes : kBnTileRowBytes), 256);
 }
 
-// finalize + apply from partial statistics rows (see bn_finalize_kernel)
+// finalize + apply from partial statistics rows (see bn_finalize_kernel).  reduces: their producer is a convolution, which
+// leaves them reduced where they are many.
 template <typename T, bool LAST>
 static void launch_fwd_tail(const rn50_bn_desc* d, int64_t m, const void* x,
                             const float* gamma, const float* beta, const void* residual, void* y,
                             uint8_t* relu_mask, float* save_mean, float* save_rstd, float* rm, float* rv,
-                            float momentum, const float* partial, int nrows, int rpp, bool self, hipStream_t s) {
+                            float momentum, const float* partial, int nrows, int rpp, bool self, bool reduces, hipStream_t s) {
   if (self && y) {
     // few tile rows: the apply pass finalizes for itself
     int gy, rpb;
@@ -746,7 +823,9 @@ static void launch_fwd_tail(const rn50_bn_desc* d, int64_t m, const void* x,
     RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, true, LAST>), dim3(static_cast<unsigned>(ceil_div(m, rpb)), gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, nullptr, nullptr, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, 3, rpb, d->mode, fin);
     return;
   }
-  RN50_LAUNCH("bn_finalize", bn_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, partial, nrows, rpp, self ? 1 : 0, m, d->C, d->eps, save_mean, save_rstd, rm, rv, momentum);
+  const bool reduced = !self && reduces && bn_reduces(nrows);
+  const double2* wide = self ? reinterpret_cast<const double2*>(partial) : (reduced ? bn_reduced_rows(partial, nrows, d->C, false) : nullptr);
+  RN50_LAUNCH("bn_finalize", bn_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, self ? nullptr : partial, nrows, rpp, wide, reduced ? kBnReducedRows : nrows, m, d->C, d->eps, save_mean, save_rstd, rm, rv, momentum);
   if (!y) return;  // statistics only: the consumer applies the layer while it loads its operand
   const BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnApplyGroups);
   RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, false, LAST>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, save_mean, save_rstd, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, ga.tx_log2, ga.rpb, d->mode, BnFinArgs{});
@@ -760,7 +839,7 @@ static void launch_fwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const 
   const bool self = bn_self_sums(m, d->C);
   RN50_LAUNCH("bn_stats", bn_stats_kernel<T>, dim3(g.nblk, g.gy), dim3(256), 0, s, static_cast<const T*>(x), m, d->C, g.tx_log2, g.rpb, self ? 1 : 0, partial);
   launch_fwd_tail<T, false>(d, m, x, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv, momentum,
-                     partial, g.nblk, g.rpb, self, s);
+                     partial, g.nblk, g.rpb, self, false, s);
 }
 
 // finalize + apply from partial sums rows [sum g, sum g*xhat]
@@ -769,7 +848,7 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
                             const void* dz2, const void* x, const void* z, const uint8_t* zmask,
                             const float* gamma, const float* beta, const float* mean, const float* rstd,
                             void* dx, void* dres, float* dgamma, float* dbeta, const float* partial,
-                            int nrows, bool self, hipStream_t s) {
+                            int nrows, bool self, bool reduces, hipStream_t s) {
   BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnBwdApplyGroups);
   BnFinArgs fin{};
   if (self) {
@@ -779,7 +858,8 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
     ga.nblk = static_cast<int>(ceil_div(m, ga.rpb));
     fin = BnFinArgs{partial, nrows, 0.f, 0.f, dbeta, dgamma, nullptr, nullptr};
   } else {
-    RN50_LAUNCH("bn_bwd_finalize", bn_bwd_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, partial, nrows, d->C, dgamma, dbeta);
+    const double2* wide = reduces && bn_reduces(nrows) ? bn_reduced_rows(partial, nrows, d->C, true) : nullptr;
+    RN50_LAUNCH("bn_bwd_finalize", bn_bwd_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, partial, nrows, wide, kBnReducedRows, d->C, dgamma, dbeta);
   }
 #define RN50_BWD_APPLY_K(DZ2, ZK, FIN)                                                                             \
   RN50_LAUNCH("bn_bwd_apply", (bn_bwd_apply_kernel<T, DZ2, ZK, FIN, LAST && ZK != 1>), dim3(ga.nblk, ga.gy), dim3(256), 0, s,       \
@@ -818,7 +898,7 @@ static void launch_bwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const 
   }
 #undef RN50_BWD_REDUCE
   launch_bwd_tail<T, LAST>(d, m, dz, dz2, x, z, zmask, gamma, beta, mean, rstd, dx, dres, dgamma, dbeta, partial,
-                     g.nblk, self, s);
+                     g.nblk, self, false, s);
 }
 
 // Entry points for the whole-step driver (last_reader) and the fused C-ABI calls: the sums come from the output stage
@@ -828,7 +908,7 @@ static void fwd_from_partials(const rn50_bn_desc* d, const void* x, const float*
                               const float* gamma, const float* beta, const void* residual, void* y, uint8_t* relu_mask,
                               float* save_mean, float* save_rstd, float* rm, float* rv, float momentum, hipStream_t s) {
   launch_fwd_tail<T, LAST>(d, static_cast<int64_t>(d->N) * d->H * d->W, x, gamma, beta, residual, y, relu_mask, save_mean,
-                           save_rstd, rm, rv, momentum, partial, nrows, rpp, bn_self_finalizes(nrows, false), s);
+                           save_rstd, rm, rv, momentum, partial, nrows, rpp, bn_self_finalizes(nrows, false), true, s);
 }
 void bn_fwd_from_partials(const rn50_bn_desc* d, const void* x, const float* partial, int nrows, int rpp,
                           const float* gamma, const float* beta, const void* residual, void* y,
@@ -864,7 +944,7 @@ static void bwd_from_partials(const rn50_bn_desc* d, const void* dz, const void*
                               const float* partial, int nrows, void* dx, void* dres, float* dgamma, float* dbeta,
                               hipStream_t s) {
   launch_bwd_tail<T, LAST>(d, static_cast<int64_t>(d->N) * d->H * d->W, dz, nullptr, x, nullptr, relu_mask, gamma, beta, mean,
-                           rstd, dx, dres, dgamma, dbeta, partial, nrows, bn_self_finalizes(nrows, true), s);
+                           rstd, dx, dres, dgamma, dbeta, partial, nrows, bn_self_finalizes(nrows, true), true, s);
 }
 void bn_bwd_from_partials(const rn50_bn_desc* d, const void* dz, const void* x, const uint8_t* relu_mask,
                           const float* gamma, const float* beta, const float* mean, const float* rstd,

@@ -1035,10 +1035,14 @@ static void launch_igemm(const IgemmArgs& a, const char* tag, hipStream_t s) {
   const bool lin_fwd = a.mode != 1 && a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0 && !a.pair;
   const TileShape t = pick_tile(rows, a.Ncols, a.R * a.S * a.cpt, a.mode == 1, classes, a.R * a.S > 1 ? 4 : 1,
                                 igemm_halo_shape(a), lin_fwd ? a.Cg : 0, sizeof(T) == 2 ? RN50_BF16 : RN50_F32);
-#define X(BM, BN, WM, WN) if (t.bm == BM && t.bn == BN && t.wm == WM && t.wn == WN) return launch_igemm_cfg<T, BM, BN, WM, WN>(a, tag, s);
+#define X(BM, BN, WM, WN) if (t.bm == BM && t.bn == BN && t.wm == WM && t.wn == WN) launch_igemm_cfg<T, BM, BN, WM, WN>(a, tag, s);
   RN50_IGEMM_SHAPES(X)
   if constexpr (sizeof(T) == 4) { RN50_IGEMM_SHAPE_F32(X) } else { RN50_IGEMM_SHAPE_BF16(X) }
 #undef X
+  if (a.partial) {  // (a stride-2 data gradient has the tiles of four classes of pixels)
+    const int mtiles = static_cast<int>((classes ? 4 : 1) * ceil_div(rows, t.bm));
+    if (bn_reduces(mtiles)) bn_reduce_rows(a.partial, mtiles, t.bm, a.M, a.Ncols, a.mode == 1, s);
+  }
 }
 
 static int check_conv(const rn50_conv_desc* d, const char* who) {

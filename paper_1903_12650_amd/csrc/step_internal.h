@@ -63,6 +63,18 @@ inline bool bn_self_finalizes(int nrows, bool backward) {
   return nrows <= (backward ? kBnSelfFinalizeRowsBwd : kBnSelfFinalizeRows);
 }
 
+// More tile rows than a finalize launch should read: the producer adds them up, in double, to kBnReducedRows rows of doubles
+// behind its own (bn_reduced_rows; there is room: such a layer's tiles have at least 64 pixels, the buffer is sized for tiles
+// of 32), and the finalize launch reads these.  Why and where the line lies: bn_reduce_rows_kernel.
+constexpr int kBnReduceRows = 4096, kBnReducedRows = 64;
+inline bool bn_reduces(int nrows) { return nrows > kBnReduceRows; }
+inline double2* bn_reduced_rows(const float* sums, int nrows, int C, bool backward) {
+  const size_t own = bn_sums_bytes(nrows, C, backward ? kBnBwdSumBytes : kBnTileRowBytes);  // (a multiple of 32)
+  return reinterpret_cast<double2*>(reinterpret_cast<uintptr_t>(sums) + own);
+}
+// bn.hip.  rpp: rows of x behind a row of sums (forward), m: of x in all.
+void bn_reduce_rows(float* sums, int nrows, int rpp, int64_t m, int C, bool backward, hipStream_t s);
+
 // A BN+ReLU layer applied to a convolution's input on the fly (1x1, stride 1 convolutions only): its parameters
 // and saved statistics, float[Cin] each.
 struct BnIn {

@@ -105,6 +105,38 @@ def test_conv_fwd_bn_sums_mean_far_from_zero(rn, N, H, C, K):
     assert np.abs(host(rstd) / rstd_o - 1).max() <= 2.0 ** -22, np.abs(host(rstd) / rstd_o - 1).max() * 2 ** 24
 
 
+@pytest.mark.parametrize("mode_name,C", [("bf16", 8), ("bf16", 24), ("f32", 12)])
+@pytest.mark.parametrize("H,W", [(512, 512), (512, 513), (577, 611)])
+def test_many_tile_rows_are_reduced_by_their_producer(rn, mode_name, C, H, W):
+    """Above 4096 tile rows (of 64 pixels here; 4096, 4104 and 5509 of them) the convolutions leave rows of doubles.  Statistics
+    and backward sums against 64 bits: per-tile sums in float over 64 values, everything behind them in double."""
+    bf = mode_name == "bf16"
+    dt = torch.bfloat16 if bf else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(H + C)
+    x = (torch.randn(1, H, W, 8, device="cuda", generator=gen) + 3.0).to(dt)
+    w = (torch.randn(C, 1, 1, 8, device="cuda", generator=gen) * 0.3 + 0.5).to(dt)
+    y, sums = rn.conv_fwd_bn_sums(x, w, 1, 0)
+    gamma, beta = torch.ones(C, device="cuda"), torch.zeros(C, device="cuda")
+    _, mean, rstd = rn.bn_relu_fwd_from_sums(y, sums, gamma, beta, None, 1e-5, 1)
+    y64 = y.double().reshape(-1, C)
+    mean_o = y64.mean(0)
+    rstd_o = 1.0 / torch.sqrt(y64.var(0, unbiased=False) + 1e-5)
+    assert ((mean - mean_o).abs() <= 2.0 ** -23 * mean_o.abs() + 2.0 ** -22 / rstd_o).all()
+    assert ((rstd / rstd_o - 1).abs() <= 2.0 ** -22).all()
+    # backward: dy [1][H][W][8] of a 1x1 layer with C input channels, whose input is that BN's output
+    dy = torch.randn(1, H, W, 8, device="cuda", generator=gen).to(dt)
+    wb = (torch.randn(8, 1, 1, C, device="cuda", generator=gen) * 0.3).to(dt)
+    dx, bsums = rn.conv_dgrad_bn_sums(dy, wb, (1, H, W, C), 1, 0, y, gamma, beta, mean, rstd)
+    _, _, dgamma, dbeta = rn.bn_relu_bwd_from_sums(dx, y, bsums, gamma, beta, mean, rstd, mode=1)
+    xhat = (y64 - mean.double()) * rstd.double()
+    # (the decision as the kernel takes it, in float: y * rstd - mean * rstd > 0)
+    on = torch.addcmul(-(mean * rstd).double(), y64, rstd.double()).float() > 0
+    g64 = dx.double().reshape(-1, C) * on
+    # a tile's float sum of 64 terms is off by at most 64 * 2^-24 of the sum of their magnitudes
+    for got, terms in ((dbeta, g64), (dgamma, g64 * xhat)):
+        assert ((got.double() - terms.sum(0)).abs() <= 64 * 2.0 ** -24 * terms.abs().sum(0)).all()
+
+
 DGRAD_SHAPES = [s for s in FUSED_SHAPES if s[3] != 3]
 
 
