@@ -84,6 +84,21 @@ __global__ __launch_bounds__(256) void maxpool_bwd_idx_kernel(const uint8_t* __r
   if (xi >= Wb * cv) return;
   const int b = static_cast<int>(fdiv(static_cast<uint32_t>(xi), div_cv)), c = xi - b * cv;
   const int a = blockIdx.y, n = blockIdx.z;
+  // the operands of all four windows are requested first (a window that does not exist repeats the first one and is nobody's)
+  Vec16 g1[4], g2[4];
+  uint2 idx[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int dp = k >> 1, dq = k & 1;
+    const bool ok = a + dp < P && b + dq < Q;
+    const int64_t o = ((static_cast<int64_t>(n) * P + (ok ? a + dp : a)) * Q + (ok ? b + dq : b)) * C + c * V;
+    g1[k] = load16(dy + o);
+    if (dy2) g2[k] = load16(dy2 + o);
+    idx[k] = make_uint2(0, 0);
+    if (V == 8) idx[k] = *reinterpret_cast<const uint2*>(argmax + o);
+    else idx[k].x = *reinterpret_cast<const uint32_t*>(argmax + o);
+    if (!ok) idx[k] = make_uint2(0xffffffffu, 0xffffffffu);
+  }
   float acc[2][2][V];
 #pragma unroll
   for (int k = 0; k < 4; ++k)
@@ -93,28 +108,24 @@ __global__ __launch_bounds__(256) void maxpool_bwd_idx_kernel(const uint8_t* __r
   for (int dp = 0; dp < 2; ++dp)
 #pragma unroll
     for (int dq = 0; dq < 2; ++dq) {
-      const int p = a + dp, q = b + dq;
-      if (p >= P || q >= Q) continue;
-      const int64_t o = ((static_cast<int64_t>(n) * P + p) * Q + q) * C + c * V;
-      uint8_t idx[V];
-      if (V == 8) *reinterpret_cast<uint2*>(idx) = *reinterpret_cast<const uint2*>(argmax + o);
-      else *reinterpret_cast<uint32_t*>(idx) = *reinterpret_cast<const uint32_t*>(argmax + o);
+      const int k = 2 * dp + dq;
       float g[V];
-      Elem<T>::unpack(load16(dy + o), g);
+      Elem<T>::unpack(g1[k], g);
       if (dy2) {
-        float g2[V];
-        Elem<T>::unpack(load16(dy2 + o), g2);
+        float f2[V];
+        Elem<T>::unpack(g2[k], f2);
 #pragma unroll
-        for (int j = 0; j < V; ++j) g[j] += g2[j];
+        for (int j = 0; j < V; ++j) g[j] += f2[j];
       }
       // pixel (2a+i, 2b+jj) sits at window position (2a+i - (2p-1))*3 + (2b+jj - (2q-1))
 #pragma unroll
       for (int ii = dp; ii < 2; ++ii)      // window row a+1 starts at pixel row 2a+1
 #pragma unroll
         for (int jj = dq; jj < 2; ++jj) {
-          const int pos = (ii + 1 - 2 * dp) * 3 + (jj + 1 - 2 * dq);
+          const uint32_t pos = (ii + 1 - 2 * dp) * 3 + (jj + 1 - 2 * dq);
 #pragma unroll
-          for (int j = 0; j < V; ++j) acc[ii][jj][j] += idx[j] == pos ? g[j] : 0.f;
+          for (int j = 0; j < V; ++j)
+            acc[ii][jj][j] += (((j < 4 ? idx[k].x : idx[k].y) >> (8 * (j & 3))) & 0xffu) == pos ? g[j] : 0.f;
         }
     }
 #pragma unroll

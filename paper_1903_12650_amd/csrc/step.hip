@@ -480,8 +480,8 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
                          run_mean ? run_mean + u.bn_off : nullptr, run_var ? run_var + u.bn_off : nullptr, bn_momentum, true, st);
   };
   stem_fwd_padded(&u0.conv, ws + plan->xp, W(u0.iw), ws + plan->wp, ws + u0.y, sums, s);
-  bn_after_conv(u0, nullptr, sums, s);
-  STEP_TRY(maxpool_fwd(cfg.N, u0.P, u0.Q, cfg.stem, dt, ws + u0.z, ws + plan->pool, ws + plan->pool_argmax, s));
+  bn_after_conv(u0, nullptr, sums, s, true);
+  bn_relu_maxpool(&u0.bn, ws + u0.y, MP(u0.ig), MP(u0.ib), F(u0.mean), F(u0.rstd), ws + plan->pool, ws + plan->pool_argmax, s);
   const unsigned char* cur = ws + plan->pool;
   auto conv_bn = [&](Unit& u, const void* in, const void* residual, float* sm, hipStream_t st) {
     fwd_run(&u.conv, in, W(u.iw), ws + u.y, sm, st);
@@ -672,7 +672,7 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
     }
     block_end();
   }
-  STEP_TRY(maxpool_bwd(cfg.N, u0.P, u0.Q, cfg.stem, dt, ws + u0.z, ws + plan->pool_argmax, dzo, dzo2, dz_next, s));
+  STEP_TRY(maxpool_bwd(cfg.N, u0.P, u0.Q, cfg.stem, dt, nullptr, ws + plan->pool_argmax, dzo, dzo2, dz_next, s));
   unit_bwd(u0, ws + plan->xp, dz_next, nullptr, nullptr, nullptr, false, nullptr, nullptr);
   block_end();
   // ------------------------------------------------------------------ LARS

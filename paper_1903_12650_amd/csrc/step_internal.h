@@ -118,6 +118,10 @@ void bn_bwd_from_partials(const rn50_bn_desc* d, const void* dz, const void* x, 
 void bn_bwd_run(const rn50_bn_desc* d, const void* dz, const void* dz2, const void* x, const void* z,
                 const uint8_t* relu_mask, const float* gamma, const float* beta, const float* mean, const float* rstd,
                 void* dx, void* dres, float* dgamma, float* dbeta, float* scratch, bool last_reader, hipStream_t s);
+// relu(bn(x)) of known statistics, through the 3x3 / stride 2 / padding 1 max-pool: pooled output and winners (maxpool_fwd's)
+// from the BN layer's input.
+void bn_relu_maxpool(const rn50_bn_desc* d, const void* x, const float* gamma, const float* beta, const float* mean,
+                     const float* rstd, void* pooled, uint8_t* argmax, hipStream_t s);
 
 // head.hip: the pieces of xent_fwd_bwd and fc_bwd that a step runs on different streams.
 // The rows of the loss: row_loss, dlogits and (bf16, or null) the copy of dlogits rounded to the storage type.

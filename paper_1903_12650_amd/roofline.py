@@ -11,6 +11,8 @@ Per unit of work (elements are activation elements of the BN's tensor, bf16 = 2 
                          block output's gradient under the block's own recorded bits)
   conv_wgrad             2*M*N*K flop;  bytes = es*(|x| + |dy|) + 4*|dw|
   bn_apply               2*es bytes/element (read x, write y) + es for the residual read (mode 2)
+                         (the stem's pass goes through the max-pool and stores the pooled tensor alone;
+                         charged like the others, 3 % of the class more than it moves)
   bn_bwd_reduce          2*es bytes/element (read dz, x); launched only for the layers whose sums are not
                          taken in the output stage of the data gradient that produces dz (the stem, the
                          last block's residual-add layer and the projection shortcuts)

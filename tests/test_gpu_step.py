@@ -297,6 +297,14 @@ def test_step_small_net_bf16(rn):
     run_step_vs_chain(rn, "bf16", 4, 64, (8, 16, 24, 32), (2, 1, 2, 1), 8, 16, ls=0.1, loss_band=0.2)
 
 
+@pytest.mark.parametrize("mode_name,loss_band", [("f32", 1e-4), ("bf16", 0.3)])
+@pytest.mark.parametrize("hw", [33, 35, 38, 64])
+def test_step_small_net_odd_images(rn, mode_name, loss_band, hw):
+    """The stem's BN + ReLU + max-pool in one pass (two pooled rows per thread) at odd and even numbers of rows and columns before
+    and after the pool, 17 / 18 / 19 / 32 -> 9 / 9 / 10 / 16: bitwise the separate operations, values and winners."""
+    run_step_vs_chain(rn, mode_name, 3, hw, (8, 16, 24, 32), (1, 1, 1, 1), 8, 16, loss_band=loss_band)
+
+
 def test_step_resnet50_batch40_bf16(rn):
     """BASELINE config 4: the full ResNet-50 v1.5 step at batch 40, mixed precision."""
     run_step_vs_chain(rn, "bf16", 40, 224, (64, 128, 256, 512), (3, 4, 6, 3), 64, 1000)
