@@ -91,6 +91,14 @@ struct IgemmArgs {
   const void* addend;
   const uint8_t* bn_zmask;
   const uint8_t* addend_mask;
+  // The addend holds the pixels with even row and column only, [nimg][ceil(P/2)][ceil(Q/2)][Ncols]; it is zero elsewhere (the data
+  // gradient of a 1x1 / stride 2 convolution; 1x1 / stride 1 launches, without addend_mask).
+  int addend_even;
+  // A 1x1 / stride 2 data gradient without sums: the tiles are those of the parity class that has the tap, and each of their
+  // pixels stores the zeros of the other three classes' pixels beside it, in front of the main loop.  (Three of four workgroups
+  // that only stored zeros had a tile's LDS and a tile's prologue each: 56x56 256 <- 512 at batch 40 29.9 -> 20.0 us, 223 -> 144 at
+  // batch 256, 28x28 512 <- 1024 25.6 -> 17.2, 118 -> 103; with the zeros behind the products 23.6, 139, 17.7, 102.)
+  int fill;
   // Forward, 1x1 / stride 1 only (BNIN kernels): the gathered tensor is the INPUT of a BN+ReLU layer, whose
   // relu(x*scale + bias) is applied to every operand vector once it sits in LDS (null: the tensor is used as is).
   // in_lds: byte offset of the per-channel coefficient table behind the ring (host side: lds bytes without it).
@@ -108,8 +116,8 @@ struct IgemmArgs {
 // MODE 1: data-gradient gather  ih = (p + pad - r)/stride when divisible (stride 1 or 2).  With stride 2
 // an output pixel only receives the taps r = (p + pad) mod 2, s = (q + pad) mod 2 (mod 2), so the pixels
 // are processed in four parity classes (p mod 2, q mod 2): a row tile holds pixels of one class and loops
-// over that class's taps only (a quarter of the taps on average, none for three classes of a 1x1 filter,
-// whose tiles just store zeros).
+// over that class's taps only (a quarter of the taps on average, none for three classes of a 1x1 filter:
+// IgemmArgs::fill).
 // MODE 2: the forward gather with an inference-mode batch norm (+ residual, + ReLU) applied to the accumulators: an
 // evaluation pass needs no statistics of the tensor it produces, so the separate pass that read y and wrote z (two
 // thirds of the bytes of a 1x1 layer with its neighbours in HBM, and a third of the pass's time at batch 256) is gone.
@@ -213,8 +221,8 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   if (classes) {
     // the four classes of one pixel range are neighbours in the tile order: they read the same rows of
     // the incoming gradient, and every XCD gets its share of the classes that have taps
-    const int cls = mt & 3;
-    m0 = (mt >> 2) * BM;
+    const int cls = a.fill ? 0 : mt & 3;
+    m0 = (a.fill ? mt : mt >> 2) * BM;
     ph = cls >> 1; pw = cls & 1;
     Hc = (a.P - ph + 1) >> 1; Wc = (a.Q - pw + 1) >> 1;
     Mc = a.nimg * Hc * Wc;
@@ -244,7 +252,8 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     int p = t - n * Hc;
     if (classes) {
       p = 2 * p + ph; q = 2 * q + pw;
-      if (slot == 0) pix_s[lrow + RPL * i] = ok ? (n * a.P + p) * a.Q + q : 0;
+      // (fill: with whether there is a pixel to the right, below; pixel numbers are below 2^28)
+      if (slot == 0) pix_s[lrow + RPL * i] = ok ? ((n * a.P + p) * a.Q + q) | (q + 1 < a.Q ? 1 << 29 : 0) | (p + 1 < a.P ? 1 << 30 : 0) : 0;
     }
     a_base[i] = n * a.H * a.W;
     // a row beyond the last gets coordinates that fail every bounds check below
@@ -265,6 +274,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   const bool col_ok = n < a.Ncols;
   Vec16 xv[DG ? NPASS : 1], av[DG || AFF ? NPASS : 1];
   uint32_t zb[DG ? NPASS : 1], ab[DG ? NPASS : 1];
+  auto pixel = [&](int row) __attribute__((always_inline)) { return pix_s[row] & ((1 << 29) - 1); };
   auto load_output_operands = [&]() __attribute__((always_inline)) {
     if (AFF ? a.addend == nullptr : a.partial == nullptr) return;
     const T* add = static_cast<const T*>(a.addend);
@@ -272,12 +282,22 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
 #pragma unroll
     for (int pass = 0; pass < NPASS; ++pass) {
       const int row = orow + pass * RPP;
-      const int px = classes ? pix_s[row] : min(m0 + row, a.M - 1);  // rows past the last read a valid pixel
+      const int px = classes ? pixel(row) : min(m0 + row, a.M - 1);  // rows past the last read a valid pixel
       const int64_t at = static_cast<int64_t>(px) * a.Ncols + nc;
       if constexpr (DG) {
         xv[pass] = load16(static_cast<const T*>(a.bn_x) + at);
         if (a.bn_zmask) zb[pass] = a.bn_zmask[at / V];
         ab[pass] = a.addend_mask ? a.addend_mask[at / V] : 0xffu;
+      }
+      if constexpr (DG && LIN) {
+        if (add && a.addend_even) {
+          const uint32_t t = fdiv(static_cast<uint32_t>(px), a.div_w[0]), w = static_cast<uint32_t>(px) - t * a.Q;
+          const uint32_t img = fdiv(t, a.div_h[0]), h = t - img * a.P;
+          const int64_t e = (static_cast<int64_t>(img) * ((a.P + 1) >> 1) + (h >> 1)) * ((a.Q + 1) >> 1) + (w >> 1);
+          av[pass].u = make_uint4(0, 0, 0, 0);
+          if (((h | w) & 1) == 0) av[pass] = load16_stream(add + e * a.Ncols + nc);
+          continue;
+        }
       }
       if (add) av[pass] = load16_stream(add + at);  // (its last reader)
     }
@@ -285,6 +305,22 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   if constexpr ((DG || AFF) && EARLY) {
     if (classes) __syncthreads();  // (pix_s)
     load_output_operands();
+  }
+  if (DG && !LIN && !HALO && a.fill) {  // (stores in front of the loads only make the hand-placed waits stricter)
+    __syncthreads();
+#pragma unroll
+    for (int pass = 0; pass < NPASS; ++pass) {
+      const int row = orow + pass * RPP;
+      if (m0 + row < Mc && col_ok) {
+        const bool right = pix_s[row] & (1 << 29), below = pix_s[row] & (1 << 30);
+        const uint4 zero = make_uint4(0, 0, 0, 0);
+        T* const at = static_cast<T*>(a.out) + (static_cast<int64_t>(pixel(row)) * a.Ncols + n);
+        const int64_t next_row = static_cast<int64_t>(a.Q) * a.Ncols;
+        if (right) *reinterpret_cast<uint4*>(at + a.Ncols) = zero;
+        if (below) *reinterpret_cast<uint4*>(at + next_row) = zero;
+        if (right && below) *reinterpret_cast<uint4*>(at + next_row + a.Ncols) = zero;
+      }
+    }
   }
   // The B tile: BN rows (output columns) of one 128-byte chunk of K each, or (data gradient) BK rows (K) of BN columns.
   constexpr int BRB = BN * static_cast<int>(sizeof(T)), LB = BRB / 16;  // data gradient: bytes and 16-byte pieces per tile row
@@ -703,7 +739,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       const int row = orow + pass * RPP;
       const int m = m0 + row;
       if (m < Mc && n < a.Ncols) {
-        const int pix = classes ? pix_s[row] : m;
+        const int pix = classes ? pixel(row) : m;
         *reinterpret_cast<uint4*>(out + (static_cast<int64_t>(pix) * a.Ncols + n)) =
             *reinterpret_cast<const uint4*>(smem + row * CP + op * 16);
       }
@@ -774,7 +810,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         } else {
           v.u = *reinterpret_cast<const uint4*>(smem + row * CP + op * 16);
         }
-        const int pix = classes ? pix_s[row] : m0 + row;
+        const int pix = classes ? pixel(row) : m0 + row;
         *reinterpret_cast<uint4*>(out + (static_cast<int64_t>(pix) * a.Ncols + n)) = v.u;
         Elem<T>::unpack(v, g);  // the sums range over the stored (rounded) values
         Elem<T>::unpack(xv[pass], xf);
@@ -917,7 +953,8 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
   // stride-2 data gradient: four parity classes of the output pixels, each with its own row tiles
   const int64_t tiles_per_class = ceil_div(static_cast<int64_t>(a.nimg) * ((a.P + 1) / 2) * ((a.Q + 1) / 2), BM);
   const bool classes = a.mode == 1 && a.stride == 2;
-  a.mtiles = static_cast<int>(classes ? 4 * tiles_per_class : ceil_div(a.M, BM));
+  a.fill = classes && a.R == 1 && a.S == 1 && a.partial == nullptr;
+  a.mtiles = static_cast<int>(classes ? (a.fill ? 1 : 4) * tiles_per_class : ceil_div(a.M, BM));
   const int64_t grid = static_cast<int64_t>(a.mtiles) * a.ntn;
   a.partial_wide = bn_self_finalizes(a.mtiles, false);
   a.div_ntn = make_fastdiv(a.ntn);
@@ -1191,7 +1228,7 @@ void dgrad_run(const rn50_conv_desc* d, const void* dy, const void* w, void* dx,
   if (bn) {
     a.partial = bn->partial; a.bn_x = bn->x;
     a.bn_gamma = bn->gamma; a.bn_beta = bn->beta; a.bn_mean = bn->mean; a.bn_rstd = bn->rstd;
-    a.addend = bn->addend; a.bn_zmask = bn->relu_mask; a.addend_mask = bn->addend ? bn->addend_mask : nullptr;
+    a.addend_even = bn->addend_even; a.addend = bn->addend; a.bn_zmask = bn->relu_mask; a.addend_mask = bn->addend ? bn->addend_mask : nullptr;
   }
   a.P = d->H; a.Q = d->W;
   a.H = out_dim(d->H, d->pad, d->R, d->stride); a.W = out_dim(d->W, d->pad, d->S, d->stride);

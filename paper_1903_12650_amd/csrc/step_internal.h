@@ -95,6 +95,7 @@ struct BnBwdSums {
   const void* addend = nullptr;
   const uint8_t* relu_mask = nullptr;
   const uint8_t* addend_mask = nullptr;
+  bool addend_even = false;  // the addend's pixels with odd row or column are zero and left out (1x1 / stride 1, no addend_mask)
 };
 void dgrad_run(const rn50_conv_desc* d, const void* dy, const void* w, void* dx, const BnBwdSums* bn, hipStream_t s,
                const char* tag = "conv_dgrad");

@@ -230,6 +230,24 @@ def test_k_split_edges(rn, mode_name, case):
     run_case(rn, mode_name, N, H, W, C, K, R, stride, pad, tag="ks" + str(case))
 
 
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("N,H,W,C,K", [(1, 1, 1, 8, 8), (1, 2, 1, 8, 8), (1, 1, 2, 8, 8), (2, 16, 16, 64, 64), (3, 17, 9, 136, 72),
+                                       (2, 7, 6, 264, 520), (5, 31, 30, 256, 512), (9, 56, 56, 256, 128)])
+def test_strided_1x1_data_gradient_stores_every_pixel(rn, mode_name, N, H, W, C, K):
+    """Tiles hold the pixels with the tap and store the zeros beside them: rows, columns and tiles at the edges, into a buffer
+    of NaNs."""
+    dt = torch.bfloat16 if mode_name == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(H * W + C)
+    dy = torch.randn(N, (H - 1) // 2 + 1, (W - 1) // 2 + 1, K, device="cuda", generator=gen).to(dt)
+    w = (torch.randn(K, 1, 1, C, device="cuda", generator=gen) * 0.1).to(dt)
+    dx = torch.full((N, H, W, C), float("nan"), device="cuda", dtype=dt)
+    rn.conv_dgrad(dy, w, dx.shape, 2, 0, dx=dx)
+    want = torch.zeros(N, H, W, C, device="cuda", dtype=torch.float64)
+    want[:, ::2, ::2] = (dy.double().reshape(-1, K) @ w.double().reshape(K, C)).reshape(dy.shape[:3] + (C,))
+    assert_close(dx, host(want), TOL[mode_name], "dx")
+    assert torch.equal(dx == 0, want == 0)
+
+
 # Weight gradient: tiles that span filter taps, channel counts at the edges of the tile widths, pixel ranges of less than one
 # chunk, one chunk more than a whole number of splits, and the most splits.
 WGRAD_EDGES = [(1, 3, 3, 40, 64, 3, 1, 1), (2, 8, 8, 64, 72, 1, 1, 0), (2, 8, 8, 72, 64, 1, 1, 0), (1, 1, 1, 128, 128, 3, 1, 1),
