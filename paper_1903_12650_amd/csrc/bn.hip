@@ -416,7 +416,7 @@ __device__ __forceinline__ void finalize_slice_fwd(const BnFinArgs& f, int64_t m
 // the weight gradient's operands.  Whole step: batch 40 4.506 -> 4.457 ms, batch 256 20.90 -> 20.55 (stores past the caches
 // made batch 40 slower).  Not for the calls of one operation, whose next one may read the same tensor: bn_relu_fwd and then
 // bn_relu_bwd over ResNet-50's layers at batch 40 take 589 us with these loads and 523 without.
-template <typename T, bool FIN, bool LAST>
+template <typename T, bool FIN, bool LAST, bool THROUGH>
 __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ x,
                                                        const float* __restrict__ gamma,
                                                        const float* __restrict__ beta,
@@ -425,8 +425,9 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ x,
                                                        const T* __restrict__ residual,
                                                        T* __restrict__ y, uint8_t* __restrict__ relu_mask,
                                                        int64_t m, int C, int tx_log2, int rpb, int mode,
-                                                       const BnFinArgs fin) {
+                                                       int through, const BnFinArgs fin) {
   constexpr int V = Elem<T>::VEC;
+  const OutTensor<T, THROUGH> out(y, through);
   const int TX = 1 << tx_log2, TY = 256 >> tx_log2;
   const int tcol = threadIdx.x & (TX - 1), trow = threadIdx.x >> tx_log2;
   const int col = blockIdx.y * TX + tcol;
@@ -491,7 +492,7 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ x,
         }
         Vec16 o;
         Elem<T>::pack(f, o);
-        store16(y + off[u], o);
+        out.store(off[u], o);
         if (relu_mask) {  // bit j: stored output j is positive; one byte per 16-byte vector
           float zf[V];
           Elem<T>::unpack(o, zf);
@@ -710,15 +711,16 @@ __device__ __forceinline__ void finalize_slice_bwd(const BnFinArgs& f, int C, in
 
 // FIN, LAST: as in bn_apply_kernel -- the pass adds up the per-tile sums of its 8 vector columns itself
 // (tx_log2 = 3) and the first row block of every column slice stores dgamma / dbeta.
-template <typename T, bool DZ2, int ZK, bool FIN, bool LAST>
+template <typename T, bool DZ2, int ZK, bool FIN, bool LAST, bool THROUGH>
 __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(
     const T* __restrict__ dz, const T* __restrict__ dz2, const T* __restrict__ x,
     const T* __restrict__ z, const uint8_t* __restrict__ zmask, const float* __restrict__ gamma,
     const float* __restrict__ beta,
     const float* __restrict__ mean, const float* __restrict__ rstd,
     const float* __restrict__ dgamma, const float* __restrict__ dbeta, T* __restrict__ dx,
-    T* __restrict__ dres, int64_t m, int C, int tx_log2, int rpb, int mode, const BnFinArgs fin) {
+    T* __restrict__ dres, int64_t m, int C, int tx_log2, int rpb, int mode, int through, const BnFinArgs fin) {
   constexpr int V = Elem<T>::VEC;
+  const OutTensor<T, THROUGH> out(dx, through);
   const int TX = 1 << tx_log2, TY = 256 >> tx_log2;
   const int tcol = threadIdx.x & (TX - 1), trow = threadIdx.x >> tx_log2;
   int col = blockIdx.y * TX + tcol;
@@ -777,7 +779,7 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(
         }
         Vec16 ov;
         Elem<T>::pack(o, ov);
-        store16(dx + b.off[u], ov);
+        out.store(b.off[u], ov);
         if (mode == 2 && dres) {
           Vec16 gv;
           Elem<T>::pack(g, gv);
@@ -815,12 +817,14 @@ static void launch_fwd_tail(const rn50_bn_desc* d, int64_t m, const void* x,
                             const float* gamma, const float* beta, const void* residual, void* y,
                             uint8_t* relu_mask, float* save_mean, float* save_rstd, float* rm, float* rv,
                             float momentum, const float* partial, int nrows, int rpp, bool self, bool reduces, hipStream_t s) {
+  const int through = writes_through(m * d->C * sizeof(T));
   if (self && y) {
     // few tile rows: the apply pass finalizes for itself
     int gy, rpb;
     bn_self_finalize_geom(m, d->C, d->dtype == RN50_BF16 ? 8 : 4, &gy, &rpb);
     const BnFinArgs fin{partial, nrows, d->eps, momentum, save_mean, save_rstd, rm, rv};
-    RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, true, LAST>), dim3(static_cast<unsigned>(ceil_div(m, rpb)), gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, nullptr, nullptr, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, 3, rpb, d->mode, fin);
+    if (through) RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, true, LAST, true>), dim3(static_cast<unsigned>(ceil_div(m, rpb)), gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, nullptr, nullptr, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, 3, rpb, d->mode, through, fin);
+    else RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, true, LAST, false>), dim3(static_cast<unsigned>(ceil_div(m, rpb)), gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, nullptr, nullptr, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, 3, rpb, d->mode, through, fin);
     return;
   }
   const bool reduced = !self && reduces && bn_reduces(nrows);
@@ -828,7 +832,8 @@ static void launch_fwd_tail(const rn50_bn_desc* d, int64_t m, const void* x,
   RN50_LAUNCH("bn_finalize", bn_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, self ? nullptr : partial, nrows, rpp, wide, reduced ? kBnReducedRows : nrows, m, d->C, d->eps, save_mean, save_rstd, rm, rv, momentum);
   if (!y) return;  // statistics only: the consumer applies the layer while it loads its operand
   const BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnApplyGroups);
-  RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, false, LAST>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, save_mean, save_rstd, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, ga.tx_log2, ga.rpb, d->mode, BnFinArgs{});
+  if (through) RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, false, LAST, true>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, save_mean, save_rstd, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, ga.tx_log2, ga.rpb, d->mode, through, BnFinArgs{});
+  else RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, false, LAST, false>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, save_mean, save_rstd, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, ga.tx_log2, ga.rpb, d->mode, through, BnFinArgs{});
 }
 
 template <typename T>
@@ -850,6 +855,7 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
                             void* dx, void* dres, float* dgamma, float* dbeta, const float* partial,
                             int nrows, bool self, bool reduces, hipStream_t s) {
   BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnBwdApplyGroups);
+  const int through = writes_through(m * d->C * sizeof(T));
   BnFinArgs fin{};
   if (self) {
     // few tile rows: the apply pass adds them up itself
@@ -861,11 +867,15 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
     const double2* wide = reduces && bn_reduces(nrows) ? bn_reduced_rows(partial, nrows, d->C, true) : nullptr;
     RN50_LAUNCH("bn_bwd_finalize", bn_bwd_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, partial, nrows, wide, kBnReducedRows, d->C, dgamma, dbeta);
   }
-#define RN50_BWD_APPLY_K(DZ2, ZK, FIN)                                                                             \
-  RN50_LAUNCH("bn_bwd_apply", (bn_bwd_apply_kernel<T, DZ2, ZK, FIN, LAST && ZK != 1>), dim3(ga.nblk, ga.gy), dim3(256), 0, s,       \
+#define RN50_BWD_APPLY_T(DZ2, ZK, FIN, THROUGH)                                                                           \
+  RN50_LAUNCH("bn_bwd_apply", (bn_bwd_apply_kernel<T, DZ2, ZK, FIN, LAST && ZK != 1, THROUGH>), dim3(ga.nblk, ga.gy), dim3(256), 0, s,       \
               static_cast<const T*>(dz), static_cast<const T*>(dz2), static_cast<const T*>(x),                     \
               static_cast<const T*>(z), zmask, gamma, beta, mean, rstd, dgamma, dbeta, static_cast<T*>(dx),        \
-              static_cast<T*>(dres), m, d->C, ga.tx_log2, ga.rpb, d->mode, fin)
+              static_cast<T*>(dres), m, d->C, ga.tx_log2, ga.rpb, d->mode, through, fin)
+#define RN50_BWD_APPLY_K(DZ2, ZK, FIN)                                                    \
+  do {                                                                           \
+    if (through) RN50_BWD_APPLY_T(DZ2, ZK, FIN, true); else RN50_BWD_APPLY_T(DZ2, ZK, FIN, false); \
+  } while (0)
 #define RN50_BWD_APPLY(DZ2, ZK)                                                  \
   do {                                                                           \
     if (self) RN50_BWD_APPLY_K(DZ2, ZK, true); else RN50_BWD_APPLY_K(DZ2, ZK, false); \
@@ -878,6 +888,7 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
   }
 #undef RN50_BWD_APPLY
 #undef RN50_BWD_APPLY_K
+#undef RN50_BWD_APPLY_T
 }
 
 template <typename T, bool LAST>
@@ -933,9 +944,9 @@ static void infer_run(const rn50_bn_desc* d, const void* x, const float* gamma, 
                      running_var, d->eps, d->C, rstd_scratch);
   const BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnApplyGroups);
   if (d->dtype == RN50_BF16)
-    RN50_LAUNCH("bn_apply", (bn_apply_kernel<uint16_t, false, false>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const uint16_t*>(x), gamma, beta, running_mean, rstd_scratch, static_cast<const uint16_t*>(residual), static_cast<uint16_t*>(y), static_cast<uint8_t*>(nullptr), m, d->C, ga.tx_log2, ga.rpb, d->mode, BnFinArgs{});
+    RN50_LAUNCH("bn_apply", (bn_apply_kernel<uint16_t, false, false, false>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const uint16_t*>(x), gamma, beta, running_mean, rstd_scratch, static_cast<const uint16_t*>(residual), static_cast<uint16_t*>(y), static_cast<uint8_t*>(nullptr), m, d->C, ga.tx_log2, ga.rpb, d->mode, 0, BnFinArgs{});
   else
-    RN50_LAUNCH("bn_apply", (bn_apply_kernel<float, false, false>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const float*>(x), gamma, beta, running_mean, rstd_scratch, static_cast<const float*>(residual), static_cast<float*>(y), static_cast<uint8_t*>(nullptr), m, d->C, ga.tx_log2, ga.rpb, d->mode, BnFinArgs{});
+    RN50_LAUNCH("bn_apply", (bn_apply_kernel<float, false, false, false>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const float*>(x), gamma, beta, running_mean, rstd_scratch, static_cast<const float*>(residual), static_cast<float*>(y), static_cast<uint8_t*>(nullptr), m, d->C, ga.tx_log2, ga.rpb, d->mode, 0, BnFinArgs{});
 }
 
 template <typename T, bool LAST>

@@ -55,6 +55,7 @@ struct IgemmArgs {
   const void* act;  // gathered activation tensor [N][H][W] pixels of PS elements
   const void* wgt;  // B: [Ncols][Ktot]
   void* out;        // C: [M][Ncols]
+  int out_through;  // writes_through of its bytes
   uint32_t act_bytes, wgt_bytes;
   int M, Ncols, Ktot;
   int H, W;         // spatial size of the gathered tensor
@@ -168,7 +169,7 @@ constexpr int igemm_ks_ring() {
 // the fragment registers, by a per-lane bit mask computed once.  The weights go through a ring of three
 // BN-row tiles, two taps ahead; the next chunk's run is loaded one pass per tap while the
 // current one is in use, so that every step issues the same number of loads (the load waits count them).
-template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN = false, bool BNIN = false, bool HALO = false>
+template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN, bool BNIN, bool HALO, bool THROUGH>
 __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kernel(const IgemmArgs a) {
   static_assert(!BNIN || (LIN && MODE == 0), "the input-side BN is compiled for the linear forward kernel only");
   static_assert(!HALO || (!LIN && !BNIN), "the halo main loop is a kernel of its own");
@@ -313,12 +314,13 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       const int row = orow + pass * RPP;
       if (m0 + row < Mc && col_ok) {
         const bool right = pix_s[row] & (1 << 29), below = pix_s[row] & (1 << 30);
-        const uint4 zero = make_uint4(0, 0, 0, 0);
-        T* const at = static_cast<T*>(a.out) + (static_cast<int64_t>(pixel(row)) * a.Ncols + n);
-        const int64_t next_row = static_cast<int64_t>(a.Q) * a.Ncols;
-        if (right) *reinterpret_cast<uint4*>(at + a.Ncols) = zero;
-        if (below) *reinterpret_cast<uint4*>(at + next_row) = zero;
-        if (right && below) *reinterpret_cast<uint4*>(at + next_row + a.Ncols) = zero;
+        Vec16 zero;
+        zero.u = make_uint4(0, 0, 0, 0);
+        const OutTensor<T, THROUGH> out(static_cast<T*>(a.out), a.out_through);
+        const int64_t at = static_cast<int64_t>(pixel(row)) * a.Ncols + n, next_row = static_cast<int64_t>(a.Q) * a.Ncols;
+        if (right) out.store(at + a.Ncols, zero);
+        if (below) out.store(at + next_row, zero);
+        if (right && below) out.store(at + next_row + a.Ncols, zero);
       }
     }
   }
@@ -710,7 +712,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     prm_s[tid] = sc; prm_s[BN + tid] = bi; prm_s[2 * BN + tid] = pr; prm_s[3 * BN + tid] = -pm * pr;
   }
   __syncthreads();
-  T* out = static_cast<T*>(a.out);
+  const OutTensor<T, THROUGH> out(static_cast<T*>(a.out), a.out_through);
   if constexpr (AFF) {
     if (a.addend != nullptr) {
 #pragma unroll
@@ -727,7 +729,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
           }
           Vec16 o;
           Elem<T>::pack(t, o);
-          store16(out + (static_cast<int64_t>(m) * a.Ncols + n), o);
+          out.store(static_cast<int64_t>(m) * a.Ncols + n, o);
         }
       }
       return;
@@ -740,8 +742,9 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       const int m = m0 + row;
       if (m < Mc && n < a.Ncols) {
         const int pix = classes ? pixel(row) : m;
-        *reinterpret_cast<uint4*>(out + (static_cast<int64_t>(pix) * a.Ncols + n)) =
-            *reinterpret_cast<const uint4*>(smem + row * CP + op * 16);
+        Vec16 v;
+        v.u = *reinterpret_cast<const uint4*>(smem + row * CP + op * 16);
+        out.store(static_cast<int64_t>(pix) * a.Ncols + n, v);
       }
     }
     return;
@@ -763,7 +766,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       if (m < Mc && col_ok) {
         Vec16 v;
         v.u = *reinterpret_cast<const uint4*>(smem + row * CP + op * 16);
-        *reinterpret_cast<uint4*>(out + (static_cast<int64_t>(m) * a.Ncols + n)) = v.u;
+        out.store(static_cast<int64_t>(m) * a.Ncols + n, v);
         float f[V];
         Elem<T>::unpack(v, f);
 #pragma unroll
@@ -811,7 +814,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
           v.u = *reinterpret_cast<const uint4*>(smem + row * CP + op * 16);
         }
         const int pix = classes ? pixel(row) : m0 + row;
-        *reinterpret_cast<uint4*>(out + (static_cast<int64_t>(pix) * a.Ncols + n)) = v.u;
+        out.store(static_cast<int64_t>(pix) * a.Ncols + n, v);
         Elem<T>::unpack(v, g);  // the sums range over the stored (rounded) values
         Elem<T>::unpack(xv[pass], xf);
 #pragma unroll
@@ -891,8 +894,8 @@ __global__ __launch_bounds__(256) void stem_pad_weight_kernel(const T* __restric
   wp[i] = (c < 3 && s < 7 && r < 7) ? w[((k * 7 + r) * 7 + s) * 3 + c] : static_cast<T>(0);
 }
 // ------------------------------------------------------------------ host side
-template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN, bool BNIN = false>
-static void launch_igemm_mode(IgemmArgs a, const char* tag, int64_t grid, hipStream_t s) {
+template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN, bool BNIN, bool THROUGH>
+static void launch_igemm_through(IgemmArgs a, const char* tag, int64_t grid, hipStream_t s) {
   constexpr bool KS = WM * WN == 1;
   constexpr int NT = KS ? 256 : 64 * WM * WN;
   constexpr int stage = (BM + BN) * 128 * (KS ? 4 : 1);  // (KS: every wave has a ring)
@@ -908,7 +911,7 @@ static void launch_igemm_mode(IgemmArgs a, const char* tag, int64_t grid, hipStr
   // input-side BN coefficients: two floats per channel, at most 4096 channels (KS: 2048)
   constexpr int kInTabMax = 8 * (KS ? 2048 : 4096);
   std::call_once(once, [] {
-    allow_big_lds(igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN>,
+    allow_big_lds(igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN, false, THROUGH>,
                   (nring * stage > out_need ? nring * stage : out_need) + (BNIN ? kInTabMax : 0));
   });
   // A short reduction never touches the later ring buffers; without them more workgroups fit a CU (the 1x1
@@ -920,7 +923,17 @@ static void launch_igemm_mode(IgemmArgs a, const char* tag, int64_t grid, hipStr
     a.in_lds = lds;
     lds += 8 * a.R * a.S * a.cpt * (128 / es);
   }
-  RN50_LAUNCH(tag, (igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN>), dim3(static_cast<unsigned>(grid)), dim3(NT), lds, s, a);
+  RN50_LAUNCH(tag, (igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN, false, THROUGH>), dim3(static_cast<unsigned>(grid)), dim3(NT), lds, s, a);
+}
+// (written through: bf16 tiles of the shared ring; the K split's tensors are small)
+template <typename T, int WM, int WN>
+constexpr bool igemm_may_write_through() { return sizeof(T) == 2 && WM * WN > 1; }
+template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN, bool BNIN = false>
+static void launch_igemm_mode(const IgemmArgs& a, const char* tag, int64_t grid, hipStream_t s) {
+  if constexpr (igemm_may_write_through<T, WM, WN>() && !BNIN) {
+    if (a.out_through) return launch_igemm_through<T, BM, BN, WM, WN, MODE, LIN, BNIN, true>(a, tag, grid, s);
+  }
+  launch_igemm_through<T, BM, BN, WM, WN, MODE, LIN, BNIN, false>(a, tag, grid, s);
 }
 // The halo kernel (3x3, stride 1, padding 1): LDS bytes of its main loop for an image width, or 0 when the shape
 // does not fit it (a run of more than 8 load passes, more LDS than a compute unit has).
@@ -934,17 +947,24 @@ static int halo_lds_bytes(int W, int cpt) {
   const int bytes = (cpt > 1 ? 2 : 1) * passes * RPL * 128 + 3 * BN * 128 + NW * 1024;
   return bytes <= kHaloLdsMax ? bytes : 0;
 }
-template <typename T, int BM, int BN, int WM, int WN, int MODE>
-static void launch_igemm_halo(IgemmArgs a, const char* tag, int64_t grid, int main_lds, hipStream_t s) {
+template <typename T, int BM, int BN, int WM, int WN, int MODE, bool THROUGH>
+static void launch_igemm_halo_through(IgemmArgs a, const char* tag, int64_t grid, int main_lds, hipStream_t s) {
   constexpr int NT = 64 * WM * WN;
   constexpr int es = static_cast<int>(sizeof(T));
   constexpr int out_tile = BM * (BN * 4 + 16);
   constexpr int col_sums = (NT / (BN * es / 16)) * 2 * BN * 4;
   constexpr int out_need = out_tile > col_sums ? out_tile : col_sums;
   static std::once_flag once;
-  std::call_once(once, [] { allow_big_lds(igemm_kernel<T, BM, BN, WM, WN, MODE, false, false, true>, kHaloLdsMax); });
+  std::call_once(once, [] { allow_big_lds(igemm_kernel<T, BM, BN, WM, WN, MODE, false, false, true, THROUGH>, kHaloLdsMax); });
   const int lds = main_lds > out_need ? main_lds : out_need;
-  RN50_LAUNCH(tag, (igemm_kernel<T, BM, BN, WM, WN, MODE, false, false, true>), dim3(static_cast<unsigned>(grid)), dim3(NT), lds, s, a);
+  RN50_LAUNCH(tag, (igemm_kernel<T, BM, BN, WM, WN, MODE, false, false, true, THROUGH>), dim3(static_cast<unsigned>(grid)), dim3(NT), lds, s, a);
+}
+template <typename T, int BM, int BN, int WM, int WN, int MODE>
+static void launch_igemm_halo(const IgemmArgs& a, const char* tag, int64_t grid, int main_lds, hipStream_t s) {
+  if constexpr (igemm_may_write_through<T, WM, WN>()) {
+    if (a.out_through) return launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, true>(a, tag, grid, main_lds, s);
+  }
+  launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, false>(a, tag, grid, main_lds, s);
 }
 template <typename T, int BM, int BN, int WM, int WN>
 static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
@@ -956,6 +976,7 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
   a.fill = classes && a.R == 1 && a.S == 1 && a.partial == nullptr;
   a.mtiles = static_cast<int>(classes ? (a.fill ? 1 : 4) * tiles_per_class : ceil_div(a.M, BM));
   const int64_t grid = static_cast<int64_t>(a.mtiles) * a.ntn;
+  a.out_through = writes_through(static_cast<int64_t>(a.M) * a.Ncols * sizeof(T));
   a.partial_wide = bn_self_finalizes(a.mtiles, false);
   a.div_ntn = make_fastdiv(a.ntn);
   a.linear = a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0 && !a.pair && a.H == a.P && a.W == a.Q;

@@ -29,11 +29,6 @@ __device__ __forceinline__ Vec16 bn_relu_vector(const Vec16& v, const float* sca
 }
 constexpr uint32_t kOob = 0x80000000u;  // buffer offset beyond every tensor: the load returns zeros
 
-// Raw buffer descriptor over a tensor: loads whose offset is >= bytes return 0, which is how padding,
-// tile tails and ragged channel counts are zero-filled without any per-element masking.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, static_cast<int>(bytes), 0x00020000);
-}
 __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t voffset, uint32_t soffset) {
   typedef int v4i __attribute__((ext_vector_type(4)));
   const v4i v = __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(voffset), static_cast<int>(soffset), 0);

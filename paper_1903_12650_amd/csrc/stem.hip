@@ -25,6 +25,7 @@ struct StemArgs {
   const void* xp;      // [N][Hp][pitch bytes]
   const uint16_t* w;   // [Cout][7][7][3]
   uint16_t* y;         // [N*P*Q][Cout]
+  int y_through;       // writes_through of its bytes
   uint32_t xp_bytes;
   int Cout, Hp, pitch, P, Q;
   int rows;            // output rows per tile, 1 or 2 (a divisor of P)
@@ -41,13 +42,14 @@ struct StemArgs {
   int relu;
 };
 
-template <bool AFF>
+template <bool AFF, bool THROUGH>
 __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const StemArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double sums[4][2][64];                 // per wave: sums of the values and of their squares
   __shared__ __align__(16) float prm[AFF ? 128 : 4];  // scale, bias
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
   unsigned char* const stage = smem + 2 * a.patch_lds + wave * kStemStage;
+  const OutTensor<uint16_t, THROUGH> out(a.y, a.y_through);
   const int tile0 = blockIdx.x * a.per_wg, tile1 = min(tile0 + a.per_wg, a.tiles);
 
   // The weights as [channel][row][tap][4 channels] in LDS (over the image buffers, which are not in use yet), then this
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(256, 2) void stem_fwd_kernel(const StemArgs a) {
       for (int p = 0; p < 4; ++p) {
         const int r = orow + p * 8;
         if (r < live && col_ok) {
-          store16(a.y + (m0 + blk * 32 + r) * a.Cout + op * 8, o[p]);
+          out.store((m0 + blk * 32 + r) * a.Cout + op * 8, o[p]);
           if (!AFF && a.partial) {
             float f[8];
             Elem<uint16_t>::unpack(o[p], f);
@@ -228,6 +230,7 @@ bool stem_fwd_run(const rn50_conv_desc* d, const void* xp, const void* w, void* 
   a.Cout = d->Cout; a.Hp = g.Hp; a.pitch = g.Wp * 8;
   a.P = out_dim(d->H, 3, 7, 2); a.Q = out_dim(d->W, 3, 7, 2);
   a.M = d->N * a.P * a.Q;
+  a.y_through = writes_through(static_cast<int64_t>(a.M) * d->Cout * 2);
   a.xp_bytes = static_cast<uint32_t>(static_cast<size_t>(d->N) * g.Hp * a.pitch);
   a.rows = p.rows; a.patch = p.patch; a.patch_lds = p.patch_lds; a.tiles = p.tiles; a.per_wg = p.per_wg;
   a.div_tpi = make_fastdiv(a.P / a.rows);
@@ -235,15 +238,19 @@ bool stem_fwd_run(const rn50_conv_desc* d, const void* xp, const void* w, void* 
   const int lds = std::max(2 * p.patch_lds + 4 * kStemStage, 64 * 448);
   static std::once_flag once;
   std::call_once(once, [] {
-    allow_big_lds(stem_fwd_kernel<false>, 76 * 1024);
-    allow_big_lds(stem_fwd_kernel<true>, 76 * 1024);
+    allow_big_lds(stem_fwd_kernel<false, false>, 76 * 1024);
+    allow_big_lds(stem_fwd_kernel<false, true>, 76 * 1024);
+    allow_big_lds(stem_fwd_kernel<true, false>, 76 * 1024);
+    allow_big_lds(stem_fwd_kernel<true, true>, 76 * 1024);
   });
   if (affine) {
     a.gamma = affine->gamma; a.beta = affine->beta; a.mean = affine->mean; a.var = affine->var;
     a.eps = affine->eps; a.relu = affine->relu;
-    RN50_LAUNCH("conv_fwd", stem_fwd_kernel<true>, dim3(p.grid), dim3(256), lds, s, a);
+    if (a.y_through) RN50_LAUNCH("conv_fwd", (stem_fwd_kernel<true, true>), dim3(p.grid), dim3(256), lds, s, a);
+    else RN50_LAUNCH("conv_fwd", (stem_fwd_kernel<true, false>), dim3(p.grid), dim3(256), lds, s, a);
   } else {
-    RN50_LAUNCH("conv_fwd", stem_fwd_kernel<false>, dim3(p.grid), dim3(256), lds, s, a);
+    if (a.y_through) RN50_LAUNCH("conv_fwd", (stem_fwd_kernel<false, true>), dim3(p.grid), dim3(256), lds, s, a);
+    else RN50_LAUNCH("conv_fwd", (stem_fwd_kernel<false, false>), dim3(p.grid), dim3(256), lds, s, a);
   }
   return true;
 }

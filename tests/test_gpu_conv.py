@@ -248,6 +248,30 @@ def test_strided_1x1_data_gradient_stores_every_pixel(rn, mode_name, N, H, W, C,
     assert torch.equal(dx == 0, want == 0)
 
 
+@pytest.mark.parametrize("N,H,W,C,K,R,stride", [(3, 120, 123, 64, 136, 1, 1), (3, 120, 123, 72, 136, 3, 1), (3, 241, 239, 16, 136, 3, 2),
+                                                (1, 200, 210, 8, 264, 1, 1), (2, 56, 57, 256, 840, 1, 1), (7, 224, 220, 3, 64, 7, 2)])
+def test_outputs_written_through(rn, N, H, W, C, K, R, stride):
+    """bf16 outputs of 10.1 to 22 MB: ragged rows and columns of every store path (plain, halo, strided, the stem), forward with
+    and without sums, the data gradient with the same sizes in the other direction; into buffers of NaNs."""
+    gen = torch.Generator().manual_seed(H + K)
+    pad = R // 2
+    x = torch.randn(N, H, W, C, generator=gen).bfloat16()
+    w = (torch.randn(K, R, R, C, generator=gen) / (R * R * C) ** 0.5).bfloat16()
+    want = torch.nn.functional.conv2d(x.permute(0, 3, 1, 2).double(), w.permute(0, 3, 1, 2).double(), stride=stride, padding=pad)
+    want = want.permute(0, 2, 3, 1).contiguous().numpy()
+    assert 2 * want.size >= 10 << 20
+    y = torch.full(want.shape, float("nan"), device="cuda", dtype=torch.bfloat16)
+    rn.conv_fwd(x.cuda(), w.cuda(), stride, pad, y=y)
+    assert_close(y, want, TOL["bf16"], "y")
+    y2, _ = rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), stride, pad)
+    assert torch.equal(y, y2)
+    if stride == 1:
+        wt = w.flip(1, 2).permute(3, 1, 2, 0).contiguous()  # the same convolution as a data gradient
+        dx = torch.full(want.shape, float("nan"), device="cuda", dtype=torch.bfloat16)
+        rn.conv_dgrad(x.cuda(), wt.cuda(), want.shape, 1, pad, dx=dx)
+        assert_close(dx, want, TOL["bf16"], "dx")
+
+
 # Weight gradient: tiles that span filter taps, channel counts at the edges of the tile widths, pixel ranges of less than one
 # chunk, one chunk more than a whole number of splits, and the most splits.
 WGRAD_EDGES = [(1, 3, 3, 40, 64, 3, 1, 1), (2, 8, 8, 64, 72, 1, 1, 0), (2, 8, 8, 72, 64, 1, 1, 0), (1, 1, 1, 128, 128, 3, 1, 1),
