@@ -152,17 +152,21 @@ __device__ __forceinline__ void store16(T* p, const Vec16& v) {
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, static_cast<int>(bytes), 0x00020000);
 }
-// A large output is written through the L2 caches.  What a kernel leaves dirty in the eight of them (4 MB each) is written back
-// at its end, before the next kernel on the chain may start; written through, the tensor goes to memory while the kernel runs
-// and is found clean.  Below kThroughBytes the stores' longer way costs as much.  The step with every output of the
-// convolutions and of the batch-norm passes written through from 0 / 5 / 10 / 20 / 40 MB on against none: batch 12 +0.6 / +0.2 /
-// +0.3 / -0.5 / -0.3 %, batch 40 -1.2 / -1.3 / -1.1 / -0.7 / -0.5 %, batch 256 -1.4 / -1.4 / -1.4 / -1.5 / -1.5 %.  (Stores past the
-// caches: batch 256 -1.4 %, but batch 40 +3 %, whose next kernel finds nothing.)  Call by call: the forward convolutions at batch
-// 40 415 -> 407 us, the data gradients 436 -> 416, evaluation at batch 256 4.54 -> 4.46 ms.
-constexpr int64_t kThroughBytes = 10 << 20;
-inline int writes_through(int64_t bytes) { return bytes >= kThroughBytes && bytes < (1ll << 31) ? static_cast<int>(bytes) : 0; }
+// Outputs that are written through the L2 caches.  What a kernel leaves dirty in the eight of them (4 MB each) is written back
+// at its end, before the next kernel on the chain may start; written through, it goes to memory while the kernel runs and is
+// found clean.  Against ordinary stores (and with stores past the caches batch 256 gains as much, but batch 40 loses 3 %: the
+// next kernel finds nothing):
+//  - partial sums and results of the weight gradients, always (whole tiles): 23 shapes at batch 8 259 -> 242 us, batch 40 560 -> 547,
+//    batch 128 1178 -> 1160, float at batch 8 531 -> 502;
+//  - the convolutions' outputs from 1 MB on: forward / data gradients at batch 12 215 / 219 -> 214 / 212 us, batch 40 409 / 423 -> 401 /
+//    410, float at batch 8 525 / 531 -> 514 / 519 (from 0, 3, 6 MB on: within 1 % of this);
+//  - the batch-norm apply passes' outputs from 10 MB on: the step at batch 256 -0.5 %; from 0 or 2 MB on batch 33 is 0.6 to 3 % slower.
+constexpr int64_t kConvThroughBytes = 1 << 20, kThroughBytes = 10 << 20;
+inline int through_bytes(int64_t bytes) { return bytes < (1ll << 31) ? static_cast<int>(bytes) : 0; }
+inline int writes_through(int64_t bytes, int64_t from = kThroughBytes) { return bytes >= from ? through_bytes(bytes) : 0; }
 // An output tensor, written through (of `bytes` bytes) or not.  Compiled in: with the choice at every store the output stages'
 // stores and the LDS reads behind them no longer overlap, which costs what the writing through gains.
+constexpr int kSystemScope = 1 | 16;  // cache policy bits sc0, sc1
 template <typename T, bool THROUGH>
 struct OutTensor {
   T* p;
@@ -170,7 +174,6 @@ struct OutTensor {
   __device__ __forceinline__ OutTensor(T* p_, int bytes) : p(p_), r(make_rsrc(p_, THROUGH ? bytes : 0)) {}
   __device__ __forceinline__ void store(int64_t at, const Vec16& v) const {
     typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-    constexpr int kSystemScope = 1 | 16;  // cache policy bits sc0, sc1
     if constexpr (THROUGH) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v.u), r, static_cast<int>(static_cast<uint32_t>(at) * sizeof(T)), 0, kSystemScope);
     else store16(p + at, v);
   }

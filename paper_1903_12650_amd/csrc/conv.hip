@@ -925,15 +925,10 @@ static void launch_igemm_through(IgemmArgs a, const char* tag, int64_t grid, hip
   }
   RN50_LAUNCH(tag, (igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN, false, THROUGH>), dim3(static_cast<unsigned>(grid)), dim3(NT), lds, s, a);
 }
-// (written through: bf16 tiles of the shared ring; the K split's tensors are small)
-template <typename T, int WM, int WN>
-constexpr bool igemm_may_write_through() { return sizeof(T) == 2 && WM * WN > 1; }
 template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN, bool BNIN = false>
 static void launch_igemm_mode(const IgemmArgs& a, const char* tag, int64_t grid, hipStream_t s) {
-  if constexpr (igemm_may_write_through<T, WM, WN>() && !BNIN) {
-    if (a.out_through) return launch_igemm_through<T, BM, BN, WM, WN, MODE, LIN, BNIN, true>(a, tag, grid, s);
-  }
-  launch_igemm_through<T, BM, BN, WM, WN, MODE, LIN, BNIN, false>(a, tag, grid, s);
+  if (a.out_through) launch_igemm_through<T, BM, BN, WM, WN, MODE, LIN, BNIN, true>(a, tag, grid, s);
+  else launch_igemm_through<T, BM, BN, WM, WN, MODE, LIN, BNIN, false>(a, tag, grid, s);
 }
 // The halo kernel (3x3, stride 1, padding 1): LDS bytes of its main loop for an image width, or 0 when the shape
 // does not fit it (a run of more than 8 load passes, more LDS than a compute unit has).
@@ -961,10 +956,8 @@ static void launch_igemm_halo_through(IgemmArgs a, const char* tag, int64_t grid
 }
 template <typename T, int BM, int BN, int WM, int WN, int MODE>
 static void launch_igemm_halo(const IgemmArgs& a, const char* tag, int64_t grid, int main_lds, hipStream_t s) {
-  if constexpr (igemm_may_write_through<T, WM, WN>()) {
-    if (a.out_through) return launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, true>(a, tag, grid, main_lds, s);
-  }
-  launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, false>(a, tag, grid, main_lds, s);
+  if (a.out_through) launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, true>(a, tag, grid, main_lds, s);
+  else launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, false>(a, tag, grid, main_lds, s);
 }
 template <typename T, int BM, int BN, int WM, int WN>
 static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
@@ -976,7 +969,7 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
   a.fill = classes && a.R == 1 && a.S == 1 && a.partial == nullptr;
   a.mtiles = static_cast<int>(classes ? (a.fill ? 1 : 4) * tiles_per_class : ceil_div(a.M, BM));
   const int64_t grid = static_cast<int64_t>(a.mtiles) * a.ntn;
-  a.out_through = writes_through(static_cast<int64_t>(a.M) * a.Ncols * sizeof(T));
+  a.out_through = writes_through(static_cast<int64_t>(a.M) * a.Ncols * sizeof(T), kConvThroughBytes);
   a.partial_wide = bn_self_finalizes(a.mtiles, false);
   a.div_ntn = make_fastdiv(a.ntn);
   a.linear = a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0 && !a.pair && a.H == a.P && a.W == a.Q;

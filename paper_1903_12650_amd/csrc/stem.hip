@@ -230,7 +230,7 @@ bool stem_fwd_run(const rn50_conv_desc* d, const void* xp, const void* w, void* 
   a.Cout = d->Cout; a.Hp = g.Hp; a.pitch = g.Wp * 8;
   a.P = out_dim(d->H, 3, 7, 2); a.Q = out_dim(d->W, 3, 7, 2);
   a.M = d->N * a.P * a.Q;
-  a.y_through = writes_through(static_cast<int64_t>(a.M) * d->Cout * 2);
+  a.y_through = writes_through(static_cast<int64_t>(a.M) * d->Cout * 2, kConvThroughBytes);
   a.xp_bytes = static_cast<uint32_t>(static_cast<size_t>(d->N) * g.Hp * a.pitch);
   a.rows = p.rows; a.patch = p.patch; a.patch_lds = p.patch_lds; a.tiles = p.tiles; a.per_wg = p.per_wg;
   a.div_tpi = make_fastdiv(a.P / a.rows);

@@ -20,6 +20,7 @@ struct WgradArgs {
   const void* x;   // gathered activation tensor [N][H][W] pixels of PS elements
   const void* dy;  // [M][Cout]
   float* out;      // dw [Cout][Ktot], or split partials
+  int out_through;  // through_bytes of their bytes
   uint32_t x_bytes, dy_bytes;
   int M, Cout, Ktot;
   int H, W, P, Q, PS, Cg, R, S, stride, pad;
@@ -226,6 +227,22 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
   }
 
   // acc[i][j][v]: ko = i*32 + (v/4)*8 + (lane/32)*4 + v%4, k = j*32 + lane%32
+  if (a.out_through != 0 && ko0 + BMO <= a.Cout && k0 + BC <= a.Ktot) {
+    // a whole tile, written through: one offset per block and lane, the rows of the block by a scalar
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(a.out, a.out_through);
+    const uint32_t base = static_cast<uint32_t>(split * a.split_stride), pitch = static_cast<uint32_t>(a.Ktot) * 4u;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const uint32_t off = (base + static_cast<uint32_t>((ko0 + wm * (BMO / 2) + i * 32 + (lane >> 5) * 4) * a.Ktot + k0 + wn * (BC / 2) + j * 32 + (lane & 31))) * 4u;
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v]), r, static_cast<int>(off),
+                                                static_cast<int>(static_cast<uint32_t>((v >> 2) * 8 + (v & 3)) * pitch), kSystemScope);
+      }
+    return;
+  }
   float* out = a.out + static_cast<int64_t>(split) * a.split_stride;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -359,8 +376,19 @@ __global__ __launch_bounds__(256) void wgrad3x3_kernel(const WgradArgs a) {
   }
 
   // acc[tap][v]: ko = (v/4)*8 + (lane/32)*4 + v%4, c = lane%32 of this wave's 32x32 block
-  float* out = a.out + static_cast<int64_t>(split) * a.split_stride;
   const int c = wn * 32 + (lane & 31);
+  if (a.out_through != 0 && a.Cout == 64 && a.Cg == 64) {  // (as in wgrad_kernel)
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(a.out, a.out_through);
+    const uint32_t off = (static_cast<uint32_t>(split * a.split_stride) + static_cast<uint32_t>((wm * 32 + (lane >> 5) * 4) * a.Ktot + c)) * 4u;
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[tap][v]), r, static_cast<int>(off),
+                                              static_cast<int>(static_cast<uint32_t>(((v >> 2) * 8 + (v & 3)) * a.Ktot + tap * a.Cg) * 4u), kSystemScope);
+    return;
+  }
+  float* out = a.out + static_cast<int64_t>(split) * a.split_stride;
   if (c < a.Cg) {
 #pragma unroll
     for (int tap = 0; tap < 9; ++tap)
@@ -589,11 +617,13 @@ void wgrad_run(const rn50_conv_desc* d, const void* x_or_xp, const void* dy, flo
   if (const Wgrad3x3Plan p9 = plan_wgrad3x3(d); p9.nbx) {
     splits = p9.splits;
     a.out = splits > 1 ? partial : target;
+    a.out_through = through_bytes(4 * splits * a.split_stride);
     launch_wgrad3x3(a, p9, d->H, s);
   } else {
     const WgradPlan p = plan_wgrad(a, d->dtype);
     splits = p.splits;
     a.out = splits > 1 ? partial : target;
+    a.out_through = through_bytes(4 * splits * a.split_stride);
     a.ctiles = p.ctiles;
     a.rows_per_split = p.rows_per_split;
     a.tiles_per_split = p.ctiles * static_cast<int>(ceil_div(a.Cout, p.bmo));
