@@ -310,21 +310,36 @@ void bn_reduce_rows(float* sums, int nrows, int rpp, int64_t m, int C, bool back
   else RN50_LAUNCH("bn_finalize", bn_reduce_rows_kernel<false>, grid, dim3(256), 0, s, sums, nrows, per, rpp, m, out);
 }
 
-// Forward: rows of sums over rpp rows of x each (the last over what is left of m), with their shifts; or (wide not null) rows of
-// doubles: about zero (for a layer whose apply pass is left to its consumer), or reduced, about the shift of partial's first row.
-__global__ __launch_bounds__(kFinThreads) void bn_finalize_kernel(const float* __restrict__ partial, int nrows, int rpp,
-                                                           const double2* __restrict__ wide, int nwide, int64_t m, int C,
-                                                           float eps, float* __restrict__ mean_out,
-                                                           float* __restrict__ rstd_out, float* running_mean,
-                                                           float* running_var, float momentum) {
+// What a pass that finalizes statistics gets: the rows of sums and where the results go (backward: mean_out = dbeta, rstd_out =
+// dgamma).
+struct BnFinArgs {
+  const float* partial;
+  int nrows, rpp;      // tile rows, rows of x behind each
+  const double2* wide; // finalize launch and shared: rows of doubles instead (bn_reduced_rows, or about zero with partial null)
+  int nwide;
+  float eps, momentum;
+  float *mean_out, *rstd_out, *running_mean, *running_var;
+  // shared
+  unsigned long long* slots;  // per channel: the two results, or kBnSlotEmpty
+  int groups, polls;          // finalizing workgroups; how often the others ask for their results
+  int nblk;                   // applying workgroups per column slice
+};
+
+// Forward: mean and 1/std of kFinCh channels by the 256 threads of a workgroup, from rows of sums over rpp rows of x each (the last
+// over what is left of m), with their shifts; or (wide not null) rows of doubles: about zero (for a layer whose apply pass is left
+// to its consumer), or reduced, about the shift of partial's first row.  True in the threads that hold a channel's results;
+// `store`: they also go to memory.
+__device__ __forceinline__ bool finalize_channels_fwd(const BnFinArgs& f, int group, int64_t m, int C, bool store, float* mean_r,
+                                                      float* rstd_r) {
   constexpr int G = kFinThreads / kFinCh;
-  const int c = blockIdx.x * kFinCh + threadIdx.x % kFinCh;
-  const BnTileRow* p = reinterpret_cast<const BnTileRow*>(partial) + bn_sums_at(0, c, nrows);  // (the last piece of C is padded)
-  const double k0 = partial ? static_cast<double>(p[0].k) : 0.0;
+  const int c = group * kFinCh + threadIdx.x % kFinCh;
+  int nrows = f.nrows;
+  const BnTileRow* p = reinterpret_cast<const BnTileRow*>(f.partial) + bn_sums_at(0, c, nrows);  // (the last piece of C is padded)
+  const double k0 = f.partial ? static_cast<double>(p[0].k) : 0.0;
   double s1 = 0.0, s2 = 0.0;
-  if (wide) {
-    const double2* pd = wide + bn_sums_at(0, c, nwide);
-    for (int b = threadIdx.x / kFinCh; b < nwide; b += G) {
+  if (f.wide) {
+    const double2* pd = f.wide + bn_sums_at(0, c, f.nwide);
+    for (int b = threadIdx.x / kFinCh; b < f.nwide; b += G) {
       s1 += pd[b * 8].x;
       s2 += pd[b * 8].y;
     }
@@ -336,27 +351,120 @@ __global__ __launch_bounds__(kFinThreads) void bn_finalize_kernel(const float* _
     for (int u = 0; u < kFinRows; ++u) v[u] = p[min(b + u * G, nrows - 1) * 8];
 #pragma unroll
     for (int u = 0; u < kFinRows; ++u)
-      if (b + u * G < nrows) add_tile_row(v[u], rows_of(b + u * G, nrows, rpp, m), k0, &s1, &s2);
+      if (b + u * G < nrows) add_tile_row(v[u], rows_of(b + u * G, nrows, f.rpp, m), k0, &s1, &s2);
   }
   finalize_combine(&s1, &s2);
-  if (threadIdx.x >= kFinCh || c >= C) return;
+  if (threadIdx.x >= kFinCh || c >= C) return false;
   const double d = s1 / static_cast<double>(m), mean = k0 + d;
   double var = s2 / static_cast<double>(m) - d * d;
   if (var < 0.0) var = 0.0;
-  mean_out[c] = static_cast<float>(mean);
-  rstd_out[c] = static_cast<float>(1.0 / sqrt(var + static_cast<double>(eps)));
-  if (running_mean) running_mean[c] = momentum * running_mean[c] + (1.f - momentum) * static_cast<float>(mean);
-  if (running_var) running_var[c] = momentum * running_var[c] + (1.f - momentum) * static_cast<float>(var);
+  *mean_r = static_cast<float>(mean);
+  *rstd_r = static_cast<float>(1.0 / sqrt(var + static_cast<double>(f.eps)));
+  if (store) {
+    f.mean_out[c] = *mean_r;
+    f.rstd_out[c] = *rstd_r;
+    if (f.running_mean) f.running_mean[c] = f.momentum * f.running_mean[c] + (1.f - f.momentum) * static_cast<float>(mean);
+    if (f.running_var) f.running_var[c] = f.momentum * f.running_var[c] + (1.f - f.momentum) * static_cast<float>(var);
+  }
+  return true;
+}
+// Backward: (dbeta, dgamma) likewise.
+__device__ __forceinline__ bool finalize_channels_bwd(const BnFinArgs& f, int group, int C, bool store, float* dbeta_r,
+                                                      float* dgamma_r) {
+  constexpr int G = kFinThreads / kFinCh;
+  const int c = group * kFinCh + threadIdx.x % kFinCh;
+  int nrows = f.nrows;
+  const float2* p = reinterpret_cast<const float2*>(f.partial) + bn_sums_at(0, c, nrows);
+  double s1 = 0.0, s2 = 0.0;
+  if (f.wide) {
+    const double2* pd = f.wide + bn_sums_at(0, c, f.nwide);
+    for (int b = threadIdx.x / kFinCh; b < f.nwide; b += G) {
+      s1 += pd[b * 8].x;
+      s2 += pd[b * 8].y;
+    }
+    nrows = 0;
+  }
+  for (int b = threadIdx.x / kFinCh; b < nrows; b += kFinRows * G) {
+    float2 v[kFinRows];
+#pragma unroll
+    for (int u = 0; u < kFinRows; ++u) v[u] = p[min(b + u * G, nrows - 1) * 8];
+#pragma unroll
+    for (int u = 0; u < kFinRows; ++u) {
+      if (b + u * G < nrows) {
+        s1 += static_cast<double>(v[u].x);
+        s2 += static_cast<double>(v[u].y);
+      }
+    }
+  }
+  finalize_combine(&s1, &s2);
+  if (threadIdx.x >= kFinCh || c >= C) return false;
+  *dbeta_r = static_cast<float>(s1);
+  *dgamma_r = static_cast<float>(s2);
+  if (store) {
+    f.mean_out[c] = *dbeta_r;
+    f.rstd_out[c] = *dgamma_r;
+  }
+  return true;
+}
+template <bool BWD>
+__device__ __forceinline__ bool finalize_channels(const BnFinArgs& f, int group, int64_t m, int C, bool store, float* a, float* b) {
+  return BWD ? finalize_channels_bwd(f, group, C, store, a, b) : finalize_channels_fwd(f, group, m, C, store, a, b);
+}
+template <bool BWD>
+__global__ __launch_bounds__(kFinThreads) void bn_finalize_kernel(int64_t m, int C, const BnFinArgs f) {
+  float a, b;
+  finalize_channels<BWD>(f, blockIdx.x, m, C, true, &a, &b);
 }
 
-// What a pass that finalizes its own statistics gets on top of the apply pass's arguments (FIN kernels below):
-// the rows of sums and where the results go (backward: mean_out = dbeta, rstd_out = dgamma).
-struct BnFinArgs {
-  const float* partial;
-  int nrows;  // tile rows
-  float eps, momentum;
-  float *mean_out, *rstd_out, *running_mean, *running_var;
-};
+// Where an apply pass has its statistics from.  kFinGiven: from memory, a finalize launch has stored them.  kFinSelf: every
+// workgroup adds up the tile rows of its channels.  kFinShared: the first `groups` workgroups of the same launch finalize, two
+// channels each, and publish the two results of a channel as one 64-bit word; the others request their rows of x and then ask
+// for the words of their channels.  Two launches in one, for grids of at most kBnShareGroups workgroups: 11 to 13 us for 4.6 to 5.5 +
+// 1.5 (between them) + 7 at 56x56, batch 40; the step at batch 12 2.518 -> 2.477 ms, batch 24 3.415 -> 3.359, batch 33 (208 px) 3.711 ->
+// 3.651, batch 40 4.339 -> 4.296.  In larger grids most workgroups start when the results are long there, and asking past the caches
+// costs each what a look into them does not (without a limit batch 90 and float at batch 8 lost 0.5 %).  kFinSelf stays for its
+// few rows: with kFinShared in its place (from 0 / 40 / 64 rows on) batch 12 loses 2.3 / 0.2 / 0.2 %.
+// The word is the message: relaxed atomics at device scope, nothing else is passed by memory within the launch.  It is made empty
+// by the convolution that produces the sums (IgemmArgs::slots).  No progress is assumed of the finalizing workgroups: after
+// `polls` unanswered questions a workgroup computes what it needs itself, in the same order, so every wait ends and the results
+// do not depend on who computed them.
+constexpr int kBnShareGroups = 2048;  // eight per compute unit: all there at once
+enum BnFin { kFinGiven, kFinSelf, kFinShared };
+__device__ __forceinline__ void publish_results(unsigned long long* slot, float a, float b) {
+  unsigned long long v = static_cast<unsigned long long>(__float_as_uint(b)) << 32 | __float_as_uint(a);
+  if (v == kBnSlotEmpty) v = 0x7fc000007fc00000ull;  // (two NaNs)
+  __hip_atomic_store(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The results of the `width` channels (at most 256) from c0 on into LDS; ends with a barrier.
+template <bool BWD>
+__device__ __forceinline__ void await_results(const BnFinArgs& f, int64_t m, int C, int c0, int width, float* a_s, float* b_s) {
+  const int tid = threadIdx.x;
+  bool missing = false;
+  if (tid < width && c0 + tid < C) {
+    missing = true;
+    for (int i = 0; i < f.polls && missing; ++i) {
+      const unsigned long long v = __hip_atomic_load(f.slots + c0 + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (v != kBnSlotEmpty) {
+        a_s[tid] = __uint_as_float(static_cast<uint32_t>(v));
+        b_s[tid] = __uint_as_float(static_cast<uint32_t>(v >> 32));
+        missing = false;
+      } else {
+        __builtin_amdgcn_s_sleep(2);
+      }
+    }
+  }
+  if (__syncthreads_or(missing)) {
+    for (int i = 0; i < width && c0 + i < C; i += kFinCh) {
+      float a, b;
+      if (finalize_channels<BWD>(f, (c0 + i) / kFinCh, m, C, false, &a, &b)) {
+        a_s[i + tid] = a;
+        b_s[i + tid] = b;
+      }
+      __syncthreads();  // (before the next ones use the same LDS)
+    }
+  }
+}
+
 // Forward statistics of the CS channels from c0 on, by all 256 threads of a workgroup, into mean_s / rstd_s (LDS).
 // Thread (channel ch, part p) adds tile rows p, p + P, ... in order, the P parts
 // are added in order: a fixed order, the same in every workgroup that computes these channels.  Ends with a barrier.
@@ -407,16 +515,16 @@ __device__ __forceinline__ void finalize_slice_fwd(const BnFinArgs& f, int64_t m
   __syncthreads();
 }
 
-// FIN: the pass takes its statistics from the per-tile sums itself (fin), every workgroup for the 8
-// vector columns it applies (tx_log2 = 3), and the first row block of every column slice stores them: no
-// finalize launch in front.  For layers with few tile rows the redundant reads of the sums are far cheaper than a
-// launch on the step's dependency chain (about 4 us whatever it computes).
+// FIN: where the statistics come from (BnFin).  kFinSelf: every workgroup for the 8 vector columns it applies (tx_log2 = 3), and
+// the first row block of every column slice stores them: no finalize launch in front.  For layers with few tile rows the redundant
+// reads of the sums are far cheaper than a launch on the step's dependency chain (about 4 us whatever it computes).  kFinShared: a
+// one-dimensional grid.
 // LAST (apply passes of both directions): nobody reads the operands again for a long while, as in a training step, where the
 // next layers are larger than the caches: their loads bypass the caches, which keep what the next kernel reads -- the output,
 // the weight gradient's operands.  Whole step: batch 40 4.506 -> 4.457 ms, batch 256 20.90 -> 20.55 (stores past the caches
 // made batch 40 slower).  Not for the calls of one operation, whose next one may read the same tensor: bn_relu_fwd and then
 // bn_relu_bwd over ResNet-50's layers at batch 40 take 589 us with these loads and 523 without.
-template <typename T, bool FIN, bool LAST, bool THROUGH>
+template <typename T, BnFin FIN, bool LAST, bool THROUGH>
 __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ x,
                                                        const float* __restrict__ gamma,
                                                        const float* __restrict__ beta,
@@ -430,11 +538,23 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ x,
   const OutTensor<T, THROUGH> out(y, through);
   const int TX = 1 << tx_log2, TY = 256 >> tx_log2;
   const int tcol = threadIdx.x & (TX - 1), trow = threadIdx.x >> tx_log2;
-  const int col = blockIdx.y * TX + tcol;
-  __shared__ float mean_s[FIN ? 8 * V : 1], rstd_s[FIN ? 8 * V : 1];
-  if (!FIN && col >= C / V) return;
-  const bool live = col < C / V;  // (FIN: every thread takes part in the statistics)
-  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * rpb;
+  int bx = blockIdx.x, by = blockIdx.y;
+  if constexpr (FIN == kFinShared) {
+    if (bx < fin.groups) {
+      float a, b;
+      if (finalize_channels<false>(fin, bx, m, C, true, &a, &b)) publish_results(fin.slots + bx * kFinCh + threadIdx.x, a, b);
+      return;
+    }
+    bx -= fin.groups;
+    by = bx / fin.nblk;
+    bx -= by * fin.nblk;
+  }
+  const int col = by * TX + tcol;
+  constexpr int kStats = FIN == kFinSelf ? 8 * V : (FIN == kFinShared ? 32 * V : 1);
+  __shared__ __align__(16) float mean_s[kStats], rstd_s[kStats];
+  if (FIN == kFinGiven && col >= C / V) return;
+  const bool live = col < C / V;  // (else: every thread takes part in the statistics)
+  const int64_t r0 = static_cast<int64_t>(bx) * rpb;
   const int64_t r1 = min(r0 + rpb, m);
   int64_t r = r0 + trow;
   int64_t off[kBnRows];
@@ -457,14 +577,12 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ x,
     load_floats<V>(gamma + col * V, cg);
     load_floats<V>(beta + col * V, cb);
   }
-  if constexpr (FIN) {
-    finalize_slice_fwd<8 * V>(fin, m, C, blockIdx.y * 8 * V, blockIdx.x == 0, mean_s, rstd_s);
+  if constexpr (FIN != kFinGiven) {
+    if constexpr (FIN == kFinSelf) finalize_slice_fwd<8 * V>(fin, m, C, by * 8 * V, bx == 0, mean_s, rstd_s);
+    else await_results<false>(fin, m, C, by * TX * V, TX * V, mean_s, rstd_s);
     if (!live) return;
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      cm[j] = mean_s[tcol * V + j];
-      cr[j] = rstd_s[tcol * V + j];
-    }
+    load_floats<V>(mean_s + tcol * V, cm);
+    load_floats<V>(rstd_s + tcol * V, cr);
   } else {
     load_floats<V>(mean + col * V, cm);
     load_floats<V>(rstd + col * V, cr);
@@ -632,40 +750,6 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(
   reinterpret_cast<float2*>(partial)[bn_sums_at(blockIdx.x, c, gridDim.x)] = make_float2(t1, t2);
 }
 
-// (wide not null: rows of doubles from bn_reduce_rows_kernel instead)
-__global__ __launch_bounds__(kFinThreads) void bn_bwd_finalize_kernel(const float* __restrict__ partial, int nrows,
-                                                               const double2* __restrict__ wide, int nwide, int C,
-                                                               float* __restrict__ dgamma, float* __restrict__ dbeta) {
-  constexpr int G = kFinThreads / kFinCh;
-  const int c = blockIdx.x * kFinCh + threadIdx.x % kFinCh;
-  const float2* p = reinterpret_cast<const float2*>(partial) + bn_sums_at(0, c, nrows);
-  double s1 = 0.0, s2 = 0.0;
-  if (wide) {
-    const double2* pd = wide + bn_sums_at(0, c, nwide);
-    for (int b = threadIdx.x / kFinCh; b < nwide; b += G) {
-      s1 += pd[b * 8].x;
-      s2 += pd[b * 8].y;
-    }
-    nrows = 0;
-  }
-  for (int b = threadIdx.x / kFinCh; b < nrows; b += kFinRows * G) {
-    float2 v[kFinRows];
-#pragma unroll
-    for (int u = 0; u < kFinRows; ++u) v[u] = p[min(b + u * G, nrows - 1) * 8];
-#pragma unroll
-    for (int u = 0; u < kFinRows; ++u) {
-      if (b + u * G < nrows) {
-        s1 += static_cast<double>(v[u].x);
-        s2 += static_cast<double>(v[u].y);
-      }
-    }
-  }
-  finalize_combine(&s1, &s2);
-  if (threadIdx.x >= kFinCh || c >= C) return;
-  dbeta[c] = static_cast<float>(s1);
-  dgamma[c] = static_cast<float>(s2);
-}
-
 // Backward sums (sum g, sum g * xhat) of the CS channels from c0 on, by all 256 threads, in double and in the fixed order of
 // finalize_slice_fwd; dbeta / dgamma land in db_s / dg_s (LDS).  Ends with a barrier.
 template <int CS>
@@ -709,9 +793,9 @@ __device__ __forceinline__ void finalize_slice_bwd(const BnFinArgs& f, int C, in
   __syncthreads();
 }
 
-// FIN, LAST: as in bn_apply_kernel -- the pass adds up the per-tile sums of its 8 vector columns itself
+// FIN, LAST: as in bn_apply_kernel -- kFinSelf: the pass adds up the per-tile sums of its 8 vector columns itself
 // (tx_log2 = 3) and the first row block of every column slice stores dgamma / dbeta.
-template <typename T, bool DZ2, int ZK, bool FIN, bool LAST, bool THROUGH>
+template <typename T, bool DZ2, int ZK, BnFin FIN, bool LAST, bool THROUGH>
 __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(
     const T* __restrict__ dz, const T* __restrict__ dz2, const T* __restrict__ x,
     const T* __restrict__ z, const uint8_t* __restrict__ zmask, const float* __restrict__ gamma,
@@ -723,12 +807,24 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(
   const OutTensor<T, THROUGH> out(dx, through);
   const int TX = 1 << tx_log2, TY = 256 >> tx_log2;
   const int tcol = threadIdx.x & (TX - 1), trow = threadIdx.x >> tx_log2;
-  int col = blockIdx.y * TX + tcol;
-  __shared__ float db_s[FIN ? 8 * V : 1], dg_s[FIN ? 8 * V : 1];
-  if (!FIN && col >= C / V) return;
-  const bool live = col < C / V;  // (FIN: every thread takes part in the sums)
+  int bx = blockIdx.x, by = blockIdx.y;
+  if constexpr (FIN == kFinShared) {
+    if (bx < fin.groups) {
+      float a, b;
+      if (finalize_channels<true>(fin, bx, m, C, true, &a, &b)) publish_results(fin.slots + bx * kFinCh + threadIdx.x, a, b);
+      return;
+    }
+    bx -= fin.groups;
+    by = bx / fin.nblk;
+    bx -= by * fin.nblk;
+  }
+  int col = by * TX + tcol;
+  constexpr int kStats = FIN == kFinSelf ? 8 * V : (FIN == kFinShared ? 32 * V : 1);
+  __shared__ __align__(16) float db_s[kStats], dg_s[kStats];
+  if (FIN == kFinGiven && col >= C / V) return;
+  const bool live = col < C / V;  // (else: every thread takes part in the sums)
   if (!live) col = C / V - 1;      // (its loads stay in range; it leaves before it stores anything)
-  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * rpb;
+  const int64_t r0 = static_cast<int64_t>(bx) * rpb;
   const int64_t r1 = min(r0 + rpb, m);
   int64_t r = r0 + trow;
   // the first rows are requested before the per-channel values, so both arrive in one round trip
@@ -739,14 +835,12 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(
   load_floats<V>(gamma + col * V, cg);
   load_floats<V>(mean + col * V, cm);
   load_floats<V>(rstd + col * V, rs);
-  if constexpr (FIN) {
-    finalize_slice_bwd<8 * V>(fin, C, blockIdx.y * 8 * V, blockIdx.x == 0, db_s, dg_s);
+  if constexpr (FIN != kFinGiven) {
+    if constexpr (FIN == kFinSelf) finalize_slice_bwd<8 * V>(fin, C, by * 8 * V, bx == 0, db_s, dg_s);
+    else await_results<true>(fin, m, C, by * TX * V, TX * V, db_s, dg_s);
     if (!live) return;
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      mg[j] = db_s[tcol * V + j];
-      mgx[j] = dg_s[tcol * V + j];
-    }
+    load_floats<V>(db_s + tcol * V, mg);
+    load_floats<V>(dg_s + tcol * V, mgx);
   } else {
     load_floats<V>(dbeta + col * V, mg);
     load_floats<V>(dgamma + col * V, mgx);
@@ -811,29 +905,49 @@ static size_t bn_ws_bytes(const rn50_bn_desc* d) {
 }
 
 // finalize + apply from partial statistics rows (see bn_finalize_kernel).  reduces: their producer is a convolution, which
-// leaves them reduced where they are many.
+// leaves them reduced where they are many.  share (or null): finalize and apply in one launch where that is two.
 template <typename T, bool LAST>
 static void launch_fwd_tail(const rn50_bn_desc* d, int64_t m, const void* x,
                             const float* gamma, const float* beta, const void* residual, void* y,
                             uint8_t* relu_mask, float* save_mean, float* save_rstd, float* rm, float* rv,
-                            float momentum, const float* partial, int nrows, int rpp, bool self, bool reduces, hipStream_t s) {
+                            float momentum, const float* partial, int nrows, int rpp, bool self, bool reduces, const BnShare* share,
+                            hipStream_t s) {
   const int through = writes_through(m * d->C * sizeof(T));
+  BnFinArgs fin{};
+  fin.partial = partial; fin.nrows = nrows; fin.rpp = rpp;
+  fin.eps = d->eps; fin.momentum = momentum;
+  fin.mean_out = save_mean; fin.rstd_out = save_rstd; fin.running_mean = rm; fin.running_var = rv;
+#define RN50_FWD_APPLY_T(FIN, THROUGH, GRID, MEAN, RSTD, TXL, RPB)                                                                 \
+  RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, FIN, LAST, THROUGH>), GRID, dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, MEAN, \
+              RSTD, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, TXL, RPB, d->mode, through, fin)
+#define RN50_FWD_APPLY(FIN, GRID, MEAN, RSTD, TXL, RPB)                    \
+  do {                                                                     \
+    if (through) RN50_FWD_APPLY_T(FIN, true, GRID, MEAN, RSTD, TXL, RPB);  \
+    else RN50_FWD_APPLY_T(FIN, false, GRID, MEAN, RSTD, TXL, RPB);         \
+  } while (0)
   if (self && y) {
     // few tile rows: the apply pass finalizes for itself
     int gy, rpb;
     bn_self_finalize_geom(m, d->C, d->dtype == RN50_BF16 ? 8 : 4, &gy, &rpb);
-    const BnFinArgs fin{partial, nrows, d->eps, momentum, save_mean, save_rstd, rm, rv};
-    if (through) RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, true, LAST, true>), dim3(static_cast<unsigned>(ceil_div(m, rpb)), gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, nullptr, nullptr, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, 3, rpb, d->mode, through, fin);
-    else RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, true, LAST, false>), dim3(static_cast<unsigned>(ceil_div(m, rpb)), gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, nullptr, nullptr, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, 3, rpb, d->mode, through, fin);
+    RN50_FWD_APPLY(kFinSelf, dim3(static_cast<unsigned>(ceil_div(m, rpb)), gy), nullptr, nullptr, 3, rpb);
     return;
   }
-  const bool reduced = !self && reduces && bn_reduces(nrows);
-  const double2* wide = self ? reinterpret_cast<const double2*>(partial) : (reduced ? bn_reduced_rows(partial, nrows, d->C, false) : nullptr);
-  RN50_LAUNCH("bn_finalize", bn_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, self ? nullptr : partial, nrows, rpp, wide, reduced ? kBnReducedRows : nrows, m, d->C, d->eps, save_mean, save_rstd, rm, rv, momentum);
-  if (!y) return;  // statistics only: the consumer applies the layer while it loads its operand
+  if (self) {
+    fin.wide = reinterpret_cast<const double2*>(partial); fin.nwide = nrows; fin.partial = nullptr;
+  } else if (reduces && bn_reduces(nrows)) {
+    fin.wide = bn_reduced_rows(partial, nrows, d->C, false); fin.nwide = kBnReducedRows;
+  }
   const BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnApplyGroups);
-  if (through) RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, false, LAST, true>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, save_mean, save_rstd, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, ga.tx_log2, ga.rpb, d->mode, through, BnFinArgs{});
-  else RN50_LAUNCH("bn_apply", (bn_apply_kernel<T, false, LAST, false>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const T*>(x), gamma, beta, save_mean, save_rstd, static_cast<const T*>(residual), static_cast<T*>(y), relu_mask, m, d->C, ga.tx_log2, ga.rpb, d->mode, through, BnFinArgs{});
+  if (share && y && ga.nblk * ga.gy <= kBnShareGroups) {
+    fin.slots = share->slots; fin.groups = finalize_grid(d->C); fin.polls = share->polls; fin.nblk = ga.nblk;
+    RN50_FWD_APPLY(kFinShared, dim3(fin.groups + static_cast<unsigned>(ga.nblk) * ga.gy), nullptr, nullptr, ga.tx_log2, ga.rpb);
+    return;
+  }
+  RN50_LAUNCH("bn_finalize", bn_finalize_kernel<false>, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, m, d->C, fin);
+  if (!y) return;  // statistics only: the consumer applies the layer while it loads its operand
+  RN50_FWD_APPLY(kFinGiven, dim3(ga.nblk, ga.gy), save_mean, save_rstd, ga.tx_log2, ga.rpb);
+#undef RN50_FWD_APPLY
+#undef RN50_FWD_APPLY_T
 }
 
 template <typename T>
@@ -844,7 +958,7 @@ static void launch_fwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const 
   const bool self = bn_self_sums(m, d->C);
   RN50_LAUNCH("bn_stats", bn_stats_kernel<T>, dim3(g.nblk, g.gy), dim3(256), 0, s, static_cast<const T*>(x), m, d->C, g.tx_log2, g.rpb, self ? 1 : 0, partial);
   launch_fwd_tail<T, false>(d, m, x, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv, momentum,
-                     partial, g.nblk, g.rpb, self, false, s);
+                     partial, g.nblk, g.rpb, self, false, nullptr, s);
 }
 
 // finalize + apply from partial sums rows [sum g, sum g*xhat]
@@ -853,22 +967,31 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
                             const void* dz2, const void* x, const void* z, const uint8_t* zmask,
                             const float* gamma, const float* beta, const float* mean, const float* rstd,
                             void* dx, void* dres, float* dgamma, float* dbeta, const float* partial,
-                            int nrows, bool self, bool reduces, hipStream_t s) {
+                            int nrows, bool self, bool reduces, const BnShare* share, hipStream_t s) {
   BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnBwdApplyGroups);
   const int through = writes_through(m * d->C * sizeof(T));
   BnFinArgs fin{};
+  fin.partial = partial; fin.nrows = nrows; fin.mean_out = dbeta; fin.rstd_out = dgamma;
+  if (!self && reduces && bn_reduces(nrows)) {
+    fin.wide = bn_reduced_rows(partial, nrows, d->C, true); fin.nwide = kBnReducedRows;
+  }
+    if (ga.nblk * ga.gy > kBnShareGroups) share = nullptr;
+  dim3 grid;
   if (self) {
     // few tile rows: the apply pass adds them up itself
     ga.tx_log2 = 3;
     bn_self_finalize_geom(m, d->C, ga.V, &ga.gy, &ga.rpb);
     ga.nblk = static_cast<int>(ceil_div(m, ga.rpb));
-    fin = BnFinArgs{partial, nrows, 0.f, 0.f, dbeta, dgamma, nullptr, nullptr};
+    grid = dim3(ga.nblk, ga.gy);
+  } else if (share) {
+    fin.slots = share->slots; fin.groups = finalize_grid(d->C); fin.polls = share->polls; fin.nblk = ga.nblk;
+    grid = dim3(fin.groups + static_cast<unsigned>(ga.nblk) * ga.gy);
   } else {
-    const double2* wide = reduces && bn_reduces(nrows) ? bn_reduced_rows(partial, nrows, d->C, true) : nullptr;
-    RN50_LAUNCH("bn_bwd_finalize", bn_bwd_finalize_kernel, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, partial, nrows, wide, kBnReducedRows, d->C, dgamma, dbeta);
+    RN50_LAUNCH("bn_bwd_finalize", bn_finalize_kernel<true>, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, m, d->C, fin);
+    grid = dim3(ga.nblk, ga.gy);
   }
 #define RN50_BWD_APPLY_T(DZ2, ZK, FIN, THROUGH)                                                                           \
-  RN50_LAUNCH("bn_bwd_apply", (bn_bwd_apply_kernel<T, DZ2, ZK, FIN, LAST && ZK != 1, THROUGH>), dim3(ga.nblk, ga.gy), dim3(256), 0, s,       \
+  RN50_LAUNCH("bn_bwd_apply", (bn_bwd_apply_kernel<T, DZ2, ZK, FIN, LAST && ZK != 1, THROUGH>), grid, dim3(256), 0, s,       \
               static_cast<const T*>(dz), static_cast<const T*>(dz2), static_cast<const T*>(x),                     \
               static_cast<const T*>(z), zmask, gamma, beta, mean, rstd, dgamma, dbeta, static_cast<T*>(dx),        \
               static_cast<T*>(dres), m, d->C, ga.tx_log2, ga.rpb, d->mode, through, fin)
@@ -878,7 +1001,17 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
   } while (0)
 #define RN50_BWD_APPLY(DZ2, ZK)                                                  \
   do {                                                                           \
-    if (self) RN50_BWD_APPLY_K(DZ2, ZK, true); else RN50_BWD_APPLY_K(DZ2, ZK, false); \
+    if (self) {                                                                   \
+      RN50_BWD_APPLY_K(DZ2, ZK, kFinSelf);                                        \
+      break;                                                                      \
+    }                                                                             \
+    if constexpr (LAST && !DZ2 && ZK != 1) {                                      \
+      if (share) {                                                                \
+        RN50_BWD_APPLY_K(DZ2, ZK, kFinShared);                                    \
+        break;                                                                    \
+      }                                                                           \
+    }                                                                             \
+    RN50_BWD_APPLY_K(DZ2, ZK, kFinGiven);                                         \
   } while (0)
   const int zk = d->mode == 0 ? 0 : (zmask ? 2 : (z ? 1 : 0));
   if (dz2) {
@@ -909,7 +1042,7 @@ static void launch_bwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const 
   }
 #undef RN50_BWD_REDUCE
   launch_bwd_tail<T, LAST>(d, m, dz, dz2, x, z, zmask, gamma, beta, mean, rstd, dx, dres, dgamma, dbeta, partial,
-                     g.nblk, self, false, s);
+                     g.nblk, self, false, nullptr, s);
 }
 
 // Entry points for the whole-step driver (last_reader) and the fused C-ABI calls: the sums come from the output stage
@@ -917,17 +1050,18 @@ static void launch_bwd(const rn50_bn_desc* d, const BnGeom& g, int64_t m, const 
 template <typename T, bool LAST>
 static void fwd_from_partials(const rn50_bn_desc* d, const void* x, const float* partial, int nrows, int rpp,
                               const float* gamma, const float* beta, const void* residual, void* y, uint8_t* relu_mask,
-                              float* save_mean, float* save_rstd, float* rm, float* rv, float momentum, hipStream_t s) {
+                              float* save_mean, float* save_rstd, float* rm, float* rv, float momentum, const BnShare* share,
+                              hipStream_t s) {
   launch_fwd_tail<T, LAST>(d, static_cast<int64_t>(d->N) * d->H * d->W, x, gamma, beta, residual, y, relu_mask, save_mean,
-                           save_rstd, rm, rv, momentum, partial, nrows, rpp, bn_self_finalizes(nrows, false), true, s);
+                           save_rstd, rm, rv, momentum, partial, nrows, rpp, bn_self_finalizes(nrows, false), true, share, s);
 }
 void bn_fwd_from_partials(const rn50_bn_desc* d, const void* x, const float* partial, int nrows, int rpp,
                           const float* gamma, const float* beta, const void* residual, void* y,
                           uint8_t* relu_mask, float* save_mean, float* save_rstd, float* rm, float* rv,
-                          float momentum, bool last_reader, hipStream_t s) {
+                          float momentum, bool last_reader, hipStream_t s, const BnShare* share) {
   auto* run = d->dtype == RN50_BF16 ? (last_reader ? fwd_from_partials<uint16_t, true> : fwd_from_partials<uint16_t, false>)
                                     : (last_reader ? fwd_from_partials<float, true> : fwd_from_partials<float, false>);
-  run(d, x, partial, nrows, rpp, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv, momentum, s);
+  run(d, x, partial, nrows, rpp, gamma, beta, residual, y, relu_mask, save_mean, save_rstd, rm, rv, momentum, share, s);
 }
 // Evaluation mode: 1/sqrt(running_var + eps) per channel, then the training pass's apply kernel with the
 // moving averages in place of the batch statistics.
@@ -944,26 +1078,26 @@ static void infer_run(const rn50_bn_desc* d, const void* x, const float* gamma, 
                      running_var, d->eps, d->C, rstd_scratch);
   const BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnApplyGroups);
   if (d->dtype == RN50_BF16)
-    RN50_LAUNCH("bn_apply", (bn_apply_kernel<uint16_t, false, false, false>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const uint16_t*>(x), gamma, beta, running_mean, rstd_scratch, static_cast<const uint16_t*>(residual), static_cast<uint16_t*>(y), static_cast<uint8_t*>(nullptr), m, d->C, ga.tx_log2, ga.rpb, d->mode, 0, BnFinArgs{});
+    RN50_LAUNCH("bn_apply", (bn_apply_kernel<uint16_t, kFinGiven, false, false>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const uint16_t*>(x), gamma, beta, running_mean, rstd_scratch, static_cast<const uint16_t*>(residual), static_cast<uint16_t*>(y), static_cast<uint8_t*>(nullptr), m, d->C, ga.tx_log2, ga.rpb, d->mode, 0, BnFinArgs{});
   else
-    RN50_LAUNCH("bn_apply", (bn_apply_kernel<float, false, false, false>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const float*>(x), gamma, beta, running_mean, rstd_scratch, static_cast<const float*>(residual), static_cast<float*>(y), static_cast<uint8_t*>(nullptr), m, d->C, ga.tx_log2, ga.rpb, d->mode, 0, BnFinArgs{});
+    RN50_LAUNCH("bn_apply", (bn_apply_kernel<float, kFinGiven, false, false>), dim3(ga.nblk, ga.gy), dim3(256), 0, s, static_cast<const float*>(x), gamma, beta, running_mean, rstd_scratch, static_cast<const float*>(residual), static_cast<float*>(y), static_cast<uint8_t*>(nullptr), m, d->C, ga.tx_log2, ga.rpb, d->mode, 0, BnFinArgs{});
 }
 
 template <typename T, bool LAST>
 static void bwd_from_partials(const rn50_bn_desc* d, const void* dz, const void* x, const uint8_t* relu_mask,
                               const float* gamma, const float* beta, const float* mean, const float* rstd,
                               const float* partial, int nrows, void* dx, void* dres, float* dgamma, float* dbeta,
-                              hipStream_t s) {
+                              const BnShare* share, hipStream_t s) {
   launch_bwd_tail<T, LAST>(d, static_cast<int64_t>(d->N) * d->H * d->W, dz, nullptr, x, nullptr, relu_mask, gamma, beta, mean,
-                           rstd, dx, dres, dgamma, dbeta, partial, nrows, bn_self_finalizes(nrows, true), true, s);
+                           rstd, dx, dres, dgamma, dbeta, partial, nrows, bn_self_finalizes(nrows, true), true, LAST ? share : nullptr, s);
 }
 void bn_bwd_from_partials(const rn50_bn_desc* d, const void* dz, const void* x, const uint8_t* relu_mask,
                           const float* gamma, const float* beta, const float* mean, const float* rstd,
                           const float* partial, int nrows, void* dx, void* dres, float* dgamma, float* dbeta,
-                          bool last_reader, hipStream_t s) {
+                          bool last_reader, hipStream_t s, const BnShare* share) {
   auto* run = d->dtype == RN50_BF16 ? (last_reader ? bwd_from_partials<uint16_t, true> : bwd_from_partials<uint16_t, false>)
                                     : (last_reader ? bwd_from_partials<float, true> : bwd_from_partials<float, false>);
-  run(d, dz, x, relu_mask, gamma, beta, mean, rstd, partial, nrows, dx, dres, dgamma, dbeta, s);
+  run(d, dz, x, relu_mask, gamma, beta, mean, rstd, partial, nrows, dx, dres, dgamma, dbeta, share, s);
 }
 void bn_bwd_run(const rn50_bn_desc* d, const void* dz, const void* dz2, const void* x, const void* z,
                 const uint8_t* relu_mask, const float* gamma, const float* beta, const float* mean, const float* rstd,

@@ -81,6 +81,7 @@ struct IgemmArgs {
   // normalized input.
   float* partial;
   int partial_wide;  // forward: as doubles (bn_self_finalizes)
+  unsigned long long* slots;  // (or null) one word per column, made empty for the pass that adds the sums up (BnShare)
   const void* bn_x;
   const float *bn_gamma, *bn_beta, *bn_mean, *bn_rstd;
   // Data gradient with sums only.  addend [M][Ncols] (or null): a second gradient branch, added to the
@@ -203,6 +204,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   const int mt = static_cast<int>(fdiv(static_cast<uint32_t>(bid), a.div_ntn)), nt = bid - mt * a.ntn;
   const int n0 = nt * BN;
   const rsrc_words rsA = make_rsrc_words(a.act, a.act_bytes), rsB = make_rsrc_words(a.wgt, a.wgt_bytes);
+  if (!AFF && a.slots != nullptr && mt == 0 && tid < BN && n0 + tid < a.Ncols) a.slots[n0 + tid] = kBnSlotEmpty;
 
   // Rows of this tile: pixels m0.. of the whole output grid, or of one parity class of it.
   const bool classes = !LIN && DG && a.stride == 2;
@@ -1215,9 +1217,9 @@ void stem_fwd_padded(const rn50_conv_desc* d, const void* xp, const void* w, voi
 }
 
 void fwd_run(const rn50_conv_desc* d, const void* x, const void* w, void* y, float* bn_partial, hipStream_t s,
-             const char* tag, const BnIn* in, const BnAffine* affine) {
+             const char* tag, const BnIn* in, const BnAffine* affine, unsigned long long* slots) {
   IgemmArgs a{};
-  a.act = x; a.wgt = w; a.out = y; a.partial = bn_partial;
+  a.act = x; a.wgt = w; a.out = y; a.partial = bn_partial; a.slots = slots;
   if (in) { a.in_gamma = in->gamma; a.in_beta = in->beta; a.in_mean = in->mean; a.in_rstd = in->rstd; }
   a.P = out_dim(d->H, d->pad, d->R, d->stride); a.Q = out_dim(d->W, d->pad, d->S, d->stride);
   a.M = d->N * a.P * a.Q; a.Ncols = d->Cout; a.Ktot = d->R * d->S * d->Cin;
@@ -1242,7 +1244,7 @@ void dgrad_run(const rn50_conv_desc* d, const void* dy, const void* w, void* dx,
   if (bn) {
     a.partial = bn->partial; a.bn_x = bn->x;
     a.bn_gamma = bn->gamma; a.bn_beta = bn->beta; a.bn_mean = bn->mean; a.bn_rstd = bn->rstd;
-    a.addend_even = bn->addend_even; a.addend = bn->addend; a.bn_zmask = bn->relu_mask; a.addend_mask = bn->addend ? bn->addend_mask : nullptr;
+    a.slots = bn->slots; a.addend_even = bn->addend_even; a.addend = bn->addend; a.bn_zmask = bn->relu_mask; a.addend_mask = bn->addend ? bn->addend_mask : nullptr;
   }
   a.P = d->H; a.Q = d->W;
   a.H = out_dim(d->H, d->pad, d->R, d->stride); a.W = out_dim(d->W, d->pad, d->S, d->stride);

@@ -63,6 +63,8 @@ struct rn50_plan {
   size_t ws_bytes = 0;
   size_t xp = 0, wp = 0, pool = 0, avg = 0, logits = 0, dlogits = 0, row_loss = 0, davg = 0;
   size_t g[5] = {0, 0, 0, 0, 0};
+  size_t bn_slots = 0, bn_slots2 = 0;  // one word per channel and BN scratch (BnShare)
+  int bn_polls = rn50::kBnPolls;
   size_t wgrad_scratch = 0, bn_scratch = 0, pool_argmax = 0, fc_scratch = 0;
   size_t fc_scratch_bytes = 0;
   std::vector<rn50::LarsGroup> lars_groups;  // in the order in which the backward pass completes them
@@ -263,6 +265,10 @@ extern "C" int resnet_plan_create(const rn50_step_config* cfg, rn50_plan** plan_
   p->wgrad_scratch = bump(&top, max_wg);
   p->bn_scratch = bump(&top, max_bn);
   p->bn_scratch2 = bump(&top, max_bn);
+  int max_c = 0;
+  for (const Unit& u : p->units) max_c = std::max(max_c, u.conv.Cout);
+  p->bn_slots = bump(&top, max_c * sizeof(unsigned long long));
+  p->bn_slots2 = bump(&top, max_c * sizeof(unsigned long long));
   plan_lars_groups(p);
   for (LarsGroup& g : p->lars_groups) g.scratch = bump(&top, lars_arena_partial_bytes(g.spec));
   p->ws_bytes = top;
@@ -346,6 +352,12 @@ extern "C" int resnet_plan_fuse_conv3_input(rn50_plan* plan, int on) {
     RN50_REQUIRE(!on || plan->units[b.u3].conv.Cin <= 4096, RN50_ERR_UNSUPPORTED,
                  "resnet_plan_fuse_conv3_input: a conv3 with more than 4096 input channels");
   plan->fuse_conv3_input = on != 0;
+  return RN50_OK;
+}
+extern "C" int resnet_plan_wait_polls(rn50_plan* plan, int polls) {
+  clear_error();
+  RN50_REQUIRE(plan && polls >= 0, RN50_ERR_INVALID, "resnet_plan_wait_polls: null plan or negative count");
+  plan->bn_polls = polls;
   return RN50_OK;
 }
 extern "C" int resnet_plan_num_tensors(const rn50_plan* plan) {
@@ -471,20 +483,23 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
   void* bn_ws2 = ws + plan->bn_scratch2;  // the projection branch's own BN scratch
   float* sums2 = static_cast<float*>(bn_ws2);
   // stats_only: the layer's output is not stored (its consumer applies it on the fly).
+  const BnShare share{reinterpret_cast<unsigned long long*>(ws + plan->bn_slots), plan->bn_polls};
+  const BnShare share2{reinterpret_cast<unsigned long long*>(ws + plan->bn_slots2), plan->bn_polls};
   auto bn_after_conv = [&](Unit& u, const void* residual, float* sm, hipStream_t st, bool stats_only = false) {
     const PartialRows pr = fwd_partial_rows(&u.conv);
     // the residual-add layers record their ReLU decisions: their backward pass then reads one byte per
     // vector instead of z
     bn_fwd_from_partials(&u.bn, ws + u.y, sm, pr.num, pr.rows, MP(u.ig), MP(u.ib), residual,
                          stats_only ? nullptr : ws + u.z, u.bn.mode == 2 ? ws + u.relu_mask : nullptr, F(u.mean), F(u.rstd),
-                         run_mean ? run_mean + u.bn_off : nullptr, run_var ? run_var + u.bn_off : nullptr, bn_momentum, true, st);
+                         run_mean ? run_mean + u.bn_off : nullptr, run_var ? run_var + u.bn_off : nullptr, bn_momentum, true, st,
+                         u.conv.Cin == 3 ? nullptr : (sm == sums ? &share : &share2));
   };
   stem_fwd_padded(&u0.conv, ws + plan->xp, W(u0.iw), ws + plan->wp, ws + u0.y, sums, s);
   bn_after_conv(u0, nullptr, sums, s, true);
   bn_relu_maxpool(&u0.bn, ws + u0.y, MP(u0.ig), MP(u0.ib), F(u0.mean), F(u0.rstd), ws + plan->pool, ws + plan->pool_argmax, s);
   const unsigned char* cur = ws + plan->pool;
   auto conv_bn = [&](Unit& u, const void* in, const void* residual, float* sm, hipStream_t st) {
-    fwd_run(&u.conv, in, W(u.iw), ws + u.y, sm, st);
+    fwd_run(&u.conv, in, W(u.iw), ws + u.y, sm, st, "conv_fwd", nullptr, nullptr, (sm == sums ? share : share2).slots);
     bn_after_conv(u, residual, sm, st);
   };
   for (const Block& b : plan->blocks) {
@@ -504,7 +519,7 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
       bn_after_conv(u2, nullptr, sums, s, true);
       if (b.up >= 0) (void)hipStreamWaitEvent(s, plan->ev_bjoin, 0);
       const BnIn in{MP(u2.ig), MP(u2.ib), F(u2.mean), F(u2.rstd)};
-      fwd_run(&u3.conv, ws + u2.y, W(u3.iw), ws + u3.y, sums, s, "conv_fwd", &in);
+      fwd_run(&u3.conv, ws + u2.y, W(u3.iw), ws + u3.y, sums, s, "conv_fwd", &in, nullptr, share.slots);
       bn_after_conv(u3, shortcut, sums, s);
     } else {
       conv_bn(u2, ws + u1.z, nullptr, sums, s);
@@ -596,7 +611,7 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
     } else if (sums_ready) {
       bn_bwd_from_partials(&u.bn, dz, ws + u.y, bits, MP(u.ig), MP(u.ib), F(u.mean), F(u.rstd),
                            static_cast<const float*>(wsx), dgrad_sums_rows, dy, u.bn.mode == 2 ? dres : nullptr,
-                           G(u.ig), G(u.ib), true, st);
+                           G(u.ig), G(u.ib), true, st, &share);
     } else {
       bn_bwd_run(&u.bn, dz, dz2, ws + u.y, nullptr, bits, MP(u.ig), MP(u.ib), F(u.mean), F(u.rstd), dy, dres, G(u.ig),
                  G(u.ib), static_cast<float*>(wsx), true, st);
@@ -612,7 +627,7 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
     BnBwdSums fuse{};
     if (below) {
       fuse = BnBwdSums{ws + below->y, MP(below->ig), MP(below->ib), F(below->mean), F(below->rstd), sums, addend,
-                       below->bn.mode == 2 ? ws + below->relu_mask : nullptr, addend_mask, addend_even};
+                       below->bn.mode == 2 ? ws + below->relu_mask : nullptr, addend_mask, share.slots, addend_even};
       dgrad_sums_rows = dgrad_partial_rows(&u.conv).num;
     }
     dgrad_run(&u.conv, dy, W(u.iw), dx, below ? &fuse : nullptr, st);

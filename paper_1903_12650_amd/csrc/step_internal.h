@@ -75,13 +75,23 @@ inline double2* bn_reduced_rows(const float* sums, int nrows, int C, bool backwa
 // bn.hip.  rpp: rows of x behind a row of sums (forward), m: of x in all.
 void bn_reduce_rows(float* sums, int nrows, int rpp, int64_t m, int C, bool backward, hipStream_t s);
 
+// An apply pass whose launch also finalizes (kFinShared): one word per channel, made empty by the producer of the sums, and how
+// often a workgroup asks for another one's results before it computes them itself.
+constexpr unsigned long long kBnSlotEmpty = ~0ull;
+constexpr int kBnPolls = 2000;
+struct BnShare {
+  unsigned long long* slots;
+  int polls;
+};
+
 // A BN+ReLU layer applied to a convolution's input on the fly (1x1, stride 1 convolutions only): its parameters
 // and saved statistics, float[Cin] each.
 struct BnIn {
   const float *gamma, *beta, *mean, *rstd;
 };
 void fwd_run(const rn50_conv_desc* d, const void* x, const void* w, void* y, float* bn_partial, hipStream_t s,
-             const char* tag = "conv_fwd", const BnIn* in = nullptr, const BnAffine* affine = nullptr);
+             const char* tag = "conv_fwd", const BnIn* in = nullptr, const BnAffine* affine = nullptr,
+             unsigned long long* slots = nullptr);  // slots: to be made empty (BnShare)
 // The BN layer (with ReLU) whose output gradient a data gradient produces: x is that
 // layer's input [N*H*W][Cin]; partial receives the pairs sum(g), sum(g * xhat) per tile and channel (bn_sums_at).
 // addend (or null): a second branch of the gradient, [N*H*W][Cin], added to the data gradient before it
@@ -95,6 +105,7 @@ struct BnBwdSums {
   const void* addend = nullptr;
   const uint8_t* relu_mask = nullptr;
   const uint8_t* addend_mask = nullptr;
+  unsigned long long* slots = nullptr;  // to be made empty (BnShare)
   bool addend_even = false;  // the addend's pixels with odd row or column are zero and left out (1x1 / stride 1, no addend_mask)
 };
 void dgrad_run(const rn50_conv_desc* d, const void* dy, const void* w, void* dx, const BnBwdSums* bn, hipStream_t s,
@@ -108,13 +119,13 @@ void wgrad_run(const rn50_conv_desc* d, const void* x_or_xp, const void* dy, flo
 void bn_fwd_from_partials(const rn50_bn_desc* d, const void* x, const float* partial, int nrows, int rpp,
                           const float* gamma, const float* beta, const void* residual, void* y,
                           uint8_t* relu_mask, float* save_mean, float* save_rstd, float* rm, float* rv,
-                          float momentum, bool last_reader, hipStream_t s);
+                          float momentum, bool last_reader, hipStream_t s, const BnShare* share = nullptr);
 // relu_mask: recorded ReLU decisions (required in mode 2, where dres receives the masked gradient), or
 // null: recomputed from x (mode 1).
 void bn_bwd_from_partials(const rn50_bn_desc* d, const void* dz, const void* x, const uint8_t* relu_mask,
                           const float* gamma, const float* beta, const float* mean, const float* rstd,
                           const float* partial, int nrows, void* dx, void* dres, float* dgamma, float* dbeta,
-                          bool last_reader, hipStream_t s);
+                          bool last_reader, hipStream_t s, const BnShare* share = nullptr);
 // The whole backward pass (bn_relu_bwd without its checks); scratch: bn_relu_bwd_workspace_bytes(d).
 void bn_bwd_run(const rn50_bn_desc* d, const void* dz, const void* dz2, const void* x, const void* z,
                 const uint8_t* relu_mask, const float* gamma, const float* beta, const float* mean, const float* rstd,

@@ -462,6 +462,30 @@ def test_step_with_conv3_input_fusion_gives_the_same_bits(rn, mode):
     assert torch.isfinite(outs[0][2]).all()
 
 
+@pytest.mark.parametrize("mode,N", [("bf16", 6), ("f32", 4)])
+def test_step_computes_the_same_statistics_whoever_computes_them(rn, mode, N):
+    """Apply passes whose launch also finalizes (the 56x56 layers here): a workgroup that never asks for another one's results
+    computes them itself, to the same bits; weights, statistics and loss of two training steps."""
+    bf = mode == "bf16"
+    out = []
+    for polls in (2000, 0):
+        plan = rn.ResnetPlan(N, rn.BF16 if bf else rn.F32)
+        plan.wait_polls(polls)
+        M = torch.empty(plan.arena_elems, device="cuda"); V = torch.empty_like(M); G = torch.zeros_like(M)
+        rn.resnet_init_params(plan, SEED, M, V)
+        Mod = M.to(torch.bfloat16) if bf else M
+        gen = torch.Generator(device="cuda").manual_seed(1)
+        img = torch.randn(N, 224, 224, 3, device="cuda", generator=gen).to(Mod.dtype)
+        lab = torch.randint(0, 1000, (N,), device="cuda", generator=gen, dtype=torch.int32)
+        ws = torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+        state = rn.TrainState(plan)
+        for _ in range(2):
+            loss = rn.resnet_train_step(plan, rn.LrSchedule(base_lr=0.1), state, img, lab, M, V, G, Mod, ws)
+        out.append([loss.clone(), M, V, G] + [t.clone() for t in state.running_mean + state.running_var])
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+
+
 def test_step_resnet50_batch256_bf16_equals_the_chain(rn):
     """The large-batch configuration (batch 256, 6.4 times the measured one: tensors of up to 411 MB, tens
     of thousands of output tiles): resnet_step is bit for bit the operation-by-operation chain, whose
