@@ -5,7 +5,6 @@ enqueued on torch's current stream.  There is no CPU fallback: importing this
 module fails loudly when the library has not been built.
 """
 import ctypes
-import functools
 import os
 import struct
 
@@ -28,10 +27,11 @@ def lib_path():
     return os.path.join(_HERE, "librn50_hip.so")
 
 
-if not os.path.exists(lib_path()):
-    raise ImportError("librn50_hip.so is not built: run `python paper_1903_12650_amd/build.py` (or "
+if not (os.path.exists(lib_path()) and os.path.exists(os.path.join(_HERE, "_ops.so"))):
+    raise ImportError("librn50_hip.so and _ops.so are not built: run `python paper_1903_12650_amd/build.py` (or "
                       "`python -c 'import __graft_entry__ as g; g.build()'`) first; there is no fallback path")
 raw = ctypes.CDLL(lib_path())
+from . import _ops  # noqa: E402
 
 
 class Rn50Error(RuntimeError):
@@ -81,20 +81,19 @@ for _n in ("resnet_plan_tensor_shape", "resnet_plan_tensor_offset", "resnet_plan
         getattr(raw, _n).restype = ctypes.c_int64
 
 
-# The operations that are called once per layer take a few microseconds of GPU time at small batches, so what the call costs
-# in Python counts: their argument types are declared (plain ints are passed as pointers and sizes, no ctypes object is made
-# per argument), descriptors and workspace sizes are kept per shape, and the stream is asked for as a number.  `raw` stays undeclared for direct use.
+# The calls of one operation that a program makes once per layer are marshalled by the native module (csrc/python/ops.cpp).  The
+# others that are called in a loop have their argument types declared (plain ints are passed as pointers and sizes, no ctypes
+# object is made per argument), and the stream is asked for as a number.  `raw` stays undeclared for direct use.
 _P, _I, _F, _Z = ctypes.c_void_p, ctypes.c_int, ctypes.c_float, ctypes.c_size_t
 _lib = ctypes.CDLL(lib_path())
-for _n, _a in (("conv_fwd", (_P,) * 5 + (_Z, _P)), ("conv_dgrad", (_P,) * 5 + (_Z, _P)), ("conv_wgrad", (_P,) * 5 + (_Z, _P)),
-               ("bn_relu_fwd", (_P,) * 11 + (_F, _P, _Z, _P)), ("bn_relu_bwd", (_P,) * 15 + (_Z, _P)),
-               ("lars_update", (_P,) * 5 + (_Z, _P)),
+for _n, _a in (("lars_update", (_P,) * 5 + (_Z, _P)),
                ("resnet_step", (_P,) * 7 + (_F, _I, _P, _P, _P, _Z, _P)),
                ("resnet_train_step", (_P,) * 3 + (_F,) + (_P,) * 9 + (_Z, _P)),
                ("resnet_eval", (_P,) * 10 + (_Z, _P))):
     getattr(_lib, _n).argtypes = _a
 _current_raw_stream = torch._C._cuda_getCurrentRawStream
 _current_device = torch._C._cuda_getDevice
+_ops.setup(Rn50Error, _current_raw_stream, _current_device)
 
 
 def _check(rc):
@@ -154,43 +153,16 @@ def conv_wgrad_workspace_bytes(desc):
     return raw.conv_wgrad_workspace_bytes(ctypes.byref(desc))
 
 
-@functools.lru_cache(maxsize=1024)
-def _conv_call(x_shape, w_shape, stride, pad, dtype, workspace_bytes):
-    """What a call of this shape needs besides its tensors: descriptor (by reference), output shape, workspace bytes."""
-    d = _conv_desc(x_shape, w_shape, stride, pad, dtype)
-    P = (d.H + 2 * pad - d.R) // stride + 1
-    Q = (d.W + 2 * pad - d.S) // stride + 1
-    return ctypes.byref(d), (d.N, P, Q, d.Cout), workspace_bytes(d)
-
-
 def conv_fwd(x, w, stride, pad, y=None, workspace=None):
-    d, y_shape, need = _conv_call(x.shape, w.shape, stride, pad, _dt(x), conv_fwd_workspace_bytes)
-    if y is None:
-        y = torch.empty(y_shape, dtype=x.dtype, device=x.device)
-    if workspace is None:
-        workspace = _ws(need, x.device)
-    _check(_lib.conv_fwd(d, _addr(x), _addr(w), _addr(y), _addr(workspace), workspace.numel(), _raw_stream()))
-    return y
+    return _ops.conv_fwd(x, w, stride, pad, y, workspace)
 
 
 def conv_dgrad(dy, w, x_shape, stride, pad, dx=None, workspace=None):
-    d, _, need = _conv_call(tuple(x_shape), w.shape, stride, pad, _dt(dy), conv_dgrad_workspace_bytes)
-    if dx is None:
-        dx = torch.empty(tuple(x_shape), dtype=dy.dtype, device=dy.device)
-    if workspace is None:
-        workspace = _ws(need, dy.device)
-    _check(_lib.conv_dgrad(d, _addr(dy), _addr(w), _addr(dx), _addr(workspace), workspace.numel(), _raw_stream()))
-    return dx
+    return _ops.conv_dgrad(dy, w, x_shape, stride, pad, dx, workspace)
 
 
 def conv_wgrad(x, dy, w_shape, stride, pad, dw=None, workspace=None):
-    d, _, need = _conv_call(x.shape, tuple(w_shape), stride, pad, _dt(x), conv_wgrad_workspace_bytes)
-    if dw is None:
-        dw = torch.empty(tuple(w_shape), dtype=torch.float32, device=x.device)
-    if workspace is None:
-        workspace = _ws(need, x.device)
-    _check(_lib.conv_wgrad(d, _addr(x), _addr(dy), _addr(dw), _addr(workspace), workspace.numel(), _raw_stream()))
-    return dw
+    return _ops.conv_wgrad(x, dy, w_shape, stride, pad, dw, workspace)
 
 
 # ----------------------------------------------------------------- batch norm
@@ -213,42 +185,15 @@ def relu_mask_like(x):
     return torch.empty(x.numel() // V, dtype=torch.uint8, device=x.device)
 
 
-@functools.lru_cache(maxsize=1024)
-def _bn_call(shape, eps, dtype, mode):
-    """Descriptor (by reference), channels, workspace bytes of either direction."""
-    C = shape[-1]
-    d = BnDesc(*shape[:3], C, eps, dtype, mode) if len(shape) == 4 else BnDesc(1, 1, shape.numel() // C, C, eps, dtype, mode)
-    return ctypes.byref(d), C, max(bn_relu_fwd_workspace_bytes(d), bn_relu_bwd_workspace_bytes(d))
-
-
 def bn_relu_fwd(x, gamma, beta, residual=None, eps=1e-5, mode=1, running_mean=None, running_var=None,
                 momentum=0.9, workspace=None, relu_mask=None):
     """Returns y, save_mean, save_rstd.  relu_mask: optional uint8 tensor (see relu_mask_like) to fill."""
-    d, C, need = _bn_call(x.shape, eps, _dt(x), mode)
-    y = torch.empty_like(x)
-    mean = torch.empty(C, dtype=torch.float32, device=x.device)
-    rstd = torch.empty_like(mean)
-    if workspace is None:
-        workspace = _ws(need, x.device)
-    _check(_lib.bn_relu_fwd(d, _addr(x), _addr(gamma), _addr(beta), _addr(residual), _addr(y), _addr(relu_mask), _addr(mean),
-                            _addr(rstd), _addr(running_mean), _addr(running_var), momentum, _addr(workspace),
-                            workspace.numel(), _raw_stream()))
-    return y, mean, rstd
+    return _ops.bn_relu_fwd(x, gamma, beta, residual, eps, mode, running_mean, running_var, momentum, workspace, relu_mask)
 
 
 def bn_relu_bwd(dz, x, z, gamma, mean, rstd, mode=1, beta=None, dz2=None, eps=1e-5, workspace=None, relu_mask=None):
     """Returns dx, dresidual (None unless mode 2), dgamma, dbeta."""
-    d, C, need = _bn_call(x.shape, eps, _dt(x), mode)
-    dx = torch.empty_like(x)
-    dres = torch.empty_like(x) if mode == 2 else None
-    dgamma = torch.empty(C, dtype=torch.float32, device=x.device)
-    dbeta = torch.empty_like(dgamma)
-    if workspace is None:
-        workspace = _ws(need, x.device)
-    _check(_lib.bn_relu_bwd(d, _addr(dz), _addr(dz2), _addr(x), _addr(z), _addr(relu_mask), _addr(gamma), _addr(beta),
-                            _addr(mean), _addr(rstd), _addr(dx), _addr(dres), _addr(dgamma), _addr(dbeta), _addr(workspace),
-                            workspace.numel(), _raw_stream()))
-    return dx, dres, dgamma, dbeta
+    return _ops.bn_relu_bwd(dz, x, z, gamma, mean, rstd, mode, beta, dz2, eps, workspace, relu_mask)
 
 
 # ------------------------------------- convolution + batch norm with fused sums

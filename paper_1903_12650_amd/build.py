@@ -1,4 +1,5 @@
-"""Compile the HIP sources under csrc/ for gfx950 into librn50_hip.so (in-tree)."""
+"""Compile the HIP sources under csrc/ for gfx950 into librn50_hip.so, and the native part of the Python binding into _ops.so
+(both in-tree)."""
 import os
 import subprocess
 import sys
@@ -7,6 +8,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librn50_hip.so")
+OPS_SRC, OPS = os.path.join(CSRC, "python", "ops.cpp"), os.path.join(HERE, "_ops.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -43,12 +45,34 @@ def _compile(src, force):
     return obj
 
 
+def _compile_ops(force):
+    """The native marshalling of the per-layer Python calls: an object now (host code against torch's headers), linked below."""
+    import sysconfig
+    from torch.utils import cpp_extension
+    obj = os.path.join(OBJ_DIR, "ops.cpp.o")
+    deps = [OPS_SRC, os.path.join(HERE, "..", "include", "rn50_hip.h")]
+    if not force and os.path.exists(obj) and all(os.path.getmtime(obj) >= os.path.getmtime(d) for d in deps):
+        return obj
+    inc = [a for p in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]] for a in ("-isystem", p)]
+    subprocess.check_call(["g++", "-O2", "-fPIC", "-std=c++17", "-Wall"] + inc + ["-c", OPS_SRC, "-o", obj])
+    return obj
+
+
+def _link_ops(obj):
+    from torch.utils import cpp_extension
+    libs = [a for p in cpp_extension.library_paths() for a in ("-L" + p,)]
+    subprocess.check_call(["g++", "-shared", "-o", OPS, obj, "-L" + HERE, "-l:librn50_hip.so", "-Wl,-rpath,$ORIGIN"] + libs +
+                          ["-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"])
+
+
 def build(force=True, jobs=8):
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        ops = ex.submit(_compile_ops, force)
         objs = list(ex.map(lambda s: _compile(s, force), sources()))
     # --no-undefined: a kernel whose host stub was not emitted must fail here, not at load time
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,--no-undefined", "-o", LIB] + objs)
+    _link_ops(ops.result())
     return LIB
 
 

@@ -4,6 +4,8 @@ import ctypes
 import os
 import re
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "rn50_hip.h")
 
@@ -149,3 +151,26 @@ def test_roofline_cost_model_totals():
     assert sum(b for _, b in apply) == 4 * E + 2 * E_add and sum(b for _, b in bwd) == 6 * E + (E_add + E_proj) / 8
     assert sum(b for _, b in rl.per_launch_cost("lars_apply", plan)) == 22 * 25_557_032
     assert len(rl.per_launch_cost("lars_norms", plan)) == 6   # groups of tensors, in the order in which they are complete
+
+
+@pytest.mark.parametrize("call, error", [
+    (lambda rn, x, w: rn.conv_fwd(x, w, 1, 0), AssertionError),                                # host tensors
+    (lambda rn, x, w: rn.conv_dgrad(x, w, (1, 8, 8, 8), 1, 0, dx=x), AssertionError),
+    (lambda rn, x, w: rn.conv_wgrad(x, x, w.shape, 1, 0, workspace=w), AssertionError),
+    (lambda rn, x, w: rn.bn_relu_fwd(x, w, w), AssertionError),
+    (lambda rn, x, w: rn.bn_relu_bwd(x, x, x, w, w, w), AssertionError),
+    (lambda rn, x, w: rn.conv_fwd(x, w[..., :4], 1, 0), AssertionError),                       # channels differ
+    (lambda rn, x, w: rn.conv_fwd(x.double(), w, 1, 0), TypeError),
+    (lambda rn, x, w: rn.bn_relu_fwd(x.half(), w, w), TypeError),
+    (lambda rn, x, w: rn.conv_fwd(x[0], w, 1, 0), ValueError),
+    (lambda rn, x, w: rn.conv_dgrad(x, w, (8, 8, 8), 1, 0), ValueError),
+    (lambda rn, x, w: rn.conv_fwd(x, w, 0, 0), ZeroDivisionError),
+    (lambda rn, x, w: rn.conv_fwd(x, w.new_zeros(8, 11, 11, 8), 2, 0), RuntimeError),          # an output of -1 pixels
+    (lambda rn, x, w: rn.conv_fwd(x, w, "1", 0), TypeError),
+    (lambda rn, x, w: rn.bn_relu_fwd(x, w, w, bogus=1), TypeError),
+])
+def test_native_calls_refuse_what_they_cannot_take(call, error):
+    import torch
+    import paper_1903_12650_amd as rn
+    with pytest.raises(error):
+        call(rn, torch.zeros(1, 8, 8, 8), torch.zeros(8, 1, 1, 8))

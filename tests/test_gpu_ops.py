@@ -385,3 +385,40 @@ def test_abi_error_codes(rn):
         rn.bn_relu_fwd(x.view(-1)[8 * 3:8 * 3 + 2 * 4 * 3 * 16].view(2, 4, 3, 16)[..., :], g, g, None, 1e-5, 1) \
             if x.view(-1)[8 * 3:].data_ptr() % 16 else (_ for _ in ()).throw(rn.Rn50Error(-4, "aligned by chance"))
     assert e.value.code == -4
+
+
+@pytest.mark.parametrize("C, hw, k, stride", [(64, 14, 3, 2), (128, 7, 1, 1)])
+def test_calls_from_several_threads_and_streams(rn, C, hw, k, stride):
+    """The per-layer calls allocate, enqueue and release the interpreter in native code: three threads, each on a stream of its
+    own, get bit for bit what one thread gets, with given outputs and workspaces as without."""
+    import threading
+    x, w = torch.randn(4, hw, hw, C, device="cuda"), torch.randn(C, k, k, C, device="cuda") * 0.05
+    g, b = torch.rand(C, device="cuda") + 0.5, torch.randn(C, device="cuda")
+    d = rn.binding._conv_desc(x.shape, w.shape, stride, k // 2, rn.F32)
+
+    def chain(given):
+        ws = lambda f: torch.empty(max(1, f(d)), dtype=torch.uint8, device="cuda") if given else None
+        y = rn.conv_fwd(x, w, stride, k // 2, workspace=ws(rn.conv_fwd_workspace_bytes))
+        z, mean, rstd = rn.bn_relu_fwd(y, g, b)
+        dy, dres, dgamma, dbeta = rn.bn_relu_bwd(z, y, z, g, mean, rstd, beta=b)
+        assert dres is None
+        dx = torch.empty_like(x) if given else None
+        got = rn.conv_dgrad(dy, w, x.shape, stride, k // 2, dx=dx, workspace=ws(rn.conv_dgrad_workspace_bytes))
+        assert not given or got is dx
+        return y, z, mean, rstd, dy, dgamma, dbeta, got, rn.conv_wgrad(x, dy, w.shape, stride, k // 2, workspace=ws(rn.conv_wgrad_workspace_bytes))
+
+    want = [t.clone() for t in chain(False)]
+    torch.cuda.synchronize()
+    results = [None] * 3
+
+    def run(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for rep in range(4):
+                results[i] = chain(rep % 2 == 1)
+            torch.cuda.current_stream().synchronize()
+
+    threads = [threading.Thread(target=run, args=(i,)) for i in range(3)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    for r in results:
+        assert r is not None and all(torch.equal(a, e) for a, e in zip(r, want))
