@@ -140,13 +140,39 @@ __global__ __launch_bounds__(256) void lars_norms_kernel(const Args a) {
 // to be read.  Where all of it fits (kLarsStreamElems), the next update finds its operands cached instead.
 // 14.4 M parameters, bf16 gradients: 77.0 -> 65.1 us; 25.6 M, float: 134.6 -> 129.1; 2.5 M: 18.5 -> 21.9, hence the line.
 constexpr int64_t kLarsStreamElems = 8 << 20;  // 96 MB of w, g and v
+// A thread requests all that it updates in front of the tensor's two sums, so the operands are on their way while those are
+// added up.  Workgroups per chunk: where the launch streams from memory, many that load two vectors per thread once (25.6 M,
+// float: 129.2 -> 123.8 us, the update itself 6.8 TB/s; 25.6 M, bf16: 123.4 -> 121.4; 10 M: 56.9 -> 53.7; with 1 / 2 / 8 of them
+// 127.1 / 126.2 / 124.3, with bf16 128.4 / 124.0 / 123.5).  Where it hits the caches, one, since each adds up the sums again (2.5 M:
+// 17.9 -> 16.6, with two 18.5; 0.5 M: 12.6 -> 11.3).  From the last chunk to the first, to meet what the norms pass has read
+// last, is 0.5 to 2.5 % slower at every size.
+constexpr int lars_parts(bool stream) { return stream ? 4 : 1; }
 template <bool GBF16, bool STREAM, typename Args>
 __global__ __launch_bounds__(256) void lars_apply_kernel(const Args a) {
+  constexpr int kParts = lars_parts(STREAM), kPart = kLarsChunk / kParts;
   __shared__ float red[8];
-  const int chunk = blockIdx.x;
+  const int chunk = blockIdx.x / kParts, part = blockIdx.x % kParts;
   const int t = find_tensor(a, chunk);
   const rn50_lars_tensor T = a.tensor(t);
   const int c0 = a.chunk_prefix[t], c1 = a.chunk_prefix[t + 1];
+  const int64_t base = static_cast<int64_t>(chunk - c0) * kLarsChunk + part * kPart;
+  if (base >= T.n) return;
+  const int64_t end = min(base + static_cast<int64_t>(kPart), T.n);
+  const int64_t vend = base + ((end - base) & ~static_cast<int64_t>(3));
+  constexpr int NV = kPart / 1024;
+  float4 w4[NV];
+  f32x4 v4[NV];
+  float g4[NV][4];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int64_t i = base + threadIdx.x * 4 + k * 1024;
+    if (i < vend) {
+      w4[k] = *reinterpret_cast<const float4*>(T.w + i);
+      const f32x4* vp = reinterpret_cast<const f32x4*>(T.v + i);
+      v4[k] = STREAM ? __builtin_nontemporal_load(vp) : *vp;
+      load_g4<GBF16>(T.g, i, g4[k]);
+    }
+  }
   // Finish the two sums of this tensor: same order in every block of the tensor.
   float sw = 0.f, sg = 0.f;
   for (int c = c0 + threadIdx.x; c < c1; c += 256) {
@@ -160,38 +186,35 @@ __global__ __launch_bounds__(256) void lars_apply_kernel(const Args a) {
   if (T.apply_trust && wn > 0.f && gn > 0.f) local = a.eta * wn / (gn + T.weight_decay * wn + a.eps);
   const float lr = a.lr_dev ? *a.lr_dev : a.lr;
   const float step = lr * local, wd = T.weight_decay, mu = a.momentum;
-  if (chunk == c0 && threadIdx.x == 0 && a.norms_out) {
+  if (chunk == c0 && part == 0 && threadIdx.x == 0 && a.norms_out) {
     a.norms_out[2 * t] = wn;
     a.norms_out[2 * t + 1] = gn;
   }
-  const int64_t base = static_cast<int64_t>(chunk - c0) * kLarsChunk;
-  const int64_t end = min(base + static_cast<int64_t>(kLarsChunk), T.n);
-  const int64_t vend = base + ((end - base) & ~static_cast<int64_t>(3));
   uint16_t* lowp = static_cast<uint16_t*>(T.w_lowp);
-  for (int64_t i = base + threadIdx.x * 4; i < vend; i += 1024) {
-    float4 w4 = *reinterpret_cast<const float4*>(T.w + i);
-    const f32x4* vp = reinterpret_cast<const f32x4*>(T.v + i);
-    const f32x4 vv = STREAM ? __builtin_nontemporal_load(vp) : *vp;
-    float4 v4 = make_float4(vv[0], vv[1], vv[2], vv[3]);
-    float g4[4];
-    load_g4<GBF16>(T.g, i, g4);
-    v4.x = mu * v4.x + step * (g4[0] + wd * w4.x);
-    v4.y = mu * v4.y + step * (g4[1] + wd * w4.y);
-    v4.z = mu * v4.z + step * (g4[2] + wd * w4.z);
-    v4.w = mu * v4.w + step * (g4[3] + wd * w4.w);
-    w4.x -= v4.x; w4.y -= v4.y; w4.z -= v4.z; w4.w -= v4.w;
-    if (STREAM) {
-      __builtin_nontemporal_store(f32x4{v4.x, v4.y, v4.z, v4.w}, reinterpret_cast<f32x4*>(T.v + i));
-      __builtin_nontemporal_store(f32x4{w4.x, w4.y, w4.z, w4.w}, reinterpret_cast<f32x4*>(T.w + i));
-    } else {
-      *reinterpret_cast<float4*>(T.v + i) = v4;
-      *reinterpret_cast<float4*>(T.w + i) = w4;
-    }
-    if (lowp) {
-      uint2 p;
-      p.x = float2_to_bf16x2_bits(w4.x, w4.y);
-      p.y = float2_to_bf16x2_bits(w4.z, w4.w);
-      *reinterpret_cast<uint2*>(lowp + i) = p;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int64_t i = base + threadIdx.x * 4 + k * 1024;
+    if (i < vend) {
+      const float w[4] = {w4[k].x, w4[k].y, w4[k].z, w4[k].w};
+      f32x4 vn, wn4;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        vn[j] = mu * v4[k][j] + step * (g4[k][j] + wd * w[j]);
+        wn4[j] = w[j] - vn[j];
+      }
+      if (STREAM) {
+        __builtin_nontemporal_store(vn, reinterpret_cast<f32x4*>(T.v + i));
+        __builtin_nontemporal_store(wn4, reinterpret_cast<f32x4*>(T.w + i));
+      } else {
+        *reinterpret_cast<f32x4*>(T.v + i) = vn;
+        *reinterpret_cast<f32x4*>(T.w + i) = wn4;
+      }
+      if (lowp) {
+        uint2 p;
+        p.x = float2_to_bf16x2_bits(wn4[0], wn4[1]);
+        p.y = float2_to_bf16x2_bits(wn4[2], wn4[3]);
+        *reinterpret_cast<uint2*>(lowp + i) = p;
+      }
     }
   }
   for (int64_t i = vend + threadIdx.x; i < end; i += 256) {
@@ -254,9 +277,9 @@ void lars_arena_run(const LarsArenaSpec& sp, float* master, const float* grads, 
     const int grid = a.chunk_prefix[a.num];
     RN50_LAUNCH("lars_norms", (lars_norms_kernel<false, LarsArenaArgs>), dim3(grid), dim3(256), 0, s, a);
     if (arena_elems > kLarsStreamElems)
-      RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, true, LarsArenaArgs>), dim3(grid), dim3(256), 0, s, a);
+      RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, true, LarsArenaArgs>), dim3(grid * lars_parts(true)), dim3(256), 0, s, a);
     else
-      RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, false, LarsArenaArgs>), dim3(grid), dim3(256), 0, s, a);
+      RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, false, LarsArenaArgs>), dim3(grid * lars_parts(false)), dim3(256), 0, s, a);
     partial += 2 * static_cast<size_t>(grid);
   }
 }
@@ -290,12 +313,12 @@ static void run_table(const rn50_lars_desc* d, const rn50_lars_tensor* table_hos
     const bool stream = static_cast<int64_t>(grid) * kLarsChunk > kLarsStreamElems;
     if (a.grad_bf16) {
       RN50_LAUNCH("lars_norms", (lars_norms_kernel<true, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
-      if (stream) RN50_LAUNCH("lars_apply", (lars_apply_kernel<true, true, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
-      else RN50_LAUNCH("lars_apply", (lars_apply_kernel<true, false, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
+      if (stream) RN50_LAUNCH("lars_apply", (lars_apply_kernel<true, true, LarsArgs>), dim3(grid * lars_parts(true)), dim3(256), 0, s, a);
+      else RN50_LAUNCH("lars_apply", (lars_apply_kernel<true, false, LarsArgs>), dim3(grid * lars_parts(false)), dim3(256), 0, s, a);
     } else {
       RN50_LAUNCH("lars_norms", (lars_norms_kernel<false, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
-      if (stream) RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, true, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
-      else RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, false, LarsArgs>), dim3(grid), dim3(256), 0, s, a);
+      if (stream) RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, true, LarsArgs>), dim3(grid * lars_parts(true)), dim3(256), 0, s, a);
+      else RN50_LAUNCH("lars_apply", (lars_apply_kernel<false, false, LarsArgs>), dim3(grid * lars_parts(false)), dim3(256), 0, s, a);
     }
     partial += 2 * static_cast<size_t>(grid);
   }

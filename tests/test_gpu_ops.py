@@ -422,3 +422,31 @@ def test_calls_from_several_threads_and_streams(rn, C, hw, k, stride):
     [t.join() for t in threads]
     for r in results:
         assert r is not None and all(torch.equal(a, e) for a, e in zip(r, want))
+
+
+@pytest.mark.parametrize("grad_bf16", [False, True])
+@pytest.mark.parametrize("lowp", [False, True])
+def test_lars_parts_of_a_chunk(rn, grad_bf16, lowp):
+    """Launches that stream from memory split a chunk of 8,192 elements over four workgroups: tensors that end at and around
+    the parts' and chunks' boundaries, the vectors' remainders in each.  The expectation is the formula in double; w and v carry
+    the rounding of the norms (float, at most 2 ulp each) and of three float operations: 1e-6 relative to the tensor's scale."""
+    sizes = [1, 3, 1023, 2047, 2048, 2049, 4095, 4097, 6143, 6146, 8191, 8192, 8193, 8192 * 3 + 2049, (8 << 20) + 5]
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    rand = lambda n, s: torch.randn(n, device="cuda", generator=gen) * s
+    W, G, V = ([rand(n, s) for n in sizes] for s in (0.05, 1e-3, 1e-4))
+    if grad_bf16:
+        G = [g.bfloat16() for g in G]
+    L = [torch.zeros(n, device="cuda", dtype=torch.bfloat16) for n in sizes] if lowp else None
+    want = []
+    for w, g, v in zip(W, G, V):
+        w, g, v = w.double(), g.double(), v.double()
+        local = 0.001 * w.norm() / (g.norm() + 5e-5 * w.norm())
+        v = 0.9 * v + 0.5 * local * (g + 5e-5 * w)
+        want.append((w - v, v, torch.stack([w.norm(), g.norm()])))
+    norms = torch.zeros(2 * len(sizes), device="cuda")
+    rn.lars_update(rn.LarsTable(W, G, V, [5e-5] * len(sizes), w_lowp=L), 0.001, 0.9, 0.5, norms_out=norms)
+    for t, (w, v, n) in enumerate(want):
+        assert (W[t].double() - w).abs().max() <= 1e-6 * w.abs().max(), sizes[t]
+        assert (V[t].double() - v).abs().max() <= 1e-6 * v.abs().max(), sizes[t]
+        assert ((norms[2 * t:2 * t + 2].double() - n).abs() <= 1e-6 * n).all(), sizes[t]
+        assert L is None or torch.equal(L[t], W[t].bfloat16())
