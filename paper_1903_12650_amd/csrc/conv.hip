@@ -223,8 +223,14 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   int r0 = 0, s0 = 0, tstep = 1;
   if (classes) {
     // the four classes of one pixel range are neighbours in the tile order: they read the same rows of
-    // the incoming gradient, and every XCD gets its share of the classes that have taps
-    const int cls = a.fill ? 0 : mt & 3;
+    // the incoming gradient, and every XCD gets its share of the classes that have taps.  An XCD hands its workgroups to its
+    // 32 compute units in turn, so in one fixed order a compute unit would have tiles of one class only, four taps or one; the
+    // order changes every 32 workgroups, each second time to the opposite one (two tiles of a compute unit have five or four
+    // taps together).  3x3 / 2 data gradients, 128 -> 128 at 56x56 and 256 -> 256 at 28x28: batch 40 24.1 -> 22.1 and 19.5 -> 18.2
+    // us, float at batch 8 41.0 -> 33.9 and 42.6 -> 35.7, batch 256 157 -> 148 and 108 -> 107 (turned by one class each time
+    // 22.6 and 18.6, 34.4 and 35.9, 144 and 109).
+    const int turn = (mt >> 2) * a.ntn >> 3;
+    const int cls = a.fill ? 0 : (mt & 3) ^ ((turn & 1) * 3) ^ ((turn >> 1) & 1);
     m0 = (a.fill ? mt : mt >> 2) * BM;
     ph = cls >> 1; pw = cls & 1;
     Hc = (a.P - ph + 1) >> 1; Wc = (a.Q - pw + 1) >> 1;

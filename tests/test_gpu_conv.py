@@ -248,6 +248,23 @@ def test_strided_1x1_data_gradient_stores_every_pixel(rn, mode_name, N, H, W, C,
     assert torch.equal(dx == 0, want == 0)
 
 
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("N,H,W,C,K,R,pad", [(1, 1, 1, 8, 8, 3, 1), (2, 5, 4, 24, 40, 3, 1), (3, 57, 55, 72, 64, 3, 1), (2, 96, 97, 264, 64, 3, 1),
+                                             (5, 33, 35, 136, 128, 2, 0), (2, 61, 62, 520, 32, 5, 2)])
+def test_strided_data_gradient_takes_every_class_of_every_range_once(rn, mode_name, N, H, W, C, K, R, pad):
+    """The order of the four parity classes changes along the grid: images of one tile per class to many turns, one to nine column
+    tiles; into a buffer of NaNs."""
+    dt = torch.bfloat16 if mode_name == "bf16" else torch.float32
+    gen = torch.Generator().manual_seed(H * W + C)
+    w = (torch.randn(K, R, R, C, generator=gen) / (R * R * K) ** 0.5).to(dt)
+    dy = torch.randn(N, (H + 2 * pad - R) // 2 + 1, (W + 2 * pad - R) // 2 + 1, K, generator=gen).to(dt)
+    x = torch.zeros(N, C, H, W, dtype=torch.float64, requires_grad=True)
+    torch.nn.functional.conv2d(x, w.permute(0, 3, 1, 2).double(), stride=2, padding=pad).backward(dy.permute(0, 3, 1, 2).double())
+    dx = torch.full((N, H, W, C), float("nan"), device="cuda", dtype=dt)
+    rn.conv_dgrad(dy.cuda(), w.cuda(), dx.shape, 2, pad, dx=dx)
+    assert_close(dx, x.grad.permute(0, 2, 3, 1).contiguous().numpy(), TOL[mode_name], "dx")
+
+
 @pytest.mark.parametrize("N,H,W,C,K,R,stride", [(3, 120, 123, 64, 136, 1, 1), (3, 120, 123, 72, 136, 3, 1), (3, 241, 239, 16, 136, 3, 2),
                                                 (1, 200, 210, 8, 264, 1, 1), (2, 56, 57, 256, 840, 1, 1), (7, 224, 220, 3, 64, 7, 2)])
 def test_outputs_written_through(rn, N, H, W, C, K, R, stride):
