@@ -1,4 +1,5 @@
-"""ctypes binding of librn50_hip.so.  Same names as the C ABI (include/rn50_hip.h).
+"""Binding of librn50_hip.so: ctypes, and native code (csrc/python/ops.cpp) for the calls made once per layer.
+Same names as the C ABI (include/rn50_hip.h).
 
 Tensors are torch CUDA (ROCm) tensors used purely as device memory; work is
 enqueued on torch's current stream.  There is no CPU fallback: importing this

@@ -422,7 +422,8 @@ __global__ __launch_bounds__(kFinThreads) void bn_finalize_kernel(int64_t m, int
 // for the words of their channels.  Two launches in one, for grids of at most kBnShareGroups workgroups: 11 to 13 us for 4.6 to 5.5 +
 // 1.5 (between them) + 7 at 56x56, batch 40; the step at batch 12 2.518 -> 2.477 ms, batch 24 3.415 -> 3.359, batch 33 (208 px) 3.711 ->
 // 3.651, batch 40 4.339 -> 4.296.  In larger grids most workgroups start when the results are long there, and asking past the caches
-// costs each what a look into them does not (without a limit batch 90 and float at batch 8 lost 0.5 %).  kFinSelf stays for its
+// costs each what a look into them does not (without a limit batch 90 and float at batch 8 lost 0.5 %;
+// with a look into the caches first batch 90 loses 0.3 %, float nothing, and batch 256 gains 0.2 %).  kFinSelf stays for its
 // few rows: with kFinShared in its place (from 0 / 40 / 64 rows on) batch 12 loses 2.3 / 0.2 / 0.2 %.
 // The word is the message: relaxed atomics at device scope, nothing else is passed by memory within the launch.  It is made empty
 // by the convolution that produces the sums (IgemmArgs::slots).  No progress is assumed of the finalizing workgroups: after
