@@ -3,16 +3,18 @@
 // costs in the interpreter (a tensor allocation 1.3 us, an address with its checks 0.3, a converted argument 0.1, five to fifteen
 // of each) is longer: a float bottleneck block at batch 2, 21 calls, forward, backward and LARS, took 250 us for 188 us of GPU
 // time with the same steps in Python, and takes 218 with them here.
-// Signatures and defaults are those of the functions of the same names in binding.py, which are the callers; errors are raised as
-// there (AssertionError, TypeError, ValueError, Rn50Error).
+// Signatures and defaults are those of the functions of the same names in binding.py, which are the callers.  Errors are raised as
+// there (AssertionError, TypeError, ValueError, Rn50Error), and torch's own as torch raises them from Python (an allocation that
+// does not fit: torch.OutOfMemoryError), without a C++ backtrace in the text.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
-#include <stdexcept>
+#include <exception>
 #include <string>
 #include <vector>
 
 #include <ATen/ATen.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../../include/rn50_hip.h"
@@ -136,8 +138,8 @@ PyObject* guarded(Py_ssize_t n, Py_ssize_t want, F f) {
     return f();
   } catch (const PyError&) {
     return nullptr;
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
+  } catch (const std::exception&) {
+    torch::translate_exception_to_python(std::current_exception());
     return nullptr;
   }
 }
@@ -195,6 +197,7 @@ PyObject* conv_wgrad_py(PyObject*, PyObject* const* a, Py_ssize_t n) {
 }
 rn50_bn_desc bn_desc(const at::Tensor& x, PyObject* eps, PyObject* mode) {
   const int64_t C = x.size(-1);
+  if (x.dim() != 4 && C == 0) raise(PyExc_ZeroDivisionError, "channels");
   rn50_bn_desc d{1, 1, static_cast<int>(C ? x.numel() / C : 0), static_cast<int>(C), static_cast<float>(to_double(eps)), dtype_of(x), to_int(mode)};
   if (x.dim() == 4) {
     d.N = static_cast<int>(x.size(0)); d.H = static_cast<int>(x.size(1)); d.W = static_cast<int>(x.size(2));

@@ -174,3 +174,19 @@ def test_native_calls_refuse_what_they_cannot_take(call, error):
     import paper_1903_12650_amd as rn
     with pytest.raises(error):
         call(rn, torch.zeros(1, 8, 8, 8), torch.zeros(8, 1, 1, 8))
+
+
+@pytest.mark.parametrize("call, error", [
+    (lambda rn, x, w: rn.bn_relu_fwd(x[0, 0, 0, 0], w, w), IndexError),                        # torch's: no dimension
+    (lambda rn, x, w: rn.bn_relu_bwd(x, x[0, 0, 0, 0], x, w, w, w), IndexError),
+    (lambda rn, x, w: rn.bn_relu_fwd(x[0, 0, :, :0], w, w), ZeroDivisionError),                # no channels
+    (lambda rn, x, w: rn.conv_fwd(x, w.new_zeros(8, 11, 11, 8), 2, 0), RuntimeError),          # torch's: a negative size
+    (lambda rn, x, w: rn.conv_dgrad(x, w, (1 << 15, 1 << 14, 1 << 14, 8), 1, 0), RuntimeError),  # torch's: host memory
+])
+def test_native_calls_raise_torchs_errors_as_torch_does(call, error):
+    """The type that a program catches, and a message of a few lines: not the C++ backtrace that torch's exceptions carry."""
+    import torch
+    import paper_1903_12650_amd as rn
+    with pytest.raises(error) as e:
+        call(rn, torch.zeros(1, 8, 8, 8), torch.zeros(8, 1, 1, 8))
+    assert e.type is error and "frame #" not in str(e.value) and len(str(e.value)) < 400

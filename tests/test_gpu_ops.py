@@ -450,3 +450,20 @@ def test_lars_parts_of_a_chunk(rn, grad_bf16, lowp):
         assert (V[t].double() - v).abs().max() <= 1e-6 * v.abs().max(), sizes[t]
         assert ((norms[2 * t:2 * t + 2].double() - n).abs() <= 1e-6 * n).all(), sizes[t]
         assert L is None or torch.equal(L[t], W[t].bfloat16())
+
+
+def test_native_calls_run_out_of_memory_as_torch_does(rn):
+    """An output that does not fit raises what a program catches to try with less (the allocator's own limit, 3 % of the GPU,
+    refuses 16 GiB), and the next call works."""
+    x, w = torch.zeros(1, 8, 8, 8, device="cuda"), torch.zeros(8, 1, 1, 8, device="cuda")
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(0.03)
+    try:
+        with pytest.raises(torch.OutOfMemoryError) as e:
+            rn.conv_dgrad(x, w, (512, 1024, 1024, 8), 1, 0)
+        assert "frame #" not in str(e.value)
+        with pytest.raises(torch.OutOfMemoryError):
+            rn.conv_wgrad(x, x, (1 << 15, 1 << 8, 1 << 6, 8), 1, 0)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert rn.conv_dgrad(x, w, x.shape, 1, 0).shape == x.shape
