@@ -86,16 +86,15 @@ Shape4 shape4(const at::Tensor& t) {
   if (t.dim() != 4) raise(PyExc_ValueError, "a tensor of four dimensions is expected");
   return {{t.size(0), t.size(1), t.size(2), t.size(3)}};
 }
-Shape4 shape4(PyObject* seq) {
+Shape4 shape4(PyObject* shape) {  // (any iterable of four numbers)
   Shape4 s;
-  if (!PySequence_Check(seq) || PySequence_Size(seq) != 4) raise(PyExc_ValueError, "a shape of four dimensions is expected");
-  for (int i = 0; i < 4; ++i) {
-    PyObject* v = PySequence_GetItem(seq, i);
-    if (!v) throw PyError();
-    s.d[i] = PyLong_AsLongLong(v);
-    Py_DECREF(v);
-    if (s.d[i] == -1 && PyErr_Occurred()) throw PyError();
-  }
+  PyObject* seq = PySequence_Fast(shape, "a shape of four dimensions is expected");  // (a tuple or list is taken as it is)
+  if (!seq) throw PyError();
+  const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
+  for (Py_ssize_t i = 0; i < 4 && n == 4 && !PyErr_Occurred(); ++i) s.d[i] = PyLong_AsLongLong(PySequence_Fast_GET_ITEM(seq, i));
+  Py_DECREF(seq);
+  if (PyErr_Occurred()) throw PyError();
+  if (n != 4) raise(PyExc_ValueError, "a shape of four dimensions is expected");
   return s;
 }
 rn50_conv_desc conv_desc(const Shape4& x, const Shape4& w, PyObject* stride, PyObject* pad, int dtype) {

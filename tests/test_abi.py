@@ -190,3 +190,21 @@ def test_native_calls_raise_torchs_errors_as_torch_does(call, error):
     with pytest.raises(error) as e:
         call(rn, torch.zeros(1, 8, 8, 8), torch.zeros(8, 1, 1, 8))
     assert e.type is error and "frame #" not in str(e.value) and len(str(e.value)) < 400
+
+
+@pytest.mark.parametrize("shape, error", [
+    ((1, 8, 8, 8), AssertionError),                # taken; the host tensors are what is refused
+    ([1, 8, 8, 8], AssertionError),
+    (range(1, 5), AssertionError),                 # taken; the channels differ
+    (iter((1, 8, 8, 8)), AssertionError),
+    (5, TypeError),
+    ((1, 8, 8, "8"), TypeError),
+    ((1, 8, 8, 8, 8), ValueError),
+    ((), ValueError),
+])
+def test_shapes_are_any_iterable_of_four(shape, error):
+    import torch
+    import paper_1903_12650_amd as rn
+    x, w = torch.zeros(1, 8, 8, 8), torch.zeros(8, 1, 1, 8)
+    with pytest.raises(error):
+        rn.conv_dgrad(x, w, shape, 1, 0, dx=x)
