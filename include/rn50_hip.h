@@ -325,9 +325,6 @@ int resnet_plan_prepare(rn50_plan* plan);
  * step are bit for bit the same either way; only the time differs.  Off when the plan is created.
  * Applies to resnet_step / resnet_train_step (resnet_infer always stores every layer's output). */
 int resnet_plan_fuse_conv3_input(rn50_plan* plan, int on);
-/* How often a workgroup of a step asks for batch-norm statistics that another workgroup of its launch computes before it
- * computes them itself (default 2000).  No result depends on it; 0 = never ask. */
-int resnet_plan_wait_polls(rn50_plan* plan, int polls);
 int resnet_plan_num_tensors(const rn50_plan* plan);
 /* Shape of parameter tensor i: dims_out[4] = {K,R,S,C} for convolution weights,
  * {K,C,0,0} for the FC weight, {C,0,0,0} for vectors.  Returns the element count. */

@@ -462,11 +462,6 @@ class ResnetPlan:
         """conv3 of every block applies conv2's BN+ReLU in its operand load (same results, other timing)."""
         _check(raw.resnet_plan_fuse_conv3_input(self.handle, int(bool(on))))
 
-    def wait_polls(self, polls):
-        """How often a workgroup asks for statistics that another one of its launch computes before it computes them
-        itself (no result depends on it)."""
-        _check(raw.resnet_plan_wait_polls(self.handle, int(polls)))
-
 
 def resnet_step(plan, images, labels, master, velocity, grads, model, lr, workspace, update=True, loss_out=None,
                 logits_out=None):

@@ -354,9 +354,9 @@ extern "C" int resnet_plan_fuse_conv3_input(rn50_plan* plan, int on) {
   plan->fuse_conv3_input = on != 0;
   return RN50_OK;
 }
-extern "C" int resnet_plan_wait_polls(rn50_plan* plan, int polls) {
+extern "C" int rn50_internal_wait_polls(rn50_plan* plan, int polls) {
   clear_error();
-  RN50_REQUIRE(plan && polls >= 0, RN50_ERR_INVALID, "resnet_plan_wait_polls: null plan or negative count");
+  RN50_REQUIRE(plan && polls >= 0, RN50_ERR_INVALID, "rn50_internal_wait_polls: null plan or negative count");
   plan->bn_polls = polls;
   return RN50_OK;
 }

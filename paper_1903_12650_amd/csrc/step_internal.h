@@ -83,6 +83,9 @@ struct BnShare {
   unsigned long long* slots;
   int polls;
 };
+// Sets `polls` for a plan's steps (0: every workgroup computes what it needs itself).  Not part of the library's interface: no
+// value of it is of use to a caller.  The tests show with it that the results are the same whoever computed them.
+extern "C" int rn50_internal_wait_polls(rn50_plan* plan, int polls);
 
 // A BN+ReLU layer applied to a convolution's input on the fly (1x1, stride 1 convolutions only): its parameters
 // and saved statistics, float[Cin] each.

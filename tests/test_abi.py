@@ -35,6 +35,16 @@ def test_library_exports_every_declared_symbol():
         assert must in names
 
 
+def test_what_only_the_tests_call_is_not_in_the_interface():
+    """How long a workgroup waits for another's results changes no result: no business of the header or the binding."""
+    import paper_1903_12650_amd as rn
+    assert not any("polls" in n or "internal" in n for n in _declared())
+    assert not any("polls" in n for n in dir(rn) + dir(rn.ResnetPlan))
+    plan = rn.ResnetPlan(8, rn.BF16, 64, 10, (8, 8, 8, 8), (1, 1, 1, 1), 8, 4)
+    assert rn.raw.rn50_internal_wait_polls(plan.handle, 1) == 0
+    assert rn.raw.rn50_internal_wait_polls(plan.handle, -1) == -1 and rn.raw.rn50_internal_wait_polls(None, 1) == -1
+
+
 def test_host_side_argument_checks_need_no_gpu():
     import paper_1903_12650_amd as rn
     raw = rn.raw

@@ -470,7 +470,7 @@ def test_step_computes_the_same_statistics_whoever_computes_them(rn, mode, N):
     out = []
     for polls in (2000, 0):
         plan = rn.ResnetPlan(N, rn.BF16 if bf else rn.F32)
-        plan.wait_polls(polls)
+        assert rn.raw.rn50_internal_wait_polls(plan.handle, polls) == 0
         M = torch.empty(plan.arena_elems, device="cuda"); V = torch.empty_like(M); G = torch.zeros_like(M)
         rn.resnet_init_params(plan, SEED, M, V)
         Mod = M.to(torch.bfloat16) if bf else M
