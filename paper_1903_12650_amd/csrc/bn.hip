@@ -939,10 +939,12 @@ static void launch_fwd_tail(const rn50_bn_desc* d, int64_t m, const void* x,
     fin.wide = bn_reduced_rows(partial, nrows, d->C, false); fin.nwide = kBnReducedRows;
   }
   const BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnApplyGroups);
-  if (share && y && ga.nblk * ga.gy <= kBnShareGroups) {
-    fin.slots = share->slots; fin.groups = finalize_grid(d->C); fin.polls = share->polls; fin.nblk = ga.nblk;
-    RN50_FWD_APPLY(kFinShared, dim3(fin.groups + static_cast<unsigned>(ga.nblk) * ga.gy), nullptr, nullptr, ga.tx_log2, ga.rpb);
-    return;
+  if constexpr (LAST) {  // (only a step shares)
+    if (share && y && ga.nblk * ga.gy <= kBnShareGroups) {
+      fin.slots = share->slots; fin.groups = finalize_grid(d->C); fin.polls = share->polls; fin.nblk = ga.nblk;
+      RN50_FWD_APPLY(kFinShared, dim3(fin.groups + static_cast<unsigned>(ga.nblk) * ga.gy), nullptr, nullptr, ga.tx_log2, ga.rpb);
+      return;
+    }
   }
   RN50_LAUNCH("bn_finalize", bn_finalize_kernel<false>, dim3(finalize_grid(d->C)), dim3(kFinThreads), 0, s, m, d->C, fin);
   if (!y) return;  // statistics only: the consumer applies the layer while it loads its operand
@@ -976,7 +978,7 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
   if (!self && reduces && bn_reduces(nrows)) {
     fin.wide = bn_reduced_rows(partial, nrows, d->C, true); fin.nwide = kBnReducedRows;
   }
-    if (ga.nblk * ga.gy > kBnShareGroups) share = nullptr;
+  if (ga.nblk * ga.gy > kBnShareGroups) share = nullptr;
   dim3 grid;
   if (self) {
     // few tile rows: the apply pass adds them up itself
@@ -992,7 +994,7 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
     grid = dim3(ga.nblk, ga.gy);
   }
 #define RN50_BWD_APPLY_T(DZ2, ZK, FIN, THROUGH)                                                                           \
-  RN50_LAUNCH("bn_bwd_apply", (bn_bwd_apply_kernel<T, DZ2, ZK, FIN, LAST && ZK != 1, THROUGH>), grid, dim3(256), 0, s,       \
+  RN50_LAUNCH("bn_bwd_apply", (bn_bwd_apply_kernel<T, DZ2, ZK, FIN, LAST, THROUGH>), grid, dim3(256), 0, s,                  \
               static_cast<const T*>(dz), static_cast<const T*>(dz2), static_cast<const T*>(x),                     \
               static_cast<const T*>(z), zmask, gamma, beta, mean, rstd, dgamma, dbeta, static_cast<T*>(dx),        \
               static_cast<T*>(dres), m, d->C, ga.tx_log2, ga.rpb, d->mode, through, fin)
@@ -1006,7 +1008,7 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
       RN50_BWD_APPLY_K(DZ2, ZK, kFinSelf);                                        \
       break;                                                                      \
     }                                                                             \
-    if constexpr (LAST && !DZ2 && ZK != 1) {                                      \
+    if constexpr (LAST) {                                                         \
       if (share) {                                                                \
         RN50_BWD_APPLY_K(DZ2, ZK, kFinShared);                                    \
         break;                                                                    \
@@ -1015,11 +1017,17 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
     RN50_BWD_APPLY_K(DZ2, ZK, kFinGiven);                                         \
   } while (0)
   const int zk = d->mode == 0 ? 0 : (zmask ? 2 : (z ? 1 : 0));
-  if (dz2) {
-    if (zk == 2) RN50_BWD_APPLY(true, 2); else if (zk == 1) RN50_BWD_APPLY(true, 1); else RN50_BWD_APPLY(true, 0);
-  } else {
-    if (zk == 2) RN50_BWD_APPLY(false, 2); else if (zk == 1) RN50_BWD_APPLY(false, 1); else RN50_BWD_APPLY(false, 0);
+  if constexpr (!LAST) {  // (a step has one gradient, and its ReLU decisions from recorded bits or x)
+    if (dz2) {
+      if (zk == 2) RN50_BWD_APPLY(true, 2); else if (zk == 1) RN50_BWD_APPLY(true, 1); else RN50_BWD_APPLY(true, 0);
+      return;
+    }
+    if (zk == 1) {
+      RN50_BWD_APPLY(false, 1);
+      return;
+    }
   }
+  if (zk == 2) RN50_BWD_APPLY(false, 2); else RN50_BWD_APPLY(false, 0);
 #undef RN50_BWD_APPLY
 #undef RN50_BWD_APPLY_K
 #undef RN50_BWD_APPLY_T
@@ -1105,6 +1113,7 @@ void bn_bwd_run(const rn50_bn_desc* d, const void* dz, const void* dz2, const vo
                 void* dx, void* dres, float* dgamma, float* dbeta, float* scratch, bool last_reader, hipStream_t s) {
   const int64_t m = static_cast<int64_t>(d->N) * d->H * d->W;
   const BnGeom g = bn_sums_geom(m, d->C, d->dtype);
+  last_reader = last_reader && !dz2 && !z;  // (what is compiled: no step passes either)
   auto* run = d->dtype == RN50_BF16 ? (last_reader ? launch_bwd<uint16_t, true> : launch_bwd<uint16_t, false>)
                                     : (last_reader ? launch_bwd<float, true> : launch_bwd<float, false>);
   run(d, g, m, dz, dz2, x, z, relu_mask, gamma, beta, mean, rstd, dx, dres, dgamma, dbeta, scratch, s);

@@ -133,15 +133,11 @@ __device__ __forceinline__ Vec16 load16(const T* p) {
   v.u = *reinterpret_cast<const uint4*>(p);
   return v;
 }
-// The same past the caches: for what nobody reads again soon (or, stored, what is too large to be found there).
+// The same past the caches: for what nobody reads again soon.
 typedef int i32x4_nt __attribute__((ext_vector_type(4)));
 template <typename T>
 __device__ __forceinline__ Vec16 load16_stream(const T* p) {
   return __builtin_bit_cast(Vec16, __builtin_nontemporal_load(reinterpret_cast<const i32x4_nt*>(p)));
-}
-template <typename T>
-__device__ __forceinline__ void store16_stream(T* p, const Vec16& v) {
-  __builtin_nontemporal_store(__builtin_bit_cast(i32x4_nt, v), reinterpret_cast<i32x4_nt*>(p));
 }
 template <typename T>
 __device__ __forceinline__ void store16(T* p, const Vec16& v) {

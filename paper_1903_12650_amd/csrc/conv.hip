@@ -933,10 +933,16 @@ static void launch_igemm_through(IgemmArgs a, const char* tag, int64_t grid, hip
   }
   RN50_LAUNCH(tag, (igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN, false, THROUGH>), dim3(static_cast<unsigned>(grid)), dim3(NT), lds, s, a);
 }
+// Tiles of 128 columns: the rules give them to outputs of 6.6 MB and more (384 tiles of 128 rows, 192 of 256, by more than 64 columns;
+// smaller ones only with a few rows by tens of thousands of columns), so they are compiled for outputs that are written through.
+template <int BN>
+constexpr bool igemm_always_through() { return BN > 64; }
 template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN, bool BNIN = false>
 static void launch_igemm_mode(const IgemmArgs& a, const char* tag, int64_t grid, hipStream_t s) {
-  if (a.out_through) launch_igemm_through<T, BM, BN, WM, WN, MODE, LIN, BNIN, true>(a, tag, grid, s);
-  else launch_igemm_through<T, BM, BN, WM, WN, MODE, LIN, BNIN, false>(a, tag, grid, s);
+  if constexpr (!igemm_always_through<BN>()) {
+    if (!a.out_through) return launch_igemm_through<T, BM, BN, WM, WN, MODE, LIN, BNIN, false>(a, tag, grid, s);
+  }
+  launch_igemm_through<T, BM, BN, WM, WN, MODE, LIN, BNIN, true>(a, tag, grid, s);
 }
 // The halo kernel (3x3, stride 1, padding 1): LDS bytes of its main loop for an image width, or 0 when the shape
 // does not fit it (a run of more than 8 load passes, more LDS than a compute unit has).
@@ -964,9 +970,17 @@ static void launch_igemm_halo_through(IgemmArgs a, const char* tag, int64_t grid
 }
 template <typename T, int BM, int BN, int WM, int WN, int MODE>
 static void launch_igemm_halo(const IgemmArgs& a, const char* tag, int64_t grid, int main_lds, hipStream_t s) {
-  if (a.out_through) launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, true>(a, tag, grid, main_lds, s);
-  else launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, false>(a, tag, grid, main_lds, s);
+  if constexpr (!igemm_always_through<BN>()) {
+    if (!a.out_through) return launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, false>(a, tag, grid, main_lds, s);
+  }
+  launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, true>(a, tag, grid, main_lds, s);
 }
+// Tuning builds can force any tile on any layer; the product compiles what the rules below can choose.
+#ifdef RN50_TUNING
+constexpr bool kTuning = true;
+#else
+constexpr bool kTuning = false;
+#endif
 template <typename T, int BM, int BN, int WM, int WN>
 static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
   a.ntn = static_cast<int>(ceil_div(a.Ncols, BN));
@@ -977,7 +991,7 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
   a.fill = classes && a.R == 1 && a.S == 1 && a.partial == nullptr;
   a.mtiles = static_cast<int>(classes ? (a.fill ? 1 : 4) * tiles_per_class : ceil_div(a.M, BM));
   const int64_t grid = static_cast<int64_t>(a.mtiles) * a.ntn;
-  a.out_through = writes_through(static_cast<int64_t>(a.M) * a.Ncols * sizeof(T), kConvThroughBytes);
+  a.out_through = writes_through(static_cast<int64_t>(a.M) * a.Ncols * sizeof(T), igemm_always_through<BN>() ? 0 : kConvThroughBytes);
   a.partial_wide = bn_self_finalizes(a.mtiles, false);
   a.div_ntn = make_fastdiv(a.ntn);
   a.linear = a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0 && !a.pair && a.H == a.P && a.W == a.Q;
@@ -986,13 +1000,15 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
     a.div_h[c] = make_fastdiv(classes ? (a.P - c + 1) >> 1 : a.P);
   }
   if (a.linear) {
-    if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, true>(a, tag, grid, s);
-    else if (a.mode == 0 && a.in_gamma) launch_igemm_mode<T, BM, BN, WM, WN, 0, true, true>(a, tag, grid, s);
-    else if (a.mode == 0) launch_igemm_mode<T, BM, BN, WM, WN, 0, true>(a, tag, grid, s);
-    else launch_igemm_mode<T, BM, BN, WM, WN, 1, true>(a, tag, grid, s);
+    if (a.mode == 1) return launch_igemm_mode<T, BM, BN, WM, WN, 1, true>(a, tag, grid, s);
+    if constexpr (BM <= 128 || kTuning) {  // (igemm_tile: the eight-wave tile is for data gradients)
+      if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, true>(a, tag, grid, s);
+      else if (a.in_gamma) launch_igemm_mode<T, BM, BN, WM, WN, 0, true, true>(a, tag, grid, s);
+      else launch_igemm_mode<T, BM, BN, WM, WN, 0, true>(a, tag, grid, s);
+    }
     return;
   }
-  if constexpr (WM * WN > 1) {
+  if constexpr (WM * WN > 1 && (BM != 128 || BN != 128 || kTuning)) {  // (igemm_halo_tile never takes the 128x128 tile)
     if (const int halo_lds = igemm_halo_shape(a) ? halo_lds_bytes<BM, BN, WM, WN>(a.W, a.cpt) : 0) {
       if (a.mode == 2) launch_igemm_halo<T, BM, BN, WM, WN, 2>(a, tag, grid, halo_lds, s);
       else if (a.mode == 0) launch_igemm_halo<T, BM, BN, WM, WN, 0>(a, tag, grid, halo_lds, s);

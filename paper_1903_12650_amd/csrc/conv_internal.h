@@ -29,12 +29,6 @@ __device__ __forceinline__ Vec16 bn_relu_vector(const Vec16& v, const float* sca
 }
 constexpr uint32_t kOob = 0x80000000u;  // buffer offset beyond every tensor: the load returns zeros
 
-__device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t voffset, uint32_t soffset) {
-  typedef int v4i __attribute__((ext_vector_type(4)));
-  const v4i v = __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(voffset), static_cast<int>(soffset), 0);
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-
 // Barrier behind LDS writes of this wave (s_barrier alone does not wait for them), leaving vector-memory loads in flight.
 __device__ __forceinline__ void lds_writes_then_barrier() {
   asm volatile("" ::: "memory");
@@ -43,7 +37,7 @@ __device__ __forceinline__ void lds_writes_then_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// The same load with LDS as its destination (buffer_load_dwordx4 ... lds): lane l of the wave writes its 16
+// A 16-byte buffer load with LDS as its destination (buffer_load_dwordx4 ... lds): lane l of the wave writes its 16
 // bytes to LDS address lds_addr + 16*l (lds_addr uniform, taken from M0), so one instruction fills 1 KB; lanes
 // whose offset is out of range write zeros.  Nothing passes through registers; the transfer is counted by
 // vmcnt like any other vector-memory load.  Written as assembly on purpose: the compiler would make every
@@ -83,10 +77,9 @@ __device__ __forceinline__ void wait_loads_then_barrier() {
 // (BARRIER = false: a ring that only this wave fills and reads.)
 template <int NSTAGE, int NL, bool BARRIER = true>
 __device__ __forceinline__ void ring_wait(int chunks_after) {
-  static_assert(NSTAGE >= 2 && NSTAGE <= 6 && NL * (NSTAGE - 2) < 64, "ring depth");
+  static_assert(NSTAGE >= 2 && NSTAGE <= 5 && NL * (NSTAGE - 2) < 64, "ring depth");
   const int ahead = chunks_after < NSTAGE - 2 ? chunks_after : NSTAGE - 2;
-  if (NSTAGE >= 6 && ahead == 4) wait_loads_then_barrier<(NSTAGE >= 6 ? 4 : 0) * NL, BARRIER>();
-  else if (NSTAGE >= 5 && ahead == 3) wait_loads_then_barrier<(NSTAGE >= 5 ? 3 : 0) * NL, BARRIER>();
+  if (NSTAGE >= 5 && ahead == 3) wait_loads_then_barrier<(NSTAGE >= 5 ? 3 : 0) * NL, BARRIER>();
   else if (NSTAGE >= 4 && ahead == 2) wait_loads_then_barrier<(NSTAGE >= 4 ? 2 : 0) * NL, BARRIER>();
   else if (NSTAGE >= 3 && ahead == 1) wait_loads_then_barrier<(NSTAGE >= 3 ? 1 : 0) * NL, BARRIER>();
   else wait_loads_then_barrier<0, BARRIER>();

@@ -557,7 +557,7 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
   // g[0], g[1]: the two summands of the gradient w.r.t. the current block output (g[1] may be unused)
   STEP_TRY(avgpool_bwd(cfg.N, HW, plan->fc_in, dt, ws + plan->davg, g[0], s));
   int dgrad_sums_rows = 0;
-  // BN backward + wgrad + dgrad of one unit.  dz (+dz2) -> dy; dgrad into `dx` (skipped if null).
+  // BN backward + wgrad + dgrad of one unit.  dz -> dy; dgrad into `dx` (skipped if null).
   // `sums_ready`: the data gradient that produced dz already left this BN layer's sums in bn_ws.
   // `below`: the unit whose BN output is this unit's input, when dx (+ addend, the gradient of that
   // output's other consumer) is its complete dz: the data gradient then stores the sum and leaves that
@@ -593,27 +593,25 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
     npending = 0;
     ++blk;
   };
-  // Phase 1 of a unit: BN backward, dz (+dz2) -> dy (the unit's buffer; returned), on stream st with BN scratch wsx.
+  // Phase 1 of a unit: BN backward, dz -> dy (the unit's buffer; returned), on stream st with BN scratch wsx.
   // outer_bits: dz is still to be masked by the ReLU bits another layer recorded (the projection shortcut's
   // BN, whose output gradient is the block output's gradient under the block's ReLU): for the backward
   // arithmetic that is a BN+ReLU layer with recorded bits.
-  auto unit_bn_bwd = [&](Unit& u, const void* in, const void* dz, const void* dz2, void* dres, bool sums_ready,
-                         hipStream_t st, void* wsx, const uint8_t* outer_bits = nullptr,
-                         const BnIn* bn_in = nullptr) -> void* {
+  auto unit_bn_bwd = [&](Unit& u, const void* in, const void* dz, bool sums_ready, hipStream_t st, void* wsx,
+                         const uint8_t* outer_bits = nullptr, const BnIn* bn_in = nullptr) -> void* {
     void* dy = ws + u.dy;
     // the ReLU mask: recorded bits (residual-add layers) or recomputed from x (BN+ReLU layers)
     const uint8_t* bits = u.bn.mode == 2 ? ws + u.relu_mask : nullptr;
     if (outer_bits) {
       rn50_bn_desc masked = u.bn;
       masked.mode = 1;
-      bn_bwd_run(&masked, dz, dz2, ws + u.y, nullptr, outer_bits, MP(u.ig), MP(u.ib), F(u.mean), F(u.rstd), dy, nullptr,
+      bn_bwd_run(&masked, dz, nullptr, ws + u.y, nullptr, outer_bits, MP(u.ig), MP(u.ib), F(u.mean), F(u.rstd), dy, nullptr,
                  G(u.ig), G(u.ib), static_cast<float*>(wsx), true, st);
     } else if (sums_ready) {
       bn_bwd_from_partials(&u.bn, dz, ws + u.y, bits, MP(u.ig), MP(u.ib), F(u.mean), F(u.rstd),
-                           static_cast<const float*>(wsx), dgrad_sums_rows, dy, u.bn.mode == 2 ? dres : nullptr,
-                           G(u.ig), G(u.ib), true, st, &share);
+                           static_cast<const float*>(wsx), dgrad_sums_rows, dy, nullptr, G(u.ig), G(u.ib), true, st, &share);
     } else {
-      bn_bwd_run(&u.bn, dz, dz2, ws + u.y, nullptr, bits, MP(u.ig), MP(u.ib), F(u.mean), F(u.rstd), dy, dres, G(u.ig),
+      bn_bwd_run(&u.bn, dz, nullptr, ws + u.y, nullptr, bits, MP(u.ig), MP(u.ib), F(u.mean), F(u.rstd), dy, nullptr, G(u.ig),
                  G(u.ib), static_cast<float*>(wsx), true, st);
     }
     pending[npending++] = PendingWgrad{&u, in, dy, bn_in != nullptr, bn_in ? *bn_in : BnIn{}};
@@ -632,15 +630,10 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
     }
     dgrad_run(&u.conv, dy, W(u.iw), dx, below ? &fuse : nullptr, st);
   };
-  auto unit_bwd = [&](Unit& u, const void* in, const void* dz, const void* dz2, void* dres, void* dx,
-                      bool sums_ready, Unit* below, const void* addend) {
-    void* const dy = unit_bn_bwd(u, in, dz, dz2, dres, sums_ready, s, bn_ws);
-    if (dx) unit_dgrad(u, dy, dx, below, addend, s);
-  };
-  // dzo (+ dzo2): the gradient w.r.t. the current block's output; top_sums: its BN sums are in bn_ws.
+  // dzo: the gradient w.r.t. the current block's output; top_sums: its BN sums are in bn_ws.
   // It alternates between two buffers: a block's conv1 data gradient reads the old one (as the shortcut's
   // gradient) while it writes the new one.
-  const void *dzo = g[0], *dzo2 = nullptr;
+  const void *dzo = g[0], *dzo2 = nullptr;  // (dzo2: the max-pool's, behind the first block)
   unsigned char* dz_next = g[2];
   bool top_sums = false;
   for (int bi = static_cast<int>(plan->blocks.size()) - 1; bi >= 0; --bi) {
@@ -656,9 +649,9 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
     void* dy3 = nullptr;
     if (plan->fuse_conv3_input) {
       const BnIn in{MP(u2.ig), MP(u2.ib), F(u2.mean), F(u2.rstd)};
-      dy3 = unit_bn_bwd(u3, ws + u2.y, dzo, dzo2, nullptr, top_sums, s, bn_ws, nullptr, &in);
+      dy3 = unit_bn_bwd(u3, ws + u2.y, dzo, top_sums, s, bn_ws, nullptr, &in);
     } else {
-      dy3 = unit_bn_bwd(u3, ws + u2.z, dzo, dzo2, nullptr, top_sums, s, bn_ws);
+      dy3 = unit_bn_bwd(u3, ws + u2.z, dzo, top_sums, s, bn_ws);
     }
     const void* shortcut_grad = dzo;
     const uint8_t* shortcut_mask = ws + u3.relu_mask;
@@ -667,7 +660,7 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
       Unit& up = plan->units[b.up];
       (void)hipEventRecord(plan->ev_bfork, s);
       (void)hipStreamWaitEvent(branch, plan->ev_bfork, 0);
-      void* const dyp = unit_bn_bwd(up, block_in, dzo, dzo2, nullptr, false, branch, bn_ws2, ws + u3.relu_mask);
+      void* const dyp = unit_bn_bwd(up, block_in, dzo, false, branch, bn_ws2, ws + u3.relu_mask);
       // With stride 2 three of four pixels of the gradient are zero: it is kept without them (the product of dy's own pixel
       // grid), and conv1's data gradient adds it to the pixels it belongs to.  At batch 256 a gigabyte
       // of writes and reads of zeros per step; 19.93 -> 19.78 ms.
@@ -684,14 +677,15 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
       shortcut_mask = nullptr;
     }
     unit_dgrad(u3, dy3, g[4], &u2, nullptr, s);
-    unit_bwd(u2, ws + u1.z, g[4], nullptr, nullptr, g[4], true, &u1, nullptr);
-    void* const dy1 = unit_bn_bwd(u1, block_in, g[4], nullptr, nullptr, true, s, bn_ws);
+    void* const dy2 = unit_bn_bwd(u2, ws + u1.z, g[4], true, s, bn_ws);
+    unit_dgrad(u2, dy2, g[4], &u1, nullptr, s);
+    void* const dy1 = unit_bn_bwd(u1, block_in, g[4], true, s, bn_ws);
     if (b.up >= 0) (void)hipStreamWaitEvent(s, plan->ev_bjoin, 0);
     unsigned char* const dz_new = dz_next;
     dz_next = const_cast<unsigned char*>(static_cast<const unsigned char*>(dzo));
     if (prev) {
       unit_dgrad(u1, dy1, dz_new, prev, shortcut_grad, s, shortcut_mask, shortcut_even);
-      dzo = dz_new; dzo2 = nullptr; top_sums = true;
+      dzo = dz_new; top_sums = true;
     } else {  // the first block (it has a projection): the max-pool's backward pass adds the two branches
       unit_dgrad(u1, dy1, dz_new, nullptr, nullptr, s);
       dzo = dz_new; dzo2 = shortcut_grad; top_sums = false;
@@ -699,7 +693,7 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
     block_end();
   }
   STEP_TRY(maxpool_bwd(cfg.N, u0.P, u0.Q, cfg.stem, dt, nullptr, ws + plan->pool_argmax, dzo, dzo2, dz_next, s));
-  unit_bwd(u0, ws + plan->xp, dz_next, nullptr, nullptr, nullptr, false, nullptr, nullptr);
+  unit_bn_bwd(u0, ws + plan->xp, dz_next, false, s, bn_ws);
   block_end();
   // ------------------------------------------------------------------ LARS
   // (the groups before these two went with their blocks)  The side stream runs in order: the event of the last block but
