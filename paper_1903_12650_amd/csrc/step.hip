@@ -62,7 +62,7 @@ struct rn50_plan {
   // workspace layout (byte offsets)
   size_t ws_bytes = 0;
   size_t xp = 0, wp = 0, pool = 0, avg = 0, logits = 0, dlogits = 0, row_loss = 0, davg = 0;
-  size_t g[5] = {0, 0, 0, 0, 0};
+  size_t g[4] = {0, 0, 0, 0};
   size_t bn_slots = 0, bn_slots2 = 0;  // one word per channel and BN scratch (BnShare)
   int bn_polls = rn50::kBnPolls;
   size_t wgrad_scratch = 0, bn_scratch = 0, pool_argmax = 0, fc_scratch = 0;
@@ -257,7 +257,7 @@ extern "C" int resnet_plan_create(const rn50_step_config* cfg, rn50_plan** plan_
   p->logits = bump(&top, static_cast<size_t>(N) * cfg->classes * sizeof(float));
   p->dlogits = bump(&top, static_cast<size_t>(N) * cfg->classes * sizeof(float));
   p->row_loss = bump(&top, static_cast<size_t>(N) * sizeof(float));
-  for (int i = 0; i < 5; ++i) p->g[i] = bump(&top, max_act * es);
+  for (int i = 0; i < 4; ++i) p->g[i] = bump(&top, max_act * es);
   p->pool_argmax = bump(&top, static_cast<size_t>(N) * Hpool * Hpool * cfg->stem);
   // (dlogits in the storage type; without the matrix-core path fc_bwd needs nothing)
   p->fc_scratch_bytes = fc_mfma_ok(cin, cfg->classes, cfg->dtype) ? static_cast<size_t>(N) * cfg->classes * es : 0;
@@ -552,9 +552,9 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
   else
     STEP_TRY(fc_bwd(cfg.N, plan->fc_in, cfg.classes, dt, ws + plan->avg, W(fcw), F(plan->dlogits), ws + plan->davg,
                     nullptr, nullptr, ws + plan->fc_scratch, plan->fc_scratch_bytes, s));
-  unsigned char* g[5];
-  for (int i = 0; i < 5; ++i) g[i] = ws + plan->g[i];
-  // g[0], g[1]: the two summands of the gradient w.r.t. the current block output (g[1] may be unused)
+  // g[0], g[2]: the gradient w.r.t. a block's output, in turn; g[1]: a projection's; g[3]: within a block
+  unsigned char* g[4];
+  for (int i = 0; i < 4; ++i) g[i] = ws + plan->g[i];
   STEP_TRY(avgpool_bwd(cfg.N, HW, plan->fc_in, dt, ws + plan->davg, g[0], s));
   int dgrad_sums_rows = 0;
   // BN backward + wgrad + dgrad of one unit.  dz -> dy; dgrad into `dx` (skipped if null).
@@ -676,10 +676,10 @@ int run_step(const char* who, rn50_plan* plan, const void* images, const int32_t
       shortcut_grad = g[1];
       shortcut_mask = nullptr;
     }
-    unit_dgrad(u3, dy3, g[4], &u2, nullptr, s);
-    void* const dy2 = unit_bn_bwd(u2, ws + u1.z, g[4], true, s, bn_ws);
-    unit_dgrad(u2, dy2, g[4], &u1, nullptr, s);
-    void* const dy1 = unit_bn_bwd(u1, block_in, g[4], true, s, bn_ws);
+    unit_dgrad(u3, dy3, g[3], &u2, nullptr, s);
+    void* const dy2 = unit_bn_bwd(u2, ws + u1.z, g[3], true, s, bn_ws);
+    unit_dgrad(u2, dy2, g[3], &u1, nullptr, s);
+    void* const dy1 = unit_bn_bwd(u1, block_in, g[3], true, s, bn_ws);
     if (b.up >= 0) (void)hipStreamWaitEvent(s, plan->ev_bjoin, 0);
     unsigned char* const dz_new = dz_next;
     dz_next = const_cast<unsigned char*>(static_cast<const unsigned char*>(dzo));
