@@ -289,6 +289,72 @@ def test_outputs_written_through(rn, N, H, W, C, K, R, stride):
         assert_close(dx, want, TOL["bf16"], "dx")
 
 
+# Output pixel grids whose tensor is one column below, exactly and one column above the 1 MB from which convolutions write their
+# outputs through: columns, filter, stride, channels on the other side (64x64 tiles; the two K splits; the halo loop; the
+# strided gather and data gradient; 1x1 / stride 2 with its zeros; the stem).
+WRITE_LINE = [(64, 1, 1, 64), (64, 1, 1, 264), (64, 3, 1, 64), (8, 3, 1, 16), (72, 3, 2, 24), (64, 1, 2, 128), (64, 7, 2, 3)]
+
+
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("K,R,stride,C", WRITE_LINE)
+@pytest.mark.parametrize("beside", [-1, 0, 1])
+def test_outputs_on_either_side_of_the_write_through_line(rn, mode_name, K, R, stride, C, beside):
+    dt = torch.bfloat16 if mode_name == "bf16" else torch.float32
+    es, pad = 2 if mode_name == "bf16" else 4, R // 2
+    P = (1 << 20) // (es * K * 32)  # (narrow: the halo loop's run fits)
+    Q = -(-(1 << 20) // (es * K * P)) + beside
+    size = es * K * P * Q
+    assert (size < 1 << 20) == (beside < 0) and (beside or K == 72 or size == 1 << 20)
+    gen = torch.Generator().manual_seed(K + R + C)
+    rand = lambda *shape, scale=1.0: (torch.randn(*shape, generator=gen) * scale).to(dt)
+    nchw = lambda t: t.double().permute(0, 3, 1, 2)
+    nan = lambda shape: torch.full(shape, float("nan"), device="cuda", dtype=dt)
+    # forward: the output has the grid
+    x, w = rand(1, stride * P, stride * Q, C), rand(K, R, R, C, scale=(R * R * C) ** -0.5)
+    want = torch.nn.functional.conv2d(nchw(x), nchw(w), stride=stride, padding=pad).permute(0, 2, 3, 1).contiguous()
+    y = nan((1, P, Q, K))
+    assert want.shape == y.shape
+    rn.conv_fwd(x.cuda(), w.cuda(), stride, pad, y=y)
+    assert_close(y, want.numpy(), TOL[mode_name], "y")
+    y2 = nan(y.shape)
+    rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), stride, pad, y=y2)
+    assert torch.equal(y, y2)
+    if C == 3:
+        return
+    # data gradient: the input has the grid
+    w, po, qo = rand(C, R, R, K, scale=(R * R * C) ** -0.5), (P + 2 * pad - R) // stride + 1, (Q + 2 * pad - R) // stride + 1
+    dy = rand(1, po, qo, C)
+    want = torch.nn.grad.conv2d_input((1, K, P, Q), nchw(w), nchw(dy), stride=stride, padding=pad).permute(0, 2, 3, 1).contiguous()
+    dx = nan((1, P, Q, K))
+    rn.conv_dgrad(dy.cuda(), w.cuda(), dx.shape, stride, pad, dx=dx)
+    assert_close(dx, want.numpy(), TOL[mode_name], "dx")
+    one, zero = torch.ones(K, device="cuda"), torch.zeros(K, device="cuda")
+    dx2 = nan(dx.shape)
+    rn.conv_dgrad_bn_sums(dy.cuda(), w.cuda(), dx.shape, stride, pad, torch.ones_like(dx), one, zero, zero, one, dx=dx2)
+    assert torch.equal(dx, dx2)
+
+
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("C,K,R", [(64, 64, 1), (72, 72, 1), (128, 136, 1), (136, 128, 1), (200, 264, 1), (64, 72, 3), (64, 64, 3), (56, 64, 3), (64, 56, 3)])
+@pytest.mark.parametrize("N,hw", [(1, 7), (6, 28)])
+def test_weight_gradient_whole_and_ragged_tiles(rn, mode_name, C, K, R, N, hw):
+    """Whole tiles are stored row by row from a scalar offset, ragged ones element by element, side by side in one result:
+    channel counts with either and both, one split (the result itself) and many (partial sums), into NaNs; twice the same bits."""
+    dt = torch.bfloat16 if mode_name == "bf16" else torch.float32
+    gen = torch.Generator().manual_seed(C + K)
+    x, dy = torch.randn(N, hw, hw, C, generator=gen).to(dt), torch.randn(N, hw, hw, K, generator=gen).to(dt)
+    nchw = lambda t: t.double().permute(0, 3, 1, 2)
+    want = torch.nn.grad.conv2d_weight(nchw(x), (K, C, R, R), nchw(dy), padding=R // 2).permute(0, 2, 3, 1).contiguous()
+    d = rn.ConvDesc(N, hw, hw, C, K, R, R, 1, R // 2, rn.BF16 if mode_name == "bf16" else rn.F32)
+    got = []
+    for _ in range(2):
+        dw = torch.full((K, R, R, C), float("nan"), device="cuda")
+        ws = torch.full((max(rn.conv_wgrad_workspace_bytes(d), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+        got.append(rn.conv_wgrad(x.cuda(), dy.cuda(), dw.shape, 1, R // 2, dw=dw, workspace=ws))
+    assert_close(got[0], want.numpy(), TOL[mode_name], "dw")
+    assert torch.equal(got[0], got[1])
+
+
 # Weight gradient: tiles that span filter taps, channel counts at the edges of the tile widths, pixel ranges of less than one
 # chunk, one chunk more than a whole number of splits, and the most splits.
 WGRAD_EDGES = [(1, 3, 3, 40, 64, 3, 1, 1), (2, 8, 8, 64, 72, 1, 1, 0), (2, 8, 8, 72, 64, 1, 1, 0), (1, 1, 1, 128, 128, 3, 1, 1),

@@ -387,6 +387,31 @@ def test_abi_error_codes(rn):
     assert e.value.code == -4
 
 
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("C", [64, 512])
+@pytest.mark.parametrize("beside", [-1, 0, 1])
+def test_bn_outputs_on_either_side_of_the_write_through_line(rn, mode_name, C, beside):
+    """The apply passes write outputs of 10 MB and more through the caches: one row less, exactly that, one row more, with
+    finalize launches (64 channels) and, in float, without (512: few rows), residual and second gradient; against doubles."""
+    dt, es = (torch.bfloat16, 2) if mode_name == "bf16" else (torch.float32, 4)
+    m = (10 << 20) // (es * C) + beside
+    gen = torch.Generator(device="cuda").manual_seed(C)
+    x, r, dz, dz2 = (torch.randn(m, C, device="cuda", generator=gen).to(dt) for _ in range(4))
+    g, b = torch.rand(C, device="cuda", generator=gen) + 0.5, torch.randn(C, device="cuda", generator=gen)
+    y, mean, rstd = rn.bn_relu_fwd(x, g, b, r, 1e-5, 2)
+    xd, gd = x.double(), g.double()
+    mu, var = xd.mean(0), xd.var(0, unbiased=False)
+    rs = (var + 1e-5).rsqrt()
+    xh = (xd - mu) * rs
+    assert_close(y, (xh * gd + b.double() + r.double()).clamp(min=0).cpu().numpy(), TOL[mode_name], "y")
+    dx, dres, dg, db = rn.bn_relu_bwd(dz, x, y, g, mean, rstd, 2, beta=b, dz2=dz2)
+    gr = (dz.double() + dz2.double()) * (y > 0)  # (the pass's own decisions)
+    assert_close(dres, gr.cpu().numpy(), TOL[mode_name], "dres")
+    assert_close(db, gr.sum(0).cpu().numpy(), TOL[mode_name], "dbeta")
+    assert_close(dg, (gr * xh).sum(0).cpu().numpy(), TOL[mode_name], "dgamma")
+    assert_close(dx, (gd * rs * (gr - gr.mean(0) - xh * (gr * xh).mean(0))).cpu().numpy(), TOL[mode_name], "dx")
+
+
 @pytest.mark.parametrize("C, hw, k, stride", [(64, 14, 3, 2), (128, 7, 1, 1)])
 def test_calls_from_several_threads_and_streams(rn, C, hw, k, stride):
     """The per-layer calls allocate, enqueue and release the interpreter in native code: three threads, each on a stream of its
