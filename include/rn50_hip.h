@@ -323,7 +323,7 @@ int resnet_plan_prepare(rn50_plan* plan);
  * (conv_fwd_bn_in in the forward pass, conv_wgrad_bn_in for conv3's weight gradient): conv2's BN
  * pass only finalises its statistics and its normalised output is never stored.  Results of the
  * step are bit for bit the same either way; only the time differs.  Off when the plan is created.
- * Applies to resnet_step / resnet_train_step (resnet_infer always stores every layer's output). */
+ * Applies to resnet_step / resnet_train_step (resnet_eval always stores every layer's output). */
 int resnet_plan_fuse_conv3_input(rn50_plan* plan, int on);
 int resnet_plan_num_tensors(const rn50_plan* plan);
 /* Shape of parameter tensor i: dims_out[4] = {K,R,S,C} for convolution weights,

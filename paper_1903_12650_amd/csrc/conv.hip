@@ -1000,9 +1000,9 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
     a.div_h[c] = make_fastdiv(classes ? (a.P - c + 1) >> 1 : a.P);
   }
   if (a.linear) {
-    if (a.mode == 1) return launch_igemm_mode<T, BM, BN, WM, WN, 1, true>(a, tag, grid, s);
-    if constexpr (BM <= 128 || kTuning) {  // (igemm_tile: the eight-wave tile is for data gradients)
-      if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, true>(a, tag, grid, s);
+    if constexpr (BM <= 128 || kTuning) {  // (the eight-wave tile is igemm_halo_tile's alone)
+      if (a.mode == 1) launch_igemm_mode<T, BM, BN, WM, WN, 1, true>(a, tag, grid, s);
+      else if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, true>(a, tag, grid, s);
       else if (a.in_gamma) launch_igemm_mode<T, BM, BN, WM, WN, 0, true, true>(a, tag, grid, s);
       else launch_igemm_mode<T, BM, BN, WM, WN, 0, true>(a, tag, grid, s);
     }
@@ -1035,14 +1035,14 @@ struct TileShape {
 // workgroups per compute unit wins -- larger tiles load fewer operand bytes per flop (the main loop's bound) but with a smaller
 // grid the latencies of a workgroup's load -> LDS -> MFMA chain are exposed; a reduction of one chunk has nothing to reuse and
 // takes the smallest tile.
-static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool dgrad, bool strided_dgrad, int live = 4) {
+static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool strided_dgrad, int live = 4) {
   const int64_t classes = strided_dgrad ? live : 1;
   auto groups = [&](int bm, int bn) { return ceil_div(M, bm) * ceil_div(Ncols, bn) * classes; };
   constexpr int64_t kCover = 384;  // workgroups: one and a half per compute unit (two four-wave workgroups fit each)
   if (chunks <= 1) return TileShape{64, 64, 2, 2};
   if (Ncols > 64) {
-    // (the eight-wave tile pays off in the data gradients of the largest layers only)
-    if (dgrad && chunks >= 2 && groups(256, 128) >= 4 * kCover) return TileShape{256, 128, 4, 2};
+    // (not the eight-wave 256x128 tile, also in the largest data gradients, which had it from 1536 tiles on: 22 shapes at batch 256
+    // 3668 -> 3504 us without it, 128 1812 -> 1775; in the step at batch 256 19.49 -> 19.31 ms)
     if (groups(128, 128) >= kCover) return TileShape{128, 128, 2, 2};
   }
   if (chunks >= 8 && groups(128, 64) >= kCover) return TileShape{128, 64, 2, 2};
@@ -1083,8 +1083,8 @@ static bool igemm_halo_shape(const IgemmArgs& a) {
 // compute unit of the shared ring do better.  Limits of 0 / 128 / 256 / 384 / 512 tiles in the whole step: float at batch 8 4.75 /
 // 4.13 / 4.06 / 4.06 / 4.49 ms, bf16 at batch 40 4.373 / 4.371 / 4.356 / 4.352 / 4.630 (profiles/step_time_against_dispatch_constants.txt;
 // layer by layer: profiles/conv_tile_sweep_*.txt).
-static TileShape pick_tile(int64_t rows, int Ncols, int chunks, bool dgrad, bool strided_dgrad, int live, bool halo,
-                           int lin_fwd_channels, int dtype) {
+static TileShape pick_tile(int64_t rows, int Ncols, int chunks, bool strided_dgrad, int live, bool halo, int lin_fwd_channels,
+                           int dtype) {
 #ifdef RN50_TUNING  // tuning builds only: RN50_IGEMM_TILE=bm,bn,wm,wn forces a compiled tile shape
   if (const char* e = getenv("RN50_IGEMM_TILE")) {
     TileShape f{0, 0, 0, 0};
@@ -1101,14 +1101,14 @@ static TileShape pick_tile(int64_t rows, int Ncols, int chunks, bool dgrad, bool
     if (groups64 > 128) return TileShape{64, 64, 1, 1};
     return dtype == RN50_F32 ? TileShape{32, 32, 1, 1} : TileShape{32, 64, 1, 1};
   }
-  return halo ? igemm_halo_tile(rows, Ncols) : igemm_tile(rows, Ncols, chunks, dgrad, strided_dgrad, live);
+  return halo ? igemm_halo_tile(rows, Ncols) : igemm_tile(rows, Ncols, chunks, strided_dgrad, live);
 }
 template <typename T>
 static void launch_igemm(const IgemmArgs& a, const char* tag, hipStream_t s) {
   const bool classes = a.mode == 1 && a.stride == 2;
   const int64_t rows = classes ? static_cast<int64_t>(a.M / (a.P * a.Q)) * ((a.P + 1) / 2) * ((a.Q + 1) / 2) : a.M;
   const bool lin_fwd = a.mode != 1 && a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0 && !a.pair;
-  const TileShape t = pick_tile(rows, a.Ncols, a.R * a.S * a.cpt, a.mode == 1, classes, a.R * a.S > 1 ? 4 : 1,
+  const TileShape t = pick_tile(rows, a.Ncols, a.R * a.S * a.cpt, classes, a.R * a.S > 1 ? 4 : 1,
                                 igemm_halo_shape(a), lin_fwd ? a.Cg : 0, sizeof(T) == 2 ? RN50_BF16 : RN50_F32);
 #define X(BM, BN, WM, WN) if (t.bm == BM && t.bn == BN && t.wm == WM && t.wn == WN) launch_igemm_cfg<T, BM, BN, WM, WN>(a, tag, s);
   RN50_IGEMM_SHAPES(X)
@@ -1170,7 +1170,7 @@ static int chunks_per_tap(int channels, int dtype) { return static_cast<int>(cei
 // stride-2 data gradient: four parity classes of ceil(N * ceil(H/2) * ceil(W/2) / bm) row tiles each
 static PartialRows class_tile_rows(const rn50_conv_desc* d) {
   const int64_t rows = static_cast<int64_t>(d->N) * ((d->H + 1) / 2) * ((d->W + 1) / 2);
-  const int bm = pick_tile(rows, d->Cin, d->R * d->S * chunks_per_tap(d->Cout, d->dtype), true, true, d->R * d->S > 1 ? 4 : 1,
+  const int bm = pick_tile(rows, d->Cin, d->R * d->S * chunks_per_tap(d->Cout, d->dtype), true, d->R * d->S > 1 ? 4 : 1,
                            false, 0, d->dtype).bm;
   return PartialRows{bm, static_cast<int>(4 * ceil_div(rows, bm))};
 }
@@ -1180,7 +1180,7 @@ PartialRows fwd_partial_rows(const rn50_conv_desc* d) {
   // the chunk count as the launch computes it (the bf16 stem runs as 4 taps of one chunk, the float stem as 7)
   const int chunks = is_stem(d) ? (d->dtype == RN50_BF16 ? 4 : 7) : d->R * d->S * chunks_per_tap(d->Cin, d->dtype);
   const bool lin = d->R == 1 && d->S == 1 && d->stride == 1 && d->pad == 0;
-  const int bm = pick_tile(M, d->Cout, chunks, false, false, 4, halo_filter(d->R, d->S, d->stride, d->pad), lin ? d->Cin : 0, d->dtype).bm;
+  const int bm = pick_tile(M, d->Cout, chunks, false, 4, halo_filter(d->R, d->S, d->stride, d->pad), lin ? d->Cin : 0, d->dtype).bm;
   return PartialRows{bm, static_cast<int>(ceil_div(M, bm))};
 }
 int64_t dgrad_partial_rows_bound(const rn50_conv_desc* d) {
@@ -1191,7 +1191,7 @@ int64_t dgrad_partial_rows_bound(const rn50_conv_desc* d) {
 PartialRows dgrad_partial_rows(const rn50_conv_desc* d) {
   if (d->stride == 2) return class_tile_rows(d);
   const int64_t M = static_cast<int64_t>(d->N) * d->H * d->W;
-  const int bm = pick_tile(M, d->Cin, d->R * d->S * chunks_per_tap(d->Cout, d->dtype), true, false, 4,
+  const int bm = pick_tile(M, d->Cin, d->R * d->S * chunks_per_tap(d->Cout, d->dtype), false, 4,
                            halo_filter(d->R, d->S, d->stride, d->pad), 0, d->dtype).bm;
   return PartialRows{bm, static_cast<int>(ceil_div(M, bm))};
 }

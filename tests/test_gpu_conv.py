@@ -289,6 +289,27 @@ def test_outputs_written_through(rn, N, H, W, C, K, R, stride):
         assert_close(dx, want, TOL["bf16"], "dx")
 
 
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("N,H,W,C,K", [(3, 128, 130, 16, 72), (2, 191, 129, 40, 136)])
+def test_images_too_wide_for_the_halo_loop(rn, mode_name, N, H, W, C, K):
+    """3x3 / stride 1 on the eight-wave tile (from 192 of them on) where its run of pixels has no room: the gathering loop, forward with
+    and without sums, data gradient with and without."""
+    dt = torch.bfloat16 if mode_name == "bf16" else torch.float32
+    gen = torch.Generator().manual_seed(W + K)
+    rand = lambda *shape, scale=1.0: (torch.randn(*shape, generator=gen) * scale).to(dt)
+    nchw = lambda t: t.double().permute(0, 3, 1, 2)
+    x, w, dy, wt = rand(N, H, W, C), rand(K, 3, 3, C, scale=(9 * C) ** -0.5), rand(N, H, W, C), rand(C, 3, 3, K, scale=(9 * C) ** -0.5)
+    want = torch.nn.functional.conv2d(nchw(x), nchw(w), padding=1).permute(0, 2, 3, 1).contiguous()
+    y = rn.conv_fwd(x.cuda(), w.cuda(), 1, 1)
+    assert_close(y, want.numpy(), TOL[mode_name], "y")
+    assert torch.equal(y, rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), 1, 1)[0])
+    want = torch.nn.grad.conv2d_input((N, K, H, W), nchw(wt), nchw(dy), padding=1).permute(0, 2, 3, 1).contiguous()
+    dx = rn.conv_dgrad(dy.cuda(), wt.cuda(), y.shape, 1, 1)
+    assert_close(dx, want.numpy(), TOL[mode_name], "dx")
+    one, zero = torch.ones(K, device="cuda"), torch.zeros(K, device="cuda")
+    assert torch.equal(dx, rn.conv_dgrad_bn_sums(dy.cuda(), wt.cuda(), y.shape, 1, 1, y, one, zero, zero, one)[0])
+
+
 # Output pixel grids whose tensor is one column below, exactly and one column above the 1 MB from which convolutions write their
 # outputs through: columns, filter, stride, channels on the other side (64x64 tiles; the two K splits; the halo loop; the
 # strided gather and data gradient; 1x1 / stride 2 with its zeros; the stem).
