@@ -64,8 +64,8 @@ static BnGeom bn_geom(int64_t m, int C, int dtype) {
 // at least 32 rows, as doubles, and their apply pass finalizes by itself (bn_apply_kernel's FIN): a finalize launch costs
 // about 4 us whatever it computes, reading 128 rows of sums in every apply workgroup 1 to 2 -- as long as the workgroups
 // are few: beyond kBnSelfElems the sums they read together are as many bytes as the tensor.  Nine layers, both directions, batch
-// 8 / 40: 272 / 485 us; never 311 / 501; up to 8192 rows 278 / 488; up to 16 M elements 280 / 495
-// (profiles/bn_standalone_sums_forms.txt).
+// 4 / 8 / 40: 211 / 231 / 469 us; never 219 / 240 / 464; up to 8192 rows 209 / 231 / 465; up to 16 M elements 212 / 240 / 480
+// (profiles/bn_standalone_sums_forms.txt; 28x28x128 at batch 40, 31,360 rows, is 3 us slower for it, 56x56x64 at batch 8 1 us faster).
 // Larger layers: up to kBnSumsGroups workgroups whose threads load their eight rows (kBnSumsRows) once.  Workgroups that
 // loop over more rows all load at the same time and all compute at the same time.
 constexpr int64_t kBnSelfRows = 32768, kBnSelfElems = 4 << 20;
@@ -420,16 +420,20 @@ __global__ __launch_bounds__(kFinThreads) void bn_finalize_kernel(int64_t m, int
 // workgroup adds up the tile rows of its channels.  kFinShared: the first `groups` workgroups of the same launch finalize, two
 // channels each, and publish the two results of a channel as one 64-bit word; the others request their rows of x and then ask
 // for the words of their channels.  Two launches in one, for grids of at most kBnShareGroups workgroups: 11 to 13 us for 4.6 to 5.5 +
-// 1.5 (between them) + 7 at 56x56, batch 40; the step at batch 12 2.518 -> 2.477 ms, batch 24 3.415 -> 3.359, batch 33 (208 px) 3.711 ->
-// 3.651, batch 40 4.339 -> 4.296.  In larger grids most workgroups start when the results are long there, and asking past the caches
-// costs each what a look into them does not (without a limit batch 90 and float at batch 8 lost 0.5 %;
-// with a look into the caches first batch 90 loses 0.3 %, float nothing, and batch 256 gains 0.2 %).  kFinSelf stays for its
-// few rows: with kFinShared in its place (from 0 / 40 / 64 rows on) batch 12 loses 2.3 / 0.2 / 0.2 %.
+// 1.5 (between them) + 7 at 56x56, batch 40.  Four workgroups of these kernels are on a compute unit at a time (117 to 126 registers,
+// as without the sharing), 1024 on the chip: a grid at the limit runs in two rounds and a few, the later ones of which find the
+// results there.  Where the limit lies hardly matters: the step with limits of 0 / 1024 / 2048 / 4096 workgroups / none, ms
+// (profiles/step_time_against_dispatch_constants.txt):
+//   batch 12 2.498 / 2.438 / 2.439 / 2.439 / 2.439, 24 3.368 / 3.336 / 3.320 / 3.319 / 3.317, 40 4.272 / 4.244 / 4.235 / 4.235 / 4.236,
+//   90 8.070 / 8.029 / 8.029 / 7.978 / 7.954, 256 19.17 / 19.16 / 19.17 / 19.16 / 19.09, float at batch 8 4.013 / 4.004 / 4.016 /
+//   4.011 / 4.014;
+// resnet_train_step at batch 90 and 192 px, 33 and 208 px, float gradients at batch 8: the same with the limit and without.
+// kFinSelf stays for its few rows: with kFinShared in its place (from 0 / 40 / 64 rows on) batch 12 loses 2.3 / 0.2 / 0.2 %.
 // The word is the message: relaxed atomics at device scope, nothing else is passed by memory within the launch.  It is made empty
 // by the convolution that produces the sums (IgemmArgs::slots).  No progress is assumed of the finalizing workgroups: after
 // `polls` unanswered questions a workgroup computes what it needs itself, in the same order, so every wait ends and the results
 // do not depend on who computed them.
-constexpr int kBnShareGroups = 2048;  // eight per compute unit: all there at once
+constexpr int kBnShareGroups = 2048;
 enum BnFin { kFinGiven, kFinSelf, kFinShared };
 __device__ __forceinline__ void publish_results(unsigned long long* slot, float a, float b) {
   unsigned long long v = static_cast<unsigned long long>(__float_as_uint(b)) << 32 | __float_as_uint(a);

@@ -1034,7 +1034,10 @@ struct TileShape {
 // batch 256 (profiles/conv_tile_sweep_*.txt): the largest tile that still leaves about one and a half
 // workgroups per compute unit wins -- larger tiles load fewer operand bytes per flop (the main loop's bound) but with a smaller
 // grid the latencies of a workgroup's load -> LDS -> MFMA chain are exposed; a reduction of one chunk has nothing to reuse and
-// takes the smallest tile.
+// takes the smallest tile (64 -> 64 at 56x56, batch 256, 30 us against 31 and 45 for 128x64 and 128x128, batch 40 5.2 against 5.6 and
+// 8.7; larger tiles would be faster where the largest data gradient has more columns: 256 <- 64 at 56x56, batch 256, 140 us against
+// 125 and 111, but 15.3 against 15.0 and 16.3 at batch 40).  Summed over the shapes the rule is within 2 % of the best tiles at
+// batch 40 and within 4 % at 256.
 static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool strided_dgrad, int live = 4) {
   const int64_t classes = strided_dgrad ? live : 1;
   auto groups = [&](int bm, int bn) { return ceil_div(M, bm) * ceil_div(Ncols, bn) * classes; };
@@ -1080,8 +1083,8 @@ static bool igemm_halo_shape(const IgemmArgs& a) {
 // both directions), so that twice (four times) as many compute units work.  Measured on the whole float gradient pass (batch 4:
 // 4055 -> 2919 us, batch 8: 4752 -> 4024, batch 16: 6789 -> 6384) and on single layers (2048 -> 512 channels at 7x7,
 // batch 40: 14.0 -> 9.3 us; 3x3 512 -> 512 at 7x7, batch 12: 28.7 -> 14.4); with 257 to 512 tiles the two workgroups per
-// compute unit of the shared ring do better.  Limits of 0 / 128 / 256 / 384 / 512 tiles in the whole step: float at batch 8 4.75 /
-// 4.13 / 4.06 / 4.06 / 4.49 ms, bf16 at batch 40 4.373 / 4.371 / 4.356 / 4.352 / 4.630 (profiles/step_time_against_dispatch_constants.txt;
+// compute unit of the shared ring do better.  Limits of 0 / 128 / 256 / 384 / 512 tiles in the whole step: float at batch 8 4.77 /
+// 4.12 / 4.02 / 4.02 / 4.40 ms, bf16 at batch 40 4.250 / 4.253 / 4.240 / 4.242 / 4.499 (profiles/step_time_against_dispatch_constants.txt;
 // layer by layer: profiles/conv_tile_sweep_*.txt).
 static TileShape pick_tile(int64_t rows, int Ncols, int chunks, bool strided_dgrad, int live, bool halo, int lin_fwd_channels,
                            int dtype) {

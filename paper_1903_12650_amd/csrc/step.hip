@@ -128,8 +128,8 @@ size_t bump(size_t* top, size_t bytes) {
 // as the backward pass has left the block, beside what is left of it: 40 % of the parameters belong to the first two blocks
 // it meets, and the layers it goes through next work out of the caches and leave the memory idle.  A group is closed at the
 // first block that brings it to kLarsGroupElems (smaller ones pay two launches for less than their latency; step at batch 12
-// with one group behind the backward pass 2.565 ms, 8 Mi 2.552, 4 Mi 2.527, 2 Mi 2.514; batch 40 4.45 with any from 2 Mi on,
-// 4.48 with 1 Mi; batch 256 0.2 % faster with 4 Mi than with none; profiles/step_time_against_dispatch_constants.txt); what the
+// with one group behind the backward pass 2.469 ms, 8 Mi 2.449, 4 Mi 2.440, 2 Mi 2.438; batch 40 4.23 to 4.24 with any from 2 Mi on,
+// 4.25 with 1 Mi; batch 256 the same with any; profiles/step_time_against_dispatch_constants.txt); what the
 // last blocks leave, with the stem's BN, is one group behind the backward pass, and the stem's weight, whose
 // gradient is the last thing to arrive, is one of its own.
 constexpr int64_t kLarsGroupElems = 4 << 20;

@@ -55,9 +55,9 @@ inline size_t bn_sums_bytes(int64_t nrows, int C, int each) { return static_cast
 // itself, in every workgroup, for the channels it applies: the launch in front of it -- about 4 us on the step's
 // dependency chain whatever it computes -- is gone.
 // Threshold from whole-step measurements (profiles/step_time_against_dispatch_constants.txt; batch 40, 64 / 128 / 256 / 512 rows
-// against none: 4.455 / 4.442 / 4.509 / 4.518 against 4.506 ms): up to 123 tile rows (the 14x14 and 7x7 layers) the
+// against none: 4.234 / 4.234 / 4.328 / 4.328 against 4.250 ms): up to 123 tile rows (the 14x14 and 7x7 layers) the
 // redundant sums cost less than the launch; at 245 (28x28) every workgroup would read more sums than data.  (At batch 256 256
-// rows would be 0.5 % faster, 512 slower.)
+// rows are 0.2 % slower, 512 0.7 %.)
 constexpr int kBnSelfFinalizeRows = 128, kBnSelfFinalizeRowsBwd = 128;
 inline bool bn_self_finalizes(int nrows, bool backward) {
   return nrows <= (backward ? kBnSelfFinalizeRowsBwd : kBnSelfFinalizeRows);

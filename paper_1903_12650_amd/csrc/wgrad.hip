@@ -450,8 +450,9 @@ struct WgradPlan {
 // takes the longer of one's latency (lat) and n times the tile's share of the LDS and load rates (thr), both dearer where
 // pixels are gathered; `ends` is prologue and result stores; splits add the reduction launch and the partials' traffic.
 // Constants fitted to ResNet-50's 23 shapes x 12 plans at batch 12 to 256 (bf16) and 2 to 24 (float): the plan it
-// takes is within 4 % of the best of the twelve, summed over the shapes (profiles/wgrad_plan_sweep.txt: 546 against 527 us at
-// batch 40, 1878 against 1822 at batch 256, float at batch 8 591 against 583).  Against the fixed rule before it (128-wide tiles, 192 or 384
+// takes is within 4 % of the best of the twelve, summed over the shapes, also since partial sums and results are written through
+// (profiles/wgrad_plan_sweep.txt: 503 against 495 us at batch 40, 1838 against 1781 at batch 256, float at batch 8 567 against
+// 552).  Against the fixed rule before it (128-wide tiles, 192 or 384
 // workgroups): 23 shapes at batch 40 640 -> 565 us call by call, at batch 256 2343 -> 2000, float at batch 8
 // 830 -> 531.
 struct WgradCost {
