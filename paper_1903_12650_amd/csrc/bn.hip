@@ -412,6 +412,7 @@ __device__ __forceinline__ bool finalize_channels(const BnFinArgs& f, int group,
 }
 template <bool BWD>
 __global__ __launch_bounds__(kFinThreads) void bn_finalize_kernel(int64_t m, int C, const BnFinArgs f) {
+  request_kernel_args<16 + sizeof(BnFinArgs)>();
   float a, b;
   finalize_channels<BWD>(f, blockIdx.x, m, C, true, &a, &b);
 }
@@ -540,6 +541,7 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ x,
                                                        int64_t m, int C, int tx_log2, int rpb, int mode,
                                                        int through, const BnFinArgs fin) {
   constexpr int V = Elem<T>::VEC;
+  request_kernel_args<96 + sizeof(BnFinArgs)>();
   const OutTensor<T, THROUGH> out(y, through);
   const int TX = 1 << tx_log2, TY = 256 >> tx_log2;
   const int tcol = threadIdx.x & (TX - 1), trow = threadIdx.x >> tx_log2;
@@ -809,6 +811,7 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(
     const float* __restrict__ dgamma, const float* __restrict__ dbeta, T* __restrict__ dx,
     T* __restrict__ dres, int64_t m, int C, int tx_log2, int rpb, int mode, int through, const BnFinArgs fin) {
   constexpr int V = Elem<T>::VEC;
+  request_kernel_args<136 + sizeof(BnFinArgs)>();
   const OutTensor<T, THROUGH> out(dx, through);
   const int TX = 1 << tx_log2, TY = 256 >> tx_log2;
   const int tcol = threadIdx.x & (TX - 1), trow = threadIdx.x >> tx_log2;

@@ -194,6 +194,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   // (the launch sizes the dynamic LDS as the larger of the ring and what the output stage stores in it)
   extern __shared__ __align__(16) unsigned char smem[];
 
+  request_kernel_args<sizeof(IgemmArgs)>();
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int lt = KS ? lane : tid, slot = lt & 7, lrow = lt >> 3;
   const int piece0 = slot ^ ((lrow >> 1) & 7);  // the 16-byte piece of its rows' chunk this thread fetches
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   if (!AFF && a.slots != nullptr && mt == 0 && tid < BN && n0 + tid < a.Ncols) a.slots[n0 + tid] = kBnSlotEmpty;
 
   // Rows of this tile: pixels m0.. of the whole output grid, or of one parity class of it.
-  const bool classes = !LIN && DG && a.stride == 2;
+  const bool classes = !LIN && !HALO && DG && a.stride == 2;
   __shared__ int pix_s[BM];  // classes only: output pixel index of every tile row
   // Data gradient with batch-norm sums: the per-channel coefficients of this tile's columns, fetched by one
   // thread per column while the main loop runs (every thread loading its own copies costs the texture path
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     const int m = m0 + lrow + RPL * i;
     const bool ok = m < Mc;
     const int mm = ok ? m : 0;
-    if (LIN || a.linear) {  // no pixel decode: "image" base mm, coordinates (0, 0)
+    if constexpr (LIN) {  // no pixel decode: "image" base mm, coordinates (0, 0)
       a_base[i] = mm;
       a_h0[i] = ok ? 0 : -(1 << 20);
       a_w0[i] = 0;

@@ -66,6 +66,7 @@ template <> struct WgradCfg<float> {
 template <typename T, int BMO, int BC, int NSTAGE, bool LIN, bool BNIN>
 __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
   static_assert(!BNIN || LIN, "the input-side BN goes with 1x1 stride-1 layers");
+  request_kernel_args<sizeof(WgradArgs)>();
   constexpr int V = 16 / sizeof(T);
   constexpr int BKM = WgradCfg<T>::BKM;
   constexpr int KSTEP = sizeof(T) == 2 ? 16 : 8;
@@ -274,6 +275,7 @@ __global__ __launch_bounds__(256) void wgrad3x3_kernel(const WgradArgs a) {
   constexpr int V = 8, BKM = 64, RBY = 128, KK = 4;
   constexpr int NA = 2, NL = NA + NBX;
   constexpr int STAGE = BKM * RBY + NBX * 4096;
+  request_kernel_args<sizeof(WgradArgs)>();
   extern __shared__ __align__(16) unsigned char smem[];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -405,6 +407,7 @@ __global__ __launch_bounds__(256) void wgrad3x3_kernel(const WgradArgs a) {
 // sixteenth split (ascending) and the sixteen sums are added in order: a fixed order.
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, int splits, int64_t n,
                                                             float* __restrict__ out) {
+  request_kernel_args<32>();
   __shared__ float4 red[16][16];
   const int lane = threadIdx.x & 15, grp = threadIdx.x >> 4;
   const int64_t i = (static_cast<int64_t>(blockIdx.x) * 16 + lane) * 4;  // (n is a multiple of 4)
