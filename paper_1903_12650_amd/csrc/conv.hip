@@ -154,6 +154,12 @@ template <int BM, int BN, bool BNIN>
 constexpr int igemm_ks_ring() {
   return BNIN || BM + BN > 96 ? 2 : (BM + BN > 64 ? 3 : 4);
 }
+// The halo loop by filter rows (TAPS = 3, below): steps by which the weights of a row are requested ahead.  One row where two
+// workgroups share a compute unit (the LDS for more is the other one's), and in float, whose products take longer than a load; three
+// where a workgroup has it alone in bf16 (512 -> 512 at 7x7, batch 40: 16.6 us, with one row 21.6; float at batch 8 34.6 with three, 31.5
+// with one).
+template <typename T, bool KS>
+constexpr int igemm_row_ahead() { return KS && sizeof(T) == 2 ? 3 : 1; }
 //
 // Data gradient (MODE 1): the B tile of a chunk is BK output channels (K) x BN input channels of the weights as they lie
 // in memory, filled and read like wgrad_kernel's tiles (transposing reads in bf16).  A transposing read delivers fewer
@@ -170,15 +176,27 @@ constexpr int igemm_ks_ring() {
 // the fragment registers, by a per-lane bit mask computed once.  The weights go through a ring of three
 // BN-row tiles, two taps ahead; the next chunk's run is loaded one pass per tap while the
 // current one is in use, so that every step issues the same number of loads (the load waits count them).
-template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN, bool BNIN, bool HALO, bool THROUGH>
+//
+// TAPS: taps between two barriers, 1 or 3 (0: no halo).  With small tiles a tap is a few MFMAs per wave between a barrier, the
+// fragment reads' latency and the issue of the next loads; three taps, a filter row, share these.  By rows run
+//  - the tiles of grids of at most 256 of 64x64, whose four waves split K (KS): every wave multiplies the whole tile with one 32-byte
+//    quarter of every chunk, so a fragment is read from LDS once, weights and run are loaded once per workgroup (own rings gathered
+//    nine times the run), and the weights come three rows ahead;
+//  - the 64x64 tile of 2x2 waves as long as two workgroups per compute unit hold the grid (512) and their LDS fits.
+// Forward, tap by tap -> by rows, us: bf16 256 -> 256 at 14x14, batch 40 15.7 -> 14.3 (2x2 waves), 16 13.0 -> 10.0, 8 9.5 -> 7.7, 4 9.0 -> 7.4;
+// 512 -> 512 at 7x7, batch 40 20.9 -> 16.6, 16 14.8 -> 12.2, 4 13.8 -> 11.2; 64 -> 64 at 56x56, batch 4 8.1 -> 5.4; float 256 -> 256 at 14x14,
+// batch 8 35.7 -> 25.4, 512 -> 512 at 7x7, batch 16 65 -> 48.  Data gradients alike.  At more than 512 tiles the third workgroup on a compute
+// unit is worth more (512 -> 512 at 7x7, batch 90, 552 tiles: 32.2 us, by rows 37.7).
+template <typename T, int BM, int BN, int WM, int WN, int MODE, bool LIN, bool BNIN, int TAPS, bool THROUGH>
 __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kernel(const IgemmArgs a) {
   static_assert(!BNIN || (LIN && MODE == 0), "the input-side BN is compiled for the linear forward kernel only");
+  constexpr bool HALO = TAPS > 0;
   static_assert(!HALO || (!LIN && !BNIN), "the halo main loop is a kernel of its own");
   constexpr bool DG = MODE == 1, FWD = !DG, AFF = MODE == 2;
   constexpr bool KS = WM * WN == 1;
-  static_assert(!KS || !HALO, "a wave's own chunks are gathered");
+  constexpr bool OWN = KS && !HALO;             // every wave has chunks and a ring of its own (halo: they share run and weights)
   constexpr int NW = KS ? 4 : WM * WN, NT = 64 * NW;
-  constexpr int LT = KS ? 64 : NT;              // threads that fill a chunk buffer together
+  constexpr int LT = OWN ? 64 : NT;              // threads that fill a chunk buffer together
   constexpr int V = 16 / sizeof(T);
   constexpr int BK = 128 / sizeof(T);
   constexpr int RPL = LT / 8;                   // tile rows covered by one load pass
@@ -186,7 +204,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   constexpr int NL = RA + RB;
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
   constexpr int STAGE = (BM + BN) * 128;
-  constexpr int NSTAGE = KS ? igemm_ks_ring<BM, BN, BNIN>() : igemm_ring<BM, BN, WM * WN>();
+  constexpr int NSTAGE = OWN ? igemm_ks_ring<BM, BN, BNIN>() : igemm_ring<BM, BN, WM * WN>();
   constexpr int CP = BN * sizeof(T) + 16;  // epilogue pitch
   static_assert((NW == 4 || NW == 8) && TM >= 1 && TN >= 1 && RA >= 1 && RB >= 1, "tile shape");
   static_assert(BM % RPL == 0 && BN % RPL == 0, "every load pass covers whole rows of the tile");
@@ -196,10 +214,10 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
 
   request_kernel_args<sizeof(IgemmArgs)>();
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int lt = KS ? lane : tid, slot = lt & 7, lrow = lt >> 3;
+  const int lt = OWN ? lane : tid, slot = lt & 7, lrow = lt >> 3;
   const int piece0 = slot ^ ((lrow >> 1) & 7);  // the 16-byte piece of its rows' chunk this thread fetches
   // (KS: passes are 8 rows apart, which moves bit 2 of the permutation from one to the next)
-  auto piece_of = [&](int i) __attribute__((always_inline)) { return KS ? piece0 ^ ((i & 1) << 2) : piece0; };
+  auto piece_of = [&](int i) __attribute__((always_inline)) { return OWN ? piece0 ^ ((i & 1) << 2) : piece0; };
   const int wm = KS ? 0 : wave % WM, wn = KS ? 0 : wave / WM;
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   const int mt = static_cast<int>(fdiv(static_cast<uint32_t>(bid), a.div_ntn)), nt = bid - mt * a.ntn;
@@ -362,7 +380,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   const int allchunks = nr * ns * a.cpt;
   int cur_r = r0, cur_s = s0, cur_cc = 0, cur = 0;
   int nchunks = allchunks, first_chunk = 0;  // this wave's (KS) or the workgroup's range of chunks
-  if constexpr (KS) {
+  if constexpr (OWN) {
     const int w = __builtin_amdgcn_readfirstlane(wave);
     first_chunk = (allchunks * w) >> 2;
     nchunks = ((allchunks * (w + 1)) >> 2) - first_chunk;
@@ -409,7 +427,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   // One chunk into one ring buffer: every wave fills its 8 rows of each load pass (1 KB per instruction).
   typedef __attribute__((address_space(3))) unsigned char* lds_byte_ptr;
   const uint32_t wave_dst = __builtin_amdgcn_readfirstlane(
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_byte_ptr)smem)) + static_cast<uint32_t>(wave) * (KS ? NSTAGE * STAGE : 1024u));
+      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_byte_ptr)smem)) + static_cast<uint32_t>(wave) * (OWN ? NSTAGE * STAGE : 1024u));
   auto load_chunk = [&](int stage) __attribute__((always_inline)) {
     const uint32_t so = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(cur_cc) * 128u);
     auto cval = [&](int i) __attribute__((always_inline)) { return !ragged || (cur_cc * BK + piece_of(i) * V < a.Cg); };
@@ -458,7 +476,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   for (int j = 0; j < TN; ++j) bt_base[j] = DG ? wgrad_frag_base<T, BRB>(lane, wn * (BN / WN) + j * 32) : 0;
   constexpr int AHEAD = (TM + TN <= 3) ? 4 : 1;  // k steps whose fragments are in registers before the first MFMA
   auto compute = [&](int stage) __attribute__((always_inline)) {
-    const unsigned char* base = smem + (KS ? wave * (NSTAGE * STAGE) : 0) + stage * STAGE;
+    const unsigned char* base = smem + (OWN ? wave * (NSTAGE * STAGE) : 0) + stage * STAGE;
     const unsigned char* sa = base + wm * (BM / WM) * 128;
     const unsigned char* sb = base + BM * 128 + (DG ? 0 : wn * (BN / WN) * 128);
     Vec16 fa[4][TM], fb[4][TN];
@@ -502,11 +520,13 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     const uint32_t lds0 = wave_dst;                           // LDS address of smem + this wave's 1 KB share of a pass
     const int q0 = m0 - Wd - 1 + lrow;                        // input pixel of this thread's row in pass 0 of a run
     const int piece = piece0;
+    // (the addresses are uniform; in the loop of filter rows the compiler does not see it)
+    auto uniform = [](uint32_t v) __attribute__((always_inline)) { return TAPS == 3 ? static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(v)) : v; };
     auto load_run_pass = [&](int j, int cc, int buf) __attribute__((always_inline)) {
       const int q = q0 + RPL * j;
       const bool ok = static_cast<unsigned>(q) < static_cast<unsigned>(a.M) && (!ragged || cc * BK + piece * V < a.Cg);
       const uint32_t off = ok ? static_cast<uint32_t>(q * a.PS + piece * V) * sizeof(T) : kOob;
-      buffer_load16_to_lds(rsA, lds0 + static_cast<uint32_t>(buf) * run_bytes + static_cast<uint32_t>(j) * (RPL * 128), off,
+      buffer_load16_to_lds(rsA, uniform(lds0 + static_cast<uint32_t>(buf) * run_bytes + static_cast<uint32_t>(j) * (RPL * 128)), off,
                            __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(cc) * 128u));
     };
     auto load_b_tile = [&](int stage, int cc, int tap, bool live) __attribute__((always_inline)) {
@@ -514,7 +534,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       const uint32_t sob = __builtin_amdgcn_readfirstlane(b_at(tap, cc));
 #pragma unroll
       for (int i = 0; i < RB; ++i)
-        buffer_load16_to_lds(rsB, lds0 + b_base + static_cast<uint32_t>(stage) * (BN * 128) + i * (RPL * 128),
+        buffer_load16_to_lds(rsB, uniform(lds0 + b_base + static_cast<uint32_t>(stage) * (BN * 128) + i * (RPL * 128)),
                              live && b_live(i, cc, cval) ? b_row[i] : kOob, sob);
     };
     auto load_nothing = [&]() __attribute__((always_inline)) { buffer_load16_to_lds(rsA, lds0 + dump, kOob, 0); };
@@ -538,43 +558,162 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       }
       vmask[i] = bits;
     }
-    auto compute_tap = [&](int buf, int bstage, int tap, int dyo, int dxo) __attribute__((always_inline)) {
+    // One tap's fragments, and their products.
+    struct Frags {
+      Vec16 a[4][TM], b[4][TN];
+    };
+    struct TapAddr {
+      int a[4];
+      const unsigned char *sa, *sb;
+    };
+    auto tap_addr = [&](int buf, int bslot, int tap) __attribute__((always_inline)) {
+      const int dyo = FWD ? tap / 3 - 1 : 1 - tap / 3, dxo = FWD ? tap % 3 - 1 : 1 - tap % 3;
       const int rl = (lane & 31) + (dyo + 1) * Wd + (dxo + 1);  // row of the run this lane's row 0 reads
       const int swz = (rl >> 1) & 7;
-      int aoff[4];
+      TapAddr r;
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) aoff[kk] = rl * 128 + (((2 * kk + (lane >> 5)) ^ swz) << 4);
-      uint32_t mk[TM];
+      for (int kk = 0; kk < 4; ++kk) r.a[kk] = rl * 128 + (((2 * kk + (lane >> 5)) ^ swz) << 4);
+      r.sa = smem + static_cast<uint32_t>(buf) * run_bytes + wm * (BM / WM) * 128;
+      r.sb = smem + b_base + bslot * (BN * 128) + (DG ? 0 : wn * (BN / WN) * 128);
+      return r;
+    };
+    auto tap_read = [&](Frags& f, const TapAddr& at, int kk) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) mk[i] = ((vmask[i] >> tap) & 1u) ? 0xffffffffu : 0u;
-      const unsigned char* sa = smem + static_cast<uint32_t>(buf) * run_bytes + wm * (BM / WM) * 128;
-      const unsigned char* sb = smem + b_base + bstage * (BN * 128) + (DG ? 0 : wn * (BN / WN) * 128);
-      Vec16 fa[4][TM], fb[4][TN];
-      auto read_frags = [&](int kk) __attribute__((always_inline)) {
+      for (int i = 0; i < TM; ++i) f.a[kk][i].u = *reinterpret_cast<const uint4*>(at.sa + i * 32 * 128 + at.a[kk]);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[kk][i].u = *reinterpret_cast<const uint4*>(sa + i * 32 * 128 + aoff[kk]);
+      for (int j = 0; j < TN; ++j) {
+        if constexpr (DG) f.b[kk][j] = wgrad_read_frag<T, BRB>(at.sb, bt_base[j], kk);
+        else f.b[kk][j].u = *reinterpret_cast<const uint4*>(at.sb + j * 32 * 128 + frag_off[kk]);
+      }
+    };
+    struct TapMask {
+      uint32_t m[TM];
+    };
+    auto tap_mask = [&](int tap) __attribute__((always_inline)) {
+      TapMask r;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          if constexpr (DG) fb[kk][j] = wgrad_read_frag<T, BRB>(sb, bt_base[j], kk);
-          else fb[kk][j].u = *reinterpret_cast<const uint4*>(sb + j * 32 * 128 + frag_off[kk]);
-        }
+      for (int i = 0; i < TM; ++i) r.m[i] = ((vmask[i] >> tap) & 1u) ? 0xffffffffu : 0u;
+      return r;
+    };
+    auto masked_mma = [&](Vec16 (&fa)[TM], const Vec16 (&fb)[TN], const TapMask& mk) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        fa[i].u.x &= mk.m[i]; fa[i].u.y &= mk.m[i]; fa[i].u.z &= mk.m[i]; fa[i].u.w &= mk.m[i];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) Mma<T>::run(fb[j], fa[i], acc[i][j]);
+      }
+    };
+    // KS: a wave multiplies the whole tile with its quarter of every chunk (k step `wave`).
+    struct FragsKw {
+      Vec16 a[TM], b[TN];
+    };
+    const int kw_slot = 2 * wave + (lane >> 5);
+    const int kw_boff = (lane & 31) * 128 + ((kw_slot ^ ((lane >> 1) & 7)) << 4);
+    auto kw_read = [&](FragsKw& f, int buf, int bslot, int tap) __attribute__((always_inline)) {
+      const int dyo = FWD ? tap / 3 - 1 : 1 - tap / 3, dxo = FWD ? tap % 3 - 1 : 1 - tap % 3;
+      const int rl = (lane & 31) + (dyo + 1) * Wd + (dxo + 1);
+      const int aoff = rl * 128 + ((kw_slot ^ ((rl >> 1) & 7)) << 4);
+      const unsigned char* sa = smem + static_cast<uint32_t>(buf) * run_bytes;
+      const unsigned char* sb = smem + b_base + bslot * (BN * 128);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) f.a[i].u = *reinterpret_cast<const uint4*>(sa + i * 32 * 128 + aoff);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        if constexpr (DG) f.b[j] = wgrad_read_frag<T, BRB>(sb, bt_base[j], wave);
+        else f.b[j].u = *reinterpret_cast<const uint4*>(sb + j * 32 * 128 + kw_boff);
+      }
+    };
+    if constexpr (TAPS == 3) {
+      // A step is a filter row: three taps.  Its three weight tiles come D steps ahead into a ring of D + 1 slots, the next
+      // chunk's run in the chunk's first steps.
+      constexpr int D = igemm_row_ahead<T, KS>(), NSLOT = D + 1, LB3 = 3 * RB;
+      constexpr int NA_MIN = (BM + 4 + RPL - 1) / RPL;  // load passes of a run, at least
+      auto load_row = [&](int slot, int cc, int row, bool live) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 3; ++t) load_b_tile(3 * slot + t, cc, 3 * row + t, live);
       };
-      constexpr int AH = (TM + TN <= 3) ? 4 : 1;
+      for (int j = 0; j < NA; ++j) load_run_pass(j, 0, 0);
 #pragma unroll
-      for (int kk = 0; kk < AH; ++kk) read_frags(kk);
+      for (int r = 0; r < D; ++r) load_row(r, 0, r, true);
+      int slot = 0;
+      for (int cc = 0; cc < cpt; ++cc) {
+        const int buf = cc & 1;  // (one chunk: 0)
+        const bool more = cc + 1 < cpt;
+#pragma unroll
+        for (int row = 0; row < 3; ++row) {
+          // What this row reads has landed: its weights were requested D steps ago, behind which D - 1 steps of LB3 loads each and
+          // (D = 3) the run's passes of this chunk's first step may be in flight.  Nobody reads the slot that is filled next any more.
+          if (D == 3 && row > 0 && more) wait_loads_then_barrier<(D - 1) * LB3 + (D == 3 ? NA_MIN : 0)>();
+          else wait_loads_then_barrier<(D - 1) * LB3>();
+          auto load_next = [&]() __attribute__((always_inline)) {
+            const int to = slot >= 1 ? slot - 1 : NSLOT - 1;
+            if constexpr (D == 3) {
+              load_row(to, cc + 1, row, more);  // (past the last chunk a load of nothing, for the count)
+              if (row == 0 && more)
+                for (int j = 0; j < NA; ++j) load_run_pass(j, cc + 1, buf ^ 1);
+            } else {
+              if (row < 2) load_row(to, cc, row + 1, true);
+              else if (more) load_row(to, cc + 1, 0, true);
+              if (more) {
+#pragma unroll
+                for (int j = 3 * row; j < 3 * row + 3; ++j)  // (the host checked NA <= 8)
+                  if (j < NA) load_run_pass(j, cc + 1, buf ^ 1);
+              }
+            }
+          };
+          if constexpr (KS) {
+            FragsKw f[3];
+            TapMask mk[3];
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+              kw_read(f[t], buf, 3 * slot + t, 3 * row + t);
+              mk[t] = tap_mask(3 * row + t);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            load_next();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) masked_mma(f[t].a, f[t].b, mk[t]);
+            __builtin_amdgcn_sched_barrier(0);
+          } else {
+            load_next();
+            Frags f[2];  // a tap's fragments are read while the tap before it is multiplied
+            auto read_all = [&](Frags& to, int t) __attribute__((always_inline)) {
+              const TapAddr at = tap_addr(buf, 3 * slot + t, 3 * row + t);
+#pragma unroll
+              for (int kk = 0; kk < 4; ++kk) tap_read(to, at, kk);
+            };
+            read_all(f[0], 0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+              if (t < 2) read_all(f[(t + 1) & 1], t + 1);
+              const TapMask mk = tap_mask(3 * row + t);
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int kk = 0; kk < 4; ++kk) masked_mma(f[t & 1].a[kk], f[t & 1].b[kk], mk);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+          slot = slot == NSLOT - 1 ? 0 : slot + 1;
+        }
+      }
+    } else {
+    auto compute_tap = [&](int buf, int bstage, int tap) __attribute__((always_inline)) {
+      Frags f;
+      constexpr int AH = (TM + TN <= 3) ? 4 : 1;
+      const TapAddr at = tap_addr(buf, bstage, tap);
+      const TapMask mk = tap_mask(tap);
+#pragma unroll
+      for (int kk = 0; kk < AH; ++kk) tap_read(f, at, kk);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         if (kk + AH < 4) {
-          read_frags(kk + AH);
+          tap_read(f, at, kk + AH);
           __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          fa[kk][i].u.x &= mk[i]; fa[kk][i].u.y &= mk[i]; fa[kk][i].u.z &= mk[i]; fa[kk][i].u.w &= mk[i];
-#pragma unroll
-          for (int j = 0; j < TN; ++j) Mma<T>::run(fb[kk][j], fa[kk][i], acc[i][j]);
-        }
+        masked_mma(f.a[kk], f.b[kk], mk);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -595,9 +734,10 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         load_b_tile(bstage >= 1 ? bstage - 1 : NSB - 1, cc2, tap2, cc2 < cpt);  // the tile of step - 1: free again
         if (tap < NA && cc + 1 < cpt) load_run_pass(tap, cc + 1, buf ^ 1);
         else load_nothing();
-        compute_tap(buf, bstage, tap, FWD ? tap / 3 - 1 : 1 - tap / 3, FWD ? tap % 3 - 1 : 1 - tap % 3);
+        compute_tap(buf, bstage, tap);
         bstage = bstage == NSB - 1 ? 0 : bstage + 1;
       }
+    }
     }
     // (the loads still in flight carry nothing and land in the dump area or in weight tiles nobody reads again;
     // they are waited for before the output stage reuses LDS)
@@ -639,7 +779,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         load_floats<V>(in_tab + kpad + at, bias);
 #pragma unroll
         for (int i = par; i < RA; i += KS ? 2 : 1) {
-          uint4* p = reinterpret_cast<uint4*>(smem + (KS ? wave * (NSTAGE * STAGE) : 0) + stage * STAGE + (lrow + RPL * i) * 128 + slot * 16);
+          uint4* p = reinterpret_cast<uint4*>(smem + (OWN ? wave * (NSTAGE * STAGE) : 0) + stage * STAGE + (lrow + RPL * i) * 128 + slot * 16);
           Vec16 v;
           v.u = *p;
           *p = bn_relu_vector<T>(v, scale, bias).u;
@@ -920,7 +1060,7 @@ static void launch_igemm_through(IgemmArgs a, const char* tag, int64_t grid, hip
   // input-side BN coefficients: two floats per channel, at most 4096 channels (KS: 2048)
   constexpr int kInTabMax = 8 * (KS ? 2048 : 4096);
   std::call_once(once, [] {
-    allow_big_lds(igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN, false, THROUGH>,
+    allow_big_lds(igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN, 0, THROUGH>,
                   (nring * stage > out_need ? nring * stage : out_need) + (BNIN ? kInTabMax : 0));
   });
   // A short reduction never touches the later ring buffers; without them more workgroups fit a CU (the 1x1
@@ -932,7 +1072,7 @@ static void launch_igemm_through(IgemmArgs a, const char* tag, int64_t grid, hip
     a.in_lds = lds;
     lds += 8 * a.R * a.S * a.cpt * (128 / es);
   }
-  RN50_LAUNCH(tag, (igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN, false, THROUGH>), dim3(static_cast<unsigned>(grid)), dim3(NT), lds, s, a);
+  RN50_LAUNCH(tag, (igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN, 0, THROUGH>), dim3(static_cast<unsigned>(grid)), dim3(NT), lds, s, a);
 }
 // Tiles of 128 columns: the rules give them to outputs of 6.6 MB and more (384 tiles of 128 rows, 192 of 256, by more than 64 columns;
 // smaller ones only with a few rows by tens of thousands of columns), so they are compiled for outputs that are written through.
@@ -948,33 +1088,44 @@ static void launch_igemm_mode(const IgemmArgs& a, const char* tag, int64_t grid,
 // The halo kernel (3x3, stride 1, padding 1): LDS bytes of its main loop for an image width, or 0 when the shape
 // does not fit it (a run of more than 8 load passes, more LDS than a compute unit has).
 static bool igemm_halo_shape(const IgemmArgs& a);
-constexpr int kHaloLdsMax = 152 * 1024;  // (the kernel's static arrays come on top; a compute unit has 160 KB)
-template <int BM, int BN, int WM, int WN>
-static int halo_lds_bytes(int W, int cpt) {
-  constexpr int NW = WM * WN, RPL = NW * 8;
+// (the kernel's static arrays come on top; a compute unit has 160 KB, for two workgroups by rows with 2x2 waves)
+constexpr int kHaloLdsMax = 152 * 1024, kHaloRowLdsMax = 78 * 1024, kHaloRowGroups = 512;
+template <typename T, int BM, int BN, int WM, int WN>
+static int halo_lds_bytes(int W, int cpt, int taps) {
+  constexpr bool KS = WM * WN == 1;
+  constexpr int NW = WM * WN == 1 ? 4 : WM * WN, RPL = NW * 8;
   const int passes = (BM + 2 * W + 2 + RPL - 1) / RPL;
   if (passes > 8) return 0;
-  const int bytes = (cpt > 1 ? 2 : 1) * passes * RPL * 128 + 3 * BN * 128 + NW * 1024;
-  return bytes <= kHaloLdsMax ? bytes : 0;
+  const int runs = (cpt > 1 ? 2 : 1) * passes * RPL * 128;
+  const int bytes = runs + (taps == 3 ? 3 * (igemm_row_ahead<T, KS>() + 1) * BN * 128 : 3 * BN * 128 + NW * 1024);
+  return bytes <= (taps == 3 && !KS ? kHaloRowLdsMax : kHaloLdsMax) ? bytes : 0;
 }
-template <typename T, int BM, int BN, int WM, int WN, int MODE, bool THROUGH>
+template <typename T, int BM, int BN, int WM, int WN, int MODE, int TAPS, bool THROUGH>
 static void launch_igemm_halo_through(IgemmArgs a, const char* tag, int64_t grid, int main_lds, hipStream_t s) {
-  constexpr int NT = 64 * WM * WN;
+  constexpr bool KS = WM * WN == 1;
+  constexpr int NT = KS ? 256 : 64 * WM * WN;
   constexpr int es = static_cast<int>(sizeof(T));
   constexpr int out_tile = BM * (BN * 4 + 16);
   constexpr int col_sums = (NT / (BN * es / 16)) * 2 * BN * 4;
-  constexpr int out_need = out_tile > col_sums ? out_tile : col_sums;
+  constexpr int exchange = KS ? 4 * BM * BN * 4 : 0;     // (KS: the four partial tiles)
+  constexpr int out_need = std::max({out_tile, col_sums, exchange});
   static std::once_flag once;
-  std::call_once(once, [] { allow_big_lds(igemm_kernel<T, BM, BN, WM, WN, MODE, false, false, true, THROUGH>, kHaloLdsMax); });
+  std::call_once(once, [] { allow_big_lds(igemm_kernel<T, BM, BN, WM, WN, MODE, false, false, TAPS, THROUGH>, kHaloLdsMax); });
   const int lds = main_lds > out_need ? main_lds : out_need;
-  RN50_LAUNCH(tag, (igemm_kernel<T, BM, BN, WM, WN, MODE, false, false, true, THROUGH>), dim3(static_cast<unsigned>(grid)), dim3(NT), lds, s, a);
+  RN50_LAUNCH(tag, (igemm_kernel<T, BM, BN, WM, WN, MODE, false, false, TAPS, THROUGH>), dim3(static_cast<unsigned>(grid)), dim3(NT), lds, s, a);
 }
-template <typename T, int BM, int BN, int WM, int WN, int MODE>
+template <typename T, int BM, int BN, int WM, int WN, int MODE, int TAPS>
 static void launch_igemm_halo(const IgemmArgs& a, const char* tag, int64_t grid, int main_lds, hipStream_t s) {
   if constexpr (!igemm_always_through<BN>()) {
-    if (!a.out_through) return launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, false>(a, tag, grid, main_lds, s);
+    if (!a.out_through) return launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, TAPS, false>(a, tag, grid, main_lds, s);
   }
-  launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, true>(a, tag, grid, main_lds, s);
+  launch_igemm_halo_through<T, BM, BN, WM, WN, MODE, TAPS, true>(a, tag, grid, main_lds, s);
+}
+template <typename T, int BM, int BN, int WM, int WN, int TAPS>
+static void launch_igemm_halo_mode(const IgemmArgs& a, const char* tag, int64_t grid, int main_lds, hipStream_t s) {
+  if (a.mode == 2) launch_igemm_halo<T, BM, BN, WM, WN, 2, TAPS>(a, tag, grid, main_lds, s);
+  else if (a.mode == 0) launch_igemm_halo<T, BM, BN, WM, WN, 0, TAPS>(a, tag, grid, main_lds, s);
+  else launch_igemm_halo<T, BM, BN, WM, WN, 1, TAPS>(a, tag, grid, main_lds, s);
 }
 // Tuning builds can force any tile on any layer; the product compiles what the rules below can choose.
 #ifdef RN50_TUNING
@@ -1009,12 +1160,14 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
     }
     return;
   }
-  if constexpr (WM * WN > 1 && (BM != 128 || BN != 128 || kTuning)) {  // (igemm_halo_tile never takes the 128x128 tile)
-    if (const int halo_lds = igemm_halo_shape(a) ? halo_lds_bytes<BM, BN, WM, WN>(a.W, a.cpt) : 0) {
-      if (a.mode == 2) launch_igemm_halo<T, BM, BN, WM, WN, 2>(a, tag, grid, halo_lds, s);
-      else if (a.mode == 0) launch_igemm_halo<T, BM, BN, WM, WN, 0>(a, tag, grid, halo_lds, s);
-      else launch_igemm_halo<T, BM, BN, WM, WN, 1>(a, tag, grid, halo_lds, s);
-      return;
+  if (igemm_halo_shape(a)) {
+    if constexpr (BM <= 64) {  // by filter rows
+      const int lds = WM * WN == 1 || grid <= kHaloRowGroups ? halo_lds_bytes<T, BM, BN, WM, WN>(a.W, a.cpt, 3) : 0;
+      if (lds) return launch_igemm_halo_mode<T, BM, BN, WM, WN, 3>(a, tag, grid, lds, s);
+    }
+    if constexpr (WM * WN > 1 && (BM != 128 || BN != 128 || kTuning)) {  // (igemm_halo_tile never takes the 128x128 tile)
+      const int lds = halo_lds_bytes<T, BM, BN, WM, WN>(a.W, a.cpt, 1);
+      if (lds) return launch_igemm_halo_mode<T, BM, BN, WM, WN, 1>(a, tag, grid, lds, s);
     }
   }
   if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, false>(a, tag, grid, s);
@@ -1080,10 +1233,10 @@ static bool igemm_halo_shape(const IgemmArgs& a) {
 // have any taps); taps x cpt 128-byte chunks of reduction; lin_fwd_channels: input channels of a 1x1 stride-1 forward
 // layer (else 0), whose coefficient table bounds the K-split kernels.
 // Where 64x64 tiles would give at most one workgroup per compute unit and there are chunks for four waves, the waves split K
-// (KS); at half of that or less the tile is halved again (in float, whose MFMAs take sixteen times as long per chunk, in
+// (KS; 3x3 / stride 1 layers by filter rows); at half of that or less the tile is halved again (in float, whose MFMAs take sixteen times as long per chunk, in
 // both directions), so that twice (four times) as many compute units work.  Measured on the whole float gradient pass (batch 4:
 // 4055 -> 2919 us, batch 8: 4752 -> 4024, batch 16: 6789 -> 6384) and on single layers (2048 -> 512 channels at 7x7,
-// batch 40: 14.0 -> 9.3 us; 3x3 512 -> 512 at 7x7, batch 12: 28.7 -> 14.4); with 257 to 512 tiles the two workgroups per
+// batch 40: 14.0 -> 9.3 us); with 257 to 512 tiles the two workgroups per
 // compute unit of the shared ring do better.  Limits of 0 / 128 / 256 / 384 / 512 tiles in the whole step: float at batch 8 4.77 /
 // 4.12 / 4.02 / 4.02 / 4.40 ms, bf16 at batch 40 4.250 / 4.253 / 4.240 / 4.242 / 4.499 (profiles/step_time_against_dispatch_constants.txt;
 // layer by layer: profiles/conv_tile_sweep_*.txt).

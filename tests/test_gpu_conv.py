@@ -310,6 +310,36 @@ def test_images_too_wide_for_the_halo_loop(rn, mode_name, N, H, W, C, K):
     assert torch.equal(dx, rn.conv_dgrad_bn_sums(dy.cuda(), wt.cuda(), y.shape, 1, 1, y, one, zero, zero, one)[0])
 
 
+# 3x3 / stride 1 layers by the filter row: tiles of 32 rows (at most 128 tiles of 64x64), of 64 rows with the reduction split over the
+# waves (to 256) and 2x2 waves (to 512, 513 the tap by tap loop), one to four chunks of channels (ragged ones too), image widths on
+# either side of those whose runs of pixels still fit, images narrower than the filter.
+HALO_ROWS = [(1, 1, 1, 8, 8), (1, 2, 1, 64, 64), (2, 5, 3, 72, 40), (1, 3, 111, 64, 64), (1, 3, 112, 64, 64), (1, 30, 95, 136, 24), (1, 30, 96, 136, 24),
+             (1, 90, 95, 64, 64), (1, 90, 96, 64, 64), (1, 120, 79, 72, 64), (1, 120, 80, 72, 64), (40, 14, 14, 200, 128), (60, 13, 15, 200, 128),
+             (60, 13, 16, 136, 128), (6, 57, 56, 64, 64), (3, 83, 79, 64, 64), (3, 83, 80, 64, 64), (81, 14, 14, 72, 128), (84, 14, 14, 72, 128)]
+
+
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("N,H,W,C,K", HALO_ROWS)
+def test_3x3_by_filter_rows(rn, mode_name, N, H, W, C, K):
+    """Forward with and without sums, data gradient with and without, into buffers of NaNs, against 64 bits."""
+    dt = torch.bfloat16 if mode_name == "bf16" else torch.float32
+    gen = torch.Generator().manual_seed(N + W + C)
+    rand = lambda *shape, scale=1.0: (torch.randn(*shape, generator=gen) * scale).to(dt)
+    nchw = lambda t: t.double().permute(0, 3, 1, 2)
+    x, w, dy, wt = rand(N, H, W, C), rand(K, 3, 3, C, scale=(9 * C) ** -0.5), rand(N, H, W, C), rand(C, 3, 3, K, scale=(9 * C) ** -0.5)
+    want = torch.nn.functional.conv2d(nchw(x), nchw(w), padding=1).permute(0, 2, 3, 1).contiguous()
+    y = torch.full(want.shape, float("nan"), device="cuda", dtype=dt)
+    rn.conv_fwd(x.cuda(), w.cuda(), 1, 1, y=y)
+    assert_close(y, want.numpy(), TOL[mode_name], "y")
+    assert torch.equal(y, rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), 1, 1)[0])
+    want = torch.nn.grad.conv2d_input((N, K, H, W), nchw(wt), nchw(dy), padding=1).permute(0, 2, 3, 1).contiguous()
+    dx = torch.full(want.shape, float("nan"), device="cuda", dtype=dt)
+    rn.conv_dgrad(dy.cuda(), wt.cuda(), y.shape, 1, 1, dx=dx)
+    assert_close(dx, want.numpy(), TOL[mode_name], "dx")
+    one, zero = torch.ones(K, device="cuda"), torch.zeros(K, device="cuda")
+    assert torch.equal(dx, rn.conv_dgrad_bn_sums(dy.cuda(), wt.cuda(), y.shape, 1, 1, y, one, zero, zero, one)[0])
+
+
 # Output pixel grids whose tensor is one column below, exactly and one column above the 1 MB from which convolutions write their
 # outputs through: columns, filter, stride, channels on the other side (64x64 tiles; the two K splits; the halo loop; the
 # strided gather and data gradient; 1x1 / stride 2 with its zeros; the stem).
