@@ -358,6 +358,15 @@ def test_lars_update_captured_with_a_table_from_outside(rn, arrived):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("num", [1, 63, 64, 65, 192, 479, 480, 481])
+def test_lars_finds_the_tensor_of_every_chunk(rn, num):
+    """Tables on either side of the 64 entries that are looked at together; some tensors of several chunks, the last one among them.
+    (At least 61 elements each: in one of a single element the two terms of a step may cancel, and 6e-8 of the larger one, a float's
+    rounding, is more than the bar of 1e-6 of their difference; of 61 the norm does not.)"""
+    table = [("t%d.w" % i, (3, 4097) if i % 29 == 28 or i == num - 1 else (1, 61 + i % 7), "fcw") for i in range(num)]
+    _lars_case(rn, table)
+
+
 def test_lars_many_tensors_needs_two_launches(rn):
     table = [(f"t{i}.w", (3 + i % 5, 1, 1, 4), "conv") for i in range(700)]
     _lars_case(rn, table, v_zero=False)
