@@ -416,3 +416,26 @@ WGRAD_EDGES = [(1, 3, 3, 40, 64, 3, 1, 1), (2, 8, 8, 64, 72, 1, 1, 0), (2, 8, 8,
 @pytest.mark.parametrize("case", WGRAD_EDGES)
 def test_wgrad_plan_edges(rn, mode_name, case):
     run_case(rn, mode_name, *case, tag="wg" + str(case))
+
+
+# Output grids along which the gathering weight gradient steps by a chunk (64 pixels, 32 in float): one pixel an image, one column,
+# one row, rows on either side of a chunk, an image exactly one, several images in one, with strides and filters of either parity.
+WGRAD_STEPS = [(70, 1, 1, 16, 24, 3, 1, 1), (70, 2, 2, 16, 24, 3, 2, 1), (3, 70, 1, 16, 24, 3, 1, 1), (3, 1, 70, 16, 24, 3, 1, 1), (2, 5, 31, 40, 72, 3, 1, 1),
+               (2, 5, 32, 40, 72, 3, 1, 1), (2, 5, 33, 40, 72, 3, 1, 1), (2, 3, 63, 72, 8, 3, 1, 1), (2, 3, 64, 72, 8, 3, 1, 1), (2, 3, 65, 72, 8, 3, 1, 1),
+               (2, 3, 130, 72, 8, 3, 1, 1), (5, 8, 8, 136, 72, 3, 1, 1), (5, 4, 8, 136, 72, 3, 1, 1), (11, 7, 7, 136, 72, 3, 1, 1), (9, 13, 15, 72, 136, 3, 2, 1),
+               (3, 29, 27, 64, 64, 1, 2, 0), (3, 17, 21, 24, 40, 2, 1, 1), (2, 33, 18, 24, 40, 5, 3, 2), (2, 9, 11, 16, 16, 1, 1, 0)]
+
+
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("N,H,W,C,K,R,stride,pad", WGRAD_STEPS)
+def test_weight_gradient_steps_over_rows_and_images(rn, mode_name, N, H, W, C, K, R, stride, pad):
+    dt = torch.bfloat16 if mode_name == "bf16" else torch.float32
+    gen = torch.Generator().manual_seed(N + H + W + C)
+    x = torch.randn(N, H, W, C, generator=gen).to(dt)
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1
+    dy = torch.randn(N, P, Q, K, generator=gen).to(dt)
+    nchw = lambda t: t.double().permute(0, 3, 1, 2)
+    want = torch.nn.grad.conv2d_weight(nchw(x), (K, C, R, R), nchw(dy), stride=stride, padding=pad).permute(0, 2, 3, 1).contiguous()
+    dw = torch.full((K, R, R, C), float("nan"), device="cuda")
+    rn.conv_wgrad(x.cuda(), dy.cuda(), (K, R, R, C), stride, pad, dw=dw)
+    assert_close(dw, want.numpy(), 1e-5, "dw", elementwise=None)  # (products of the inputs as they are, float sums of at most 3,000)
