@@ -420,21 +420,20 @@ __global__ __launch_bounds__(kFinThreads) void bn_finalize_kernel(int64_t m, int
 // Where an apply pass has its statistics from.  kFinGiven: from memory, a finalize launch has stored them.  kFinSelf: every
 // workgroup adds up the tile rows of its channels.  kFinShared: the first `groups` workgroups of the same launch finalize, two
 // channels each, and publish the two results of a channel as one 64-bit word; the others request their rows of x and then ask
-// for the words of their channels.  Two launches in one, for grids of at most kBnShareGroups workgroups: 11 to 13 us for 4.6 to 5.5 +
-// 1.5 (between them) + 7 at 56x56, batch 40.  Four workgroups of these kernels are on a compute unit at a time (117 to 126 registers,
-// as without the sharing), 1024 on the chip: a grid at the limit runs in two rounds and a few, the later ones of which find the
-// results there.  Where the limit lies hardly matters: the step with limits of 0 / 1024 / 2048 / 4096 workgroups / none, ms
-// (profiles/step_time_against_dispatch_constants.txt):
+// for the words of their channels.  Two launches in one: 11 to 13 us for 4.6 to 5.5 + 1.5 (between them) + 7 at 56x56, batch 40.  Four
+// workgroups of these kernels are on a compute unit at a time (117 to 126 registers, as without the sharing), 1024 on the chip; those of
+// a larger grid that come later find the results there.  The step with the sharing for grids of at most 0 / 1024 / 2048 / 4096 workgroups /
+// all, ms (profiles/step_time_against_dispatch_constants.txt):
 //   batch 12 2.498 / 2.438 / 2.439 / 2.439 / 2.439, 24 3.368 / 3.336 / 3.320 / 3.319 / 3.317, 40 4.272 / 4.244 / 4.235 / 4.235 / 4.236,
 //   90 8.070 / 8.029 / 8.029 / 7.978 / 7.954, 256 19.17 / 19.16 / 19.17 / 19.16 / 19.09, float at batch 8 4.013 / 4.004 / 4.016 /
 //   4.011 / 4.014;
-// resnet_train_step at batch 90 and 192 px, 33 and 208 px, float gradients at batch 8: the same with the limit and without.
+// with the present kernels, 2048 / all: batch 90 8.029 / 7.984, 128 at 192 px 8.295 / 8.244, 256 19.10 / 19.06, 40 the same.  (Stand-alone calls,
+// their sums passes making the words empty, gained nothing from it: batch 40 520 / 523 us, batch 200 2004 / 2019.)
 // kFinSelf stays for its few rows: with kFinShared in its place (from 0 / 40 / 64 rows on) batch 12 loses 2.3 / 0.2 / 0.2 %.
 // The word is the message: relaxed atomics at device scope, nothing else is passed by memory within the launch.  It is made empty
 // by the convolution that produces the sums (IgemmArgs::slots).  No progress is assumed of the finalizing workgroups: after
 // `polls` unanswered questions a workgroup computes what it needs itself, in the same order, so every wait ends and the results
 // do not depend on who computed them.
-constexpr int kBnShareGroups = 2048;
 enum BnFin { kFinGiven, kFinSelf, kFinShared };
 __device__ __forceinline__ void publish_results(unsigned long long* slot, float a, float b) {
   unsigned long long v = static_cast<unsigned long long>(__float_as_uint(b)) << 32 | __float_as_uint(a);
@@ -947,7 +946,7 @@ static void launch_fwd_tail(const rn50_bn_desc* d, int64_t m, const void* x,
   }
   const BnGeom ga = bn_apply_geom(m, d->C, d->dtype, kBnApplyGroups);
   if constexpr (LAST) {  // (only a step shares)
-    if (share && y && ga.nblk * ga.gy <= kBnShareGroups) {
+    if (share && y) {
       fin.slots = share->slots; fin.groups = finalize_grid(d->C); fin.polls = share->polls; fin.nblk = ga.nblk;
       RN50_FWD_APPLY(kFinShared, dim3(fin.groups + static_cast<unsigned>(ga.nblk) * ga.gy), nullptr, nullptr, ga.tx_log2, ga.rpb);
       return;
@@ -985,7 +984,6 @@ static void launch_bwd_tail(const rn50_bn_desc* d, int64_t m, const void* dz,
   if (!self && reduces && bn_reduces(nrows)) {
     fin.wide = bn_reduced_rows(partial, nrows, d->C, true); fin.nwide = kBnReducedRows;
   }
-  if (ga.nblk * ga.gy > kBnShareGroups) share = nullptr;
   dim3 grid;
   if (self) {
     // few tile rows: the apply pass adds them up itself
