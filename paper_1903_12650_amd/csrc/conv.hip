@@ -144,6 +144,19 @@ template <int BM, int BN, int NW>
 constexpr int igemm_ring() {
   return (NW == 4 && 3 * (BM + BN) * 128 > 80 * 1024) ? 2 : 3;
 }
+// DEEP: the 128x128 tile of the forward modes, whose three whole buffers would leave a compute unit one workgroup, has three for A and two
+// for B: 80 KB, two workgroups to the byte (so these kernels have no static LDS; MODE 2's coefficients lie behind the output tile).  A
+// comes from memory, B, the weights, from the L2: with both one chunk ahead a chunk took as long as A's loads, 1.2 us.  23 shapes
+// forward at batch 256 1817 -> 1751 us, 100 869 -> 846, 40 392 -> 390; evaluation at batch 256 4.40 -> 4.28 ms, 64 1.331 -> 1.297.  Not the
+// data gradients: beside the weight gradients they leave them no LDS (step at batch 256 19.14 -> 19.18 ms), alone 1807 -> 1804 us.
+template <int BM, int BN, int WM, int WN, int MODE, bool BNIN, bool HALO>
+constexpr bool igemm_deep_a() {
+  return BM == 128 && BN == 128 && WM * WN == 4 && MODE != 1 && !BNIN && !HALO;
+}
+template <int BM, int BN>
+constexpr int igemm_out_tile() { return BM * (BN * 4 + 16); }  // the output tile in float, with its pitch
+template <int BM, int BN>
+constexpr int igemm_deep_out() { return igemm_out_tile<BM, BN>() + 2 * BN * 4; }  // ... and what lies behind it
 // KS (launched with WM = WN = 1): the four waves of a workgroup split K instead of the tile.  Every wave computes the whole
 // BM x BN tile over a quarter of the chunks, with a ring of its own that it fills and reads without any barrier; at the end
 // the four partial tiles are added in wave order through LDS.  For grids that leave compute units idle or give each a single
@@ -204,6 +217,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   constexpr int NL = RA + RB;
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
   constexpr int STAGE = (BM + BN) * 128;
+  constexpr bool DEEP = igemm_deep_a<BM, BN, WM, WN, MODE, BNIN, HALO>();
   constexpr int NSTAGE = OWN ? igemm_ks_ring<BM, BN, BNIN>() : igemm_ring<BM, BN, WM * WN>();
   constexpr int CP = BN * sizeof(T) + 16;  // epilogue pitch
   static_assert((NW == 4 || NW == 8) && TM >= 1 && TN >= 1 && RA >= 1 && RB >= 1, "tile shape");
@@ -232,7 +246,13 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   // thread per column while the main loop runs (every thread loading its own copies costs the texture path
   // as much as two chunks of the main loop).
   // (MODE 2: the same for the inference-mode affine step.)
-  __shared__ __align__(16) float prm_s[DG ? 4 * BN : (AFF ? 2 * BN : 4)];
+  float* prm_s;
+  if constexpr (DEEP) {
+    prm_s = reinterpret_cast<float*>(smem + igemm_out_tile<BM, BN>());
+  } else {
+    __shared__ __align__(16) float prm_static[DG ? 4 * BN : (AFF ? 2 * BN : 4)];
+    prm_s = prm_static;
+  }
   float pg = 0.f, pb = 0.f, pm = 0.f, pr = 0.f;
   if ((AFF || (DG && a.partial != nullptr)) && tid < BN) {
     const int c = min(n0 + tid, a.Ncols - 1);
@@ -428,17 +448,17 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   typedef __attribute__((address_space(3))) unsigned char* lds_byte_ptr;
   const uint32_t wave_dst = __builtin_amdgcn_readfirstlane(
       static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_byte_ptr)smem)) + static_cast<uint32_t>(wave) * (OWN ? NSTAGE * STAGE : 1024u));
-  auto load_chunk = [&](int stage) __attribute__((always_inline)) {
+  // A's part moves the cursor on and leaves what B's part of the same chunk needs: B's may follow one chunk later (DEEP).
+  uint32_t sob = 0;
+  int b_cc = 0;
+  auto load_a = [&](uint32_t sa) __attribute__((always_inline)) {
     const uint32_t so = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(cur_cc) * 128u);
     auto cval = [&](int i) __attribute__((always_inline)) { return !ragged || (cur_cc * BK + piece_of(i) * V < a.Cg); };
     ++cur;
-    const uint32_t sa = wave_dst + static_cast<uint32_t>(stage) * STAGE;
-    const uint32_t sb = sa + BM * 128;
-    const uint32_t sob = __builtin_amdgcn_readfirstlane(b_at(b_tap, cur_cc));
+    b_cc = cur_cc;
+    sob = __builtin_amdgcn_readfirstlane(b_at(b_tap, cur_cc));
 #pragma unroll
     for (int i = 0; i < RA; ++i) buffer_load16_to_lds(rsA, sa + i * (RPL * 128), cval(i) ? a_off[i] : kOob, so);
-#pragma unroll
-    for (int i = 0; i < RB; ++i) buffer_load16_to_lds(rsB, sb + i * (RPL * 128), b_live(i, cur_cc, cval(i)) ? b_row[i] : kOob, sob);
     // advance the cursor
     if constexpr (LIN) {
       ++cur_cc;
@@ -452,6 +472,16 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       b_tap = cur_r * a.S + cur_s;
       if (cur < nchunks) tap_setup();  // (nothing is loaded past the last chunk)
     }
+  };
+  auto load_b = [&](uint32_t sb, int cc, uint32_t so) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+      buffer_load16_to_lds(rsB, sb + i * (RPL * 128), b_live(i, cc, !ragged || (cc * BK + piece_of(i) * V < a.Cg)) ? b_row[i] : kOob, so);
+  };
+  auto load_chunk = [&](int stage) __attribute__((always_inline)) {
+    const uint32_t sa = wave_dst + static_cast<uint32_t>(stage) * STAGE;
+    load_a(sa);
+    load_b(sa + BM * 128, b_cc, sob);
   };
 
   f32x16 acc[TM][TN];
@@ -475,10 +505,10 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
 #pragma unroll
   for (int j = 0; j < TN; ++j) bt_base[j] = DG ? wgrad_frag_base<T, BRB>(lane, wn * (BN / WN) + j * 32) : 0;
   constexpr int AHEAD = (TM + TN <= 3) ? 4 : 1;  // k steps whose fragments are in registers before the first MFMA
-  auto compute = [&](int stage) __attribute__((always_inline)) {
-    const unsigned char* base = smem + (OWN ? wave * (NSTAGE * STAGE) : 0) + stage * STAGE;
-    const unsigned char* sa = base + wm * (BM / WM) * 128;
-    const unsigned char* sb = base + BM * 128 + (DG ? 0 : wn * (BN / WN) * 128);
+  // `next` issues the loads that go out behind the first fragment reads.
+  auto compute = [&](const unsigned char* tile_a, const unsigned char* tile_b, auto&& next) __attribute__((always_inline)) {
+    const unsigned char* sa = tile_a + wm * (BM / WM) * 128;
+    const unsigned char* sb = tile_b + (DG ? 0 : wn * (BN / WN) * 128);
     Vec16 fa[4][TM], fb[4][TN];
     auto read_frags = [&](int kk) __attribute__((always_inline)) {
 #pragma unroll
@@ -492,6 +522,8 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
 #pragma unroll
     for (int kk = 0; kk < AHEAD; ++kk) read_frags(kk);
     __builtin_amdgcn_sched_barrier(0);  // (the instruction scheduler would sink every read to its first use)
+    next();
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       if (kk + AHEAD < 4) {
@@ -755,6 +787,25 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     }
     __syncthreads();
   }
+  if constexpr (DEEP) {
+    // B's two buffers, then A's three.  Chunk k: A was requested two chunks ago, B one; in front of the wait only A of chunk k + 1 may
+    // still be in flight.
+    const uint32_t dst_a = wave_dst + 2 * BN * 128;
+    if (nchunks > 0) {
+      load_a(dst_a);
+      load_b(wave_dst, b_cc, sob);
+    }
+    if (nchunks > 1) load_a(dst_a + BM * 128);
+    int ia = 0;
+    for (int kc = 0; kc < nchunks; ++kc) {
+      if (kc + 1 < nchunks) wait_loads_then_barrier<RA>(); else wait_loads_then_barrier<0>();
+      compute(smem + 2 * BN * 128 + ia * (BM * 128), smem + (kc & 1) * (BN * 128), [&]() __attribute__((always_inline)) {
+        if (kc + 1 < nchunks) load_b(wave_dst + static_cast<uint32_t>((kc & 1) ^ 1) * (BN * 128), b_cc, sob);
+        if (kc + 2 < nchunks) load_a(dst_a + static_cast<uint32_t>(ia >= 1 ? ia - 1 : 2) * (BM * 128));
+      });
+      ia = ia == 2 ? 0 : ia + 1;
+    }
+  } else {
 #pragma unroll
   for (int c = 0; c < NSTAGE - 1; ++c)
     if (c < nchunks) load_chunk(c);
@@ -787,8 +838,10 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       }
       if (!KS) lds_writes_then_barrier();  // (KS: the wave's own LDS operations stay in order)
     }
-    compute(stage);
+    const unsigned char* const tile = smem + (OWN ? wave * (NSTAGE * STAGE) : 0) + stage * STAGE;
+    compute(tile, tile + BM * 128, [] {});
     stage = stage == NSTAGE - 1 ? 0 : stage + 1;
+  }
   }
   }
   if constexpr (KS) {
@@ -818,6 +871,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       }
   }
   if constexpr (AFF) {
+    if (DEEP) __syncthreads();  // (prm_s lies in the ring)
     if (tid < BN) {
       float sc, bi;
       bn_coeffs(pg, pb, pm, static_cast<float>(1.0 / sqrt(static_cast<double>(pr) + static_cast<double>(a.aff_eps))), &sc, &bi);
@@ -1051,22 +1105,25 @@ static void launch_igemm_through(IgemmArgs a, const char* tag, int64_t grid, hip
   constexpr int es = static_cast<int>(sizeof(T));
   // the output stage reuses the ring: the tile (in float when a bf16 data gradient adds a second branch) and
   // the column sums of the fused batch norm
-  constexpr int out_tile = BM * (BN * 4 + 16);
+  constexpr bool deep = igemm_deep_a<BM, BN, WM, WN, MODE, BNIN, false>();
+  constexpr int out_tile = deep ? igemm_deep_out<BM, BN>() : igemm_out_tile<BM, BN>();
   constexpr int col_sums = (NT / (BN * es / 16)) * 2 * BN * 4;
   constexpr int exchange = KS ? 4 * BM * BN * 4 : 0;     // (KS: the four partial tiles)
   constexpr int out_need = std::max({out_tile, col_sums, exchange});
   static std::once_flag once;
+  constexpr int deep_ring = (2 * BN + 3 * BM) * 128;
+  static_assert(!deep || (deep_ring <= 80 * 1024 && out_need <= deep_ring), "two workgroups per compute unit");
   constexpr int nring = KS ? igemm_ks_ring<BM, BN, BNIN>() : igemm_ring<BM, BN, WM * WN>();
   // input-side BN coefficients: two floats per channel, at most 4096 channels (KS: 2048)
   constexpr int kInTabMax = 8 * (KS ? 2048 : 4096);
   std::call_once(once, [] {
     allow_big_lds(igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN, 0, THROUGH>,
-                  (nring * stage > out_need ? nring * stage : out_need) + (BNIN ? kInTabMax : 0));
+                  std::max({nring * stage, out_need, deep ? deep_ring : 0}) + (BNIN ? kInTabMax : 0));
   });
   // A short reduction never touches the later ring buffers; without them more workgroups fit a CU (the 1x1
   // layers with 64 channels, the largest pixel counts of the net, have a single chunk).
   const int chunks = a.R * a.S * a.cpt;
-  const int ring = (!KS && chunks < nring ? (chunks < 1 ? 1 : chunks) : nring) * stage;
+  const int ring = deep ? (2 * BN + std::min(chunks, 3) * BM) * 128 : (!KS && chunks < nring ? (chunks < 1 ? 1 : chunks) : nring) * stage;
   int lds = ring > out_need ? ring : out_need;
   if (BNIN) {
     a.in_lds = lds;
@@ -1105,7 +1162,7 @@ static void launch_igemm_halo_through(IgemmArgs a, const char* tag, int64_t grid
   constexpr bool KS = WM * WN == 1;
   constexpr int NT = KS ? 256 : 64 * WM * WN;
   constexpr int es = static_cast<int>(sizeof(T));
-  constexpr int out_tile = BM * (BN * 4 + 16);
+  constexpr int out_tile = igemm_out_tile<BM, BN>();
   constexpr int col_sums = (NT / (BN * es / 16)) * 2 * BN * 4;
   constexpr int exchange = KS ? 4 * BM * BN * 4 : 0;     // (KS: the four partial tiles)
   constexpr int out_need = std::max({out_tile, col_sums, exchange});

@@ -439,3 +439,22 @@ def test_weight_gradient_steps_over_rows_and_images(rn, mode_name, N, H, W, C, K
     dw = torch.full((K, R, R, C), float("nan"), device="cuda")
     rn.conv_wgrad(x.cuda(), dy.cuda(), (K, R, R, C), stride, pad, dw=dw)
     assert_close(dw, want.numpy(), 1e-5, "dw", elementwise=None)  # (products of the inputs as they are, float sums of at most 3,000)
+
+
+# Forward on the 128x128 tile (from 384 of them on), whose two rings are of different depth: reductions of two chunks (no third buffer of A),
+# three, four and more, ragged channels on both sides, a strided gather with one chunk and with several per tap, a last row tile of one row.
+DEEP_RING = [(8, 56, 56, 128, 256, 1, 1), (8, 56, 56, 136, 200, 1, 1), (8, 56, 56, 200, 256, 1, 1), (1, 157, 157, 328, 136, 1, 1), (8, 112, 112, 40, 200, 3, 2),
+             (8, 111, 112, 72, 136, 3, 2), (2, 159, 157, 64, 128, 2, 1)]
+
+
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("N,H,W,C,K,R,stride", DEEP_RING)
+def test_forward_with_rings_of_different_depth(rn, mode_name, N, H, W, C, K, R, stride):
+    dt, pad = torch.bfloat16 if mode_name == "bf16" else torch.float32, R // 2
+    gen = torch.Generator().manual_seed(C + K)
+    x, w = torch.randn(N, H, W, C, generator=gen).to(dt), (torch.randn(K, R, R, C, generator=gen) / (R * R * C) ** 0.5).to(dt)
+    want = torch.nn.functional.conv2d(x.float().permute(0, 3, 1, 2), w.float().permute(0, 3, 1, 2), stride=stride, padding=pad).permute(0, 2, 3, 1).contiguous()
+    y = torch.full(want.shape, float("nan"), device="cuda", dtype=dt)
+    rn.conv_fwd(x.cuda(), w.cuda(), stride, pad, y=y)
+    assert_close(y, want.numpy(), TOL[mode_name], "y")
+    assert torch.equal(y, rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), stride, pad)[0])
