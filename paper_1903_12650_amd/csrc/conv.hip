@@ -155,8 +155,6 @@ constexpr bool igemm_deep_a() {
 }
 template <int BM, int BN>
 constexpr int igemm_out_tile() { return BM * (BN * 4 + 16); }  // the output tile in float, with its pitch
-template <int BM, int BN>
-constexpr int igemm_deep_out() { return igemm_out_tile<BM, BN>() + 2 * BN * 4; }  // ... and what lies behind it
 // KS (launched with WM = WN = 1): the four waves of a workgroup split K instead of the tile.  Every wave computes the whole
 // BM x BN tile over a quarter of the chunks, with a ring of its own that it fills and reads without any barrier; at the end
 // the four partial tiles are added in wave order through LDS.  For grids that leave compute units idle or give each a single
@@ -788,20 +786,22 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     __syncthreads();
   }
   if constexpr (DEEP) {
-    // B's two buffers, then A's three.  Chunk k: A was requested two chunks ago, B one; in front of the wait only A of chunk k + 1 may
-    // still be in flight.
-    const uint32_t dst_a = wave_dst + 2 * BN * 128;
+    // Buffers of 16 KB: B0 A0 A1 B1 A2 (a reduction of one chunk has the first two, of two the first four).  Chunk k: A was requested two
+    // chunks ago, B one; behind the wait only A of chunk k + 1 may still be in flight.
+    static_assert(!DEEP || BM == BN, "buffers of one size");
+    auto buf_a = [](int i) __attribute__((always_inline)) { return static_cast<uint32_t>(i + 1 + (i >> 1)) * (BM * 128); };
+    auto buf_b = [](int i) __attribute__((always_inline)) { return static_cast<uint32_t>(3 * i) * (BM * 128); };
     if (nchunks > 0) {
-      load_a(dst_a);
-      load_b(wave_dst, b_cc, sob);
+      load_a(wave_dst + buf_a(0));
+      load_b(wave_dst + buf_b(0), b_cc, sob);
     }
-    if (nchunks > 1) load_a(dst_a + BM * 128);
+    if (nchunks > 1) load_a(wave_dst + buf_a(1));
     int ia = 0;
     for (int kc = 0; kc < nchunks; ++kc) {
       if (kc + 1 < nchunks) wait_loads_then_barrier<RA>(); else wait_loads_then_barrier<0>();
-      compute(smem + 2 * BN * 128 + ia * (BM * 128), smem + (kc & 1) * (BN * 128), [&]() __attribute__((always_inline)) {
-        if (kc + 1 < nchunks) load_b(wave_dst + static_cast<uint32_t>((kc & 1) ^ 1) * (BN * 128), b_cc, sob);
-        if (kc + 2 < nchunks) load_a(dst_a + static_cast<uint32_t>(ia >= 1 ? ia - 1 : 2) * (BM * 128));
+      compute(smem + buf_a(ia), smem + buf_b(kc & 1), [&]() __attribute__((always_inline)) {
+        if (kc + 1 < nchunks) load_b(wave_dst + buf_b((kc & 1) ^ 1), b_cc, sob);
+        if (kc + 2 < nchunks) load_a(wave_dst + buf_a(ia >= 1 ? ia - 1 : 2));
       });
       ia = ia == 2 ? 0 : ia + 1;
     }
@@ -1106,24 +1106,26 @@ static void launch_igemm_through(IgemmArgs a, const char* tag, int64_t grid, hip
   // the output stage reuses the ring: the tile (in float when a bf16 data gradient adds a second branch) and
   // the column sums of the fused batch norm
   constexpr bool deep = igemm_deep_a<BM, BN, WM, WN, MODE, BNIN, false>();
-  constexpr int out_tile = deep ? igemm_deep_out<BM, BN>() : igemm_out_tile<BM, BN>();
   constexpr int col_sums = (NT / (BN * es / 16)) * 2 * BN * 4;
   constexpr int exchange = KS ? 4 * BM * BN * 4 : 0;     // (KS: the four partial tiles)
-  constexpr int out_need = std::max({out_tile, col_sums, exchange});
+  constexpr int behind = deep ? 2 * BN * 4 : 0;          // (behind the output tile: MODE 2's coefficients)
+  constexpr int out_most = std::max({igemm_out_tile<BM, BN>() + behind, col_sums, exchange});
   static std::once_flag once;
   constexpr int deep_ring = (2 * BN + 3 * BM) * 128;
-  static_assert(!deep || (deep_ring <= 80 * 1024 && out_need <= deep_ring), "two workgroups per compute unit");
+  static_assert(!deep || (deep_ring <= 80 * 1024 && out_most <= deep_ring), "two workgroups per compute unit");
   constexpr int nring = KS ? igemm_ks_ring<BM, BN, BNIN>() : igemm_ring<BM, BN, WM * WN>();
   // input-side BN coefficients: two floats per channel, at most 4096 channels (KS: 2048)
   constexpr int kInTabMax = 8 * (KS ? 2048 : 4096);
   std::call_once(once, [] {
     allow_big_lds(igemm_kernel<T, BM, BN, WM, WN, MODE, LIN, BNIN, 0, THROUGH>,
-                  std::max({nring * stage, out_need, deep ? deep_ring : 0}) + (BNIN ? kInTabMax : 0));
+                  std::max({nring * stage, out_most, deep ? deep_ring : 0}) + (BNIN ? kInTabMax : 0));
   });
-  // A short reduction never touches the later ring buffers; without them more workgroups fit a CU (the 1x1
-  // layers with 64 channels, the largest pixel counts of the net, have a single chunk).
+  // A short reduction never touches the later ring buffers, and an output tile in the storage type is half as large as in float; with
+  // less LDS more workgroups fit a CU (the 1x1 layers with 64 channels, the largest pixel counts of the net, have a single chunk).
   const int chunks = a.R * a.S * a.cpt;
-  const int ring = deep ? (2 * BN + std::min(chunks, 3) * BM) * 128 : (!KS && chunks < nring ? (chunks < 1 ? 1 : chunks) : nring) * stage;
+  const int ring = deep ? (chunks >= 3 ? deep_ring : chunks * stage) : (!KS && chunks < nring ? (chunks < 1 ? 1 : chunks) : nring) * stage;
+  const bool wide = es == 2 && (MODE == 2 || (MODE == 1 && a.partial != nullptr && a.addend != nullptr));
+  const int out_need = std::max({(wide ? igemm_out_tile<BM, BN>() : BM * (BN * es + 16)) + behind, col_sums, exchange});
   int lds = ring > out_need ? ring : out_need;
   if (BNIN) {
     a.in_lds = lds;
@@ -1246,14 +1248,14 @@ struct TileShape {
 // workgroups per compute unit wins -- larger tiles load fewer operand bytes per flop (the main loop's bound) but with a smaller
 // grid the latencies of a workgroup's load -> LDS -> MFMA chain are exposed; a reduction of one chunk has nothing to reuse and
 // takes the smallest tile (64 -> 64 at 56x56, batch 256, 30 us against 31 and 45 for 128x64 and 128x128, batch 40 5.2 against 5.6 and
-// 8.7; larger tiles would be faster where the largest data gradient has more columns: 256 <- 64 at 56x56, batch 256, 140 us against
-// 125 and 111, but 15.3 against 15.0 and 16.3 at batch 40).  Summed over the shapes the rule is within 2 % of the best tiles at
-// batch 40 and within 4 % at 256.
+// 8.7), but with more than 64 columns and kCover tiles of 128x128 or more that one, which reads A half as often (and, with one chunk,
+// fits a compute unit four times): 23 shapes forward / 22 data gradients at batch 256 1790 / 1855 -> 1764 / 1816 us, 100 861 / 877 -> 850 / 869, 40
+// 394 / 390 -> 390 / 387, 18 259 / 262 -> 257 / 261, the step at batch 256 19.17 -> 18.98 ms.
 static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool strided_dgrad, int live = 4) {
   const int64_t classes = strided_dgrad ? live : 1;
   auto groups = [&](int bm, int bn) { return ceil_div(M, bm) * ceil_div(Ncols, bn) * classes; };
   constexpr int64_t kCover = 384;  // workgroups: one and a half per compute unit (two four-wave workgroups fit each)
-  if (chunks <= 1) return TileShape{64, 64, 2, 2};
+  if (chunks <= 1) return Ncols > 64 && groups(128, 128) >= kCover ? TileShape{128, 128, 2, 2} : TileShape{64, 64, 2, 2};
   if (Ncols > 64) {
     // (not the eight-wave 256x128 tile, also in the largest data gradients, which had it from 1536 tiles on: 22 shapes at batch 256
     // 3668 -> 3504 us without it, 128 1812 -> 1775; in the step at batch 256 19.49 -> 19.31 ms)

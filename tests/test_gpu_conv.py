@@ -458,3 +458,28 @@ def test_forward_with_rings_of_different_depth(rn, mode_name, N, H, W, C, K, R, 
     rn.conv_fwd(x.cuda(), w.cuda(), stride, pad, y=y)
     assert_close(y, want.numpy(), TOL[mode_name], "y")
     assert torch.equal(y, rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), stride, pad)[0])
+
+
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("N,H,W,C,K", [(21, 56, 56, 64, 200), (1, 257, 255, 24, 136), (16, 64, 64, 32, 264), (6, 64, 64, 16, 256)])
+def test_one_chunk_on_large_tiles(rn, mode_name, N, H, W, C, K):
+    """1x1 layers whose reduction is one chunk and whose grid has at least 384 tiles of 128x128 (the second: 512 rows of tiles, the last of 127 rows):
+    forward with and without sums, the data gradient likewise, with a second branch and at stride 2, into buffers of NaNs."""
+    dt = torch.bfloat16 if mode_name == "bf16" else torch.float32
+    gen = torch.Generator().manual_seed(C + K)
+    rand = lambda *shape, scale=1.0: (torch.randn(*shape, generator=gen) * scale).to(dt)
+    nan = lambda *shape: torch.full(shape, float("nan"), device="cuda", dtype=dt)
+    x, w, wt, add = rand(N, H, W, C), rand(K, 1, 1, C, scale=C ** -0.5), rand(C, 1, 1, K, scale=C ** -0.5), rand(N, H, W, K)
+    y = rn.conv_fwd(x.cuda(), w.cuda(), 1, 0, y=nan(N, H, W, K))
+    want = x.float().reshape(-1, C) @ w.float().reshape(K, C).t()
+    assert_close(y.view(-1, K), want.numpy(), TOL[mode_name], "y")
+    assert torch.equal(y, rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), 1, 0)[0])
+    dx = rn.conv_dgrad(x.cuda(), wt.cuda(), (N, H, W, K), 1, 0, dx=nan(N, H, W, K))
+    want = x.float().reshape(-1, C) @ wt.float().reshape(C, K)
+    assert_close(dx.view(-1, K), want.numpy(), TOL[mode_name], "dx")
+    one, zero = torch.ones(K, device="cuda"), torch.zeros(K, device="cuda")
+    assert torch.equal(dx, rn.conv_dgrad_bn_sums(x.cuda(), wt.cuda(), (N, H, W, K), 1, 0, y, one, zero, zero, one)[0])
+    both = rn.conv_dgrad_bn_sums(x.cuda(), wt.cuda(), (N, H, W, K), 1, 0, y, one, zero, zero, one, addend=add.cuda())[0]
+    assert_close(both.view(-1, K), (want + add.float().reshape(-1, K)).numpy(), TOL[mode_name], "dx + addend")
+    dx2 = rn.conv_dgrad(x.cuda(), wt.cuda(), (N, 2 * H, 2 * W, K), 2, 0, dx=nan(N, 2 * H, 2 * W, K))
+    assert torch.equal(dx2[:, ::2, ::2], dx) and not dx2[:, 1::2].any() and not dx2[:, :, 1::2].any()
