@@ -1154,7 +1154,7 @@ static int halo_lds_bytes(int W, int cpt, int taps) {
   constexpr bool KS = WM * WN == 1;
   constexpr int NW = WM * WN == 1 ? 4 : WM * WN, RPL = NW * 8;
   const int passes = (BM + 2 * W + 2 + RPL - 1) / RPL;
-  if (passes > 8) return 0;
+  if (passes > 8 && (cpt > 1 || BM != 256 || BN != 64)) return 0;  // (a chunk's taps load the next one's run)
   const int runs = (cpt > 1 ? 2 : 1) * passes * RPL * 128;
   const int bytes = runs + (taps == 3 ? 3 * (igemm_row_ahead<T, KS>() + 1) * BN * 128 : 3 * BN * 128 + NW * 1024);
   return bytes <= (taps == 3 && !KS ? kHaloRowLdsMax : kHaloLdsMax) ? bytes : 0;
@@ -1211,7 +1211,7 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
     a.div_h[c] = make_fastdiv(classes ? (a.P - c + 1) >> 1 : a.P);
   }
   if (a.linear) {
-    if constexpr (BM <= 128 || kTuning) {  // (the eight-wave tile is igemm_halo_tile's alone)
+    if constexpr (BM <= 128 || kTuning) {  // (the tiles of 256 rows are igemm_halo_tile's alone)
       if (a.mode == 1) launch_igemm_mode<T, BM, BN, WM, WN, 1, true>(a, tag, grid, s);
       else if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, true>(a, tag, grid, s);
       else if (a.in_gamma) launch_igemm_mode<T, BM, BN, WM, WN, 0, true, true>(a, tag, grid, s);
@@ -1229,16 +1229,18 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
       if (lds) return launch_igemm_halo_mode<T, BM, BN, WM, WN, 1>(a, tag, grid, lds, s);
     }
   }
-  if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, false>(a, tag, grid, s);
-  else if (a.mode == 0) launch_igemm_mode<T, BM, BN, WM, WN, 0, false>(a, tag, grid, s);
-  else launch_igemm_mode<T, BM, BN, WM, WN, 1, false>(a, tag, grid, s);
+  if constexpr (BM != 256 || BN != 64 || kTuning) {  // (igemm_halo_tile takes the 256x64 tile where its run fits)
+    if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, false>(a, tag, grid, s);
+    else if (a.mode == 0) launch_igemm_mode<T, BM, BN, WM, WN, 0, false>(a, tag, grid, s);
+    else launch_igemm_mode<T, BM, BN, WM, WN, 1, false>(a, tag, grid, s);
+  }
 }
 
 // Tile per layer shape.  The compiled shapes: rows x columns of the workgroup tile, waves along rows x columns.
 struct TileShape {
   int bm, bn, wm, wn;
 };
-#define RN50_IGEMM_SHAPES(X) X(64, 64, 2, 2) X(128, 64, 2, 2) X(128, 128, 2, 2) X(256, 128, 4, 2) X(64, 64, 1, 1)
+#define RN50_IGEMM_SHAPES(X) X(64, 64, 2, 2) X(128, 64, 2, 2) X(256, 64, 4, 1) X(128, 128, 2, 2) X(256, 128, 4, 2) X(64, 64, 1, 1)
 #define RN50_IGEMM_SHAPE_BF16(X) X(32, 64, 1, 1)
 #define RN50_IGEMM_SHAPE_F32(X) X(32, 32, 1, 1)
 // The tile of a layer shape: M rows (output pixels; of one parity class for a stride-2 data gradient, `live` of
@@ -1255,7 +1257,6 @@ static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool strided_dgrad
   const int64_t classes = strided_dgrad ? live : 1;
   auto groups = [&](int bm, int bn) { return ceil_div(M, bm) * ceil_div(Ncols, bn) * classes; };
   constexpr int64_t kCover = 384;  // workgroups: one and a half per compute unit (two four-wave workgroups fit each)
-  if (chunks <= 1) return Ncols > 64 && groups(128, 128) >= kCover ? TileShape{128, 128, 2, 2} : TileShape{64, 64, 2, 2};
   if (Ncols > 64) {
     // (not the eight-wave 256x128 tile, also in the largest data gradients, which had it from 1536 tiles on: 22 shapes at batch 256
     // 3668 -> 3504 us without it, 128 1812 -> 1775; in the step at batch 256 19.49 -> 19.31 ms)
@@ -1269,8 +1270,14 @@ static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool strided_dgrad
 // eight-wave 256x128 tile once it gives three quarters of the compute units a workgroup, else 128x64 while that
 // leaves one and a half workgroups per compute unit, else 64x64 (the 128x128 tile never won: its two runs and
 // three weight tiles leave room for one workgroup per compute unit only).
-static TileShape igemm_halo_tile(int64_t M, int Ncols) {
+constexpr int kHaloTallWidth = 63;
+static TileShape igemm_halo_tile(int64_t M, int Ncols, int cpt, int W) {
   auto groups = [&](int bm, int bn) { return ceil_div(M, bm) * ceil_div(Ncols, bn); };
+  // One chunk of channels into at most 64 columns: four waves of 64x64 one above the other read two thirds of the fragment bytes per product
+  // of the 128x64 tile's 64x32 waves, and a run of 256 + 2W + 2 pixels with its weights still leaves a compute unit two workgroups
+  // (kHaloTallWidth: 12 load passes).  64 -> 64 at 56x56, us, forward / data gradient: batch 256 89.8 / 102.4 -> 67.3 / 74.2, 90 34.4 / 39.3 ->
+  // 28.0 / 30.5, 40 16.1 / 18.5 -> 12.4 / 15.1, 32 15.4 / 18.2 -> 11.7 / 13.7.
+  if (Ncols <= 64 && cpt == 1 && W <= kHaloTallWidth && groups(256, 64) >= 384) return TileShape{256, 64, 4, 1};
   if (Ncols > 64 && groups(256, 128) >= 192) return TileShape{256, 128, 4, 2};
   if (groups(128, 64) >= 384) return TileShape{128, 64, 2, 2};
   return TileShape{64, 64, 2, 2};
@@ -1299,7 +1306,7 @@ static bool igemm_halo_shape(const IgemmArgs& a) {
 // compute unit of the shared ring do better.  Limits of 0 / 128 / 256 / 384 / 512 tiles in the whole step: float at batch 8 4.77 /
 // 4.12 / 4.02 / 4.02 / 4.40 ms, bf16 at batch 40 4.250 / 4.253 / 4.240 / 4.242 / 4.499 (profiles/step_time_against_dispatch_constants.txt;
 // layer by layer: profiles/conv_tile_sweep_*.txt).
-static TileShape pick_tile(int64_t rows, int Ncols, int chunks, bool strided_dgrad, int live, bool halo, int lin_fwd_channels,
+static TileShape pick_tile(int64_t rows, int Ncols, int chunks, bool strided_dgrad, int live, int halo_width, int lin_fwd_channels,
                            int dtype) {
 #ifdef RN50_TUNING  // tuning builds only: RN50_IGEMM_TILE=bm,bn,wm,wn forces a compiled tile shape
   if (const char* e = getenv("RN50_IGEMM_TILE")) {
@@ -1317,7 +1324,7 @@ static TileShape pick_tile(int64_t rows, int Ncols, int chunks, bool strided_dgr
     if (groups64 > 128) return TileShape{64, 64, 1, 1};
     return dtype == RN50_F32 ? TileShape{32, 32, 1, 1} : TileShape{32, 64, 1, 1};
   }
-  return halo ? igemm_halo_tile(rows, Ncols) : igemm_tile(rows, Ncols, chunks, strided_dgrad, live);
+  return halo_width > 0 ? igemm_halo_tile(rows, Ncols, chunks / 9, halo_width) : igemm_tile(rows, Ncols, chunks, strided_dgrad, live);
 }
 template <typename T>
 static void launch_igemm(const IgemmArgs& a, const char* tag, hipStream_t s) {
@@ -1325,7 +1332,7 @@ static void launch_igemm(const IgemmArgs& a, const char* tag, hipStream_t s) {
   const int64_t rows = classes ? static_cast<int64_t>(a.M / (a.P * a.Q)) * ((a.P + 1) / 2) * ((a.Q + 1) / 2) : a.M;
   const bool lin_fwd = a.mode != 1 && a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0 && !a.pair;
   const TileShape t = pick_tile(rows, a.Ncols, a.R * a.S * a.cpt, classes, a.R * a.S > 1 ? 4 : 1,
-                                igemm_halo_shape(a), lin_fwd ? a.Cg : 0, sizeof(T) == 2 ? RN50_BF16 : RN50_F32);
+                                igemm_halo_shape(a) ? a.W : 0, lin_fwd ? a.Cg : 0, sizeof(T) == 2 ? RN50_BF16 : RN50_F32);
 #define X(BM, BN, WM, WN) if (t.bm == BM && t.bn == BN && t.wm == WM && t.wn == WN) launch_igemm_cfg<T, BM, BN, WM, WN>(a, tag, s);
   RN50_IGEMM_SHAPES(X)
   if constexpr (sizeof(T) == 4) { RN50_IGEMM_SHAPE_F32(X) } else { RN50_IGEMM_SHAPE_BF16(X) }
@@ -1387,7 +1394,7 @@ static int chunks_per_tap(int channels, int dtype) { return static_cast<int>(cei
 static PartialRows class_tile_rows(const rn50_conv_desc* d) {
   const int64_t rows = static_cast<int64_t>(d->N) * ((d->H + 1) / 2) * ((d->W + 1) / 2);
   const int bm = pick_tile(rows, d->Cin, d->R * d->S * chunks_per_tap(d->Cout, d->dtype), true, d->R * d->S > 1 ? 4 : 1,
-                           false, 0, d->dtype).bm;
+                           0, 0, d->dtype).bm;
   return PartialRows{bm, static_cast<int>(4 * ceil_div(rows, bm))};
 }
 PartialRows fwd_partial_rows(const rn50_conv_desc* d) {
@@ -1396,7 +1403,7 @@ PartialRows fwd_partial_rows(const rn50_conv_desc* d) {
   // the chunk count as the launch computes it (the bf16 stem runs as 4 taps of one chunk, the float stem as 7)
   const int chunks = is_stem(d) ? (d->dtype == RN50_BF16 ? 4 : 7) : d->R * d->S * chunks_per_tap(d->Cin, d->dtype);
   const bool lin = d->R == 1 && d->S == 1 && d->stride == 1 && d->pad == 0;
-  const int bm = pick_tile(M, d->Cout, chunks, false, 4, halo_filter(d->R, d->S, d->stride, d->pad), lin ? d->Cin : 0, d->dtype).bm;
+  const int bm = pick_tile(M, d->Cout, chunks, false, 4, halo_filter(d->R, d->S, d->stride, d->pad) ? d->W : 0, lin ? d->Cin : 0, d->dtype).bm;
   return PartialRows{bm, static_cast<int>(ceil_div(M, bm))};
 }
 int64_t dgrad_partial_rows_bound(const rn50_conv_desc* d) {
@@ -1408,7 +1415,7 @@ PartialRows dgrad_partial_rows(const rn50_conv_desc* d) {
   if (d->stride == 2) return class_tile_rows(d);
   const int64_t M = static_cast<int64_t>(d->N) * d->H * d->W;
   const int bm = pick_tile(M, d->Cin, d->R * d->S * chunks_per_tap(d->Cout, d->dtype), false, 4,
-                           halo_filter(d->R, d->S, d->stride, d->pad), 0, d->dtype).bm;
+                           halo_filter(d->R, d->S, d->stride, d->pad) ? d->W : 0, 0, d->dtype).bm;
   return PartialRows{bm, static_cast<int>(ceil_div(M, bm))};
 }
 

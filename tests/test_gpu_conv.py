@@ -316,10 +316,13 @@ def test_images_too_wide_for_the_halo_loop(rn, mode_name, N, H, W, C, K):
 HALO_ROWS = [(1, 1, 1, 8, 8), (1, 2, 1, 64, 64), (2, 5, 3, 72, 40), (1, 3, 111, 64, 64), (1, 3, 112, 64, 64), (1, 30, 95, 136, 24), (1, 30, 96, 136, 24),
              (1, 90, 95, 64, 64), (1, 90, 96, 64, 64), (1, 120, 79, 72, 64), (1, 120, 80, 72, 64), (40, 14, 14, 200, 128), (60, 13, 15, 200, 128),
              (60, 13, 16, 136, 128), (6, 57, 56, 64, 64), (3, 83, 79, 64, 64), (3, 83, 80, 64, 64), (81, 14, 14, 72, 128), (84, 14, 14, 72, 128)]
+# ... and the tap by tap loop of the tallest tile (256x64, from 384 of them on): whole and ragged, the widest image it takes and one column
+# more, images of one column, more channels than a chunk (bf16: 64).
+HALO_TALL = [(32, 56, 56, 64, 64), (25, 63, 63, 40, 24), (25, 62, 64, 40, 24), (33, 3000, 1, 16, 64), (1, 1, 98400, 8, 8), (33, 56, 54, 72, 64)]
 
 
 @pytest.mark.parametrize("mode_name", ["f32", "bf16"])
-@pytest.mark.parametrize("N,H,W,C,K", HALO_ROWS)
+@pytest.mark.parametrize("N,H,W,C,K", HALO_ROWS + HALO_TALL)
 def test_3x3_by_filter_rows(rn, mode_name, N, H, W, C, K):
     """Forward with and without sums, data gradient with and without, into buffers of NaNs, against 64 bits."""
     dt = torch.bfloat16 if mode_name == "bf16" else torch.float32
