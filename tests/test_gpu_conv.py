@@ -426,7 +426,12 @@ def test_wgrad_plan_edges(rn, mode_name, case):
 WGRAD_STEPS = [(70, 1, 1, 16, 24, 3, 1, 1), (70, 2, 2, 16, 24, 3, 2, 1), (3, 70, 1, 16, 24, 3, 1, 1), (3, 1, 70, 16, 24, 3, 1, 1), (2, 5, 31, 40, 72, 3, 1, 1),
                (2, 5, 32, 40, 72, 3, 1, 1), (2, 5, 33, 40, 72, 3, 1, 1), (2, 3, 63, 72, 8, 3, 1, 1), (2, 3, 64, 72, 8, 3, 1, 1), (2, 3, 65, 72, 8, 3, 1, 1),
                (2, 3, 130, 72, 8, 3, 1, 1), (5, 8, 8, 136, 72, 3, 1, 1), (5, 4, 8, 136, 72, 3, 1, 1), (11, 7, 7, 136, 72, 3, 1, 1), (9, 13, 15, 72, 136, 3, 2, 1),
-               (3, 29, 27, 64, 64, 1, 2, 0), (3, 17, 21, 24, 40, 2, 1, 1), (2, 33, 18, 24, 40, 5, 3, 2), (2, 9, 11, 16, 16, 1, 1, 0)]
+               (3, 29, 27, 64, 64, 1, 2, 0), (3, 17, 21, 24, 40, 2, 1, 1), (2, 33, 18, 24, 40, 5, 3, 2), (2, 9, 11, 16, 16, 1, 1, 0),
+               # (all nine taps in one workgroup: an image of exactly a chunk of 64 padded positions, of fewer, of one more row; widths on both
+               # sides of every count of passes over the run of x, and the first that no run holds)
+               (11, 7, 7, 64, 64, 3, 1, 1), (9, 6, 6, 16, 24, 3, 1, 1), (5, 8, 7, 64, 64, 3, 1, 1), (40, 2, 1, 64, 48, 3, 1, 1), (3, 9, 14, 64, 64, 3, 1, 1),
+               (3, 9, 15, 64, 64, 3, 1, 1), (3, 9, 30, 64, 64, 3, 1, 1), (3, 9, 31, 64, 64, 3, 1, 1), (3, 5, 62, 64, 64, 3, 1, 1), (3, 5, 63, 64, 64, 3, 1, 1),
+               (2, 3, 64, 64, 64, 3, 1, 1)]
 
 
 @pytest.mark.parametrize("mode_name", ["f32", "bf16"])
