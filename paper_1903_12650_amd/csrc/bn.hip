@@ -30,6 +30,14 @@ namespace rn50 {
 
 constexpr int kBnRows = 4;  // rows a thread loads before it touches any of them (memory-level parallelism)
 
+// 16 bytes at a uniform address plus a lane's byte offset: the address costs the lanes nothing.  A row's offset of fewer than 256 rows
+// fits 32 bits up to this many channels.
+constexpr int kBnLaneOffsetChannels = 1 << 21;
+template <typename T>
+__device__ __forceinline__ Vec16 load16_at(const T* uniform_base, uint32_t lane_bytes) {
+  return load16(reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(uniform_base) + lane_bytes));
+}
+
 struct BnGeom {
   int V;        // elements per 16-byte vector
   int cvecs;    // C / V
@@ -156,7 +164,10 @@ __device__ __forceinline__ bool combine_sums(float* acc, float* lds, int tx_log2
 // ------------------------------------------------------------------- forward
 // Sums of a row block, about a shift of its own channel's first element, stored in either form (wide: doubles).  Bound by the
 // bytes in flight: eight rows per thread are requested before the first is used (with four, and the LDS tree at the end, 64 MB
-// took 29 us).
+// took 29 us).  A batch of rows that are all there (nearly every one) has one offset per lane behind uniform row addresses and no test per
+// row; an address of 64 bits per row, clamped, delayed the loads of small layers by as much as they take (bf16, batch 40: 56x56x64 8.9 ->
+// 7.5 us, 28x28x128 7.5 -> 5.2, 14x14x256 5.3 -> 4.5; 64 MB the same; the nine layers' both directions 521 -> 506, float at batch 8 298 ->
+// 281).  The apply passes lose by the same change (step at batch 12 1.6 %, 40 and 256 0.6 %: they need the row offsets again to store).
 template <typename T>
 __global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ x, int64_t m, int C,
                                                        int tx_log2, int rpb, int wide,
@@ -174,25 +185,37 @@ __global__ __launch_bounds__(256) void bn_stats_kernel(const T* __restrict__ x, 
   if (col < C / V) {
     const T* p = x + static_cast<int64_t>(col) * V;
     const Vec16 k0 = load16(p);
+    const uint32_t lane_off = (static_cast<uint32_t>(trow) * C + static_cast<uint32_t>(col) * V) * sizeof(T);
     Vec16 v[U];
     bool first = true;
-    for (int64_t r = r0 + trow; r < r1; r += U * TY) {
+    auto add = [&](const Vec16& w) __attribute__((always_inline)) {
+      float f[V];
+      Elem<T>::unpack(w, f);
 #pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = load16(p + min(r + u * TY, r1 - 1) * C);
+      for (int j = 0; j < V; ++j) {
+        const float d = f[j] - K[j];
+        acc[j] += d;
+        acc[V + j] = fmaf(d, d, acc[V + j]);
+      }
+    };
+    for (int64_t rb = r0; rb < r1; rb += U * TY) {
+      const bool whole = rb + U * TY <= r1 && C <= kBnLaneOffsetChannels;
+      if (whole) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = load16_at(x + (rb + u * TY) * C, lane_off);
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = load16(p + min(rb + trow + u * TY, r1 - 1) * C);
+      }
       if (first) Elem<T>::unpack(k0, K);
       first = false;
+      if (whole) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (r + u * TY < r1) {
-          float f[V];
-          Elem<T>::unpack(v[u], f);
+        for (int u = 0; u < U; ++u) add(v[u]);
+      } else {
 #pragma unroll
-          for (int j = 0; j < V; ++j) {
-            const float d = f[j] - K[j];
-            acc[j] += d;
-            acc[V + j] = fmaf(d, d, acc[V + j]);
-          }
-        }
+        for (int u = 0; u < U; ++u)
+          if (rb + trow + u * TY < r1) add(v[u]);
       }
     }
   }
@@ -665,6 +688,27 @@ __device__ __forceinline__ void load_bwd_rows(BwdRows<DZ2, ZK>& b, const T* dz, 
   }
 }
 
+// The same where all of the workgroup's rows from rb on are there (b.off is left alone).
+template <typename T, bool DZ2, int ZK>
+__device__ __forceinline__ void load_bwd_whole_rows(BwdRows<DZ2, ZK>& b, const T* dz, const T* dz2, const T* x, const T* z,
+                                                    const uint8_t* zmask, int64_t rb, int TY, int C, uint32_t lane_elem) {
+  constexpr int V = Elem<T>::VEC;
+  const uint32_t lane_off = lane_elem * static_cast<uint32_t>(sizeof(T)), lane_vec = lane_elem / V;
+#pragma unroll
+  for (int u = 0; u < kBnRows; ++u) {
+    const int64_t at = (rb + u * TY) * C;
+    b.x[u] = load16_at(x + at, lane_off);
+    b.dz[u] = load16_at(dz + at, lane_off);
+  }
+#pragma unroll
+  for (int u = 0; u < kBnRows; ++u) {
+    const int64_t at = (rb + u * TY) * C;
+    if (DZ2) b.dz2[DZ2 ? u : 0] = load16_at(dz2 + at, lane_off);
+    if (ZK == 2) b.zbits[ZK == 2 ? u : 0] = (zmask + at / V)[lane_vec];
+    else if (ZK == 1) b.z[ZK == 1 ? u : 0] = load16_at(z + at, lane_off);
+  }
+}
+
 // g = (dz + dz2) * mask for one 16-byte vector.
 template <typename T, bool DZ2, int ZK>
 __device__ __forceinline__ void masked_grad(const BwdRows<DZ2, ZK>& b, int u, const float* xf, const float* scale,
@@ -732,21 +776,28 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(
     }
     const int64_t r0 = static_cast<int64_t>(blockIdx.x) * rpb;
     const int64_t r1 = min(r0 + rpb, m);
-    for (int64_t r = r0 + trow; r < r1; r += kBnRows * TY) {
+    const uint32_t lane_elem = static_cast<uint32_t>(trow) * C + static_cast<uint32_t>(col) * V;
+    auto add = [&](const BwdRows<DZ2, ZK>& b, int u) __attribute__((always_inline)) {
+      float xf[V], g[V];
+      Elem<T>::unpack(b.x[u], xf);
+      masked_grad<T, DZ2, ZK>(b, u, xf, scale, bias, mode, g);
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        acc[j] += g[j];
+        acc[V + j] = fmaf(g[j], fmaf(xf[j], rs[j], nmr[j]), acc[V + j]);
+      }
+    };
+    for (int64_t rb = r0; rb < r1; rb += kBnRows * TY) {
       BwdRows<DZ2, ZK> b;
-      load_bwd_rows<false, T, DZ2, ZK>(b, dz, dz2, x, z, zmask, r, r1, TY, C, col);
+      if (rb + kBnRows * TY <= r1 && C <= kBnLaneOffsetChannels) {
+        load_bwd_whole_rows<T, DZ2, ZK>(b, dz, dz2, x, z, zmask, rb, TY, C, lane_elem);
 #pragma unroll
-      for (int u = 0; u < kBnRows; ++u) {
-        if (r + u * TY < r1) {
-          float xf[V], g[V];
-          Elem<T>::unpack(b.x[u], xf);
-          masked_grad<T, DZ2, ZK>(b, u, xf, scale, bias, mode, g);
+        for (int u = 0; u < kBnRows; ++u) add(b, u);
+      } else {
+        load_bwd_rows<false, T, DZ2, ZK>(b, dz, dz2, x, z, zmask, rb + trow, r1, TY, C, col);
 #pragma unroll
-          for (int j = 0; j < V; ++j) {
-            acc[j] += g[j];
-            acc[V + j] = fmaf(g[j], fmaf(xf[j], rs[j], nmr[j]), acc[V + j]);
-          }
-        }
+        for (int u = 0; u < kBnRows; ++u)
+          if (rb + trow + u * TY < r1) add(b, u);
       }
     }
   }

@@ -135,6 +135,36 @@ def test_bn_sums_forms(rn, mode_name, mean, std, shape):
         assert_close(got, want, TOL[mode_name], name)
 
 
+# Rows on both sides of what a workgroup of the sums passes takes in whole batches (256 rows at 64 channels, 64 at 520), several such batches
+# per workgroup, a ragged last slice of channels; the ReLU decision from z, from recorded bits and from x, with a second gradient.
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,C", [(33024, 64), (33025, 64), (33279, 64), (8128, 520), (8129, 520), (8191, 520), (140000, 264), (2200000, 8)])
+def test_bn_sums_of_whole_and_ragged_row_blocks(rn, mode_name, rows, C):
+    """Batch statistics as in test_bn_sums_forms.  Backward sums against 64 bits: at most 32 float additions lie between an addend and its
+    sum, 32 * 2^-24 of the addends' magnitudes; the normalised value adds three roundings of itself and of mean * rstd."""
+    bf = mode_name == "bf16"
+    gen = torch.Generator().manual_seed(rows + C)
+    x, dz, dz2 = (torch.randn(1, 1, rows, C, generator=gen).to(torch.bfloat16 if bf else torch.float32) for _ in range(3))
+    gamma, beta = 1 + 0.3 * torch.randn(C, generator=gen), 0.2 * torch.randn(C, generator=gen)
+    xd, gd, bd, dzd, dz2d = x.cuda(), gamma.cuda(), beta.cuda(), dz.cuda(), dz2.cuda()
+    bits = rn.relu_mask_like(xd)
+    z, mean, rstd = rn.bn_relu_fwd(xd, gd, bd, None, 1e-5, 1, relu_mask=bits)
+    x64 = x.double().reshape(rows, C)
+    mean_o, rstd_o = x64.mean(0), 1.0 / (x64.var(0, unbiased=False) + 1e-5).sqrt()
+    assert ((mean.cpu().double() - mean_o).abs() <= 2.0 ** -24 * mean_o.abs() + 2.0 ** -22 / rstd_o).all()
+    assert (rstd.cpu().double() / rstd_o - 1).abs().max() <= 2.0 ** -22
+    on = z.cpu().reshape(rows, C) > 0
+    m64, r64 = mean.cpu().double(), rstd.cpu().double()
+    xhat = (x64 - m64) * r64
+    for second in (None, dz2d):
+        g = (dz.float() + (dz2.float() if second is not None else 0)).double().reshape(rows, C) * on
+        want_b, want_g = g.sum(0), (g * xhat).sum(0)
+        bound_b, bound_g = 2.0 ** -19 * g.abs().sum(0), 2.0 ** -18 * (g.abs() * (xhat.abs() + (m64 * r64).abs() + 1)).sum(0)
+        for zt, mask in ((z, None), (None, bits), (None, None)):
+            dx, _, dg, db = rn.bn_relu_bwd(dzd, xd, zt, gd, mean, rstd, 1, beta=bd, relu_mask=mask, dz2=second)
+            assert ((db.cpu().double() - want_b).abs() <= bound_b).all() and ((dg.cpu().double() - want_g).abs() <= bound_g).all()
+
+
 def test_bn_bitwise_reproducible(rn):
     x = dev(synth.activation_nhwc(SEED, "x", 8, 64, 56, 56), True)
     g = dev(np.ones(64, np.float32)); b = dev(np.zeros(64, np.float32))
