@@ -1250,17 +1250,30 @@ struct TileShape {
 // workgroups per compute unit wins -- larger tiles load fewer operand bytes per flop (the main loop's bound) but with a smaller
 // grid the latencies of a workgroup's load -> LDS -> MFMA chain are exposed; a reduction of one chunk has nothing to reuse and
 // takes the smallest tile (64 -> 64 at 56x56, batch 256, 30 us against 31 and 45 for 128x64 and 128x128, batch 40 5.2 against 5.6 and
-// 8.7), but with more than 64 columns and kCover tiles of 128x128 or more that one, which reads A half as often (and, with one chunk,
-// fits a compute unit four times): 23 shapes forward / 22 data gradients at batch 256 1790 / 1855 -> 1764 / 1816 us, 100 861 / 877 -> 850 / 869, 40
-// 394 / 390 -> 390 / 387, 18 259 / 262 -> 257 / 261, the step at batch 256 19.17 -> 18.98 ms.
-static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool strided_dgrad, int live = 4) {
+// 8.7), except in bf16 with more than 64 columns and kCover tiles of 128x128 or more: that one reads A half as often.  By what the
+// output stage does, 64 channels at 56x56, operands from memory, us, 64x64 -> 128x128 (profiles/conv_one_chunk_tile_sweep.txt):
+//  - forward, with its sums (120 registers and 35 KB: four workgroups per compute unit): 64 -> 256 at batch 18 / 40 / 256 13.4 -> 9.9 / 24.9 ->
+//    19.3 / 147 -> 99.  Every size, also from warm caches;
+//  - data gradient without sums (150 registers: three): 11.8 -> 9.7 / 22.6 -> 17.4 / 137 -> 95 (warm 7.3 -> 8.0 / 13.3 -> 13.8 / 136 -> 94);
+//  - data gradient with sums (three; two with a second branch), evaluation (160 registers and 69 KB: two): only where the output is larger
+//    than half the last-level cache.  Data gradient with sums at batch 40 / 100 / 256 34.7 -> 35.2 / 79.9 -> 73.9 / 197 -> 176; with a second branch, whose tile
+//    lies in LDS in float, 128x128 always loses (40.5 -> 45.5 / 92.5 -> 101 / 225 -> 248), there the 128x64 tile of the same rows of sums (90 /
+//    217); evaluation with the residual at batch 16 / 40 / 64 / 100 / 256 10.2 -> 11.8 / 24.0 -> 27.0 / 38 -> 45 / 70 -> 64 / 168 -> 153.
+// In float the products take longer than the loads and the tile (68 KB in LDS) leaves two workgroups: 32 -> 256 at batch 64 54 -> 62, from warm
+// caches 38 -> 57.
+enum class TileUse { kForward, kAffine, kGrad, kGradSums, kGradSumsAdd };  // what the output stage does (MODE 0, MODE 2, MODE 1)
+constexpr int64_t kOneChunkBytes = 128 << 20;
+static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool strided_dgrad, int live, TileUse use, int dtype) {
   const int64_t classes = strided_dgrad ? live : 1;
   auto groups = [&](int bm, int bn) { return ceil_div(M, bm) * ceil_div(Ncols, bn) * classes; };
   constexpr int64_t kCover = 384;  // workgroups: one and a half per compute unit (two four-wave workgroups fit each)
-  if (Ncols > 64) {
-    // (not the eight-wave 256x128 tile, also in the largest data gradients, which had it from 1536 tiles on: 22 shapes at batch 256
-    // 3668 -> 3504 us without it, 128 1812 -> 1775; in the step at batch 256 19.49 -> 19.31 ms)
-    if (groups(128, 128) >= kCover) return TileShape{128, 128, 2, 2};
+  // (not the eight-wave 256x128 tile, also in the largest data gradients, which had it from 1536 tiles on: 22 shapes at batch 256
+  // 3668 -> 3504 us without it, 128 1812 -> 1775; in the step at batch 256 19.49 -> 19.31 ms)
+  if (Ncols > 64 && groups(128, 128) >= kCover) {
+    const int64_t out_bytes = M * (strided_dgrad ? 4 : 1) * Ncols * 2;  // (asked in bf16)
+    const bool large = use == TileUse::kForward || use == TileUse::kGrad || out_bytes >= kOneChunkBytes;
+    if (chunks > 1) return TileShape{128, 128, 2, 2};
+    if (dtype == RN50_BF16 && large) return use == TileUse::kGradSumsAdd ? TileShape{128, 64, 2, 2} : TileShape{128, 128, 2, 2};
   }
   if (chunks >= 8 && groups(128, 64) >= kCover) return TileShape{128, 64, 2, 2};
   return TileShape{64, 64, 2, 2};
@@ -1297,7 +1310,8 @@ static bool igemm_halo_shape(const IgemmArgs& a) {
 }
 // The tile of a launch.  rows: output pixels (of one parity class for a stride-2 data gradient, `live` of whose four classes
 // have any taps); taps x cpt 128-byte chunks of reduction; lin_fwd_channels: input channels of a 1x1 stride-1 forward
-// layer (else 0), whose coefficient table bounds the K-split kernels.
+// layer (else 0), whose coefficient table bounds the K-split kernels.  (The rows of sums of a data gradient are the same with a second
+// branch and without: their callers do not know which.)
 // Where 64x64 tiles would give at most one workgroup per compute unit and there are chunks for four waves, the waves split K
 // (KS; 3x3 / stride 1 layers by filter rows); at half of that or less the tile is halved again (in float, whose MFMAs take sixteen times as long per chunk, in
 // both directions), so that twice (four times) as many compute units work.  Measured on the whole float gradient pass (batch 4:
@@ -1307,7 +1321,7 @@ static bool igemm_halo_shape(const IgemmArgs& a) {
 // 4.12 / 4.02 / 4.02 / 4.40 ms, bf16 at batch 40 4.250 / 4.253 / 4.240 / 4.242 / 4.499 (profiles/step_time_against_dispatch_constants.txt;
 // layer by layer: profiles/conv_tile_sweep_*.txt).
 static TileShape pick_tile(int64_t rows, int Ncols, int chunks, bool strided_dgrad, int live, int halo_width, int lin_fwd_channels,
-                           int dtype) {
+                           TileUse use, int dtype) {
 #ifdef RN50_TUNING  // tuning builds only: RN50_IGEMM_TILE=bm,bn,wm,wn forces a compiled tile shape
   if (const char* e = getenv("RN50_IGEMM_TILE")) {
     TileShape f{0, 0, 0, 0};
@@ -1324,15 +1338,17 @@ static TileShape pick_tile(int64_t rows, int Ncols, int chunks, bool strided_dgr
     if (groups64 > 128) return TileShape{64, 64, 1, 1};
     return dtype == RN50_F32 ? TileShape{32, 32, 1, 1} : TileShape{32, 64, 1, 1};
   }
-  return halo_width > 0 ? igemm_halo_tile(rows, Ncols, chunks / 9, halo_width) : igemm_tile(rows, Ncols, chunks, strided_dgrad, live);
+  return halo_width > 0 ? igemm_halo_tile(rows, Ncols, chunks / 9, halo_width) : igemm_tile(rows, Ncols, chunks, strided_dgrad, live, use, dtype);
 }
 template <typename T>
 static void launch_igemm(const IgemmArgs& a, const char* tag, hipStream_t s) {
   const bool classes = a.mode == 1 && a.stride == 2;
   const int64_t rows = classes ? static_cast<int64_t>(a.M / (a.P * a.Q)) * ((a.P + 1) / 2) * ((a.Q + 1) / 2) : a.M;
+  const TileUse use = a.mode == 0 ? TileUse::kForward : a.mode == 2 ? TileUse::kAffine : !a.partial ? TileUse::kGrad
+                      : a.addend ? TileUse::kGradSumsAdd : TileUse::kGradSums;
   const bool lin_fwd = a.mode != 1 && a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0 && !a.pair;
   const TileShape t = pick_tile(rows, a.Ncols, a.R * a.S * a.cpt, classes, a.R * a.S > 1 ? 4 : 1,
-                                igemm_halo_shape(a) ? a.W : 0, lin_fwd ? a.Cg : 0, sizeof(T) == 2 ? RN50_BF16 : RN50_F32);
+                                igemm_halo_shape(a) ? a.W : 0, lin_fwd ? a.Cg : 0, use, sizeof(T) == 2 ? RN50_BF16 : RN50_F32);
 #define X(BM, BN, WM, WN) if (t.bm == BM && t.bn == BN && t.wm == WM && t.wn == WN) launch_igemm_cfg<T, BM, BN, WM, WN>(a, tag, s);
   RN50_IGEMM_SHAPES(X)
   if constexpr (sizeof(T) == 4) { RN50_IGEMM_SHAPE_F32(X) } else { RN50_IGEMM_SHAPE_BF16(X) }
@@ -1394,7 +1410,7 @@ static int chunks_per_tap(int channels, int dtype) { return static_cast<int>(cei
 static PartialRows class_tile_rows(const rn50_conv_desc* d) {
   const int64_t rows = static_cast<int64_t>(d->N) * ((d->H + 1) / 2) * ((d->W + 1) / 2);
   const int bm = pick_tile(rows, d->Cin, d->R * d->S * chunks_per_tap(d->Cout, d->dtype), true, d->R * d->S > 1 ? 4 : 1,
-                           0, 0, d->dtype).bm;
+                           0, 0, TileUse::kGradSums, d->dtype).bm;
   return PartialRows{bm, static_cast<int>(4 * ceil_div(rows, bm))};
 }
 PartialRows fwd_partial_rows(const rn50_conv_desc* d) {
@@ -1403,7 +1419,8 @@ PartialRows fwd_partial_rows(const rn50_conv_desc* d) {
   // the chunk count as the launch computes it (the bf16 stem runs as 4 taps of one chunk, the float stem as 7)
   const int chunks = is_stem(d) ? (d->dtype == RN50_BF16 ? 4 : 7) : d->R * d->S * chunks_per_tap(d->Cin, d->dtype);
   const bool lin = d->R == 1 && d->S == 1 && d->stride == 1 && d->pad == 0;
-  const int bm = pick_tile(M, d->Cout, chunks, false, 4, halo_filter(d->R, d->S, d->stride, d->pad) ? d->W : 0, lin ? d->Cin : 0, d->dtype).bm;
+  const int bm = pick_tile(M, d->Cout, chunks, false, 4, halo_filter(d->R, d->S, d->stride, d->pad) ? d->W : 0, lin ? d->Cin : 0,
+                           TileUse::kForward, d->dtype).bm;
   return PartialRows{bm, static_cast<int>(ceil_div(M, bm))};
 }
 int64_t dgrad_partial_rows_bound(const rn50_conv_desc* d) {
@@ -1415,7 +1432,7 @@ PartialRows dgrad_partial_rows(const rn50_conv_desc* d) {
   if (d->stride == 2) return class_tile_rows(d);
   const int64_t M = static_cast<int64_t>(d->N) * d->H * d->W;
   const int bm = pick_tile(M, d->Cin, d->R * d->S * chunks_per_tap(d->Cout, d->dtype), false, 4,
-                           halo_filter(d->R, d->S, d->stride, d->pad) ? d->W : 0, 0, d->dtype).bm;
+                           halo_filter(d->R, d->S, d->stride, d->pad) ? d->W : 0, 0, TileUse::kGradSums, d->dtype).bm;
   return PartialRows{bm, static_cast<int>(ceil_div(M, bm))};
 }
 

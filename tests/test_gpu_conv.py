@@ -17,6 +17,30 @@ def rn():
     return rn
 
 
+def check_sums(rn, y, handle, grad_of=None):
+    """The batch-norm sums that a convolution leaves beside its output, against 64 bits of the stored values.  A channel's sums are
+    float sums of at most 256 values per tile (at most 48 additions behind each other), added up in double: each within
+    48 * 2^-24 < 1e-5 of the sum of its terms' sizes.  Forward: mean and variance (about a value of the channel itself, whose
+    distance from the mean adds to the terms).  Gradients (grad_of: the BN layer's input, scale 1, shift 0, mean 0, 1/std 1):
+    dbeta and dgamma under the layer's ReLU."""
+    C = y.shape[-1]
+    one, zero = torch.ones(C, device="cuda"), torch.zeros(C, device="cuda")
+    y64 = y.double().reshape(-1, C)
+    if grad_of is None:
+        _, mean, rstd = rn.bn_relu_fwd_from_sums(y, handle, one, zero, None, 1e-5, 1)
+        m64, var = y64.mean(0), y64.var(0, unbiased=False)
+        spread = 2 * (var.sqrt() + (y64 - m64).abs().amax(0))
+        assert bool(((mean.double() - m64).abs() <= 1e-5 * spread + 2.0 ** -23 * m64.abs()).all()), "mean"
+        off = (rstd.double() ** -2 - 1e-5 - var).abs()
+        assert bool((off <= 1e-5 * spread ** 2 + 2.0 ** -21 * (var + 1e-5)).all()), "variance"
+        return
+    x64 = grad_of.double().reshape(-1, C)
+    _, _, dgamma, dbeta = rn.bn_relu_bwd_from_sums(y, grad_of, handle, one, zero, zero, one)
+    g = torch.where(x64 > 0, y64, torch.zeros_like(y64))
+    assert bool(((dbeta.double() - g.sum(0)).abs() <= 1e-5 * g.abs().sum(0) + 1e-30).all()), "dbeta"
+    assert bool(((dgamma.double() - (g * x64).sum(0)).abs() <= 1e-5 * (g * x64).abs().sum(0) + 1e-30).all()), "dgamma"
+
+
 def run_case(rn, mode_name, N, H, W, C, K, R, stride, pad, do_dgrad=True, tag=""):
     bf = mode_name == "bf16"
     tol = TOL[mode_name]
@@ -302,12 +326,16 @@ def test_images_too_wide_for_the_halo_loop(rn, mode_name, N, H, W, C, K):
     want = torch.nn.functional.conv2d(nchw(x), nchw(w), padding=1).permute(0, 2, 3, 1).contiguous()
     y = rn.conv_fwd(x.cuda(), w.cuda(), 1, 1)
     assert_close(y, want.numpy(), TOL[mode_name], "y")
-    assert torch.equal(y, rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), 1, 1)[0])
+    y2, sums = rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), 1, 1)
+    assert torch.equal(y, y2)
+    check_sums(rn, y, sums)
     want = torch.nn.grad.conv2d_input((N, K, H, W), nchw(wt), nchw(dy), padding=1).permute(0, 2, 3, 1).contiguous()
     dx = rn.conv_dgrad(dy.cuda(), wt.cuda(), y.shape, 1, 1)
     assert_close(dx, want.numpy(), TOL[mode_name], "dx")
     one, zero = torch.ones(K, device="cuda"), torch.zeros(K, device="cuda")
-    assert torch.equal(dx, rn.conv_dgrad_bn_sums(dy.cuda(), wt.cuda(), y.shape, 1, 1, y, one, zero, zero, one)[0])
+    dx2, sums = rn.conv_dgrad_bn_sums(dy.cuda(), wt.cuda(), y.shape, 1, 1, y, one, zero, zero, one)
+    assert torch.equal(dx, dx2)
+    check_sums(rn, dx, sums, grad_of=y)
 
 
 # 3x3 / stride 1 layers by the filter row: tiles of 32 rows (at most 128 tiles of 64x64), of 64 rows with the reduction split over the
@@ -334,13 +362,17 @@ def test_3x3_by_filter_rows(rn, mode_name, N, H, W, C, K):
     y = torch.full(want.shape, float("nan"), device="cuda", dtype=dt)
     rn.conv_fwd(x.cuda(), w.cuda(), 1, 1, y=y)
     assert_close(y, want.numpy(), TOL[mode_name], "y")
-    assert torch.equal(y, rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), 1, 1)[0])
+    y2, sums = rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), 1, 1)
+    assert torch.equal(y, y2)
+    check_sums(rn, y, sums)
     want = torch.nn.grad.conv2d_input((N, K, H, W), nchw(wt), nchw(dy), padding=1).permute(0, 2, 3, 1).contiguous()
     dx = torch.full(want.shape, float("nan"), device="cuda", dtype=dt)
     rn.conv_dgrad(dy.cuda(), wt.cuda(), y.shape, 1, 1, dx=dx)
     assert_close(dx, want.numpy(), TOL[mode_name], "dx")
     one, zero = torch.ones(K, device="cuda"), torch.zeros(K, device="cuda")
-    assert torch.equal(dx, rn.conv_dgrad_bn_sums(dy.cuda(), wt.cuda(), y.shape, 1, 1, y, one, zero, zero, one)[0])
+    dx2, sums = rn.conv_dgrad_bn_sums(dy.cuda(), wt.cuda(), y.shape, 1, 1, y, one, zero, zero, one)
+    assert torch.equal(dx, dx2)
+    check_sums(rn, dx, sums, grad_of=y)
 
 
 # Output pixel grids whose tensor is one column below, exactly and one column above the 1 MB from which convolutions write their
@@ -465,14 +497,18 @@ def test_forward_with_rings_of_different_depth(rn, mode_name, N, H, W, C, K, R, 
     y = torch.full(want.shape, float("nan"), device="cuda", dtype=dt)
     rn.conv_fwd(x.cuda(), w.cuda(), stride, pad, y=y)
     assert_close(y, want.numpy(), TOL[mode_name], "y")
-    assert torch.equal(y, rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), stride, pad)[0])
+    y2, sums = rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), stride, pad)
+    assert torch.equal(y, y2)
+    check_sums(rn, y, sums)
 
 
 @pytest.mark.parametrize("mode_name", ["f32", "bf16"])
-@pytest.mark.parametrize("N,H,W,C,K", [(21, 56, 56, 64, 200), (1, 257, 255, 24, 136), (16, 64, 64, 32, 264), (6, 64, 64, 16, 256)])
+@pytest.mark.parametrize("N,H,W,C,K", [(21, 56, 56, 64, 200), (1, 257, 255, 24, 136), (16, 64, 64, 32, 264), (6, 64, 64, 16, 256), (1, 505, 504, 64, 264)])
 def test_one_chunk_on_large_tiles(rn, mode_name, N, H, W, C, K):
     """1x1 layers whose reduction is one chunk and whose grid has at least 384 tiles of 128x128 (the second: 512 rows of tiles, the last of 127 rows):
-    forward with and without sums, the data gradient likewise, with a second branch and at stride 2, into buffers of NaNs."""
+    forward with and without sums, the data gradient likewise, with a second branch and at stride 2, into buffers of NaNs.  In bf16 a data
+    gradient's sums come from 64x64 tiles, and from 128 MB of output on (the last one, just above; the one with 264 columns at stride 2, below)
+    from 128x128, with a second branch from 128x64: the same rows of sums."""
     dt = torch.bfloat16 if mode_name == "bf16" else torch.float32
     gen = torch.Generator().manual_seed(C + K)
     rand = lambda *shape, scale=1.0: (torch.randn(*shape, generator=gen) * scale).to(dt)
@@ -481,13 +517,22 @@ def test_one_chunk_on_large_tiles(rn, mode_name, N, H, W, C, K):
     y = rn.conv_fwd(x.cuda(), w.cuda(), 1, 0, y=nan(N, H, W, K))
     want = x.float().reshape(-1, C) @ w.float().reshape(K, C).t()
     assert_close(y.view(-1, K), want.numpy(), TOL[mode_name], "y")
-    assert torch.equal(y, rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), 1, 0)[0])
+    y2, sums = rn.conv_fwd_bn_sums(x.cuda(), w.cuda(), 1, 0)
+    assert torch.equal(y, y2)
+    check_sums(rn, y, sums)
     dx = rn.conv_dgrad(x.cuda(), wt.cuda(), (N, H, W, K), 1, 0, dx=nan(N, H, W, K))
     want = x.float().reshape(-1, C) @ wt.float().reshape(C, K)
     assert_close(dx.view(-1, K), want.numpy(), TOL[mode_name], "dx")
     one, zero = torch.ones(K, device="cuda"), torch.zeros(K, device="cuda")
-    assert torch.equal(dx, rn.conv_dgrad_bn_sums(x.cuda(), wt.cuda(), (N, H, W, K), 1, 0, y, one, zero, zero, one)[0])
-    both = rn.conv_dgrad_bn_sums(x.cuda(), wt.cuda(), (N, H, W, K), 1, 0, y, one, zero, zero, one, addend=add.cuda())[0]
+    dx2, sums = rn.conv_dgrad_bn_sums(x.cuda(), wt.cuda(), (N, H, W, K), 1, 0, y, one, zero, zero, one, dx=nan(N, H, W, K))
+    assert torch.equal(dx, dx2)
+    check_sums(rn, dx, sums, grad_of=y)
+    both, sums = rn.conv_dgrad_bn_sums(x.cuda(), wt.cuda(), (N, H, W, K), 1, 0, y, one, zero, zero, one, addend=add.cuda(), dx=nan(N, H, W, K))
     assert_close(both.view(-1, K), (want + add.float().reshape(-1, K)).numpy(), TOL[mode_name], "dx + addend")
+    check_sums(rn, both, sums, grad_of=y)
     dx2 = rn.conv_dgrad(x.cuda(), wt.cuda(), (N, 2 * H, 2 * W, K), 2, 0, dx=nan(N, 2 * H, 2 * W, K))
     assert torch.equal(dx2[:, ::2, ::2], dx) and not dx2[:, 1::2].any() and not dx2[:, :, 1::2].any()
+    below = torch.randn(dx2.shape, device="cuda").to(dt)
+    dx3, sums = rn.conv_dgrad_bn_sums(x.cuda(), wt.cuda(), dx2.shape, 2, 0, below, one, zero, zero, one, dx=nan(*dx2.shape))
+    assert torch.equal(dx2, dx3)
+    check_sums(rn, dx3, sums, grad_of=below)

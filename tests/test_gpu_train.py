@@ -337,16 +337,19 @@ def test_resnet_eval_vs_oracle_after_training_steps(rn, mode_name, cfg):
 
 
 @pytest.mark.parametrize("mode_name", ["f32", "bf16"])
-@pytest.mark.parametrize("N", [2, 40, 200])
-def test_resnet_eval_is_the_chain_of_its_operations(rn, mode_name, N):
+@pytest.mark.parametrize("N,stem,widths,blocks", [(2, 64, (64, 128, 256, 512), (3, 4, 6, 3)), (40, 64, (64, 128, 256, 512), (3, 4, 6, 3)),
+                                                  (200, 64, (64, 128, 256, 512), (3, 4, 6, 3)), (40, 32, (32, 64, 128, 256), (1, 1, 1, 1))])
+def test_resnet_eval_is_the_chain_of_its_operations(rn, mode_name, N, stem, widths, blocks):
     """The evaluation pass applies every batch norm (with the residual) in its convolution's output stage.  ResNet-50 at batches
-    whose layers run on every forward tile: the K splits, 64x64, 128x64, 128x128, the one-run 3x3 loop's 64x64 to 256x128.
+    whose layers run on every forward tile: the K splits, 64x64, 128x64, 128x128 (a reduction of one chunk of 64 channels: from an output of
+    128 MB on, batch 200), the one-run 3x3 loop by filter rows on 32x64 (float 32x32) and 64x64 tiles, tap by tap on 128x64 and 256x128; a
+    narrow network whose first stage is one chunk of channels in float as well: the 256x64 tile.
     In float the products are those of conv_fwd and the arithmetic that of bn_relu_infer: the same bits.  In bf16 the chain
     multiplies the rounded operands in float and rounds once behind the batch norm, as the output stage does, so only the
     order of the sums differs (and what a value on the other side of a rounding makes of it downstream)."""
     bf = mode_name == "bf16"
     dt = torch.bfloat16 if bf else torch.float32
-    plan = rn.ResnetPlan(N, rn.BF16 if bf else rn.F32)
+    plan = rn.ResnetPlan(N, rn.BF16 if bf else rn.F32, 224, 1000, widths, blocks, stem)
     gen = torch.Generator(device="cuda").manual_seed(SEED)
     M = torch.empty(plan.arena_elems, device="cuda")
     rn.resnet_init_params(plan, SEED, M)
@@ -369,8 +372,8 @@ def test_resnet_eval_is_the_chain_of_its_operations(rn, mode_name, N):
                                 None if res is None else res.float(), 1e-5, mode).to(dt)
 
     x = rn.maxpool_fwd(cbn(img, 2, 3, 1))
-    for stage, blocks in enumerate((3, 4, 6, 3)):
-        for b in range(blocks):
+    for stage, count in enumerate(blocks):
+        for b in range(count):
             stride = 2 if b == 0 and stage > 0 else 1
             z = cbn(cbn(x, 1, 0, 1), stride, 1, 1)
             if b == 0:                                       # (parameter order: conv3, then the projection)
