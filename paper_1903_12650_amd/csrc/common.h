@@ -73,6 +73,8 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) {
 // 0.3 us each, in front of the first operand load of every workgroup, all of which start at the same time where a layer has few.
 // Start of a convolution's workgroup to its first load, batch 40: 1x1 layers 0.5-1.0 -> 0.3 us, 3x3 1.0-1.6 -> 0.5, 3x3 data gradients
 // 1.8-2.5 -> 0.9-1.1; 22 data gradients call by call 400 -> 387 us, the step at batch 4 1.94 -> 1.91 ms, 40 4.31 -> 4.28.
+// Not in the weight gradients, where it makes no difference: 23 shapes at batch 40 / 256 550 / 1974 us without, 550 / 1971 with, float at batch 8
+// 481 / 480, the step at batch 40 / 256 4.320 / 19.21 ms without, 4.324 / 19.21 with.
 template <int BYTES>
 __device__ __forceinline__ void request_kernel_args() {
   static_assert(BYTES <= 512, "eight lines");

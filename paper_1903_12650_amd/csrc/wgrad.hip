@@ -277,7 +277,7 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
     }
 }
 
-// Weight gradient of a 3x3 / stride 1 / padding 1 layer of at most 64 channels each way, bf16, all nine taps in one workgroup.
+// Weight gradient of a 3x3 / stride 1 / padding 1 layer of 64 -> at most 64 channels, bf16, all nine taps in one workgroup.
 // The reduction index is a PADDED pixel position: every image row gets one more column and every image one more
 // row, whose dy and x are zero (never stored: the loads of those positions carry an out-of-range offset and
 // write zeros).  In that index space tap (r, s) of position k reads x at k + (r-1)(W+1) + (s-1), a constant shift,
@@ -505,12 +505,11 @@ struct WgradPlan {
 // The estimate: workgroups fill the compute units in rounds of `slots` each; a chunk of n workgroups on one compute unit
 // takes the longer of one's latency (lat) and n times the tile's share of the LDS and load rates (thr), both dearer where
 // pixels are gathered; `ends` is prologue and result stores; splits add the reduction launch and the partials' traffic.
-// Constants fitted to ResNet-50's 23 shapes x 12 plans at batch 12 to 256 (bf16) and 2 to 24 (float): the plan it
-// takes is within 4 % of the best of the twelve, summed over the shapes, also since partial sums and results are written through
-// (profiles/wgrad_plan_sweep.txt: 503 against 495 us at batch 40, 1838 against 1781 at batch 256, float at batch 8 567 against
-// 552).  Against the fixed rule before it (128-wide tiles, 192 or 384
-// workgroups): 23 shapes at batch 40 640 -> 565 us call by call, at batch 256 2343 -> 2000, float at batch 8
-// 830 -> 531.
+// Constants fitted to ResNet-50's 23 shapes x 12 plans at batch 12 to 256 (bf16) and 2 to 24 (float), when a chunk's pixels were still
+// divided out; since they are advanced from chunk to chunk the plan it takes is within 1 to 4 % of the best of the twelve, summed over the
+// shapes, 6 % at batch 90 (profiles/wgrad_plan_sweep.txt: 478 against 467 us at batch 40, 804 against 757 at 90, 1755 against 1713 at 256, float
+// at batch 8 510 against 502).  Against the fixed rule before it (128-wide tiles, 192 or 384 workgroups), when it was fitted: 23 shapes at
+// batch 40 640 -> 565 us call by call, at batch 256 2343 -> 2000, float at batch 8 830 -> 531.
 struct WgradCost {
   float thr[3], lat[3], ends[3];  // us; tile area 64x64, 128x64, 128x128
   float thr_gather, lat_gather, reduce, partial_us_per_mb;
@@ -596,10 +595,14 @@ static WgradArgs wgrad_args(const rn50_conv_desc* d, const void* x, const void* 
   a.split_stride = static_cast<int64_t>(a.Cout) * a.Ktot;
   return a;
 }
-// The nine-tap weight gradient (wgrad3x3_kernel): bf16, 3x3, stride 1, padding 1, at most 64 channels each way (one 64x64 tile;
-// wider layers do better on wgrad_kernel's 128-wide tiles; 56x56, batch 40: 33.5 us, per tap 31.1, batch 256:
-// 106 against 130), and an image width whose run of 2W + 68 rows fits six load passes.
-// Plan: the padded pixel range split to give about 384 workgroups, each at least 8 chunks long.
+// The nine-tap weight gradient (wgrad3x3_kernel): bf16, 3x3, stride 1, padding 1, 64 input and at most 64 output channels (one 64x64 tile;
+// wider layers do better on wgrad_kernel's 128-wide tiles), an image width whose run of 2W + 68 rows fits six load passes, and
+// kNineTapPositions padded positions or more: 384 workgroups each write a partial of all nine taps, 20 us however few the pixels, and the
+// nine products are as long with fewer input channels.  64 -> 64, us, per tap / nine taps: 56x56 at batch 4 12 / 22, 40 28.7 / 30.1, 64 37.2 /
+// 39.9, 90 45.8 / 46.2, 128 54.4 / 52.8, 180 72 / 65, 256 97 / 83; 28x28 at batch 320 38.5 / 41.0, 640 64.8 / 59.4; 64 -> 16 at 56x56, batch 40 24.8 / 25.8,
+// 64 32.5 / 30.5; 56 -> 64 at batch 256 82 / 81, 32 -> 64 56 / 72.
+// Plan: the padded pixel range split to give about 384 workgroups.
+constexpr int64_t kNineTapPositions = 300000;
 struct Wgrad3x3Plan {
   int nbx;  // load passes of the x run: 3, 4 or 6; 0: the layer does not run this kernel
   int splits, rows_per_split, gpad;
@@ -607,36 +610,27 @@ struct Wgrad3x3Plan {
 static Wgrad3x3Plan plan_wgrad3x3(const rn50_conv_desc* d) {
   Wgrad3x3Plan p{};
   if (d->dtype != RN50_BF16 || d->R != 3 || d->S != 3 || d->stride != 1 || d->pad != 1) return p;
-  if (d->Cin > 64 || d->Cout > 64) return p;
+  if (d->Cin != 64 || d->Cout > 64) return p;
   const int need = static_cast<int>(ceil_div(2 * d->W + 68, 32));
   if (need > 6) return p;
   const int64_t gpad = static_cast<int64_t>(d->N) * (d->H + 1) * (d->W + 1);
-  if (gpad >= (1ll << 31) - 64) return p;
+  if (gpad < kNineTapPositions || gpad >= (1ll << 31) - 64) return p;
   p.nbx = need <= 3 ? 3 : (need == 4 ? 4 : 6);
   p.gpad = static_cast<int>(gpad);
-  constexpr int target = 384, min_chunks = 8;
-  const int64_t cap = gpad / (min_chunks * 64) > 1 ? gpad / (min_chunks * 64) : 1;
-  const int64_t sp = std::min<int64_t>(target, cap);
-  const int64_t rps = ceil_div(ceil_div(gpad, sp), 64) * 64;
+  constexpr int target = 384;
+  const int64_t rps = ceil_div(ceil_div(gpad, target), 64) * 64;
   p.rows_per_split = static_cast<int>(rps);
   p.splits = static_cast<int>(ceil_div(gpad, rps));
   return p;
 }
-template <int NBX, int NSTAGE>
-static void launch_wgrad3x3_ring(const WgradArgs& a, dim3 grid, hipStream_t s) {
+template <int NBX>
+static void launch_wgrad3x3_nbx(const WgradArgs& a, dim3 grid, hipStream_t s) {
+  // three chunk buffers where two workgroups on a compute unit have the LDS for them, else two
+  constexpr int NSTAGE = 2 * 3 * (64 * 128 + NBX * 4096) <= 156 * 1024 ? 3 : 2;
   constexpr int lds = NSTAGE * (64 * 128 + NBX * 4096);
   static std::once_flag once;
   std::call_once(once, [] { allow_big_lds(wgrad3x3_kernel<NBX, NSTAGE>, lds); });
   RN50_LAUNCH("conv_wgrad", (wgrad3x3_kernel<NBX, NSTAGE>), grid, dim3(256), lds, s, a);
-}
-template <int NBX>
-static void launch_wgrad3x3_nbx(const WgradArgs& a, dim3 grid, hipStream_t s) {
-  // three chunk buffers where the workgroups sharing a compute unit have the LDS for them, else two
-  int64_t per_cu = ceil_div(grid.x, 256);
-  if (per_cu > 3) per_cu = 3;
-  const bool three = 3 * (64 * 128 + NBX * 4096) * per_cu <= 156 * 1024;
-  if (three) launch_wgrad3x3_ring<NBX, 3>(a, grid, s);
-  else launch_wgrad3x3_ring<NBX, 2>(a, grid, s);
 }
 static void launch_wgrad3x3(WgradArgs a, const Wgrad3x3Plan& p, int H, hipStream_t s) {
   a.rows_per_split = p.rows_per_split;

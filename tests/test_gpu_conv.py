@@ -89,7 +89,7 @@ SMALL = [  # N,H,W,C,K,R,stride,pad : ragged tiles, tails, every stride/pad/filt
     (1, 1, 1, 8, 8, 3, 1, 1),        # a single pixel: eight of the nine taps are padding
     (2, 2, 2, 16, 8, 3, 1, 1),       # 2x2 images: every pixel is a corner
     (1, 3, 100, 8, 8, 3, 1, 1),      # too wide for the one-run kernels (run of 2W + 2 rows): the general path
-    (2, 3, 62, 8, 16, 3, 1, 1),      # the widest image the nine-tap weight gradient takes
+    (2, 3, 62, 8, 16, 3, 1, 1),      # wide, low images of few channels
 ]
 
 
@@ -459,8 +459,7 @@ WGRAD_STEPS = [(70, 1, 1, 16, 24, 3, 1, 1), (70, 2, 2, 16, 24, 3, 2, 1), (3, 70,
                (2, 5, 32, 40, 72, 3, 1, 1), (2, 5, 33, 40, 72, 3, 1, 1), (2, 3, 63, 72, 8, 3, 1, 1), (2, 3, 64, 72, 8, 3, 1, 1), (2, 3, 65, 72, 8, 3, 1, 1),
                (2, 3, 130, 72, 8, 3, 1, 1), (5, 8, 8, 136, 72, 3, 1, 1), (5, 4, 8, 136, 72, 3, 1, 1), (11, 7, 7, 136, 72, 3, 1, 1), (9, 13, 15, 72, 136, 3, 2, 1),
                (3, 29, 27, 64, 64, 1, 2, 0), (3, 17, 21, 24, 40, 2, 1, 1), (2, 33, 18, 24, 40, 5, 3, 2), (2, 9, 11, 16, 16, 1, 1, 0),
-               # (all nine taps in one workgroup: an image of exactly a chunk of 64 padded positions, of fewer, of one more row; widths on both
-               # sides of every count of passes over the run of x, and the first that no run holds)
+               # (64 channels and fewer: images of less than a chunk and more, widths from one column to one more than a chunk)
                (11, 7, 7, 64, 64, 3, 1, 1), (9, 6, 6, 16, 24, 3, 1, 1), (5, 8, 7, 64, 64, 3, 1, 1), (40, 2, 1, 64, 48, 3, 1, 1), (3, 9, 14, 64, 64, 3, 1, 1),
                (3, 9, 15, 64, 64, 3, 1, 1), (3, 9, 30, 64, 64, 3, 1, 1), (3, 9, 31, 64, 64, 3, 1, 1), (3, 5, 62, 64, 64, 3, 1, 1), (3, 5, 63, 64, 64, 3, 1, 1),
                (2, 3, 64, 64, 64, 3, 1, 1)]
@@ -479,6 +478,31 @@ def test_weight_gradient_steps_over_rows_and_images(rn, mode_name, N, H, W, C, K
     dw = torch.full((K, R, R, C), float("nan"), device="cuda")
     rn.conv_wgrad(x.cuda(), dy.cuda(), (K, R, R, C), stride, pad, dw=dw)
     assert_close(dw, want.numpy(), 1e-5, "dw", elementwise=None)  # (products of the inputs as they are, float sums of at most 3,000)
+
+
+# All nine taps in one workgroup (bf16, 64 channels into at most 64, from 300,000 positions of the images padded by a row and a column on; the
+# third case has fewer): an image of exactly a chunk of 64 padded positions, of fewer, of one more row, of a column; widths on both sides of
+# every count of passes over the run of x (14, 30, 62), and the first that no run holds.
+NINE_TAPS = [(4688, 7, 7, 64), (6123, 6, 6, 24), (4687, 7, 7, 64), (4167, 8, 7, 64), (50000, 2, 1, 48), (2000, 9, 14, 64), (1876, 9, 15, 8), (968, 9, 30, 64),
+             (938, 9, 31, 64), (97, 56, 54, 64), (794, 5, 62, 64), (782, 5, 63, 64)]
+
+
+@pytest.mark.parametrize("N,H,W,K", NINE_TAPS)
+def test_weight_gradient_of_nine_taps_at_once(rn, N, H, W, K):
+    gen = torch.Generator(device="cuda").manual_seed(N + W)
+    x = torch.randn(N, H, W, 64, device="cuda", generator=gen).bfloat16()
+    dy = torch.randn(N, H, W, K, device="cuda", generator=gen).bfloat16()
+    dw = [torch.full((K, 3, 3, 64), float("nan"), device="cuda") for _ in range(2)]
+    for d in dw:
+        rn.conv_wgrad(x, dy, d.shape, 1, 1, dw=d)
+    assert torch.equal(dw[0], dw[1])
+    xp = torch.nn.functional.pad(x.float(), (0, 0, 1, 1, 1, 1))
+    rows = dy.double().reshape(-1, K)
+    for r in range(3):
+        for s in range(3):
+            want = rows.t().contiguous() @ xp[:, r:r + H, s:s + W].reshape(-1, 64).double()
+            # (float sums of products that are exact in float: at most 1,700 per workgroup, 384 of those)
+            assert_close(dw[0][:, r, s], want.cpu().numpy(), 1e-5, f"dw tap {r},{s}", elementwise=None)
 
 
 # Forward on the 128x128 tile (from 384 of them on), whose two rings are of different depth: reductions of two chunks (no third buffer of A),
