@@ -71,7 +71,6 @@ struct IgemmArgs {
   // instructions, and every workgroup starts with several of them).  div_w / div_h: by the width / height of
   // the row tiles' pixel grid -- [1] for the odd parity class of a stride-2 data gradient.
   int mtiles;       // row tiles (grid = mtiles * ntn)
-  int linear;       // 1x1 filter, stride 1, no padding: row m of the output is pixel m of the gathered tensor
   FastDiv div_ntn, div_w[2], div_h[2];
   int mode;         // host side only: selects the MODE template argument
   // Optional batch-norm sums over the rows of each output tile, taken from the rounded values that are
@@ -542,7 +541,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   if constexpr (HALO) {
     constexpr int NSB = 3;                       // weight tiles in the ring
     const int Wd = a.W;
-    const int NA = (BM + 2 * Wd + 2 + RPL - 1) / RPL;  // load passes of one run (the host checked NA <= 8)
+    const int NA = (BM + 2 * Wd + 2 + RPL - 1) / RPL;  // load passes of one run (with another chunk to load: the host checked NA <= 8)
     const uint32_t run_bytes = static_cast<uint32_t>(NA) * (RPL * 128);
     const int cpt = a.cpt;
     const uint32_t b_base = (cpt > 1 ? 2u : 1u) * run_bytes;  // two runs when there is a next chunk to prefetch
@@ -686,7 +685,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
               else if (more) load_row(to, cc + 1, 0, true);
               if (more) {
 #pragma unroll
-                for (int j = 3 * row; j < 3 * row + 3; ++j)  // (the host checked NA <= 8)
+                for (int j = 3 * row; j < 3 * row + 3; ++j)  // (nine passes at most; the host checked NA <= 8)
                   if (j < NA) load_run_pass(j, cc + 1, buf ^ 1);
               }
             }
@@ -729,120 +728,120 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         }
       }
     } else {
-    auto compute_tap = [&](int buf, int bstage, int tap) __attribute__((always_inline)) {
-      Frags f;
-      constexpr int AH = (TM + TN <= 3) ? 4 : 1;
-      const TapAddr at = tap_addr(buf, bstage, tap);
-      const TapMask mk = tap_mask(tap);
+      auto compute_tap = [&](int buf, int bstage, int tap) __attribute__((always_inline)) {
+        Frags f;
+        constexpr int AH = (TM + TN <= 3) ? 4 : 1;
+        const TapAddr at = tap_addr(buf, bstage, tap);
+        const TapMask mk = tap_mask(tap);
 #pragma unroll
-      for (int kk = 0; kk < AH; ++kk) tap_read(f, at, kk);
-      __builtin_amdgcn_sched_barrier(0);
+        for (int kk = 0; kk < AH; ++kk) tap_read(f, at, kk);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        if (kk + AH < 4) {
-          tap_read(f, at, kk + AH);
+        for (int kk = 0; kk < 4; ++kk) {
+          if (kk + AH < 4) {
+            tap_read(f, at, kk + AH);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          masked_mma(f.a[kk], f.b[kk], mk);
           __builtin_amdgcn_sched_barrier(0);
         }
-        masked_mma(f.a[kk], f.b[kk], mk);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    // Prologue: the first run, the weight tiles of steps 0 and 1.  Every step of the loop then issues RB + 1
-    // loads (the weight tile two steps ahead; one pass of the next chunk's run, or a load of nothing), so at its
-    // top "at most RB + 1 outstanding" means: everything up to the step before the previous one has landed.
-    for (int j = 0; j < NA; ++j) load_run_pass(j, 0, 0);
-    load_b_tile(0, 0, 0, true);
-    load_b_tile(1, 0, 1, true);
-    load_nothing();
-    int bstage = 0;
-    for (int cc = 0; cc < cpt; ++cc) {
-      const int buf = cpt > 1 ? (cc & 1) : 0;
+      };
+      // Prologue: the first run, the weight tiles of steps 0 and 1.  Every step of the loop then issues RB + 1
+      // loads (the weight tile two steps ahead; one pass of the next chunk's run, or a load of nothing), so at its
+      // top "at most RB + 1 outstanding" means: everything up to the step before the previous one has landed.
+      for (int j = 0; j < NA; ++j) load_run_pass(j, 0, 0);
+      load_b_tile(0, 0, 0, true);
+      load_b_tile(1, 0, 1, true);
+      load_nothing();
+      int bstage = 0;
+      for (int cc = 0; cc < cpt; ++cc) {
+        const int buf = cpt > 1 ? (cc & 1) : 0;
 #pragma unroll
-      for (int tap = 0; tap < 9; ++tap) {
-        wait_loads_then_barrier<RB + 1>();
-        const int tap2 = (tap + 2) % 9, cc2 = cc + (tap + 2 >= 9 ? 1 : 0);
-        load_b_tile(bstage >= 1 ? bstage - 1 : NSB - 1, cc2, tap2, cc2 < cpt);  // the tile of step - 1: free again
-        if (tap < NA && cc + 1 < cpt) load_run_pass(tap, cc + 1, buf ^ 1);
-        else load_nothing();
-        compute_tap(buf, bstage, tap);
-        bstage = bstage == NSB - 1 ? 0 : bstage + 1;
+        for (int tap = 0; tap < 9; ++tap) {
+          wait_loads_then_barrier<RB + 1>();
+          const int tap2 = (tap + 2) % 9, cc2 = cc + (tap + 2 >= 9 ? 1 : 0);
+          load_b_tile(bstage >= 1 ? bstage - 1 : NSB - 1, cc2, tap2, cc2 < cpt);  // the tile of step - 1: free again
+          if (tap < NA && cc + 1 < cpt) load_run_pass(tap, cc + 1, buf ^ 1);
+          else load_nothing();
+          compute_tap(buf, bstage, tap);
+          bstage = bstage == NSB - 1 ? 0 : bstage + 1;
+        }
       }
-    }
     }
     // (the loads still in flight carry nothing and land in the dump area or in weight tiles nobody reads again;
     // they are waited for before the output stage reuses LDS)
     wait_loads_then_barrier<0>();
   } else {
-  tap_setup();
-  float* const in_tab = reinterpret_cast<float*>(smem + (BNIN ? a.in_lds : 0));  // [2][nchunks * BK]: scale, bias
-  if constexpr (BNIN) {
-    const int kpad = allchunks * BK;
-    for (int c = tid; c < kpad; c += NT) {
-      float sc = 0.f, bi = 0.f;
-      if (c < a.Cg) bn_coeffs(a.in_gamma[c], a.in_beta[c], a.in_mean[c], a.in_rstd[c], &sc, &bi);
-      in_tab[c] = sc;
-      in_tab[kpad + c] = bi;
-    }
-    __syncthreads();
-  }
-  if constexpr (DEEP) {
-    // Buffers of 16 KB: B0 A0 A1 B1 A2 (a reduction of one chunk has the first two, of two the first four).  Chunk k: A was requested two
-    // chunks ago, B one; behind the wait only A of chunk k + 1 may still be in flight.
-    static_assert(!DEEP || BM == BN, "buffers of one size");
-    auto buf_a = [](int i) __attribute__((always_inline)) { return static_cast<uint32_t>(i + 1 + (i >> 1)) * (BM * 128); };
-    auto buf_b = [](int i) __attribute__((always_inline)) { return static_cast<uint32_t>(3 * i) * (BM * 128); };
-    if (nchunks > 0) {
-      load_a(wave_dst + buf_a(0));
-      load_b(wave_dst + buf_b(0), b_cc, sob);
-    }
-    if (nchunks > 1) load_a(wave_dst + buf_a(1));
-    int ia = 0;
-    for (int kc = 0; kc < nchunks; ++kc) {
-      if (kc + 1 < nchunks) wait_loads_then_barrier<RA>(); else wait_loads_then_barrier<0>();
-      compute(smem + buf_a(ia), smem + buf_b(kc & 1), [&]() __attribute__((always_inline)) {
-        if (kc + 1 < nchunks) load_b(wave_dst + buf_b((kc & 1) ^ 1), b_cc, sob);
-        if (kc + 2 < nchunks) load_a(wave_dst + buf_a(ia >= 1 ? ia - 1 : 2));
-      });
-      ia = ia == 2 ? 0 : ia + 1;
-    }
-  } else {
-#pragma unroll
-  for (int c = 0; c < NSTAGE - 1; ++c)
-    if (c < nchunks) load_chunk(c);
-  int stage = 0;
-  for (int kc = 0; kc < nchunks; ++kc) {
-    if constexpr (KS) {  // (nobody else reads this wave's buffers: the next loads go out before the wait)
-      if (kc + NSTAGE - 1 < nchunks) load_chunk(stage >= 1 ? stage - 1 : NSTAGE - 1);
-      ring_wait<NSTAGE + 1, NL, false>(nchunks - 1 - kc);
-    } else {
-      ring_wait<NSTAGE, NL>(nchunks - 1 - kc);
-      if (kc + NSTAGE - 1 < nchunks) load_chunk(stage >= 1 ? stage - 1 : NSTAGE - 1);  // buffer (kc - 1) mod NSTAGE
-    }
+    tap_setup();
+    float* const in_tab = reinterpret_cast<float*>(smem + (BNIN ? a.in_lds : 0));  // [2][nchunks * BK]: scale, bias
     if constexpr (BNIN) {
-      // every thread transforms, in place, the vectors of chunk kc that its own loads brought (its slot of its
-      // rows holds piece `piece`, i.e. channels kc*BK + piece*V ..), then a second barrier
-      float scale[V], bias[V];
       const int kpad = allchunks * BK;
-#pragma unroll
-      for (int par = 0; par < (KS ? 2 : 1); ++par) {
-        const int at = (first_chunk + kc) * BK + piece_of(par) * V;
-        load_floats<V>(in_tab + at, scale);
-        load_floats<V>(in_tab + kpad + at, bias);
-#pragma unroll
-        for (int i = par; i < RA; i += KS ? 2 : 1) {
-          uint4* p = reinterpret_cast<uint4*>(smem + (OWN ? wave * (NSTAGE * STAGE) : 0) + stage * STAGE + (lrow + RPL * i) * 128 + slot * 16);
-          Vec16 v;
-          v.u = *p;
-          *p = bn_relu_vector<T>(v, scale, bias).u;
-        }
+      for (int c = tid; c < kpad; c += NT) {
+        float sc = 0.f, bi = 0.f;
+        if (c < a.Cg) bn_coeffs(a.in_gamma[c], a.in_beta[c], a.in_mean[c], a.in_rstd[c], &sc, &bi);
+        in_tab[c] = sc;
+        in_tab[kpad + c] = bi;
       }
-      if (!KS) lds_writes_then_barrier();  // (KS: the wave's own LDS operations stay in order)
+      __syncthreads();
     }
-    const unsigned char* const tile = smem + (OWN ? wave * (NSTAGE * STAGE) : 0) + stage * STAGE;
-    compute(tile, tile + BM * 128, [] {});
-    stage = stage == NSTAGE - 1 ? 0 : stage + 1;
-  }
-  }
+    if constexpr (DEEP) {
+      // Buffers of 16 KB: B0 A0 A1 B1 A2 (a reduction of one chunk has the first two, of two the first four).  Chunk k: A was requested two
+      // chunks ago, B one; behind the wait only A of chunk k + 1 may still be in flight.
+      static_assert(!DEEP || BM == BN, "buffers of one size");
+      auto buf_a = [](int i) __attribute__((always_inline)) { return static_cast<uint32_t>(i + 1 + (i >> 1)) * (BM * 128); };
+      auto buf_b = [](int i) __attribute__((always_inline)) { return static_cast<uint32_t>(3 * i) * (BM * 128); };
+      if (nchunks > 0) {
+        load_a(wave_dst + buf_a(0));
+        load_b(wave_dst + buf_b(0), b_cc, sob);
+      }
+      if (nchunks > 1) load_a(wave_dst + buf_a(1));
+      int ia = 0;
+      for (int kc = 0; kc < nchunks; ++kc) {
+        if (kc + 1 < nchunks) wait_loads_then_barrier<RA>(); else wait_loads_then_barrier<0>();
+        compute(smem + buf_a(ia), smem + buf_b(kc & 1), [&]() __attribute__((always_inline)) {
+          if (kc + 1 < nchunks) load_b(wave_dst + buf_b((kc & 1) ^ 1), b_cc, sob);
+          if (kc + 2 < nchunks) load_a(wave_dst + buf_a(ia >= 1 ? ia - 1 : 2));
+        });
+        ia = ia == 2 ? 0 : ia + 1;
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < NSTAGE - 1; ++c)
+        if (c < nchunks) load_chunk(c);
+      int stage = 0;
+      for (int kc = 0; kc < nchunks; ++kc) {
+        if constexpr (KS) {  // (nobody else reads this wave's buffers: the next loads go out before the wait)
+          if (kc + NSTAGE - 1 < nchunks) load_chunk(stage >= 1 ? stage - 1 : NSTAGE - 1);
+          ring_wait<NSTAGE + 1, NL, false>(nchunks - 1 - kc);
+        } else {
+          ring_wait<NSTAGE, NL>(nchunks - 1 - kc);
+          if (kc + NSTAGE - 1 < nchunks) load_chunk(stage >= 1 ? stage - 1 : NSTAGE - 1);  // buffer (kc - 1) mod NSTAGE
+        }
+        if constexpr (BNIN) {
+          // every thread transforms, in place, the vectors of chunk kc that its own loads brought (its slot of its
+          // rows holds piece `piece`, i.e. channels kc*BK + piece*V ..), then a second barrier
+          float scale[V], bias[V];
+          const int kpad = allchunks * BK;
+#pragma unroll
+          for (int par = 0; par < (KS ? 2 : 1); ++par) {
+            const int at = (first_chunk + kc) * BK + piece_of(par) * V;
+            load_floats<V>(in_tab + at, scale);
+            load_floats<V>(in_tab + kpad + at, bias);
+#pragma unroll
+            for (int i = par; i < RA; i += KS ? 2 : 1) {
+              uint4* p = reinterpret_cast<uint4*>(smem + (OWN ? wave * (NSTAGE * STAGE) : 0) + stage * STAGE + (lrow + RPL * i) * 128 + slot * 16);
+              Vec16 v;
+              v.u = *p;
+              *p = bn_relu_vector<T>(v, scale, bias).u;
+            }
+          }
+          if (!KS) lds_writes_then_barrier();  // (KS: the wave's own LDS operations stay in order)
+        }
+        const unsigned char* const tile = smem + (OWN ? wave * (NSTAGE * STAGE) : 0) + stage * STAGE;
+        compute(tile, tile + BM * 128, [] {});
+        stage = stage == NSTAGE - 1 ? 0 : stage + 1;
+      }
+    }
   }
   if constexpr (KS) {
     // wave w takes rows g = w (four consecutive output channels) of every 32x32 block from the four partial tiles
@@ -1145,7 +1144,8 @@ static void launch_igemm_mode(const IgemmArgs& a, const char* tag, int64_t grid,
   launch_igemm_through<T, BM, BN, WM, WN, MODE, LIN, BNIN, true>(a, tag, grid, s);
 }
 // The halo kernel (3x3, stride 1, padding 1): LDS bytes of its main loop for an image width, or 0 when the shape
-// does not fit it (a run of more than 8 load passes, more LDS than a compute unit has).
+// does not fit it (a run of more than 8 load passes where there is another chunk whose run is loaded beside this one's taps, more LDS than a
+// compute unit has).
 static bool igemm_halo_shape(const IgemmArgs& a);
 // (the kernel's static arrays come on top; a compute unit has 160 KB, for two workgroups by rows with 2x2 waves)
 constexpr int kHaloLdsMax = 152 * 1024, kHaloRowLdsMax = 78 * 1024, kHaloRowGroups = 512;
@@ -1205,12 +1205,13 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
   a.out_through = writes_through(static_cast<int64_t>(a.M) * a.Ncols * sizeof(T), igemm_always_through<BN>() ? 0 : kConvThroughBytes);
   a.partial_wide = bn_self_finalizes(a.mtiles, false);
   a.div_ntn = make_fastdiv(a.ntn);
-  a.linear = a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0 && !a.pair && a.H == a.P && a.W == a.Q;
+  // 1x1 filter, stride 1, no padding: row m of the output is pixel m of the gathered tensor
+  const bool linear = a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0 && !a.pair && a.H == a.P && a.W == a.Q;
   for (int c = 0; c < 2; ++c) {
     a.div_w[c] = make_fastdiv(classes ? (a.Q - c + 1) >> 1 : a.Q);
     a.div_h[c] = make_fastdiv(classes ? (a.P - c + 1) >> 1 : a.P);
   }
-  if (a.linear) {
+  if (linear) {
     if constexpr (BM <= 128 || kTuning) {  // (the tiles of 256 rows are igemm_halo_tile's alone)
       if (a.mode == 1) launch_igemm_mode<T, BM, BN, WM, WN, 1, true>(a, tag, grid, s);
       else if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, true>(a, tag, grid, s);
