@@ -1247,11 +1247,11 @@ struct TileShape {
 // The tile of a layer shape: M rows (output pixels; of one parity class for a stride-2 data gradient, `live` of
 // whose four classes have any taps), Ncols output channels, `chunks` 128-byte steps of the reduction.  The rule
 // is fitted to per-layer sweeps of all compiled shapes over ResNet-50's 23 convolution shapes at batch 40 and at
-// batch 256 (profiles/conv_tile_sweep_*.txt): the largest tile that still leaves about one and a half
+// batch 256 (profiles/conv_tile_sweep_*.txt: summed over the shapes within 1 % of the best tiles, the data gradients at batch 256 3 %): the largest tile that still leaves about one and a half
 // workgroups per compute unit wins -- larger tiles load fewer operand bytes per flop (the main loop's bound) but with a smaller
 // grid the latencies of a workgroup's load -> LDS -> MFMA chain are exposed; a reduction of one chunk has nothing to reuse and
-// takes the smallest tile (64 -> 64 at 56x56, batch 256, 30 us against 31 and 45 for 128x64 and 128x128, batch 40 5.2 against 5.6 and
-// 8.7), except in bf16 with more than 64 columns and kCover tiles of 128x128 or more: that one reads A half as often.  By what the
+// takes the smallest tile (64 -> 64 at 56x56, batch 256, forward / data gradient 28.3 / 28.4 us against 29.1 / 31.5 with 128x64 and 30.7 / 37.0 with
+// 128x128), except in bf16 with more than 64 columns and kCover tiles of 128x128 or more: that one reads A half as often.  By what the
 // output stage does, 64 channels at 56x56, operands from memory, us, 64x64 -> 128x128 (profiles/conv_one_chunk_tile_sweep.txt):
 //  - forward, with its sums (120 registers and 35 KB: four workgroups per compute unit): 64 -> 256 at batch 18 / 40 / 256 13.4 -> 9.9 / 24.9 ->
 //    19.3 / 147 -> 99.  Every size, also from warm caches;
@@ -1290,7 +1290,9 @@ static TileShape igemm_halo_tile(int64_t M, int Ncols, int cpt, int W) {
   // One chunk of channels into at most 64 columns: four waves of 64x64 one above the other read two thirds of the fragment bytes per product
   // of the 128x64 tile's 64x32 waves, and a run of 256 + 2W + 2 pixels with its weights still leaves a compute unit two workgroups
   // (kHaloTallWidth: 12 load passes).  64 -> 64 at 56x56, us, forward / data gradient: batch 256 89.8 / 102.4 -> 67.3 / 74.2, 90 34.4 / 39.3 ->
-  // 28.0 / 30.5, 40 16.1 / 18.5 -> 12.4 / 15.1, 32 15.4 / 18.2 -> 11.7 / 13.7.
+  // 28.0 / 30.5, 40 16.1 / 18.5 -> 12.4 / 15.1, 32 15.4 / 18.2 -> 11.7 / 13.7.  In float, whose products are the bound, it is the rounds of the grid
+// that decide, two workgroups against three of the 128x64 tile (32 -> 64 forward, batch 32 46.7 -> 40.2, 64 81 -> 81, 128 149 -> 138; 63x63, batch 40 59 -> 62, 64
+// 94 -> 83).
   if (Ncols <= 64 && cpt == 1 && W <= kHaloTallWidth && groups(256, 64) >= 384) return TileShape{256, 64, 4, 1};
   if (Ncols > 64 && groups(256, 128) >= 192) return TileShape{256, 128, 4, 2};
   if (groups(128, 64) >= 384) return TileShape{128, 64, 2, 2};
@@ -1314,13 +1316,12 @@ static bool igemm_halo_shape(const IgemmArgs& a) {
 // layer (else 0), whose coefficient table bounds the K-split kernels.  (The rows of sums of a data gradient are the same with a second
 // branch and without: their callers do not know which.)
 // Where 64x64 tiles would give at most one workgroup per compute unit and there are chunks for four waves, the waves split K
-// (KS; 3x3 / stride 1 layers by filter rows); at half of that or less the tile is halved again (in float, whose MFMAs take sixteen times as long per chunk, in
-// both directions), so that twice (four times) as many compute units work.  Measured on the whole float gradient pass (batch 4:
-// 4055 -> 2919 us, batch 8: 4752 -> 4024, batch 16: 6789 -> 6384) and on single layers (2048 -> 512 channels at 7x7,
-// batch 40: 14.0 -> 9.3 us); with 257 to 512 tiles the two workgroups per
-// compute unit of the shared ring do better.  Limits of 0 / 128 / 256 / 384 / 512 tiles in the whole step: float at batch 8 4.77 /
-// 4.12 / 4.02 / 4.02 / 4.40 ms, bf16 at batch 40 4.250 / 4.253 / 4.240 / 4.242 / 4.499 (profiles/step_time_against_dispatch_constants.txt;
-// layer by layer: profiles/conv_tile_sweep_*.txt).
+// (KS; 3x3 / stride 1 layers by filter rows); at half of that or less the tile is halved again (in float, whose MFMAs take sixteen times as
+// long per chunk, in both directions), so that twice (four times) as many compute units work; with 257 to 512 tiles the two workgroups per
+// compute unit of the shared ring do better.  Limits of 0 / 128 / 256 / 384 / 512 tiles, ms: step at batch 12 2.49 / 2.46 / 2.41 / 2.59 /
+// 2.59, 24 3.37 / 3.36 / 3.32 / 3.48 / 3.50, 40 4.29 / 4.29 / 4.26 / 4.26 / 4.47; float gradients at batch 2 3.64 / 2.20 / 2.17 / 2.17 / 2.24, 8
+// 4.66 / 4.04 / 3.80 / 3.80 / 4.08, 16 6.55 / 6.41 / 6.05 / 6.06 / 6.30; evaluation at batch 16 0.63 / 0.60 / 0.57 / 0.57 / 0.66
+// (profiles/step_time_against_dispatch_constants.txt; layer by layer: profiles/conv_tile_sweep_*.txt).
 static TileShape pick_tile(int64_t rows, int Ncols, int chunks, bool strided_dgrad, int live, int halo_width, int lin_fwd_channels,
                            TileUse use, int dtype) {
 #ifdef RN50_TUNING  // tuning builds only: RN50_IGEMM_TILE=bm,bn,wm,wn forces a compiled tile shape
