@@ -277,7 +277,7 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
     }
 }
 
-// Weight gradient of a 3x3 / stride 1 / padding 1 layer of 64 -> at most 64 channels, bf16, all nine taps in one workgroup.
+// Weight gradient of a 3x3 / stride 1 / padding 1 layer of at most 64 channels each way, bf16, all nine taps in one workgroup.
 // The reduction index is a PADDED pixel position: every image row gets one more column and every image one more
 // row, whose dy and x are zero (never stored: the loads of those positions carry an out-of-range offset and
 // write zeros).  In that index space tap (r, s) of position k reads x at k + (r-1)(W+1) + (s-1), a constant shift,
@@ -506,9 +506,9 @@ struct WgradPlan {
 // takes the longer of one's latency (lat) and n times the tile's share of the LDS and load rates (thr), both dearer where
 // pixels are gathered; `ends` is prologue and result stores; splits add the reduction launch and the partials' traffic.
 // Constants fitted to ResNet-50's 23 shapes x 12 plans at batch 12 to 256 (bf16) and 2 to 24 (float), when a chunk's pixels were still
-// divided out; since they are advanced from chunk to chunk the plan it takes is within 1 to 4 % of the best of the twelve, summed over the
-// shapes, 6 % at batch 90 (profiles/wgrad_plan_sweep.txt: 478 against 467 us at batch 40, 804 against 757 at 90, 1755 against 1713 at 256, float
-// at batch 8 510 against 502).  Against the fixed rule before it (128-wide tiles, 192 or 384 workgroups), when it was fitted: 23 shapes at
+// divided out; since they are advanced from chunk to chunk the plan it takes is within 0 to 5 % of the best of the twelve, summed over the
+// shapes, 6 % at batch 90 and in float at batch 4 (profiles/wgrad_plan_sweep.txt: 480 against 467 us at batch 40, 805 against 757 at 90, 1755 against
+// 1713 at 256, float at batch 8 510 against 502).  Against the fixed rule before it (128-wide tiles, 192 or 384 workgroups), when it was fitted: 23 shapes at
 // batch 40 640 -> 565 us call by call, at batch 256 2343 -> 2000, float at batch 8 830 -> 531.
 struct WgradCost {
   float thr[3], lat[3], ends[3];  // us; tile area 64x64, 128x64, 128x128
@@ -595,42 +595,58 @@ static WgradArgs wgrad_args(const rn50_conv_desc* d, const void* x, const void* 
   a.split_stride = static_cast<int64_t>(a.Cout) * a.Ktot;
   return a;
 }
-// The nine-tap weight gradient (wgrad3x3_kernel): bf16, 3x3, stride 1, padding 1, 64 input and at most 64 output channels (one 64x64 tile;
-// wider layers do better on wgrad_kernel's 128-wide tiles), an image width whose run of 2W + 68 rows fits six load passes, and
-// kNineTapPositions padded positions or more: 384 workgroups each write a partial of all nine taps, 20 us however few the pixels, and the
-// nine products are as long with fewer input channels.  64 -> 64, us, per tap / nine taps: 56x56 at batch 4 12 / 22, 40 28.7 / 30.1, 64 37.2 /
-// 39.9, 90 45.8 / 46.2, 128 54.4 / 52.8, 180 72 / 65, 256 97 / 83; 28x28 at batch 320 38.5 / 41.0, 640 64.8 / 59.4; 64 -> 16 at 56x56, batch 40 24.8 / 25.8,
-// 64 32.5 / 30.5; 56 -> 64 at batch 256 82 / 81, 32 -> 64 56 / 72.
-// Plan: the padded pixel range split to give about 384 workgroups.
-constexpr int64_t kNineTapPositions = 300000;
+// 3x3, stride 1, padding 1 layers of at most 64 channels each way in bf16 (one 64x64 tile per tap; wider layers do better on wgrad_kernel's
+// 128-wide tiles), of an image width whose run of 2W + 68 rows fits six load passes, from kNineTapPositions padded positions on: the nine-tap
+// kernel (wgrad3x3_kernel).  With fewer, its workgroups are too few or too short: there one tile per tap, in splits of kShortSplitRows rows,
+// whose float sums are no longer than the nine-tap kernel's.  64 -> 64, us, nine taps / per tap / per tap as plan_wgrad would split it, and their
+// errors against 64 bits in 1e-7: 56x56 at batch 4 22.0 / 11.8 / 11.8 (1.31 / 1.09 / 1.09), 12 23.8 / 16.0 / 15.8 (1.37 / 1.33 / 1.46), 24 26.8 / 24.2 /
+// 20.3, 40 28.7 / 30.5 / 27.1 (1.40 / 1.38 / 1.77), 90 46.2 / - / 45.8 (1.75 / - / 2.80), 256 83 / - / 97; 28x28 at batch 70 28 / 21 / 18 (1.34 / 1.34 / 1.63).
+// In the step short splits gain at batch 12 (2.398 -> 2.386 ms), not at 24 and 33, and lose at 40 (4.165 -> 4.187); splits as plan_wgrad
+// would take them gain up to batch 64 (4.165 -> 4.146 at 40), but their sums are less exact than the nine-tap kernel's.
+// Plan: the padded pixel range split to give about 384 workgroups, each at least 8 chunks long.
+constexpr int64_t kNineTapPositions = 1 << 16;
+constexpr int kShortSplitRows = 512;
 struct Wgrad3x3Plan {
   int nbx;  // load passes of the x run: 3, 4 or 6; 0: the layer does not run this kernel
   int splits, rows_per_split, gpad;
 };
-static Wgrad3x3Plan plan_wgrad3x3(const rn50_conv_desc* d) {
+static Wgrad3x3Plan plan_wgrad3x3(const rn50_conv_desc* d, bool* fewer) {  // fewer: such a layer, with fewer positions
   Wgrad3x3Plan p{};
+  *fewer = false;
   if (d->dtype != RN50_BF16 || d->R != 3 || d->S != 3 || d->stride != 1 || d->pad != 1) return p;
-  if (d->Cin != 64 || d->Cout > 64) return p;
+  if (d->Cin > 64 || d->Cout > 64) return p;
   const int need = static_cast<int>(ceil_div(2 * d->W + 68, 32));
   if (need > 6) return p;
   const int64_t gpad = static_cast<int64_t>(d->N) * (d->H + 1) * (d->W + 1);
-  if (gpad < kNineTapPositions || gpad >= (1ll << 31) - 64) return p;
+  *fewer = gpad < kNineTapPositions;
+  if (*fewer || gpad >= (1ll << 31) - 64) return p;
   p.nbx = need <= 3 ? 3 : (need == 4 ? 4 : 6);
   p.gpad = static_cast<int>(gpad);
-  constexpr int target = 384;
-  const int64_t rps = ceil_div(ceil_div(gpad, target), 64) * 64;
+  constexpr int target = 384, min_chunks = 8;
+  const int64_t sp = std::min<int64_t>(target, gpad / (min_chunks * 64));
+  const int64_t rps = ceil_div(ceil_div(gpad, sp), 64) * 64;
   p.rows_per_split = static_cast<int>(rps);
   p.splits = static_cast<int>(ceil_div(gpad, rps));
   return p;
 }
-template <int NBX>
-static void launch_wgrad3x3_nbx(const WgradArgs& a, dim3 grid, hipStream_t s) {
-  // three chunk buffers where two workgroups on a compute unit have the LDS for them, else two
-  constexpr int NSTAGE = 2 * 3 * (64 * 128 + NBX * 4096) <= 156 * 1024 ? 3 : 2;
+static WgradPlan short_splits(WgradPlan p, const WgradArgs& a) {
+  if (p.rows_per_split <= kShortSplitRows) return p;
+  return WgradPlan{64, 64, static_cast<int>(ceil_div(a.Ktot, 64)), static_cast<int>(ceil_div(a.M, kShortSplitRows)), kShortSplitRows};
+}
+template <int NBX, int NSTAGE>
+static void launch_wgrad3x3_ring(const WgradArgs& a, dim3 grid, hipStream_t s) {
   constexpr int lds = NSTAGE * (64 * 128 + NBX * 4096);
   static std::once_flag once;
   std::call_once(once, [] { allow_big_lds(wgrad3x3_kernel<NBX, NSTAGE>, lds); });
   RN50_LAUNCH("conv_wgrad", (wgrad3x3_kernel<NBX, NSTAGE>), grid, dim3(256), lds, s, a);
+}
+template <int NBX>
+static void launch_wgrad3x3_nbx(const WgradArgs& a, dim3 grid, hipStream_t s) {
+  // three chunk buffers where the workgroups on a compute unit, two at most, have the LDS for them, else two
+  if constexpr (2 * 3 * (64 * 128 + NBX * 4096) > 156 * 1024) {
+    if (grid.x > 256) return launch_wgrad3x3_ring<NBX, 2>(a, grid, s);
+  }
+  launch_wgrad3x3_ring<NBX, 3>(a, grid, s);
 }
 static void launch_wgrad3x3(WgradArgs a, const Wgrad3x3Plan& p, int H, hipStream_t s) {
   a.rows_per_split = p.rows_per_split;
@@ -649,8 +665,11 @@ static void launch_wgrad3x3(WgradArgs a, const Wgrad3x3Plan& p, int H, hipStream
 
 size_t wgrad_partial_bytes(const rn50_conv_desc* d) {
   const size_t dw_elems = static_cast<size_t>(d->Cout) * (is_stem(d) ? kStemK : d->R * d->S * d->Cin);
-  const Wgrad3x3Plan p9 = plan_wgrad3x3(d);
-  const int splits = std::max(p9.nbx ? p9.splits : 1, plan_wgrad(wgrad_args(d, nullptr, nullptr), d->dtype).splits);
+  bool fewer;
+  const Wgrad3x3Plan p9 = plan_wgrad3x3(d, &fewer);
+  const WgradArgs a = wgrad_args(d, nullptr, nullptr);
+  const WgradPlan p = plan_wgrad(a, d->dtype);
+  const int splits = std::max(p9.nbx ? p9.splits : 1, fewer ? short_splits(p, a).splits : p.splits);
   size_t b = splits > 1 ? align_up(dw_elems * splits * sizeof(float), 256) : 0;
   if (is_stem(d)) b += align_up(dw_elems * sizeof(float), 256);  // padded dw
   return b;
@@ -669,13 +688,15 @@ void wgrad_run(const rn50_conv_desc* d, const void* x_or_xp, const void* dy, flo
     partial += align_up(static_cast<size_t>(d->Cout) * kStemK * sizeof(float), 256) / sizeof(float);
   }
   int splits;
-  if (const Wgrad3x3Plan p9 = plan_wgrad3x3(d); p9.nbx) {
+  bool fewer;
+  if (const Wgrad3x3Plan p9 = plan_wgrad3x3(d, &fewer); p9.nbx) {
     splits = p9.splits;
     a.out = splits > 1 ? partial : target;
     a.out_through = through_bytes(4 * splits * a.split_stride);
     launch_wgrad3x3(a, p9, d->H, s);
   } else {
-    const WgradPlan p = plan_wgrad(a, d->dtype);
+    WgradPlan p = plan_wgrad(a, d->dtype);
+    if (fewer) p = short_splits(p, a);
     splits = p.splits;
     a.out = splits > 1 ? partial : target;
     a.out_through = through_bytes(4 * splits * a.split_stride);

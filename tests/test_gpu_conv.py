@@ -480,19 +480,20 @@ def test_weight_gradient_steps_over_rows_and_images(rn, mode_name, N, H, W, C, K
     assert_close(dw, want.numpy(), 1e-5, "dw", elementwise=None)  # (products of the inputs as they are, float sums of at most 3,000)
 
 
-# All nine taps in one workgroup (bf16, 64 channels into at most 64, from 300,000 positions of the images padded by a row and a column on; the
-# third case has fewer): an image of exactly a chunk of 64 padded positions, of fewer, of one more row, of a column; widths on both sides of
-# every count of passes over the run of x (14, 30, 62), and the first that no run holds.
-NINE_TAPS = [(4688, 7, 7, 64), (6123, 6, 6, 24), (4687, 7, 7, 64), (4167, 8, 7, 64), (50000, 2, 1, 48), (2000, 9, 14, 64), (1876, 9, 15, 8), (968, 9, 30, 64),
-             (938, 9, 31, 64), (97, 56, 54, 64), (794, 5, 62, 64), (782, 5, 63, 64)]
+# All nine taps in one workgroup (bf16, at most 64 channels each way, from 65,536 positions of the images padded by a row and a column on; the
+# third case has fewer: one tile per tap, in short splits): an image of exactly a chunk of 64 padded positions, of fewer, of one more row, of a
+# column; widths on both sides of every count of passes over the run of x (14, 30, 62), and the first that no run holds; grids of at most one
+# workgroup per compute unit (131,072 positions) and of more.
+NINE_TAPS = [(1024, 7, 7, 64, 64), (1338, 6, 6, 48, 24), (1023, 7, 7, 64, 64), (911, 8, 7, 64, 64), (10923, 2, 1, 64, 48), (437, 9, 14, 64, 64), (410, 9, 15, 40, 8),
+             (212, 9, 30, 64, 64), (205, 9, 31, 64, 64), (40, 56, 56, 64, 56), (174, 5, 62, 64, 64), (171, 5, 63, 64, 64), (347, 5, 62, 64, 64), (128, 56, 56, 16, 64)]
 
 
-@pytest.mark.parametrize("N,H,W,K", NINE_TAPS)
-def test_weight_gradient_of_nine_taps_at_once(rn, N, H, W, K):
+@pytest.mark.parametrize("N,H,W,C,K", NINE_TAPS)
+def test_weight_gradient_of_nine_taps_at_once(rn, N, H, W, C, K):
     gen = torch.Generator(device="cuda").manual_seed(N + W)
-    x = torch.randn(N, H, W, 64, device="cuda", generator=gen).bfloat16()
+    x = torch.randn(N, H, W, C, device="cuda", generator=gen).bfloat16()
     dy = torch.randn(N, H, W, K, device="cuda", generator=gen).bfloat16()
-    dw = [torch.full((K, 3, 3, 64), float("nan"), device="cuda") for _ in range(2)]
+    dw = [torch.full((K, 3, 3, C), float("nan"), device="cuda") for _ in range(2)]
     for d in dw:
         rn.conv_wgrad(x, dy, d.shape, 1, 1, dw=d)
     assert torch.equal(dw[0], dw[1])
@@ -500,8 +501,8 @@ def test_weight_gradient_of_nine_taps_at_once(rn, N, H, W, K):
     rows = dy.double().reshape(-1, K)
     for r in range(3):
         for s in range(3):
-            want = rows.t().contiguous() @ xp[:, r:r + H, s:s + W].reshape(-1, 64).double()
-            # (float sums of products that are exact in float: at most 1,700 per workgroup, 384 of those)
+            want = rows.t().contiguous() @ xp[:, r:r + H, s:s + W].reshape(-1, C).double()
+            # (float sums of products that are exact in float: at most 1,100 per workgroup, 384 workgroups)
             assert_close(dw[0][:, r, s], want.cpu().numpy(), 1e-5, f"dw tap {r},{s}", elementwise=None)
 
 
