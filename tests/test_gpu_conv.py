@@ -532,7 +532,7 @@ def test_forward_with_rings_of_different_depth(rn, mode_name, N, H, W, C, K, R, 
 def test_one_chunk_on_large_tiles(rn, mode_name, N, H, W, C, K):
     """1x1 layers whose reduction is one chunk and whose grid has at least 384 tiles of 128x128 (the second: 512 rows of tiles, the last of 127 rows):
     forward with and without sums, the data gradient likewise, with a second branch and at stride 2, into buffers of NaNs.  In bf16 a data
-    gradient's sums come from 64x64 tiles, and from 128 MB of output on (the last one, just above; the one with 264 columns at stride 2, below)
+    gradient's sums come from 64x64 tiles, and from 128 MB of output on (the last one, just above; at stride 2 both of 264 columns)
     from 128x128, with a second branch from 128x64: the same rows of sums."""
     dt = torch.bfloat16 if mode_name == "bf16" else torch.float32
     gen = torch.Generator().manual_seed(C + K)
