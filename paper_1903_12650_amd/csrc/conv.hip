@@ -152,6 +152,13 @@ template <int BM, int BN, int WM, int WN, int MODE, bool BNIN, bool HALO>
 constexpr bool igemm_deep_a() {
   return BM == 128 && BN == 128 && WM * WN == 4 && MODE != 1 && !BNIN && !HALO;
 }
+// PAIRED: the 128x128 tile's halo loop.  Its two runs and two weight tiles (three everywhere else) are at most 80 KB up to images 31 wide, so
+// two workgroups share a compute unit (no static LDS; the output stage's coefficients lie behind its tile).  A step takes a pair as long as
+// the 256x128 tile's one workgroup (0.75 to 0.85 us, 0.46 of it products), but a rest of the grid that gives each unit a single workgroup
+// takes little more than half a round, where the taller tile takes a whole one, and the two cover each other's prologue and output stage
+// (5 us of a round): see igemm_halo_tile.
+template <int BM, int BN, int WM, int WN>
+constexpr bool igemm_halo_paired() { return BM == 128 && BN == 128 && WM * WN == 4; }
 template <int BM, int BN>
 constexpr int igemm_out_tile() { return BM * (BN * 4 + 16); }  // the output tile in float, with its pitch
 // KS (launched with WM = WN = 1): the four waves of a workgroup split K instead of the tile.  Every wave computes the whole
@@ -215,6 +222,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
   constexpr int STAGE = (BM + BN) * 128;
   constexpr bool DEEP = igemm_deep_a<BM, BN, WM, WN, MODE, BNIN, HALO>();
+  constexpr bool PAIRED = HALO && igemm_halo_paired<BM, BN, WM, WN>();
   constexpr int NSTAGE = OWN ? igemm_ks_ring<BM, BN, BNIN>() : igemm_ring<BM, BN, WM * WN>();
   constexpr int CP = BN * sizeof(T) + 16;  // epilogue pitch
   static_assert((NW == 4 || NW == 8) && TM >= 1 && TN >= 1 && RA >= 1 && RB >= 1, "tile shape");
@@ -244,7 +252,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   // as much as two chunks of the main loop).
   // (MODE 2: the same for the inference-mode affine step.)
   float* prm_s;
-  if constexpr (DEEP) {
+  if constexpr (DEEP || PAIRED) {
     prm_s = reinterpret_cast<float*>(smem + igemm_out_tile<BM, BN>());
   } else {
     __shared__ __align__(16) float prm_static[DG ? 4 * BN : (AFF ? 2 * BN : 4)];
@@ -746,25 +754,48 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
           __builtin_amdgcn_sched_barrier(0);
         }
       };
-      // Prologue: the first run, the weight tiles of steps 0 and 1.  Every step of the loop then issues RB + 1
-      // loads (the weight tile two steps ahead; one pass of the next chunk's run, or a load of nothing), so at its
-      // top "at most RB + 1 outstanding" means: everything up to the step before the previous one has landed.
-      for (int j = 0; j < NA; ++j) load_run_pass(j, 0, 0);
-      load_b_tile(0, 0, 0, true);
-      load_b_tile(1, 0, 1, true);
-      load_nothing();
-      int bstage = 0;
-      for (int cc = 0; cc < cpt; ++cc) {
-        const int buf = cpt > 1 ? (cc & 1) : 0;
+      if constexpr (PAIRED) {
+        // The weights come one tap ahead, and behind them a pass of the next chunk's run, which may stay in flight for one more tap:
+        // it comes from memory, the weights from the L2.
+        for (int j = 0; j < NA; ++j) load_run_pass(j, 0, 0);
+        load_b_tile(0, 0, 0, true);
+        int bstage = 0;
+        bool pass_behind = false;  // the tap before requested a pass of the next run behind its weights
+        for (int cc = 0; cc < cpt; ++cc) {
+          const int buf = cpt > 1 ? (cc & 1) : 0;
+          const bool more = cc + 1 < cpt;
 #pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-          wait_loads_then_barrier<RB + 1>();
-          const int tap2 = (tap + 2) % 9, cc2 = cc + (tap + 2 >= 9 ? 1 : 0);
-          load_b_tile(bstage >= 1 ? bstage - 1 : NSB - 1, cc2, tap2, cc2 < cpt);  // the tile of step - 1: free again
-          if (tap < NA && cc + 1 < cpt) load_run_pass(tap, cc + 1, buf ^ 1);
-          else load_nothing();
-          compute_tap(buf, bstage, tap);
-          bstage = bstage == NSB - 1 ? 0 : bstage + 1;
+          for (int tap = 0; tap < 9; ++tap) {
+            if (pass_behind) wait_loads_then_barrier<1>();
+            else wait_loads_then_barrier<0>();
+            if (tap < 8 || more) load_b_tile(bstage ^ 1, tap < 8 ? cc : cc + 1, (tap + 1) % 9, true);  // the tile of the tap before: free again
+            pass_behind = more && tap < NA;
+            if (pass_behind) load_run_pass(tap, cc + 1, buf ^ 1);
+            compute_tap(buf, bstage, tap);
+            bstage ^= 1;
+          }
+        }
+      } else {
+        // Prologue: the first run, the weight tiles of steps 0 and 1.  Every step of the loop then issues RB + 1
+        // loads (the weight tile two steps ahead; one pass of the next chunk's run, or a load of nothing), so at its
+        // top "at most RB + 1 outstanding" means: everything up to the step before the previous one has landed.
+        for (int j = 0; j < NA; ++j) load_run_pass(j, 0, 0);
+        load_b_tile(0, 0, 0, true);
+        load_b_tile(1, 0, 1, true);
+        load_nothing();
+        int bstage = 0;
+        for (int cc = 0; cc < cpt; ++cc) {
+          const int buf = cpt > 1 ? (cc & 1) : 0;
+#pragma unroll
+          for (int tap = 0; tap < 9; ++tap) {
+            wait_loads_then_barrier<RB + 1>();
+            const int tap2 = (tap + 2) % 9, cc2 = cc + (tap + 2 >= 9 ? 1 : 0);
+            load_b_tile(bstage >= 1 ? bstage - 1 : NSB - 1, cc2, tap2, cc2 < cpt);  // the tile of step - 1: free again
+            if (tap < NA && cc + 1 < cpt) load_run_pass(tap, cc + 1, buf ^ 1);
+            else load_nothing();
+            compute_tap(buf, bstage, tap);
+            bstage = bstage == NSB - 1 ? 0 : bstage + 1;
+          }
         }
       }
     }
@@ -1148,7 +1179,7 @@ static void launch_igemm_mode(const IgemmArgs& a, const char* tag, int64_t grid,
 // compute unit has).
 static bool igemm_halo_shape(const IgemmArgs& a);
 // (the kernel's static arrays come on top; a compute unit has 160 KB, for two workgroups by rows with 2x2 waves)
-constexpr int kHaloLdsMax = 152 * 1024, kHaloRowLdsMax = 78 * 1024, kHaloRowGroups = 512;
+constexpr int kHaloLdsMax = 152 * 1024, kHaloRowLdsMax = 78 * 1024, kHaloRowGroups = 512, kHaloPairLdsMax = 80 * 1024;
 template <typename T, int BM, int BN, int WM, int WN>
 static int halo_lds_bytes(int W, int cpt, int taps) {
   constexpr bool KS = WM * WN == 1;
@@ -1156,6 +1187,7 @@ static int halo_lds_bytes(int W, int cpt, int taps) {
   const int passes = (BM + 2 * W + 2 + RPL - 1) / RPL;
   if (passes > 8 && (cpt > 1 || BM != 256 || BN != 64)) return 0;  // (a chunk's taps load the next one's run)
   const int runs = (cpt > 1 ? 2 : 1) * passes * RPL * 128;
+  if (igemm_halo_paired<BM, BN, WM, WN>()) return runs + 2 * BN * 128 <= kHaloPairLdsMax ? runs + 2 * BN * 128 : 0;
   const int bytes = runs + (taps == 3 ? 3 * (igemm_row_ahead<T, KS>() + 1) * BN * 128 : 3 * BN * 128 + NW * 1024);
   return bytes <= (taps == 3 && !KS ? kHaloRowLdsMax : kHaloLdsMax) ? bytes : 0;
 }
@@ -1167,7 +1199,10 @@ static void launch_igemm_halo_through(IgemmArgs a, const char* tag, int64_t grid
   constexpr int out_tile = igemm_out_tile<BM, BN>();
   constexpr int col_sums = (NT / (BN * es / 16)) * 2 * BN * 4;
   constexpr int exchange = KS ? 4 * BM * BN * 4 : 0;     // (KS: the four partial tiles)
-  constexpr int out_need = std::max({out_tile, col_sums, exchange});
+  constexpr bool paired = igemm_halo_paired<BM, BN, WM, WN>();
+  constexpr int behind = paired ? (MODE == 1 ? 4 : 2) * BN * 4 : 0;  // (the output stage's coefficients)
+  constexpr int out_need = std::max({out_tile + behind, col_sums, exchange});
+  static_assert(!paired || out_need <= kHaloPairLdsMax, "two workgroups per compute unit");
   static std::once_flag once;
   std::call_once(once, [] { allow_big_lds(igemm_kernel<T, BM, BN, WM, WN, MODE, false, false, TAPS, THROUGH>, kHaloLdsMax); });
   const int lds = main_lds > out_need ? main_lds : out_need;
@@ -1225,7 +1260,7 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
       const int lds = WM * WN == 1 || grid <= kHaloRowGroups ? halo_lds_bytes<T, BM, BN, WM, WN>(a.W, a.cpt, 3) : 0;
       if (lds) return launch_igemm_halo_mode<T, BM, BN, WM, WN, 3>(a, tag, grid, lds, s);
     }
-    if constexpr (WM * WN > 1 && (BM != 128 || BN != 128 || kTuning)) {  // (igemm_halo_tile never takes the 128x128 tile)
+    if constexpr (WM * WN > 1) {
       const int lds = halo_lds_bytes<T, BM, BN, WM, WN>(a.W, a.cpt, 1);
       if (lds) return launch_igemm_halo_mode<T, BM, BN, WM, WN, 1>(a, tag, grid, lds, s);
     }
@@ -1281,10 +1316,19 @@ static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool strided_dgrad
 }
 // The tile of a 3x3 / stride 1 / padding 1 layer, which runs the halo main loop (forward and data gradient
 // alike): fitted to sweeps of the compiled shapes over ResNet-50's four such layers at batch 40 and 256.  The
-// eight-wave 256x128 tile once it gives three quarters of the compute units a workgroup, else 128x64 while that
-// leaves one and a half workgroups per compute unit, else 64x64 (the 128x128 tile never won: its two runs and
-// three weight tiles leave room for one workgroup per compute unit only).
-constexpr int kHaloTallWidth = 63;
+// eight-wave 256x128 tile, or two 128x128 ones per compute unit (PAIRED), once the former gives three quarters of the compute units a
+// workgroup, else 128x64 while that leaves one and a half workgroups per compute unit, else 64x64.
+constexpr int kHaloTallWidth = 63, kHaloPairWidth = 31;
+// Of the two tiles of 128 columns, whether the paired one.  A round of either takes as long (36 steps: 33 us, 18: 18 us); 256x128 tiles make
+// ceil(tiles / 256) of them, pairs tiles / 512 and for the rest one more, or 0.55 of one where it leaves every compute unit a single tile at most.  At equal
+// rounds the taller tile loads its weights half as often.  us, forward / data gradient, 256x128 -> pairs: 128 -> 128 at 28x28, batch 256 (4 rounds,
+// 3.55) 73.7 / 79.3 -> 63.5 / 66.8, 200 (3, 2.55) 56.0 / 60.3 -> 48.1 / 50.4, 128 (2, 2) 38.1 / 40.6 -> 36.5 / 39.0, 90 (2, 1.55) 36.1 / 38.5 -> 29.0 /
+// 30.9; 256 -> 256 at 14x14, 256 (2, 2) 65.8 / 68.5 -> 64.8 / 68.0, 200 (2, 1.55) 62.9 / 66.2 -> 51.7 / 54.1, 128 (1, 1) 34.0 / 35.8 -> 34.3 / 35.3; 512 ->
+// 512 at 7x7, 256 (1, 1) 57 / 61 -> 62 / 66.
+static bool igemm_halo_pairs(int64_t tall, int64_t pairs) {  // (tiles of 256 and of 128 rows)
+  const int64_t rest = pairs % 512;
+  return 20 * (pairs / 512) + (rest == 0 ? 0 : rest <= 256 ? 11 : 20) < 20 * ceil_div(tall, 256);
+}
 static TileShape igemm_halo_tile(int64_t M, int Ncols, int cpt, int W) {
   auto groups = [&](int bm, int bn) { return ceil_div(M, bm) * ceil_div(Ncols, bn); };
   // One chunk of channels into at most 64 columns: four waves of 64x64 one above the other read two thirds of the fragment bytes per product
@@ -1294,7 +1338,8 @@ static TileShape igemm_halo_tile(int64_t M, int Ncols, int cpt, int W) {
 // that decide, two workgroups against three of the 128x64 tile (32 -> 64 forward, batch 32 46.7 -> 40.2, 64 81 -> 81, 128 149 -> 138; 63x63, batch 40 59 -> 62, 64
 // 94 -> 83).
   if (Ncols <= 64 && cpt == 1 && W <= kHaloTallWidth && groups(256, 64) >= 384) return TileShape{256, 64, 4, 1};
-  if (Ncols > 64 && groups(256, 128) >= 192) return TileShape{256, 128, 4, 2};
+  if (Ncols > 64 && groups(256, 128) >= 192)
+    return W <= kHaloPairWidth && igemm_halo_pairs(groups(256, 128), groups(128, 128)) ? TileShape{128, 128, 2, 2} : TileShape{256, 128, 4, 2};
   if (groups(128, 64) >= 384) return TileShape{128, 64, 2, 2};
   return TileShape{64, 64, 2, 2};
 }

@@ -348,9 +348,14 @@ HALO_ROWS = [(1, 1, 1, 8, 8), (1, 2, 1, 64, 64), (2, 5, 3, 72, 40), (1, 3, 111, 
 # more, images of one column, more channels than a chunk (bf16: 64).
 HALO_TALL = [(32, 56, 56, 64, 64), (25, 63, 63, 40, 24), (25, 62, 64, 40, 24), (33, 3000, 1, 16, 64), (1, 1, 98400, 8, 8), (33, 56, 54, 72, 64)]
 
+# ... and of 128x128 tiles, two workgroups per compute unit: the widest image they take and one column more, one chunk, images of one column,
+# whole images and tiles, the longest rest that still counts as half a round (768 tiles) and one row of tiles more.
+HALO_PAIRS = [(1, 265, 31, 72, 1000), (1, 257, 32, 72, 1000), (1, 265, 31, 8, 1000), (1, 8200, 1, 64, 1016), (42, 14, 14, 136, 1024),
+              (48, 16, 16, 64, 1024), (1, 12300, 1, 8, 1024)]
+
 
 @pytest.mark.parametrize("mode_name", ["f32", "bf16"])
-@pytest.mark.parametrize("N,H,W,C,K", HALO_ROWS + HALO_TALL)
+@pytest.mark.parametrize("N,H,W,C,K", HALO_ROWS + HALO_TALL + HALO_PAIRS)
 def test_3x3_by_filter_rows(rn, mode_name, N, H, W, C, K):
     """Forward with and without sums, data gradient with and without, into buffers of NaNs, against 64 bits."""
     dt = torch.bfloat16 if mode_name == "bf16" else torch.float32
