@@ -28,6 +28,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "conv_internal.h"
@@ -315,13 +316,14 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   }
   // What the output stage reads besides the tile: the BN layer's input, the second branch, recorded ReLU bits.  EARLY: requested
   // here, in front of everything the main loop loads (the hand-placed load waits count in order, and these are the oldest), so
-  // that it is there when the last product is.  That is for workgroups that have a compute unit to themselves (KS: step at
-  // batch 4 2.03 -> 1.99 ms) and for the evaluation pass (4.68 -> 4.65 ms at batch 256); where several workgroups hide each
-  // other's latencies the registers cost more than the wait (step at batch 256 20.65 -> 20.9 ms).
-  constexpr bool EARLY = KS || AFF;
+  // that it is there when the last product is: workgroups of an earlier round are not enough to cover the 2 us these loads take from memory.
+  // Step at batch 12 2395 -> 2375 us, 40 4161 -> 4134, 64 5852 -> 5809 (all against the 128x128 tile alone, which had given 4271 -> 4190 and at
+  // batch 256 19024 -> 18840).  Not where the registers leave a compute unit a workgroup less: the paired 128x128 tiles (three data gradients at
+  // 28x28, batch 256 250 -> 325 us) and, in float, tiles of more than eight rows a thread.
   constexpr int PPR = BN * sizeof(T) / 16;  // 16-byte pieces per output row
   constexpr int RPP = NT / PPR;             // rows per pass
   constexpr int NPASS = BM / RPP;
+  constexpr bool EARLY = KS || AFF || (!PAIRED && NPASS <= 8);
   const int op = tid % PPR, orow = tid / PPR;
   const int n = n0 + op * V;
   const bool col_ok = n < a.Ncols;
@@ -332,27 +334,46 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     if (AFF ? a.addend == nullptr : a.partial == nullptr) return;
     const T* add = static_cast<const T*>(a.addend);
     const int nc = col_ok ? n : 0;
-#pragma unroll
-    for (int pass = 0; pass < NPASS; ++pass) {
+    auto pixel_of = [&](int pass) __attribute__((always_inline)) {
       const int row = orow + pass * RPP;
-      const int px = classes ? pixel(row) : min(m0 + row, a.M - 1);  // rows past the last read a valid pixel
-      const int64_t at = static_cast<int64_t>(px) * a.Ncols + nc;
-      if constexpr (DG) {
-        xv[pass] = load16(static_cast<const T*>(a.bn_x) + at);
-        if (a.bn_zmask) zb[pass] = a.bn_zmask[at / V];
-        ab[pass] = a.addend_mask ? a.addend_mask[at / V] : 0xffu;
+      return classes ? pixel(row) : min(m0 + row, a.M - 1);  // rows past the last read a valid pixel
+    };
+    // (one loop per operand: a test of a pointer per row is a branch per row, and no load passes a branch; byte offsets are 31-bit)
+    uint32_t at[NPASS];
+#pragma unroll
+    for (int pass = 0; pass < NPASS; ++pass) at[pass] = static_cast<uint32_t>(pixel_of(pass)) * static_cast<uint32_t>(a.Ncols) + nc;
+    if constexpr (DG) {
+#pragma unroll
+      for (int pass = 0; pass < NPASS; ++pass) xv[pass] = load16(static_cast<const T*>(a.bn_x) + at[pass]);
+      if (a.bn_zmask) {
+#pragma unroll
+        for (int pass = 0; pass < NPASS; ++pass) zb[pass] = a.bn_zmask[at[pass] / V];
       }
-      if constexpr (DG && LIN) {
-        if (add && a.addend_even) {
+      if (a.addend_mask) {
+#pragma unroll
+        for (int pass = 0; pass < NPASS; ++pass) ab[pass] = a.addend_mask[at[pass] / V];
+      } else {
+#pragma unroll
+        for (int pass = 0; pass < NPASS; ++pass) ab[pass] = 0xffu;
+      }
+    }
+    if constexpr (DG && LIN) {
+      if (add && a.addend_even) {
+#pragma unroll
+        for (int pass = 0; pass < NPASS; ++pass) {
+          const int px = pixel_of(pass);
           const uint32_t t = fdiv(static_cast<uint32_t>(px), a.div_w[0]), w = static_cast<uint32_t>(px) - t * a.Q;
           const uint32_t img = fdiv(t, a.div_h[0]), h = t - img * a.P;
           const int64_t e = (static_cast<int64_t>(img) * ((a.P + 1) >> 1) + (h >> 1)) * ((a.Q + 1) >> 1) + (w >> 1);
           av[pass].u = make_uint4(0, 0, 0, 0);
           if (((h | w) & 1) == 0) av[pass] = load16_stream(add + e * a.Ncols + nc);
-          continue;
         }
+        return;
       }
-      if (add) av[pass] = load16_stream(add + at);  // (its last reader)
+    }
+    if (add) {
+#pragma unroll
+      for (int pass = 0; pass < NPASS; ++pass) av[pass] = load16_stream(add + at[pass]);  // (its last reader)
     }
   };
   if constexpr ((DG || AFF) && EARLY) {
@@ -917,28 +938,36 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
 
   // Epilogue.  acc[i][j][v]: output channel n = j*32 + (v/4)*8 + (lane/32)*4 + v%4, pixel m = i*32 + lane%32.
   // The tile goes to LDS in the storage type, or in float when a bf16 data gradient has an addend.
+  // What a launch's output stage does is chosen once per workgroup, with a copy of the loops each: tests inside them were two branches per
+  // element, 130 a wave and tile in data gradients with sums (with sums at batch 256: 64 <- 64 3x3 at 56x56 113 -> 99 us; 128 <- 128 3x3 at 28x28
+  // 93 -> 86).  The forward sums keep their one test per row: with rows past the end added as zeros instead 30 layers at batch 256 1905 -> 1950 us.
   const bool wide = sizeof(T) == 2 && (AFF || (DG && a.partial != nullptr)) && a.addend != nullptr;
+  auto stage_tile = [&](auto wide_tile, auto relu) __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int row = wm * (BM / WM) + i * 32 + (lane & 31);
+      for (int j = 0; j < TN; ++j) {
+        const int row = wm * (BM / WM) + i * 32 + (lane & 31);
 #pragma unroll
-      for (int g0 = 0; g0 < (KS ? 1 : 4); ++g0) {
-        const int g = KS ? wave : g0;
-        const int col = wn * (BN / WN) + j * 32 + g * 8 + (lane >> 5) * 4;
-        unsigned char* dst = smem + row * CP + col * sizeof(T);
-        float4 v = make_float4(acc[i][j][g0 * 4 + 0], acc[i][j][g0 * 4 + 1], acc[i][j][g0 * 4 + 2], acc[i][j][g0 * 4 + 3]);
-        if constexpr (AFF) {
-          const float4 sc = *reinterpret_cast<const float4*>(prm_s + col), bi = *reinterpret_cast<const float4*>(prm_s + BN + col);
-          v = make_float4(bn_affine(v.x, sc.x, bi.x), bn_affine(v.y, sc.y, bi.y), bn_affine(v.z, sc.z, bi.z), bn_affine(v.w, sc.w, bi.w));
-          if (a.aff_relu && !a.addend) v = make_float4(fmaxf(v.x, 0.f), fmaxf(v.y, 0.f), fmaxf(v.z, 0.f), fmaxf(v.w, 0.f));
+        for (int g0 = 0; g0 < (KS ? 1 : 4); ++g0) {
+          const int g = KS ? wave : g0;
+          const int col = wn * (BN / WN) + j * 32 + g * 8 + (lane >> 5) * 4;
+          unsigned char* dst = smem + row * CP + col * sizeof(T);
+          float4 v = make_float4(acc[i][j][g0 * 4 + 0], acc[i][j][g0 * 4 + 1], acc[i][j][g0 * 4 + 2], acc[i][j][g0 * 4 + 3]);
+          if constexpr (AFF) {
+            const float4 sc = *reinterpret_cast<const float4*>(prm_s + col), bi = *reinterpret_cast<const float4*>(prm_s + BN + col);
+            v = make_float4(bn_affine(v.x, sc.x, bi.x), bn_affine(v.y, sc.y, bi.y), bn_affine(v.z, sc.z, bi.z), bn_affine(v.w, sc.w, bi.w));
+            if (decltype(relu)::value) v = make_float4(fmaxf(v.x, 0.f), fmaxf(v.y, 0.f), fmaxf(v.z, 0.f), fmaxf(v.w, 0.f));
+          }
+          if (decltype(wide_tile)::value) *reinterpret_cast<float4*>(smem + row * CPW + col * 4) = v;
+          else if (sizeof(T) == 2) *reinterpret_cast<uint2*>(dst) = make_uint2(float2_to_bf16x2_bits(v.x, v.y), float2_to_bf16x2_bits(v.z, v.w));
+          else *reinterpret_cast<float4*>(dst) = v;
         }
-        if (wide) *reinterpret_cast<float4*>(smem + row * CPW + col * 4) = v;
-        else if (sizeof(T) == 2) *reinterpret_cast<uint2*>(dst) = make_uint2(float2_to_bf16x2_bits(v.x, v.y), float2_to_bf16x2_bits(v.z, v.w));
-        else *reinterpret_cast<float4*>(dst) = v;
       }
-    }
+  };
+  if (AFF && a.aff_relu && !a.addend) stage_tile(std::false_type{}, std::bool_constant<AFF>{});
+  else if ((AFF || DG) && sizeof(T) == 2 && wide) stage_tile(std::bool_constant<(AFF || DG) && sizeof(T) == 2>{}, std::false_type{});
+  else stage_tile(std::false_type{}, std::false_type{});
   if (DG && a.partial != nullptr && tid < BN) {
     float sc, bi;
     bn_coeffs(pg, pb, pm, pr, &sc, &bi);
@@ -948,23 +977,25 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   const OutTensor<T, THROUGH> out(static_cast<T*>(a.out), a.out_through);
   if constexpr (AFF) {
     if (a.addend != nullptr) {
+      auto rows = [&](auto relu) __attribute__((always_inline)) {
 #pragma unroll
-      for (int pass = 0; pass < NPASS; ++pass) {
-        const int row = orow + pass * RPP, m = m0 + row;
-        if (m < Mc && n < a.Ncols) {
+        for (int pass = 0; pass < NPASS; ++pass) {
+          const int row = orow + pass * RPP, m = m0 + row;
           float r[V], t[V];
           Elem<T>::unpack(av[pass], r);
           load_floats<V>(reinterpret_cast<const float*>(smem + row * CPW) + op * V, t);
 #pragma unroll
           for (int j = 0; j < V; ++j) {
             t[j] += r[j];
-            if (a.aff_relu) t[j] = fmaxf(t[j], 0.f);
+            if (decltype(relu)::value) t[j] = fmaxf(t[j], 0.f);
           }
           Vec16 o;
           Elem<T>::pack(t, o);
-          out.store(static_cast<int64_t>(m) * a.Ncols + n, o);
+          if (m < Mc && col_ok) out.store(static_cast<int64_t>(m) * a.Ncols + n, o);
         }
-      }
+      };
+      if (a.aff_relu) rows(std::true_type{});
+      else rows(std::false_type{});
       return;
     }
   }
@@ -1011,7 +1042,6 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       }
     }
   } else {
-    const bool add = a.addend != nullptr;
     if constexpr (!EARLY) load_output_operands();
     float scale[V], bias[V], rs[V], nmr[V];
 #pragma unroll
@@ -1019,45 +1049,49 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       scale[j] = prm_s[op * V + j]; bias[j] = prm_s[BN + op * V + j];
       rs[j] = prm_s[2 * BN + op * V + j]; nmr[j] = prm_s[3 * BN + op * V + j];
     }
+    // masked: the BN layer's recorded ReLU bits are there; added: a second branch
+    auto rows = [&](auto masked, auto added) __attribute__((always_inline)) {
 #pragma unroll
-    for (int pass = 0; pass < NPASS; ++pass) {
-      const int row = orow + pass * RPP;
-      if (m0 + row < Mc && col_ok) {
+      for (int pass = 0; pass < NPASS; ++pass) {
+        const int row = orow + pass * RPP;
         Vec16 v;
         float g[V], xf[V];
-        if (add) {
+        if constexpr (decltype(added)::value) {
           float ad[V];
           Elem<T>::unpack(av[pass], ad);
 #pragma unroll
           for (int j = 0; j < V; ++j) ad[j] = ((ab[pass] >> j) & 1u) ? ad[j] : 0.f;
-          if (wide) {
-            const float4 lo = *reinterpret_cast<const float4*>(smem + row * CPW + op * 32);
-            const float4 hi = *reinterpret_cast<const float4*>(smem + row * CPW + op * 32 + 16);
-            const float t[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+          // (in bf16 the tile lies in LDS in float)
+          load_floats<V>(reinterpret_cast<const float*>(smem + row * (sizeof(T) == 2 ? CPW : CP)) + op * V, g);
 #pragma unroll
-            for (int j = 0; j < V; ++j) g[j] = t[j] + ad[j];
-          } else {
-            v.u = *reinterpret_cast<const uint4*>(smem + row * CP + op * 16);
-            Elem<T>::unpack(v, g);
-#pragma unroll
-            for (int j = 0; j < V; ++j) g[j] += ad[j];
-          }
+          for (int j = 0; j < V; ++j) g[j] += ad[j];
           Elem<T>::pack(g, v);
         } else {
           v.u = *reinterpret_cast<const uint4*>(smem + row * CP + op * 16);
         }
-        const int pix = classes ? pixel(row) : m0 + row;
-        out.store(static_cast<int64_t>(pix) * a.Ncols + n, v);
+        if (m0 + row < Mc && col_ok) {
+          const int pix = classes ? pixel(row) : m0 + row;
+          out.store(static_cast<int64_t>(pix) * a.Ncols + n, v);
+        } else {
+          v.u = make_uint4(0, 0, 0, 0);  // (a row past the last adds zeros)
+        }
         Elem<T>::unpack(v, g);  // the sums range over the stored (rounded) values
         Elem<T>::unpack(xv[pass], xf);
 #pragma unroll
         for (int j = 0; j < V; ++j) {
-          const bool on = a.bn_zmask ? ((zb[pass] >> j) & 1u) != 0 : bn_affine(xf[j], scale[j], bias[j]) > 0.f;
+          const bool on = decltype(masked)::value ? ((zb[pass] >> j) & 1u) != 0 : bn_affine(xf[j], scale[j], bias[j]) > 0.f;
           const float gm = on ? g[j] : 0.f;
           s1[j] += gm;
           s2[j] = fmaf(gm, fmaf(xf[j], rs[j], nmr[j]), s2[j]);
         }
       }
+    };
+    if (a.bn_zmask) {
+      if (a.addend) rows(std::true_type{}, std::true_type{});
+      else rows(std::true_type{}, std::false_type{});
+    } else {
+      if (a.addend) rows(std::false_type{}, std::true_type{});
+      else rows(std::false_type{}, std::false_type{});
     }
   }
   // The per-thread sums of a column meet through LDS: [row group][plane][column], over the tile buffer
