@@ -149,9 +149,20 @@ constexpr int igemm_ring() {
 // comes from memory, B, the weights, from the L2: with both one chunk ahead a chunk took as long as A's loads, 1.2 us.  23 shapes
 // forward at batch 256 1817 -> 1751 us, 100 869 -> 846, 40 392 -> 390; evaluation at batch 256 4.40 -> 4.28 ms, 64 1.331 -> 1.297.  Not the
 // data gradients: beside the weight gradients they leave them no LDS (step at batch 256 19.14 -> 19.18 ms), alone 1807 -> 1804 us.
-template <int BM, int BN, int WM, int WN, int MODE, bool BNIN, bool HALO>
+template <typename T, int BM, int BN, int WM, int WN, int MODE, bool BNIN, bool HALO>
 constexpr bool igemm_deep_a() {
-  return BM == 128 && BN == 128 && WM * WN == 4 && MODE != 1 && !BNIN && !HALO;
+  return BM == 128 && BN == 128 && WM * WN == 4 && (MODE == 2 || (MODE == 0 && sizeof(T) == 4)) && !BNIN && !HALO;
+}
+// LEAN: the same tile's training forward in bf16 has two buffers for A and one for B, 48 KB: three workgroups per compute unit (at most 168 registers; no
+// static LDS).  What these layers are short of is not depth but another workgroup: a workgroup's products and its output stage, which
+// writes most of the bytes, take as long as each other and two workgroups do not keep them side by side (256 -> 1024 at 14x14, batch 256: 29 us without the
+// output stage, 24 without the products, 58 together).  B, from the L2, is requested behind the barrier that ends its last reading, a wait that
+// the other two workgroups cover.  With sums, from memory, DEEP -> LEAN at batch 256: 256 -> 1024 at 14x14 57.8 -> 50.7 us, 128 -> 512 at 28x28 92.7 -> 80.3,
+// 512 -> 256 at 28x28 82.7 -> 76.8, 1024 -> 512 at 14x14 70.5 -> 64.6; step 18540 -> 18440.  Not the evaluation pass (160 registers and more, with a
+// residual 69 KB: two workgroups; 4180 -> 4240 us) and not float (an output tile of 68 KB).
+template <typename T, int BM, int BN, int WM, int WN, int MODE, bool BNIN, bool HALO>
+constexpr bool igemm_lean_b() {
+  return BM == 128 && BN == 128 && WM * WN == 4 && MODE == 0 && sizeof(T) == 2 && !BNIN && !HALO;
 }
 // PAIRED: the 128x128 tile's halo loop.  Its two runs and two weight tiles (three everywhere else) are at most 80 KB up to images 31 wide, so
 // two workgroups share a compute unit (no static LDS; the output stage's coefficients lie behind its tile).  A step takes a pair as long as
@@ -222,7 +233,8 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   constexpr int NL = RA + RB;
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
   constexpr int STAGE = (BM + BN) * 128;
-  constexpr bool DEEP = igemm_deep_a<BM, BN, WM, WN, MODE, BNIN, HALO>();
+  constexpr bool DEEP = igemm_deep_a<T, BM, BN, WM, WN, MODE, BNIN, HALO>();
+  constexpr bool LEAN = igemm_lean_b<T, BM, BN, WM, WN, MODE, BNIN, HALO>();
   constexpr bool PAIRED = HALO && igemm_halo_paired<BM, BN, WM, WN>();
   constexpr int NSTAGE = OWN ? igemm_ks_ring<BM, BN, BNIN>() : igemm_ring<BM, BN, WM * WN>();
   constexpr int CP = BN * sizeof(T) + 16;  // epilogue pitch
@@ -856,6 +868,24 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         });
         ia = ia == 2 ? 0 : ia + 1;
       }
+    } else if constexpr (LEAN) {
+      // Buffers B A0 A1.  Chunk k: A was requested two chunks ago, B behind chunk k - 1's products; only A of chunk k + 1 may still be in flight.
+      auto buf_a = [](int i) __attribute__((always_inline)) { return static_cast<uint32_t>(BN + i * BM) * 128; };
+      if (nchunks > 0) {
+        load_a(wave_dst + buf_a(0));
+        load_b(wave_dst, b_cc, sob);
+      }
+      if (nchunks > 1) load_a(wave_dst + buf_a(1));
+      for (int kc = 0; kc < nchunks; ++kc) {
+        if (kc + 1 < nchunks) wait_loads_then_barrier<RA>(); else wait_loads_then_barrier<0>();
+        compute(smem + buf_a(kc & 1), smem, [] {});
+        if (kc + 1 < nchunks) {
+          __builtin_amdgcn_s_barrier();  // (every wave's fragments of B and of this A are in registers)
+          asm volatile("" ::: "memory");
+          load_b(wave_dst, b_cc, sob);
+          if (kc + 2 < nchunks) load_a(wave_dst + buf_a(kc & 1));
+        }
+      }
     } else {
 #pragma unroll
       for (int c = 0; c < NSTAGE - 1; ++c)
@@ -1169,13 +1199,15 @@ static void launch_igemm_through(IgemmArgs a, const char* tag, int64_t grid, hip
   constexpr int es = static_cast<int>(sizeof(T));
   // the output stage reuses the ring: the tile (in float when a bf16 data gradient adds a second branch) and
   // the column sums of the fused batch norm
-  constexpr bool deep = igemm_deep_a<BM, BN, WM, WN, MODE, BNIN, false>();
+  constexpr bool deep = igemm_deep_a<T, BM, BN, WM, WN, MODE, BNIN, false>();
   constexpr int col_sums = (NT / (BN * es / 16)) * 2 * BN * 4;
   constexpr int exchange = KS ? 4 * BM * BN * 4 : 0;     // (KS: the four partial tiles)
   constexpr int behind = deep ? 2 * BN * 4 : 0;          // (behind the output tile: MODE 2's coefficients)
   constexpr int out_most = std::max({igemm_out_tile<BM, BN>() + behind, col_sums, exchange});
   static std::once_flag once;
   constexpr int deep_ring = (2 * BN + 3 * BM) * 128;
+  constexpr bool lean = igemm_lean_b<T, BM, BN, WM, WN, MODE, BNIN, false>();
+  constexpr int lean_ring = (BN + 2 * BM) * 128;
   static_assert(!deep || (deep_ring <= 80 * 1024 && out_most <= deep_ring), "two workgroups per compute unit");
   constexpr int nring = KS ? igemm_ks_ring<BM, BN, BNIN>() : igemm_ring<BM, BN, WM * WN>();
   // input-side BN coefficients: two floats per channel, at most 4096 channels (KS: 2048)
@@ -1187,7 +1219,7 @@ static void launch_igemm_through(IgemmArgs a, const char* tag, int64_t grid, hip
   // A short reduction never touches the later ring buffers, and an output tile in the storage type is half as large as in float; with
   // less LDS more workgroups fit a CU (the 1x1 layers with 64 channels, the largest pixel counts of the net, have a single chunk).
   const int chunks = a.R * a.S * a.cpt;
-  const int ring = deep ? (chunks >= 3 ? deep_ring : chunks * stage) : (!KS && chunks < nring ? (chunks < 1 ? 1 : chunks) : nring) * stage;
+  const int ring = deep ? (chunks >= 3 ? deep_ring : chunks * stage) : lean ? (chunks >= 2 ? lean_ring : stage) : (!KS && chunks < nring ? (chunks < 1 ? 1 : chunks) : nring) * stage;
   const bool wide = es == 2 && (MODE == 2 || (MODE == 1 && a.partial != nullptr && a.addend != nullptr));
   const int out_need = std::max({(wide ? igemm_out_tile<BM, BN>() : BM * (BN * es + 16)) + behind, col_sums, exchange});
   int lds = ring > out_need ? ring : out_need;
