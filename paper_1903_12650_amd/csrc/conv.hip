@@ -880,8 +880,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         if (kc + 1 < nchunks) wait_loads_then_barrier<RA>(); else wait_loads_then_barrier<0>();
         compute(smem + buf_a(kc & 1), smem, [] {});
         if (kc + 1 < nchunks) {
-          __builtin_amdgcn_s_barrier();  // (every wave's fragments of B and of this A are in registers)
-          asm volatile("" ::: "memory");
+          lds_reads_then_barrier();  // every wave's fragments of B and of this A are in registers
           load_b(wave_dst, b_cc, sob);
           if (kc + 2 < nchunks) load_a(wave_dst + buf_a(kc & 1));
         }

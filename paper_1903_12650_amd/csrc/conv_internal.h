@@ -36,6 +36,8 @@ __device__ __forceinline__ void lds_writes_then_barrier() {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
+// Barrier behind LDS reads of this wave, whose buffers loads overwrite right behind it: the same waits.
+__device__ __forceinline__ void lds_reads_then_barrier() { lds_writes_then_barrier(); }
 
 // A 16-byte buffer load with LDS as its destination (buffer_load_dwordx4 ... lds): lane l of the wave writes its 16
 // bytes to LDS address lds_addr + 16*l (lds_addr uniform, taken from M0), so one instruction fills 1 KB; lanes
