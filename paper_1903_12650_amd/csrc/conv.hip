@@ -1078,8 +1078,9 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       scale[j] = prm_s[op * V + j]; bias[j] = prm_s[BN + op * V + j];
       rs[j] = prm_s[2 * BN + op * V + j]; nmr[j] = prm_s[3 * BN + op * V + j];
     }
-    // masked: the BN layer's recorded ReLU bits are there; added: a second branch
-    auto rows = [&](auto masked, auto added) __attribute__((always_inline)) {
+    // masked: the BN layer's recorded ReLU bits are there; added: a second branch; whole: no row or column of the tile is past the last (a test
+    // per row is a branch per row: step at batch 256 18.28 -> 18.20 ms without them, forward and evaluation no difference)
+    auto rows = [&](auto masked, auto added, auto whole) __attribute__((always_inline)) {
 #pragma unroll
       for (int pass = 0; pass < NPASS; ++pass) {
         const int row = orow + pass * RPP;
@@ -1087,9 +1088,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         float g[V], xf[V];
         if constexpr (decltype(added)::value) {
           float ad[V];
-          Elem<T>::unpack(av[pass], ad);
-#pragma unroll
-          for (int j = 0; j < V; ++j) ad[j] = ((ab[pass] >> j) & 1u) ? ad[j] : 0.f;
+          Elem<T>::unpack(keep_bits<T>(av[pass], ab[pass]), ad);
           // (in bf16 the tile lies in LDS in float)
           load_floats<V>(reinterpret_cast<const float*>(smem + row * (sizeof(T) == 2 ? CPW : CP)) + op * V, g);
 #pragma unroll
@@ -1098,29 +1097,33 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         } else {
           v.u = *reinterpret_cast<const uint4*>(smem + row * CP + op * 16);
         }
-        if (m0 + row < Mc && col_ok) {
+        if (decltype(whole)::value || (m0 + row < Mc && col_ok)) {
           const int pix = classes ? pixel(row) : m0 + row;
           out.store(static_cast<int64_t>(pix) * a.Ncols + n, v);
         } else {
           v.u = make_uint4(0, 0, 0, 0);  // (a row past the last adds zeros)
         }
+        if constexpr (decltype(masked)::value) v = keep_bits<T>(v, zb[pass]);
         Elem<T>::unpack(v, g);  // the sums range over the stored (rounded) values
         Elem<T>::unpack(xv[pass], xf);
 #pragma unroll
         for (int j = 0; j < V; ++j) {
-          const bool on = decltype(masked)::value ? ((zb[pass] >> j) & 1u) != 0 : bn_affine(xf[j], scale[j], bias[j]) > 0.f;
-          const float gm = on ? g[j] : 0.f;
+          const float gm = decltype(masked)::value || bn_affine(xf[j], scale[j], bias[j]) > 0.f ? g[j] : 0.f;
           s1[j] += gm;
           s2[j] = fmaf(gm, fmaf(xf[j], rs[j], nmr[j]), s2[j]);
         }
       }
     };
+    auto form = [&](auto masked, auto added) __attribute__((always_inline)) {
+      if (m0 + BM <= Mc && n0 + BN <= a.Ncols) rows(masked, added, std::true_type{});
+      else rows(masked, added, std::false_type{});
+    };
     if (a.bn_zmask) {
-      if (a.addend) rows(std::true_type{}, std::true_type{});
-      else rows(std::true_type{}, std::false_type{});
+      if (a.addend) form(std::true_type{}, std::true_type{});
+      else form(std::true_type{}, std::false_type{});
     } else {
-      if (a.addend) rows(std::false_type{}, std::true_type{});
-      else rows(std::false_type{}, std::false_type{});
+      if (a.addend) form(std::false_type{}, std::true_type{});
+      else form(std::false_type{}, std::false_type{});
     }
   }
   // The per-thread sums of a column meet through LDS: [row group][plane][column], over the tile buffer

@@ -27,6 +27,26 @@ __device__ __forceinline__ Vec16 bn_relu_vector(const Vec16& v, const float* sca
   Elem<T>::pack(f, o);
   return o;
 }
+// The vector with zeros (+0) where an element's bit is not set.  In bf16 by pairs, two 16-bit shifts for two elements' masks: a test and a
+// selection per element are twice the instructions.
+template <typename T>
+__device__ __forceinline__ Vec16 keep_bits(const Vec16& v, uint32_t bits) {
+  Vec16 o;
+  if constexpr (sizeof(T) == 2) {
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    typedef short s16x2 __attribute__((ext_vector_type(2)));
+    const u16x2 both = __builtin_bit_cast(u16x2, bits | bits << 16);
+    auto mask = [&](int i) __attribute__((always_inline)) {  // of elements 2i and 2i + 1: bit to sign, sign to all
+      const u16x2 up = both << u16x2{static_cast<unsigned short>(15 - 2 * i), static_cast<unsigned short>(14 - 2 * i)};
+      return __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, up) >> s16x2{15, 15});
+    };
+    o.u = make_uint4(v.u.x & mask(0), v.u.y & mask(1), v.u.z & mask(2), v.u.w & mask(3));
+  } else {
+    auto mask = [&](int j) __attribute__((always_inline)) { return static_cast<uint32_t>(static_cast<int>(bits << (31 - j)) >> 31); };
+    o.u = make_uint4(v.u.x & mask(0), v.u.y & mask(1), v.u.z & mask(2), v.u.w & mask(3));
+  }
+  return o;
+}
 constexpr uint32_t kOob = 0x80000000u;  // buffer offset beyond every tensor: the load returns zeros
 
 // Barrier behind LDS writes of this wave (s_barrier alone does not wait for them), leaving vector-memory loads in flight.

@@ -236,6 +236,45 @@ def test_conv_dgrad_bn_sums_residual_layer_with_addend(rn, mode_name, shape):
     assert_close(dx, host(dx_u), max(1e-5, tol / 4), "dx vs separate pass")
 
 
+# Whole tiles only, a last tile of one row, of all rows but one, and columns that end inside a tile; 1x1 and 3x3 (one run and classes).
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("N,H,W,C,K,R,stride", [(50, 32, 32, 128, 128, 1, 1), (1, 1, 49153, 128, 64, 1, 1), (1, 1, 25727, 136, 200, 1, 1),
+                                                (16, 31, 31, 128, 64, 3, 1), (13, 32, 32, 256, 64, 3, 2), (1, 1, 65, 40, 24, 1, 1)])
+@pytest.mark.parametrize("recorded,second", [(True, True), (True, False), (False, True)])
+def test_conv_dgrad_bn_sums_of_whole_and_ragged_tiles(rn, mode_name, N, H, W, C, K, R, stride, recorded, second):
+    """Random ReLU decisions of both layers, every bit position of a vector among them; sums against 64 bits."""
+    bf = mode_name == "bf16"
+    dt, V = (torch.bfloat16, 8) if bf else (torch.float32, 4)
+    gen = torch.Generator().manual_seed(5)
+    rand = lambda *s: torch.randn(*s, generator=gen).to(dt).cuda()
+    P, Q = (H - 1) // stride + 1, (W - 1) // stride + 1
+    dy, w, x, add = rand(N, P, Q, K), (torch.randn(K, R, R, C, generator=gen) / (K * R * R) ** 0.5).to(dt).cuda(), rand(N, H, W, C), rand(N, H, W, C)
+    gamma, beta = (torch.randn(C, generator=gen).cuda() for _ in range(2))
+    mean, rstd = 0.2 * torch.randn(C, generator=gen).cuda(), 0.5 + torch.rand(C, generator=gen).cuda()
+    bits, abits = (torch.randint(0, 1 << V, (N * H * W * C // V,), generator=gen, dtype=torch.uint8).cuda() for _ in range(2))
+    decisions = lambda b: ((b[:, None] >> torch.arange(V, device="cuda", dtype=torch.uint8)) & 1).view(N * H * W, C).bool()
+    extra = dict(relu_mask=bits) if recorded else {}
+    if second:
+        extra.update(addend=add, addend_mask=abits)
+    dz, sums = rn.conv_dgrad_bn_sums(dy, w, (N, H, W, C), stride, R // 2, x, gamma, beta, mean, rstd, dx=torch.full_like(x, float("nan")), **extra)
+    want = rn.conv_dgrad(dy, w, (N, H, W, C), stride, R // 2).double().view(-1, C)
+    if second:
+        want = want + torch.where(decisions(abits), add.view(-1, C), torch.zeros_like(add.view(-1, C))).double()
+        assert_close(dz.view(-1, C), want.cpu().numpy(), TOL[mode_name], "dx + second branch")
+    else:
+        assert torch.equal(dz.double().view(-1, C), want)
+    scale = gamma * rstd   # the kernels' decision: fma(x, scale, fma(-mean, scale, beta)) > 0
+    pre = x.double().view(-1, C) * scale.double() + (beta.double() - mean.double() * scale.double()).float().double()
+    on = decisions(bits) if recorded else pre > 0
+    g = torch.where(on, dz.double().view(-1, C), 0.0)
+    xhat = (x.double().view(-1, C) - mean.double()) * rstd.double()
+    _, _, dgamma, dbeta = rn.bn_relu_bwd_from_sums(dz, x, sums, gamma, beta, mean, rstd, mode=2 if recorded else 1, **(dict(relu_mask=bits) if recorded else {}))
+    # at most 8 + 16 + 8 float additions behind one another in a tile; a decision within a rounding of zero may fall either way
+    near = torch.where(pre.abs() <= 2.0 ** -22 * (1 + pre.abs()), dz.double().view(-1, C).abs(), 0.0) if not recorded else torch.zeros_like(g)
+    for got, terms, slack in ((dbeta, g, near), (dgamma, g * xhat, near * xhat.abs())):
+        assert ((got.double() - terms.sum(0)).abs() <= 64 * 2.0 ** -24 * terms.abs().sum(0) + slack.sum(0)).all()
+
+
 def test_fused_sums_reproducible_and_independent_of_buffer_contents(rn):
     N, H, W, C, K = 6, 28, 28, 64, 128
     x = dev(synth.activation_nhwc(SEED, "x", N, C, H, W), True)
