@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   const OutTensor<T, THROUGH> out(static_cast<T*>(a.out), a.out_through);
   if constexpr (AFF) {
     if (a.addend != nullptr) {
-      auto rows = [&](auto relu) __attribute__((always_inline)) {
+      auto rows = [&](auto relu, auto whole) __attribute__((always_inline)) {
 #pragma unroll
         for (int pass = 0; pass < NPASS; ++pass) {
           const int row = orow + pass * RPP, m = m0 + row;
@@ -1020,11 +1020,18 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
           }
           Vec16 o;
           Elem<T>::pack(t, o);
-          if (m < Mc && col_ok) out.store(static_cast<int64_t>(m) * a.Ncols + n, o);
+          if (decltype(whole)::value || (m < Mc && col_ok)) out.store(static_cast<int64_t>(m) * a.Ncols + n, o);
         }
       };
-      if (a.aff_relu) rows(std::true_type{});
-      else rows(std::false_type{});
+      // (a tile without rows or columns past the last stores without a test per row, which kept the LDS reads of a row behind the store of the
+      // one before: evaluation at batch 256 4380 -> 4260 us; not worth a copy of the stage without a residual, 4260 -> 4253)
+      const bool whole = m0 + BM <= Mc && n0 + BN <= a.Ncols;
+      if (a.aff_relu) {
+        if (whole) rows(std::true_type{}, std::true_type{});
+        else rows(std::true_type{}, std::false_type{});
+      } else {
+        rows(std::false_type{}, std::false_type{});
+      }
       return;
     }
   }
