@@ -1091,6 +1091,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
 #pragma unroll
       for (int pass = 0; pass < NPASS; ++pass) {
         const int row = orow + pass * RPP;
+        if (!decltype(whole)::value && !(m0 + row < Mc && col_ok)) continue;  // (its operands are another pixel's: not even zero times them)
         Vec16 v;
         float g[V], xf[V];
         if constexpr (decltype(added)::value) {
@@ -1104,12 +1105,8 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         } else {
           v.u = *reinterpret_cast<const uint4*>(smem + row * CP + op * 16);
         }
-        if (decltype(whole)::value || (m0 + row < Mc && col_ok)) {
-          const int pix = classes ? pixel(row) : m0 + row;
-          out.store(static_cast<int64_t>(pix) * a.Ncols + n, v);
-        } else {
-          v.u = make_uint4(0, 0, 0, 0);  // (a row past the last adds zeros)
-        }
+        const int pix = classes ? pixel(row) : m0 + row;
+        out.store(static_cast<int64_t>(pix) * a.Ncols + n, v);
         if constexpr (decltype(masked)::value) v = keep_bits<T>(v, zb[pass]);
         Elem<T>::unpack(v, g);  // the sums range over the stored (rounded) values
         Elem<T>::unpack(xv[pass], xf);

@@ -275,6 +275,38 @@ def test_conv_dgrad_bn_sums_of_whole_and_ragged_tiles(rn, mode_name, N, H, W, C,
         assert ((got.double() - terms.sum(0)).abs() <= 64 * 2.0 ** -24 * terms.abs().sum(0) + slack.sum(0)).all()
 
 
+# A last tile with rows past the last, in one run of pixels (64x64, K split over the waves, 128x128 tiles), in classes and in 3x3 / stride 1 layers.
+@pytest.mark.parametrize("mode_name", ["f32", "bf16"])
+@pytest.mark.parametrize("N,H,W,C,K,R,stride", [(1, 1, 65, 40, 24, 1, 1), (1, 5, 13, 64, 512, 1, 1), (1, 1, 24577, 136, 128, 1, 1), (3, 15, 15, 40, 24, 3, 2),
+                                                (3, 13, 13, 40, 24, 3, 1)])
+@pytest.mark.parametrize("recorded,second", [(True, True), (True, False), (False, True), (False, False)])
+def test_an_infinity_in_a_ragged_tile_counts_once(rn, mode_name, N, H, W, C, K, R, stride, recorded, second):
+    """An infinite input of the BN layer under an open ReLU makes its channel's dgamma infinite, with the sign of its gradient, as in a whole tile;
+    rows past the last, which read a pixel of the image, do not add zero times it (not a number)."""
+    bf = mode_name == "bf16"
+    dt, V = (torch.bfloat16, 8) if bf else (torch.float32, 4)
+    gen = torch.Generator().manual_seed(9)
+    rand = lambda *s: torch.randn(*s, generator=gen).to(dt).cuda()
+    P, Q = (H - 1) // stride + 1, (W - 1) // stride + 1
+    dy, w, x = rand(N, P, Q, K), (torch.randn(K, R, R, C, generator=gen) / (K * R * R) ** 0.5).to(dt).cuda(), rand(N, H, W, C)
+    hit = [(0, 0), (N * H * W - 1, C - 1), (N * H * W - 1, 3)]     # (pixel, channel): the pixels that rows past the last read
+    for p, c in hit:
+        x.view(-1, C)[p, c] = float("inf")
+    gamma, beta, mean, rstd = torch.ones(C).cuda(), torch.zeros(C).cuda(), torch.zeros(C).cuda(), torch.ones(C).cuda()
+    extra = dict(relu_mask=torch.full((N * H * W * C // V,), (1 << V) - 1, dtype=torch.uint8, device="cuda")) if recorded else {}
+    if second:
+        extra["addend"] = rand(N, H, W, C)
+    dz, sums = rn.conv_dgrad_bn_sums(dy, w, (N, H, W, C), stride, R // 2, x, gamma, beta, mean, rstd, **extra)
+    _, _, dgamma, dbeta = rn.bn_relu_bwd_from_sums(dz, x, sums, gamma, beta, mean, rstd, mode=2 if recorded else 1,
+                                                   **(dict(relu_mask=extra["relu_mask"]) if recorded else {}))
+    g = dz.double().view(-1, C)
+    for p, c in hit:
+        assert float(g[p, c]) != 0.0 and float(dgamma[c]) == float("inf") * (1 if float(g[p, c]) > 0 else -1), (p, c, float(dgamma[c]))
+    others = torch.ones(C, dtype=torch.bool, device="cuda")
+    others[[c for _, c in hit]] = False
+    assert torch.isfinite(dgamma[others]).all() and torch.isfinite(dbeta).all()
+
+
 def test_fused_sums_reproducible_and_independent_of_buffer_contents(rn):
     N, H, W, C, K = 6, 28, 28, 64, 128
     x = dev(synth.activation_nhwc(SEED, "x", N, C, H, W), True)
