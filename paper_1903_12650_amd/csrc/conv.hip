@@ -330,19 +330,24 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   // here, in front of everything the main loop loads (the hand-placed load waits count in order, and these are the oldest), so
   // that it is there when the last product is: workgroups of an earlier round are not enough to cover the 2 us these loads take from memory.
   // Step at batch 12 2395 -> 2375 us, 40 4161 -> 4134, 64 5852 -> 5809 (all against the 128x128 tile alone, which had given 4271 -> 4190 and at
-  // batch 256 19024 -> 18840).  Not where the registers leave a compute unit a workgroup less: the paired 128x128 tiles (three data gradients at
-  // 28x28, batch 256 250 -> 325 us) and, in float, tiles of more than eight rows a thread.
+  // batch 256 19024 -> 18840).  Not the paired 128x128 tiles (three data gradients at 28x28, batch 256 250 -> 325 us) and tiles of more than eight
+  // rows a thread (float, 128 columns or 256 rows), whose registers would leave a compute unit a workgroup less.  These request the operands in front of
+  // the rows that use them, eight rows at a time: with all sixteen at once they needed more than 256 registers, one workgroup per compute unit (22
+  // float data gradients at batch 24, with sums / with a second branch 2895 / 3050 -> 2820 / 2975 us; 128 <- 128 3x3 / 2 at 56x56 120 -> 92, 256 <- 64 at
+  // 56x56 without sums 37 -> 32).
   constexpr int PPR = BN * sizeof(T) / 16;  // 16-byte pieces per output row
   constexpr int RPP = NT / PPR;             // rows per pass
   constexpr int NPASS = BM / RPP;
   constexpr bool EARLY = KS || AFF || (!PAIRED && NPASS <= 8);
+  constexpr int GROUP = EARLY ? NPASS : std::min(NPASS, 8);  // rows whose operands are requested together
+  static_assert(NPASS % GROUP == 0, "whole groups of rows");
   const int op = tid % PPR, orow = tid / PPR;
   const int n = n0 + op * V;
   const bool col_ok = n < a.Ncols;
   Vec16 xv[DG ? NPASS : 1], av[DG || AFF ? NPASS : 1];
   uint32_t zb[DG ? NPASS : 1], ab[DG ? NPASS : 1];
   auto pixel = [&](int row) __attribute__((always_inline)) { return pix_s[row] & ((1 << 29) - 1); };
-  auto load_output_operands = [&]() __attribute__((always_inline)) {
+  auto load_output_operands = [&](int first) __attribute__((always_inline)) {
     if (AFF ? a.addend == nullptr : a.partial == nullptr) return;
     const T* add = static_cast<const T*>(a.addend);
     const int nc = col_ok ? n : 0;
@@ -351,28 +356,29 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       return classes ? pixel(row) : min(m0 + row, a.M - 1);  // rows past the last read a valid pixel
     };
     // (one loop per operand: a test of a pointer per row is a branch per row, and no load passes a branch; byte offsets are 31-bit)
+    const int last = first + GROUP;
     uint32_t at[NPASS];
 #pragma unroll
-    for (int pass = 0; pass < NPASS; ++pass) at[pass] = static_cast<uint32_t>(pixel_of(pass)) * static_cast<uint32_t>(a.Ncols) + nc;
+    for (int pass = first; pass < last; ++pass) at[pass] = static_cast<uint32_t>(pixel_of(pass)) * static_cast<uint32_t>(a.Ncols) + nc;
     if constexpr (DG) {
 #pragma unroll
-      for (int pass = 0; pass < NPASS; ++pass) xv[pass] = load16(static_cast<const T*>(a.bn_x) + at[pass]);
+      for (int pass = first; pass < last; ++pass) xv[pass] = load16(static_cast<const T*>(a.bn_x) + at[pass]);
       if (a.bn_zmask) {
 #pragma unroll
-        for (int pass = 0; pass < NPASS; ++pass) zb[pass] = a.bn_zmask[at[pass] / V];
+        for (int pass = first; pass < last; ++pass) zb[pass] = a.bn_zmask[at[pass] / V];
       }
       if (a.addend_mask) {
 #pragma unroll
-        for (int pass = 0; pass < NPASS; ++pass) ab[pass] = a.addend_mask[at[pass] / V];
+        for (int pass = first; pass < last; ++pass) ab[pass] = a.addend_mask[at[pass] / V];
       } else {
 #pragma unroll
-        for (int pass = 0; pass < NPASS; ++pass) ab[pass] = 0xffu;
+        for (int pass = first; pass < last; ++pass) ab[pass] = 0xffu;
       }
     }
     if constexpr (DG && LIN) {
       if (add && a.addend_even) {
 #pragma unroll
-        for (int pass = 0; pass < NPASS; ++pass) {
+        for (int pass = first; pass < last; ++pass) {
           const int px = pixel_of(pass);
           const uint32_t t = fdiv(static_cast<uint32_t>(px), a.div_w[0]), w = static_cast<uint32_t>(px) - t * a.Q;
           const uint32_t img = fdiv(t, a.div_h[0]), h = t - img * a.P;
@@ -385,12 +391,12 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     }
     if (add) {
 #pragma unroll
-      for (int pass = 0; pass < NPASS; ++pass) av[pass] = load16_stream(add + at[pass]);  // (its last reader)
+      for (int pass = first; pass < last; ++pass) av[pass] = load16_stream(add + at[pass]);  // (its last reader)
     }
   };
   if constexpr ((DG || AFF) && EARLY) {
     if (classes) __syncthreads();  // (pix_s)
-    load_output_operands();
+    load_output_operands(0);
   }
   if (DG && !LIN && !HALO && a.fill) {  // (stores in front of the loads only make the hand-placed waits stricter)
     __syncthreads();
@@ -1078,7 +1084,6 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       }
     }
   } else {
-    if constexpr (!EARLY) load_output_operands();
     float scale[V], bias[V], rs[V], nmr[V];
 #pragma unroll
     for (int j = 0; j < V; ++j) {
@@ -1090,6 +1095,10 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     auto rows = [&](auto masked, auto added, auto whole) __attribute__((always_inline)) {
 #pragma unroll
       for (int pass = 0; pass < NPASS; ++pass) {
+        if (!EARLY && pass % GROUP == 0) {
+          if (pass > 0) __builtin_amdgcn_sched_barrier(0);  // (the scheduler would request a group in front of the one before, and hold both)
+          load_output_operands(pass);
+        }
         const int row = orow + pass * RPP;
         if (!decltype(whole)::value && !(m0 + row < Mc && col_ok)) continue;  // (its operands are another pixel's: not even zero times them)
         Vec16 v;

@@ -1,0 +1,101 @@
+"""The registers of the built convolution kernels, read from the library's own code objects (no GPU).
+
+A compute unit's four SIMDs have 512 vector registers per lane each, ordinary and accumulation registers together: a kernel of
+at most 256 leaves a SIMD two waves, of at most 168 three.  How many workgroups share a compute unit is what the tile rules count on, and
+nothing else would show when an edit or a compiler takes a kernel over such an edge."""
+import os
+import re
+import struct
+
+import pytest
+
+LIB = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1903_12650_amd", "librn50_hip.so")
+
+
+def _section(elf, name):
+    start, = struct.unpack_from("<Q", elf, 0x28)
+    size, count, strings = struct.unpack_from("<HHH", elf, 0x3A)
+    header = lambda i: struct.unpack_from("<IIQQQQ", elf, start + i * size)
+    names = header(strings)[4]
+    for i in range(count):
+        h = header(i)
+        at = names + h[0]
+        if elf[at:elf.index(b"\0", at)].decode() == name:
+            return elf[h[4]:h[4] + h[5]]
+    raise AssertionError("no section " + name)
+
+
+def _decode(b, p):
+    """One msgpack value (the kinds that kernel metadata holds) at b[p:], and where the next one starts."""
+    t = b[p]
+    p += 1
+    if t <= 0x7F or t >= 0xE0:
+        return (t if t <= 0x7F else t - 256), p
+    if t in (0xC0, 0xC2, 0xC3):
+        return {0xC0: None, 0xC2: False, 0xC3: True}[t], p
+    if 0xCC <= t <= 0xCF:
+        n = 1 << (t - 0xCC)
+        return int.from_bytes(b[p:p + n], "big"), p + n
+    if 0xD0 <= t <= 0xD3:
+        n = 1 << (t - 0xD0)
+        return int.from_bytes(b[p:p + n], "big", signed=True), p + n
+    kind, n = {0x8: ("map", t & 15), 0x9: ("list", t & 15), 0xA: ("str", t & 31), 0xB: ("str", t & 31)}.get(t >> 4, (None, 0))
+    if kind is None:
+        kind, width = {0xD9: ("str", 1), 0xDA: ("str", 2), 0xDB: ("str", 4), 0xDC: ("list", 2), 0xDD: ("list", 4), 0xDE: ("map", 2), 0xDF: ("map", 4)}[t]
+        n, p = int.from_bytes(b[p:p + width], "big"), p + width
+    if kind == "str":
+        return b[p:p + n].decode(), p + n
+    out = []
+    for _ in range(n * (2 if kind == "map" else 1)):
+        v, p = _decode(b, p)
+        out.append(v)
+    return (dict(zip(out[::2], out[1::2])) if kind == "map" else out), p
+
+
+def _kernels():
+    """The metadata of every kernel: one code object per source file, bundled in a section of the library."""
+    bundles, magic, at, found = _section(open(LIB, "rb").read(), ".hip_fatbin"), b"__CLANG_OFFLOAD_BUNDLE__", 0, []
+    while (at := bundles.find(magic, at)) >= 0:
+        count, = struct.unpack_from("<Q", bundles, at + len(magic))
+        p = at + len(magic) + 8
+        for _ in range(count):
+            offset, size, length = struct.unpack_from("<QQQ", bundles, p)
+            target = bundles[p + 24:p + 24 + length]
+            p += 24 + length
+            if b"gfx950" not in target:
+                continue
+            note, q = _section(bundles[at + offset:at + offset + size], ".note"), 0
+            while q < len(note):
+                name, desc, kind = struct.unpack_from("<III", note, q)
+                q += 12 + (name + 3 & ~3)
+                if kind == 32:
+                    found += _decode(note, q)[0]["amdhsa.kernels"]
+                q += desc + 3 & ~3
+        at += len(magic)
+    return found
+
+
+IGEMM = re.compile(r"igemm_kernelI([ft])" + "Li([0-9]+)E" * 5 + "Lb([01])ELb([01])ELi([0-9])ELb([01])E")
+
+
+def _convolutions():
+    """(element type, rows, columns, waves along rows, along columns, mode, linear, input BN, taps, written through) -> metadata."""
+    out = {}
+    for k in _kernels():
+        m = IGEMM.search(k[".name"])
+        if m:
+            out[("f32" if m.group(1) == "f" else "bf16",) + tuple(int(g) for g in m.groups()[1:])] = k
+    assert len(out) >= 200, len(out)
+    return out
+
+
+@pytest.fixture(scope="module")
+def convolutions():
+    return _convolutions()
+
+
+def test_every_tile_leaves_a_simd_two_waves_and_keeps_its_values_in_registers(convolutions):
+    """(.vgpr_count counts accumulation registers too)"""
+    bad = {key: (k[".vgpr_count"], k[".agpr_count"], k[".vgpr_spill_count"]) for key, k in convolutions.items()
+           if k[".vgpr_count"] > 256 or k[".agpr_count"] or k[".vgpr_spill_count"]}
+    assert not bad, bad
