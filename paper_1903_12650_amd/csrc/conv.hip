@@ -73,7 +73,7 @@ struct IgemmArgs {
   // the row tiles' pixel grid -- [1] for the odd parity class of a stride-2 data gradient.
   int mtiles;       // row tiles (grid = mtiles * ntn)
   FastDiv div_ntn, div_w[2], div_h[2];
-  int mode;         // host side only: selects the MODE template argument
+  int mode;         // host side only: forward, data gradient, evaluation; selects the MODE template argument with `partial`
   // Optional batch-norm sums over the rows of each output tile, taken from the rounded values that are
   // stored (null: none), one row per tile row (bn_sums_at).  Forward: float sums of the values and of their squares about
   // the tile's first row.  Data gradient: sum(g), sum(g * xhat) with g the output
@@ -115,7 +115,10 @@ struct IgemmArgs {
 };
 
 // MODE 0: forward gather  ih = p*stride - pad + r.
-// MODE 1: data-gradient gather  ih = (p + pad - r)/stride when divisible (stride 1 or 2).  With stride 2
+// MODE 1: data gradient with the batch-norm sums of the layer below.  MODE 3: without, a kernel of its own: in one for both, launches without sums
+// held the registers of the sums' operands, a workgroup less per compute unit (bf16 128x128 224 registers, alone 128: 256 <- 64 at 56x56, batch 256
+// 113 -> 92 us; 22 shapes, operands from memory, batch 256 3512 -> 3428 us, 40 709 -> 702; float at batch 24 2677 -> 2600).
+// Their gather is  ih = (p + pad - r)/stride when divisible (stride 1 or 2).  With stride 2
 // an output pixel only receives the taps r = (p + pad) mod 2, s = (q + pad) mod 2 (mod 2), so the pixels
 // are processed in four parity classes (p mod 2, q mod 2): a row tile holds pixels of one class and loops
 // over that class's taps only (a quarter of the taps on average, none for three classes of a 1x1 filter:
@@ -190,7 +193,7 @@ constexpr int igemm_ks_ring() {
 template <typename T, bool KS>
 constexpr int igemm_row_ahead() { return KS && sizeof(T) == 2 ? 3 : 1; }
 //
-// Data gradient (MODE 1): the B tile of a chunk is BK output channels (K) x BN input channels of the weights as they lie
+// Data gradient (MODE 1 and 3): the B tile of a chunk is BK output channels (K) x BN input channels of the weights as they lie
 // in memory, filled and read like wgrad_kernel's tiles (transposing reads in bf16).  A transposing read delivers fewer
 // bytes per clock than a plain one, but the tile is the smaller half of the fragment traffic and was never what bounds
 // these layers: per layer at batch 40 7.5 to 33 us against 8.9 to 34 with a transposed copy (whole network 794 against
@@ -221,7 +224,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   static_assert(!BNIN || (LIN && MODE == 0), "the input-side BN is compiled for the linear forward kernel only");
   constexpr bool HALO = TAPS > 0;
   static_assert(!HALO || (!LIN && !BNIN), "the halo main loop is a kernel of its own");
-  constexpr bool DG = MODE == 1, FWD = !DG, AFF = MODE == 2;
+  constexpr bool DG = MODE == 1 || MODE == 3, FWD = !DG, AFF = MODE == 2, DGS = MODE == 1, DGP = MODE == 3;
   constexpr bool KS = WM * WN == 1;
   constexpr bool OWN = KS && !HALO;             // every wave has chunks and a ring of its own (halo: they share run and weights)
   constexpr int NW = KS ? 4 : WM * WN, NT = 64 * NW;
@@ -268,11 +271,11 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   if constexpr (DEEP || PAIRED) {
     prm_s = reinterpret_cast<float*>(smem + igemm_out_tile<BM, BN>());
   } else {
-    __shared__ __align__(16) float prm_static[DG ? 4 * BN : (AFF ? 2 * BN : 4)];
+    __shared__ __align__(16) float prm_static[DGS ? 4 * BN : (AFF ? 2 * BN : 4)];
     prm_s = prm_static;
   }
   float pg = 0.f, pb = 0.f, pm = 0.f, pr = 0.f;
-  if ((AFF || (DG && a.partial != nullptr)) && tid < BN) {
+  if ((AFF || DGS) && tid < BN) {
     const int c = min(n0 + tid, a.Ncols - 1);
     pg = a.bn_gamma[c]; pb = a.bn_beta[c]; pm = a.bn_mean[c]; pr = AFF ? a.aff_var[c] : a.bn_rstd[c];
   }
@@ -287,8 +290,9 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     // us, float at batch 8 41.0 -> 33.9 and 42.6 -> 35.7, batch 256 157 -> 148 and 108 -> 107 (turned by one class each time
     // 22.6 and 18.6, 34.4 and 35.9, 144 and 109).
     const int turn = (mt >> 2) * a.ntn >> 3;
-    const int cls = a.fill ? 0 : (mt & 3) ^ ((turn & 1) * 3) ^ ((turn >> 1) & 1);
-    m0 = (a.fill ? mt : mt >> 2) * BM;
+    const bool fill = DGP && a.fill;
+    const int cls = fill ? 0 : (mt & 3) ^ ((turn & 1) * 3) ^ ((turn >> 1) & 1);
+    m0 = (fill ? mt : mt >> 2) * BM;
     ph = cls >> 1; pw = cls & 1;
     Hc = (a.P - ph + 1) >> 1; Wc = (a.Q - pw + 1) >> 1;
     Mc = a.nimg * Hc * Wc;
@@ -333,8 +337,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   // batch 256 19024 -> 18840).  Not the paired 128x128 tiles (three data gradients at 28x28, batch 256 250 -> 325 us) and tiles of more than eight
   // rows a thread (float, 128 columns or 256 rows), whose registers would leave a compute unit a workgroup less.  These request the operands in front of
   // the rows that use them, eight rows at a time: with all sixteen at once they needed more than 256 registers, one workgroup per compute unit (22
-  // float data gradients at batch 24, with sums / with a second branch 2895 / 3050 -> 2820 / 2975 us; 128 <- 128 3x3 / 2 at 56x56 120 -> 92, 256 <- 64 at
-  // 56x56 without sums 37 -> 32).
+  // float data gradients at batch 24, with sums / with a second branch 2895 / 3050 -> 2820 / 2975 us; 128 <- 128 3x3 / 2 at 56x56 120 -> 92).
   constexpr int PPR = BN * sizeof(T) / 16;  // 16-byte pieces per output row
   constexpr int RPP = NT / PPR;             // rows per pass
   constexpr int NPASS = BM / RPP;
@@ -344,11 +347,11 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   const int op = tid % PPR, orow = tid / PPR;
   const int n = n0 + op * V;
   const bool col_ok = n < a.Ncols;
-  Vec16 xv[DG ? NPASS : 1], av[DG || AFF ? NPASS : 1];
-  uint32_t zb[DG ? NPASS : 1], ab[DG ? NPASS : 1];
+  Vec16 xv[DGS ? NPASS : 1], av[DGS || AFF ? NPASS : 1];
+  uint32_t zb[DGS ? NPASS : 1], ab[DGS ? NPASS : 1];
   auto pixel = [&](int row) __attribute__((always_inline)) { return pix_s[row] & ((1 << 29) - 1); };
   auto load_output_operands = [&](int first) __attribute__((always_inline)) {
-    if (AFF ? a.addend == nullptr : a.partial == nullptr) return;
+    if (AFF && a.addend == nullptr) return;
     const T* add = static_cast<const T*>(a.addend);
     const int nc = col_ok ? n : 0;
     auto pixel_of = [&](int pass) __attribute__((always_inline)) {
@@ -360,7 +363,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     uint32_t at[NPASS];
 #pragma unroll
     for (int pass = first; pass < last; ++pass) at[pass] = static_cast<uint32_t>(pixel_of(pass)) * static_cast<uint32_t>(a.Ncols) + nc;
-    if constexpr (DG) {
+    if constexpr (DGS) {
 #pragma unroll
       for (int pass = first; pass < last; ++pass) xv[pass] = load16(static_cast<const T*>(a.bn_x) + at[pass]);
       if (a.bn_zmask) {
@@ -375,7 +378,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         for (int pass = first; pass < last; ++pass) ab[pass] = 0xffu;
       }
     }
-    if constexpr (DG && LIN) {
+    if constexpr (DGS && LIN) {
       if (add && a.addend_even) {
 #pragma unroll
         for (int pass = first; pass < last; ++pass) {
@@ -394,11 +397,11 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       for (int pass = first; pass < last; ++pass) av[pass] = load16_stream(add + at[pass]);  // (its last reader)
     }
   };
-  if constexpr ((DG || AFF) && EARLY) {
+  if constexpr ((DGS || AFF) && EARLY) {
     if (classes) __syncthreads();  // (pix_s)
     load_output_operands(0);
   }
-  if (DG && !LIN && !HALO && a.fill) {  // (stores in front of the loads only make the hand-placed waits stricter)
+  if (DGP && !LIN && !HALO && a.fill) {  // (stores in front of the loads only make the hand-placed waits stricter)
     __syncthreads();
 #pragma unroll
     for (int pass = 0; pass < NPASS; ++pass) {
@@ -966,8 +969,12 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     lds_writes_then_barrier();
   } else if constexpr (KS) {
     __syncthreads();  // the output tile below reuses the exchange buffers
+  } else if constexpr (DGS && EARLY) {
+    // (every load has landed; the wait is for the compiler, which counts stores with loads and would wait for a row's operands behind the store of
+    // the row before: 256 <- 64 at 56x56, batch 40 38 -> 35 us)
+    wait_loads_then_barrier<0>();  // the output tile below reuses the pipeline buffers
   } else {
-    __builtin_amdgcn_s_barrier();  // the output tile below reuses the pipeline buffers
+    __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   }
 
@@ -976,7 +983,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   // What a launch's output stage does is chosen once per workgroup, with a copy of the loops each: tests inside them were two branches per
   // element, 130 a wave and tile in data gradients with sums (with sums at batch 256: 64 <- 64 3x3 at 56x56 113 -> 99 us; 128 <- 128 3x3 at 28x28
   // 93 -> 86).  The forward sums keep their one test per row: with rows past the end added as zeros instead 30 layers at batch 256 1905 -> 1950 us.
-  const bool wide = sizeof(T) == 2 && (AFF || (DG && a.partial != nullptr)) && a.addend != nullptr;
+  const bool wide = sizeof(T) == 2 && (AFF || DGS) && a.addend != nullptr;
   auto stage_tile = [&](auto wide_tile, auto relu) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -1001,9 +1008,9 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       }
   };
   if (AFF && a.aff_relu && !a.addend) stage_tile(std::false_type{}, std::bool_constant<AFF>{});
-  else if ((AFF || DG) && sizeof(T) == 2 && wide) stage_tile(std::bool_constant<(AFF || DG) && sizeof(T) == 2>{}, std::false_type{});
+  else if ((AFF || DGS) && sizeof(T) == 2 && wide) stage_tile(std::bool_constant<(AFF || DGS) && sizeof(T) == 2>{}, std::false_type{});
   else stage_tile(std::false_type{}, std::false_type{});
-  if (DG && a.partial != nullptr && tid < BN) {
+  if (DGS && tid < BN) {
     float sc, bi;
     bn_coeffs(pg, pb, pm, pr, &sc, &bi);
     prm_s[tid] = sc; prm_s[BN + tid] = bi; prm_s[2 * BN + tid] = pr; prm_s[3 * BN + tid] = -pm * pr;
@@ -1041,7 +1048,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
       return;
     }
   }
-  if (AFF || a.partial == nullptr) {
+  if (AFF || DGP || (MODE == 0 && a.partial == nullptr)) {
 #pragma unroll
     for (int pass = 0; pass < NPASS; ++pass) {
       const int row = orow + pass * RPP;
@@ -1083,7 +1090,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         }
       }
     }
-  } else {
+  } else if constexpr (DGS) {
     float scale[V], bias[V], rs[V], nmr[V];
 #pragma unroll
     for (int j = 0; j < V; ++j) {
@@ -1092,6 +1099,11 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
     }
     // masked: the BN layer's recorded ReLU bits are there; added: a second branch; whole: no row or column of the tile is past the last (a test
     // per row is a branch per row: step at batch 256 18.28 -> 18.20 ms without them; the forward sums gain nothing by it)
+    // (opaque: where a launch may have no bits the compiler would move what is made of them up to their loads, in front of the main loop, and wait there)
+    auto opaque = [](uint32_t bits) __attribute__((always_inline)) {
+      if constexpr (EARLY) asm("" : "+v"(bits));
+      return bits;
+    };
     auto rows = [&](auto masked, auto added, auto whole) __attribute__((always_inline)) {
 #pragma unroll
       for (int pass = 0; pass < NPASS; ++pass) {
@@ -1105,7 +1117,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         float g[V], xf[V];
         if constexpr (decltype(added)::value) {
           float ad[V];
-          Elem<T>::unpack(keep_bits<T>(av[pass], ab[pass]), ad);
+          Elem<T>::unpack(keep_bits<T>(av[pass], opaque(ab[pass])), ad);
           // (in bf16 the tile lies in LDS in float)
           load_floats<V>(reinterpret_cast<const float*>(smem + row * (sizeof(T) == 2 ? CPW : CP)) + op * V, g);
 #pragma unroll
@@ -1116,7 +1128,7 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
         }
         const int pix = classes ? pixel(row) : m0 + row;
         out.store(static_cast<int64_t>(pix) * a.Ncols + n, v);
-        if constexpr (decltype(masked)::value) v = keep_bits<T>(v, zb[pass]);
+        if constexpr (decltype(masked)::value) v = keep_bits<T>(v, opaque(zb[pass]));
         Elem<T>::unpack(v, g);  // the sums range over the stored (rounded) values
         Elem<T>::unpack(xv[pass], xf);
 #pragma unroll
@@ -1235,7 +1247,7 @@ static void launch_igemm_through(IgemmArgs a, const char* tag, int64_t grid, hip
   // less LDS more workgroups fit a CU (the 1x1 layers with 64 channels, the largest pixel counts of the net, have a single chunk).
   const int chunks = a.R * a.S * a.cpt;
   const int ring = deep ? (chunks >= 3 ? deep_ring : chunks * stage) : lean ? (chunks >= 2 ? lean_ring : stage) : (!KS && chunks < nring ? (chunks < 1 ? 1 : chunks) : nring) * stage;
-  const bool wide = es == 2 && (MODE == 2 || (MODE == 1 && a.partial != nullptr && a.addend != nullptr));
+  const bool wide = es == 2 && (MODE == 2 || (MODE == 1 && a.addend != nullptr));
   const int out_need = std::max({(wide ? igemm_out_tile<BM, BN>() : BM * (BN * es + 16)) + behind, col_sums, exchange});
   int lds = ring > out_need ? ring : out_need;
   if (BNIN) {
@@ -1300,7 +1312,8 @@ template <typename T, int BM, int BN, int WM, int WN, int TAPS>
 static void launch_igemm_halo_mode(const IgemmArgs& a, const char* tag, int64_t grid, int main_lds, hipStream_t s) {
   if (a.mode == 2) launch_igemm_halo<T, BM, BN, WM, WN, 2, TAPS>(a, tag, grid, main_lds, s);
   else if (a.mode == 0) launch_igemm_halo<T, BM, BN, WM, WN, 0, TAPS>(a, tag, grid, main_lds, s);
-  else launch_igemm_halo<T, BM, BN, WM, WN, 1, TAPS>(a, tag, grid, main_lds, s);
+  else if (a.partial) launch_igemm_halo<T, BM, BN, WM, WN, 1, TAPS>(a, tag, grid, main_lds, s);
+  else launch_igemm_halo<T, BM, BN, WM, WN, 3, TAPS>(a, tag, grid, main_lds, s);
 }
 // Tuning builds can force any tile on any layer; the product compiles what the rules below can choose.
 #ifdef RN50_TUNING
@@ -1329,7 +1342,8 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
   }
   if (linear) {
     if constexpr (BM <= 128 || kTuning) {  // (the tiles of 256 rows are igemm_halo_tile's alone)
-      if (a.mode == 1) launch_igemm_mode<T, BM, BN, WM, WN, 1, true>(a, tag, grid, s);
+      if (a.mode == 1 && a.partial) launch_igemm_mode<T, BM, BN, WM, WN, 1, true>(a, tag, grid, s);
+      else if (a.mode == 1) launch_igemm_mode<T, BM, BN, WM, WN, 3, true>(a, tag, grid, s);
       else if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, true>(a, tag, grid, s);
       else if (a.in_gamma) launch_igemm_mode<T, BM, BN, WM, WN, 0, true, true>(a, tag, grid, s);
       else launch_igemm_mode<T, BM, BN, WM, WN, 0, true>(a, tag, grid, s);
@@ -1349,7 +1363,8 @@ static void launch_igemm_cfg(IgemmArgs a, const char* tag, hipStream_t s) {
   if constexpr (BM != 256 || BN != 64 || kTuning) {  // (igemm_halo_tile takes the 256x64 tile where its run fits)
     if (a.mode == 2) launch_igemm_mode<T, BM, BN, WM, WN, 2, false>(a, tag, grid, s);
     else if (a.mode == 0) launch_igemm_mode<T, BM, BN, WM, WN, 0, false>(a, tag, grid, s);
-    else launch_igemm_mode<T, BM, BN, WM, WN, 1, false>(a, tag, grid, s);
+    else if (a.partial) launch_igemm_mode<T, BM, BN, WM, WN, 1, false>(a, tag, grid, s);
+    else launch_igemm_mode<T, BM, BN, WM, WN, 3, false>(a, tag, grid, s);
   }
 }
 
@@ -1378,7 +1393,7 @@ struct TileShape {
 //    217); evaluation with the residual at batch 16 / 40 / 64 / 100 / 256 10.2 -> 11.8 / 24.0 -> 27.0 / 38 -> 45 / 70 -> 64 / 168 -> 153.
 // In float the products take longer than the loads and the tile (68 KB in LDS) leaves two workgroups: 32 -> 256 at batch 64 54 -> 62, from warm
 // caches 38 -> 57.
-enum class TileUse { kForward, kAffine, kGrad, kGradSums, kGradSumsAdd };  // what the output stage does (MODE 0, MODE 2, MODE 1)
+enum class TileUse { kForward, kAffine, kGrad, kGradSums, kGradSumsAdd };  // what the output stage does (MODE 0, 2, 3, 1, 1)
 constexpr int64_t kOneChunkBytes = 128 << 20;
 static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool strided_dgrad, int live, TileUse use, int dtype) {
   const int64_t classes = strided_dgrad ? live : 1;
