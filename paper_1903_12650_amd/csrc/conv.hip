@@ -1236,6 +1236,7 @@ static void launch_igemm_through(IgemmArgs a, const char* tag, int64_t grid, hip
   constexpr bool lean = igemm_lean_b<T, BM, BN, WM, WN, MODE, BNIN, false>();
   constexpr int lean_ring = (BN + 2 * BM) * 128;
   static_assert(!deep || (deep_ring <= 80 * 1024 && out_most <= deep_ring), "two workgroups per compute unit");
+  static_assert(!lean || 3 * std::max({lean_ring, BM * (BN * es + 16), col_sums}) <= 160 * 1024, "three workgroups per compute unit");
   constexpr int nring = KS ? igemm_ks_ring<BM, BN, BNIN>() : igemm_ring<BM, BN, WM * WN>();
   // input-side BN coefficients: two floats per channel, at most 4096 channels (KS: 2048)
   constexpr int kInTabMax = 8 * (KS ? 2048 : 4096);

@@ -110,3 +110,18 @@ def test_data_gradients_without_sums_do_not_hold_the_operands_of_the_sums(convol
             most[key] = max(most.get(key, 0), k[".vgpr_count"])
     assert set(most) == {(64, 64, False), (64, 64, True), (128, 64, False), (128, 128, False)}
     assert most[(64, 64, False)] <= 128 and most[(128, 64, False)] <= 128 and most[(64, 64, True)] <= 168 and most[(128, 128, False)] <= 168, most
+
+
+def test_tiles_whose_lds_is_counted_to_the_byte(convolutions):
+    """128x128 tiles that count on two or three workgroups per compute unit have no static LDS beside what their launch asks for; the bf16 forward one counts on
+    three, so on three waves per SIMD (its two buffers of one operand and one of the other are 48 KB)."""
+    lean = 0
+    for (dt, bm, bn, wm, wn, mode, lin, in_bn, taps, through), k in convolutions.items():
+        if (bm, bn, wm, wn) != (128, 128, 2, 2) or in_bn:
+            continue
+        if taps or mode in (0, 2):
+            assert k[".group_segment_fixed_size"] == 0, (dt, mode, lin, taps)
+        if dt == "bf16" and mode == 0 and not taps:
+            lean += 1
+            assert k[".vgpr_count"] <= 168, (lin, k[".vgpr_count"])
+    assert lean == 2
