@@ -337,19 +337,21 @@ def test_resnet_eval_vs_oracle_after_training_steps(rn, mode_name, cfg):
 
 
 @pytest.mark.parametrize("mode_name", ["f32", "bf16"])
-@pytest.mark.parametrize("N,stem,widths,blocks", [(2, 64, (64, 128, 256, 512), (3, 4, 6, 3)), (40, 64, (64, 128, 256, 512), (3, 4, 6, 3)),
-                                                  (200, 64, (64, 128, 256, 512), (3, 4, 6, 3)), (40, 32, (32, 64, 128, 256), (1, 1, 1, 1))])
-def test_resnet_eval_is_the_chain_of_its_operations(rn, mode_name, N, stem, widths, blocks):
+@pytest.mark.parametrize("N,hw,stem,widths,blocks", [(2, 224, 64, (64, 128, 256, 512), (3, 4, 6, 3)), (40, 224, 64, (64, 128, 256, 512), (3, 4, 6, 3)),
+                                                     (200, 224, 64, (64, 128, 256, 512), (3, 4, 6, 3)), (40, 224, 32, (32, 64, 128, 256), (1, 1, 1, 1)),
+                                                     (46, 264, 64, (64, 128, 256, 512), (1, 2, 1, 1)), (64, 224, 64, (64, 128, 256, 512), (1, 2, 1, 1))])
+def test_resnet_eval_is_the_chain_of_its_operations(rn, mode_name, N, hw, stem, widths, blocks):
     """The evaluation pass applies every batch norm (with the residual) in its convolution's output stage.  ResNet-50 at batches
     whose layers run on every forward tile: the K splits, 64x64, 128x64, 128x128 (a reduction of one chunk of 64 channels: from an output of
-    128 MB on, batch 200), the one-run 3x3 loop by filter rows on 32x64 (float 32x32) and 64x64 tiles, tap by tap on 128x64 and 256x128; a
-    narrow network whose first stage is one chunk of channels in float as well: the 256x64 tile.
+    128 MB on, batch 200), the one-run 3x3 loop by filter rows on 32x64 (float 32x32) and 64x64 tiles, tap by tap on 128x64 and on pairs of 128x128
+    (batch 200); a narrow network whose first stage is one chunk of channels in float as well: the 256x64 tile; networks whose second
+    stage's last 3x3 runs on 256x128 tiles: 196 of them with a ragged last one (images of 33 pixels), and 196 whole ones where pairs would fill no fewer rounds.
     In float the products are those of conv_fwd and the arithmetic that of bn_relu_infer: the same bits.  In bf16 the chain
     multiplies the rounded operands in float and rounds once behind the batch norm, as the output stage does, so only the
     order of the sums differs (and what a value on the other side of a rounding makes of it downstream)."""
     bf = mode_name == "bf16"
     dt = torch.bfloat16 if bf else torch.float32
-    plan = rn.ResnetPlan(N, rn.BF16 if bf else rn.F32, 224, 1000, widths, blocks, stem)
+    plan = rn.ResnetPlan(N, rn.BF16 if bf else rn.F32, hw, 1000, widths, blocks, stem)
     gen = torch.Generator(device="cuda").manual_seed(SEED)
     M = torch.empty(plan.arena_elems, device="cuda")
     rn.resnet_init_params(plan, SEED, M)
@@ -359,7 +361,7 @@ def test_resnet_eval_is_the_chain_of_its_operations(rn, mode_name, N, stem, widt
     for rm, rv in zip(st.running_mean, st.running_var):
         rm.copy_(0.1 * torch.randn(rm.shape, device="cuda", generator=gen))
         rv.copy_(torch.exp(0.2 * torch.randn(rv.shape, device="cuda", generator=gen)))
-    img = torch.randn((N, 224, 224, 3), device="cuda", generator=gen).to(dt)
+    img = torch.randn((N, hw, hw, 3), device="cuda", generator=gen).to(dt)
     lab = torch.zeros(N, dtype=torch.int32, device="cuda")
     logits = torch.empty((N, 1000), device="cuda")
     rn.resnet_eval(plan, st, img, lab, M, Mod, torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda"), logits_out=logits)
