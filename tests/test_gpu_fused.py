@@ -236,10 +236,13 @@ def test_conv_dgrad_bn_sums_residual_layer_with_addend(rn, mode_name, shape):
     assert_close(dx, host(dx_u), max(1e-5, tol / 4), "dx vs separate pass")
 
 
-# Whole tiles only, a last tile of one row, of all rows but one, and columns that end inside a tile; 1x1 and 3x3 (one run and classes).
+# Whole tiles only, a last tile of one row, of all rows but one, and columns that end inside a tile; 1x1 and 3x3 (one run and classes); the large tiles of
+# the 3x3 / stride 1 layers, whole and with ragged rows and columns: pairs of 128x128, 256x128, 256x64.
 @pytest.mark.parametrize("mode_name", ["f32", "bf16"])
 @pytest.mark.parametrize("N,H,W,C,K,R,stride", [(50, 32, 32, 128, 128, 1, 1), (1, 1, 49153, 128, 64, 1, 1), (1, 1, 25727, 136, 200, 1, 1),
-                                                (16, 31, 31, 128, 64, 3, 1), (13, 32, 32, 256, 64, 3, 2), (1, 1, 65, 40, 24, 1, 1)])
+                                                (16, 31, 31, 128, 64, 3, 1), (13, 32, 32, 256, 64, 3, 2), (1, 1, 65, 40, 24, 1, 1),
+                                                (48, 16, 16, 1024, 64, 3, 1), (1, 265, 31, 1000, 72, 3, 1), (8, 32, 32, 1024, 64, 3, 1),
+                                                (1, 257, 32, 1000, 72, 3, 1), (32, 56, 56, 64, 32, 3, 1), (25, 63, 63, 40, 24, 3, 1)])
 @pytest.mark.parametrize("recorded,second", [(True, True), (True, False), (False, True)])
 def test_conv_dgrad_bn_sums_of_whole_and_ragged_tiles(rn, mode_name, N, H, W, C, K, R, stride, recorded, second):
     """Random ReLU decisions of both layers, every bit position of a vector among them; sums against 64 bits."""
@@ -269,7 +272,9 @@ def test_conv_dgrad_bn_sums_of_whole_and_ragged_tiles(rn, mode_name, N, H, W, C,
     g = torch.where(on, dz.double().view(-1, C), 0.0)
     xhat = (x.double().view(-1, C) - mean.double()) * rstd.double()
     _, _, dgamma, dbeta = rn.bn_relu_bwd_from_sums(dz, x, sums, gamma, beta, mean, rstd, mode=2 if recorded else 1, **(dict(relu_mask=bits) if recorded else {}))
-    # at most 8 + 16 + 8 float additions behind one another in a tile; a decision within a rounding of zero may fall either way
+    # A tile's float sum adds at most 40 terms one behind another: the rows of a thread (tile rows / row groups), then the row groups of a column (8 + 32 at
+    # bf16 tiles of 256 rows, 2 + 32 at 64x64, 16 + 16 in float).  Beside them the normalised value's two roundings, of at most 1 + |mean * rstd| / |xhat|
+    # units each: 64 in all.  Without recorded bits a decision within a rounding of zero may fall either way.
     near = torch.where(pre.abs() <= 2.0 ** -22 * (1 + pre.abs()), dz.double().view(-1, C).abs(), 0.0) if not recorded else torch.zeros_like(g)
     for got, terms, slack in ((dbeta, g, near), (dgamma, g * xhat, near * xhat.abs())):
         assert ((got.double() - terms.sum(0)).abs() <= 64 * 2.0 ** -24 * terms.abs().sum(0) + slack.sum(0)).all()
