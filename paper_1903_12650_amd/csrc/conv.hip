@@ -147,11 +147,11 @@ template <int BM, int BN, int NW>
 constexpr int igemm_ring() {
   return (NW == 4 && 3 * (BM + BN) * 128 > 80 * 1024) ? 2 : 3;
 }
-// DEEP: the 128x128 tile of the forward modes, whose three whole buffers would leave a compute unit one workgroup, has three for A and two
-// for B: 80 KB, two workgroups to the byte (so these kernels have no static LDS; MODE 2's coefficients lie behind the output tile).  A
-// comes from memory, B, the weights, from the L2: with both one chunk ahead a chunk took as long as A's loads, 1.2 us.  23 shapes
-// forward at batch 256 1817 -> 1751 us, 100 869 -> 846, 40 392 -> 390; evaluation at batch 256 4.40 -> 4.28 ms, 64 1.331 -> 1.297.  Not the
-// data gradients: beside the weight gradients they leave them no LDS (step at batch 256 19.14 -> 19.18 ms), alone 1807 -> 1804 us.
+// DEEP: the 128x128 tile of the evaluation pass and of the float forward pass, whose three whole buffers would leave a compute unit one workgroup, has
+// three for A and two for B: 80 KB, two workgroups to the byte (so these kernels have no static LDS; MODE 2's coefficients lie behind the output
+// tile).  A comes from memory, B, the weights, from the L2: with both one chunk ahead a chunk took as long as A's loads, 1.2 us.  Evaluation at batch
+// 256 4.40 -> 4.28 ms, 64 1.331 -> 1.297; float forward, 23 shapes at batch 24 1308 -> 1287 us.  Not the data gradients: beside the weight gradients they
+// leave them no LDS (step at batch 256 19.14 -> 19.18 ms when it was tried).
 template <typename T, int BM, int BN, int WM, int WN, int MODE, bool BNIN, bool HALO>
 constexpr bool igemm_deep_a() {
   return BM == 128 && BN == 128 && WM * WN == 4 && (MODE == 2 || (MODE == 0 && sizeof(T) == 4)) && !BNIN && !HALO;
@@ -168,7 +168,7 @@ constexpr bool igemm_lean_b() {
   return BM == 128 && BN == 128 && WM * WN == 4 && MODE == 0 && sizeof(T) == 2 && !BNIN && !HALO;
 }
 // PAIRED: the 128x128 tile's halo loop.  Its two runs and two weight tiles (three everywhere else) are at most 80 KB up to images 31 wide, so
-// two workgroups share a compute unit (no static LDS; the output stage's coefficients lie behind its tile).  A step takes a pair as long as
+// two workgroups share a compute unit (no static LDS; the output stage's coefficients lie behind its tile; at most 256 registers, in both types).  A step takes a pair as long as
 // the 256x128 tile's one workgroup (0.75 to 0.85 us, 0.46 of it products), but a rest of the grid that gives each unit a single workgroup
 // takes little more than half a round, where the taller tile takes a whole one, and the two cover each other's prologue and output stage
 // (5 us of a round): see igemm_halo_tile.
@@ -207,7 +207,8 @@ constexpr int igemm_row_ahead() { return KS && sizeof(T) == 2 ? 3 : 1; }
 // further down in it.  Taps that fall off the image (or into the neighbouring image of the run) are zeroed in
 // the fragment registers, by a per-lane bit mask computed once.  The weights go through a ring of three
 // BN-row tiles, two taps ahead; the next chunk's run is loaded one pass per tap while the
-// current one is in use, so that every step issues the same number of loads (the load waits count them).
+// current one is in use, so that every step issues the same number of loads (the load waits count them).  (PAIRED: two weight
+// tiles, one tap ahead, and a step with or without a pass of the next run behind them.)
 //
 // TAPS: taps between two barriers, 1 or 3 (0: no halo).  With small tiles a tap is a few MFMAs per wave between a barrier, the
 // fragment reads' latency and the issue of the next loads; three taps, a filter row, share these.  By rows run
@@ -334,10 +335,13 @@ __global__ __launch_bounds__(WM * WN == 1 ? 256 : 64 * WM * WN) void igemm_kerne
   // here, in front of everything the main loop loads (the hand-placed load waits count in order, and these are the oldest), so
   // that it is there when the last product is: workgroups of an earlier round are not enough to cover the 2 us these loads take from memory.
   // Step at batch 12 2395 -> 2375 us, 40 4161 -> 4134, 64 5852 -> 5809 (all against the 128x128 tile alone, which had given 4271 -> 4190 and at
-  // batch 256 19024 -> 18840).  Not the paired 128x128 tiles (three data gradients at 28x28, batch 256 250 -> 325 us) and tiles of more than eight
-  // rows a thread (float, 128 columns or 256 rows), whose registers would leave a compute unit a workgroup less.  These request the operands in front of
-  // the rows that use them, eight rows at a time: with all sixteen at once they needed more than 256 registers, one workgroup per compute unit (22
-  // float data gradients at batch 24, with sums / with a second branch 2895 / 3050 -> 2820 / 2975 us; 128 <- 128 3x3 / 2 at 56x56 120 -> 92).
+  // batch 256 19024 -> 18840).  The operands take 20 to 90 registers through the main loop; from three chunks on LDS allows no more workgroups per
+  // compute unit than are left (two of 128 rows, three of 64x64), with one or two chunks it is one or two workgroups less, and still the faster form
+  // (256 <- 64 at 56x56 with a second branch, batch 256 257 -> 235 us).  Not the paired 128x128 tiles (three data gradients at 28x28, batch 256
+  // 250 -> 325 us) and tiles of more than eight rows a thread (float, 128 columns or 256 rows), which it would leave a single workgroup.  These request the
+  // operands in front of the rows that use them, eight rows at a time: with all sixteen at once they needed more than 256 registers, a single
+  // workgroup too (22 float data gradients at batch 24, with sums / with a second branch 2895 / 3050 -> 2820 / 2975 us; 128 <- 128 3x3 / 2 at 56x56
+  // 120 -> 92).
   constexpr int PPR = BN * sizeof(T) / 16;  // 16-byte pieces per output row
   constexpr int RPP = NT / PPR;             // rows per pass
   constexpr int NPASS = BM / RPP;
@@ -1379,21 +1383,22 @@ struct TileShape {
 // The tile of a layer shape: M rows (output pixels; of one parity class for a stride-2 data gradient, `live` of
 // whose four classes have any taps), Ncols output channels, `chunks` 128-byte steps of the reduction.  The rule
 // is fitted to per-layer sweeps of all compiled shapes over ResNet-50's 23 convolution shapes at batch 40 and at
-// batch 256 (profiles/conv_tile_sweep_*.txt: summed over the shapes within 1 % of the best tiles, the data gradients at batch 256 3 %): the largest tile that still leaves about one and a half
+// batch 256 (profiles/conv_tile_sweep_*.txt: summed over the shapes within 1 % of the best tiles): the largest tile that still leaves about one and a half
 // workgroups per compute unit wins -- larger tiles load fewer operand bytes per flop (the main loop's bound) but with a smaller
 // grid the latencies of a workgroup's load -> LDS -> MFMA chain are exposed; a reduction of one chunk has nothing to reuse and
-// takes the smallest tile (64 -> 64 at 56x56, batch 256, forward / data gradient 28.3 / 28.4 us against 29.1 / 31.5 with 128x64 and 30.7 / 37.0 with
+// takes the smallest tile (64 -> 64 at 56x56, batch 256, forward / data gradient 28.5 / 28.4 us against 29.1 / 29.0 with 128x64 and 31.2 / 31.4 with
 // 128x128), except in bf16 with more than 64 columns and kCover tiles of 128x128 or more: that one reads A half as often.  By what the
 // output stage does, 64 channels at 56x56, operands from memory, us, 64x64 -> 128x128 (profiles/conv_one_chunk_tile_sweep.txt):
-//  - forward, with its sums (120 registers and 35 KB: four workgroups per compute unit): 64 -> 256 at batch 18 / 40 / 256 13.4 -> 9.9 / 24.9 ->
-//    19.3 / 147 -> 99.  Every size, also from warm caches;
-//  - data gradient without sums (150 registers: three): 11.8 -> 9.7 / 22.6 -> 17.4 / 137 -> 95 (warm 7.3 -> 8.0 / 13.3 -> 13.8 / 136 -> 94);
-//  - data gradient with sums (three; two with a second branch), evaluation (160 registers and 69 KB: two): only where the output is larger
-//    than half the last-level cache.  Data gradient with sums at batch 40 / 100 / 256 34.7 -> 35.2 / 79.9 -> 73.9 / 197 -> 176; with a second branch, whose tile
-//    lies in LDS in float, 128x128 always loses (40.5 -> 45.5 / 92.5 -> 101 / 225 -> 248), there the 128x64 tile of the same rows of sums (90 /
-//    217); evaluation with the residual at batch 16 / 40 / 64 / 100 / 256 10.2 -> 11.8 / 24.0 -> 27.0 / 38 -> 45 / 70 -> 64 / 168 -> 153.
-// In float the products take longer than the loads and the tile (68 KB in LDS) leaves two workgroups: 32 -> 256 at batch 64 54 -> 62, from warm
-// caches 38 -> 57.
+//  - forward, with its sums (118 registers and 35 KB: four workgroups per compute unit): 64 -> 256 at batch 18 / 40 / 256 11.6 -> 8.6 / 25.5 ->
+//    19.8 / 152 -> 98.  Every size, also from warm caches;
+//  - data gradient without sums (128 registers: four): 8.7 -> 7.2 / 22.3 -> 17.6 / 129 -> 91 (warm 7.3 -> 6.5 / 13.2 -> 12.6 / 135 -> 92);
+//  - data gradient with sums (225 registers: two), evaluation (158 registers and 69 KB: two): from an output of half the last-level cache on.  Data
+//    gradient with sums at batch 40 / 100 / 256 35.0 -> 32.2 / 80.6 -> 71.5 / 199 -> 175; with a second branch, whose tile lies in LDS in float, the
+//    128x64 tile of the same rows of sums is a little faster still (101 -> 93.4, 128x128 97.0 / 253 -> 232, 234); evaluation with the residual at batch
+//    16 / 40 / 64 / 100 / 256 9.8 -> 12.0 / 23.9 -> 27.6 / 37 -> 43 / 66 -> 64 / 169 -> 149.  (The line was drawn where data gradients with sums lost
+//    below it too, before their operands were requested early; now 128x64 and 128x128 are 6 to 8 % faster there as well, from batch 18 on.)
+// In float the products take longer than the loads and the tile (68 KB in LDS) leaves two workgroups: 32 -> 256 at batch 64 with sums 61 -> 67, from
+// warm caches 45 -> 61.
 enum class TileUse { kForward, kAffine, kGrad, kGradSums, kGradSumsAdd };  // what the output stage does (MODE 0, 2, 3, 1, 1)
 constexpr int64_t kOneChunkBytes = 128 << 20;
 static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool strided_dgrad, int live, TileUse use, int dtype) {
@@ -1416,12 +1421,14 @@ static TileShape igemm_tile(int64_t M, int Ncols, int chunks, bool strided_dgrad
 // eight-wave 256x128 tile, or two 128x128 ones per compute unit (PAIRED), once the former gives three quarters of the compute units a
 // workgroup, else 128x64 while that leaves one and a half workgroups per compute unit, else 64x64.
 constexpr int kHaloTallWidth = 63, kHaloPairWidth = 31;
-// Of the two tiles of 128 columns, whether the paired one.  A round of either takes as long (36 steps: 33 us, 18: 18 us); 256x128 tiles make
-// ceil(tiles / 256) of them, pairs tiles / 512 and for the rest one more, or 0.55 of one where it leaves every compute unit a single tile at most.  At equal
-// rounds the taller tile loads its weights half as often.  us, forward / data gradient, 256x128 -> pairs: 128 -> 128 at 28x28, batch 256 (4 rounds,
-// 3.55) 73.7 / 79.3 -> 63.5 / 66.8, 200 (3, 2.55) 56.0 / 60.3 -> 48.1 / 50.4, 128 (2, 2) 38.1 / 40.6 -> 36.5 / 39.0, 90 (2, 1.55) 36.1 / 38.5 -> 29.0 /
-// 30.9; 256 -> 256 at 14x14, 256 (2, 2) 65.8 / 68.5 -> 64.8 / 68.0, 200 (2, 1.55) 62.9 / 66.2 -> 51.7 / 54.1, 128 (1, 1) 34.0 / 35.8 -> 34.3 / 35.3; 512 ->
-// 512 at 7x7, 256 (1, 1) 57 / 61 -> 62 / 66.
+// Of the two tiles of 128 columns, whether the paired one: where it fills fewer rounds of the grid.  A round of either takes about as long (bf16: 36 steps
+// 33 us, 18 18 us; float nine times that); 256x128 tiles make ceil(tiles / 256) of them, pairs tiles / 512 and for the rest one more, or 0.55 of one where
+// it leaves every compute unit a single tile at most.  us, forward / data gradient, 256x128 -> pairs (profiles/conv_halo_pairs_sweep.txt), bf16: 128 -> 128
+// at 28x28, batch 256 (4 rounds, 3.55) 77.2 / 82.0 -> 65.2 / 67.2, 200 (3, 2.55) 55.7 / 58.2 -> 47.6 / 47.6, 90 (2, 1.55) 35.2 / 36.1 -> 28.4 / 28.8; 256 ->
+// 256 at 14x14, 200 (2, 1.55) 59.8 / 62.1 -> 49.2 / 50.6.  Float likewise: 128 -> 128, 256 611 / 589 -> 509 / 510, 90 291 / 290 -> 219 / 224; 256 -> 256,
+// 200 574 / 570 -> 433 / 438.  At equal rounds the two are within 5 % of each other: bf16 in one round the taller (512 -> 512 at 7x7, batch 256 56.0 /
+// 60.6 -> 58.4 / 60.1; 128 -> 128 with sums, 64 19.8 -> 20.6), in two and more, and float, the pairs (128 -> 128, 128 36.7 / 37.6 -> 35.3 / 35.9; float 296 / 295
+// -> 287 / 288); the taller one, which loads its weights half as often, stays.
 static bool igemm_halo_pairs(int64_t tall, int64_t pairs) {  // (tiles of 256 and of 128 rows)
   const int64_t rest = pairs % 512;
   return 20 * (pairs / 512) + (rest == 0 ? 0 : rest <= 256 ? 11 : 20) < 20 * ceil_div(tall, 256);

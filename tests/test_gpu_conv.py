@@ -511,8 +511,8 @@ def test_weight_gradient_of_nine_taps_at_once(rn, N, H, W, C, K):
             assert_close(dw[0][:, r, s], want.cpu().numpy(), 1e-5, f"dw tap {r},{s}", elementwise=None)
 
 
-# Forward on the 128x128 tile (from 384 of them on), whose two rings are of different depth: reductions of two chunks (no third buffer of A),
-# three, four and more, ragged channels on both sides, a strided gather with one chunk and with several per tap, a last row tile of one row.
+# Forward on the 128x128 tile (from 384 of them on), whose two rings are of different depth (float: three buffers of A, two of B; bf16: two and
+# one): reductions of two chunks (no third buffer of A), three, four and more, ragged channels on both sides, a strided gather with one chunk and with several per tap, a last row tile of one row.
 DEEP_RING = [(8, 56, 56, 128, 256, 1, 1), (8, 56, 56, 136, 200, 1, 1), (8, 56, 56, 200, 256, 1, 1), (1, 157, 157, 328, 136, 1, 1), (8, 112, 112, 40, 200, 3, 2),
              (8, 111, 112, 72, 136, 3, 2), (2, 159, 157, 64, 128, 2, 1)]
 
